@@ -63,29 +63,6 @@ __device__ inline V8 lds_read_tr_pair(const void* p0, const void* p1) {
   return __builtin_bit_cast(V8, r);
 }
 
-// Exchange between the wave halves: v_permlane32_swap swaps the upper 32 lanes of its first
-// operand with the lower 32 lanes of its second; fed the same value twice it leaves, in every
-// lane, the values of lanes l % 32 (first operand) and l % 32 + 32 (second operand). Written as
-// inline asm with both registers read-write: the builtin's second result was dropped by the
-// compiler when both inputs were the same value. The s_nop covers the VALU-write -> permlane
-// read hazard, which the compiler cannot see inside an asm block.
-__device__ inline void half_pair(float x, float& lo, float& hi) {
-  float a = x, b = x;
-  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-  lo = a;
-  hi = b;
-}
-__device__ inline float half_swap_max(float x) {
-  float lo, hi;
-  half_pair(x, lo, hi);
-  return fmaxf(lo, hi);
-}
-__device__ inline float half_swap_sum(float x) {
-  float lo, hi;
-  half_pair(x, lo, hi);
-  return lo + hi;
-}
-
 // Swizzle of the 32-byte segments of a tile that is read with transposing accesses
 // (ds_read_b64_tr_b16): the LDS serves 32 lanes of such a read per cycle, which address the rows
 // r..r+3 (r a multiple of 4) at two adjacent 32-byte segments, 4 lanes x 8 bytes per row and

@@ -2,195 +2,429 @@
 // path, for float tensors and (the mirrored form only) for bf16 tensors converted on load.
 //
 // Same steps as the bf16 kernel (Sec. 2.2.2 tiling; Sec. 3.2 sampling and fusion per Q block,
-// Sec. 3.3; Eq. 2), in plain float FMAs on the vector ALUs. Four adjacent lanes share one query
-// row: each takes every fourth (sampled) channel of the score product, the partial sums are
-// added across the four lanes, and each lane accumulates a quarter of the output channels.
-// K/V tiles of 32 rows go through LDS; the fused tile K_f is built in LDS once per (Q block,
-// K tile) and shared by the block's rows; the softmax is online per tile (Sec. 2.2.2).
-// Built for accuracy checks on small problems.
+// Sec. 3.3; Eq. 2) on the float matrix instruction v_mfma_f32_32x32x2_f32 (float operands, float
+// products and sums: the precision of the vector ALUs at twice their rate without packed forms).
+// Bound: that instruction, 64 cycles for 4096 FLOP. Both products are taken transposed, so that
+// one lane owns one query row:
+//   S^T[kv][q] = Kx Qx^T     A = keys from LDS, B = queries in registers
+//   O^T[ch][q] = V^T P^T     A = V straight from global memory, B = P in registers: register i of
+//                            a score accumulator holds the keys 8*(i/4) + i%4 (+ 4 in the upper
+//                            half of the wave), which is the contraction index of step i.
 //
-// side = 1 is the mirrored form of Sec. 3.1 (last sentence of the Eq. 2 paragraph, Fig. 4 right
-// side): the grouping belongs to the K block (Bc rows, table [B][Hkv][Tk][d] from the LSH
-// stage run on K), one K column per group is sampled and the group's Q columns are summed.
-// Every K block then needs its own permutation and its own fused queries -- the reloading
-// Sec. 3.3 gives as the reason for sampling Q instead.
+// Split: a workgroup owns 32 query rows and its NW waves deal the 32-key tiles out among
+// themselves, each with a softmax state of its own; the states meet in LDS once at the end. No wave
+// waits for another before that, and a problem of few rows still fills the chip: sharing tiles
+// among waves of different rows instead would leave N = 256 with 8 working waves.
+// Measured (B1 H8 N2048 d64 n_groups 32): 71 us, 92 TFLOP/s of the 157 the instruction can reach
+// (float multiply-adds on the vector ALUs, a thread quad per row: 1430 us); mirrored 78 us (1439);
+// B1 H1 N256: 9 us (162).
+//
+// Score product, by MODE:
+//   kQueryFused  the wave writes its K tile into LDS in sorted channel order, a group's G channels
+//                are then adjacent and are summed as they are read (Sec. 3.2 fusion); contraction
+//                over n_groups. Built for groups of 2 and 4 channels.
+//   kQueryFull   the same product as Q~ K^T, Q~ = Q with every channel replaced by its group's
+//                sampled channel (a sum over groups of sums over members): contraction over d, for
+//                every other group size; exact attention is groups of one channel.
+//   kKeyFused,   the mirrored form of Sec. 3.1 (last sentence of the Eq. 2 paragraph, Fig. 4 right
+//   kKeyFull     side): the grouping belongs to the K block (Bc rows, table [B][Hkv][Tk][d] from
+//                the LSH stage run on K), one K column per group is sampled and the group's Q columns are
+//                summed: every K block needs its own fused queries (the reloading Sec. 3.3 gives as
+//                the reason for sampling Q instead), gathered from the Q rows in LDS. kKeyFull
+//                replaces every key channel by its group's sampled one instead.
+#include <type_traits>
+
 #include "da_common.h"
 
 namespace da {
 
-constexpr int kF32Tile = 32;  // key rows per LDS tile of this kernel
-constexpr int kF32Lanes = 4;  // lanes per query row
+namespace {
 
-template <typename E, int D, int BR>
-__global__ __launch_bounds__(BR * kF32Lanes) void attn_f32_kernel(
-    const E* __restrict__ q, const E* __restrict__ k, const E* __restrict__ v,
-    E* __restrict__ o, const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Tq,
-    int n_groups, int causal, float scale, int distr, int side, int Bc, float* __restrict__ lse) {
-  constexpr int T = BR * kF32Lanes;
-  constexpr int QS = D / kF32Lanes;            // most channels of the score product one lane takes
-  constexpr int CS = D / kF32Lanes;            // output channels per lane
-  __shared__ float k_lds[kF32Tile][D + 1];     // raw key tile
-  __shared__ float kf_lds[kF32Tile][D + 1];    // fused key tile (distr only)
-  __shared__ __attribute__((aligned(16))) float v_lds[kF32Tile][D];
-  __shared__ uint8_t perm_lds[D];
+constexpr int kTile = 32;   // query rows per workgroup, key rows per tile
 
-  const int tid = threadIdx.x;
-  const int row = tid / kF32Lanes;             // query row of the block
-  const int part = tid % kF32Lanes;
-  const int t = blockIdx.x % Tq;
-  const int bh = blockIdx.x / Tq;
-  const int b = bh / H, h = bh % H;
-  const int hk = h / (H / Hkv);
-  const int r0 = t * BR;
-  const int rows = min(BR, N - r0);
-  const int kred = distr ? n_groups : D;
-  const int G = D / kred;
+enum Mode { kQueryFull, kQueryFused, kKeyFull, kKeyFused };
 
-  const E* qh = q + ((size_t)bh * N + r0) * D;
-  const E* kh = k + ((size_t)(b * Hkv + hk) * Nk) * D;
-  const E* vh = v + ((size_t)(b * Hkv + hk) * Nk) * D;
+// Four consecutive channels of a row, as loaded and as floats.
+template <typename E>
+struct Quad;
+template <>
+struct Quad<float> {
+  typedef u32x4 raw;
+  static __device__ raw load(__amdgpu_buffer_rsrc_t rsrc, int voff, int soff) {
+    return __builtin_bit_cast(raw, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, soff, 0));
+  }
+  static __device__ f32x4 values(raw x) { return __builtin_bit_cast(f32x4, x); }
+};
+template <>
+struct Quad<bf16> {
+  typedef u32x2 raw;
+  static __device__ raw load(__amdgpu_buffer_rsrc_t rsrc, int voff, int soff) {
+    return __builtin_bit_cast(raw, __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, soff, 0));
+  }
+  static __device__ f32x4 values(raw x) {
+    const u32x4 y = {x[0] << 16, x[0] & 0xffff0000u, x[1] << 16, x[1] & 0xffff0000u};
+    return __builtin_bit_cast(f32x4, y);
+  }
+};
+// Two consecutive channels.
+template <typename E>
+struct Pair;
+template <>
+struct Pair<float> {
+  typedef u32x2 raw;
+  static __device__ raw load(__amdgpu_buffer_rsrc_t rsrc, int voff, int soff) {
+    return __builtin_bit_cast(raw, __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, soff, 0));
+  }
+  static __device__ float value(raw x, int i) { return __builtin_bit_cast(f32x2, x)[i]; }
+};
+template <>
+struct Pair<bf16> {
+  typedef uint32_t raw;
+  static __device__ raw load(__amdgpu_buffer_rsrc_t rsrc, int voff, int soff) {
+    return __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, soff, 0);
+  }
+  static __device__ float value(raw x, int i) { return __builtin_bit_cast(float, i ? x & 0xffff0000u : x << 16); }
+};
+
+// LDS written by some lanes of a wave is read by others: nothing moves across (no instruction).
+__device__ inline void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+template <typename E, int D, int G, int MODE, int NW>
+__global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
+    const E* __restrict__ q, const E* __restrict__ k, const E* __restrict__ v, E* __restrict__ o,
+    const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Br, int Tq, int Tw, int n_groups,
+    int causal, float scale_log2e, int Bc, float* __restrict__ lse) {
+  constexpr bool kMirrored = MODE == kKeyFull || MODE == kKeyFused;
+  constexpr bool kFused = MODE == kQueryFused || MODE == kKeyFused;
+  constexpr int T = NW * 64;
+  constexpr int KRED = kFused ? D / G : D;       // contraction length of the score product
+  constexpr int HS = KRED / 2;                   // steps: each takes one slot from either half of the wave
+  constexpr int NB = D / 32;                     // 32-channel blocks of the output; lane m owns channels NB*m ..
+  constexpr int RS = D + 4;                      // LDS row length in floats: 16-byte aligned rows whose starts
+                                                 // are 4 banks apart (16 lanes cover all 64 banks)
+  constexpr int KU = kTile * D / 4 / 64;         // 4-channel pieces of a K tile per lane
+  __shared__ __attribute__((aligned(16))) float q_lds[kTile * RS];
+  __shared__ __attribute__((aligned(16))) float k_lds[NW][kTile * RS];   // K tile of each wave, at the end its output
+  __shared__ float stat_lds[NW][2][kTile];
+  __shared__ __attribute__((aligned(16))) uint8_t map_lds[kMirrored ? NW : 1][D];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lq = lane & 31, hh = lane >> 5;
+  // causal: the row tiles with the most keys first, over all heads
+  const int n_bh = gridDim.x / Tw;
+  const int t = causal ? Tw - 1 - (int)blockIdx.x / n_bh : (int)blockIdx.x / n_bh;
+  const int bh = blockIdx.x % n_bh;
+  const int b = bh / H, h = bh % H, hk = h / (H / Hkv);
+  const int r0 = t * kTile;
   const int shift = Nk - N;   // causal: key n is visible to query i iff n <= i + shift
-  const bool mirrored = distr && side == 1;
-  const int Tk = (Nk + Bc - 1) / Bc;
 
-  if (distr && !mirrored)
-    // D is a power of two: an out-of-range entry of a caller's table cannot index past a row
-    for (int i = tid; i < D; i += T) perm_lds[i] = perm[(size_t)blockIdx.x * D + i] & (D - 1);
-  __syncthreads();
-  const bool active = row < rows;
-  const int i_abs = r0 + row;
-  // sampling: column j of Q_r is the first channel of group j in sorted order; this lane keeps
-  // columns part, part + 4, ...
-  float qreg[QS];
+  const unsigned kv_bytes = (unsigned)Nk * D * sizeof(E);
+  const __amdgpu_buffer_rsrc_t k_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(k + (size_t)(b * Hkv + hk) * Nk * D), 0, kv_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t v_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(v + (size_t)(b * Hkv + hk) * Nk * D), 0, kv_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t q_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(q + (size_t)bh * N * D), 0, (unsigned)N * D * sizeof(E), 0x00020000);
+
+  const int n_end = causal ? min(Nk, r0 + kTile + shift) : Nk;
+  const int n_tiles = (n_end + kTile - 1) / kTile;
+  const int TB = kMirrored ? Bc / kTile : 1;     // tiles dealt out together: one K block of the mirrored form
+  auto next_tile = [&](int tile) { return (TB > 1 && (tile + 1) % TB != 0 && tile + 1 < n_tiles) ? tile + 1 : (tile / TB + NW) * TB; };
+
+  // K tile: piece u of this lane is row (u*64 + lane) / (D/4), channels 4*((u*64 + lane) % (D/4)) ..
+  // (64 lanes cover whole rows); rows past the end read as zeros (range check of the descriptor).
+  typename Quad<E>::raw kreg[KU];
+  uint8_t map_reg[D / 64];
+  auto load_k = [&](int tile) {
 #pragma unroll
-  for (int i = 0; i < QS; ++i) {
-    const int j = part + kF32Lanes * i;
-    qreg[i] = (active && j < kred && !mirrored) ? (float)qh[(size_t)row * D + (distr ? perm_lds[j * G] : j)] : 0.0f;
+    for (int u = 0; u < KU; ++u) kreg[u] = Quad<E>::load(k_rsrc, (u * 64 + lane) * 4 * (int)sizeof(E), tile * (kTile * D * (int)sizeof(E)));
+    if constexpr (kMirrored) {
+      const size_t row = (size_t)(b * Hkv + hk) * ((Nk + Bc - 1) / Bc) + tile / TB;
+#pragma unroll
+      for (int u = 0; u < D / 64; ++u) map_reg[u] = perm[row * D + u * 64 + lane];
+    }
+  };
+  int tile = w * TB;
+  if (tile < n_tiles) load_k(tile);
+
+  // Q rows of the workgroup into LDS; the Q block's permutation beside them.
+  {
+    constexpr int QU = kTile * D / 4 / T;
+    typename Quad<E>::raw x[QU];
+#pragma unroll
+    for (int u = 0; u < QU; ++u) x[u] = Quad<E>::load(q_rsrc, (u * T + tid) * 4 * (int)sizeof(E), r0 * (D * (int)sizeof(E)));
+#pragma unroll
+    for (int u = 0; u < QU; ++u) *(f32x4*)&q_lds[(u * T + tid) / (D / 4) * RS + (u * T + tid) % (D / 4) * 4] = Quad<E>::values(x[u]);
+  }
+  int kdst[4];          // kQueryFused: where the lane's four channels go in a row sorted by group
+  float qop[HS];
+  if constexpr (!kMirrored) {
+    // map: position of a channel in sorted order (kQueryFused) / sampled channel of its group (kQueryFull)
+    if (perm) {
+      // D is a power of two: an out-of-range entry of a caller's table cannot index past a row
+      const uint8_t* pr = perm + ((size_t)bh * Tq + r0 / Br) * D;
+      const int group = D / n_groups;
+      for (int i = tid; i < D; i += T)
+        map_lds[0][pr[i] & (D - 1)] = kFused ? (uint8_t)i : (uint8_t)(pr[i / group * group] & (D - 1));
+    } else {
+      for (int i = tid; i < D; i += T) map_lds[0][i] = (uint8_t)i;
+    }
+    __syncthreads();
+    if constexpr (kFused) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) kdst[e] = map_lds[0][(lane * 4 + e) % D] & (D - 1);
+      // sampling: the group's first channel in sorted order
+      const uint8_t* pr = perm + ((size_t)bh * Tq + r0 / Br) * D;
+#pragma unroll
+      for (int s = 0; s < HS; ++s) qop[s] = q_lds[lq * RS + (pr[(hh * HS + s) * G] & (D - 1))];
+    } else {
+#pragma unroll
+      for (int s = 0; s < HS; ++s) qop[s] = q_lds[lq * RS + (map_lds[0][hh * HS + s] & (D - 1))];
+    }
+  } else {
+    __syncthreads();
+    if constexpr (MODE == kKeyFull) {
+#pragma unroll
+      for (int s = 0; s < HS; ++s) qop[s] = q_lds[lq * RS + hh * HS + s];
+    }
   }
 
-  float acc[CS];
+  float* kt = k_lds[w];
+  int koff[kMirrored ? HS : 1];   // channel of the K row that contraction slot s takes (mirrored form)
+  f32x16 oacc[NB];
 #pragma unroll
-  for (int c = 0; c < CS; ++c) acc[c] = 0.0f;
-  float m_run = -INFINITY, l_run = 0.0f;
-  const int n_end = causal ? min(Nk, r0 + rows + shift) : Nk;
+  for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) oacc[mb][i] = 0.0f;
+  float m_run = -1e30f, l_run = 0.0f;   // exp2 domain; l over this lane's half of the keys
+  const int q_abs = r0 + lq;
+  const int lim = causal ? min(q_abs + shift, Nk - 1) : Nk - 1;   // last key this row sees
 
-  for (int n0 = 0; n0 < n_end; n0 += kF32Tile) {
-    const int tn = min(kF32Tile, n_end - n0);
-    __syncthreads();
-    if (mirrored && n0 % Bc == 0) {
-      // a new K block: its permutation, and the queries fused by it (members in sorted order)
-      const size_t pbase = (((size_t)(b * Hkv + hk)) * Tk + n0 / Bc) * D;
-      for (int i = tid; i < D; i += T) perm_lds[i] = perm[pbase + i] & (D - 1);
-      __syncthreads();
+  while (tile < n_tiles) {
+    // ---- stage the K tile (and, mirrored, the K block's grouping) -------------------------------
+    wave_order();   // the reads of the previous tile come first
 #pragma unroll
-      for (int i = 0; i < QS; ++i) {
-        const int j = part + kF32Lanes * i;
-        float s = 0.0f;
-        if (active && j < kred)
-          for (int g = 0; g < G; ++g) s += (float)qh[(size_t)row * D + perm_lds[j * G + g]];
-        qreg[i] = s;
+    for (int u = 0; u < KU; ++u) {
+      const f32x4 x = Quad<E>::values(kreg[u]);
+      const int row = (u * 64 + lane) / (D / 4), c = (u * 64 + lane) % (D / 4) * 4;
+      if constexpr (MODE == kQueryFused) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) kt[row * RS + kdst[e]] = x[e];
+      } else {
+        *(f32x4*)&kt[row * RS + c] = x;
       }
     }
-    for (int i = tid; i < tn * D; i += T) {
-      int n = i / D, c = i % D;
-      k_lds[n][c] = (float)kh[(size_t)(n0 + n) * D + c];
-      v_lds[n][c] = (float)vh[(size_t)(n0 + n) * D + c];
-    }
-    __syncthreads();
-    if (mirrored) {  // sampling on the K side: the group's first channel in sorted order
-      for (int i = tid; i < tn * kred; i += T) {
-        int n = i / kred, j = i % kred;
-        kf_lds[n][j] = k_lds[n][perm_lds[j * G]];
-      }
-      __syncthreads();
-    } else if (distr) {  // fusion: sum the group's key channels, members in sorted order
-      for (int i = tid; i < tn * kred; i += T) {
-        int n = i / kred, j = i % kred;
-        float s = 0.0f;
-        for (int g = 0; g < G; ++g) s += k_lds[n][perm_lds[j * G + g]];
-        kf_lds[n][j] = s;
-      }
-      __syncthreads();
-    }
-    const float(*kx)[D + 1] = distr ? kf_lds : k_lds;
-    // scores of the tile: partial dot products, summed over the row's four lanes
-    float sc[kF32Tile];
-    float m_tile = -INFINITY;
+    const bool new_block = kMirrored && tile % TB == 0;
+    if constexpr (kMirrored) {
+      if (new_block) {
+        if constexpr (kFused) {
 #pragma unroll
-    for (int n = 0; n < kF32Tile; ++n) {
-      float s = 0.0f;
-      if (n < tn) {
+          for (int u = 0; u < D / 64; ++u) map_lds[w][u * 64 + lane] = map_reg[u] & (D - 1);
+        } else {
+          // a channel's group's first channel: lane i of the sorted order names its own
+          const int group = D / n_groups;
+          uint8_t* tmp = (uint8_t*)&stat_lds[w][0][0];   // (the softmax states use it after the loop only)
 #pragma unroll
-        for (int i = 0; i < QS; ++i) {
-          const int j = part + kF32Lanes * i;
-          if (j < kred) s = __builtin_fmaf(qreg[i], kx[n][j], s);
+          for (int u = 0; u < D / 64; ++u) tmp[u * 64 + lane] = map_reg[u] & (D - 1);
+          wave_order();
+#pragma unroll
+          for (int u = 0; u < D / 64; ++u) {
+            const int i = u * 64 + lane;
+            map_lds[w][tmp[i]] = tmp[i / group * group];
+          }
         }
       }
-      s += __shfl_xor(s, 1);
-      s += __shfl_xor(s, 2);
-      s *= scale;
-      if (n >= tn || (causal && n0 + n > i_abs + shift)) s = -INFINITY;
-      sc[n] = s;
-      m_tile = fmaxf(m_tile, s);
     }
-    // online softmax step for the tile (Sec. 2.2.2); a row whose keys of this tile are all
-    // masked keeps its state (its first tile always holds key 0, so m_run is finite by then)
-    const float m_new = fmaxf(m_run, m_tile);
-    const float alpha = (m_new == -INFINITY) ? 1.0f : expf(m_run - m_new);   // exp(-inf) = 0 on the first tile
-    float psum = 0.0f;
+    wave_order();
+    // V of this tile, then K of the next one: in flight under the score product and P.V
+    constexpr int VR = NB / 2;   // raw pairs per row of V and lane
+    typename Pair<E>::raw vreg[16][VR];
+    auto load_v = [&](int i) {
 #pragma unroll
-    for (int n = 0; n < kF32Tile; ++n) {
-      sc[n] = (sc[n] == -INFINITY) ? 0.0f : expf(sc[n] - m_new);
-      psum += sc[n];
+      for (int j = 0; j < VR; ++j)
+        vreg[i][j] = Pair<E>::load(v_rsrc, ((8 * (i >> 2) + 4 * hh + (i & 3)) * D + lq * NB + 2 * j) * (int)sizeof(E), tile * (kTile * D * (int)sizeof(E)));
+    };
+#pragma unroll
+    for (int i = 0; i < 16; ++i) load_v(i);
+    // (unconditional, so that the waits for V can count the loads of K behind it: the last tile again
+    // when there is no next one)
+    const int following = next_tile(tile);
+    load_k(min(following, n_tiles - 1));
+
+    if constexpr (kMirrored) {
+      if (new_block) {
+        // entries of this half of the wave: positions hh*D/2 .. of the sorted order (kKeyFused), the
+        // sampled channels of its channels (kKeyFull)
+#pragma unroll
+        for (int c16 = 0; c16 < D / 2; c16 += 16) {
+          const u32x4 e4 = *(const u32x4*)&map_lds[w][hh * (D / 2) + c16];
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int ch = (e4[e >> 2] >> (8 * (e & 3))) & (D - 1);
+            if constexpr (MODE == kKeyFull) {
+              koff[c16 + e] = ch;
+            } else {
+              const float x = q_lds[lq * RS + ch];   // fusion of Q, members in sorted order
+              if ((c16 + e) % G == 0) {
+                koff[(c16 + e) / G] = ch;
+                qop[(c16 + e) / G] = x;
+              } else {
+                qop[(c16 + e) / G] += x;
+              }
+            }
+          }
+        }
+      }
     }
-    l_run = l_run * alpha + psum;
-    m_run = m_new;
+
+    // ---- scores -----------------------------------------------------------------------------------
+    f32x16 sacc;
 #pragma unroll
-    for (int c = 0; c < CS; ++c) acc[c] *= alpha;
+    for (int i = 0; i < 16; ++i) sacc[i] = 0.0f;
+    if constexpr (kMirrored) {
 #pragma unroll
-    for (int n = 0; n < kF32Tile; ++n) {
-      if (n < tn) {
-        const float p = sc[n];
+      for (int s = 0; s < HS; ++s) sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kt[lq * RS + koff[s]], qop[s], sacc, 0, 0, 0);
+    } else {
 #pragma unroll
-        for (int c = 0; c < CS; ++c) acc[c] = __builtin_fmaf(p, v_lds[n][part * CS + c], acc[c]);
+      for (int c = 0; c < D / 2; c += 4) {
+        const f32x4 x = *(const f32x4*)&kt[lq * RS + hh * (D / 2) + c];
+        if constexpr (MODE == kQueryFull) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], qop[c + e], sacc, 0, 0, 0);
+        } else if constexpr (G == 2) {
+          sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[0] + x[1], qop[c / 2], sacc, 0, 0, 0);
+          sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[2] + x[3], qop[c / 2 + 1], sacc, 0, 0, 0);
+        } else {
+          sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(((x[0] + x[1]) + x[2]) + x[3], qop[c / 4], sacc, 0, 0, 0);
+        }
+      }
+    }
+    const int n0 = tile * kTile;
+    if (n0 + kTile > Nk || (causal && n0 + kTile - 1 > r0 + shift)) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (n0 + 8 * (i >> 2) + 4 * hh + (i & 3) > lim) sacc[i] = -INFINITY;
+    }
+    // ---- online softmax step (Sec. 2.2.2) -------------------------------------------------------
+    float mt = sacc[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mt = fmaxf(mt, sacc[i]);
+    const float m_new = fmaxf(m_run, half_swap_max(mt) * scale_log2e);
+    if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      l_run *= alpha;
+#pragma unroll
+      for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[mb][i] *= alpha;
+      m_run = m_new;
+    }
+    float ps[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      ps[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], scale_log2e, -m_run));
+      l_run += ps[i];
+    }
+    // ---- O^T += V^T P^T -----------------------------------------------------------------------------
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+      for (int mb = 0; mb < NB; ++mb)
+        oacc[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(Pair<E>::value(vreg[i][mb >> 1], mb & 1), ps[i], oacc[mb], 0, 0, 0);
+    tile = following;
+  }
+
+  // ---- the waves' states meet: rows of (reference, sum), then the outputs -------------------------
+  const float l_tot = half_swap_sum(l_run);
+  wave_order();
+  if (hh == 0) {
+    stat_lds[w][0][lq] = m_run;
+    stat_lds[w][1][lq] = l_tot;
+  }
+  __syncthreads();
+  float m_all = stat_lds[0][0][lq];
+#pragma unroll
+  for (int j = 1; j < NW; ++j) m_all = fmaxf(m_all, stat_lds[j][0][lq]);
+  float l_all = 0.0f;
+#pragma unroll
+  for (int j = 0; j < NW; ++j) l_all += stat_lds[j][1][lq] * __builtin_amdgcn_exp2f(stat_lds[j][0][lq] - m_all);
+  const float weight = __builtin_amdgcn_exp2f(m_run - m_all) / l_all;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int m = 8 * (i >> 2) + 4 * hh + (i & 3);
+    if constexpr (NB == 2) {
+      const float x[2] = {oacc[0][i] * weight, oacc[1][i] * weight};
+      __builtin_memcpy(__builtin_assume_aligned(&kt[lq * RS + m * 2], 8), x, 8);
+    } else {
+      const f32x4 x = {oacc[0][i] * weight, oacc[1][i] * weight, oacc[2][i] * weight, oacc[NB - 1][i] * weight};
+      *(f32x4*)&kt[lq * RS + m * 4] = x;
+    }
+  }
+  // row statistics for a backward pass: ln(sum of exp(score)) = ln 2 * (reference + log2(sum))
+  if (lse && w == 0 && hh == 0 && q_abs < N) lse[(size_t)bh * N + q_abs] = 0.6931471805599453f * (m_all + __builtin_log2f(l_all));
+  __syncthreads();
+  for (int i = tid; i < kTile * D / 4; i += T) {
+    const int row = i / (D / 4), c = i % (D / 4) * 4;
+    if (r0 + row < N) {
+      f32x4 x = *(const f32x4*)&k_lds[0][row * RS + c];
+#pragma unroll
+      for (int j = 1; j < NW; ++j) x += *(const f32x4*)&k_lds[j][row * RS + c];
+      E* dst = o + ((size_t)bh * N + r0 + row) * D + c;
+      if constexpr (std::is_same<E, float>::value) {
+        *(f32x4*)dst = x;
+      } else {
+        const bf16x4 y = {(bf16)x[0], (bf16)x[1], (bf16)x[2], (bf16)x[3]};
+        *(bf16x4*)dst = y;
       }
     }
   }
-  if (active) {
-    if (lse && part == 0) lse[(size_t)bh * N + i_abs] = m_run + logf(l_run);   // row statistics for a backward pass
-    float inv = 1.0f / l_run;
-    E* orow = o + ((size_t)bh * N + i_abs) * D + part * CS;
-#pragma unroll
-    for (int c = 0; c < CS; ++c) orow[c] = (E)(acc[c] * inv);
-  }
 }
 
-template <typename E>
-static hipError_t launch_f32_typed(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
-                                   const Problem& pb, int distr, hipStream_t stream) {
-  const int Tq = (pb.N + pb.Br - 1) / pb.Br;
-  const long long units = (long long)pb.B * pb.H * Tq;
-  dim3 grid((unsigned)units);
-#define DA_F32_LAUNCH(DD, BB)                                                                          \
-  hipLaunchKernelGGL((attn_f32_kernel<E, DD, BB>), grid, dim3(BB * kF32Lanes), 0, stream, (const E*)q,  \
-                     (const E*)k, (const E*)v, (E*)o, perm, pb.H, pb.Hkv, pb.N, pb.Nk, Tq, pb.n_groups, \
-                     pb.causal, pb.scale, distr, pb.side, pb.Bc, pb.lse)
-  if (pb.d == 64 && pb.Br == 64) DA_F32_LAUNCH(64, 64);
-  else if (pb.d == 64 && pb.Br == 128) DA_F32_LAUNCH(64, 128);
-  else if (pb.d == 128 && pb.Br == 64) DA_F32_LAUNCH(128, 64);
-  else if (pb.d == 128 && pb.Br == 128) DA_F32_LAUNCH(128, 128);
-  else if (pb.d == 64 && pb.Br == 256) DA_F32_LAUNCH(64, 256);
-  else if (pb.d == 128 && pb.Br == 256) DA_F32_LAUNCH(128, 256);
-  else return hipErrorInvalidValue;
-#undef DA_F32_LAUNCH
+template <typename E, int D, int G, int MODE, int NW>
+hipError_t launch_one(const void* q, const void* k, const void* v, void* o, const uint8_t* perm, const Problem& pb,
+                      int n_groups, hipStream_t stream) {
+  const int Tq = (pb.N + pb.Br - 1) / pb.Br, Tw = (pb.N + kTile - 1) / kTile;
+  hipLaunchKernelGGL((attn_f32_kernel<E, D, G, MODE, NW>), dim3((unsigned)((long long)pb.B * pb.H * Tw)), dim3(NW * 64), 0, stream,
+                     (const E*)q, (const E*)k, (const E*)v, (E*)o, perm, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, Tw, n_groups,
+                     pb.causal, pb.scale * 1.4426950408889634f, pb.Bc, pb.lse);
   return hipGetLastError();
 }
+
+template <typename E, int D>
+hipError_t launch_typed(const void* q, const void* k, const void* v, void* o, const uint8_t* perm, const Problem& pb,
+                        int distr, hipStream_t stream) {
+  if ((long long)pb.B * pb.H * ((pb.N + kTile - 1) / kTile) > 0x7fffffffLL) return hipErrorInvalidValue;
+  const int G = distr ? D / pb.n_groups : 1;
+  if (distr && pb.side == 1) {
+    if (G == 2) return launch_one<E, D, 2, kKeyFused, 4>(q, k, v, o, perm, pb, pb.n_groups, stream);
+    if (G == 4) return launch_one<E, D, 4, kKeyFused, 4>(q, k, v, o, perm, pb, pb.n_groups, stream);
+    return launch_one<E, D, 1, kKeyFull, 4>(q, k, v, o, perm, pb, pb.n_groups, stream);
+  }
+  if constexpr (std::is_same<E, float>::value) {
+    if (!distr) return launch_one<E, D, 1, kQueryFull, 4>(q, k, v, o, nullptr, pb, D, stream);
+    if (G == 2) return launch_one<E, D, 2, kQueryFused, 4>(q, k, v, o, perm, pb, pb.n_groups, stream);
+    if (G == 4) return launch_one<E, D, 4, kQueryFused, 4>(q, k, v, o, perm, pb, pb.n_groups, stream);
+    return launch_one<E, D, 1, kQueryFull, 4>(q, k, v, o, perm, pb, pb.n_groups, stream);
+  }
+  return hipErrorInvalidValue;   // bf16 tensors take this path for the mirrored form only
+}
+
+}  // namespace
 
 // dtype 0: bf16 tensors (converted on load, rounded on store), 1: float tensors; float arithmetic either way
 hipError_t launch_attn_f32(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                            const Problem& pb, int dtype, int distr, hipStream_t stream) {
-  return dtype == 0 ? launch_f32_typed<bf16>(q, k, v, o, perm, pb, distr, stream)
-                    : launch_f32_typed<float>(q, k, v, o, perm, pb, distr, stream);
+  if (pb.d == 64)
+    return dtype == 0 ? launch_typed<bf16, 64>(q, k, v, o, perm, pb, distr, stream)
+                      : launch_typed<float, 64>(q, k, v, o, perm, pb, distr, stream);
+  if (pb.d == 128)
+    return dtype == 0 ? launch_typed<bf16, 128>(q, k, v, o, perm, pb, distr, stream)
+                      : launch_typed<float, 128>(q, k, v, o, perm, pb, distr, stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace da

@@ -11,6 +11,7 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
@@ -40,6 +41,29 @@ __host__ __device__ inline uint32_t lsh_hash_of_code(uint32_t code, int gray_mod
   uint32_t h = code;
   h ^= h >> 1; h ^= h >> 2; h ^= h >> 4; h ^= h >> 8; h ^= h >> 16;
   return h;
+}
+
+// Exchange between the wave halves: v_permlane32_swap swaps the upper 32 lanes of its first
+// operand with the lower 32 lanes of its second; fed the same value twice it leaves, in every
+// lane, the values of lanes l % 32 (first operand) and l % 32 + 32 (second operand). Written as
+// inline asm with both registers read-write: the builtin's second result was dropped by the
+// compiler when both inputs were the same value. The s_nop covers the VALU-write -> permlane
+// read hazard, which the compiler cannot see inside an asm block.
+__device__ inline void half_pair(float x, float& lo, float& hi) {
+  float a = x, b = x;
+  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+  lo = a;
+  hi = b;
+}
+__device__ inline float half_swap_max(float x) {
+  float lo, hi;
+  half_pair(x, lo, hi);
+  return fmaxf(lo, hi);
+}
+__device__ inline float half_swap_sum(float x) {
+  float lo, hi;
+  half_pair(x, lo, hi);
+  return lo + hi;
 }
 
 // Behind the K^T copy the key pre-pass leaves the projection matrix of the LSH stage (Sec. 3.2),
