@@ -34,63 +34,13 @@
 //                replaces every key channel by its group's sampled one instead.
 #include <type_traits>
 
-#include "da_common.h"
+#include "f32_tiles.h"
 
 namespace da {
 
 namespace {
 
-constexpr int kTile = 32;   // query rows per workgroup, key rows per tile
-
 enum Mode { kQueryFull, kQueryFused, kKeyFull, kKeyFused };
-
-// Four consecutive channels of a row, as loaded and as floats.
-template <typename E>
-struct Quad;
-template <>
-struct Quad<float> {
-  typedef u32x4 raw;
-  static __device__ raw load(__amdgpu_buffer_rsrc_t rsrc, int voff, int soff) {
-    return __builtin_bit_cast(raw, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, soff, 0));
-  }
-  static __device__ f32x4 values(raw x) { return __builtin_bit_cast(f32x4, x); }
-};
-template <>
-struct Quad<bf16> {
-  typedef u32x2 raw;
-  static __device__ raw load(__amdgpu_buffer_rsrc_t rsrc, int voff, int soff) {
-    return __builtin_bit_cast(raw, __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, soff, 0));
-  }
-  static __device__ f32x4 values(raw x) {
-    const u32x4 y = {x[0] << 16, x[0] & 0xffff0000u, x[1] << 16, x[1] & 0xffff0000u};
-    return __builtin_bit_cast(f32x4, y);
-  }
-};
-// Two consecutive channels.
-template <typename E>
-struct Pair;
-template <>
-struct Pair<float> {
-  typedef u32x2 raw;
-  static __device__ raw load(__amdgpu_buffer_rsrc_t rsrc, int voff, int soff) {
-    return __builtin_bit_cast(raw, __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, soff, 0));
-  }
-  static __device__ float value(raw x, int i) { return __builtin_bit_cast(f32x2, x)[i]; }
-};
-template <>
-struct Pair<bf16> {
-  typedef uint32_t raw;
-  static __device__ raw load(__amdgpu_buffer_rsrc_t rsrc, int voff, int soff) {
-    return __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, soff, 0);
-  }
-  static __device__ float value(raw x, int i) { return __builtin_bit_cast(float, i ? x & 0xffff0000u : x << 16); }
-};
-
-// LDS written by some lanes of a wave is read by others: nothing moves across (no instruction).
-__device__ inline void wave_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 
 template <typename E, int D, int G, int MODE, int NW>
 __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
@@ -123,12 +73,9 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
   const int shift = Nk - N;   // causal: key n is visible to query i iff n <= i + shift
 
   const unsigned kv_bytes = (unsigned)Nk * D * sizeof(E);
-  const __amdgpu_buffer_rsrc_t k_rsrc =
-      __builtin_amdgcn_make_buffer_rsrc((void*)(k + (size_t)(b * Hkv + hk) * Nk * D), 0, kv_bytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t v_rsrc =
-      __builtin_amdgcn_make_buffer_rsrc((void*)(v + (size_t)(b * Hkv + hk) * Nk * D), 0, kv_bytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t q_rsrc =
-      __builtin_amdgcn_make_buffer_rsrc((void*)(q + (size_t)bh * N * D), 0, (unsigned)N * D * sizeof(E), 0x00020000);
+  const __amdgpu_buffer_rsrc_t k_rsrc = head_rsrc(k + (size_t)(b * Hkv + hk) * Nk * D, kv_bytes);
+  const __amdgpu_buffer_rsrc_t v_rsrc = head_rsrc(v + (size_t)(b * Hkv + hk) * Nk * D, kv_bytes);
+  const __amdgpu_buffer_rsrc_t q_rsrc = head_rsrc(q + (size_t)bh * N * D, (unsigned)N * D * sizeof(E));
 
   const int n_end = causal ? min(Nk, r0 + kTile + shift) : Nk;
   const int n_tiles = (n_end + kTile - 1) / kTile;
@@ -197,9 +144,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
   int koff[kMirrored ? HS : 1];   // channel of the K row that contraction slot s takes (mirrored form)
   f32x16 oacc[NB];
 #pragma unroll
-  for (int mb = 0; mb < NB; ++mb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) oacc[mb][i] = 0.0f;
+  for (int mb = 0; mb < NB; ++mb) zero(oacc[mb]);
   float m_run = -1e30f, l_run = 0.0f;   // exp2 domain; l over this lane's half of the keys
   const int q_abs = r0 + lq;
   const int lim = causal ? min(q_abs + shift, Nk - 1) : Nk - 1;   // last key this row sees
@@ -246,7 +191,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     auto load_v = [&](int i) {
 #pragma unroll
       for (int j = 0; j < VR; ++j)
-        vreg[i][j] = Pair<E>::load(v_rsrc, ((8 * (i >> 2) + 4 * hh + (i & 3)) * D + lq * NB + 2 * j) * (int)sizeof(E), tile * (kTile * D * (int)sizeof(E)));
+        vreg[i][j] = Pair<E>::load(v_rsrc, (acc_row(i, hh) * D + lq * NB + 2 * j) * (int)sizeof(E), tile * (kTile * D * (int)sizeof(E)));
     };
 #pragma unroll
     for (int i = 0; i < 16; ++i) load_v(i);
@@ -283,23 +228,22 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
 
     // ---- scores -----------------------------------------------------------------------------------
     f32x16 sacc;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) sacc[i] = 0.0f;
+    zero(sacc);
     if constexpr (kMirrored) {
 #pragma unroll
-      for (int s = 0; s < HS; ++s) sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kt[lq * RS + koff[s]], qop[s], sacc, 0, 0, 0);
+      for (int s = 0; s < HS; ++s) sacc = mfma(kt[lq * RS + koff[s]], qop[s], sacc);
     } else {
 #pragma unroll
       for (int c = 0; c < D / 2; c += 4) {
         const f32x4 x = *(const f32x4*)&kt[lq * RS + hh * (D / 2) + c];
         if constexpr (MODE == kQueryFull) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], qop[c + e], sacc, 0, 0, 0);
+          for (int e = 0; e < 4; ++e) sacc = mfma(x[e], qop[c + e], sacc);
         } else if constexpr (G == 2) {
-          sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[0] + x[1], qop[c / 2], sacc, 0, 0, 0);
-          sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[2] + x[3], qop[c / 2 + 1], sacc, 0, 0, 0);
+          sacc = mfma(x[0] + x[1], qop[c / 2], sacc);
+          sacc = mfma(x[2] + x[3], qop[c / 2 + 1], sacc);
         } else {
-          sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(((x[0] + x[1]) + x[2]) + x[3], qop[c / 4], sacc, 0, 0, 0);
+          sacc = mfma(((x[0] + x[1]) + x[2]) + x[3], qop[c / 4], sacc);
         }
       }
     }
@@ -307,7 +251,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     if (n0 + kTile > Nk || (causal && n0 + kTile - 1 > r0 + shift)) {
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        if (n0 + 8 * (i >> 2) + 4 * hh + (i & 3) > lim) sacc[i] = -INFINITY;
+        if (n0 + acc_row(i, hh) > lim) sacc[i] = -INFINITY;
     }
     // ---- online softmax step (Sec. 2.2.2) -------------------------------------------------------
     float mt = sacc[0];
@@ -334,7 +278,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     for (int i = 0; i < 16; ++i)
 #pragma unroll
       for (int mb = 0; mb < NB; ++mb)
-        oacc[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(Pair<E>::value(vreg[i][mb >> 1], mb & 1), ps[i], oacc[mb], 0, 0, 0);
+        oacc[mb] = mfma(Pair<E>::value(vreg[i][mb >> 1], mb & 1), ps[i], oacc[mb]);
     tile = following;
   }
 
@@ -355,7 +299,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
   const float weight = __builtin_amdgcn_exp2f(m_run - m_all) / l_all;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    const int m = 8 * (i >> 2) + 4 * hh + (i & 3);
+    const int m = acc_row(i, hh);
     if constexpr (NB == 2) {
       const float x[2] = {oacc[0][i] * weight, oacc[1][i] * weight};
       __builtin_memcpy(__builtin_assume_aligned(&kt[lq * RS + m * 2], 8), x, 8);

@@ -1,6 +1,7 @@
-// Backward of the attention forward (exact and DistrAttention) for gfx950 in float arithmetic on
-// the vector ALUs: the reference-precision path, for float tensors (bf16 tensors take the
-// matrix-core kernels of attn_bf16_bwd.hip); two kernels, no atomics (results do not depend on the run).
+// Backward of the attention forward (exact and DistrAttention) for gfx950 in float arithmetic: the
+// reference-precision path, for float tensors (bf16 tensors take the matrix-core kernels of
+// attn_bf16_bwd.hip). Products on v_mfma_f32_32x32x2_f32 (float operands and sums), no atomics
+// (results do not depend on the run), no scratch.
 //
 // The paper trains through the approximation (Sec. 4.3, 4.4) and gives no gradient. Computed
 // here: the derivative of the forward with every Q block's grouping held fixed (the permutation
@@ -12,311 +13,496 @@
 // (Eq. 2 with Q_r the sampled and K_f the fused columns of Sec. 3.2; one grouping per Q block,
 // Sec. 3.3). Exact attention is the case of one channel per group.
 //
-// Kernel 1 (dQ): one workgroup per Q block, four lanes per query row as in the forward; K/V tiles
-// of 32 rows through LDS, the fused tile K_f rebuilt per tile.
-// Kernel 2 (dK, dV): one workgroup per (kv head, 32 keys), four lanes per key; it walks every
-// query head of the kv head and every Q block that sees the keys, rebuilds that block's fused
-// keys in registers, and un-fuses the block's dK_f into a dK tile in LDS through the block's
-// permutation (the mirror image of the forward's fusion).
-#include "da_common.h"
+//   bwd_delta_kernel  D_i of every row, left at the head of dq, which the last kernel overwrites
+//   bwd_dkv_kernel    one workgroup per (kv head, 32 keys), lane = key, K and V rows resident as
+//                     operands; its waves deal the 32-row query tiles of all query heads of the kv head
+//                     out among themselves. Contracts over d with Q~ = Q whose channels are
+//                     replaced by their group's sampled one (S^ = Q~ K^T, dK = scale dS^T Q~: every
+//                     member of a group receives its group's column), gathered from global memory.
+//   bwd_dq_kernel     one workgroup per 32 query rows, lane = query row, waves deal the key tiles
+//                     out. Groups of 2 and 4 channels: the K tile lies in LDS in sorted channel order,
+//                     members adjacent and summed as they are read, S^ and dQ_r contract over
+//                     n_groups; other group sizes take Q~ and sum dQ~ over the members at the end.
+// The waves' partial sums meet in LDS once, at the end, in a fixed order: as in the forward no wave waits
+// for another before that, and few rows still give every SIMD work. Bound: the matrix
+// instruction (64 cycles for 4096 FLOP), 7 products over d per (query, key) pair, 6 with groups of two.
+// Measured (B1 H8 N2048 d64 n_groups 32): delta 4, dK/dV 180, dQ 84 us, 96 and 102 TFLOP/s of the 157 the
+// instruction can reach (float multiply-adds on the vector ALUs: dK/dV 2740, dQ 1980 us). dK/dV needs
+// more than half a SIMD's registers (resident K, V and both sums), so one wave per SIMD has to hide its own waits.
+#include "f32_tiles.h"
 
 namespace da {
 
-constexpr int kBwdTile = 32;   // key rows per tile (both kernels)
-constexpr int kBwdLanes = 4;   // lanes per query row (kernel 1) / per key (kernel 2)
-constexpr int kBwdChunk = 16;  // query rows staged at a time by kernel 2
+namespace {
 
-__device__ inline float quad_sum(float x) {
-  x += __shfl_xor(x, 1);
-  x += __shfl_xor(x, 2);
-  return x;
+constexpr int kWaves = 4;
+constexpr int kThreads = kWaves * 64;
+constexpr float kLog2e = 1.4426950408889634f;
+
+typedef Quad<float> Q4;
+
+// A row of 32-row tile registers: piece u of a lane is row (u*64 + lane) / (D/4) of the tile, channels
+// 4*((u*64 + lane) % (D/4)) ..; rows past the end of the head read as zeros.
+template <int D>
+struct Tile {
+  static constexpr int KU = kTile * D / 4 / 64;
+  static constexpr int RS = D + 4;   // LDS row length: 16-byte aligned rows whose starts are 4 banks apart
+  static constexpr int BYTES = kTile * D * 4;
+  u32x4 x[KU];
+  __device__ void load(__amdgpu_buffer_rsrc_t rsrc, int tile, int lane) {
+#pragma unroll
+    for (int u = 0; u < KU; ++u) x[u] = Q4::load(rsrc, (u * 64 + lane) * 16, tile * BYTES);
+  }
+  // every channel replaced by `from` (the lane's four channels, the same in all its pieces)
+  __device__ void gather(__amdgpu_buffer_rsrc_t rsrc, int tile, int lane, uint32_t from) {
+#pragma unroll
+    for (int u = 0; u < KU; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        x[u][e] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (u * 64 + lane) / (D / 4) * (D * 4) + ((from >> (8 * e)) & (D - 1)) * 4, tile * BYTES, 0);
+  }
+  __device__ void store(float* lds, int lane) const {
+#pragma unroll
+    for (int u = 0; u < KU; ++u) *(u32x4*)&lds[(u * 64 + lane) / (D / 4) * RS + (u * 64 + lane) % (D / 4) * 4] = x[u];
+  }
+  __device__ void scatter(float* lds, int lane, const int (&to)[4]) const {
+#pragma unroll
+    for (int u = 0; u < KU; ++u) {
+      const f32x4 y = Q4::values(x[u]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lds[(u * 64 + lane) / (D / 4) * RS + to[e]] = y[e];
+    }
+  }
+};
+
+// acc += (tile rows as lanes) x (operand b): contraction over the channels hh*D/2 + s of step s
+template <int D>
+__device__ inline void row_product(const float* row, int hh, const float (&b)[D / 2], f32x16& acc) {
+#pragma unroll
+  for (int c = 0; c < D / 2; c += 4) {
+    const f32x4 x = *(const f32x4*)&row[hh * (D / 2) + c];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = mfma(x[e], b[c + e], acc);
+  }
 }
-
-template <typename E, int D, int BR>
-__global__ __launch_bounds__(BR * kBwdLanes) void attn_f32_bwd_dq_kernel(
-    const E* __restrict__ q, const E* __restrict__ k, const E* __restrict__ v,
-    const E* __restrict__ o, const E* __restrict__ dout, const float* __restrict__ lse,
-    E* __restrict__ dq, const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Tq,
-    int n_groups, int causal, float scale, int distr) {
-  constexpr int T = BR * kBwdLanes;
-  constexpr int QS = D / kBwdLanes;   // most columns of the score product one lane takes
-  constexpr int CS = D / kBwdLanes;   // channels of dO, O and V per lane
-  __shared__ float k_lds[kBwdTile][D + 1];
-  __shared__ float kf_lds[kBwdTile][D + 1];
-  __shared__ __attribute__((aligned(16))) float v_lds[kBwdTile][D];
-  __shared__ uint8_t perm_lds[D];
-  __shared__ uint8_t sampled_lds[D];   // 1 where the channel is its group's first in sorted order
-
-  const int tid = threadIdx.x;
-  const int row = tid / kBwdLanes, part = tid % kBwdLanes;
-  const int t = blockIdx.x % Tq;
-  const int bh = blockIdx.x / Tq;
-  const int b = bh / H, h = bh % H;
-  const int hk = h / (H / Hkv);
-  const int r0 = t * BR;
-  const int rows = min(BR, N - r0);
-  const int kred = distr ? n_groups : D;
-  const int G = D / kred;
-  const int shift = Nk - N;   // causal: key n is visible to query i iff n <= i + shift
-
-  const E* kh = k + ((size_t)(b * Hkv + hk) * Nk) * D;
-  const E* vh = v + ((size_t)(b * Hkv + hk) * Nk) * D;
-
-  for (int i = tid; i < D; i += T) {
-    perm_lds[i] = distr ? (perm[(size_t)blockIdx.x * D + i] & (D - 1)) : (uint8_t)i;
-    sampled_lds[i] = 0;
-  }
-  __syncthreads();
-  for (int j = tid; j < kred; j += T) sampled_lds[perm_lds[j * G]] = 1;
-  __syncthreads();
-
-  const bool active = row < rows;
-  const int i_abs = r0 + row;
-  const size_t row_off = ((size_t)bh * N + (active ? i_abs : r0)) * D;
-  float qreg[QS], dqr[QS], doreg[CS];
+// acc[mb] += (tile transposed) x (accumulator p as operand): lane m owns channels NB*m .. NB*m + NB-1
+template <int D>
+__device__ inline void column_product(const float* tile, int lq, int hh, const f32x16& p, f32x16 (&acc)[D / 32]) {
+  constexpr int NB = D / 32, RS = Tile<D>::RS;
 #pragma unroll
-  for (int i = 0; i < QS; ++i) {
-    const int j = part + kBwdLanes * i;
-    qreg[i] = (active && j < kred) ? (float)q[row_off + perm_lds[j * G]] : 0.0f;
-    dqr[i] = 0.0f;
-  }
-  float dsum = 0.0f;
-#pragma unroll
-  for (int c = 0; c < CS; ++c) {
-    doreg[c] = active ? (float)dout[row_off + part * CS + c] : 0.0f;
-    dsum = __builtin_fmaf(doreg[c], active ? (float)o[row_off + part * CS + c] : 0.0f, dsum);
-  }
-  const float Drow = quad_sum(dsum);
-  const float lse_row = active ? lse[(size_t)bh * N + i_abs] : 0.0f;
-  const int n_end = causal ? min(Nk, r0 + rows + shift) : Nk;
-
-  for (int n0 = 0; n0 < n_end; n0 += kBwdTile) {
-    const int tn = min(kBwdTile, n_end - n0);
-    __syncthreads();
-    for (int i = tid; i < tn * D; i += T) {
-      int n = i / D, c = i % D;
-      k_lds[n][c] = (float)kh[(size_t)(n0 + n) * D + c];
-      v_lds[n][c] = (float)vh[(size_t)(n0 + n) * D + c];
+  for (int i = 0; i < 16; ++i) {
+    const float* src = &tile[acc_row(i, hh) * RS + lq * NB];
+    float x[NB];
+    if constexpr (NB == 2) {
+      const f32x2 y = *(const f32x2*)src;
+      x[0] = y[0], x[1] = y[1];
+    } else {
+      const f32x4 y = *(const f32x4*)src;
+      x[0] = y[0], x[1] = y[1], x[2] = y[2], x[3] = y[3];
     }
-    __syncthreads();
-    for (int i = tid; i < tn * kred; i += T) {   // fusion, members in sorted order
-      int n = i / kred, j = i % kred;
-      float s = 0.0f;
-      for (int g = 0; g < G; ++g) s += k_lds[n][perm_lds[j * G + g]];
-      kf_lds[n][j] = s;
-    }
-    __syncthreads();
-    for (int n = 0; n < tn; ++n) {
-      float s = 0.0f, dp = 0.0f;
 #pragma unroll
-      for (int i = 0; i < QS; ++i) {
-        const int j = part + kBwdLanes * i;
-        if (j < kred) s = __builtin_fmaf(qreg[i], kf_lds[n][j], s);
-      }
-#pragma unroll
-      for (int c = 0; c < CS; ++c) dp = __builtin_fmaf(doreg[c], v_lds[n][part * CS + c], dp);
-      s = quad_sum(s) * scale;
-      dp = quad_sum(dp);
-      const bool visible = active && !(causal && n0 + n > i_abs + shift);
-      const float p = visible ? expf(s - lse_row) : 0.0f;
-      const float ds = p * (dp - Drow);
-#pragma unroll
-      for (int i = 0; i < QS; ++i) {
-        const int j = part + kBwdLanes * i;
-        if (j < kred) dqr[i] = __builtin_fmaf(ds, kf_lds[n][j], dqr[i]);
-      }
-    }
+    for (int mb = 0; mb < NB; ++mb) acc[mb] = mfma(x[mb], p[i], acc[mb]);
   }
-  if (active) {
-    E* dqrow = dq + row_off;
-    // the row's four lanes write disjoint columns: zeros where the channel was not sampled,
-    // the gradient of column j of Q_r at the channel it was sampled from
-    for (int c = part; c < D; c += kBwdLanes)
-      if (!sampled_lds[c]) dqrow[c] = (E)0.0f;
+}
+// the accumulators of column_product into LDS rows (row = lane's own)
+template <int D>
+__device__ inline void store_columns(float* row, int hh, const f32x16 (&acc)[D / 32]) {
 #pragma unroll
-    for (int i = 0; i < QS; ++i) {
-      const int j = part + kBwdLanes * i;
-      if (j < kred) dqrow[perm_lds[j * G]] = (E)(scale * dqr[i]);
-    }
+  for (int i = 0; i < 16; ++i) {
+    const int m = acc_row(i, hh);
+    if constexpr (D == 64) *(f32x2*)&row[m * 2] = f32x2{acc[0][i], acc[1][i]};
+    else *(f32x4*)&row[m * 4] = f32x4{acc[0][i], acc[1][i], acc[D / 32 - 2][i], acc[D / 32 - 1][i]};
   }
 }
 
-template <typename E, int D>
-__global__ __launch_bounds__(kBwdTile * kBwdLanes) void attn_f32_bwd_dkv_kernel(
-    const E* __restrict__ q, const E* __restrict__ k, const E* __restrict__ v,
-    const E* __restrict__ o, const E* __restrict__ dout, const float* __restrict__ lse,
-    E* __restrict__ dk, E* __restrict__ dv, const uint8_t* __restrict__ perm, int H, int Hkv,
-    int N, int Nk, int Br, int Tq, int Tk, int n_groups, int causal, float scale, int distr) {
-  constexpr int T = kBwdTile * kBwdLanes;
-  constexpr int QS = D / kBwdLanes;
-  constexpr int CS = D / kBwdLanes;
-  __shared__ float k_lds[kBwdTile][D + 1];     // the keys of this workgroup
-  __shared__ float dk_lds[kBwdTile][D + 1];    // their gradient, channel order
-  __shared__ float qr_lds[kBwdChunk][D + 1];   // sampled query columns of the staged rows
-  __shared__ float do_lds[kBwdChunk][D + 1];   // dO of the staged rows
-  __shared__ float lse_lds[kBwdChunk];
-  __shared__ float drow_lds[kBwdChunk];        // D_i = sum_c dO_ic O_ic
-  __shared__ uint8_t perm_lds[D];
+// ------------------------------------------------------------------------------------------------
+// D_i of 256 / (D/4) rows per workgroup.
+template <int D>
+__global__ __launch_bounds__(kThreads) void bwd_delta_kernel(const float* __restrict__ o, const float* __restrict__ dout,
+                                                             float* __restrict__ delta, size_t rows) {
+  const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;   // 4-channel piece
+  float s = 0.0f;
+  if (i < rows * (D / 4)) {
+    const f32x4 a = *(const f32x4*)(o + i * 4), b = *(const f32x4*)(dout + i * 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s = __builtin_fmaf(a[e], b[e], s);
+  }
+#pragma unroll
+  for (int m = 1; m < D / 4; m <<= 1) s += __shfl_xor(s, m);
+  if (i % (D / 4) == 0 && i < rows * (D / 4)) delta[i / (D / 4)] = s;
+}
 
-  const int tid = threadIdx.x;
-  const int key = tid / kBwdLanes, part = tid % kBwdLanes;
-  const int tk = blockIdx.x % Tk;
-  const int bk = blockIdx.x / Tk;          // b * Hkv + hk
-  const int b = bk / Hkv, hk = bk % Hkv;
-  const int rep = H / Hkv;
-  const int n0 = tk * kBwdTile;
-  const int tn = min(kBwdTile, Nk - n0);
-  const int n_abs = n0 + key;
-  const bool valid = key < tn;
-  const int kred = distr ? n_groups : D;
-  const int G = D / kred;
+// ------------------------------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(kThreads, 1) void bwd_dkv_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ dout,
+    const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dk, float* __restrict__ dv,
+    const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Br, int Tq, int n_groups, int causal, float scale) {
+  constexpr int NB = D / 32, RS = Tile<D>::RS;
+  __shared__ __attribute__((aligned(16))) float q_lds[kWaves][kTile * RS];    // Q~ tile of each wave, at the end its dK
+  __shared__ __attribute__((aligned(16))) float do_lds[kWaves][kTile * RS];   // dO tile, at the end dV
+  __shared__ __attribute__((aligned(16))) float stat_lds[kWaves][2][kTile];   // lse * log2(e), D_i
+  __shared__ __attribute__((aligned(16))) uint8_t map_lds[kWaves][2][D];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lq = lane & 31, hh = lane >> 5;
+  // causal: the keys that most queries see come first; the tile index is the slow one, so that a
+  // kv head stays on one XCD when their number is a multiple of 8
+  const int n_bk = gridDim.x / ((Nk + kTile - 1) / kTile);
+  const int t = blockIdx.x / n_bk, bk = blockIdx.x % n_bk;
+  const int b = bk / Hkv, hk = bk % Hkv, rep = H / Hkv;
+  const int n0 = t * kTile, key = n0 + lq;
+  const int shift = Nk - N;   // causal: query i sees key n iff n <= i + shift
+  const float sl2e = scale * kLog2e;
+  const int group = D / n_groups;
+
+  const int first = causal ? max(0, n0 - shift) / kTile : 0;   // first tile with a row that sees key n0
+  const int tiles = (N + kTile - 1) / kTile - first;           // per query head
+  const int n_it = tiles * rep;
+  auto head_of = [&](int it) { return (size_t)b * H + hk * rep + it / tiles; };
+  auto tile_of = [&](int it) { return first + it % tiles; };
+
+  // The sampled channels of the lane's four channels in the block of iteration `it` (0, 1, 2, 3 .. for
+  // exact attention), from the bytes of its table row.
+  uint8_t map_reg[D / 64];
+  auto load_map = [&](int it) {
+    const uint8_t* pr = perm + (head_of(it) * Tq + tile_of(it) * kTile / Br) * D;
+#pragma unroll
+    for (int u = 0; u < D / 64; ++u) map_reg[u] = pr[u * 64 + lane];
+  };
+  auto sampled = [&]() -> uint32_t {
+    uint8_t* order = map_lds[w][0];
+    uint8_t* from = map_lds[w][1];
+    wave_order();
+#pragma unroll
+    for (int u = 0; u < D / 64; ++u) order[u * 64 + lane] = map_reg[u] & (D - 1);
+    wave_order();
+#pragma unroll
+    for (int u = 0; u < D / 64; ++u) from[order[u * 64 + lane]] = order[(u * 64 + lane) / group * group];
+    wave_order();
+    return *(const uint32_t*)&from[lane % (D / 4) * 4];
+  };
+  Tile<D> qt, dt;
+  float lse_reg, delta_reg;
+  auto load_tile = [&](int it) {
+    const size_t bh = head_of(it);
+    const int i0 = tile_of(it);
+    const __amdgpu_buffer_rsrc_t q_rsrc = head_rsrc(q + bh * N * D, (unsigned)N * D * 4);
+    if (perm) qt.gather(q_rsrc, i0, lane, sampled());
+    else qt.load(q_rsrc, i0, lane);
+    dt.load(head_rsrc(dout + bh * N * D, (unsigned)N * D * 4), i0, lane);
+    const int row = min(i0 * kTile + lq, N - 1);
+    lse_reg = lse[bh * N + row];
+    delta_reg = delta[bh * N + row];
+  };
+  int it = w;
+  if (it < n_it) {
+    if (perm) load_map(it);
+    load_tile(it);
+    if (perm && it + kWaves < n_it) load_map(it + kWaves);
+  }
+
+  float kop[D / 2], vop[D / 2];
+  {
+    const __amdgpu_buffer_rsrc_t k_rsrc = head_rsrc(k + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
+    const __amdgpu_buffer_rsrc_t v_rsrc = head_rsrc(v + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
+#pragma unroll
+    for (int c = 0; c < D / 2; c += 4) {
+      const f32x4 x = Q4::values(Q4::load(k_rsrc, (lq * D + hh * (D / 2) + c) * 4, n0 * (D * 4)));
+      const f32x4 y = Q4::values(Q4::load(v_rsrc, (lq * D + hh * (D / 2) + c) * 4, n0 * (D * 4)));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) kop[c + e] = x[e], vop[c + e] = y[e];
+    }
+  }
+  f32x16 dkacc[NB], dvacc[NB];
+#pragma unroll
+  for (int mb = 0; mb < NB; ++mb) {
+    zero(dkacc[mb]);
+    zero(dvacc[mb]);
+  }
+
+  for (; it < n_it; it += kWaves) {
+    const int i0 = tile_of(it) * kTile;
+    wave_order();   // the reads of the previous tile come first
+    qt.store(q_lds[w], lane);
+    dt.store(do_lds[w], lane);
+    stat_lds[w][hh][lq] = hh ? delta_reg : lse_reg * kLog2e;
+    if (it + kWaves < n_it) {
+      load_tile(it + kWaves);
+      if (perm && it + 2 * kWaves < n_it) load_map(it + 2 * kWaves);
+    }
+    wave_order();
+    f32x16 s, dp;
+    zero(s);
+    zero(dp);
+    row_product<D>(&q_lds[w][lq * RS], hh, kop, s);
+    row_product<D>(&do_lds[w][lq * RS], hh, vop, dp);
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const f32x4 l2 = *(const f32x4*)&stat_lds[w][0][8 * i4 + 4 * hh], dl = *(const f32x4*)&stat_lds[w][1][8 * i4 + 4 * hh];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = 4 * i4 + e;
+        s[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], sl2e, -l2[e]));
+        dp[i] = dp[i] - dl[e];
+      }
+    }
+    if (i0 + kTile > N || (causal && i0 + shift < n0 + kTile - 1)) {   // rows past N; the causal diagonal
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int row = i0 + acc_row(i, hh);
+        if (row >= N || (causal && key > row + shift)) s[i] = 0.0f;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) dp[i] *= s[i];
+    column_product<D>(do_lds[w], lq, hh, s, dvacc);
+    column_product<D>(q_lds[w], lq, hh, dp, dkacc);
+  }
+
+  wave_order();
+  store_columns<D>(&q_lds[w][lq * RS], hh, dkacc);
+  store_columns<D>(&do_lds[w][lq * RS], hh, dvacc);
+  __syncthreads();
+  for (int i = tid; i < kTile * D / 4; i += kThreads) {
+    const int row = i / (D / 4), c = i % (D / 4) * 4;
+    if (n0 + row < Nk) {
+      f32x4 x = *(const f32x4*)&q_lds[0][row * RS + c], y = *(const f32x4*)&do_lds[0][row * RS + c];
+#pragma unroll
+      for (int j = 1; j < kWaves; ++j) {
+        x += *(const f32x4*)&q_lds[j][row * RS + c];
+        y += *(const f32x4*)&do_lds[j][row * RS + c];
+      }
+      const size_t dst = ((size_t)bk * Nk + n0 + row) * D + c;
+      *(f32x4*)(dk + dst) = x * scale;
+      *(f32x4*)(dv + dst) = y;
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// G: channels per group where the score and dQ_r products contract over the groups (2, 4); 1: over the
+// channels, with Q~.
+template <int D, int G>
+__global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dq_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ o,
+    const float* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ dq, const uint8_t* __restrict__ perm,
+    int H, int Hkv, int N, int Nk, int Br, int Tq, int n_groups, int causal, float scale) {
+  constexpr int NB = D / 32, RS = Tile<D>::RS;
+  constexpr int KRED = D / G, HS = KRED / 2;
+  constexpr int NG = G == 1 ? NB : (KRED + 31) / 32;   // 32-row blocks of the dQ_r accumulator
+  __shared__ __attribute__((aligned(16))) float k_lds[kWaves][kTile * RS];   // at the end the wave's dQ_r
+  __shared__ __attribute__((aligned(16))) float v_lds[kWaves][kTile * RS];
+  __shared__ uint8_t order_lds[D];   // sorted order of the block's channels
+  __shared__ uint8_t map_lds[D];     // G > 1: a channel's position in it; G = 1: its group's sampled channel
+  __shared__ uint8_t pos_lds[D];     // (G = 1) a channel's position in the sorted order
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lq = lane & 31, hh = lane >> 5;
+  const int Tw = (N + kTile - 1) / kTile;
+  const int n_bh = gridDim.x / Tw;
+  const int t = causal ? Tw - 1 - (int)blockIdx.x / n_bh : (int)blockIdx.x / n_bh;   // longest first
+  const int bh = blockIdx.x % n_bh;
+  const int b = bh / H, hk = bh % H / (H / Hkv);
+  const int r0 = t * kTile, q_abs = r0 + lq;
   const int shift = Nk - N;
+  const float sl2e = scale * kLog2e;
+  const int group = D / n_groups;
 
-  const E* kh = k + ((size_t)bk * Nk + n0) * D;
-  const E* vh = v + ((size_t)bk * Nk + n0) * D;
-  for (int i = tid; i < kBwdTile * D; i += T) {
-    int n = i / D, c = i % D;
-    k_lds[n][c] = n < tn ? (float)kh[(size_t)n * D + c] : 0.0f;
-    dk_lds[n][c] = 0.0f;
-  }
-  float vreg[CS], dvacc[CS];
-#pragma unroll
-  for (int c = 0; c < CS; ++c) {
-    vreg[c] = valid ? (float)vh[(size_t)key * D + part * CS + c] : 0.0f;
-    dvacc[c] = 0.0f;
-  }
-  // causal: the first Q block with a row that sees key n0 (row i sees it iff i >= n0 - shift)
-  const int t_first = causal ? max(0, n0 - shift) / Br : 0;
+  const size_t head = (size_t)bh * N * D;
+  const __amdgpu_buffer_rsrc_t k_rsrc = head_rsrc(k + (size_t)(b * Hkv + hk) * Nk * D, (unsigned)Nk * D * 4);
+  const __amdgpu_buffer_rsrc_t v_rsrc = head_rsrc(v + (size_t)(b * Hkv + hk) * Nk * D, (unsigned)Nk * D * 4);
+  const int n_end = causal ? min(Nk, r0 + kTile + shift) : Nk;
+  const int n_tiles = (n_end + kTile - 1) / kTile;
+  const int lim = causal ? min(q_abs + shift, Nk - 1) : Nk - 1;   // last key this row sees
 
-  for (int h = hk * rep; h < (hk + 1) * rep; ++h) {
-    const size_t bh = (size_t)b * H + h;
-    for (int t = t_first; t < Tq; ++t) {
-      const int r0 = t * Br;
-      const int rows = min(Br, N - r0);
-      __syncthreads();   // previous block's reads of perm_lds and the staging buffers are done
-      for (int i = tid; i < D; i += T)
-        perm_lds[i] = distr ? (perm[(bh * Tq + t) * D + i] & (D - 1)) : (uint8_t)i;
-      __syncthreads();
-      float kf[QS], dkf[QS];
+  Tile<D> kt, vt;
+  if (w < n_tiles) {
+    kt.load(k_rsrc, w, lane);
+    vt.load(v_rsrc, w, lane);
+  }
+  // Q, dO and O rows pass through LDS (one tile per wave 0, 1, 2)
+  {
+    const float* src = w == 0 ? q : w == 1 ? dout : o;
+    Tile<D> x;
+    if (w < 3) {
+      x.load(head_rsrc(src + head, (unsigned)N * D * 4), t, lane);
+      x.store(w == 2 ? v_lds[0] : k_lds[w], lane);
+    }
+  }
+  if (perm) {
+    // D is a power of two: an out-of-range entry of a caller's table cannot index past a row
+    const uint8_t* pr = perm + ((size_t)bh * Tq + r0 / Br) * D;
+    for (int i = tid; i < D; i += kThreads) {
+      order_lds[i] = pr[i] & (D - 1);
+      pos_lds[pr[i] & (D - 1)] = (uint8_t)i;
+      map_lds[pr[i] & (D - 1)] = G > 1 ? (uint8_t)i : (uint8_t)(pr[i / group * group] & (D - 1));
+    }
+  } else {
+    for (int i = tid; i < D; i += kThreads) order_lds[i] = map_lds[i] = (uint8_t)i;
+  }
+  __syncthreads();
+  float qop[HS], doop[D / 2], dl = 0.0f;
+  int kdst[4];
 #pragma unroll
-      for (int i = 0; i < QS; ++i) {
-        const int j = part + kBwdLanes * i;
-        float s = 0.0f;
-        if (j < kred)
-          for (int g = 0; g < G; ++g) s += k_lds[key][perm_lds[j * G + g]];
-        kf[i] = s;
-        dkf[i] = 0.0f;
-      }
-      for (int c0 = 0; c0 < rows; c0 += kBwdChunk) {
-        const int cr = min(kBwdChunk, rows - c0);
-        __syncthreads();
-        // stage the chunk: sampled query columns, dO, row statistics; eight threads per row
-        // take the row's dO.O product
-        const size_t base = (bh * N + r0 + c0) * D;
-        for (int i = tid; i < cr * D; i += T) {
-          int r = i / D, c = i % D;
-          do_lds[r][c] = (float)dout[base + (size_t)r * D + c];
-          if (c < kred) qr_lds[r][c] = (float)q[base + (size_t)r * D + perm_lds[c * G]];
-        }
-        {
-          constexpr int TPR = T / kBwdChunk;   // threads per staged row
-          const int r = tid / TPR, sub = tid % TPR;
-          float acc = 0.0f;
-          if (r < cr)
-            for (int c = sub; c < D; c += TPR)
-              acc = __builtin_fmaf((float)dout[base + (size_t)r * D + c], (float)o[base + (size_t)r * D + c], acc);
+  for (int s = 0; s < HS; ++s)
+    qop[s] = k_lds[0][lq * RS + (G > 1 ? order_lds[(hh * HS + s) * G] : (map_lds[hh * HS + s] & (D - 1)))];
 #pragma unroll
-          for (int m = 1; m < TPR; m <<= 1) acc += __shfl_xor(acc, m);
-          if (r < cr && sub == 0) {
-            drow_lds[r] = acc;
-            lse_lds[r] = lse[bh * N + r0 + c0 + r];
-          }
-        }
-        __syncthreads();
-        for (int r = 0; r < cr; ++r) {
-          const int i_abs = r0 + c0 + r;
-          float s = 0.0f, dp = 0.0f;
+  for (int c = 0; c < D / 2; ++c) {
+    doop[c] = k_lds[1][lq * RS + hh * (D / 2) + c];
+    dl = __builtin_fmaf(doop[c], v_lds[0][lq * RS + hh * (D / 2) + c], dl);
+  }
+  dl = half_swap_sum(dl);
 #pragma unroll
-          for (int i = 0; i < QS; ++i) {
-            const int j = part + kBwdLanes * i;
-            if (j < kred) s = __builtin_fmaf(qr_lds[r][j], kf[i], s);
-          }
+  for (int e = 0; e < 4; ++e) kdst[e] = map_lds[lane % (D / 4) * 4 + e] & (D - 1);
+  const float lse2 = lse[(size_t)bh * N + min(q_abs, N - 1)] * kLog2e;
+  __syncthreads();   // the staged rows have been read
+
+  f32x16 dqacc[NG];
 #pragma unroll
-          for (int c = 0; c < CS; ++c) dp = __builtin_fmaf(do_lds[r][part * CS + c], vreg[c], dp);
-          s = quad_sum(s) * scale;
-          dp = quad_sum(dp);
-          const bool visible = valid && !(causal && n_abs > i_abs + shift);
-          const float p = visible ? expf(s - lse_lds[r]) : 0.0f;
-          const float ds = p * (dp - drow_lds[r]);
+  for (int mb = 0; mb < NG; ++mb) zero(dqacc[mb]);
+  for (int tile = w; tile < n_tiles; tile += kWaves) {
+    wave_order();   // the reads of the previous tile come first
+    if constexpr (G > 1) kt.scatter(k_lds[w], lane, kdst);
+    else kt.store(k_lds[w], lane);
+    vt.store(v_lds[w], lane);
+    if (tile + kWaves < n_tiles) {
+      kt.load(k_rsrc, tile + kWaves, lane);
+      vt.load(v_rsrc, tile + kWaves, lane);
+    }
+    wave_order();
+    f32x16 s, dp;
+    zero(s);
+    zero(dp);
+    if constexpr (G == 1) {
+      row_product<D>(&k_lds[w][lq * RS], hh, qop, s);
+    } else {
 #pragma unroll
-          for (int c = 0; c < CS; ++c) dvacc[c] = __builtin_fmaf(p, do_lds[r][part * CS + c], dvacc[c]);
-#pragma unroll
-          for (int i = 0; i < QS; ++i) {
-            const int j = part + kBwdLanes * i;
-            if (j < kred) dkf[i] = __builtin_fmaf(ds, qr_lds[r][j], dkf[i]);
-          }
+      for (int c = 0; c < D / 2; c += 4) {
+        const f32x4 x = *(const f32x4*)&k_lds[w][lq * RS + hh * (D / 2) + c];
+        if constexpr (G == 2) {
+          s = mfma(x[0] + x[1], qop[c / 2], s);
+          s = mfma(x[2] + x[3], qop[c / 2 + 1], s);
+        } else {
+          s = mfma(((x[0] + x[1]) + x[2]) + x[3], qop[c / 4], s);
         }
       }
-      // un-fuse: every member of group j receives the gradient of the fused column j. The four
-      // lanes of a key hold different groups, hence different channels: no two threads meet.
+    }
+    row_product<D>(&v_lds[w][lq * RS], hh, doop, dp);
+    const int n0 = tile * kTile;
 #pragma unroll
-      for (int i = 0; i < QS; ++i) {
-        const int j = part + kBwdLanes * i;
-        if (j < kred)
-          for (int g = 0; g < G; ++g) dk_lds[key][perm_lds[j * G + g]] += dkf[i];
+    for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], sl2e, -lse2));
+    if (n0 + kTile > Nk || (causal && n0 + kTile - 1 > r0 + shift)) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (n0 + acc_row(i, hh) > lim) s[i] = 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] *= dp[i] - dl;
+    if constexpr (G == 1) {
+      column_product<D>(k_lds[w], lq, hh, s, dqacc);
+    } else {
+      // lane m owns the groups NG*m .. (of 32 * NG slots; with 16 groups the upper lanes repeat the lower)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float* src = &k_lds[w][acc_row(i, hh) * RS + (lq * NG % KRED) * G];
+#pragma unroll
+        for (int mb = 0; mb < NG; ++mb) {
+          float x;
+          if constexpr (G == 2) {
+            const f32x2 y = *(const f32x2*)(src + mb * G);
+            x = y[0] + y[1];
+          } else {
+            const f32x4 y = *(const f32x4*)(src + mb * G);
+            x = ((y[0] + y[1]) + y[2]) + y[3];
+          }
+          dqacc[mb] = mfma(x, s[i], dqacc[mb]);
+        }
       }
     }
   }
-  __syncthreads();
-  E* dkh = dk + ((size_t)bk * Nk + n0) * D;
-  E* dvh = dv + ((size_t)bk * Nk + n0) * D;
-  for (int i = tid; i < tn * D; i += T) {
-    int n = i / D, c = i % D;
-    dkh[(size_t)n * D + c] = (E)(scale * dk_lds[n][c]);
-  }
-  if (valid) {
+
+  wave_order();
+  // dQ_r (G > 1: by group; G = 1: dQ~ by channel) of the wave, then summed over the waves
+  float* mine = &k_lds[w][lq * RS];
 #pragma unroll
-    for (int c = 0; c < CS; ++c) dvh[(size_t)key * D + part * CS + c] = (E)dvacc[c];
+  for (int i = 0; i < 16; ++i)
+#pragma unroll
+    for (int mb = 0; mb < NG; ++mb)
+      if (KRED >= 32 || acc_row(i, hh) < KRED) mine[acc_row(i, hh) * NG + mb] = dqacc[mb][i];
+  __syncthreads();
+  for (int i = tid; i < kTile * KRED / 4; i += kThreads) {
+    const int row = i / (KRED / 4), c = i % (KRED / 4) * 4;
+    f32x4 x = *(const f32x4*)&k_lds[0][row * RS + c];
+#pragma unroll
+    for (int j = 1; j < kWaves; ++j) x += *(const f32x4*)&k_lds[j][row * RS + c];
+    *(f32x4*)&v_lds[0][row * RS + c] = x;
+  }
+  __syncthreads();
+  for (int i = tid; i < kTile * D / 4; i += kThreads) {
+    const int row = i / (D / 4), c = i % (D / 4) * 4;
+    if (r0 + row >= N) continue;
+    f32x4 y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if constexpr (G > 1) {
+        const int pos = map_lds[c + e] & (D - 1);
+        y[e] = pos % G == 0 ? scale * v_lds[0][row * RS + pos / G] : 0.0f;
+      } else if (!perm) {
+        y[e] = scale * v_lds[0][row * RS + c + e];
+      } else {
+        // the sampled channel of a group receives the sum over its members, the others 0
+        float s = 0.0f;
+        if (map_lds[c + e] == c + e) {
+          const int pos = (pos_lds[c + e] & (D - 1)) / group * group;
+          for (int g = 0; g < group; ++g) s += v_lds[0][row * RS + order_lds[pos + g]];
+        }
+        y[e] = scale * s;
+      }
+    }
+    *(f32x4*)(dq + head + (size_t)(r0 + row) * D + c) = y;
   }
 }
 
-template <typename T>
-static hipError_t launch_bwd_typed(const void* q, const void* k, const void* v, const void* o, const void* dout,
-                                   const float* lse, void* dq, void* dk, void* dv, const uint8_t* perm,
-                                   const Problem& pb, int distr, hipStream_t stream) {
+template <int D>
+hipError_t launch_d(const float* q, const float* k, const float* v, const float* o, const float* dout, const float* lse,
+                    float* dq, float* dk, float* dv, const uint8_t* perm, const Problem& pb, int distr, hipStream_t stream) {
   const int Tq = (pb.N + pb.Br - 1) / pb.Br;
-  const int Tk = (pb.Nk + kBwdTile - 1) / kBwdTile;
-  const long long q_units = (long long)pb.B * pb.H * Tq;
-  const long long k_units = (long long)pb.B * pb.Hkv * Tk;
-  if (k_units > 0x7fffffffLL) return hipErrorInvalidValue;
-#define DA_BWD_DQ(DD, BB)                                                                                       \
-  hipLaunchKernelGGL((attn_f32_bwd_dq_kernel<T, DD, BB>), dim3((unsigned)q_units), dim3(BB * kBwdLanes), 0, stream, \
-                     (const T*)q, (const T*)k, (const T*)v, (const T*)o, (const T*)dout, lse, (T*)dq, perm, pb.H, \
-                     pb.Hkv, pb.N, pb.Nk, Tq, pb.n_groups, pb.causal, pb.scale, distr)
-  if (pb.d == 64 && pb.Br == 64) DA_BWD_DQ(64, 64);
-  else if (pb.d == 64 && pb.Br == 128) DA_BWD_DQ(64, 128);
-  else if (pb.d == 64 && pb.Br == 256) DA_BWD_DQ(64, 256);
-  else if (pb.d == 128 && pb.Br == 64) DA_BWD_DQ(128, 64);
-  else if (pb.d == 128 && pb.Br == 128) DA_BWD_DQ(128, 128);
-  else if (pb.d == 128 && pb.Br == 256) DA_BWD_DQ(128, 256);
-  else return hipErrorInvalidValue;
-#undef DA_BWD_DQ
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-#define DA_BWD_DKV(DD)                                                                                            \
-  hipLaunchKernelGGL((attn_f32_bwd_dkv_kernel<T, DD>), dim3((unsigned)k_units), dim3(kBwdTile * kBwdLanes), 0, stream, \
-                     (const T*)q, (const T*)k, (const T*)v, (const T*)o, (const T*)dout, lse, (T*)dk, (T*)dv, perm,  \
-                     pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, Tk, pb.n_groups, pb.causal, pb.scale, distr)
-  if (pb.d == 64) DA_BWD_DKV(64);
-  else DA_BWD_DKV(128);
-#undef DA_BWD_DKV
+  const size_t rows = (size_t)pb.B * pb.H * pb.N;
+  const long long q_units = (long long)pb.B * pb.H * ((pb.N + kTile - 1) / kTile);
+  const long long k_units = (long long)pb.B * pb.Hkv * ((pb.Nk + kTile - 1) / kTile);
+  const size_t d_units = (rows * (D / 4) + kThreads - 1) / kThreads;
+  if (q_units > 0x7fffffffLL || k_units > 0x7fffffffLL || d_units > 0x7fffffffULL) return hipErrorInvalidValue;
+  const uint8_t* table = distr ? perm : nullptr;
+  const int n_groups = distr ? pb.n_groups : D;
+  float* delta = dq;   // one float per row: dq is overwritten after its last use
+  hipLaunchKernelGGL((bwd_delta_kernel<D>), dim3((unsigned)d_units), dim3(kThreads), 0, stream, o, dout, delta, rows);
+  hipLaunchKernelGGL((bwd_dkv_kernel<D>), dim3((unsigned)k_units), dim3(kThreads), 0, stream, q, k, v, dout, lse, delta, dk, dv,
+                     table, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, n_groups, pb.causal, pb.scale);
+#define DA_DQ(GG)                                                                                                          \
+  hipLaunchKernelGGL((bwd_dq_kernel<D, GG>), dim3((unsigned)q_units), dim3(kThreads), 0, stream, q, k, v, o, dout, lse, dq, \
+                     table, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, n_groups, pb.causal, pb.scale)
+  if (D / n_groups == 2) DA_DQ(2);
+  else if (D / n_groups == 4) DA_DQ(4);
+  else DA_DQ(1);
+#undef DA_DQ
   return hipGetLastError();
 }
+
+}  // namespace
 
 hipError_t launch_attn_f32_bwd(const void* q, const void* k, const void* v, const void* o, const void* dout,
                                const float* lse, void* dq, void* dk, void* dv, const uint8_t* perm,
                                const Problem& pb, int distr, hipStream_t stream) {
-  return launch_bwd_typed<float>(q, k, v, o, dout, lse, dq, dk, dv, perm, pb, distr, stream);
+  if (pb.d == 64)
+    return launch_d<64>((const float*)q, (const float*)k, (const float*)v, (const float*)o, (const float*)dout, lse, (float*)dq,
+                        (float*)dk, (float*)dv, perm, pb, distr, stream);
+  if (pb.d == 128)
+    return launch_d<128>((const float*)q, (const float*)k, (const float*)v, (const float*)o, (const float*)dout, lse, (float*)dq,
+                         (float*)dk, (float*)dv, perm, pb, distr, stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace da

@@ -29,3 +29,21 @@ def test_float_forward(d, N, Nk, causal, side, Bc, G):
     _forward(cfg)
     if side == 0 and G == 1:
         _forward(cfg, distr=False)
+
+
+# Float backward: 32-row tiles on both sides, dealt out to 4 waves; groups of 2 and 4 have products
+# over the groups, other sizes over the channels. Bound: float rounding, the parity bar of the backward tests.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N,Nk,causal", [(1, 1, False), (31, 33, True), (33, 31, False), (129, 290, True)])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_float_backward(d, N, Nk, causal, G):
+    import gpu_util as U
+    from test_gpu_backward import TOL, run_backward
+    cfg = W.CONFIGS["tiny"].scaled(B=2, H=4, Hkv=2, N=N, Nk=Nk, d=d, causal=causal, n_groups=d // G, recipe="normal")
+    print(f"case {cfg}", flush=True)
+    q, k, v = W.make(cfg)
+    dout = W.make_grad(cfg)
+    got = run_backward(cfg, q, k, v, dout, True)
+    for what, g, r in zip(("dq", "dk", "dv"), got, oracle.distr_bwd(q, k, v, dout, U.oracle_params(cfg))):
+        err = np.abs(g - r).max()
+        assert err <= TOL * max(1.0, np.abs(r).max()), f"{what}: {err:.4g}"
