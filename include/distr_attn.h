@@ -49,9 +49,11 @@ typedef enum { DA_BF16 = 0, DA_F32 = 1 } da_dtype;
  * to one MFMA step of 16, and need Bc = 64), for float any divisor of d; 1 <= n_planes <= 32;
  * N, Nk >= 1 arbitrary (ragged last blocks are masked), N * d * 4 and Nk * d * 4 < 2^31; at most
  * 2^31 - 1 query blocks.
- * bf16 DistrAttention path: the reduced product S^ = Q_r K_f^T runs in half precision on
- * Q_r * softmax_scale * log2(e) and on K. Full precision needs magnitudes inside half's normal
- * range: |q| * softmax_scale * log2(e) beyond 65504 and |k| beyond 65504 / G* are clamped; below
+ * bf16 DistrAttention path: where the reduced product S^ = Q_r K_f^T is taken over the groups it runs
+ * in half precision on Q_r * softmax_scale * log2(e) and on K; small problems and few query rows
+ * against many keys take it over the channels of the bf16 tensors (S^ = Q~ K^T, Q~ = Q with every
+ * channel replaced by its group's sampled one) and have no such limit. Full precision in half needs
+ * magnitudes inside its normal range: |q| * softmax_scale * log2(e) beyond 65504 and |k| beyond 65504 / G* are clamped; below
  * 2^-14 (6.1e-5) values keep fewer significand bits (absolute step 2^-24) and below 2^-25 they
  * become 0. The exact path and the float path have no such limit.
  */
@@ -73,9 +75,13 @@ typedef struct {
                            growth; outgrown buffers are kept until distr_attn_release; growing
                            while the stream is being captured into a graph is refused). Calls that
                            may overlap in time on different streams must each bring their own
-                           workspace. Only what the call writes is needed: no K^T part with kt_in,
-                           no table with perm_in / perm_out or when the attention kernel does the
-                           LSH stage itself.                                                        */
+                           workspace. Needed: the K^T part unless kt_in is given, and the table unless
+                           perm_in / perm_out are or the attention kernel does the LSH stage itself.
+                           Calls with few query rows deal their keys out to several workgroups
+                           and sum up in the rest of a workspace of distr_attn_workspace_bytes(), or, with
+                           none, in a library-owned buffer per device and stream (32 MB, for up to
+                           16 streams, kept until distr_attn_release); without either they run
+                           undivided. Never refused for it.                                         */
   size_t workspace_bytes;
   uint8_t *perm_out;    /* optional device [B][H][Tq][d]: channel at sorted position s of each block */
   uint32_t *hash_out;   /* optional device [B][H][Tq][d]: hash of each channel of each block          */
@@ -175,8 +181,8 @@ int distr_attn_lsh_group(const void *q, const da_params *p);
 int distr_attn_key_prepass(const void *k, void *kt_out, const da_params *p);
 size_t distr_attn_kt_bytes(const da_params *p);
 
-/* Bytes of device scratch distr_attn_fwd_ex needs for p: permutation table + transposed keys
- * (0 on invalid p). */
+/* Bytes of device scratch distr_attn_fwd_ex (and distr_attn_exact_fwd_ex) can use for p: permutation
+ * table + transposed keys, or the partial sums of a call whose keys are dealt out (0 on invalid p). */
 size_t distr_attn_workspace_bytes(const da_params *p);
 
 /*
@@ -189,8 +195,8 @@ int distr_attn_hyperplanes(uint64_t seed, int n_planes, int Br, float *host_out)
 /*
  * distr_attn_fwd_ex for callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc. Same arguments, same kernels, same
- * result; the scratch the forward needs (the transposed copy of K, and the permutation table
- * when the LSH stage runs as a kernel of its own) lives in a fixed device array of
+ * result; the scratch the forward needs (the transposed copy of K or partial sums, and the permutation
+ * table when the LSH stage runs as a kernel of its own) lives in a fixed device array of
  * DISTR_ATTN_NOALLOC_MAX_BYTES inside the library instead of a workspace, so the call allocates
  * and frees nothing (p->workspace is ignored). Each GPU the library runs on holds its own copy
  * of the array until the process ends. A problem whose scratch exceeds the array is refused

@@ -3,6 +3,7 @@
 
 #include <cstdlib>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -25,6 +26,20 @@ size_t g_ws_bytes[kMaxDevices] = {0};
 // thread that fetched the pointer just before the growth) may still use them, so they are kept
 // until distr_attn_release instead of being freed inside a forward call.
 std::vector<void*> g_ws_retired[kMaxDevices];
+
+// Scratch of calls whose keys are dealt out to several workgroups per Q block (partial sums, and the
+// table of a LSH stage of their own): one buffer per device and stream, so that calls on different
+// streams do not meet in it; the lock is held from the first launch that writes it to the last that reads
+// it, so that calls of several threads on one stream do not interleave. At most kMaxShareBuffers streams
+// of a device get one: later streams, and a stream under capture that has none yet, go without the split.
+constexpr int kMaxShareBuffers = 16;
+constexpr size_t kShareBytes = (size_t)32 << 20;
+struct ShareBuffer {
+  hipStream_t stream;
+  void* ptr;
+};
+std::mutex g_share_mutex;
+std::vector<ShareBuffer> g_shares[kMaxDevices];
 
 // Scratch of distr_attn_fwd_noalloc: a fixed device array, one copy per GPU the library is
 // loaded on, resident until the process ends. Host code never uses the array's name as an
@@ -135,9 +150,33 @@ size_t kt_bytes(const Resolved& r) {
   return da::kt_copy_bytes(r.pb.B, r.pb.Hkv, r.pb.d, r.pb.Nk) + da::kRtabBytes;
 }
 
-// The transposed copy of K is read by the bf16 matrix-core kernels (the mirrored form runs on the
-// float-arithmetic kernel and needs none).
+// The transposed copy of K is what a bf16 call's workspace is sized for (the mirrored form runs on the
+// float-arithmetic kernel and needs none); calls that take S^ as Q~ K^T leave it unwritten.
 bool needs_kt(const Resolved& r) { return r.dtype == DA_BF16 && r.pb.side == 0; }
+
+// Scratch of a call that deals a Q block's keys out: [row statistics | sums].
+size_t share_stat_bytes(const Resolved& r, int n) { return ((size_t)n * r.pb.B * r.pb.H * r.pb.N * 8 + 255) & ~(size_t)255; }
+size_t share_bytes(const Resolved& r, int n) {
+  return n > 1 ? share_stat_bytes(r, n) + (((size_t)n * r.pb.B * r.pb.H * r.pb.N * r.pb.d * 4 + 255) & ~(size_t)255) : 0;
+}
+
+// The stream's own buffer of kShareBytes on the current device (null: go without). g_share_mutex is held.
+char* share_buffer(hipStream_t stream) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
+  for (const ShareBuffer& x : g_shares[dev])
+    if (x.stream == stream) return (char*)x.ptr;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (g_shares[dev].size() >= kMaxShareBuffers || hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
+    return nullptr;
+  void* ptr = nullptr;
+  if (hipMalloc(&ptr, kShareBytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  g_shares[dev].push_back(ShareBuffer{stream, ptr});
+  return (char*)ptr;
+}
 
 // Address of the static scratch array on the current device (looked up once per device).
 int static_scratch(void** out) {
@@ -154,10 +193,8 @@ int static_scratch(void** out) {
   return DA_OK;
 }
 
-// Device scratch of the distr path: [K^T copy | permutation table]. Only the parts this call
-// writes are asked for: no K^T copy when the caller brings kt_in (or on the float path), no
-// table when the grouping comes from perm_in, goes to perm_out, or stays inside the attention
-// kernel. Source: the caller's workspace, the static array (no_alloc), or the library-owned buffer.
+// `need` bytes of device scratch: from the caller's workspace, the static array (no_alloc), or the
+// library-owned buffer.
 int scratch_base(const da_params* p, const Resolved& r, size_t need, bool no_alloc, char** out) {
   char* base = nullptr;
   if (no_alloc) {
@@ -193,23 +230,6 @@ int scratch_base(const da_params* p, const Resolved& r, size_t need, bool no_all
     base = (char*)g_ws_ptr[dev];
   }
   *out = base;
-  return DA_OK;
-}
-
-int get_scratch(const da_params* p, const Resolved& r, bool need_table, bool no_alloc, uint8_t** perm, void** kt) {
-  const size_t kt_need = (needs_kt(r) && !p->kt_in) ? kt_bytes(r) : 0;
-  const size_t perm_need = need_table ? perm_bytes(r) : 0;
-  const size_t need = kt_need + perm_need;
-  char* base = nullptr;
-  if (need == 0) {
-    *kt = nullptr;
-    *perm = nullptr;
-    return DA_OK;
-  }
-  int rc = scratch_base(p, r, need, no_alloc, &base);
-  if (rc) return rc;
-  *kt = kt_need ? (void*)base : nullptr;
-  *perm = perm_need ? (uint8_t*)(base + kt_need) : nullptr;
   return DA_OK;
 }
 
@@ -249,8 +269,6 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   if (r.dtype == DA_BF16 && r.pb.side == 0 && !da::attn_bf16_supported(r.pb, distr ? 1 : 0))
     return fail(DA_ERR_UNSUPPORTED, "bf16 kernels need n_groups in {4, 8, 16, 32, 64, 128} (16, 32, 64 or d when Bc is not "
                 "64) and groups of at most 16 channels; got d=%d Br=%d Bc=%d n_groups=%d", p->d, p->Br, p->Bc, p->n_groups);
-  const uint8_t* perm = nullptr;
-  void* kt = nullptr;
   // Groups of one channel (G* = 1): S^ = Q_r K_f^T is Q K^T with its terms taken in the sorted
   // channel order (Sec. 3.1: one column per group reproduces S). The bf16 path then runs the
   // exact kernel; the LSH stage still runs if the caller asked for its tables.
@@ -262,40 +280,90 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
     }
     distr = false;
   }
-  if (distr) {
-    // bf16 path, up to 16 projections, no hashes asked for: the attention kernel hashes and groups
-    // its own Q block in its prologue (same arithmetic as the LSH kernel); the table is written
-    // only if the caller gave perm_out.
-    const bool lsh_in_kernel = r.dtype == DA_BF16 && r.pb.side == 0 && !p->perm_in && !p->hash_out && r.pb.n_planes <= 16;
-    if (lsh_in_kernel) r.pb.perm_w = p->perm_out;
-    const bool run_lsh = !p->perm_in && !lsh_in_kernel;
-    uint8_t* table = nullptr;
-    rc = get_scratch(p, r, run_lsh && !p->perm_out, no_alloc, &table, &kt);
+  const bool matrix = r.dtype == DA_BF16 && r.pb.side == 0;
+  const bool replicated = distr && matrix && da::attn_bf16_replicated(r.pb);
+  const bool fused = distr && matrix && !replicated;
+  // bf16 path, up to 16 projections, no hashes asked for: the attention kernel hashes and groups
+  // its own Q block in its prologue (same arithmetic as the LSH kernel); the table is written
+  // only if the caller gave perm_out.
+  bool lsh_in_kernel = distr && matrix && !p->perm_in && !p->hash_out && r.pb.n_planes <= 16;
+  const bool own_table = distr && !p->perm_in && !p->perm_out;
+  // Scratch: [K^T copy | permutation table]. Only the parts this call writes are asked for: no K^T
+  // copy when the caller brings kt_in, on the float path or for Q~ K^T, no table when the grouping comes
+  // from perm_in, goes to perm_out, or stays inside the attention kernel. (A caller's workspace is
+  // checked for the K^T copy whichever product the call takes: what is enough depends on the
+  // arguments alone.)
+  if (distr && matrix && p->kt_in && ((uintptr_t)p->kt_in & 255u) != 0)
+    return fail(DA_ERR_INVALID_ARG, "kt_in must be 256-byte aligned");
+  const size_t kt_need = (distr && matrix && !p->kt_in) ? kt_bytes(r) : 0;
+  const size_t table_need = (own_table && !lsh_in_kernel) ? perm_bytes(r) : 0;
+  uint8_t* table = nullptr;
+  void* kt = nullptr;
+  char* base = nullptr;
+  size_t kt_room = fused ? kt_need : 0;
+  if (distr && p->workspace && !no_alloc && kt_need + table_need) {
+    kt_room = kt_need;
+    rc = scratch_base(p, r, kt_need + table_need, false, &base);
     if (rc) return rc;
-    if (p->perm_in) {
-      perm = p->perm_in;
-    } else if (run_lsh) {
-      if (p->perm_out) table = p->perm_out;
-      rc = check_launch(r.pb.side == 1
-                            ? da::launch_lsh_group(k, r.dtype, key_side_problem(r.pb), table, p->hash_out, r.stream)
-                            : da::launch_lsh_group(q, r.dtype, r.pb, table, p->hash_out, r.stream),
-                        "lsh_group launch", r.stream);
-      if (rc) return rc;
-      perm = table;
-    }
-    if (needs_kt(r) && p->kt_in) {
-      if (((uintptr_t)p->kt_in & 255u) != 0) return fail(DA_ERR_INVALID_ARG, "kt_in must be 256-byte aligned");
-      kt = const_cast<void*>(p->kt_in);
-    } else if (needs_kt(r)) {
-      rc = check_launch(da::launch_kt_prepass(k, kt, r.pb, r.stream), "key pre-pass launch", r.stream);
-      if (rc) return rc;
+  }
+  // Keys dealt out to several workgroups per Q block, where scratch for their sums is at hand. Every
+  // such workgroup would repeat the LSH stage: it then runs as a kernel of its own (not for the few rows
+  // of a decoding call, whose grouping is done before the first keys arrive).
+  const bool few = matrix && !fused && da::attn_bf16_few_rows(r.pb);
+  const int n_split = (matrix && !fused) ? da::attn_bf16_splits(r.pb, distr ? 1 : 0) : 1;
+  const size_t split_table = (own_table && n_split > 1 && !(few && lsh_in_kernel)) ? perm_bytes(r) : 0;
+  const size_t split_need = split_table + share_bytes(r, n_split);
+  std::unique_lock<std::mutex> share_lock(g_share_mutex, std::defer_lock);
+  char* share = nullptr;
+  if (n_split > 1) {
+    if (no_alloc || p->workspace) {
+      const size_t room = no_alloc ? kStaticScratchBytes : p->workspace_bytes;
+      if (room >= split_need && (no_alloc || ((uintptr_t)p->workspace & 255u) == 0)) {
+        rc = scratch_base(p, r, split_need, no_alloc, &share);
+        if (rc) return rc;
+      }
+    } else if (split_need <= kShareBytes) {
+      share_lock.lock();
+      share = share_buffer(r.stream);
+      if (!share) share_lock.unlock();
     }
   }
+  if (share) {
+    r.pb.n_split = n_split;
+    table = split_table ? (uint8_t*)share : nullptr;
+    r.pb.part_stat = (float*)(share + split_table);
+    r.pb.part_o = (float*)(share + split_table + share_stat_bytes(r, n_split));
+    lsh_in_kernel = lsh_in_kernel && few;
+  } else if (!base && kt_room + table_need) {
+    rc = scratch_base(p, r, kt_room + table_need, no_alloc, &base);
+    if (rc) return rc;
+  }
+  if (!share && table_need) table = (uint8_t*)(base + kt_room);
+  const uint8_t* perm = p->perm_in;
+  if (lsh_in_kernel) r.pb.perm_w = p->perm_out;
+  if (distr && !p->perm_in && !lsh_in_kernel) {
+    if (p->perm_out) table = p->perm_out;
+    rc = check_launch(r.pb.side == 1
+                          ? da::launch_lsh_group(k, r.dtype, key_side_problem(r.pb), table, p->hash_out, r.stream)
+                          : da::launch_lsh_group(q, r.dtype, r.pb, table, p->hash_out, r.stream),
+                      "lsh_group launch", r.stream);
+    if (rc) return rc;
+    perm = table;
+  }
+  if (fused && p->kt_in) {
+    kt = const_cast<void*>(p->kt_in);
+  } else if (fused) {
+    kt = base;
+    rc = check_launch(da::launch_kt_prepass(k, kt, r.pb, r.stream), "key pre-pass launch", r.stream);
+    if (rc) return rc;
+  }
+  if (!distr) perm = nullptr;
   // (the mirrored form runs on the float-arithmetic kernel for either dtype)
-  hipError_t e = (r.dtype == DA_BF16 && !(distr && r.pb.side == 1))
-                     ? da::launch_attn_bf16(q, k, v, o, perm, kt, r.pb, distr ? 1 : 0, r.stream)
-                     : da::launch_attn_f32(q, k, v, o, perm, r.pb, r.dtype, distr ? 1 : 0, r.stream);
-  return check_launch(e, "attention launch", r.stream);
+  rc = check_launch(matrix ? da::launch_attn_bf16(q, k, v, o, perm, kt, r.pb, distr ? 1 : 0, r.stream)
+                           : da::launch_attn_f32(q, k, v, o, perm, r.pb, r.dtype, distr ? 1 : 0, r.stream),
+                    "attention launch", r.stream);
+  if (rc || r.pb.n_split == 1) return rc;
+  return check_launch(da::launch_attn_bf16_combine(o, r.pb, r.stream), "combine launch", r.stream);
 }
 
 // Backward of the float path. The grouping is the forward's: the LSH stage runs again on q with
@@ -424,7 +492,9 @@ size_t distr_attn_kt_bytes(const da_params* p) {
 size_t distr_attn_workspace_bytes(const da_params* p) {
   Resolved r;
   if (resolve(p, true, &r)) return 0;
-  return (needs_kt(r) ? kt_bytes(r) : 0) + perm_bytes(r);
+  const size_t whole = (needs_kt(r) ? kt_bytes(r) : 0) + perm_bytes(r);
+  const size_t split = needs_kt(r) ? perm_bytes(r) + share_bytes(r, std::max(da::attn_bf16_splits(r.pb, 0), da::attn_bf16_splits(r.pb, 1))) : 0;
+  return whole > split ? whole : split;
 }
 
 size_t distr_attn_bwd_workspace_bytes(const da_params* p) {
@@ -449,14 +519,17 @@ int distr_attn_set_stream(void* hip_stream) {
 
 int distr_attn_release(void) {
   std::lock_guard<std::mutex> lock(g_ws_mutex);
+  std::lock_guard<std::mutex> share_lock(g_share_mutex);
   int rc = DA_OK;
   int cur = 0;
   bool have_cur = hipGetDevice(&cur) == hipSuccess;
   for (int dev = 0; dev < kMaxDevices; ++dev) {
-    if (!g_ws_ptr[dev] && g_ws_retired[dev].empty()) continue;
+    if (!g_ws_ptr[dev] && g_ws_retired[dev].empty() && g_shares[dev].empty()) continue;
     bool ok = hipSetDevice(dev) == hipSuccess && hipDeviceSynchronize() == hipSuccess;
     if (ok && g_ws_ptr[dev]) ok = hipFree(g_ws_ptr[dev]) == hipSuccess;
     for (void* old : g_ws_retired[dev]) ok = ok && hipFree(old) == hipSuccess;
+    for (const ShareBuffer& x : g_shares[dev]) ok = ok && hipFree(x.ptr) == hipSuccess;
+    g_shares[dev].clear();
     if (!ok) rc = fail(DA_ERR_HIP, "release: freeing the workspace of device %d failed", dev);
     g_ws_retired[dev].clear();
     g_ws_ptr[dev] = nullptr;

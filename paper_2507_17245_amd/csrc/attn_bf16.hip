@@ -27,10 +27,101 @@ bool attn_bf16_supported(const Problem& pb, int distr) {
   return true;
 }
 
+// Q~ K^T (see ScoreMode in attn_bf16_impl.h) instead of Q_r K_f^T where the transposed copy of K costs more
+// than the shorter contraction saves. Per key of a kv head the copy moves 4 d bytes (0.8 ps d at 5 TB/s), and
+// its launch costs 4 us; the fused kernel saves about a seventh of 4 d FLOP per visible (query, key) pair
+// (0.5 fs d at 1.1 PFLOP/s): equal at 1570 visible rows per key plus the launch's share.
+// Measured, Q~ K^T | fused: B64 H12 N197 d64 40 | 46 us; H16 N1024 d64 causal 20 | 22; H16 N4096 d64 causal 53 | 54;
+// H32 Hkv8 N4096 d64 causal 84 | 77; H16 N2048 d128 causal 47 | 49; N8192 282 | 253; N200 Nk32768 d128 109 | 500.
+bool attn_bf16_replicated(const Problem& pb) {
+  if (attn_bf16_few_rows(pb)) return true;
+  const double rows = (double)(pb.H / pb.Hkv) * pb.N * (pb.causal ? 1.0 - 0.5 * pb.N / pb.Nk : 1.0);
+  return rows < 1570.0 + 7.8e9 / ((double)pb.d * pb.B * pb.Hkv * pb.Nk);
+}
+
+// Key shares per Q block, for launches that would leave compute units without a workgroup: one
+// four-wave workgroup (two of two waves) for each, at least four tiles per share, and only where the
+// tiles taken off a workgroup's walk outweigh the combine kernel (4 us, about 12 tiles) and, grouped,
+// the LSH stage in a kernel of its own (another 18). Measured, 1 | 256 | 512 workgroups: exact H16 N200 Nk8192
+// d64 71 | 19 | 22 us; N1000 Nk8192 d128 109 | 72 | 80; N200 Nk32768 d128 486 | 90 | 87; N2048 d64 causal 22 | 22 | 29.
+int attn_bf16_splits(const Problem& pb, int distr) {
+  const long long units = (long long)pb.B * pb.H * ((pb.N + pb.Br - 1) / pb.Br);
+  const int tiles = (pb.Nk + pb.Bc - 1) / pb.Bc;
+  long long n = 1024 / (pb.Br / 32) / units;
+  if (n > tiles / 4) n = tiles / 4;
+  if (n < 2 || tiles - tiles / n < (distr ? 30 : 12)) n = 1;
+  if (attn_bf16_few_rows(pb)) n = attn_bf16_few_splits(pb);
+  const long long row_bytes = (long long)pb.B * pb.H * pb.N * (pb.d * 4 + 8);
+  if (n * row_bytes > (24LL << 20)) n = (24LL << 20) / row_bytes;
+  return n > 1 ? (int)n : 1;
+}
+
+// O of a row = sum over the shares of 2^(reference - largest reference) O_share, over the same sum of the
+// row sums. A workgroup takes 256 / L / (D/4) rows, a thread four channels of every L-th share: few rows
+// with many shares (decoding) would otherwise be a chain of loads in a handful of waves.
+template <int D, int L>
+__global__ __launch_bounds__(256) void attn_bf16_combine_kernel(const float* __restrict__ part_o, const f32x2* __restrict__ part_stat,
+                                                                bf16* __restrict__ o, float* __restrict__ lse, int rows, int n_split) {
+  constexpr int Q = D / 4, R = 256 / L / Q;
+  __shared__ float l_lds[L > 1 ? 256 : 1];
+  __shared__ __attribute__((aligned(16))) f32x4 acc_lds[L > 1 ? 256 : 1];
+  const int tid = threadIdx.x;
+  const int c = tid % Q, row = blockIdx.x * R + tid / Q % R, part = tid / Q / R;
+  const int row_ld = min(row, rows - 1);
+  float ref = -INFINITY;
+#pragma unroll 8
+  for (int s = 0; s < n_split; ++s) {
+    const f32x2 st = part_stat[(size_t)s * rows + row_ld];
+    ref = fmaxf(ref, st[1] > 0.0f ? st[0] : -INFINITY);   // (an empty share has left no sums)
+  }
+  float l = 0.0f;
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+  for (int s = part; s < n_split; s += L) {
+    const f32x2 st = part_stat[(size_t)s * rows + row_ld];
+    const f32x4 x = *(const f32x4*)(part_o + ((size_t)s * rows + row_ld) * D + c * 4);
+    const bool some = st[1] > 0.0f;
+    const float w = some ? __builtin_amdgcn_exp2f(st[0] - ref) : 0.0f;
+    l = __builtin_fmaf(w, st[1], l);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(w, some ? x[e] : 0.0f, acc[e]);
+  }
+  if constexpr (L > 1) {
+    l_lds[tid] = l;
+    acc_lds[tid] = acc;
+    __syncthreads();
+    if (part != 0) return;
+#pragma unroll
+    for (int j = 1; j < L; ++j) {
+      l += l_lds[j * Q * R + tid];
+      acc += acc_lds[j * Q * R + tid];
+    }
+  }
+  if (row >= rows) return;
+  const float inv = 1.0f / l;
+  const bf16x4 y = {(bf16)(acc[0] * inv), (bf16)(acc[1] * inv), (bf16)(acc[2] * inv), (bf16)(acc[3] * inv)};
+  *(bf16x4*)(o + (size_t)row * D + c * 4) = y;
+  if (lse && c == 0) lse[row] = 0.6931471805599453f * (ref + __builtin_log2f(l));
+}
+
+template <int D>
+static hipError_t launch_combine(void* o, const Problem& pb, hipStream_t stream) {
+  const long long rows = (long long)pb.B * pb.H * pb.N;
+#define DA_COMBINE(L)                                                                                                     hipLaunchKernelGGL((attn_bf16_combine_kernel<D, L>), dim3((unsigned)((rows + 1024 / L / D - 1) / (1024 / L / D))), dim3(256), 0,                      stream, pb.part_o, (const f32x2*)pb.part_stat, (bf16*)o, pb.lse, (int)rows, pb.n_split)
+  if (rows * (D / 4) >= 65536 || pb.n_split < 8) DA_COMBINE(1);   // a wave for every SIMD as it is
+  else DA_COMBINE(8);
+#undef DA_COMBINE
+  return hipGetLastError();
+}
+
+hipError_t launch_attn_bf16_combine(void* o, const Problem& pb, hipStream_t stream) {
+  return pb.d == 64 ? launch_combine<64>(o, pb, stream) : launch_combine<128>(o, pb, stream);
+}
+
 hipError_t launch_attn_bf16(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                             const void* kt, const Problem& pb, int distr, hipStream_t stream) {
   if (!attn_bf16_supported(pb, distr)) return hipErrorInvalidValue;
-  if (distr && !kt) return hipErrorInvalidValue;
+  if (!kt && attn_bf16_few_rows(pb)) return launch_attn_bf16_few(q, k, v, o, perm, pb, distr, stream);
   if (pb.Bc == 32) return launch_attn_bf16_bc32(q, k, v, o, perm, kt, pb, distr, stream);
   if (pb.Bc == 128) return launch_attn_bf16_bc128(q, k, v, o, perm, kt, pb, distr, stream);
   return launch_attn_bf16_bc64(q, k, v, o, perm, kt, pb, distr, stream);

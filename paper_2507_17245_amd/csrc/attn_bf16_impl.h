@@ -85,10 +85,22 @@ __device__ inline int kf_swizzle(int row) {
   else return (row >> 1) & 1;
 }
 
+// What the score product is taken of.
+//   kExact       Q and K.
+//   kFused       Q_r and K_f, on the f16 matrix path, contraction over the groups.
+//   kReplicated  Q~ and K: Q~ is Q with every channel replaced by its group's sampled channel, so
+//                S^ = Q_r K_f^T = Q~ K^T (a sum over groups of sums over members). The exact kernel's
+//                loop with the grouping in the prologue: d / n_groups times the products, but no
+//                transposed copy of K to make first and no fusion (rule: attn_bf16.hip).
+enum ScoreMode { kExact, kFused, kReplicated };
+
 // KRED: contraction length of the score product (a multiple of the MFMA step, 16). NG: number of
-// channel groups; smaller than KRED only for n_groups 4 and 8, whose operands are zero-padded to 16.
-template <int D, int BR, int BC, int KRED, bool DISTR, int NG = KRED>
+// channel groups; smaller than KRED only for n_groups 4 and 8, whose operands are zero-padded to 16
+// (kFused; the other modes are built once for every n_groups, NG = KRED = D).
+template <int D, int BR, int BC, int KRED, int MODE, int NG = KRED>
 struct Cfg {
+  static constexpr bool FUSED = MODE == kFused;
+  static constexpr bool GROUPED = MODE != kExact;
   static constexpr int NW = BR / 32;              // wavefronts per workgroup
   static constexpr int T = NW * 64;               // threads
   static constexpr int G = D / NG;                // channels per group
@@ -118,7 +130,7 @@ struct Cfg {
   static constexpr int TILEB = BC * ROWB;         // bytes of an unpadded tile
   static constexpr int KTROWB = BC * 2;           // bytes of a K^T / K_f^T row (BC keys)
   static constexpr int PPR = BC / 8;              // 16-byte pieces (8 keys) per K^T / K_f^T row
-  static constexpr int KX_BYTES = DISTR ? KRED * KTROWB : TILEB;   // one Kx buffer: K_f^T or K
+  static constexpr int KX_BYTES = FUSED ? KRED * KTROWB : TILEB;   // one Kx buffer: K_f^T or K
   static constexpr int FUSE_OUT = (NG * PPR + T - 1) / T;   // 16-byte fused outputs per thread and tile
   static constexpr int KSTEPS = KRED / 16;        // MFMA steps of the score product
   // Register budget: two waves per SIMD, except the widest tile at d = 128, whose two score sets
@@ -134,16 +146,17 @@ struct Cfg {
 // overflowed or NaN sum fails the comparison too), and the sum is needed anyway.
 constexpr float kTau = 8.0f;
 
-template <int D, int BR, int BC, int KRED, bool DISTR, int NG>
-__global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER_SIMD)) void attn_bf16_kernel(
+template <int D, int BR, int BC, int KRED, int MODE, int NG>
+__global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_SIMD)) void attn_bf16_kernel(
     const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
     bf16* __restrict__ o, const uint8_t* __restrict__ perm, const f16* __restrict__ kt, int Npad,
     int H, int Hkv, int N, int Nk, int Tq, int causal, float scale_log2e, int total_units, int n_planes,
     int gray_mode, uint64_t lsh_seed, float* __restrict__ lse, const char* __restrict__ rtab,
-    uint8_t* __restrict__ perm_w) {
-  using C = Cfg<D, BR, BC, KRED, DISTR, NG>;
+    uint8_t* __restrict__ perm_w, int n_groups, int n_split, float* __restrict__ part_o, f32x2* __restrict__ part_stat) {
+  using C = Cfg<D, BR, BC, KRED, MODE, NG>;
+  constexpr bool FUSED = C::FUSED, GROUPED = C::GROUPED;
   constexpr float kSumTrigger = (BC / 2) * 256.0f;   // BC/2 keys per lane and tile, each at most 2^kTau
-  using kx8 = typename std::conditional<DISTR, f16x8, bf16x8>::type;
+  using kx8 = typename std::conditional<FUSED, f16x8, bf16x8>::type;
   // Kx and V tiles are double-buffered: while tile i multiplies, tile i+1 (V) / i+2 (K) lands.
   // Each buffer is a separate LDS object: the compiler can then tell that the operand reads of
   // one buffer do not depend on the direct loads still in flight into the other.
@@ -165,7 +178,8 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
   const int hh = lane >> 5;   // which half of each 8-wide contraction chunk this lane feeds
 
   // Workgroup -> (batch*head, Q block). Consecutive workgroup ids go round-robin over the 8 XCDs.
-  int unit = blockIdx.x;
+  // n_split > 1: the unit's key tiles are dealt out to that many workgroups (below).
+  int unit = n_split > 1 ? (int)blockIdx.x % total_units : (int)blockIdx.x;
   int bh, t;
   if (causal == 2) {
     // Causal blocks differ up to Tq-fold in length. When (nearly) all of them are resident at
@@ -179,7 +193,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
   } else {
     // Each XCD walks a contiguous range of units, so the Q blocks of one head run together
     // and share that XCD's L2 for K and V; the causal blocks of a head longest first.
-    if ((total_units & 7) == 0) unit = (blockIdx.x & 7) * (total_units >> 3) + (blockIdx.x >> 3);
+    if ((total_units & 7) == 0) unit = (unit & 7) * (total_units >> 3) + (unit >> 3);
     bh = unit / Tq;
     t = unit % Tq;
     if (causal) t = Tq - 1 - t;
@@ -193,19 +207,40 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
   const bf16* vh = v + (size_t)(b * Hkv + hk) * Nk * D;
   // N queries against Nk keys; under the causal mask the last query is aligned with the last
   // key: key n is visible to query i iff n <= i + shift.
-  const int shift = Nk - N;
+  int shift = Nk - N;
+
+  int n_end = causal ? min(Nk, r0 + BR + shift) : Nk;
+  int n_tiles = (n_end + BC - 1) / BC;
+  if (n_split > 1) {
+    // This workgroup's share of the tiles: the head's keys from its first tile on become the keys
+    // it knows. It leaves sums relative to its own reference for the combine kernel; a workgroup
+    // without tiles leaves an empty share.
+    const int part = (int)blockIdx.x / total_units;
+    const int t0 = (int)((long long)n_tiles * part / n_split), t1 = (int)((long long)n_tiles * (part + 1) / n_split);
+    part_stat += ((size_t)part * (total_units / Tq) + bh) * N;
+    part_o += ((size_t)part * (total_units / Tq) + bh) * N * D;
+    if (t0 == t1) {
+      for (int i = r0 + tid; i < min(r0 + BR, N); i += C::T) part_stat[i] = f32x2{0.0f, 0.0f};
+      return;
+    }
+    kh += (size_t)t0 * BC * D;
+    vh += (size_t)t0 * BC * D;
+    Nk -= t0 * BC;
+    shift -= t0 * BC;
+    n_tiles = t1 - t0;
+  }
 
   const int qw0 = r0 + wave * 32;              // first query row of this wave
   const int q_abs = qw0 + lq;                  // this lane's query row
   const int q_ld = min(q_abs, N - 1);          // ragged block: load a valid row, never store it
 
-  // distr at d = 64: the Q block first lands in LDS by direct loads, all in flight at once
+  // grouped at d = 64: the Q block first lands in LDS by direct loads, all in flight at once
   // (16-byte chunks, rows past N zero-filled by the range check); the LSH stage and the sampling
   // then read its columns from there. Walking the columns in global memory instead costs the
   // workgroup one memory round trip per 16 rows and another for the sampled columns, which at
   // d = 64, where a block only has a few short tiles of work, is a large part of its lifetime.
   // (At d = 128 the stage is a percent of the block's time and the 32 KB are not spent.)
-  constexpr bool QSTAGE = DISTR && D == 64;
+  constexpr bool QSTAGE = GROUPED && D == 64;
   __shared__ __attribute__((aligned(1024))) char q_stage[QSTAGE ? BR * C::ROWB : 16];
   // The 16-byte chunks of a staged row are exchanged by the row index (chunk ^ ((row >> 1) & 7);
   // two rows of 128 bytes share a line of banks): the sampling reads one column of 32 different
@@ -250,7 +285,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
     static_assert(QBLK % C::NW == 0, "whole blocks per wave");
     stage_q_block(std::integral_constant<int, QBLK / C::NW>(), q_stage);
   }
-  if constexpr (DISTR) {
+  if constexpr (GROUPED) {
     if (perm != nullptr) {
       const size_t pbase = ((size_t)bh * Tq + t) * D;
       // D is a power of two: an out-of-range entry of a caller's table cannot index past a row
@@ -462,7 +497,21 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
   // and re-rounding to bf16 would cost accuracy on rows with close top scores, so there the
   // factor is applied to the float scores, one fused multiply-add per score.
   kx8 qop[C::KSTEPS];
-  if constexpr (DISTR) {
+  if constexpr (MODE == kReplicated) {
+    // Q~: the sampled channel of every channel's group, by way of a map in LDS
+    uint8_t* from_lds = perm_lds + D;
+    const int group = D / n_groups;
+    if (tid < D) from_lds[perm_lds[tid]] = perm_lds[tid / group * group];
+    __syncthreads();
+    const bf16* qrow = qh + (size_t)q_ld * D;
+#pragma unroll
+    for (int s = 0; s < C::KSTEPS; ++s)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int ch = from_lds[16 * s + 8 * hh + j] & (D - 1);
+        qop[s][j] = QSTAGE ? q_staged(wave * 32 + lq, ch) : qrow[ch];
+      }
+  } else if constexpr (FUSED) {
     // (staged block: a row past N reads as zeros and is never stored)
     const bf16* qrow = qh + (size_t)q_ld * D;
 #pragma unroll
@@ -491,9 +540,9 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
   // idx / PPR, idx = tid + u*T: it sums the same piece of the group's G channel rows of K^T
   // (f_src: byte offset of the piece inside the head's K^T, tile 0) and lands in row idx / 8 of
   // K_f^T at the swizzled position (f_dst).
-  int f_src[DISTR ? C::FUSE_OUT : 1][DISTR ? C::G : 1];
-  int f_dst[DISTR ? C::FUSE_OUT : 1];
-  if constexpr (DISTR) {
+  int f_src[FUSED ? C::FUSE_OUT : 1][FUSED ? C::G : 1];
+  int f_dst[FUSED ? C::FUSE_OUT : 1];
+  if constexpr (FUSED) {
 #pragma unroll
     for (int u = 0; u < C::FUSE_OUT; ++u) {
       const int idx = min(tid + u * C::T, NG * C::PPR - 1);
@@ -505,10 +554,8 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
     }
   }
 
-  const int n_end = causal ? min(Nk, r0 + BR + shift) : Nk;
-  const int n_tiles = (n_end + BC - 1) / BC;
   // tiles [0, n_full) need no masking for any row of the block
-  const int n_full = causal ? min(r0 + shift, Nk) / BC : Nk / BC;
+  const int n_full = min(causal ? max(0, min(r0 + shift, Nk)) / BC : Nk / BC, n_tiles);
 
   // ---- tile loads: global -> LDS ---------------------------------------------------------------
   // K and V rows are fetched through buffer descriptors: the per-lane byte offset inside a
@@ -522,12 +569,12 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
   // j*NW + wave of the tile; lane i owns the 16 bytes at offset 16*i of that block, i.e. LDS
   // row (slot / CH), chunk position (slot % CH) with slot = 64*block + i, and fetches the global
   // chunk the swizzle assigns to that position.
-  int dma_k[DISTR ? 1 : C::CPT], dma_v[C::CPT];
+  int dma_k[FUSED ? 1 : C::CPT], dma_v[C::CPT];
 #pragma unroll
   for (int j = 0; j < C::CPT; ++j) {
     const int slot = (j * C::NW + wave) * 64 + lane;
     const int row = slot / C::CH, pc = slot % C::CH;
-    if constexpr (!DISTR) dma_k[j] = row * C::ROWB + (pc ^ (D == 128 ? (row & 15) : ((row >> 1) & 7))) * 16;
+    if constexpr (!FUSED) dma_k[j] = row * C::ROWB + (pc ^ (D == 128 ? (row & 15) : ((row >> 1) & 7))) * 16;
     const int lseg = (pc >> 1) ^ v_swizzle<C::ROWB>(row);
     dma_v[j] = row * C::ROWB + (lseg * 2 + (pc & 1)) * 16;
   }
@@ -546,7 +593,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
 
   // distr: K^T of this kv head, [D channel rows][Npad keys] half.
   const __amdgpu_buffer_rsrc_t kt_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(DISTR ? kt + (size_t)(b * Hkv + hk) * D * Npad : nullptr), 0, (unsigned)D * Npad * 2, 0x00020000);
+      (void*)(FUSED ? kt + (size_t)(b * Hkv + hk) * D * Npad : nullptr), 0, (unsigned)D * Npad * 2, 0x00020000);
   // ---- fusion (Sec. 3.2): K_f^T[j][n] = sum over the group's channels c of K^T[c][n], eight keys
   // at a time with packed half adds (for G* = 2 the sum of two bf16-valued halves is rounded to
   // half once; larger groups add one channel after the other). Every thread loads the 16-byte
@@ -554,10 +601,10 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
   // one tile iteration before it adds them, so the LDS only sees K_f^T (8-16 KB per tile): with
   // the raw tile staged in LDS and summed from there (direct load, 16 KB read, K_f^T written)
   // the kernel was bound by LDS traffic and 2-12 % slower.
-    typedef f16x8 Pieces[DISTR ? C::FUSE_OUT : 1][DISTR ? C::G : 1];
+    typedef f16x8 Pieces[FUSED ? C::FUSE_OUT : 1][FUSED ? C::G : 1];
   Pieces piece;   // the set the main loop carries from one iteration to the next
   auto load_pieces = [&](int tile, Pieces& pc) {
-    if constexpr (DISTR) {
+    if constexpr (FUSED) {
 #pragma unroll
       for (int u = 0; u < C::FUSE_OUT; ++u)
 #pragma unroll
@@ -566,7 +613,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
     }
   };
   auto fuse_pieces = [&](int buf, const Pieces& pc) {   // loaded pieces -> K_f^T in kx_buf(buf)
-    if constexpr (DISTR) {
+    if constexpr (FUSED) {
       char* dst = kx_buf(buf);
 #pragma unroll
       for (int u = 0; u < C::FUSE_OUT; ++u) {
@@ -588,7 +635,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
   // and the row sum relative to it. distr: the negated reference also sits in all 16 registers
   // of neg_ref, which the first MFMA of every score chain takes as its addend, so the
   // accumulators come out as (scaled score - m_ref) and go straight into exp2.
-  constexpr bool PRESCALED = DISTR;
+  constexpr bool PRESCALED = FUSED;
   float nref = 0.0f;
   f32x16 neg_ref;
 #pragma unroll
@@ -597,8 +644,8 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
 
   // LDS byte offsets of this lane's operands inside a buffer.
   // Score product, A operand (exact): row lq (+32 per key block), logical chunk 2*s + hh.
-  int ka_off[DISTR ? 2 * C::MB : C::KSTEPS];
-  if constexpr (DISTR) {
+  int ka_off[FUSED ? 2 * C::MB : C::KSTEPS];
+  if constexpr (FUSED) {
     // K_f^T is read like V: lane addresses group row 8*hh + 4*half + (lane%16)/4 (+16*s), 32-byte
     // segment 2*mb + (lane/16)%2 (keys 32*mb + 16*((lane/16)%2) ..), 8-byte piece lane%4.
     const int r4 = (lane & 15) >> 2;
@@ -633,7 +680,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
 #pragma unroll
       for (int s = 0; s < C::KSTEPS; ++s) {
         kx8 a;
-        if constexpr (DISTR)
+        if constexpr (FUSED)
           a = lds_read_tr_pair<kx8>(base + ka_off[mb * 2] + s * 16 * C::KTROWB,
                                     base + ka_off[mb * 2 + 1] + s * 16 * C::KTROWB);
         else
@@ -732,11 +779,11 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
       // distr: the pieces of K^T(it+2), loaded during the previous iteration, are summed now
       // into the buffer K_f^T(it) has left, and the loads of K^T(it+3) take their registers.
       // Nothing in this iteration depends on the fusion: it runs beside the MFMAs.
-      if constexpr (DISTR) {
+      if constexpr (FUSED) {
         fuse_pieces(par, piece);       // K^T(it+2), loaded during the previous iteration
         load_pieces(it + 3, piece);
       }
-      if constexpr (!DISTR) dma_tile(k_rsrc, it + 2, dma_k, kx_buf(par));
+      if constexpr (!FUSED) dma_tile(k_rsrc, it + 2, dma_k, kx_buf(par));
       dma_tile(v_rsrc, it + 1, dma_v, v_buf(par ^ 1));
     }
     if constexpr (HAS_NEXT) qk(par ^ 1, sn);
@@ -795,7 +842,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
 
   // ---- prologue: tiles 0 (K, V) and 1 (K) into LDS, scores of tile 0 ---------------------------
   dma_tile(v_rsrc, 0, dma_v, v_lds0);
-  if constexpr (DISTR) {
+  if constexpr (FUSED) {
     Pieces first;        // tiles 0 and 1 travel together (registers are plentiful before the loop)
     load_pieces(0, first);
     load_pieces(1, piece);
@@ -818,7 +865,9 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
   apply_mask(0, s0);
   // The first tile sets the reference to its row maximum (key 0 is visible to every row, so the
   // maximum is finite); nothing has been accumulated yet, so nothing is rescaled.
-  shift_reference(tile_max(s0), no, s0, no, s1);
+  // (a row that sees no key of a workgroup's share, whose first tile is then masked, keeps reference 0)
+  const float first_max = tile_max(s0);
+  shift_reference(first_max > -INFINITY ? first_max : 0.0f, no, s0, no, s1);
   // The first iteration refills the buffer of tile 0 (direct load of K(2), or the fusion of
   // K_f^T(2)): every wave must have read its scores of tile 0 out of it first.
   __syncthreads();
@@ -839,6 +888,19 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
 
   // ---- epilogue: O = O_acc / l, bf16, 8-byte stores ---------------------------------------------
   const float l_tot = half_swap_sum(l_run);
+  if (n_split > 1) {
+    if (q_abs < N) {
+      if (hh == 0) part_stat[q_abs] = f32x2{-nref, l_tot};
+      float* prow = part_o + (size_t)q_abs * D;
+#pragma unroll
+      for (int mb = 0; mb < D / 32; ++mb)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4)
+          *(f32x4*)(prow + 32 * mb + 8 * i4 + 4 * hh) =
+              f32x4{oacc[mb][4 * i4], oacc[mb][4 * i4 + 1], oacc[mb][4 * i4 + 2], oacc[mb][4 * i4 + 3]};
+    }
+    return;
+  }
   const float inv = 1.0f / l_tot;
   // row statistics for a backward pass: ln(sum of exp(score)) = ln 2 * (reference + log2(l))
   if (lse && q_abs < N && hh == 0) lse[(size_t)bh * N + q_abs] = 0.6931471805599453f * (__builtin_log2f(l_tot) - nref);
@@ -856,7 +918,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, DISTR, NG>::WAVES_PER
   }
 }
 
-template <int D, int BR, int BC, int KRED, bool DISTR, int NG = KRED>
+template <int D, int BR, int BC, int KRED, int MODE, int NG = KRED>
 hipError_t launch_one(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                       const void* kt, const Problem& pb, hipStream_t stream) {
   const int Tq = (pb.N + BR - 1) / BR;
@@ -867,12 +929,12 @@ hipError_t launch_one(const void* q, const void* k, const void* v, void* o, cons
   // (with more blocks the dispatcher balances by itself and the head-major order fetches half
   // as many bytes from HBM).
   const int causal_mode = pb.causal ? (units <= 8 * 256 ? 2 : 1) : 0;
-  hipLaunchKernelGGL((attn_bf16_kernel<D, BR, BC, KRED, DISTR, NG>), dim3((unsigned)units), dim3(BR * 2), 0,
+  hipLaunchKernelGGL((attn_bf16_kernel<D, BR, BC, KRED, MODE, NG>), dim3((unsigned)(units * pb.n_split)), dim3(BR * 2), 0,
                      stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, perm, (const f16*)kt,
                      (pb.Nk + kKtPad - 1) / kKtPad * kKtPad, pb.H, pb.Hkv, pb.N, pb.Nk, Tq, causal_mode,
                      scale_log2e, (int)units, pb.n_planes, pb.gray_mode, pb.seed, pb.lse,
-                     (DISTR && kt) ? (const char*)kt + kt_copy_bytes(pb.B, pb.Hkv, pb.d, pb.Nk) : nullptr,
-                     DISTR ? pb.perm_w : nullptr);
+                     kt ? (const char*)kt + kt_copy_bytes(pb.B, pb.Hkv, pb.d, pb.Nk) : nullptr,
+                     MODE != kExact ? pb.perm_w : nullptr, pb.n_groups, pb.n_split, pb.part_o, (f32x2*)pb.part_stat);
   return hipGetLastError();
 }
 
@@ -888,18 +950,19 @@ constexpr bool attn_bf16_groups_built(int BC, int d, int n_groups) {
 template <int D, int BR, int BC>
 hipError_t dispatch_kred(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                          const void* kt, const Problem& pb, int distr, hipStream_t stream) {
-  if (!distr) return launch_one<D, BR, BC, D, false>(q, k, v, o, perm, kt, pb, stream);
+  if (!distr) return launch_one<D, BR, BC, D, kExact>(q, k, v, o, nullptr, nullptr, pb, stream);
+  if (!kt) return launch_one<D, BR, BC, D, kReplicated>(q, k, v, o, perm, nullptr, pb, stream);
   switch (pb.n_groups) {   // n_groups = d (groups of one channel) is the exact product: dispatched by the caller
     case 4:                // fewer groups than one MFMA step: contraction zero-padded to 16
-      if constexpr (D == 64 && BC == 64) return launch_one<D, BR, BC, 16, true, 4>(q, k, v, o, perm, kt, pb, stream);
+      if constexpr (D == 64 && BC == 64) return launch_one<D, BR, BC, 16, kFused, 4>(q, k, v, o, perm, kt, pb, stream);
       return hipErrorInvalidValue;
     case 8:
-      if constexpr (BC == 64) return launch_one<D, BR, BC, 16, true, 8>(q, k, v, o, perm, kt, pb, stream);
+      if constexpr (BC == 64) return launch_one<D, BR, BC, 16, kFused, 8>(q, k, v, o, perm, kt, pb, stream);
       return hipErrorInvalidValue;
-    case 16: return launch_one<D, BR, BC, 16, true>(q, k, v, o, perm, kt, pb, stream);
-    case 32: return launch_one<D, BR, BC, 32, true>(q, k, v, o, perm, kt, pb, stream);
+    case 16: return launch_one<D, BR, BC, 16, kFused>(q, k, v, o, perm, kt, pb, stream);
+    case 32: return launch_one<D, BR, BC, 32, kFused>(q, k, v, o, perm, kt, pb, stream);
     case 64:
-      if constexpr (D == 128) return launch_one<D, BR, BC, 64, true>(q, k, v, o, perm, kt, pb, stream);
+      if constexpr (D == 128) return launch_one<D, BR, BC, 64, kFused>(q, k, v, o, perm, kt, pb, stream);
       [[fallthrough]];
     default: return hipErrorInvalidValue;
   }

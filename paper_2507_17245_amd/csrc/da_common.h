@@ -96,6 +96,11 @@ struct Problem {
   float* lse; // optional device [B][H][N]: log-sum-exp of every row's visible scores (natural log)
   uint8_t* perm_w = nullptr;   // optional device [B][H][Tq][d]: where the bf16 attention kernel's own LSH
                                // stage leaves its table
+  // bf16 forward with the key tiles of a Q block dealt out to n_split workgroups: their sums, float
+  // [n_split][B][H][N][d], and (reference, row sum) pairs, float [n_split][B][H][N][2], exp2 domain
+  int n_split = 1;
+  float* part_o = nullptr;
+  float* part_stat = nullptr;
 };
 
 // Launchers (defined next to their kernels). All return hipError_t of the launch.
@@ -104,14 +109,25 @@ hipError_t launch_lsh_group(const void* q, int dtype, const Problem& pb, uint8_t
 // K [B][Hkv][Nk][d] bf16 -> K^T [B][Hkv][d][Npad] half (Npad = Nk rounded up to kKtPad), for the distr path,
 // followed at kt_copy_bytes() by the projection-matrix table (kRtabBytes) for pb's seed, n_planes and Br.
 hipError_t launch_kt_prepass(const void* k, void* kt, const Problem& pb, hipStream_t stream);
-// distr != 0: S^ = Q_r K_f^T with the per-block permutation table `perm` [B][H][Tq][d] and the
-// transposed keys `kt` written by launch_kt_prepass (k itself is then unused; the table behind the
-// copy is used when its header matches the call).
+// distr != 0: S^ with the per-block permutation table `perm` [B][H][Tq][d] (null: grouped in the kernel),
+// as Q_r K_f^T from the transposed keys `kt` written by launch_kt_prepass (k itself is then unused; the
+// table behind the copy is used when its header matches the call), or, without `kt`, as Q~ K^T.
+// With pb.n_split > 1 (never with kt) launch_attn_bf16_combine follows.
 hipError_t launch_attn_bf16(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                             const void* kt, const Problem& pb, int distr, hipStream_t stream);
 hipError_t launch_attn_f32(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                            const Problem& pb, int dtype, int distr, hipStream_t stream);
 bool attn_bf16_supported(const Problem& pb, int distr);
+// The rules of the bf16 forward (attn_bf16.hip): whether S^ is taken as Q~ K^T, and into how many
+// shares the keys of a Q block are cut when the product is that one or the exact one.
+bool attn_bf16_replicated(const Problem& pb);
+int attn_bf16_splits(const Problem& pb, int distr);
+// Few query rows against many keys (decoding): a kernel of its own, with its own number of shares.
+bool attn_bf16_few_rows(const Problem& pb);
+int attn_bf16_few_splits(const Problem& pb);
+hipError_t launch_attn_bf16_few(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
+                                const Problem& pb, int distr, hipStream_t stream);
+hipError_t launch_attn_bf16_combine(void* o, const Problem& pb, hipStream_t stream);
 // Backward in float arithmetic on the vector ALUs (float tensors): dq [B][H][N][d], dk and dv
 // [B][Hkv][Nk][d] from the forward's inputs, its output o, the output gradient dout and the
 // forward's row statistics lse; perm as in launch_attn_f32.

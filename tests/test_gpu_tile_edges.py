@@ -47,3 +47,83 @@ def test_float_backward(d, N, Nk, causal, G):
     for what, g, r in zip(("dq", "dk", "dv"), got, oracle.distr_bwd(q, k, v, dout, U.oracle_params(cfg))):
         err = np.abs(g - r).max()
         assert err <= TOL * max(1.0, np.abs(r).max()), f"{what}: {err:.4g}"
+
+
+# bf16, few query rows against many keys: rows of all query heads of a kv head packed into tiles of 32,
+# key tiles of 64 (d = 64) or 32 (d = 128) dealt out to four waves of each share.
+@pytest.mark.parametrize("base,d", [("llama", 64), ("long", 128)])
+@pytest.mark.parametrize("B,H,Hkv,N,Nk,causal", [(1, 4, 1, 1, 256, True), (2, 8, 2, 3, 300, True), (1, 4, 4, 32, 1000, True), (1, 2, 1, 64, 513, False),
+                                                 (1, 32, 1, 1, 777, True), (1, 12, 2, 17, 4100, True), (3, 2, 2, 5, 16383, False), (300, 1, 1, 2, 320, True)])
+def test_bf16_few_rows(base, d, B, H, Hkv, N, Nk, causal):
+    cfg = W.CONFIGS[base].scaled(B=B, H=H, Hkv=Hkv, N=N, Nk=Nk, Br=64, n_groups=d // 2, causal=causal, recipe="normal")
+    assert cfg.d == d
+    import gpu_util as U
+    print(f"case {cfg}", flush=True)
+    q, k, v = W.make(cfg)
+    p = U.oracle_params(cfg)
+    import torch
+    lse = torch.empty((B, H, N), dtype=torch.float32, device="cuda")
+    o, perm, _ = U.run_gpu(cfg, q, k, v, want_perm_only=True, lse_out=lse)
+    assert np.array_equal(perm, oracle.lsh_group(q, p)[1])
+    U.assert_close(o, oracle.distr_fwd(q, k, v, p), "bf16")
+    tab, _, _ = U.run_gpu(cfg, q, k, v, want_tables=True)      # the LSH kernel's table: the same output
+    assert np.array_equal(tab, o)
+    assert np.abs(lse.cpu().numpy() - oracle.lse(q, k, p)).max() <= 2e-2
+    o, _, _ = U.run_gpu(cfg, q, k, v, distr=False)
+    U.assert_close(o, oracle.exact_fwd(q, k, v, p), "bf16")
+
+
+# bf16, a Q block's keys dealt out to several workgroups (general kernel and combine kernel): ragged last
+# rows and keys, shares that the causal mask leaves empty for some rows, more shares than a block has tiles.
+@pytest.mark.parametrize("base", ["llama", "long"])
+@pytest.mark.parametrize("H,Hkv,N,Nk,Br,causal", [(2, 1, 200, 4099, 128, True), (1, 1, 33, 2100, 64, False), (4, 2, 130, 2500, 64, True), (2, 2, 2300, 2300, 256, True)])
+def test_bf16_key_shares(base, H, Hkv, N, Nk, Br, causal):
+    import torch
+
+    import gpu_util as U
+    cfg = W.CONFIGS[base].scaled(B=1, H=H, Hkv=Hkv, N=N, Nk=Nk, Br=Br, causal=causal, recipe="normal")
+    print(f"case {cfg}", flush=True)
+    q, k, v = W.make(cfg)
+    p = U.oracle_params(cfg)
+    lse = torch.empty((1, H, N), dtype=torch.float32, device="cuda")
+    for distr in (True, False):
+        o, _, _ = U.run_gpu(cfg, q, k, v, distr=distr, lse_out=lse)
+        U.assert_close(o, oracle.distr_fwd(q, k, v, p) if distr else oracle.exact_fwd(q, k, v, p), "bf16")
+        assert np.abs(lse.cpu().numpy() - oracle.lse(q, k, p, distr=distr)).max() <= 2e-2
+
+
+def test_bf16_key_shares_with_little_room():
+    """A caller's workspace that only holds what a call must have: the keys stay together, the result
+    is the same to rounding. Threads on one stream and on several: each call's own result."""
+    import threading
+
+    import torch
+
+    import paper_2507_17245_amd as da
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q = torch.randn((1, 4, 100, 64), generator=gen, device="cuda").bfloat16()
+    k, v = (torch.randn((1, 4, 4096, 64), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    whole = da.make_params(q, k, v, Br=64, causal=True)
+    o = da.distr_attn_exact_fwd_ex(q, k, v, torch.empty_like(q), whole).float()
+    small = torch.empty(256, dtype=torch.uint8, device="cuda")
+    o1 = da.distr_attn_exact_fwd_ex(q, k, v, torch.empty_like(q), da.make_params(q, k, v, Br=64, causal=True, workspace=small)).float()
+    assert (o - o1).abs().max() <= 2.0 ** -7 * o.abs().max()
+    scale = [1.0, 0.5, 2.0, 4.0]
+    vs = [(v * s).contiguous() for s in scale]
+    torch.cuda.synchronize()
+    for shared in (True, False):
+        outs = [[] for _ in scale]
+        streams = [torch.cuda.Stream()] * 4 if shared else [torch.cuda.Stream() for _ in scale]
+
+        def work(i):
+            with torch.cuda.stream(streams[i]):
+                params = da.make_params(q, k, vs[i], Br=64, causal=True)
+                for _ in range(8):
+                    outs[i].append(da.distr_attn_exact_fwd_ex(q, k, vs[i], torch.empty_like(q), params))
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+        [t.start() for t in threads]
+        [t.join() for t in threads]
+        torch.cuda.synchronize()
+        for i, s in enumerate(scale):
+            for x in outs[i]:
+                assert torch.equal(x.float(), o * s)     # powers of two scale every step exactly
