@@ -80,8 +80,9 @@ typedef struct {
                            Calls with few query rows deal their keys out to several workgroups
                            and sum up in the rest of a workspace of distr_attn_workspace_bytes(), or, with
                            none, in a library-owned buffer per device and stream (32 MB, for up to
-                           16 streams, kept until distr_attn_release); without either they run
-                           undivided. Never refused for it.                                         */
+                           16 streams, kept until distr_attn_release; not under capture and not on
+                           the per-thread default stream); without either they run undivided.
+                           Never refused for it.                                                    */
   size_t workspace_bytes;
   uint8_t *perm_out;    /* optional device [B][H][Tq][d]: channel at sorted position s of each block */
   uint32_t *hash_out;   /* optional device [B][H][Tq][d]: hash of each channel of each block          */

@@ -31,7 +31,9 @@ std::vector<void*> g_ws_retired[kMaxDevices];
 // table of a LSH stage of their own): one buffer per device and stream, so that calls on different
 // streams do not meet in it; the lock is held from the first launch that writes it to the last that reads
 // it, so that calls of several threads on one stream do not interleave. At most kMaxShareBuffers streams
-// of a device get one: later streams, and a stream under capture that has none yet, go without the split.
+// of a device get one. Later streams go without the split, and so do a stream under capture (its graph may
+// be replayed on any stream, beside calls on this one) and the per-thread default stream (one handle,
+// but a stream of its own in every thread).
 constexpr int kMaxShareBuffers = 16;
 constexpr size_t kShareBytes = (size_t)32 << 20;
 struct ShareBuffer {
@@ -164,16 +166,27 @@ size_t share_bytes(const Resolved& r, int n) {
 char* share_buffer(hipStream_t stream) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
-  for (const ShareBuffer& x : g_shares[dev])
-    if (x.stream == stream) return (char*)x.ptr;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (g_shares[dev].size() >= kMaxShareBuffers || hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
-    return nullptr;
-  void* ptr = nullptr;
-  if (hipMalloc(&ptr, kShareBytes) != hipSuccess) {
+  if (stream == hipStreamPerThread) return nullptr;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
     (void)hipGetLastError();
     return nullptr;
   }
+  if (cap != hipStreamCaptureStatusNone) return nullptr;
+  for (const ShareBuffer& x : g_shares[dev])
+    if (x.stream == stream) return (char*)x.ptr;
+  if (g_shares[dev].size() >= kMaxShareBuffers) return nullptr;
+  // (relaxed: another thread's capture in global mode must not be broken by this allocation)
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  void* ptr = nullptr;
+  const hipError_t e = hipMalloc(&ptr, kShareBytes);
+  if (e != hipSuccess) (void)hipGetLastError();
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) return nullptr;
   g_shares[dev].push_back(ShareBuffer{stream, ptr});
   return (char*)ptr;
 }

@@ -127,3 +127,41 @@ def test_bf16_key_shares_with_little_room():
         for i, s in enumerate(scale):
             for x in outs[i]:
                 assert torch.equal(x.float(), o * s)     # powers of two scale every step exactly
+
+
+def test_bf16_key_shares_under_capture():
+    """A captured call without a workspace uses no library-owned buffer: graphs captured on one stream replay
+    on different streams at once, each with its own result, beside eager calls on the capture stream."""
+    import torch
+
+    import paper_2507_17245_amd as da
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    q = torch.randn((1, 4, 100, 64), generator=gen, device="cuda").bfloat16()
+    k, v = (torch.randn((1, 4, 4096, 64), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    scale = [1.0, 0.5, 2.0]
+    vs, outs = [(v * s).contiguous() for s in scale], [torch.empty_like(q) for _ in scale]
+    side = torch.cuda.Stream()
+
+    def call(i, o):
+        return da.distr_attn_exact_fwd_ex(q, k, vs[i], o, da.make_params(q, k, vs[i], Br=64, causal=True))
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        eager = call(0, torch.empty_like(q))     # the capture stream has a buffer before the captures
+    torch.cuda.synchronize()
+    graphs = [torch.cuda.CUDAGraph() for _ in scale]
+    for i, g in enumerate(graphs):
+        with torch.cuda.graph(g, stream=side):
+            call(i, outs[i])
+    streams = [torch.cuda.Stream() for _ in scale]
+    torch.cuda.synchronize()
+    for _ in range(4):
+        for s, g in zip(streams, graphs):
+            with torch.cuda.stream(s):
+                g.replay()
+        with torch.cuda.stream(side):
+            again = call(0, torch.empty_like(q))
+        torch.cuda.synchronize()
+        assert torch.equal(again, eager)
+        for i, s in enumerate(scale):
+            assert torch.equal(outs[i].float(), outs[0].float() * s)      # powers of two scale every step exactly
+            assert (outs[i].float() - eager.float() * s).abs().max() <= 2.0 ** -7 * s * eager.float().abs().max()
