@@ -13,7 +13,7 @@
 // sum over each group's members for dQ. P = exp(S^ - lse) is rebuilt from the forward's row
 // statistics, dP = dO V^T, D_i = sum_c dO_ic O_ic, dS = P o (dP - D), dV = P^T dO.
 //
-//   bwd_prepare_kernel  D_i and lse * log2(e) for every row; Q~ (DistrAttention only) into scratch
+//   bwd_prepare_kernel  -D_i and lse * log2(e) for every row; Q~ (DistrAttention only) into scratch
 //   bwd_dq_kernel       one workgroup per 128 query rows, lane = query row; K and V tiles of 64
 //                       rows stream through LDS:  S^T = K Q~^T, dP^T = V dO^T, dQ~^T += K^T dS^T
 //   bwd_dkv_kernel      one workgroup per 128 keys of a kv head, lane = key; Q~ and dO tiles of 64
@@ -143,6 +143,27 @@ __device__ inline void read_transposed(const char* tile, int blk, const OperandO
     }
 }
 
+// Which (head, tile) a workgroup takes: `tile` counts from the longest causal tile on. Consecutive
+// workgroup ids go round-robin over the 8 XCDs.
+//   kHeadMajor     every XCD walks a contiguous range of units: the tiles of a head share its L2.
+//   kLongestFirst  (causal, at most kBalancedUnits) tile by tile over all heads. Causal tiles differ up to
+//                  Tw-fold in length; with (nearly) all of them resident at once, head after head leaves compute
+//                  units with only long or only short ones. A head still stays on one XCD when the head count
+//                  is a multiple of 8.
+enum UnitOrder { kHeadMajor, kLongestFirst };
+constexpr int kBalancedUnits = 8 * 256;
+__device__ inline void unit_of(int id, int units, int Tw, int order, int& head, int& tile) {
+  if (order == kLongestFirst) {
+    const int heads = units / Tw;
+    tile = id / heads;
+    head = id % heads;
+  } else {
+    if ((units & 7) == 0) id = (id & 7) * (units >> 3) + (id >> 3);
+    head = id / Tw;
+    tile = id % Tw;
+  }
+}
+
 // nothing moves across: operand reads issued before it stay ahead of the MFMAs behind it
 __device__ inline void fence() { __builtin_amdgcn_sched_barrier(0); }
 
@@ -157,7 +178,7 @@ __device__ inline void zero(f32x16& x) {
 }  // namespace
 
 // ------------------------------------------------------------------------------------------------
-// D_i = sum_c dO_ic O_ic and lse_i * log2(e) for every query row; for DistrAttention also Q~:
+// -D_i, D_i = sum_c dO_ic O_ic, and lse_i * log2(e) for every query row; for DistrAttention also Q~:
 // channel c of a row takes the value of the first channel (sorted order) of c's group in the
 // row's Q block.
 template <int D>
@@ -195,7 +216,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_prepare_kernel(
 #pragma unroll
     for (int m = 1; m < CH; m <<= 1) acc += __shfl_xor(acc, m);
     if (on && chunk == 0) {
-      delta[bh * N + r0 + row] = acc;
+      delta[bh * N + r0 + row] = -acc;
       lse2[bh * N + r0 + row] = lse[bh * N + r0 + row] * kLog2e;
     }
     if (perm) {
@@ -218,7 +239,7 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(
     const bf16* __restrict__ qrep, const bf16* __restrict__ k, const bf16* __restrict__ v,
     const bf16* __restrict__ dout, const float* __restrict__ lse2p, const float* __restrict__ delta,
     bf16* __restrict__ dq, const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Br, int Tq,
-    int Tw, int n_groups, int causal, float scale) {
+    int Tw, int n_groups, int causal, int order, float scale) {
   constexpr int CH = D / 8;
   constexpr int KS = D / 16;    // MFMA steps over the channels
   constexpr int CB = D / 32;    // 32-channel blocks of the dQ~ accumulator
@@ -234,9 +255,10 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int lq = lane & 31, hh = lane >> 5;
-  // causal: the blocks with the most keys first
-  const int t = causal ? Tw - 1 - (int)(blockIdx.x % Tw) : (int)(blockIdx.x % Tw);
-  const size_t bh = blockIdx.x / Tw;
+  int head, t;
+  unit_of((int)blockIdx.x, (int)gridDim.x, Tw, order, head, t);
+  if (causal) t = Tw - 1 - t;   // the blocks with the most keys first
+  const size_t bh = head;
   const int b = (int)(bh / H), h = (int)(bh % H);
   const int hk = h / (H / Hkv);
   const int r0 = t * kBwdRows;
@@ -270,7 +292,11 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(
     doop[s] = __builtin_bit_cast(bf16x8, y);
   }
   const float lse2 = active ? lse2p[bh * N + q_abs] : 0.0f;
+  // dP^T accumulates from -D on (the products' addend, held in 16 registers: no subtraction per score)
   const float dl = active ? delta[bh * N + q_abs] : 0.0f;
+  f32x16 neg_d;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) neg_d[i] = dl;
   const int lim = causal ? min(q_abs + shift, Nk - 1) : Nk - 1;   // last key this row sees
 
   f32x16 dqacc[CB];
@@ -288,7 +314,7 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(
       for (int i = 0; i < 16; ++i) pv[i] = kv0 + acc_row(i, hh) <= lim ? pv[i] : 0.0f;
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) dsop[i >> 3][i & 7] = (bf16)(pv[i] * (dpacc[i] - dl));
+    for (int i = 0; i < 16; ++i) dsop[i >> 3][i & 7] = (bf16)(pv[i] * dpacc[i]);
   };
   auto dq_update = [&](const bf16x8 (&at)[CB][2], const bf16x8 (&dsop)[2]) {
 #pragma unroll
@@ -321,7 +347,7 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(
       bf16x8 ak[HB], av[HB], at[CB][2], ds[2];
       f32x16 sacc, dpacc;
       zero(sacc);
-      zero(dpacc);
+      dpacc = neg_d;
 #pragma unroll
       for (int h0 = 0; h0 < KS; h0 += HB) {
 #pragma unroll
@@ -428,7 +454,7 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
     const bf16* __restrict__ qrep, const bf16* __restrict__ k, const bf16* __restrict__ v,
     const bf16* __restrict__ dout, const float* __restrict__ lse2p, const float* __restrict__ delta,
     bf16* __restrict__ dk, bf16* __restrict__ dv, float* __restrict__ part, int hsplit, int H, int Hkv, int N,
-    int Nk, int Tw, int causal, float scale) {
+    int Nk, int Tw, int causal, int order, float scale) {
   constexpr int KS = D / 16;
   constexpr int CB = D / 32;
   constexpr int TILE = kBwdStream * D * 2;
@@ -445,9 +471,10 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
   const int lq = lane & 31, hh = lane >> 5;
   // hsplit > 1: the query heads of the kv head are dealt out to hsplit workgroups, which leave
   // float partial sums in `part` for the reduction kernel
-  const int hs = blockIdx.x % hsplit;
-  const int t = (blockIdx.x / hsplit) % Tw;
-  const size_t bk = blockIdx.x / hsplit / Tw;   // b * Hkv + hk
+  int head, t;   // (kv head, share of its query heads); causal: the first keys are seen by the most rows
+  unit_of((int)blockIdx.x, (int)gridDim.x, Tw, order, head, t);
+  const int hs = head % hsplit;
+  const size_t bk = head / hsplit;              // b * Hkv + hk
   const int b = (int)(bk / Hkv), hk = (int)(bk % Hkv);
   const int rep = H / Hkv / hsplit;             // query heads of this workgroup
   const int n0 = t * kBwdRows;
@@ -514,17 +541,23 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
     // block sits next to the matrix work of the other one.
     bf16x8 ar[KS], at[CB][2], pop0[2], ds0[2], pop1[2], ds1[2];
     f32x16 s0, p0, s1, p1;
-    f32x4 l4[4], d4[4];
+    f32x4 l4[4];
     auto product = [&](const bf16x8 (&b)[KS], f32x16& acc) {
-      zero(acc);
 #pragma unroll
       for (int s = 0; s < KS; ++s) acc = mfma(ar[s], b[s], acc);
     };
-    auto read_stats = [&](int qb) {
+    // a block's row statistics come in the accumulator's order: lse for the exponent, -D straight into the
+    // accumulator of dP
+    auto read_lse = [&](int qb) {
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) l4[i4] = *(const f32x4*)&lse_lds[32 * qb + 8 * i4 + 4 * hh];
+    };
+    auto read_neg_d = [&](int qb, f32x16& acc) {
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
-        l4[i4] = *(const f32x4*)&lse_lds[32 * qb + 8 * i4 + 4 * hh];
-        d4[i4] = *(const f32x4*)&dl_lds[32 * qb + 8 * i4 + 4 * hh];
+        const f32x4 x = *(const f32x4*)&dl_lds[32 * qb + 8 * i4 + 4 * hh];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[4 * i4 + e] = x[e];
       }
     };
     auto p_ds_operands = [&](const f32x16& sacc, const f32x16& dpacc, int qb, bf16x8 (&pop)[2], bf16x8 (&dsop)[2]) {
@@ -542,7 +575,7 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         pop[i >> 3][i & 7] = (bf16)pv[i];
-        dsop[i >> 3][i & 7] = (bf16)(pv[i] * (dpacc[i] - d4[i >> 2][i & 3]));
+        dsop[i >> 3][i & 7] = (bf16)(pv[i] * dpacc[i]);
       }
     };
     auto update = [&](const bf16x8 (&b)[2], f32x16 (&acc)[CB]) {
@@ -551,17 +584,21 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt) acc[cb] = mfma(at[cb][tt], b[tt], acc[cb]);
     };
+    zero(s0);
+    zero(s1);
     read_rows<D>(q_lds, 0, off, ar);
     fence();
     product(kop, s0);
     read_rows<D>(do_lds, 0, off, ar);
+    read_neg_d(0, p0);
     fence();
     product(vop, p0);
     read_rows<D>(q_lds, 1, off, ar);
-    read_stats(0);
+    read_lse(0);
     fence();
     product(kop, s1);
     read_rows<D>(do_lds, 1, off, ar);
+    read_neg_d(1, p1);
     fence();
     product(vop, p1);
     p_ds_operands(s0, p0, 0, pop0, ds0);
@@ -569,7 +606,7 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
     fence();
     update(pop0, dvacc);
     read_transposed<D>(q_lds, 0, off, at);
-    read_stats(1);
+    read_lse(1);
     fence();
     update(ds0, dkacc);
     p_ds_operands(s1, p1, 1, pop1, ds1);
@@ -698,16 +735,18 @@ hipError_t launch_attn_bf16_bwd(const void* q, const void* k, const void* v, con
   const uint8_t* table = distr ? perm : nullptr;
   const bf16* qx = distr ? qrep : (const bf16*)q;
   const int n_groups = distr ? pb.n_groups : pb.d;
+  const int dq_order = pb.causal && q_units <= kBalancedUnits ? kLongestFirst : kHeadMajor;
+  const int dkv_order = pb.causal && k_units * hsplit <= kBalancedUnits ? kLongestFirst : kHeadMajor;
 #define DA_BWD(DD)                                                                                                   \
   do {                                                                                                               \
     hipLaunchKernelGGL((bwd_prepare_kernel<DD>), dim3((unsigned)prep_units), dim3(kBwdThreads), 0, stream,           \
                        (const bf16*)q, (const bf16*)o, (const bf16*)dout, lse, table, qrep, delta, lse2, pb.N, pb.Br, Tq, n_groups); \
     hipLaunchKernelGGL((bwd_dq_kernel<DD>), dim3((unsigned)q_units), dim3(kBwdThreads), 0, stream, qx, (const bf16*)k, \
                        (const bf16*)v, (const bf16*)dout, lse2, delta, (bf16*)dq, table, pb.H, pb.Hkv, pb.N, pb.Nk,   \
-                       pb.Br, Tq, Twq, n_groups, pb.causal, pb.scale);                                               \
+                       pb.Br, Tq, Twq, n_groups, pb.causal, dq_order, pb.scale);                                               \
     hipLaunchKernelGGL((bwd_dkv_kernel<DD>), dim3((unsigned)(k_units * hsplit)), dim3(kBwdThreads), 0, stream, qx,   \
                        (const bf16*)k, (const bf16*)v, (const bf16*)dout, lse2, delta, (bf16*)dk, (bf16*)dv, part,    \
-                       hsplit, pb.H, pb.Hkv, pb.N, pb.Nk, Twk, pb.causal, pb.scale);                                 \
+                       hsplit, pb.H, pb.Hkv, pb.N, pb.Nk, Twk, pb.causal, dkv_order, pb.scale);                                 \
     if (hsplit > 1)                                                                                                  \
       hipLaunchKernelGGL(bwd_reduce_kernel, dim3((unsigned)((2 * kv_elems / 4 + 255) / 256)), dim3(256), 0, stream,  \
                          part, (bf16*)dk, (bf16*)dv, kv_elems, hsplit);                                              \
