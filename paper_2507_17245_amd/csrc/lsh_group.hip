@@ -1,136 +1,273 @@
-// LSH hash-and-group kernel (arXiv 2507.17245, Sec. 3.2 "similar columns identification" and
-// Fig. 5; once per Q block as in Sec. 3.3).
+// LSH hash-and-group kernel (arXiv 2507.17245, Sec. 3.2 "similar columns identification" and Fig. 5; once per
+// block as in Sec. 3.3). One workgroup per (batch, head, block of rows).
 //
-// One workgroup per (batch, head, Q block). For every channel column of the block:
-//   projection onto n_planes random directions -> sign bits -> Gray map -> integer hash;
-// then the d hashes are ranked (ascending, ties by channel index) and the inverse of the rank
-// is written as the block's channel permutation.
+// For every channel column of the block: projection onto n_planes random directions -> sign bits -> Gray
+// map -> integer hash; then the d hashes are ranked (ascending, ties by channel index) and the inverse of
+// the rank is the block's channel permutation.
 //
-// The sign of a projection decides an integer, so the sum is taken in a fixed order that a CPU
-// can repeat bit for bit: float, one fused multiply-add per row, rows ascending, starting at +0.
-// That is why this stage runs on the vector ALUs and not on the matrix cores, although the
-// paper picked N' = 16 with tensor cores in mind.
+// The sign of a projection decides an integer, so its sum has a defining order that a CPU can repeat bit for
+// bit: float, one fused multiply-add per row, rows ascending, starting at +0.
+//
+// Bound: the latency of reading the block (there are often fewer blocks than compute units). All of its rows
+// are asked for at once by direct global->LDS loads, and the projection table is generated while they travel.
+//   bf16   the projections are taken on the matrix pipe, from R split into two bf16 pieces (an entry is an integer of
+//          17 bits times 2^-16: r1 = R rounded to bf16 and r2 = R - r1 hold it exactly), next to sum |q| |r1|,
+//          which bounds how far that sum can be from the defining one; only sums inside the bound are
+//          taken again the defining way.
+//   float  the defining sums on the vector ALUs, from LDS.
+// Measured (rows walked column by column in global memory, four at a time | now): bf16 H16 N200 d128 Br128
+// 21.5 | 9.8 us, float H8 N2048 d64 Br128 13.8 | 5.7 us, float H8 N2048 d64 blocks of 64 rows 6.4 | 4.9 us.
 #include "da_common.h"
 
 namespace da {
 
 constexpr int kLshThreads = 256;
-constexpr int kMaxLshRows = 256;   // largest block the stage hashes (Q blocks up to 256 rows, K blocks up to 128)
 
-template <typename T>
-__device__ inline float to_float(T x);
-template <>
-__device__ inline float to_float<float>(float x) { return x; }
-template <>
-__device__ inline float to_float<bf16>(bf16 x) { return (float)x; }
+// LDS of one workgroup
+template <typename T, int D, int BR>
+struct LshLds {
+  static constexpr bool MATRIX = sizeof(T) == 2;
+  static constexpr int CR = MATRIX || BR < 128 ? BR : 128;   // rows staged at a time
+  static constexpr int RPAD = BR + 8;                        // bf16 pieces: 16 lanes read 16 rows of the table at once
+  __attribute__((aligned(1024))) char rows[CR * D * sizeof(T)];
+  __attribute__((aligned(16))) char table[MATRIX ? 2 * 16 * RPAD * 2 : BR * 16 * 4];
+  __attribute__((aligned(16))) uint32_t code[D];
+  __attribute__((aligned(16))) uint32_t hash[D];
+  uint8_t perm[D];
+};
 
-// Accumulate JMAX planes for one channel over the block's rows.
-template <typename T, int D, int JMAX>
-__device__ inline uint32_t project_bits(const T* __restrict__ qcol, int rows, const float* R_lds,
-                                        int pg, int n_planes) {
-  constexpr int NPG = kLshThreads / D;
-  float acc[JMAX];
-#pragma unroll
-  for (int j = 0; j < JMAX; ++j) acc[j] = 0.0f;
-  const float* Rt = R_lds + pg * (kMaxPlanes / NPG);
-#pragma unroll 4
-  for (int r = 0; r < rows; ++r) {
-    float x = to_float<T>(qcol[(size_t)r * D]);
-#pragma unroll
-    for (int j = 0; j < JMAX; ++j) acc[j] = __builtin_fmaf(x, Rt[r * kMaxPlanes + j], acc[j]);
+// Position of a 16-byte chunk inside its staged bf16 row: the transposing reads address, per 32 lanes, the same
+// two chunks of rows r..r+3 and r+8..r+11, which this spreads over all banks.
+template <int D>
+__device__ inline int lsh_chunk_swz(int row) {
+  return D == 128 ? (((row & 3) | ((row >> 1) & 4)) << 1) : ((((row >> 1) & 1) | ((row >> 2) & 2)) << 1);
+}
+
+// Rows r0 .. of `block` (`rows` of them exist, the rest reads as zeros) into LDS.
+template <typename T, int D, int CR, bool SWZ>
+__device__ inline void lsh_stage_rows(const T* block, int rows, int r0, char* dst) {
+  typedef __attribute__((address_space(3))) void lds_void;
+  constexpr int CH = D * (int)sizeof(T) / 16, N = CR * CH / kLshThreads;
+  static_assert(CR * CH % kLshThreads == 0, "whole loads per thread");
+  if (((uintptr_t)block & 15) != 0) {   // (a tensor of the stand-alone entry, which asks for no alignment)
+    for (int i = threadIdx.x; i < CR * D; i += kLshThreads) {
+      const int row = i / D, at = i % D * (int)sizeof(T), chunk = at / 16;
+      *(T*)(dst + row * (D * (int)sizeof(T)) + (SWZ ? chunk ^ lsh_chunk_swz<D>(row) : chunk) * 16 + at % 16) =
+          r0 + row < rows ? block[(size_t)(r0 + row) * D + i % D] : (T)0.0f;
+    }
+    return;
   }
-  uint32_t bits = 0;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)block, 0, (unsigned)rows * D * sizeof(T), 0x00020000);
 #pragma unroll
-  for (int j = 0; j < JMAX; ++j) {
-    int p = j * NPG + pg;  // plane handled in slot j of this thread
-    if (p < n_planes && acc[j] > 0.0f) bits |= 1u << (n_planes - 1 - p);  // plane 0 = top bit
+  for (int j = 0; j < N; ++j) {
+    const int blk = j * (kLshThreads / 64) + wave, slot = blk * 64 + lane;
+    const int row = slot / CH, pc = slot % CH;
+    const int chunk = SWZ ? pc ^ lsh_chunk_swz<D>(row) : pc;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + blk * 1024), 16, row * (D * (int)sizeof(T)) + chunk * 16,
+                                             r0 * (D * (int)sizeof(T)), 0, 0);
   }
-  return bits;
+}
+
+// Sign codes of the bf16 block's channels, projections p0 .. p0 + 15, into lds.code.
+template <int D, int BR>
+__device__ inline void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int p0, int n_planes) {
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  constexpr int RPAD = LshLds<bf16, D, BR>::RPAD, ROWB = D * 2;
+  const bf16* rp1 = (const bf16*)lds.table;
+  const bf16* rp2 = rp1 + 16 * RPAD;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int np = min(16, n_planes - p0);
+  // v_mfma_f32_16x16x32_bf16: 16 channels x 16 projections per product, 32 rows of the block per step;
+  // lane = (projection pl16 = lane % 16, row group kg = lane / 16) on the R side and (channel, row
+  // group) on the Q side, whose operand comes out of the staged block by transposing reads. Register i of
+  // the result belongs to channel 16*ct + 4*kg + i and projection pl16.
+  const int pl16 = lane & 15, kg = lane >> 4;
+  // The sign of a sum is taken from the matrix pipe only if the sum is further from zero than both
+  // roundings can reach, each relative to sum |q| |R| <= (1 + 2^-8) sum |q| |r1|: the pipe's, at most
+  // 2*BR products and BR/16 chained accumulators added in any order with any rounding direction
+  // (2 * (2*BR + BR/16) * 2^-24), and the defining chain's, BR fused multiply-adds (BR * 2^-24).
+  // The absolute term covers products flushed to zero.
+  constexpr float kDoubt = 3.1e-7f * BR, kTiny = 1e-30f;
+  for (int ct = wave; ct < D / 16; ct += kLshThreads / 64) {
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f}, bnd = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int ks = 0; ks < BR / 32; ++ks) {
+      const int row0 = 32 * ks + 8 * kg + (pl16 >> 2), row1 = row0 + 4;
+      const int chunk = 2 * ct + ((pl16 & 3) >> 1), inch = 8 * (pl16 & 1);
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds.rows + row0 * ROWB + ((chunk ^ lsh_chunk_swz<D>(row0)) << 4) + inch));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds.rows + row1 * ROWB + ((chunk ^ lsh_chunk_swz<D>(row1)) << 4) + inch));
+      const s16x8 a = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      const s16x8 b1 = *(const s16x8*)&rp1[pl16 * RPAD + 32 * ks + 8 * kg];
+      const s16x8 b2 = *(const s16x8*)&rp2[pl16 * RPAD + 32 * ks + 8 * kg];
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b1), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b2), acc, 0, 0, 0);
+      bnd = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a & (short)0x7fff),
+                                                    __builtin_bit_cast(bf16x8, b1 & (short)0x7fff), bnd, 0, 0, 0);
+    }
+    bool positive[4], doubt[4], any_doubt = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      positive[i] = acc[i] > 0.0f;
+      doubt[i] = pl16 < np && !(__builtin_fabsf(acc[i]) > kDoubt * bnd[i] + kTiny);
+      any_doubt |= doubt[i];
+    }
+    if (__builtin_amdgcn_ballot_w64(any_doubt) != 0) {
+      // the defining sums of this lane's four channels, an 8-byte piece of every staged row
+      float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      const int ch0 = 16 * ct + 4 * kg;
+      const char* col = lds.rows + (ch0 & 7) * 2;
+      for (int r8 = 0; r8 < BR; r8 += 8) {
+#pragma unroll
+        for (int j8 = 0; j8 < 8; ++j8) {
+          const s16x4 x4 = *(const s16x4*)(col + (r8 + j8) * ROWB + (((ch0 >> 3) ^ lsh_chunk_swz<D>(r8 + j8)) << 4));
+          const float rv = (float)rp1[pl16 * RPAD + r8 + j8] + (float)rp2[pl16 * RPAD + r8 + j8];   // exact
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            sum[i] = __builtin_fmaf(__builtin_bit_cast(float, (uint32_t)(uint16_t)x4[i] << 16), rv, sum[i]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (doubt[i]) positive[i] = sum[i] > 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      // lanes 16*kg .. 16*kg + 15 of the ballot are the projections of channel 16*ct + 4*kg + i; projection 0
+      // is the top bit of the n_planes-bit code
+      const uint64_t signs = __builtin_amdgcn_ballot_w64(positive[i]);
+      if (pl16 == 0) {
+        const uint32_t bits = __builtin_bitreverse32((uint32_t)(signs >> (16 * kg)) & 0xffffu) >> (32 - np);
+        const uint32_t before = p0 ? lds.code[16 * ct + 4 * kg + i] : 0;
+        lds.code[16 * ct + 4 * kg + i] = before | bits << (n_planes - p0 - np);
+      }
+    }
+  }
+}
+
+// `rows` rows of D channels at `block`; perm and hash (either may be null): the block's table entries.
+template <typename T, int D, int BR>
+__device__ inline void lsh_block(const T* __restrict__ block, int rows, int n_planes, int gray_mode, uint64_t seed,
+                                 uint8_t* __restrict__ perm, uint32_t* __restrict__ hash, LshLds<T, D, BR>& lds) {
+  using L = LshLds<T, D, BR>;
+  constexpr int NPG = kLshThreads / D;        // threads per channel
+  const int tid = threadIdx.x, c = tid % D, pg = tid / D;
+  for (int p0 = 0; p0 < n_planes; p0 += 16) {
+    if constexpr (L::MATRIX) {
+      if (p0 == 0) lsh_stage_rows<T, D, BR, true>(block, rows, 0, lds.rows);
+      else __syncthreads();                   // the last table is no longer read
+      bf16* rp1 = (bf16*)lds.table;
+      bf16* rp2 = rp1 + 16 * L::RPAD;
+      for (int i = tid; i < BR * 16; i += kLshThreads) {
+        const int r = i % BR, pl = i / BR;
+        const float rv = p0 + pl < n_planes ? hyperplane_entry(seed, (uint32_t)(p0 + pl), (uint32_t)r) : 0.0f;
+        const bf16 r1 = (bf16)rv;
+        rp1[pl * L::RPAD + r] = r1;
+        rp2[pl * L::RPAD + r] = (bf16)(rv - (float)r1);
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      lsh_codes_matrix<D, BR>(lds, p0, n_planes);
+    } else {
+      constexpr int PPT = 16 / NPG;           // projections per thread: pg*PPT .. pg*PPT + PPT - 1
+      float* R = (float*)lds.table;           // [row][16]
+      float acc[PPT];
+#pragma unroll
+      for (int j = 0; j < PPT; ++j) acc[j] = 0.0f;
+      for (int r0 = 0; r0 < BR; r0 += L::CR) {
+        if (p0 + r0 > 0) __syncthreads();     // the staged rows are no longer read
+        lsh_stage_rows<T, D, L::CR, false>(block, rows, r0, lds.rows);
+        if (r0 == 0) {
+          for (int i = tid; i < BR * 16; i += kLshThreads)
+            R[i] = p0 + (i & 15) < n_planes ? hyperplane_entry(seed, (uint32_t)(p0 + (i & 15)), (uint32_t)(i >> 4)) : 0.0f;
+          if (p0 == 0 && tid < D) lds.code[tid] = 0;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        const float* x = (const float*)lds.rows + c;
+        const float* Rt = R + r0 * 16 + pg * PPT;
+        const int n = min(L::CR, rows - r0);
+#pragma unroll 8
+        for (int r = 0; r < n; ++r) {
+          const float xr = x[r * D];
+#pragma unroll
+          for (int j = 0; j < PPT; ++j) acc[j] = __builtin_fmaf(xr, Rt[r * 16 + j], acc[j]);
+        }
+      }
+      uint32_t bits = 0;
+#pragma unroll
+      for (int j = 0; j < PPT; ++j) {
+        const int p = p0 + pg * PPT + j;
+        if (p < n_planes && acc[j] > 0.0f) bits |= 1u << (n_planes - 1 - p);   // projection 0 = top bit
+      }
+      if (bits) atomicOr(&lds.code[c], bits);
+    }
+  }
+  __syncthreads();
+  if (tid < D) {
+    const uint32_t h = lsh_hash_of_code(lds.code[tid], gray_mode);
+    lds.hash[tid] = h;
+    lds.code[tid] = 0;   // from here on the channel's rank is counted in this word
+    if (hash) hash[tid] = h;
+  }
+  __syncthreads();
+  // Rank by counting = stable ascending sort; perm = inverse of the rank. Every thread counts a slice of
+  // the other channels for its own (hashes read four at a time); the slices meet in an integer LDS add.
+  constexpr int SL = D / NPG;
+  const int first = pg * SL;
+  const uint32_t mine = lds.hash[c];
+  uint32_t cnt = 0;
+#pragma unroll
+  for (int o4 = 0; o4 < SL; o4 += 4) {
+    const u32x4 h = *(const u32x4*)&lds.hash[first + o4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) cnt += (h[j] < mine || (h[j] == mine && first + o4 + j < c)) ? 1u : 0u;
+  }
+  if (cnt) atomicAdd(&lds.code[c], cnt);
+  __syncthreads();
+  if (!perm) return;
+  if (tid < D) lds.perm[lds.code[tid]] = (uint8_t)tid;
+  __syncthreads();
+  if (tid < D) perm[tid] = lds.perm[tid];
+}
+
+template <typename T, int D, int BR>
+__global__ __launch_bounds__(kLshThreads) void lsh_group_kernel(
+    const T* __restrict__ q, uint8_t* __restrict__ perm_out, uint32_t* __restrict__ hash_out,
+    int N, int Tq, int n_planes, int gray_mode, uint64_t seed) {
+  __shared__ LshLds<T, D, BR> lds;
+  const int t = blockIdx.x % Tq;
+  const size_t bh = blockIdx.x / Tq;
+  const size_t at = (size_t)blockIdx.x * D;
+  lsh_block<T, D, BR>(q + (bh * N + (size_t)t * BR) * D, min(BR, N - t * BR), n_planes, gray_mode, seed,
+                      perm_out ? perm_out + at : nullptr, hash_out ? hash_out + at : nullptr, lds);
 }
 
 template <typename T, int D>
-__global__ __launch_bounds__(kLshThreads) void lsh_group_kernel(
-    const T* __restrict__ q, uint8_t* __restrict__ perm_out, uint32_t* __restrict__ hash_out,
-    int N, int Br, int Tq, int n_planes, int gray_mode, uint64_t seed) {
-  constexpr int NPG = kLshThreads / D;        // threads per channel, each takes planes p = j*NPG + pg
-  constexpr int PPT = kMaxPlanes / NPG;       // plane slots per thread
-  __shared__ float R_lds[kMaxLshRows * kMaxPlanes];   // [row][pg][j], zero where the plane does not exist
-  __shared__ uint32_t code_lds[D];
-  __shared__ __attribute__((aligned(16))) uint32_t hash_lds[D];
-  __shared__ uint8_t perm_lds[D];
-
-  const int tid = threadIdx.x;
-  const int t = blockIdx.x % Tq;
-  const size_t bh = blockIdx.x / Tq;
-  const int r0 = t * Br;
-  const int rows = min(Br, N - r0);
-
-  for (int i = tid; i < Br * kMaxPlanes; i += kLshThreads) {
-    int r = i / kMaxPlanes, rem = i % kMaxPlanes;
-    int pg = rem / PPT, j = rem % PPT;
-    int p = j * NPG + pg;
-    R_lds[i] = (p < n_planes) ? hyperplane_entry(seed, (uint32_t)p, (uint32_t)r) : 0.0f;
+static hipError_t launch_rows(const T* q, const Problem& pb, uint8_t* perm_out, uint32_t* hash_out, hipStream_t stream) {
+  const int Tq = (pb.N + pb.Br - 1) / pb.Br;
+  const dim3 grid((unsigned)((long long)pb.B * pb.H * Tq)), block(kLshThreads);
+#define DA_LSH(BR)                                                                                                       \
+  hipLaunchKernelGGL((lsh_group_kernel<T, D, BR>), grid, block, 0, stream, q, perm_out, hash_out, pb.N, Tq, pb.n_planes, \
+                     pb.gray_mode, pb.seed)
+  switch (pb.Br) {   // Q blocks of 64, 128, 256 rows, K blocks (mirrored form) of 32, 64, 128
+    case 32: DA_LSH(32); break;
+    case 64: DA_LSH(64); break;
+    case 128: DA_LSH(128); break;
+    case 256: DA_LSH(256); break;
+    default: return hipErrorInvalidValue;
   }
-  if (tid < D) code_lds[tid] = 0;
-  __syncthreads();
-
-  const int c = tid % D;
-  const int pg = tid / D;
-  const T* qcol = q + (bh * N + r0) * D + c;
-  const int slots = (n_planes + NPG - 1) / NPG;
-  uint32_t bits;
-  if (slots <= 4) bits = project_bits<T, D, (PPT < 4 ? PPT : 4)>(qcol, rows, R_lds, pg, n_planes);
-  else if (slots <= 8) bits = project_bits<T, D, (PPT < 8 ? PPT : 8)>(qcol, rows, R_lds, pg, n_planes);
-  else bits = project_bits<T, D, PPT>(qcol, rows, R_lds, pg, n_planes);
-  if (bits) atomicOr(&code_lds[c], bits);
-  __syncthreads();
-
-  if (tid < D) {
-    const uint32_t h = lsh_hash_of_code(code_lds[tid], gray_mode);
-    hash_lds[tid] = h;
-    code_lds[tid] = 0;   // from here on the channel's rank is counted in this word
-    if (hash_out) hash_out[(size_t)blockIdx.x * D + tid] = h;
-  }
-  __syncthreads();
-  {
-    // Rank by counting = stable ascending sort; perm = inverse of the rank. Every thread counts a
-    // slice of the other channels for its own (NPG threads per channel, hashes read four at a
-    // time); the slices meet in an integer LDS add.
-    constexpr int SL = D / NPG;
-    uint32_t* rank_lds = code_lds;
-    const int first = pg * SL;
-    const uint32_t mine = hash_lds[c];
-    uint32_t cnt = 0;
-#pragma unroll
-    for (int o4 = 0; o4 < SL; o4 += 4) {
-      const u32x4 h = *(const u32x4*)&hash_lds[first + o4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) cnt += (h[j] < mine || (h[j] == mine && first + o4 + j < c)) ? 1u : 0u;
-    }
-    if (cnt) atomicAdd(&rank_lds[c], cnt);
-    __syncthreads();
-    if (tid < D) perm_lds[rank_lds[tid]] = (uint8_t)tid;
-  }
-  __syncthreads();
-  if (perm_out && tid < D) perm_out[(size_t)blockIdx.x * D + tid] = perm_lds[tid];
+#undef DA_LSH
+  return hipGetLastError();
 }
 
 hipError_t launch_lsh_group(const void* q, int dtype, const Problem& pb, uint8_t* perm_out,
                             uint32_t* hash_out, hipStream_t stream) {
-  if (pb.Br < 1 || pb.Br > kMaxLshRows) return hipErrorInvalidValue;
-  const int Tq = (pb.N + pb.Br - 1) / pb.Br;
-  const long long units = (long long)pb.B * pb.H * Tq;
-  dim3 grid((unsigned)units), block(kLshThreads);
-#define DA_LSH_LAUNCH(T, DD)                                                                   \
-  hipLaunchKernelGGL((lsh_group_kernel<T, DD>), grid, block, 0, stream, (const T*)q, perm_out, \
-                     hash_out, pb.N, pb.Br, Tq, pb.n_planes, pb.gray_mode, pb.seed)
-  if (dtype == 0 && pb.d == 64) DA_LSH_LAUNCH(bf16, 64);
-  else if (dtype == 0 && pb.d == 128) DA_LSH_LAUNCH(bf16, 128);
-  else if (dtype == 1 && pb.d == 64) DA_LSH_LAUNCH(float, 64);
-  else if (dtype == 1 && pb.d == 128) DA_LSH_LAUNCH(float, 128);
-  else return hipErrorInvalidValue;
-#undef DA_LSH_LAUNCH
-  return hipGetLastError();
+  if (dtype == 0 && pb.d == 64) return launch_rows<bf16, 64>((const bf16*)q, pb, perm_out, hash_out, stream);
+  if (dtype == 0 && pb.d == 128) return launch_rows<bf16, 128>((const bf16*)q, pb, perm_out, hash_out, stream);
+  if (dtype == 1 && pb.d == 64) return launch_rows<float, 64>((const float*)q, pb, perm_out, hash_out, stream);
+  if (dtype == 1 && pb.d == 128) return launch_rows<float, 128>((const float*)q, pb, perm_out, hash_out, stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace da

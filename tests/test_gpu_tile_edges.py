@@ -165,3 +165,30 @@ def test_bf16_key_shares_under_capture():
         for i, s in enumerate(scale):
             assert torch.equal(outs[i].float(), outs[0].float() * s)      # powers of two scale every step exactly
             assert (outs[i].float() - eager.float() * s).abs().max() <= 2.0 ** -7 * s * eager.float().abs().max()
+
+
+# LSH kernel: blocks staged 128 rows at a time (float) or whole (bf16, matrix pipe), 16 projections at a time;
+# a tensor that is not 16-byte aligned takes a path of its own. Tables and hashes to the bit.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,Br", [(64, 64), (64, 256), (128, 64), (128, 128), (128, 256)])
+@pytest.mark.parametrize("N,n_planes,offset", [(1, 16, 0), (65, 3, 0), (257, 17, 0), (300, 32, 1), (129, 16, 1)])
+def test_lsh_kernel(dtype, d, Br, N, n_planes, offset):
+    import torch
+
+    import gpu_util as U
+    import paper_2507_17245_amd as da
+    cfg = W.CONFIGS["tiny"].scaled(B=2, H=2, Hkv=1, N=N, d=d, Br=Br, n_groups=d // 2, n_planes=n_planes, recipe="normal")
+    q = W.make(cfg)[0]
+    if dtype == "bf16":
+        q = torch.from_numpy(q).bfloat16().float().numpy()
+    print(f"case {cfg} {dtype} offset {offset}", flush=True)
+    room = torch.empty(q.size + 8, dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+    tq = room[offset:offset + q.size].view(q.shape)
+    tq.copy_(torch.from_numpy(q))
+    perm = torch.zeros((2, 2, cfg.Tq, d), dtype=torch.uint8, device="cuda")
+    hsh = torch.zeros((2, 2, cfg.Tq, d), dtype=torch.int32, device="cuda")
+    da.distr_attn_lsh_group(tq, da.make_params(tq, tq, tq, Br=Br, n_groups=d // 2, lsh_seed=cfg.lsh_seed, n_planes=n_planes,
+                                               perm_out=perm, hash_out=hsh))
+    want_hash, want_perm, _ = oracle.lsh_group(q, U.oracle_params(cfg))
+    assert np.array_equal(perm.cpu().numpy(), want_perm)
+    assert np.array_equal(hsh.cpu().numpy().view(np.uint32), want_hash)
