@@ -20,6 +20,7 @@
 //                       rows of every query head of the group stream through LDS:
 //                       S = Q~ K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q~^T dS
 //   bwd_reduce_kernel   sums the float partial dK, dV of a head-split dK/dV launch
+//   bwd_short_kernel    short sequences at d = 64: all of it in one workgroup per head, one launch
 // In both, the accumulator layout of the first products (registers = streamed rows, lanes =
 // resident rows) is the B-operand layout of the last ones, so P and dS never leave registers; the
 // streamed tiles are read once row-wise (16-byte reads) and once with transposing reads. Tiles are
@@ -694,6 +695,339 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(const float* __restrict
   *(bf16x4*)((second ? dv : dk) + j) = y;
 }
 
+// ------------------------------------------------------------------------------------------------
+// Short sequences (at most 32 * NW keys), d = 64, as many kv heads as query heads: the whole backward of a
+// head in one workgroup and one launch. Wave w owns the keys 32*w .. as in bwd_dkv_kernel; row tiles of 64
+// pass through LDS, where they are also prepared (D_i, Q~). dS of a tile, of all keys, meets in LDS, and
+// the workgroup takes dQ~^T = K^T dS^T from it: five products instead of the seven of the two kernels, Q, dO
+// and O read once, no scratch.
+//
+// Bound: memory traffic (5 + 3 tensors of N rows) where there are heads to fill the chip, LDS cycles next.
+// Iteration `it`, one barrier each, so that a wave's products, LDS phases and waits fall beside
+// those of the SIMD's other wave:
+//   S, dP, P, dS, dV, dK of tile it | rows of tile it + 1 into LDS, those of it + 2 asked for |
+//   dQ~ of tile it - 1 into LDS | dQ of tile it - 2 grouped and stored
+constexpr int kShortMaxGroup = 4;
+template <int NW, bool GROUPED>
+__global__ __launch_bounds__(NW * 64, 2) void bwd_short_kernel(
+    const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v, const bf16* __restrict__ o,
+    const bf16* __restrict__ dout, const float* __restrict__ lse, bf16* __restrict__ dq, bf16* __restrict__ dk,
+    bf16* __restrict__ dv, const uint8_t* __restrict__ perm, int N, int Nk, int Br, int Tq, int G,
+    int causal, float scale) {
+  constexpr int D = 64, CH = D / 8, KS = D / 16, CB = D / 32, T = NW * 64, KEYS = NW * 32;
+  constexpr int TILE = kBwdStream * D * 2, RAW = D * 2 + 16;
+  constexpr int CPT = kBwdStream * CH / T;           // 16-byte chunks of a row tile per thread
+  constexpr int QB = 16 / NW;                        // 16-row blocks of dQ~ per wave (16 channels each)
+  constexpr int SLOTS = 8;                           // tables of the tiles in flight (it - 2 .. it + 2)
+  __shared__ __attribute__((aligned(1024))) char ds_lds[2][KEYS * kBwdStream * 2];   // [key][row of the tile]
+  __shared__ __attribute__((aligned(1024))) char q_lds[2][TILE];                     // Q~
+  __shared__ __attribute__((aligned(1024))) char do_lds[2][TILE];
+  __shared__ __attribute__((aligned(1024))) float stage_lds[2][kBwdStream][D];       // dQ~, 16-byte pieces ^ row
+  __shared__ __attribute__((aligned(16))) char raw_lds[GROUPED ? kBwdStream * RAW : 16];
+  __shared__ __attribute__((aligned(16))) float lse_lds[2][kBwdStream];              // lse * log2(e)
+  __shared__ __attribute__((aligned(16))) float nd_lds[2][kBwdStream];               // -D
+  // tables of a tile's Q block: the sampled channel of a channel's group; per sampled channel the group's other
+  // members (255 in the first row for channels that are not sampled)
+  __shared__ __attribute__((aligned(8))) uint8_t rep_lds[GROUPED ? SLOTS : 1][D];
+  __shared__ __attribute__((aligned(8))) uint8_t mem_lds[GROUPED ? SLOTS : 1][kShortMaxGroup][D];
+
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lq = lane & 31, hh = lane >> 5;
+  const size_t bh = blockIdx.x;                      // b * H + h
+  const int key0 = 32 * w, key = key0 + lq;
+  const bool valid = key < Nk;
+  const int shift = Nk - N;
+  const float sl2e = scale * kLog2e;
+  const int n_it = (N + kBwdStream - 1) / kBwdStream;
+  const size_t row0 = bh * N;                        // the head's first row
+
+  // (the thread's index, renewed for every iteration: kept from one to the next, the addresses that follow from
+  // it would take the registers of the products)
+  int tl = tid;
+
+  // ---- tables: wave 0 alone, a byte per lane
+  auto load_table = [&](int it) -> int {
+    if (!GROUPED || w != 0 || it >= n_it) return 0;
+    return perm[(bh * Tq + it * kBwdStream / Br) * D + lane] & (D - 1);
+  };
+  auto write_table = [&](int it, int c) {
+    if constexpr (GROUPED) {
+      if (w != 0 || it >= n_it) return;
+      const int slot = it & (SLOTS - 1), first = lane / G * G;
+      rep_lds[slot][c] = (uint8_t)__shfl(c, first);
+#pragma unroll
+      for (int m = 0; m < kShortMaxGroup; ++m) {
+        const int other = __shfl(c, min(lane + m, D - 1));
+        if (m < G) mem_lds[slot][m][c] = (uint8_t)(lane == first ? other : 255);
+      }
+    }
+  };
+
+  // ---- rows: this thread's chunks of a tile (and, from the first thread of a row, its statistics)
+  u32x4 qx[CPT], ox[CPT], dx[CPT];
+  float lx[CPT];
+  auto fetch = [&](int it) {
+    if (it >= n_it) return;
+    const int r0 = it * kBwdStream;
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+      const int row = r0 + (u * T + tl) / CH, chunk = tl % CH;
+      qx[u] = ox[u] = dx[u] = u32x4{0u, 0u, 0u, 0u};
+      lx[u] = 0.0f;
+      if (row < N) {
+        const size_t at = (row0 + row) * D + chunk * 8;
+        qx[u] = *(const u32x4*)(q + at);
+        ox[u] = *(const u32x4*)(o + at);
+        dx[u] = *(const u32x4*)(dout + at);
+        if (chunk == 0) lx[u] = lse[row0 + row];
+      }
+    }
+  };
+  auto place = [&](int it) {                          // the fetched rows into the tile's buffers
+    const int par = it & 1;
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+      const int lr = (u * T + tl) / CH, chunk = tl % CH;
+      const bf16x8 a = __builtin_bit_cast(bf16x8, dx[u]), b = __builtin_bit_cast(bf16x8, ox[u]);
+      float acc = 0.0f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc = __builtin_fmaf((float)a[j], (float)b[j], acc);
+#pragma unroll
+      for (int m = 1; m < CH; m <<= 1) acc += __shfl_xor(acc, m);
+      if (chunk == 0) {
+        nd_lds[par][lr] = -acc;
+        lse_lds[par][lr] = lx[u] * kLog2e;
+      }
+      *(u32x4*)chunk_addr<D>(do_lds[par], lr, chunk) = dx[u];
+      if constexpr (GROUPED) {
+        // (the eight threads of a row are lanes of one wave: their writes precede the reads in its order)
+        *(u32x4*)(raw_lds + lr * RAW + chunk * 16) = qx[u];
+        __builtin_amdgcn_wave_barrier();
+        const u32x2 from = *(const u32x2*)&rep_lds[it & (SLOTS - 1)][chunk * 8];
+        bf16x8 y;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) y[j] = *(const bf16*)(raw_lds + lr * RAW + ((from[j >> 2] >> (8 * (j & 3))) & (D - 1)) * 2);
+        *(bf16x8*)chunk_addr<D>(q_lds[par], lr, chunk) = y;
+        __builtin_amdgcn_wave_barrier();
+      } else {
+        *(u32x4*)chunk_addr<D>(q_lds[par], lr, chunk) = qx[u];
+      }
+    }
+  };
+  // dQ of tile `it` from the staged dQ~: the members' columns summed into the sampled channel
+  auto store_dq = [&](int it) {
+    const int r0 = it * kBwdStream;
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+      const int lr = (u * T + tl) / CH, chunk = tl % CH;
+      const float* row = stage_lds[it & 1][lr];
+      const f32x4 lo = *(const f32x4*)(row + (((2 * chunk) ^ (lr & 15)) << 2)), hi = *(const f32x4*)(row + (((2 * chunk + 1) ^ (lr & 15)) << 2));
+      float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      if constexpr (GROUPED) {
+        const uint8_t(*mem)[D] = mem_lds[it & (SLOTS - 1)];
+        const u32x2 own = *(const u32x2*)&mem[0][chunk * 8];
+        for (int m = 1; m < G; ++m) {
+          const u32x2 other = *(const u32x2*)&mem[m][chunk * 8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int c = (other[e >> 2] >> (8 * (e & 3))) & (D - 1);
+            x[e] += row[(((c >> 2) ^ (lr & 15)) << 2) | (c & 3)];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (((own[e >> 2] >> (8 * (e & 3))) & 255) == 255) x[e] = 0.0f;
+      }
+      if (r0 + lr < N) {
+        bf16x8 y;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] = (bf16)(scale * x[e]);
+        *(bf16x8*)(dq + (row0 + r0 + lr) * D + chunk * 8) = y;
+      }
+    }
+  };
+
+  fetch(0);
+  {   // K passes through the dS buffers on its way to the operands of dQ~
+    const __amdgpu_buffer_rsrc_t k_rsrc = head_rsrc(k + bh * Nk * D, (unsigned)Nk * D * 2);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int slot = (j * NW + w) * 64 + lane, row = slot / CH, pc = slot % CH;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rsrc, (lds_void*)(ds_lds[0] + (j * NW + w) * 1024), 16,
+                                               row * (D * 2) + ((pc ^ chunk_swz<D>(row)) << 4), 0, 0, 0);
+    }
+  }
+  write_table(0, load_table(0));
+  write_table(1, load_table(1));
+  int next_table = load_table(2);
+  bf16x8 kop[KS], vop[KS];
+  {
+    const size_t row_off = (bh * Nk + (valid ? key : 0)) * D;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      u32x4 x = {0u, 0u, 0u, 0u}, y = {0u, 0u, 0u, 0u};
+      if (valid) {
+        x = *(const u32x4*)(k + row_off + (2 * s + hh) * 8);
+        y = *(const u32x4*)(v + row_off + (2 * s + hh) * 8);
+      }
+      kop[s] = __builtin_bit_cast(bf16x8, x);
+      vop[s] = __builtin_bit_cast(bf16x8, y);
+    }
+  }
+  f32x16 dkacc[CB], dvacc[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) {
+    zero(dkacc[cb]);
+    zero(dvacc[cb]);
+  }
+  const OperandOffsets<D> off(lane);
+  // dS of this wave's keys: 8-byte pieces (4 rows of the tile) of key row `key`; the tile's other 32 rows: ^ 64
+  int ds_off[4];
+#pragma unroll
+  for (int i4 = 0; i4 < 4; ++i4) ds_off[i4] = (int)(chunk_addr<D>(nullptr, key, i4) - (char*)nullptr) + 8 * hh;
+  // dQ~^T[ch][row] on v_mfma_f32_16x16x32_bf16: this wave's 16 channels and QB blocks of 16 rows, all keys.
+  // Transposing reads of a [key][64] buffer: lanes address keys 8*(lane/16) + (lane%16)/4 (+4), columns
+  // 16*block + 4*(lane%4) ..; lane i%16 receives column 16*block + i%16 of its 8 keys.
+  const int ch16 = w & 3, qb0 = (w >> 2) * QB;
+  auto tr16 = [&](const char* buf, int block, int step) {
+    const int ln = tl & 63, row = 8 * (ln >> 4) + ((ln & 15) >> 2), chunk = 2 * block + ((ln & 3) >> 1);
+    const char* base = buf + step * 32 * (D * 2) + 8 * (ln & 1);
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(base + row * (D * 2) + ((chunk ^ chunk_swz<D>(row)) << 4)));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(base + (row + 4) * (D * 2) + ((chunk ^ chunk_swz<D>(row + 4)) << 4)));
+    const s16x8 r = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, r);
+  };
+  wait_loads();                                      // K has landed
+  __syncthreads();
+  place(0);
+  fetch(1);
+  asm volatile("" : "+v"(tl));
+  bf16x8 kt[NW];
+#pragma unroll
+  for (int s = 0; s < NW; ++s) kt[s] = tr16(ds_lds[0], ch16, s);
+  __syncthreads();
+
+#pragma unroll 1
+  for (int it = 0; it < n_it + 2; ++it) {
+    asm volatile("" : "+v"(tl));
+    if (it < n_it) {
+      const int par = it & 1, r0 = it * kBwdStream;
+      const char* qt = q_lds[par];
+      const char* dot = do_lds[par];
+      // ---- S, dP, P, dS; dV, dK; dS into LDS
+      const int blocks = r0 + 32 < N ? 2 : 1;        // 32-row blocks of the tile that hold rows
+#pragma unroll 1
+      for (int qb = 0; qb < blocks; ++qb) {
+        char* ds_dst = ds_lds[par];
+        const int flip = qb << 6;
+        const int q0 = r0 + 32 * qb;
+        bf16x8 ar[KS], at[CB][2], pop[2], dsop[2];
+        f32x16 sacc, dpacc;
+        f32x4 l4[4];
+        zero(sacc);
+        read_rows<D>(qt, qb, off, ar);
+        fence();
+#pragma unroll
+        for (int s = 0; s < KS; ++s) sacc = mfma(ar[s], kop[s], sacc);
+        read_rows<D>(dot, qb, off, ar);
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          l4[i4] = *(const f32x4*)&lse_lds[par][32 * qb + 8 * i4 + 4 * hh];
+          const f32x4 x = *(const f32x4*)&nd_lds[par][32 * qb + 8 * i4 + 4 * hh];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dpacc[4 * i4 + e] = x[e];
+        }
+        fence();
+#pragma unroll
+        for (int s = 0; s < KS; ++s) dpacc = mfma(ar[s], vop[s], dpacc);
+        read_transposed<D>(dot, qb, off, at);
+        float pv[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) pv[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], sl2e, -l4[i >> 2][i & 3]));
+        // (rows past N hold zeros and reach nothing; keys past Nk must not reach dQ)
+        if (key0 + 32 > Nk || (causal && key0 + 31 > q0 + shift)) {
+          const int first = valid ? (causal ? key - shift - q0 : 0) : 32;   // row of the block that sees this key first
+#pragma unroll
+          for (int i = 0; i < 16; ++i) pv[i] = acc_row(i, hh) >= first ? pv[i] : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          pop[i >> 3][i & 7] = (bf16)pv[i];
+          dsop[i >> 3][i & 7] = (bf16)(pv[i] * dpacc[i]);
+        }
+        fence();
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+          for (int tt = 0; tt < 2; ++tt) dvacc[cb] = mfma(at[cb][tt], pop[tt], dvacc[cb]);
+        read_transposed<D>(qt, qb, off, at);
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4)
+          *(u32x2*)(ds_dst + (ds_off[i4] ^ flip)) =
+              i4 & 1 ? __builtin_bit_cast(u32x2, __builtin_shufflevector(dsop[i4 >> 1], dsop[i4 >> 1], 4, 5, 6, 7))
+                     : __builtin_bit_cast(u32x2, __builtin_shufflevector(dsop[i4 >> 1], dsop[i4 >> 1], 0, 1, 2, 3));
+        fence();
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+          for (int tt = 0; tt < 2; ++tt) dkacc[cb] = mfma(at[cb][tt], dsop[tt], dkacc[cb]);
+      }
+    }
+    if (it + 1 < n_it) {
+      place(it + 1);
+      fetch(it + 2);
+      write_table(it + 2, next_table);
+      next_table = load_table(it + 3);
+    }
+    if (it > 0 && it <= n_it) {
+      // ---- dQ~ of the last tile (buffers of keys past Nk hold zeros; a block of rows past N is never stored)
+      const char* ds = ds_lds[(it - 1) & 1];
+      const int r0 = (it - 1) * kBwdStream;
+#pragma unroll
+      for (int b = 0; b < QB; ++b) {
+        if (r0 + 16 * (qb0 + b) >= N) break;
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int s0 = 0; s0 < NW; s0 += 4) {
+          bf16x8 x[4];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) x[s] = tr16(ds, qb0 + b, s0 + s);
+          fence();
+#pragma unroll
+          for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[s0 + s], x[s], acc, 0, 0, 0);
+        }
+        const int ln = tl & 63, lr = 16 * (qb0 + b) + (ln & 15);   // register i: channel 16*ch16 + 4*(lane/16) + i of this row
+        *(f32x4*)&stage_lds[(it - 1) & 1][lr][((4 * ch16 + (ln >> 4)) ^ (lr & 15)) << 2] = acc;
+      }
+    }
+    if (it > 1) store_dq(it - 2);
+    __syncthreads();
+  }
+  // ---- dK, dV: 32 rows of a wave by way of its part of the dS buffers, whole rows to memory
+  char* out = ds_lds[0] + w * 4096;
+  auto store_rows = [&](const f32x16 (&acc)[CB], float factor, bf16* dst) {
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        bf16x4 a;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[e] = (bf16)(factor * acc[cb][4 * i4 + e]);
+        *(bf16x4*)(out + lq * (D * 2) + (((4 * cb + i4) ^ (lq & 7)) << 4) + 8 * hh) = a;
+      }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int row = u * 8 + lane / CH, chunk = lane % CH;
+      const u32x4 x = *(const u32x4*)(out + row * (D * 2) + ((chunk ^ (row & 7)) << 4));
+      if (key0 + row < Nk) *(u32x4*)(dst + (bh * Nk + key0 + row) * D + chunk * 8) = x;
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+  store_rows(dkacc, scale, dk);
+  store_rows(dvacc, 1.0f, dv);
+}
+
 // Workgroups of the dK/dV launch that share one kv head's keys but take different query heads: used
 // when the launch would otherwise not fill the chip twice over (grouped-query shapes with few kv
 // heads; under the causal mask its workgroups differ many-fold in length and need company).
@@ -701,6 +1035,14 @@ static int dkv_head_split(const Problem& pb) {
   const int rep = pb.H / pb.Hkv;
   const long long k_units = (long long)pb.B * pb.Hkv * ((pb.Nk + kBwdRows - 1) / kBwdRows);
   return (rep > 1 && k_units < 512) ? rep : 1;
+}
+
+// Where the one-workgroup backward is taken: what its LDS holds (keys, and the tables of groups of up to 4
+// channels), and no grouped query heads, which one workgroup would have to take one after the other.
+// Measured, three kernels | one: H12 N197 B64 100 | 68 us, B8 31 | 20, B1 29 | 19; N256 B64 106 | 75; N128 B64 52 | 42; N64
+// B64 40 | 26, B4 23 | 10; with the loop over grouped heads H32 Hkv8 N200 B8 48 | 62, B1 30 | 63.
+static bool bwd_short(const Problem& pb, int distr) {
+  return pb.d == 64 && pb.H == pb.Hkv && pb.N <= 256 && pb.Nk <= 256 && (!distr || pb.d / pb.n_groups <= kShortMaxGroup);
 }
 
 size_t attn_bf16_bwd_scratch_bytes(const Problem& pb, int distr) {
@@ -735,6 +1077,18 @@ hipError_t launch_attn_bf16_bwd(const void* q, const void* k, const void* v, con
   const uint8_t* table = distr ? perm : nullptr;
   const bf16* qx = distr ? qrep : (const bf16*)q;
   const int n_groups = distr ? pb.n_groups : pb.d;
+  if (bwd_short(pb, distr)) {
+#define DA_SHORT(NW, GR)                                                                                            \
+  hipLaunchKernelGGL((bwd_short_kernel<NW, GR>), dim3((unsigned)(pb.B * pb.H)), dim3(NW * 64), 0, stream, (const bf16*)q, \
+                     (const bf16*)k, (const bf16*)v, (const bf16*)o, (const bf16*)dout, lse, (bf16*)dq, (bf16*)dk,    \
+                     (bf16*)dv, table, pb.N, pb.Nk, pb.Br, Tq, pb.d / n_groups, pb.causal, pb.scale)
+    if (pb.Nk <= 128 && distr) DA_SHORT(4, true);
+    else if (pb.Nk <= 128) DA_SHORT(4, false);
+    else if (distr) DA_SHORT(8, true);
+    else DA_SHORT(8, false);
+#undef DA_SHORT
+    return hipGetLastError();
+  }
   const int dq_order = pb.causal && q_units <= kBalancedUnits ? kLongestFirst : kHeadMajor;
   const int dkv_order = pb.causal && k_units * hsplit <= kBalancedUnits ? kLongestFirst : kHeadMajor;
 #define DA_BWD(DD)                                                                                                   \

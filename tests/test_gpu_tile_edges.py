@@ -192,3 +192,27 @@ def test_lsh_kernel(dtype, d, Br, N, n_planes, offset):
     want_hash, want_perm, _ = oracle.lsh_group(q, U.oracle_params(cfg))
     assert np.array_equal(perm.cpu().numpy(), want_perm)
     assert np.array_equal(hsh.cpu().numpy().view(np.uint32), want_hash)
+
+
+# bf16 backward of short sequences in one workgroup per head: 32 keys per wave (4 waves up to 128 keys, 8 up to 256),
+# row tiles of 64 in blocks of 32 and 16; one past the range on either side takes the general kernels. Same bar as the
+# bf16 backward tests; a call's results do not depend on the run.
+@pytest.mark.parametrize("N,Nk,causal", [(1, 1, False), (31, 33, True), (33, 31, False), (64, 128, True), (65, 129, False), (127, 64, False),
+                                         (128, 128, True), (196, 225, True), (256, 256, True), (256, 256, False), (257, 256, False), (200, 257, True)])
+@pytest.mark.parametrize("Br,G", [(64, 2), (128, 4), (256, 1)])
+def test_bf16_backward_short(N, Nk, causal, Br, G):
+    import gpu_util as U
+    from test_gpu_backward import run_backward
+    cfg = W.CONFIGS["vit"].scaled(B=2, H=3, Hkv=3, N=N, Nk=Nk, Br=Br, causal=causal, n_groups=64 // G, recipe="normal")
+    print(f"case {cfg}", flush=True)
+    q, k, v = W.make(cfg)
+    dout = W.make_grad(cfg)
+    p = U.oracle_params(cfg)
+    for distr in (True, False):
+        got = run_backward(cfg, q, k, v, dout, distr)
+        ref = oracle.distr_bwd(q, k, v, dout, p) if distr else oracle.exact_bwd(q, k, v, dout, p)
+        for what, g, r in zip(("dq", "dk", "dv"), got, ref):
+            err, unit = np.abs(g - r), max(1.0, np.abs(r).max())
+            assert np.isfinite(g).all(), what
+            assert err.max() <= 2e-2 * unit and err.mean() <= 2e-3 * unit, f"distr={distr} {what}: {err.max():.4g}"
+        assert all(np.array_equal(x, y) for x, y in zip(got, run_backward(cfg, q, k, v, dout, distr)))
