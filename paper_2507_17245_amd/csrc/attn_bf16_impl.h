@@ -390,25 +390,16 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
             any_doubt |= doubt[i];
           }
           if (__builtin_amdgcn_ballot_w64(any_doubt) != 0) {
-            // The defining sums of this lane's four channels (float, one fused multiply-add per
-            // row, rows ascending): the channels 16*ct + 4*kg + 0..3 sit in one 8-byte piece of
-            // every staged row.
-            float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            const int ch0 = 16 * ct + 4 * kg;
-            const char* col = q_stage + (ch0 & 7) * 2;
-            for (int r8 = 0; r8 < BR; r8 += 8) {
-#pragma unroll
-              for (int j8 = 0; j8 < 8; ++j8) {
-                const s16x4 x4 = *(const s16x4*)(col + (r8 + j8) * C::ROWB + (((ch0 >> 3) ^ q_swz(r8 + j8)) << 4));
-                const float rv = (float)rp1[pl16 * RPAD + r8 + j8] + (float)rp2[pl16 * RPAD + r8 + j8];   // exact
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                  sum[i] = __builtin_fmaf(__builtin_bit_cast(float, (uint32_t)(uint16_t)x4[i] << 16), rv, sum[i]);
-              }
-            }
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-              if (doubt[i]) positive[i] = sum[i] > 0.0f;
+              for (uint64_t left = __builtin_amdgcn_ballot_w64(doubt[i]); left != 0; left &= left - 1) {
+                const int who = __builtin_ctzll(left), ch = 16 * ct + 4 * (who >> 4) + i, p = (who & 15) * RPAD;
+                const float sum = defining_sum(BR, [&](int row, float& x, float& r) {
+                  x = (float)q_staged(row, ch);
+                  r = (float)rp1[p + row] + (float)rp2[p + row];   // exact
+                });
+                if (lane == who) positive[i] = sum > 0.0f;
+              }
           }
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -442,7 +433,8 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
       }
       __syncthreads();
       if (tid < D) {
-        hash_lds[tid] = lsh_hash_of_code(code_lds[tid], gray_mode);
+        // (at most 16 bits: hash and channel make one key)
+        hash_lds[tid] = lsh_hash_of_code(code_lds[tid], gray_mode) << 7 | tid;
         code_lds[tid] = 0;   // from here on the channel's rank is counted in this word
       }
       __syncthreads();
@@ -460,7 +452,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
         for (int o4 = 0; o4 < SL; o4 += 4) {
           const u32x4 h = *(const u32x4*)&hash_lds[first + o4];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) cnt += (h[j] < mine || (h[j] == mine && first + o4 + j < c)) ? 1u : 0u;
+          for (int j = 0; j < 4; ++j) cnt += h[j] < mine ? 1u : 0u;
         }
         if (NPG == 1) rank_lds[c] = cnt;
         else if (cnt) atomicAdd(&rank_lds[c], cnt);

@@ -43,6 +43,31 @@ __host__ __device__ inline uint32_t lsh_hash_of_code(uint32_t code, int gray_mod
   return h;
 }
 
+// The defining sum of a projection (float, one fused multiply-add per row, rows ascending, from +0), for the few
+// whose sign the matrix pipe leaves in doubt, by a whole wave: lane = row while the operands are read,
+// `operands(row, x, r)`, 64 rows at a time (0 and 0 past the block's end leave the sum as it is); the
+// chain itself takes them lane by lane. (Every lane walking the rows for its own channels, all but one or
+// two of them for nothing, took four times as long: 2.2 us per 64 rows.)
+template <typename F>
+__device__ inline float defining_sum(int rows, F operands) {
+  float sum = 0.0f;
+#pragma unroll 1
+  for (int r0 = 0; r0 < rows; r0 += 64) {
+    float x = 0.0f, r = 0.0f;
+    const int row = r0 + (int)(threadIdx.x & 63);
+    if (row < rows) operands(row, x, r);
+    const int xi = __builtin_bit_cast(int, x), ri = __builtin_bit_cast(int, r);
+#pragma unroll 1
+    for (int k0 = 0; k0 < 64; k0 += 16) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        sum = __builtin_fmaf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, k0 + j)),
+                             __builtin_bit_cast(float, __builtin_amdgcn_readlane(ri, k0 + j)), sum);
+    }
+  }
+  return sum;
+}
+
 // Exchange between the wave halves: v_permlane32_swap swaps the upper 32 lanes of its first
 // operand with the lower 32 lanes of its second; fed the same value twice it leaves, in every
 // lane, the values of lanes l % 32 (first operand) and l % 32 + 32 (second operand). Written as
@@ -127,6 +152,10 @@ bool attn_bf16_few_rows(const Problem& pb);
 int attn_bf16_few_splits(const Problem& pb);
 hipError_t launch_attn_bf16_few(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                                 const Problem& pb, int distr, hipStream_t stream);
+// Short sequences at d = 64: a workgroup per head.
+bool attn_bf16_short(const Problem& pb, int distr);
+hipError_t launch_attn_bf16_short(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
+                                  const Problem& pb, int distr, hipStream_t stream);
 hipError_t launch_attn_bf16_combine(void* o, const Problem& pb, hipStream_t stream);
 // Backward in float arithmetic on the vector ALUs (float tensors): dq [B][H][N][d], dk and dv
 // [B][Hkv][Nk][d] from the forward's inputs, its output o, the output gradient dout and the

@@ -113,23 +113,16 @@ __device__ inline void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int p0, int n_
       any_doubt |= doubt[i];
     }
     if (__builtin_amdgcn_ballot_w64(any_doubt) != 0) {
-      // the defining sums of this lane's four channels, an 8-byte piece of every staged row
-      float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      const int ch0 = 16 * ct + 4 * kg;
-      const char* col = lds.rows + (ch0 & 7) * 2;
-      for (int r8 = 0; r8 < BR; r8 += 8) {
-#pragma unroll
-        for (int j8 = 0; j8 < 8; ++j8) {
-          const s16x4 x4 = *(const s16x4*)(col + (r8 + j8) * ROWB + (((ch0 >> 3) ^ lsh_chunk_swz<D>(r8 + j8)) << 4));
-          const float rv = (float)rp1[pl16 * RPAD + r8 + j8] + (float)rp2[pl16 * RPAD + r8 + j8];   // exact
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            sum[i] = __builtin_fmaf(__builtin_bit_cast(float, (uint32_t)(uint16_t)x4[i] << 16), rv, sum[i]);
-        }
-      }
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (doubt[i]) positive[i] = sum[i] > 0.0f;
+        for (uint64_t left = __builtin_amdgcn_ballot_w64(doubt[i]); left != 0; left &= left - 1) {
+          const int who = __builtin_ctzll(left), ch = 16 * ct + 4 * (who >> 4) + i, p = (who & 15) * RPAD;
+          const float sum = defining_sum(BR, [&](int row, float& x, float& r) {
+            x = (float)*(const bf16*)(lds.rows + row * ROWB + (((ch >> 3) ^ lsh_chunk_swz<D>(row)) << 4) + (ch & 7) * 2);
+            r = (float)rp1[p + row] + (float)rp2[p + row];   // exact
+          });
+          if (lane == who) positive[i] = sum > 0.0f;
+        }
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
