@@ -34,7 +34,7 @@ bool attn_bf16_supported(const Problem& pb, int distr) {
 // Measured, Q~ K^T | fused: B64 H12 N197 d64 40 | 46 us; H16 N1024 d64 causal 20 | 22; H16 N4096 d64 causal 53 | 54;
 // H32 Hkv8 N4096 d64 causal 84 | 77; H16 N2048 d128 causal 47 | 49; N8192 282 | 253; N200 Nk32768 d128 109 | 500.
 bool attn_bf16_replicated(const Problem& pb) {
-  if (attn_bf16_few_rows(pb)) return true;
+  if (attn_bf16_few_rows(pb) || attn_bf16_short(pb, 1)) return true;
   const double rows = (double)(pb.H / pb.Hkv) * pb.N * (pb.causal ? 1.0 - 0.5 * pb.N / pb.Nk : 1.0);
   return rows < 1570.0 + 7.8e9 / ((double)pb.d * pb.B * pb.Hkv * pb.Nk);
 }
@@ -45,6 +45,7 @@ bool attn_bf16_replicated(const Problem& pb) {
 // the LSH stage in a kernel of its own (another 18). Measured, 1 | 256 | 512 workgroups: exact H16 N200 Nk8192
 // d64 71 | 19 | 22 us; N1000 Nk8192 d128 109 | 72 | 80; N200 Nk32768 d128 486 | 90 | 87; N2048 d64 causal 22 | 22 | 29.
 int attn_bf16_splits(const Problem& pb, int distr) {
+  if (attn_bf16_short(pb, distr)) return 1;
   const long long units = (long long)pb.B * pb.H * ((pb.N + pb.Br - 1) / pb.Br);
   const int tiles = (pb.Nk + pb.Bc - 1) / pb.Bc;
   long long n = 1024 / (pb.Br / 32) / units;
@@ -122,6 +123,7 @@ hipError_t launch_attn_bf16(const void* q, const void* k, const void* v, void* o
                             const void* kt, const Problem& pb, int distr, hipStream_t stream) {
   if (!attn_bf16_supported(pb, distr)) return hipErrorInvalidValue;
   if (!kt && attn_bf16_few_rows(pb)) return launch_attn_bf16_few(q, k, v, o, perm, pb, distr, stream);
+  if (!kt && attn_bf16_short(pb, distr)) return launch_attn_bf16_short(q, k, v, o, perm, pb, distr, stream);
   if (pb.Bc == 32) return launch_attn_bf16_bc32(q, k, v, o, perm, kt, pb, distr, stream);
   if (pb.Bc == 128) return launch_attn_bf16_bc128(q, k, v, o, perm, kt, pb, distr, stream);
   return launch_attn_bf16_bc64(q, k, v, o, perm, kt, pb, distr, stream);

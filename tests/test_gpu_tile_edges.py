@@ -216,3 +216,27 @@ def test_bf16_backward_short(N, Nk, causal, Br, G):
             assert np.isfinite(g).all(), what
             assert err.max() <= 2e-2 * unit and err.mean() <= 2e-3 * unit, f"distr={distr} {what}: {err.max():.4g}"
         assert all(np.array_equal(x, y) for x, y in zip(got, run_backward(cfg, q, k, v, dout, distr)))
+
+
+# bf16 forward of short sequences, one workgroup per head: 32 rows per wave, two, four or eight waves by the longer
+# side; one past the range takes the general kernel. Tables to the bit, row statistics, the table handed in.
+@pytest.mark.parametrize("N,Nk,causal", [(1, 1, False), (31, 33, True), (64, 64, True), (65, 64, False), (33, 129, True), (128, 128, False),
+                                         (197, 197, False), (256, 255, False), (256, 256, True), (257, 256, False)])
+@pytest.mark.parametrize("B,Br,G", [(2, 64, 2), (2, 128, 4), (80, 256, 8)])
+def test_bf16_short(N, Nk, causal, B, Br, G):
+    import torch
+
+    import gpu_util as U
+    cfg = W.CONFIGS["vit"].scaled(B=B, H=4, Hkv=2, N=N, Nk=Nk, Br=Br, causal=causal, n_groups=64 // G, recipe="normal")
+    print(f"case {cfg}", flush=True)
+    q, k, v = W.make(cfg)
+    p = U.oracle_params(cfg)
+    lse = torch.empty((B, 4, N), dtype=torch.float32, device="cuda")
+    o, perm, _ = U.run_gpu(cfg, q, k, v, want_perm_only=True, lse_out=lse)
+    assert np.array_equal(perm, oracle.lsh_group(q, p)[1])
+    U.assert_close(o, oracle.distr_fwd(q, k, v, p), "bf16")
+    assert np.abs(lse.cpu().numpy() - oracle.lse(q, k, p)).max() <= 2e-2
+    assert np.array_equal(U.run_gpu(cfg, q, k, v, perm_in=perm)[0], o)
+    o, _, _ = U.run_gpu(cfg, q, k, v, distr=False, lse_out=lse)
+    U.assert_close(o, oracle.exact_fwd(q, k, v, p), "bf16")
+    assert np.abs(lse.cpu().numpy() - oracle.lse(q, k, p, distr=False)).max() <= 2e-2
