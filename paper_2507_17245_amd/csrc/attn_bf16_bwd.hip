@@ -1,5 +1,5 @@
 // Backward of the attention forward (exact and DistrAttention) for bf16 tensors on the gfx950
-// matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulate). Three kernels (and a reduction when the
+// matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulate). Two kernels (and a reduction when the
 // dK/dV launch is split over query heads), no atomics (results do not depend on the run).
 //
 // The paper trains through the approximation (Sec. 4.3, 4.4) and gives no gradient; computed here
@@ -13,9 +13,11 @@
 // sum over each group's members for dQ. P = exp(S^ - lse) is rebuilt from the forward's row
 // statistics, dP = dO V^T, D_i = sum_c dO_ic O_ic, dS = P o (dP - D), dV = P^T dO.
 //
-//   bwd_prepare_kernel  -D_i and lse * log2(e) for every row; Q~ (DistrAttention only) into scratch
 //   bwd_dq_kernel       one workgroup per 128 query rows, lane = query row; K and V tiles of 64
-//                       rows stream through LDS:  S^T = K Q~^T, dP^T = V dO^T, dQ~^T += K^T dS^T
+//                       rows stream through LDS:  S^T = K Q~^T, dP^T = V dO^T, dQ~^T += K^T dS^T.
+//                       Takes -D_i, lse * log2(e) and Q~ (DistrAttention only) of its rows on the way
+//                       and leaves them in scratch for the next kernel (a kernel of its own for it read Q, dO
+//                       and O once more: backward H16 N1024 d64 52 -> 48 us, d128 90 -> 79, H32 Hkv8 N4096 d64 292 -> 287)
 //   bwd_dkv_kernel      one workgroup per 128 keys of a kv head, lane = key; Q~ and dO tiles of 64
 //                       rows of every query head of the group stream through LDS:
 //                       S = Q~ K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q~^T dS
@@ -179,67 +181,11 @@ __device__ inline void zero(f32x16& x) {
 }  // namespace
 
 // ------------------------------------------------------------------------------------------------
-// -D_i, D_i = sum_c dO_ic O_ic, and lse_i * log2(e) for every query row; for DistrAttention also Q~:
-// channel c of a row takes the value of the first channel (sorted order) of c's group in the
-// row's Q block.
-template <int D>
-__global__ __launch_bounds__(kBwdThreads) void bwd_prepare_kernel(
-    const bf16* __restrict__ q, const bf16* __restrict__ o, const bf16* __restrict__ dout,
-    const float* __restrict__ lse, const uint8_t* __restrict__ perm, bf16* __restrict__ qrep,
-    float* __restrict__ delta, float* __restrict__ lse2, int N, int Br, int Tq, int n_groups) {
-  constexpr int CH = D / 8;
-  constexpr int RPP = kBwdThreads / CH;   // rows per pass
-  __shared__ uint8_t rep_lds[D];
-  __shared__ __attribute__((aligned(16))) bf16 row_lds[RPP][D];
-  const int tid = threadIdx.x;
-  const int t = blockIdx.x % Tq;
-  const size_t bh = blockIdx.x / Tq;
-  const int r0 = t * Br;
-  const int rows = min(Br, N - r0);
-  if (perm) {
-    const int G = D / n_groups;
-    for (int i = tid; i < D; i += kBwdThreads) {
-      const uint8_t* pr = perm + (size_t)blockIdx.x * D;
-      rep_lds[pr[i] & (D - 1)] = pr[i / G * G] & (D - 1);
-    }
-  }
-  const int rr = tid / CH, chunk = tid % CH;
-  for (int p0 = 0; p0 < rows; p0 += RPP) {
-    const int row = p0 + rr;
-    const bool on = row < rows;
-    const size_t off = ((bh * N) + r0 + (on ? row : 0)) * D + chunk * 8;
-    float acc = 0.0f;
-    if (on) {
-      const bf16x8 a = *(const bf16x8*)(dout + off), b = *(const bf16x8*)(o + off);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc = __builtin_fmaf((float)a[j], (float)b[j], acc);
-    }
-#pragma unroll
-    for (int m = 1; m < CH; m <<= 1) acc += __shfl_xor(acc, m);
-    if (on && chunk == 0) {
-      delta[bh * N + r0 + row] = -acc;
-      lse2[bh * N + r0 + row] = lse[bh * N + r0 + row] * kLog2e;
-    }
-    if (perm) {
-      __syncthreads();   // rep_lds written; the previous pass's reads of row_lds done
-      if (on) *(bf16x8*)&row_lds[rr][chunk * 8] = *(const bf16x8*)(q + off);
-      __syncthreads();
-      if (on) {
-        bf16x8 y;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) y[j] = row_lds[rr][rep_lds[chunk * 8 + j] & (D - 1)];
-        *(bf16x8*)(qrep + off) = y;
-      }
-    }
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(
-    const bf16* __restrict__ qrep, const bf16* __restrict__ k, const bf16* __restrict__ v,
-    const bf16* __restrict__ dout, const float* __restrict__ lse2p, const float* __restrict__ delta,
-    bf16* __restrict__ dq, const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Br, int Tq,
+    const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v, const bf16* __restrict__ o,
+    const bf16* __restrict__ dout, const float* __restrict__ lse, bf16* __restrict__ qrep, float* __restrict__ lse2p,
+    float* __restrict__ delta, bf16* __restrict__ dq, const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Br, int Tq,
     int Tw, int n_groups, int causal, int order, float scale) {
   constexpr int CH = D / 8;
   constexpr int KS = D / 16;    // MFMA steps over the channels
@@ -253,6 +199,7 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(
   __shared__ __attribute__((aligned(1024))) char v_lds1[TILE];
   __shared__ uint8_t perm_lds[kBwdRows / 32][D];
   __shared__ uint8_t group_lds[kBwdRows / 32][D];   // group whose sampled channel c is, else 255
+  __shared__ __attribute__((aligned(8))) uint8_t from_lds[kBwdRows / 32][D];   // byte offset in a row of a channel's sampled one
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int lq = lane & 31, hh = lane >> 5;
@@ -282,19 +229,76 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(
 
   const size_t row_off = (bh * N + (active ? q_abs : r0)) * D;
   bf16x8 qop[KS], doop[KS];
+  // The wave's rows of Q and its table entries, asked for ahead of dO and O (used below).
+  constexpr int QU = 32 * CH / 64, PU = D / 64;
+  const int G = D / n_groups;
+  u32x4 qx[QU];
+  int entry[PU], first[PU];
+  if (perm) {
+    const int blk = min((r0 + 32 * w) / Br, Tq - 1);   // a wave's 32 rows lie in one Q block (Br is a multiple of 32)
+    const uint8_t* pr = perm + (bh * Tq + blk) * D;
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
+      entry[u] = pr[u * 64 + lane] & (D - 1);
+      first[u] = pr[(u * 64 + lane) / G * G] & (D - 1);
+    }
+#pragma unroll
+    for (int j = 0; j < QU; ++j) {
+      const int row = min(r0 + 32 * w + (j * 64 + lane) / CH, N - 1);   // (a row past the end is never stored)
+      qx[j] = *(const u32x4*)(q + (bh * N + row) * D + lane % CH * 8);
+    }
+    fence();
+  }
+  float dl = 0.0f;   // -D: dP^T accumulates from there on (the products' addend, in 16 registers: no subtraction per score)
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
-    u32x4 x = {0u, 0u, 0u, 0u}, y = {0u, 0u, 0u, 0u};
+    u32x4 x = {0u, 0u, 0u, 0u}, y = {0u, 0u, 0u, 0u}, z = {0u, 0u, 0u, 0u};
     if (active) {
-      x = *(const u32x4*)(qrep + row_off + (2 * s + hh) * 8);
+      if (!perm) x = *(const u32x4*)(q + row_off + (2 * s + hh) * 8);
       y = *(const u32x4*)(dout + row_off + (2 * s + hh) * 8);
+      z = *(const u32x4*)(o + row_off + (2 * s + hh) * 8);
     }
     qop[s] = __builtin_bit_cast(bf16x8, x);
     doop[s] = __builtin_bit_cast(bf16x8, y);
+    const bf16x8 ov = __builtin_bit_cast(bf16x8, z);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) dl = __builtin_fmaf((float)doop[s][j], -(float)ov[j], dl);
   }
-  const float lse2 = active ? lse2p[bh * N + q_abs] : 0.0f;
-  // dP^T accumulates from -D on (the products' addend, held in 16 registers: no subtraction per score)
-  const float dl = active ? delta[bh * N + q_abs] : 0.0f;
+  dl = half_swap_sum(dl);
+  const float lse2 = active ? lse[bh * N + q_abs] * kLog2e : 0.0f;
+  if (active && hh == 0) {
+    lse2p[bh * N + q_abs] = lse2;
+    delta[bh * N + q_abs] = dl;
+  }
+  if (perm) {
+    // Q~: channel c of a row takes the value of the first channel (sorted order) of c's group in the row's Q block. The
+    // wave's rows pass through its quarter of the tile buffers that stay free until the loop (16-byte chunks exchanged
+    // by the row); its LDS accesses take effect in its order.
+    char* rows_lds = (w & 2 ? v_lds1 : k_lds1) + (w & 1) * (32 * D * 2);
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
+      perm_lds[w][u * 64 + lane] = (uint8_t)entry[u];
+      from_lds[w][entry[u]] = (uint8_t)(2 * first[u]);
+    }
+    auto swz = [](int row) { return D == 64 ? (row >> 1) & 7 : row & 15; };
+#pragma unroll
+    for (int j = 0; j < QU; ++j) {
+      const int row = (j * 64 + lane) / CH, chunk = lane % CH;
+      *(u32x4*)(rows_lds + row * (D * 2) + ((chunk ^ swz(row)) << 4)) = qx[j];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t flip = swz(lq) * 0x10101010u;       // chunk ^ x is offset ^ 16 x, for four channels at once
+    const char* row = rows_lds + lq * (D * 2);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const u32x2 f = *(const u32x2*)&from_lds[w][16 * s + 8 * hh];
+      const uint32_t at[2] = {(f[0] & 0xfefefefeu) ^ flip, (f[1] & 0xfefefefeu) ^ flip};
+#pragma unroll
+      for (int j = 0; j < 8; ++j) qop[s][j] = *(const bf16*)(row + ((at[j >> 2] >> (8 * (j & 3))) & (2 * D - 1)));
+      if (active) *(bf16x8*)(qrep + row_off + (2 * s + hh) * 8) = qop[s];
+    }
+  }
   f32x16 neg_d;
 #pragma unroll
   for (int i = 0; i < 16; ++i) neg_d[i] = dl;
@@ -396,14 +400,9 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
     for (int i = 0; i < 16; ++i) stage[lq * D + ((32 * cb + acc_row(i, hh)) ^ lq)] = dqacc[cb][i];
-  const int G = D / n_groups;
-  {
-    const int blk = (r0 + 32 * w) / Br;   // a wave's 32 rows lie in one Q block (Br is a multiple of 32)
-    const uint8_t* pr = perm ? perm + (bh * Tq + min(blk, Tq - 1)) * D : nullptr;
-    for (int i = lane; i < D; i += 64) {
-      perm_lds[w][i] = pr ? (pr[i] & (D - 1)) : (uint8_t)i;
-      group_lds[w][i] = 255;
-    }
+  for (int i = lane; i < D; i += 64) {
+    if (!perm) perm_lds[w][i] = (uint8_t)i;
+    group_lds[w][i] = 255;
   }
   __syncthreads();
   for (int j = lane; j < n_groups; j += 64) group_lds[w][perm_lds[w][j * G]] = (uint8_t)j;
@@ -1059,10 +1058,9 @@ hipError_t launch_attn_bf16_bwd(const void* q, const void* k, const void* v, con
   const int Tq = (pb.N + pb.Br - 1) / pb.Br;
   const int Twq = (pb.N + kBwdRows - 1) / kBwdRows;
   const int Twk = (pb.Nk + kBwdRows - 1) / kBwdRows;
-  const long long prep_units = (long long)pb.B * pb.H * Tq;
   const long long q_units = (long long)pb.B * pb.H * Twq;
   const long long k_units = (long long)pb.B * pb.Hkv * Twk;
-  if (prep_units > 0x7fffffffLL || q_units > 0x7fffffffLL || k_units > 0x7fffffffLL / 16) return hipErrorInvalidValue;
+  if (q_units > 0x7fffffffLL || k_units > 0x7fffffffLL / 16) return hipErrorInvalidValue;
   if ((pb.d != 64 && pb.d != 128) || pb.Br % 32 != 0 || pb.d % pb.n_groups != 0) return hipErrorInvalidValue;
   // tiles are addressed by 32-bit byte offsets inside a head
   if ((size_t)pb.N * pb.d * 2 >= 0x7fffffffULL || (size_t)pb.Nk * pb.d * 2 >= 0x7fffffffULL) return hipErrorInvalidValue;
@@ -1093,10 +1091,9 @@ hipError_t launch_attn_bf16_bwd(const void* q, const void* k, const void* v, con
   const int dkv_order = pb.causal && k_units * hsplit <= kBalancedUnits ? kLongestFirst : kHeadMajor;
 #define DA_BWD(DD)                                                                                                   \
   do {                                                                                                               \
-    hipLaunchKernelGGL((bwd_prepare_kernel<DD>), dim3((unsigned)prep_units), dim3(kBwdThreads), 0, stream,           \
-                       (const bf16*)q, (const bf16*)o, (const bf16*)dout, lse, table, qrep, delta, lse2, pb.N, pb.Br, Tq, n_groups); \
-    hipLaunchKernelGGL((bwd_dq_kernel<DD>), dim3((unsigned)q_units), dim3(kBwdThreads), 0, stream, qx, (const bf16*)k, \
-                       (const bf16*)v, (const bf16*)dout, lse2, delta, (bf16*)dq, table, pb.H, pb.Hkv, pb.N, pb.Nk,   \
+    hipLaunchKernelGGL((bwd_dq_kernel<DD>), dim3((unsigned)q_units), dim3(kBwdThreads), 0, stream, (const bf16*)q,   \
+                       (const bf16*)k, (const bf16*)v, (const bf16*)o, (const bf16*)dout, lse, qrep, lse2, delta,     \
+                       (bf16*)dq, table, pb.H, pb.Hkv, pb.N, pb.Nk,                                                  \
                        pb.Br, Tq, Twq, n_groups, pb.causal, dq_order, pb.scale);                                               \
     hipLaunchKernelGGL((bwd_dkv_kernel<DD>), dim3((unsigned)(k_units * hsplit)), dim3(kBwdThreads), 0, stream, qx,   \
                        (const bf16*)k, (const bf16*)v, (const bf16*)dout, lse2, delta, (bf16*)dk, (bf16*)dv, part,    \
