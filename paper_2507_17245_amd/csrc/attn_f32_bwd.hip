@@ -14,8 +14,7 @@
 // Sec. 3.3). Exact attention is the case of one channel per group.
 //
 //   bwd_delta_kernel  D_i of every row, left at the head of dq, which the last kernel overwrites
-//   bwd_dkv_kernel    one workgroup per (kv head, 32 keys), lane = key, K and V rows resident as
-//                     operands; its waves deal the 32-row query tiles of all query heads of the kv head
+//   bwd_dkv_kernel    one workgroup per (kv head, 32 keys), lane = key, K and V rows resident; its waves deal the 32-row query tiles of all query heads of the kv head
 //                     out among themselves. Contracts over d with Q~ = Q whose channels are
 //                     replaced by their group's sampled one (S^ = Q~ K^T, dK = scale dS^T Q~: every
 //                     member of a group receives its group's column), gathered from global memory.
@@ -26,9 +25,8 @@
 // The waves' partial sums meet in LDS once, at the end, in a fixed order: as in the forward no wave waits
 // for another before that, and few rows still give every SIMD work. Bound: the matrix
 // instruction (64 cycles for 4096 FLOP), 7 products over d per (query, key) pair, 6 with groups of two.
-// Measured (B1 H8 N2048 d64 n_groups 32): delta 4, dK/dV 180, dQ 84 us, 96 and 102 TFLOP/s of the 157 the
-// instruction can reach (float multiply-adds on the vector ALUs: dK/dV 2740, dQ 1980 us). dK/dV needs
-// more than half a SIMD's registers (resident K, V and both sums), so one wave per SIMD has to hide its own waits.
+// Measured (B1 H8 N2048 d64 n_groups 32): delta 4, dK/dV 175, dQ 86 us, 98 and 100 TFLOP/s of the 157 the
+// instruction can reach (float multiply-adds on the vector ALUs: dK/dV 2740, dQ 1980 us).
 #include "f32_tiles.h"
 
 namespace da {
@@ -85,6 +83,16 @@ __device__ inline void row_product(const float* row, int hh, const float (&b)[D 
     for (int e = 0; e < 4; ++e) acc = mfma(x[e], b[c + e], acc);
   }
 }
+// the same with the operand b as a row in LDS
+template <int D>
+__device__ inline void row_product(const float* row, int hh, const float* b, f32x16& acc) {
+#pragma unroll
+  for (int c = 0; c < D / 2; c += 4) {
+    const f32x4 x = *(const f32x4*)&row[hh * (D / 2) + c], y = *(const f32x4*)&b[hh * (D / 2) + c];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = mfma(x[e], y[e], acc);
+  }
+}
 // acc[mb] += (tile transposed) x (accumulator p as operand): lane m owns channels NB*m .. NB*m + NB-1
 template <int D>
 __device__ inline void column_product(const float* tile, int lq, int hh, const f32x16& p, f32x16 (&acc)[D / 32]) {
@@ -133,16 +141,22 @@ __global__ __launch_bounds__(kThreads) void bwd_delta_kernel(const float* __rest
 }
 
 // ------------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(kThreads, 1) void bwd_dkv_kernel(
+// W waves. Eight at d = 64, two per SIMD, with the K and V rows that all of them multiply by in LDS; four, with K and V
+// in registers, at d = 128, where their tiles fill the LDS, and for fewer than eight query tiles, which would
+// leave waves without any (backward of d = 64, four | eight waves: H8 N2048 248 | 237 us, H8 Hkv2 N1024 causal 189 | 171,
+// H8 N256 29.1 | 27.9, H1 N64 17.2 | 17.7).
+template <int D, int W>
+__global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ dout,
     const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dk, float* __restrict__ dv,
     const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Br, int Tq, int n_groups, int causal, float scale) {
   constexpr int NB = D / 32, RS = Tile<D>::RS;
-  __shared__ __attribute__((aligned(16))) float q_lds[kWaves][kTile * RS];    // Q~ tile of each wave, at the end its dK
-  __shared__ __attribute__((aligned(16))) float do_lds[kWaves][kTile * RS];   // dO tile, at the end dV
-  __shared__ __attribute__((aligned(16))) float stat_lds[kWaves][2][kTile];   // lse * log2(e), D_i
-  __shared__ __attribute__((aligned(16))) uint8_t map_lds[kWaves][2][D];
+  constexpr bool SHARED = W == 8;
+  __shared__ __attribute__((aligned(16))) float q_lds[W][kTile * RS];    // Q~ tile of each wave, at the end its dK
+  __shared__ __attribute__((aligned(16))) float do_lds[W][kTile * RS];   // dO tile, at the end dV
+  __shared__ __attribute__((aligned(16))) float kv_lds[SHARED ? 2 : 1][SHARED ? kTile * RS : 4];
+  __shared__ __attribute__((aligned(16))) float stat_lds[W][2][kTile];   // lse * log2(e), D_i
+  __shared__ __attribute__((aligned(16))) uint8_t map_lds[W][2][D];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -200,11 +214,18 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkv_kernel(
   if (it < n_it) {
     if (perm) load_map(it);
     load_tile(it);
-    if (perm && it + kWaves < n_it) load_map(it + kWaves);
+    if (perm && it + W < n_it) load_map(it + W);
   }
 
-  float kop[D / 2], vop[D / 2];
-  {
+  float kop[SHARED ? 1 : D / 2], vop[SHARED ? 1 : D / 2];
+  if constexpr (SHARED) {
+    if (w < 2) {
+      Tile<D> x;
+      x.load(head_rsrc((w ? v : k) + (size_t)bk * Nk * D, (unsigned)Nk * D * 4), t, lane);
+      x.store(kv_lds[w], lane);
+    }
+    __syncthreads();
+  } else {
     const __amdgpu_buffer_rsrc_t k_rsrc = head_rsrc(k + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
     const __amdgpu_buffer_rsrc_t v_rsrc = head_rsrc(v + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
 #pragma unroll
@@ -222,22 +243,27 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkv_kernel(
     zero(dvacc[mb]);
   }
 
-  for (; it < n_it; it += kWaves) {
+  for (; it < n_it; it += W) {
     const int i0 = tile_of(it) * kTile;
     wave_order();   // the reads of the previous tile come first
     qt.store(q_lds[w], lane);
     dt.store(do_lds[w], lane);
     stat_lds[w][hh][lq] = hh ? delta_reg : lse_reg * kLog2e;
-    if (it + kWaves < n_it) {
-      load_tile(it + kWaves);
-      if (perm && it + 2 * kWaves < n_it) load_map(it + 2 * kWaves);
+    if (it + W < n_it) {
+      load_tile(it + W);
+      if (perm && it + 2 * W < n_it) load_map(it + 2 * W);
     }
     wave_order();
     f32x16 s, dp;
     zero(s);
     zero(dp);
-    row_product<D>(&q_lds[w][lq * RS], hh, kop, s);
-    row_product<D>(&do_lds[w][lq * RS], hh, vop, dp);
+    if constexpr (SHARED) {
+      row_product<D>(&q_lds[w][lq * RS], hh, &kv_lds[0][lq * RS], s);
+      row_product<D>(&do_lds[w][lq * RS], hh, &kv_lds[1][lq * RS], dp);
+    } else {
+      row_product<D>(&q_lds[w][lq * RS], hh, kop, s);
+      row_product<D>(&do_lds[w][lq * RS], hh, vop, dp);
+    }
 #pragma unroll
     for (int i4 = 0; i4 < 4; ++i4) {
       const f32x4 l2 = *(const f32x4*)&stat_lds[w][0][8 * i4 + 4 * hh], dl = *(const f32x4*)&stat_lds[w][1][8 * i4 + 4 * hh];
@@ -265,12 +291,12 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dkv_kernel(
   store_columns<D>(&q_lds[w][lq * RS], hh, dkacc);
   store_columns<D>(&do_lds[w][lq * RS], hh, dvacc);
   __syncthreads();
-  for (int i = tid; i < kTile * D / 4; i += kThreads) {
+  for (int i = tid; i < kTile * D / 4; i += W * 64) {
     const int row = i / (D / 4), c = i % (D / 4) * 4;
     if (n0 + row < Nk) {
       f32x4 x = *(const f32x4*)&q_lds[0][row * RS + c], y = *(const f32x4*)&do_lds[0][row * RS + c];
 #pragma unroll
-      for (int j = 1; j < kWaves; ++j) {
+      for (int j = 1; j < W; ++j) {
         x += *(const f32x4*)&q_lds[j][row * RS + c];
         y += *(const f32x4*)&do_lds[j][row * RS + c];
       }
@@ -479,8 +505,16 @@ hipError_t launch_d(const float* q, const float* k, const float* v, const float*
   const int n_groups = distr ? pb.n_groups : D;
   float* delta = dq;   // one float per row: dq is overwritten after its last use
   hipLaunchKernelGGL((bwd_delta_kernel<D>), dim3((unsigned)d_units), dim3(kThreads), 0, stream, o, dout, delta, rows);
-  hipLaunchKernelGGL((bwd_dkv_kernel<D>), dim3((unsigned)k_units), dim3(kThreads), 0, stream, q, k, v, dout, lse, delta, dk, dv,
-                     table, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, n_groups, pb.causal, pb.scale);
+#define DA_DKV(W)                                                                                                          \
+  hipLaunchKernelGGL((bwd_dkv_kernel<D, W>), dim3((unsigned)k_units), dim3(W * 64), 0, stream, q, k, v, dout, lse, delta, dk, dv, \
+                     table, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, n_groups, pb.causal, pb.scale)
+  if constexpr (D == 64) {
+    if ((long long)(pb.H / pb.Hkv) * ((pb.N + kTile - 1) / kTile) >= 8) DA_DKV(8);
+    else DA_DKV(4);
+  } else {
+    DA_DKV(4);
+  }
+#undef DA_DKV
 #define DA_DQ(GG)                                                                                                          \
   hipLaunchKernelGGL((bwd_dq_kernel<D, GG>), dim3((unsigned)q_units), dim3(kThreads), 0, stream, q, k, v, o, dout, lse, dq, \
                      table, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, n_groups, pb.causal, pb.scale)

@@ -31,10 +31,10 @@ def test_float_forward(d, N, Nk, causal, side, Bc, G):
         _forward(cfg, distr=False)
 
 
-# Float backward: 32-row tiles on both sides, dealt out to 4 waves; groups of 2 and 4 have products
+# Float backward: 32-row tiles on both sides, dealt out to 4 waves (dK/dV at d = 64 from 8 query tiles on: 8); groups of 2 and 4 have products
 # over the groups, other sizes over the channels. Bound: float rounding, the parity bar of the backward tests.
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("N,Nk,causal", [(1, 1, False), (31, 33, True), (33, 31, False), (129, 290, True)])
+@pytest.mark.parametrize("N,Nk,causal", [(1, 1, False), (31, 33, True), (33, 31, False), (96, 97, False), (97, 33, False), (129, 290, True), (289, 320, True)])
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 def test_float_backward(d, N, Nk, causal, G):
     import gpu_util as U
