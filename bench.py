@@ -269,7 +269,7 @@ def main():
 
     def backward_table(cfg, tensors, steps):
         """The backward pass for bf16 tensors on the matrix cores (gradient with the grouping held
-        fixed), DistrAttention and exact: three launches (prepare, dQ, dK/dV; a reduction when the
+        fixed), DistrAttention and exact: two launches (dQ, dK/dV; one for short sequences; a reduction when the
         dK/dV launch is split over query heads); the two main kernels execute seven products of d
         multiply-adds per visible (query, key) pair."""
         q, k, v = tensors

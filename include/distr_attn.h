@@ -97,7 +97,7 @@ typedef struct {
   int side;             /* 0: sample Q columns, fuse K columns, one grouping per Q block (Sec. 3.2-3.3,
                            the form the paper builds). 1: the mirrored form of Sec. 3.1 / Fig. 4 right:
                            sample K columns, fuse Q columns, one grouping per K block of Bc rows taken
-                           from that K block; Bc in {32, 64, 128}; float arithmetic on the vector ALUs
+                           from that K block; Bc in {32, 64, 128}; float arithmetic
                            for both dtypes (bf16 tensors are converted on load); perm_in / perm_out /
                            hash_out are then [B][Hkv][Tk][d]                                        */
   float *lse_out;       /* optional device [B][H][N] float: natural logarithm of the sum over the visible
@@ -138,7 +138,7 @@ int distr_attn_exact_fwd_ex(const void *q, const void *k, const void *v, void *o
  * one channel per group (Sec. 2.1).
  * bf16 tensors: matrix-core kernels (bf16 operands, fp32 accumulate; P and dS^ are rounded to bf16
  * before the products that take them), d in {64, 128}, any n_groups that divides d. float tensors:
- * float arithmetic on the vector ALUs (a reference-precision path).
+ * float arithmetic on the float matrix instruction (a reference-precision path).
  * q, k, v, p: as given to the forward; o: its output; lse: its lse_out; dout [B][H][N][d]: gradient
  * of the loss with respect to o, same dtype. Written: dq [B][H][N][d], dk and dv [B][Hkv][Nk][d]
  * (p->dtype, device, 16-byte aligned, distinct from every input and from each other). The grouping is recomputed

@@ -157,7 +157,7 @@ bool attn_bf16_short(const Problem& pb, int distr);
 hipError_t launch_attn_bf16_short(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                                   const Problem& pb, int distr, hipStream_t stream);
 hipError_t launch_attn_bf16_combine(void* o, const Problem& pb, hipStream_t stream);
-// Backward in float arithmetic on the vector ALUs (float tensors): dq [B][H][N][d], dk and dv
+// Backward in float arithmetic (float tensors): dq [B][H][N][d], dk and dv
 // [B][Hkv][Nk][d] from the forward's inputs, its output o, the output gradient dout and the
 // forward's row statistics lse; perm as in launch_attn_f32.
 hipError_t launch_attn_f32_bwd(const void* q, const void* k, const void* v, const void* o, const void* dout,
