@@ -32,7 +32,8 @@ bool attn_bf16_supported(const Problem& pb, int distr) {
 // its launch costs 4 us; the fused kernel saves about a seventh of 4 d FLOP per visible (query, key) pair
 // (0.5 fs d at 1.1 PFLOP/s): equal at 1570 visible rows per key plus the launch's share.
 // Measured, Q~ K^T | fused: B64 H12 N197 d64 40 | 46 us; H16 N1024 d64 causal 20 | 22; H16 N4096 d64 causal 53 | 54;
-// H32 Hkv8 N4096 d64 causal 84 | 77; H16 N2048 d128 causal 47 | 49; N8192 282 | 253; N200 Nk32768 d128 109 | 500.
+// H32 Hkv8 N4096 d64 causal 84 | 77; H16 N2048 d128 causal 40 | 49; H8 N852 d128
+// Br256 G4 35 | 38; H16 N8192 d128 causal 282 | 253; N200 Nk32768 d128 109 | 500.
 bool attn_bf16_replicated(const Problem& pb) {
   if (attn_bf16_few_rows(pb) || attn_bf16_short(pb, 1)) return true;
   const double rows = (double)(pb.H / pb.Hkv) * pb.N * (pb.causal ? 1.0 - 0.5 * pb.N / pb.Nk : 1.0);

@@ -493,16 +493,52 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
     // Q~: the sampled channel of every channel's group, by way of a map in LDS
     uint8_t* from_lds = perm_lds + D;
     const int group = D / n_groups;
-    if (tid < D) from_lds[perm_lds[tid]] = perm_lds[tid / group * group];
-    __syncthreads();
-    const bf16* qrow = qh + (size_t)q_ld * D;
+    if constexpr (QSTAGE) {
+      if (tid < D) from_lds[perm_lds[tid]] = perm_lds[tid / group * group];
+      __syncthreads();
 #pragma unroll
-    for (int s = 0; s < C::KSTEPS; ++s)
+      for (int s = 0; s < C::KSTEPS; ++s)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int ch = from_lds[16 * s + 8 * hh + j] & (D - 1);
-        qop[s][j] = QSTAGE ? q_staged(wave * 32 + lq, ch) : qrow[ch];
+        for (int j = 0; j < 8; ++j) qop[s][j] = q_staged(wave * 32 + lq, from_lds[16 * s + 8 * hh + j] & (D - 1));
+    } else {
+      // The wave's rows pass through its part of the K buffers, RPR at a time (16-byte chunks exchanged by the row; its
+      // LDS accesses take effect in its order): gathered from global memory, two bytes per load and lane, they cost a
+      // launch of few blocks several microseconds (H8 N852 causal Br256 45 -> 35 us, H16 N1024 Br128 32 -> 27). The map holds byte offsets; chunk ^ x is offset ^ 16 x.
+      constexpr int PART = C::KX_BYTES / (C::NW / 2), RPR = PART / C::ROWB < 32 ? PART / C::ROWB : 32;
+      static_assert(RPR >= 4 && 32 % RPR == 0 && D == 128, "whole loads per round");
+      u32x4 x[8];                          // load j: rows 4*j .. 4*j + 3
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        x[j] = *(const u32x4*)(qh + (size_t)min(qw0 + 4 * j + (lane >> 4), N - 1) * D + (lane & 15) * 8);
+      if (tid < D) from_lds[perm_lds[tid]] = (uint8_t)(2 * perm_lds[tid / group * group]);
+      __syncthreads();
+      char* mine = (wave & 1 ? kx_lds1 : kx_lds0) + (wave >> 1) * (RPR * C::ROWB);
+      const int row = lq % RPR;
+      const uint32_t flip = (row & 15) * 0x10101010u;
+#pragma unroll
+      for (int r = 0; r < 32 / RPR; ++r) {
+#pragma unroll
+        for (int j = 0; j < RPR / 4; ++j) {
+          const int dst = 4 * j + (lane >> 4);
+          *(u32x4*)(mine + dst * C::ROWB + (((lane & 15) ^ (dst & 15)) << 4)) = x[r * (RPR / 4) + j];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int s = 0; s < C::KSTEPS; ++s) {
+          const u32x2 f = *(const u32x2*)&from_lds[16 * s + 8 * hh];
+          const uint32_t at[2] = {(f[0] & 0xfefefefeu) ^ flip, (f[1] & 0xfefefefeu) ^ flip};
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const bf16 y = *(const bf16*)(mine + row * C::ROWB + ((at[j >> 2] >> (8 * (j & 3))) & 255));
+            qop[s][j] = RPR == 32 || lq / RPR == r ? y : qop[s][j];
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
       }
+      __syncthreads();                     // K tiles may land
+    }
   } else if constexpr (FUSED) {
     // (staged block: a row past N reads as zeros and is never stored)
     const bf16* qrow = qh + (size_t)q_ld * D;
