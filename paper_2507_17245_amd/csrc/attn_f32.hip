@@ -16,7 +16,7 @@
 // waits for another before that, and a problem of few rows still fills the chip: sharing tiles
 // among waves of different rows instead would leave N = 256 with 8 working waves.
 // Measured (B1 H8 N2048 d64 n_groups 32): 71 us, 92 TFLOP/s of the 157 the instruction can reach
-// (float multiply-adds on the vector ALUs, a thread quad per row: 1430 us); mirrored 78 us (1439);
+// (float multiply-adds on the vector ALUs, a thread quad per row: 1430 us); mirrored 73 us (1439);
 // B1 H1 N256: 9 us (162).
 //
 // Score product, by MODE:
@@ -32,6 +32,7 @@
 //                summed: every K block needs its own fused queries (the reloading Sec. 3.3 gives as
 //                the reason for sampling Q instead), gathered from the Q rows in LDS. kKeyFull
 //                replaces every key channel by its group's sampled one instead.
+#include <cfloat>
 #include <type_traits>
 
 #include "f32_tiles.h"
@@ -46,7 +47,7 @@ template <typename E, int D, int G, int MODE, int NW>
 __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     const E* __restrict__ q, const E* __restrict__ k, const E* __restrict__ v, E* __restrict__ o,
     const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Br, int Tq, int Tw, int n_groups,
-    int causal, float scale_log2e, int Bc, float* __restrict__ lse) {
+    int causal, float scale, int Bc, float* __restrict__ lse) {
   constexpr bool kMirrored = MODE == kKeyFull || MODE == kKeyFused;
   constexpr bool kFused = MODE == kQueryFused || MODE == kKeyFused;
   constexpr int T = NW * 64;
@@ -145,7 +146,10 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
   f32x16 oacc[NB];
 #pragma unroll
   for (int mb = 0; mb < NB; ++mb) zero(oacc[mb]);
-  float m_run = -1e30f, l_run = 0.0f;   // exp2 domain; l over this lane's half of the keys
+  // Reference and scores stay unscaled until their difference is taken: exact to the last bit of the difference
+  // whatever their size (one fused multiply-add against a scaled reference keeps the rounding of the reference).
+  float m_run = -FLT_MAX, l_run = 0.0f;   // l over this lane's half of the keys
+  const float scale_log2e = scale * 1.4426950408889634f;
   const int q_abs = r0 + lq;
   const int lim = causal ? min(q_abs + shift, Nk - 1) : Nk - 1;   // last key this row sees
 
@@ -227,26 +231,26 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     }
 
     // ---- scores -----------------------------------------------------------------------------------
-    f32x16 sacc;
-    zero(sacc);
+    ChannelSum<HS> acc;
     if constexpr (kMirrored) {
 #pragma unroll
-      for (int s = 0; s < HS; ++s) sacc = mfma(kt[lq * RS + koff[s]], qop[s], sacc);
+      for (int s = 0; s < HS; ++s) acc.step(s, kt[lq * RS + koff[s]], qop[s]);
     } else {
 #pragma unroll
       for (int c = 0; c < D / 2; c += 4) {
         const f32x4 x = *(const f32x4*)&kt[lq * RS + hh * (D / 2) + c];
         if constexpr (MODE == kQueryFull) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) sacc = mfma(x[e], qop[c + e], sacc);
+          for (int e = 0; e < 4; ++e) acc.step(c + e, x[e], qop[c + e]);
         } else if constexpr (G == 2) {
-          sacc = mfma(x[0] + x[1], qop[c / 2], sacc);
-          sacc = mfma(x[2] + x[3], qop[c / 2 + 1], sacc);
+          acc.step(c / 2, x[0] + x[1], qop[c / 2]);
+          acc.step(c / 2 + 1, x[2] + x[3], qop[c / 2 + 1]);
         } else {
-          sacc = mfma(((x[0] + x[1]) + x[2]) + x[3], qop[c / 4], sacc);
+          acc.step(c / 4, ((x[0] + x[1]) + x[2]) + x[3], qop[c / 4]);
         }
       }
     }
+    f32x16 sacc = acc.sum();
     const int n0 = tile * kTile;
     if (n0 + kTile > Nk || (causal && n0 + kTile - 1 > r0 + shift)) {
 #pragma unroll
@@ -257,9 +261,9 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     float mt = sacc[0];
 #pragma unroll
     for (int i = 1; i < 16; ++i) mt = fmaxf(mt, sacc[i]);
-    const float m_new = fmaxf(m_run, half_swap_max(mt) * scale_log2e);
+    const float m_new = fmaxf(m_run, half_swap_max(mt));
     if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
       l_run *= alpha;
 #pragma unroll
       for (int mb = 0; mb < NB; ++mb)
@@ -267,12 +271,15 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
         for (int i = 0; i < 16; ++i) oacc[mb][i] *= alpha;
       m_run = m_new;
     }
-    float ps[16];
+    float ps[16], sum0 = 0.0f, sum1 = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      ps[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], scale_log2e, -m_run));
-      l_run += ps[i];
+    for (int i = 0; i < 16; i += 2) {
+      ps[i] = __builtin_amdgcn_exp2f((sacc[i] - m_run) * scale_log2e);
+      ps[i + 1] = __builtin_amdgcn_exp2f((sacc[i + 1] - m_run) * scale_log2e);
+      sum0 += ps[i];
+      sum1 += ps[i + 1];
     }
+    l_run += sum0 + sum1;
     // ---- O^T += V^T P^T -----------------------------------------------------------------------------
 #pragma unroll
     for (int i = 0; i < 16; ++i)
@@ -295,8 +302,8 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
   for (int j = 1; j < NW; ++j) m_all = fmaxf(m_all, stat_lds[j][0][lq]);
   float l_all = 0.0f;
 #pragma unroll
-  for (int j = 0; j < NW; ++j) l_all += stat_lds[j][1][lq] * __builtin_amdgcn_exp2f(stat_lds[j][0][lq] - m_all);
-  const float weight = __builtin_amdgcn_exp2f(m_run - m_all) / l_all;
+  for (int j = 0; j < NW; ++j) l_all += stat_lds[j][1][lq] * __builtin_amdgcn_exp2f((stat_lds[j][0][lq] - m_all) * scale_log2e);
+  const float weight = __builtin_amdgcn_exp2f((m_run - m_all) * scale_log2e) / l_all;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int m = acc_row(i, hh);
@@ -308,8 +315,9 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
       *(f32x4*)&kt[lq * RS + m * 4] = x;
     }
   }
-  // row statistics for a backward pass: ln(sum of exp(score)) = ln 2 * (reference + log2(sum))
-  if (lse && w == 0 && hh == 0 && q_abs < N) lse[(size_t)bh * N + q_abs] = 0.6931471805599453f * (m_all + __builtin_log2f(l_all));
+  // row statistics for a backward pass: ln(sum of exp(score)) = rounded reference (see scaled_plus) + ln(sum)
+  if (lse && w == 0 && hh == 0 && q_abs < N)
+    lse[(size_t)bh * N + q_abs] = __builtin_fmaf(__builtin_log2f(l_all), 0.6931471805599453f, m_all * scale);
   __syncthreads();
   for (int i = tid; i < kTile * D / 4; i += T) {
     const int row = i / (D / 4), c = i % (D / 4) * 4;
@@ -334,7 +342,7 @@ hipError_t launch_one(const void* q, const void* k, const void* v, void* o, cons
   const int Tq = (pb.N + pb.Br - 1) / pb.Br, Tw = (pb.N + kTile - 1) / kTile;
   hipLaunchKernelGGL((attn_f32_kernel<E, D, G, MODE, NW>), dim3((unsigned)((long long)pb.B * pb.H * Tw)), dim3(NW * 64), 0, stream,
                      (const E*)q, (const E*)k, (const E*)v, (E*)o, perm, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, Tw, n_groups,
-                     pb.causal, pb.scale * 1.4426950408889634f, pb.Bc, pb.lse);
+                     pb.causal, pb.scale, pb.Bc, pb.lse);
   return hipGetLastError();
 }
 

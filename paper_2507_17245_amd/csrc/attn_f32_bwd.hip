@@ -15,9 +15,10 @@
 //
 //   bwd_delta_kernel  D_i of every row, left at the head of dq, which the last kernel overwrites
 //   bwd_dkv_kernel    one workgroup per (kv head, 32 keys), lane = key, K and V rows resident; its waves deal the 32-row query tiles of all query heads of the kv head
-//                     out among themselves. Contracts over d with Q~ = Q whose channels are
-//                     replaced by their group's sampled one (S^ = Q~ K^T, dK = scale dS^T Q~: every
-//                     member of a group receives its group's column), gathered from global memory.
+//                     out among themselves. Q~ = Q whose channels are replaced by their group's
+//                     sampled one, gathered from global memory (dK = scale dS^T Q~: every member of a
+//                     group receives its group's column). S^ over the groups of 2 or 4 channels, as in
+//                     the other kernels, else Q~ K^T.
 //   bwd_dq_kernel     one workgroup per 32 query rows, lane = query row, waves deal the key tiles
 //                     out. Groups of 2 and 4 channels: the K tile lies in LDS in sorted channel order,
 //                     members adjacent and summed as they are read, S^ and dQ_r contract over
@@ -25,8 +26,10 @@
 // The waves' partial sums meet in LDS once, at the end, in a fixed order: as in the forward no wave waits
 // for another before that, and few rows still give every SIMD work. Bound: the matrix
 // instruction (64 cycles for 4096 FLOP), 7 products over d per (query, key) pair, 6 with groups of two.
-// Measured (B1 H8 N2048 d64 n_groups 32): delta 4, dK/dV 175, dQ 86 us, 98 and 100 TFLOP/s of the 157 the
+// Measured (B1 H8 N2048 d64 n_groups 32): delta 4, dK/dV 174, dQ 90 us, 87 and 95 TFLOP/s of the 157 the
 // instruction can reach (float multiply-adds on the vector ALUs: dK/dV 2740, dQ 1980 us).
+#include <type_traits>
+
 #include "f32_tiles.h"
 
 namespace da {
@@ -73,25 +76,53 @@ struct Tile {
   }
 };
 
-// acc += (tile rows as lanes) x (operand b): contraction over the channels hh*D/2 + s of step s
+// dP = dO V^T. (64 channels: one chain is precise enough, and the chains' joints cost 2 % of the backward.)
 template <int D>
-__device__ inline void row_product(const float* row, int hh, const float (&b)[D / 2], f32x16& acc) {
+using DpSum = typename std::conditional<D == 64, OneChain, ChannelSum<D / 2>>::type;
+
+// (tile rows as lanes) x (operand b): contraction over the channels hh*D/2 + s of step s
+template <int D, typename SUM = ChannelSum<D / 2>>
+__device__ inline f32x16 row_product(const float* row, int hh, const float (&b)[D / 2]) {
+  SUM acc;
 #pragma unroll
   for (int c = 0; c < D / 2; c += 4) {
     const f32x4 x = *(const f32x4*)&row[hh * (D / 2) + c];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc = mfma(x[e], b[c + e], acc);
+    for (int e = 0; e < 4; ++e) acc.step(c + e, x[e], b[c + e]);
   }
+  return acc.sum();
 }
 // the same with the operand b as a row in LDS
-template <int D>
-__device__ inline void row_product(const float* row, int hh, const float* b, f32x16& acc) {
+template <int D, typename SUM = ChannelSum<D / 2>>
+__device__ inline f32x16 row_product(const float* row, int hh, const float* b) {
+  SUM acc;
 #pragma unroll
   for (int c = 0; c < D / 2; c += 4) {
     const f32x4 x = *(const f32x4*)&row[hh * (D / 2) + c], y = *(const f32x4*)&b[hh * (D / 2) + c];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc = mfma(x[e], y[e], acc);
+    for (int e = 0; e < 4; ++e) acc.step(c + e, x[e], y[e]);
   }
+  return acc.sum();
+}
+// contraction over groups of G channels: `order` is the block's sorted order, q a row of Q~, k a row of K
+template <int D, int G>
+__device__ inline f32x16 group_product(const float* q, const float* k, int hh, const uint8_t* order) {
+  ChannelSum<D / G / 2> acc;
+#pragma unroll
+  for (int c16 = 0; c16 < D / 2; c16 += 16) {
+    const u32x4 e4 = *(const u32x4*)&order[hh * (D / 2) + c16];
+#pragma unroll
+    for (int e = 0; e < 16; e += G) {
+      int ch[G];
+#pragma unroll
+      for (int m = 0; m < G; ++m) ch[m] = (e4[(e + m) >> 2] >> (8 * ((e + m) & 3))) & (D - 1);
+      float x = k[ch[0]];
+#pragma unroll
+      for (int m = 1; m < G; ++m) x += k[ch[m]];
+      acc.step((c16 + e) / G, q[ch[0]], x);
+    }
+  }
+  return acc.sum();
 }
 // acc[mb] += (tile transposed) x (accumulator p as operand): lane m owns channels NB*m .. NB*m + NB-1
 template <int D>
@@ -145,7 +176,10 @@ __global__ __launch_bounds__(kThreads) void bwd_delta_kernel(const float* __rest
 // in registers, at d = 128, where their tiles fill the LDS, and for fewer than eight query tiles, which would
 // leave waves without any (backward of d = 64, four | eight waves: H8 N2048 248 | 237 us, H8 Hkv2 N1024 causal 189 | 171,
 // H8 N256 29.1 | 27.9, H1 N64 17.2 | 17.7).
-template <int D, int W>
+// G: channels per group where the scores are summed over the groups, as the forward sums them (2, 4); 1: over the
+// channels, with Q~. P = exp(S - lse) then rests on the bits of S that lse was taken of: with S over the channels and lse
+// of sums over groups, scores of 25 put dK and dV 2.6 times as far from 64 bits.
+template <int D, int W, int G>
 __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ dout,
     const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dk, float* __restrict__ dv,
@@ -154,9 +188,10 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
   constexpr bool SHARED = W == 8;
   __shared__ __attribute__((aligned(16))) float q_lds[W][kTile * RS];    // Q~ tile of each wave, at the end its dK
   __shared__ __attribute__((aligned(16))) float do_lds[W][kTile * RS];   // dO tile, at the end dV
-  __shared__ __attribute__((aligned(16))) float kv_lds[SHARED ? 2 : 1][SHARED ? kTile * RS : 4];
-  __shared__ __attribute__((aligned(16))) float stat_lds[W][2][kTile];   // lse * log2(e), D_i
-  __shared__ __attribute__((aligned(16))) uint8_t map_lds[W][2][D];
+  __shared__ __attribute__((aligned(16))) float k_lds[SHARED || G > 1 ? kTile * RS : 4];
+  __shared__ __attribute__((aligned(16))) float v_lds[SHARED ? kTile * RS : 4];
+  __shared__ __attribute__((aligned(16))) float stat_lds[W][2][kTile];   // lse, D_i
+  __shared__ __attribute__((aligned(16))) uint8_t map_lds[W][3][D];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -168,8 +203,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
   const int b = bk / Hkv, hk = bk % Hkv, rep = H / Hkv;
   const int n0 = t * kTile, key = n0 + lq;
   const int shift = Nk - N;   // causal: query i sees key n iff n <= i + shift
-  const float sl2e = scale * kLog2e;
-  const int group = D / n_groups;
+  const int group = G > 1 ? G : D / n_groups;
 
   const int first = causal ? max(0, n0 - shift) / kTile : 0;   // first tile with a row that sees key n0
   const int tiles = (N + kTile - 1) / kTile - first;           // per query head
@@ -199,41 +233,49 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
   };
   Tile<D> qt, dt;
   float lse_reg, delta_reg;
-  auto load_tile = [&](int it) {
+  auto load_q = [&](int it) {
     const size_t bh = head_of(it);
     const int i0 = tile_of(it);
     const __amdgpu_buffer_rsrc_t q_rsrc = head_rsrc(q + bh * N * D, (unsigned)N * D * 4);
     if (perm) qt.gather(q_rsrc, i0, lane, sampled());
     else qt.load(q_rsrc, i0, lane);
-    dt.load(head_rsrc(dout + bh * N * D, (unsigned)N * D * 4), i0, lane);
     const int row = min(i0 * kTile + lq, N - 1);
     lse_reg = lse[bh * N + row];
     delta_reg = delta[bh * N + row];
   };
+  auto load_do = [&](int it) { dt.load(head_rsrc(dout + head_of(it) * N * D, (unsigned)N * D * 4), tile_of(it), lane); };
   int it = w;
   if (it < n_it) {
     if (perm) load_map(it);
-    load_tile(it);
+    load_q(it);
+    load_do(it);
     if (perm && it + W < n_it) load_map(it + W);
   }
 
-  float kop[SHARED ? 1 : D / 2], vop[SHARED ? 1 : D / 2];
-  if constexpr (SHARED) {
-    if (w < 2) {
+  float kop[SHARED || G > 1 ? 1 : D / 2], vop[SHARED ? 1 : D / 2];
+  const __amdgpu_buffer_rsrc_t k_rsrc = head_rsrc(k + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
+  const __amdgpu_buffer_rsrc_t v_rsrc = head_rsrc(v + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
+  if constexpr (SHARED || G > 1) {
+    if (w < (SHARED ? 2 : 1)) {
       Tile<D> x;
-      x.load(head_rsrc((w ? v : k) + (size_t)bk * Nk * D, (unsigned)Nk * D * 4), t, lane);
-      x.store(kv_lds[w], lane);
+      x.load(w ? v_rsrc : k_rsrc, t, lane);
+      x.store(w ? v_lds : k_lds, lane);
     }
     __syncthreads();
   } else {
-    const __amdgpu_buffer_rsrc_t k_rsrc = head_rsrc(k + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
-    const __amdgpu_buffer_rsrc_t v_rsrc = head_rsrc(v + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
 #pragma unroll
     for (int c = 0; c < D / 2; c += 4) {
       const f32x4 x = Q4::values(Q4::load(k_rsrc, (lq * D + hh * (D / 2) + c) * 4, n0 * (D * 4)));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) kop[c + e] = x[e];
+    }
+  }
+  if constexpr (!SHARED) {
+#pragma unroll
+    for (int c = 0; c < D / 2; c += 4) {
       const f32x4 y = Q4::values(Q4::load(v_rsrc, (lq * D + hh * (D / 2) + c) * 4, n0 * (D * 4)));
 #pragma unroll
-      for (int e = 0; e < 4; ++e) kop[c + e] = x[e], vop[c + e] = y[e];
+      for (int e = 0; e < 4; ++e) vop[c + e] = y[e];
     }
   }
   f32x16 dkacc[NB], dvacc[NB];
@@ -248,29 +290,29 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
     wave_order();   // the reads of the previous tile come first
     qt.store(q_lds[w], lane);
     dt.store(do_lds[w], lane);
-    stat_lds[w][hh][lq] = hh ? delta_reg : lse_reg * kLog2e;
+    stat_lds[w][hh][lq] = hh ? delta_reg : lse_reg;
+    if constexpr (G > 1) {   // this tile's sorted order, before the next tile's takes its place
+      if (lane < D / 4) ((uint32_t*)map_lds[w][2])[lane] = ((const uint32_t*)map_lds[w][0])[lane];
+    }
     if (it + W < n_it) {
-      load_tile(it + W);
+      load_q(it + W);
       if (perm && it + 2 * W < n_it) load_map(it + 2 * W);
     }
     wave_order();
     f32x16 s, dp;
-    zero(s);
-    zero(dp);
-    if constexpr (SHARED) {
-      row_product<D>(&q_lds[w][lq * RS], hh, &kv_lds[0][lq * RS], s);
-      row_product<D>(&do_lds[w][lq * RS], hh, &kv_lds[1][lq * RS], dp);
-    } else {
-      row_product<D>(&q_lds[w][lq * RS], hh, kop, s);
-      row_product<D>(&do_lds[w][lq * RS], hh, vop, dp);
-    }
+    if constexpr (G > 1) s = group_product<D, G>(&q_lds[w][lq * RS], &k_lds[lq * RS], hh, map_lds[w][2]);
+    else if constexpr (SHARED) s = row_product<D>(&q_lds[w][lq * RS], hh, &k_lds[lq * RS]);
+    else s = row_product<D>(&q_lds[w][lq * RS], hh, kop);
+    if (it + W < n_it) load_do(it + W);   // (only now: the registers were those of the sum)
+    if constexpr (SHARED) dp = row_product<D, DpSum<D>>(&do_lds[w][lq * RS], hh, &v_lds[lq * RS]);
+    else dp = row_product<D, DpSum<D>>(&do_lds[w][lq * RS], hh, vop);
 #pragma unroll
     for (int i4 = 0; i4 < 4; ++i4) {
-      const f32x4 l2 = *(const f32x4*)&stat_lds[w][0][8 * i4 + 4 * hh], dl = *(const f32x4*)&stat_lds[w][1][8 * i4 + 4 * hh];
+      const f32x4 ls = *(const f32x4*)&stat_lds[w][0][8 * i4 + 4 * hh], dl = *(const f32x4*)&stat_lds[w][1][8 * i4 + 4 * hh];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int i = 4 * i4 + e;
-        s[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], sl2e, -l2[e]));
+        s[i] = __builtin_amdgcn_exp2f(scaled_plus(s[i], scale, -ls[e]) * kLog2e);
         dp[i] = dp[i] - dl[e];
       }
     }
@@ -284,7 +326,13 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) dp[i] *= s[i];
     column_product<D>(do_lds[w], lq, hh, s, dvacc);
-    column_product<D>(q_lds[w], lq, hh, dp, dkacc);
+    // (a tile's dK is summed by itself first: many heads and rows would make the chain long)
+    f32x16 part[NB];
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb) zero(part[mb]);
+    column_product<D>(q_lds[w], lq, hh, dp, part);
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb) dkacc[mb] += part[mb];
   }
 
   wave_order();
@@ -334,7 +382,6 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dq_kernel(
   const int b = bh / H, hk = bh % H / (H / Hkv);
   const int r0 = t * kTile, q_abs = r0 + lq;
   const int shift = Nk - N;
-  const float sl2e = scale * kLog2e;
   const int group = D / n_groups;
 
   const size_t head = (size_t)bh * N * D;
@@ -383,7 +430,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dq_kernel(
   dl = half_swap_sum(dl);
 #pragma unroll
   for (int e = 0; e < 4; ++e) kdst[e] = map_lds[lane % (D / 4) * 4 + e] & (D - 1);
-  const float lse2 = lse[(size_t)bh * N + min(q_abs, N - 1)] * kLog2e;
+  const float lse_row = lse[(size_t)bh * N + min(q_abs, N - 1)];
   __syncthreads();   // the staged rows have been read
 
   f32x16 dqacc[NG];
@@ -399,27 +446,27 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dq_kernel(
       vt.load(v_rsrc, tile + kWaves, lane);
     }
     wave_order();
-    f32x16 s, dp;
-    zero(s);
-    zero(dp);
+    f32x16 s;
     if constexpr (G == 1) {
-      row_product<D>(&k_lds[w][lq * RS], hh, qop, s);
+      s = row_product<D>(&k_lds[w][lq * RS], hh, qop);
     } else {
+      ChannelSum<HS> acc;
 #pragma unroll
       for (int c = 0; c < D / 2; c += 4) {
         const f32x4 x = *(const f32x4*)&k_lds[w][lq * RS + hh * (D / 2) + c];
         if constexpr (G == 2) {
-          s = mfma(x[0] + x[1], qop[c / 2], s);
-          s = mfma(x[2] + x[3], qop[c / 2 + 1], s);
+          acc.step(c / 2, x[0] + x[1], qop[c / 2]);
+          acc.step(c / 2 + 1, x[2] + x[3], qop[c / 2 + 1]);
         } else {
-          s = mfma(((x[0] + x[1]) + x[2]) + x[3], qop[c / 4], s);
+          acc.step(c / 4, ((x[0] + x[1]) + x[2]) + x[3], qop[c / 4]);
         }
       }
+      s = acc.sum();
     }
-    row_product<D>(&v_lds[w][lq * RS], hh, doop, dp);
+    const f32x16 dp = row_product<D, DpSum<D>>(&v_lds[w][lq * RS], hh, doop);
     const int n0 = tile * kTile;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], sl2e, -lse2));
+    for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f(scaled_plus(s[i], scale, -lse_row) * kLog2e);
     if (n0 + kTile > Nk || (causal && n0 + kTile - 1 > r0 + shift)) {
 #pragma unroll
       for (int i = 0; i < 16; ++i)
@@ -505,21 +552,30 @@ hipError_t launch_d(const float* q, const float* k, const float* v, const float*
   const int n_groups = distr ? pb.n_groups : D;
   float* delta = dq;   // one float per row: dq is overwritten after its last use
   hipLaunchKernelGGL((bwd_delta_kernel<D>), dim3((unsigned)d_units), dim3(kThreads), 0, stream, o, dout, delta, rows);
-#define DA_DKV(W)                                                                                                          \
-  hipLaunchKernelGGL((bwd_dkv_kernel<D, W>), dim3((unsigned)k_units), dim3(W * 64), 0, stream, q, k, v, dout, lse, delta, dk, dv, \
+#define DA_DKV(W, GG)                                                                                                      \
+  hipLaunchKernelGGL((bwd_dkv_kernel<D, W, GG>), dim3((unsigned)k_units), dim3(W * 64), 0, stream, q, k, v, dout, lse, delta, dk, dv, \
                      table, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, n_groups, pb.causal, pb.scale)
+  const bool eight = D == 64 && (long long)(pb.H / pb.Hkv) * ((pb.N + kTile - 1) / kTile) >= 8;
+  const int G = D / n_groups;
   if constexpr (D == 64) {
-    if ((long long)(pb.H / pb.Hkv) * ((pb.N + kTile - 1) / kTile) >= 8) DA_DKV(8);
-    else DA_DKV(4);
+    if (eight && G == 2) DA_DKV(8, 2);
+    else if (eight && G == 4) DA_DKV(8, 4);
+    else if (eight) DA_DKV(8, 1);
+  }
+  if (eight) {
+  } else if (G == 2) {
+    DA_DKV(4, 2);
+  } else if (G == 4) {
+    DA_DKV(4, 4);
   } else {
-    DA_DKV(4);
+    DA_DKV(4, 1);
   }
 #undef DA_DKV
 #define DA_DQ(GG)                                                                                                          \
   hipLaunchKernelGGL((bwd_dq_kernel<D, GG>), dim3((unsigned)q_units), dim3(kThreads), 0, stream, q, k, v, o, dout, lse, dq, \
                      table, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, n_groups, pb.causal, pb.scale)
-  if (D / n_groups == 2) DA_DQ(2);
-  else if (D / n_groups == 4) DA_DQ(4);
+  if (G == 2) DA_DQ(2);
+  else if (G == 4) DA_DQ(4);
   else DA_DQ(1);
 #undef DA_DQ
   return hipGetLastError();

@@ -18,6 +18,50 @@ __device__ inline void zero(f32x16& x) {
 }
 __device__ inline f32x16 mfma(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 
+// A sum over STEPS contraction steps (all unrolled: `s` is known). ChannelSum takes it in two or four chains, for the
+// rounding of short sums: in one chain, scores of up to 25 put the output of exact attention 1.6 times (d = 64) and
+// twice (d = 128) as far from 64 bits as four partial sums per row do. Forward and backward sum alike, so that
+// P = exp(S - lse) is taken of the S that lse was. The chains run one by one (the empty asm wants a chain's sum before
+// the next one starts): several at once do not fit the registers (100 of them spilled).
+struct OneChain {
+  f32x16 total;
+  __device__ void step(int s, float a, float b) {
+    if (s == 0) zero(total);
+    total = mfma(a, b, total);
+  }
+  __device__ f32x16 sum() const { return total; }
+};
+template <int STEPS>
+struct ChannelSum {
+  static constexpr int CHAIN = STEPS >= 32 ? STEPS / 4 : STEPS / 2;
+  f32x16 total, chain;
+  __device__ void step(int s, float a, float b) {
+    if (s % CHAIN == 0) {
+      if (s > 0) close(s == CHAIN);
+      zero(chain);
+    }
+    chain = mfma(a, b, chain);
+  }
+  __device__ f32x16 sum() {
+    close(false);
+    return total;
+  }
+
+ private:
+  __device__ void close(bool first) {
+    if (first) total = chain;
+    else total += chain;
+    asm volatile("" : "+v"(total));
+  }
+};
+
+// x * scale + y with the product rounded: a score that is its row's maximum, whose lse is the rounded maximum plus
+// ln(sum), then gives exactly -ln(sum) in the backward pass, however large it is.
+__device__ inline float scaled_plus(float x, float scale, float y) {
+#pragma clang fp contract(off)
+  return x * scale + y;
+}
+
 // Buffer descriptor over `bytes` of one head: loads past the end read as zeros.
 __device__ inline __amdgpu_buffer_rsrc_t head_rsrc(const void* base, unsigned bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);

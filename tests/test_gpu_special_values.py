@@ -96,3 +96,65 @@ def test_infinite_scores(shape, undivided, low):
     assert not torch.isfinite(lse[~rows]).any()
     tol = 1e-4 if shape[0] == "f32" else 2e-2
     assert (o - want)[rows].abs().max() <= tol and (lse - want_lse)[rows].abs().max() <= tol
+
+
+@pytest.mark.parametrize("shape", FLOAT, ids=str)
+@pytest.mark.parametrize("undivided", [False, True])
+@pytest.mark.parametrize("size", [2.0 ** 30, 2.0 ** 101])
+@pytest.mark.parametrize("sign", [-1, 1])
+def test_scores_far_from_zero(shape, undivided, size, sign):
+    """Every score an exact product of one size, the keys 1, 4, 7, .. twice the others: a row's output is the mean
+    over the keys with its largest score, however large that is."""
+    import torch
+    q, k, v = _inputs(shape)
+    q.zero_()
+    k.zero_()
+    q[..., 5] = 1.0
+    k[..., 5] = sign * 171 * size          # (not a power of two: its product with the scale is rounded)
+    k[:, :, 1::3, 5] *= 2.0
+    o, lse = _call(shape, q, k, v, undivided=undivided)
+    want, want_lse = _plain(shape, q, k, v)
+    assert (o.double().cpu() - want).abs().max() <= (1e-4 if shape[0] == "f32" else 2e-2)
+    assert ((lse.double().cpu() - want_lse) / want_lse).abs().max() <= 1e-6
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("d", [64, 128])
+def test_float_gradients_at_large_scores(d, G):
+    """Scores of up to 150: P = exp(S - lse) of a row with one large score rests on the last bits of both. Relative
+    errors (2-norm) against 64 bits; the bounds are twice what sums in short chains, the same in both passes, give.
+    Summed over the channels against statistics of sums over groups, dv was at 1.5e-5."""
+    import torch
+
+    import paper_2507_17245_amd as da
+    B, H, Hkv, N, Nk, Br = 1, 4, 2, 500, 700, 128
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    q, k, v, dout = (torch.randn(s, generator=gen, device="cuda") for s in ((B, H, N, d), (B, Hkv, Nk, d), (B, Hkv, Nk, d), (B, H, N, d)))
+    q *= 30.0
+    o, lse = torch.empty_like(q), torch.empty((B, H, N), device="cuda")
+    table = torch.empty((B, H, -(-N // Br), d), dtype=torch.uint8, device="cuda")
+    print(f"case d {d} G {G}", flush=True)
+    da.distr_attn_fwd_ex(q, k, v, o, da.make_params(q, k, v, Br=Br, n_groups=d // G, causal=True, lse_out=lse, perm_out=table))
+    dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+    da.distr_attn_bwd_ex(q, k, v, o, dout, lse, dq, dk, dv, da.make_params(q, k, v, Br=Br, n_groups=d // G, causal=True, perm_in=table))
+    # Q~: every channel replaced by its group's first in the sorted order
+    order = table.long().cpu().view(B, H, -1, d // G, G)
+    source = torch.empty((B, H, order.shape[2], d), dtype=torch.long)
+    source.scatter_(3, order.flatten(3), order[..., :1].expand_as(order).flatten(3))
+    source = source.repeat_interleave(Br, dim=2)[:, :, :N]
+    qr = torch.gather(q.double().cpu(), 3, source)
+    kk, vv = (x.double().cpu().repeat_interleave(H // Hkv, dim=1) for x in (k, v))
+    s = torch.matmul(qr, kk.transpose(2, 3).contiguous()) / math.sqrt(d)
+    s = s.masked_fill(torch.arange(Nk)[None, :] > torch.arange(N)[:, None] + Nk - N, -math.inf)
+    p, g = torch.softmax(s, dim=-1), dout.double().cpu()
+    out = torch.matmul(p, vv)
+    ds = p * (torch.matmul(g, vv.transpose(2, 3).contiguous()) - (g * out).sum(-1, keepdim=True)) / math.sqrt(d)
+    want = {"o": out, "lse": torch.logsumexp(s, dim=-1),
+            "dq": torch.zeros_like(qr).scatter_add_(3, source, torch.matmul(ds, kk)),
+            "dk": torch.matmul(ds.transpose(2, 3).contiguous(), qr).view(B, Hkv, 2, Nk, d).sum(2),
+            "dv": torch.matmul(p.transpose(2, 3).contiguous(), g).view(B, Hkv, 2, Nk, d).sum(2)}
+    bound = {"o": 3e-6, "lse": 1.5e-7, "dq": 1e-5, "dk": 1e-5, "dv": 6e-6}
+    for name, x in (("o", o), ("lse", lse), ("dq", dq), ("dk", dk), ("dv", dv)):
+        err = ((x.double().cpu() - want[name]).norm() / want[name].norm()).item()
+        print(f"  {name}: {err:.2e}", flush=True)
+        assert err <= bound[name], f"{name}: {err:.3g}"
