@@ -16,6 +16,8 @@
 // Layouts, operands and the rounding of P are the general kernel's (attn_bf16_impl.h).
 // Measured (B1 H32 Hkv8 N1 Nk16384 d64, 34 MB of keys and values): 12 us + 4 us for the combine kernel, 130 us +
 // 7 us for the key pre-pass before; B16 H32 Hkv4 N1 Nk8192: 33 us, 4.1 TB/s (174 us).
+#include <cfloat>
+
 #include "attn_bf16_impl.h"
 
 namespace da {
@@ -193,7 +195,9 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
   for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
     for (int i = 0; i < 16; ++i) oacc[mb][i] = 0.0f;
-  float ref = -1e30f, l_run = 0.0f;   // exp2 domain; the sum is over this lane's half of the keys
+  // The reference is the largest score so far, unscaled like the scores until their difference is taken: exact
+  // however large they are (a scaled reference is a rounded one; with scores of 1e10 P came out as 0 or infinity).
+  float ref = -FLT_MAX, l_run = 0.0f;   // the sum is over this lane's half of the keys
   const int lim = causal ? m_ld % N + shift : Nk - 1;   // last key this row sees
 
   auto step = [&](auto par_c, int t) {
@@ -228,9 +232,9 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sc[mb][i]);
-    const float ref_new = fmaxf(ref, half_swap_max(mx) * scale_log2e);
+    const float ref_new = fmaxf(ref, half_swap_max(mx));
     if (__builtin_amdgcn_ballot_w64(ref_new > ref) != 0) {
-      const float alpha = __builtin_amdgcn_exp2f(ref - ref_new);
+      const float alpha = __builtin_amdgcn_exp2f((ref - ref_new) * scale_log2e);
       l_run *= alpha;
 #pragma unroll
       for (int mb = 0; mb < NMB; ++mb)
@@ -245,8 +249,8 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int i = 0; i < 16; i += 2) {
-        const bf16x2 pr = {(bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[mb][i], scale_log2e, -ref)),
-                           (bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[mb][i + 1], scale_log2e, -ref))};
+        const bf16x2 pr = {(bf16)__builtin_amdgcn_exp2f((sc[mb][i] - ref) * scale_log2e),
+                           (bf16)__builtin_amdgcn_exp2f((sc[mb][i + 1] - ref) * scale_log2e)};
         pop[mb * 2 + (i >> 3)][i & 7] = pr[0];
         pop[mb * 2 + (i >> 3)][(i & 7) + 1] = pr[1];
         l_run = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l_run, false);
@@ -275,8 +279,8 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
 #pragma unroll
   for (int j = 1; j < kFewWaves; ++j) ref_all = fmaxf(ref_all, stat_lds[j][lq][0]);
 #pragma unroll
-  for (int j = 0; j < kFewWaves; ++j) l_all += stat_lds[j][lq][1] * __builtin_amdgcn_exp2f(stat_lds[j][lq][0] - ref_all);
-  const float weight = __builtin_amdgcn_exp2f(ref - ref_all) * (n_split > 1 ? 1.0f : 1.0f / l_all);
+  for (int j = 0; j < kFewWaves; ++j) l_all += stat_lds[j][lq][1] * __builtin_amdgcn_exp2f((stat_lds[j][lq][0] - ref_all) * scale_log2e);
+  const float weight = __builtin_amdgcn_exp2f((ref - ref_all) * scale_log2e) * (n_split > 1 ? 1.0f : 1.0f / l_all);
   // wave w's sums: 32 rows of D floats, the 16-byte pieces exchanged by the row (its own buffers: K at
   // d = 64, K and V at d = 128)
   float* half0 = (float*)k_lds0[wave];
@@ -311,8 +315,8 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
   finish(k_lds0, 0);
   if constexpr (D == 128) finish(v_lds0, 64);
   if (wave == 0 && hh == 0 && m < rows) {
-    if (n_split > 1) part_stat[(size_t)part * (units / RT) * rows + row0 + m] = f32x2{ref_all, l_all};
-    else if (lse) lse[row0 + m] = 0.6931471805599453f * (ref_all + __builtin_log2f(l_all));
+    if (n_split > 1) part_stat[(size_t)part * (units / RT) * rows + row0 + m] = f32x2{ref_all * scale_log2e, l_all};
+    else if (lse) lse[row0 + m] = 0.6931471805599453f * (ref_all * scale_log2e + __builtin_log2f(l_all));
   }
 }
 

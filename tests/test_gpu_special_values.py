@@ -98,7 +98,7 @@ def test_infinite_scores(shape, undivided, low):
     assert (o - want)[rows].abs().max() <= tol and (lse - want_lse)[rows].abs().max() <= tol
 
 
-@pytest.mark.parametrize("shape", FLOAT, ids=str)
+@pytest.mark.parametrize("shape", FEW + FLOAT, ids=str)
 @pytest.mark.parametrize("undivided", [False, True])
 @pytest.mark.parametrize("size", [2.0 ** 30, 2.0 ** 101])
 @pytest.mark.parametrize("sign", [-1, 1])
