@@ -79,10 +79,12 @@ typedef struct {
                            perm_in / perm_out are or the attention kernel does the LSH stage itself.
                            Calls with few query rows deal their keys out to several workgroups
                            and sum up in the rest of a workspace of distr_attn_workspace_bytes(), or, with
-                           none, in a library-owned buffer per device and stream (32 MB, for up to
-                           16 streams, kept until distr_attn_release; not under capture and not on
-                           the per-thread default stream); without either they run undivided.
-                           Never refused for it.                                                    */
+                           none, in a library-owned buffer (32 MB, one per stream of a device with
+                           such calls in flight, 16 at most, reused by other streams when these have
+                           ended, kept until distr_attn_release; not under capture and not on the
+                           per-thread default stream); without either they run undivided. Never
+                           refused for it. A library-owned buffer costs a stream other than the null
+                           stream an event per call (1 us).                                         */
   size_t workspace_bytes;
   uint8_t *perm_out;    /* optional device [B][H][Tq][d]: channel at sorted position s of each block */
   uint32_t *hash_out;   /* optional device [B][H][Tq][d]: hash of each channel of each block          */

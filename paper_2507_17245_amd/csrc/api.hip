@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "da_common.h"
+#include "share_pool.h"
 
 namespace {
 
@@ -27,21 +28,41 @@ size_t g_ws_bytes[kMaxDevices] = {0};
 // until distr_attn_release instead of being freed inside a forward call.
 std::vector<void*> g_ws_retired[kMaxDevices];
 
-// Scratch of calls whose keys are dealt out to several workgroups per Q block (partial sums, and the
-// table of a LSH stage of their own): one buffer per device and stream, so that calls on different
-// streams do not meet in it; the lock is held from the first launch that writes it to the last that reads
-// it, so that calls of several threads on one stream do not interleave. At most kMaxShareBuffers streams
-// of a device get one. Later streams go without the split, and so do a stream under capture (its graph may
-// be replayed on any stream, beside calls on this one) and the per-thread default stream (one handle,
-// but a stream of its own in every thread).
-constexpr int kMaxShareBuffers = 16;
+// Scratch of calls whose keys are dealt out to several workgroups (partial sums, and the table of a LSH stage of their
+// own): at most 16 buffers per device, each lent to one call at a time (share_pool.h); the lock is held from the first
+// launch that writes a buffer to the event behind the last that reads it, so that calls of several threads on one
+// stream do not interleave. Calls that get none go without the split, and so do a stream under capture (its graph may be
+// replayed on any stream, beside calls on this one) and the per-thread default stream (one handle, but a stream of
+// its own in every thread).
 constexpr size_t kShareBytes = (size_t)32 << 20;
-struct ShareBuffer {
-  hipStream_t stream;
-  void* ptr;
+// For calls that a capture in another thread (global mode) must not be broken by.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool ok = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  ~RelaxedCapture() {
+    if (ok) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+};
+struct ShareRuntime {
+  typedef hipStream_t Stream;
+  typedef hipEvent_t Event;
+  static bool good(hipError_t e) {
+    if (e != hipSuccess) (void)hipGetLastError();   // (the call goes on without a buffer)
+    return e == hipSuccess;
+  }
+  static bool allocate(void** ptr) { return good(hipMalloc(ptr, kShareBytes)); }
+  static bool deallocate(void* ptr) { return good(hipFree(ptr)); }
+  // No fence with the event (1.1 us a call instead of 3.3): it says that the last kernel to read a buffer has ended. What
+  // was written to the buffer was made visible before that kernel began, by the order of the stream.
+  static bool create(Event* event) { return good(hipEventCreateWithFlags(event, hipEventDisableTiming | hipEventDisableSystemFence)); }
+  static bool destroy(Event event) { return good(hipEventDestroy(event)); }
+  static bool record(Event event, Stream stream) { return good(hipEventRecord(event, stream)); }
+  static bool wait(Stream stream, Event event) { return good(hipStreamWaitEvent(stream, event, 0)); }
+  static bool done(Event event) { return good(hipEventQuery(event)); }
+  static bool lasting(Stream stream) { return stream == nullptr; }   // the device's null stream
 };
 std::mutex g_share_mutex;
-std::vector<ShareBuffer> g_shares[kMaxDevices];
+da::SharePool<ShareRuntime> g_shares[kMaxDevices];
 
 // Scratch of distr_attn_fwd_noalloc: a fixed device array, one copy per GPU the library is
 // loaded on, resident until the process ends. Host code never uses the array's name as an
@@ -162,34 +183,33 @@ size_t share_bytes(const Resolved& r, int n) {
   return n > 1 ? share_stat_bytes(r, n) + (((size_t)n * r.pb.B * r.pb.H * r.pb.N * r.pb.d * 4 + 255) & ~(size_t)255) : 0;
 }
 
-// The stream's own buffer of kShareBytes on the current device (null: go without). g_share_mutex is held.
-char* share_buffer(hipStream_t stream) {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (stream == hipStreamPerThread) return nullptr;
-  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;
+// A library-owned buffer of kShareBytes for one call, held until the object goes (ptr null: go without).
+struct ShareLease {
+  std::unique_lock<std::mutex> lock;
+  da::SharePool<ShareRuntime>* pool = nullptr;
+  char* ptr = nullptr;
+  void take(hipStream_t stream) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (stream == hipStreamPerThread) return;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    if (cap != hipStreamCaptureStatusNone) return;
+    lock = std::unique_lock<std::mutex>(g_share_mutex);
+    RelaxedCapture relaxed;
+    if (relaxed.ok) ptr = (char*)g_shares[dev].lend(stream);
+    if (ptr) pool = &g_shares[dev];
+    else lock.unlock();
   }
-  if (cap != hipStreamCaptureStatusNone) return nullptr;
-  for (const ShareBuffer& x : g_shares[dev])
-    if (x.stream == stream) return (char*)x.ptr;
-  if (g_shares[dev].size() >= kMaxShareBuffers) return nullptr;
-  // (relaxed: another thread's capture in global mode must not be broken by this allocation)
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;
+  ~ShareLease() {
+    if (!pool) return;
+    RelaxedCapture relaxed;
+    pool->give_back();
   }
-  void* ptr = nullptr;
-  const hipError_t e = hipMalloc(&ptr, kShareBytes);
-  if (e != hipSuccess) (void)hipGetLastError();
-  (void)hipThreadExchangeStreamCaptureMode(&mode);
-  if (e != hipSuccess) return nullptr;
-  g_shares[dev].push_back(ShareBuffer{stream, ptr});
-  return (char*)ptr;
-}
+};
 
 // Address of the static scratch array on the current device (looked up once per device).
 int static_scratch(void** out) {
@@ -326,7 +346,7 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   const int n_split = (matrix && !fused) ? da::attn_bf16_splits(r.pb, distr ? 1 : 0) : 1;
   const size_t split_table = (own_table && n_split > 1 && !(few && lsh_in_kernel)) ? perm_bytes(r) : 0;
   const size_t split_need = split_table + share_bytes(r, n_split);
-  std::unique_lock<std::mutex> share_lock(g_share_mutex, std::defer_lock);
+  ShareLease lease;
   char* share = nullptr;
   if (n_split > 1) {
     if (no_alloc || p->workspace) {
@@ -336,9 +356,8 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
         if (rc) return rc;
       }
     } else if (split_need <= kShareBytes) {
-      share_lock.lock();
-      share = share_buffer(r.stream);
-      if (!share) share_lock.unlock();
+      lease.take(r.stream);
+      share = lease.ptr;
     }
   }
   if (share) {
@@ -541,8 +560,7 @@ int distr_attn_release(void) {
     bool ok = hipSetDevice(dev) == hipSuccess && hipDeviceSynchronize() == hipSuccess;
     if (ok && g_ws_ptr[dev]) ok = hipFree(g_ws_ptr[dev]) == hipSuccess;
     for (void* old : g_ws_retired[dev]) ok = ok && hipFree(old) == hipSuccess;
-    for (const ShareBuffer& x : g_shares[dev]) ok = ok && hipFree(x.ptr) == hipSuccess;
-    g_shares[dev].clear();
+    if (ok) ok = g_shares[dev].clear();
     if (!ok) rc = fail(DA_ERR_HIP, "release: freeing the workspace of device %d failed", dev);
     g_ws_retired[dev].clear();
     g_ws_ptr[dev] = nullptr;

@@ -167,6 +167,46 @@ def test_bf16_key_shares_under_capture():
             assert (outs[i].float() - eager.float() * s).abs().max() <= 2.0 ** -7 * s * eager.float().abs().max()
 
 
+def test_bf16_key_shares_on_many_streams():
+    """However many streams a process has used one after the other, a call deals its keys out and gives the same bits;
+    and again when a stream is destroyed with its work in flight and another takes its place."""
+    import torch
+
+    import paper_2507_17245_amd as da
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q = torch.randn((1, 4, 100, 64), generator=gen, device="cuda").bfloat16()
+    k, v = (torch.randn((1, 4, 4096, 64), generator=gen, device="cuda").bfloat16() for _ in range(2))
+
+    def call(vx, o, **kw):
+        return da.distr_attn_exact_fwd_ex(q, k, vx, o, da.make_params(q, k, vx, Br=64, causal=True, **kw))
+    small = torch.empty(256, dtype=torch.uint8, device="cuda")
+    undivided = call(v, torch.empty_like(q), workspace=small)
+    outs = [torch.empty_like(q) for _ in range(24)]
+    torch.cuda.synchronize()
+    for stream, o in zip([torch.cuda.Stream() for _ in outs], outs):
+        with torch.cuda.stream(stream):
+            call(v, o)
+        stream.synchronize()
+    assert not torch.equal(undivided, outs[0])      # (the two ways differ in rounding: equal bits say which was taken)
+    for i, o in enumerate(outs):
+        assert torch.equal(o, outs[0]), f"stream {i}"
+    # streams of the runtime's own, each destroyed as soon as its call is queued
+    import ctypes
+    hip = ctypes.CDLL("libamdhip64.so")
+    vs = [(v * s).contiguous() for s in (1.0, 0.5, 2.0, 4.0)]
+    outs = [torch.empty_like(q) for _ in range(40)]
+    torch.cuda.synchronize()
+    for i, o in enumerate(outs):
+        handle = ctypes.c_void_p()
+        assert hip.hipStreamCreate(ctypes.byref(handle)) == 0
+        with torch.cuda.stream(torch.cuda.ExternalStream(handle.value)):
+            call(vs[i % 4], o)
+        assert hip.hipStreamDestroy(handle) == 0
+    torch.cuda.synchronize()
+    for i, o in enumerate(outs):
+        assert torch.equal(o.float(), outs[0].float() * (1.0, 0.5, 2.0, 4.0)[i % 4])   # powers of two scale every step exactly
+
+
 # LSH kernel: blocks staged 128 rows at a time (float) or whole (bf16, matrix pipe), 16 projections at a time;
 # a tensor that is not 16-byte aligned takes a path of its own. Tables and hashes to the bit.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
