@@ -389,18 +389,8 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
             doubt[i] = pl16 < n_planes && !(__builtin_fabsf(acc[i]) > kDoubt * bnd[i] + kTiny);
             any_doubt |= doubt[i];
           }
-          if (__builtin_amdgcn_ballot_w64(any_doubt) != 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              for (uint64_t left = __builtin_amdgcn_ballot_w64(doubt[i]); left != 0; left &= left - 1) {
-                const int who = __builtin_ctzll(left), ch = 16 * ct + 4 * (who >> 4) + i, p = (who & 15) * RPAD;
-                const float sum = defining_sum(BR, [&](int row, float& x, float& r) {
-                  x = (float)q_staged(row, ch);
-                  r = (float)rp1[p + row] + (float)rp2[p + row];   // exact
-                });
-                if (lane == who) positive[i] = sum > 0.0f;
-              }
-          }
+          if (__builtin_amdgcn_ballot_w64(any_doubt) != 0)
+            settle_doubts(doubt, positive, BR, rp1, rp2, RPAD, [&](int row, int ch) { return q_staged(row, 16 * ct + ch); });
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             // lanes 16*kg .. 16*kg + 15 of the ballot are projections 0..15 of channel 16*ct + 4*kg + i;

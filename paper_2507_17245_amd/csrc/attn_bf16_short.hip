@@ -126,18 +126,10 @@ __global__ __launch_bounds__(NW * 64, 4) void attn_bf16_short_kernel(
           doubt[i] = pl16 < n_planes && !(__builtin_fabsf(acc[i]) > doubt_rel * bnd[i] + kTiny);
           any_doubt |= doubt[i];
         }
-        if (__builtin_amdgcn_ballot_w64(any_doubt) != 0) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            for (uint64_t left = __builtin_amdgcn_ballot_w64(doubt[i]); left != 0; left &= left - 1) {
-              const int who = __builtin_ctzll(left), ch = 16 * ct + 4 * (who >> 4) + i, p = (who & 15) * RPAD;
-              const float sum = defining_sum(rr, [&](int row, float& x, float& r) {
-                x = (float)*(const bf16*)(q_at(b0 + row, ch >> 3) + (ch & 7) * 2);
-                r = (float)rp1[p + row] + (float)rp2[p + row];   // exact
-              });
-              if (lane == who) positive[i] = sum > 0.0f;
-            }
-        }
+        if (__builtin_amdgcn_ballot_w64(any_doubt) != 0)
+          settle_doubts(doubt, positive, rr, rp1, rp2, RPAD, [&, block = (const char*)v_lds + b0 * ROWB](int row, int ch) {
+            return *(const bf16*)(block + row * ROWB + (((2 * ct + (ch >> 3)) ^ ((row >> 1) & 7)) << 4) + (ch & 7) * 2);
+          });
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const uint64_t signs = __builtin_amdgcn_ballot_w64(positive[i]);

@@ -43,20 +43,53 @@ __host__ __device__ inline uint32_t lsh_hash_of_code(uint32_t code, int gray_mod
   return h;
 }
 
-// The defining sum of a projection (float, one fused multiply-add per row, rows ascending, from +0), for the few
-// whose sign the matrix pipe leaves in doubt, by a whole wave: lane = row while the operands are read,
-// `operands(row, x, r)`, 64 rows at a time (0 and 0 past the block's end leave the sum as it is); the
-// chain itself takes them lane by lane. (Every lane walking the rows for its own channels, all but one or
-// two of them for nothing, took four times as long: 2.2 us per 64 rows.)
-template <typename F>
-__device__ inline float defining_sum(int rows, F operands) {
-  float sum = 0.0f;
+// Projections whose sign the matrix pipe leaves in doubt: taken again by their defining sum (float, one fused multiply-add
+// per row, rows ascending, from +0). Lane `who` doubts the sign of channel 4*(who/16) + i of the wave's 16, projection
+// who%16, if doubt[i]. x_at(row, channel of the 16) is the block's entry; a projection's entries are r1 + r2 (exact),
+// [projection][rpad]. Usually there are one to three in a wave:
+//   one, of 64 rows   is summed by the whole wave: lane = row while the entries are read, the chain takes them lane by lane.
+//                     Three instructions a row, half of what follows (short forward H12 N197 B64 28.3 -> 26.8 us).
+//   a few             go to a lane each and are summed at once (by the whole wave, 4.2 us for each at 256 rows).
+//   many              come with channels of zeros, which leave every projection in doubt: each lane walks the rows for its
+//                     own four channels (by the whole wave, a block of zeros took a millisecond).
+template <typename X>
+__device__ inline void settle_doubts(const bool (&doubt)[4], bool (&positive)[4], int rows, const bf16* r1, const bf16* r2, int rpad, X x_at) {
+  const int lane = threadIdx.x & 63;
+  uint64_t masks[4];
+  int count = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    masks[i] = __builtin_amdgcn_ballot_w64(doubt[i]);
+    count += __builtin_popcountll(masks[i]);
+  }
+  auto entries = [&](int at, float (&r)[8]) {
+    const s16x8 a = *(const s16x8*)(r1 + at), b = *(const s16x8*)(r2 + at);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      r[j] = __builtin_bit_cast(float, (uint32_t)(uint16_t)a[j] << 16) + __builtin_bit_cast(float, (uint32_t)(uint16_t)b[j] << 16);
+  };
+  if (count > 12) {
+    float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll 1
-  for (int r0 = 0; r0 < rows; r0 += 64) {
-    float x = 0.0f, r = 0.0f;
-    const int row = r0 + (int)(threadIdx.x & 63);
-    if (row < rows) operands(row, x, r);
-    const int xi = __builtin_bit_cast(int, x), ri = __builtin_bit_cast(int, r);
+    for (int r0 = 0; r0 < rows; r0 += 8) {
+      float r[8];
+      entries((lane & 15) * rpad + r0, r);
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] = __builtin_fmaf((float)x_at(r0 + j, 4 * (lane >> 4) + i), r[j], sum[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (doubt[i]) positive[i] = sum[i] > 0.0f;
+    return;
+  }
+  if (count == 1 && rows == 64) {
+    const int i = masks[0] != 0 ? 0 : masks[1] != 0 ? 1 : masks[2] != 0 ? 2 : 3;
+    const int who = __builtin_ctzll(masks[0] | masks[1] | masks[2] | masks[3]);
+    const int xi = __builtin_bit_cast(int, (float)x_at(lane, 4 * (who >> 4) + i));
+    const int ri = __builtin_bit_cast(int, (float)r1[(who & 15) * rpad + lane] + (float)r2[(who & 15) * rpad + lane]);
+    float sum = 0.0f;
 #pragma unroll 1
     for (int k0 = 0; k0 < 64; k0 += 16) {
 #pragma unroll
@@ -64,8 +97,32 @@ __device__ inline float defining_sum(int rows, F operands) {
         sum = __builtin_fmaf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, k0 + j)),
                              __builtin_bit_cast(float, __builtin_amdgcn_readlane(ri, k0 + j)), sum);
     }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (doubt[j]) positive[j] = sum > 0.0f;
+    return;
   }
-  return sum;
+  int mine = 0, n = 0;   // the n-th doubt goes to lane n (the others repeat something)
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    for (uint64_t left = masks[i]; left != 0; left &= left - 1, ++n) mine = lane == n ? __builtin_ctzll(left) << 2 | i : mine;
+  const int who = mine >> 2, ch = 4 * (who >> 4) + (mine & 3);
+  float sum = 0.0f;
+#pragma unroll 1
+  for (int r0 = 0; r0 < rows; r0 += 32) {
+    float r[4][8], x[32];
+#pragma unroll
+    for (int j = 0; j < 32; ++j) x[j] = (float)x_at(r0 + j, ch);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) entries((who & 15) * rpad + r0 + 8 * j, r[j]);
+#pragma unroll
+    for (int j = 0; j < 32; ++j) sum = __builtin_fmaf(x[j], r[j >> 3][j & 7], sum);
+  }
+  uint64_t up = __builtin_amdgcn_ballot_w64(sum > 0.0f);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    for (uint64_t left = masks[i]; left != 0; left &= left - 1, up >>= 1)
+      if (lane == __builtin_ctzll(left)) positive[i] = up & 1;
 }
 
 // Exchange between the wave halves: v_permlane32_swap swaps the upper 32 lanes of its first

@@ -16,7 +16,8 @@
 //          taken again the defining way.
 //   float  the defining sums on the vector ALUs, from LDS.
 // Measured (rows walked column by column in global memory, four at a time | now): bf16 H16 N200 d128 Br128
-// 21.5 | 9.8 us, float H8 N2048 d64 Br128 13.8 | 5.7 us, float H8 N2048 d64 blocks of 64 rows 6.4 | 4.9 us.
+// 21.5 | 9.2 us, H16 N2048 d64 Br256 17 | 9.0, float H8 N2048 d64 Br128 13.8 | 5.7 us, float H8 N2048 d64 blocks of 64 rows
+// 6.4 | 4.9 us.
 #include "da_common.h"
 
 namespace da {
@@ -112,18 +113,10 @@ __device__ inline void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int p0, int n_
       doubt[i] = pl16 < np && !(__builtin_fabsf(acc[i]) > kDoubt * bnd[i] + kTiny);
       any_doubt |= doubt[i];
     }
-    if (__builtin_amdgcn_ballot_w64(any_doubt) != 0) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        for (uint64_t left = __builtin_amdgcn_ballot_w64(doubt[i]); left != 0; left &= left - 1) {
-          const int who = __builtin_ctzll(left), ch = 16 * ct + 4 * (who >> 4) + i, p = (who & 15) * RPAD;
-          const float sum = defining_sum(BR, [&](int row, float& x, float& r) {
-            x = (float)*(const bf16*)(lds.rows + row * ROWB + (((ch >> 3) ^ lsh_chunk_swz<D>(row)) << 4) + (ch & 7) * 2);
-            r = (float)rp1[p + row] + (float)rp2[p + row];   // exact
-          });
-          if (lane == who) positive[i] = sum > 0.0f;
-        }
-    }
+    if (__builtin_amdgcn_ballot_w64(any_doubt) != 0)
+      settle_doubts(doubt, positive, BR, rp1, rp2, RPAD, [&](int row, int ch) {
+        return *(const bf16*)(lds.rows + row * ROWB + (((2 * ct + (ch >> 3)) ^ lsh_chunk_swz<D>(row)) << 4) + (ch & 7) * 2);
+      });
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       // lanes 16*kg .. 16*kg + 15 of the ballot are the projections of channel 16*ct + 4*kg + i; projection 0

@@ -234,6 +234,59 @@ def test_lsh_kernel(dtype, d, Br, N, n_planes, offset):
     assert np.array_equal(hsh.cpu().numpy().view(np.uint32), want_hash)
 
 
+# Projections the matrix pipe leaves in doubt: `n` channels of every 16 sum to almost nothing along one projection (columns
+# built as in test_projections_that_nearly_cancel). One at a time is summed by the wave, a few by a lane each, many by
+# every lane for its own channels; in the LSH kernel and in the forward kernels' own stages. Tables to the bit.
+@pytest.mark.parametrize("base,N,Br", [("vit", 128, 64), ("vit", 250, 128), ("vit", 256, 256), ("llama", 300, 64), ("llama", 384, 128), ("llama", 300, 256), ("mid", 256, 128)])
+@pytest.mark.parametrize("n", [1, 2, 5, 12, 13])
+def test_doubtful_projections(base, N, Br, n):
+    import gpu_util as U
+    import paper_2507_17245_amd as da
+    cfg = W.CONFIGS[base].scaled(B=1, H=2, Hkv=1, N=N, Br=Br, recipe="normal", data_seed=4000 + n)
+    q, k, v = W.make(cfg)
+    R = da.distr_attn_hyperplanes(cfg.lsh_seed, cfg.n_planes, cfg.Br).astype(np.float64)
+    for t in range(cfg.Tq):
+        r0, rows = t * Br, min(Br, N - t * Br)
+        for c in [c for c in range(cfg.d) if c % 16 < n]:
+            w, col, run = R[c % cfg.n_planes, :rows], np.zeros(rows), 0.0
+            for r in range(rows):
+                if r >= rows - 3 and abs(w[r]) > 0.1:
+                    col[r] = float(W.round_to_bf16(np.array([-run / w[r]], dtype=np.float32))[0])
+                else:
+                    col[r] = -1.0 if run * w[r] > 0 else 1.0
+                run += col[r] * w[r]
+            q[:, :, r0:r0 + rows, c] = col
+    print(f"case {cfg} n {n}", flush=True)
+    want_hash, want_perm, _ = oracle.lsh_group(q, U.oracle_params(cfg))
+    o, perm, hsh = U.run_gpu(cfg, q, k, v, want_tables=True)
+    assert np.array_equal(hsh, want_hash) and np.array_equal(perm, want_perm)
+    own, perm, _ = U.run_gpu(cfg, q, k, v, want_perm_only=True)
+    assert np.array_equal(perm, want_perm) and np.array_equal(own, o)
+
+
+def test_zero_queries_cost_what_others_do():
+    """Queries of zeros (padding) leave every projection in doubt; summed one by one they took 33 times as long."""
+    import torch
+
+    import paper_2507_17245_amd as da
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    for B, N, d, Br in ((8, 512, 64, 64), (2, 1024, 64, 256), (16, 197, 64, 64)):
+        q, k, v = (torch.randn((B, 12, N, d), generator=gen, device="cuda").bfloat16() for _ in range(3))
+        o, zero = torch.empty_like(q), torch.zeros_like(q)
+        p = da.make_params(q, k, v, Br=Br, n_groups=d // 2)
+        times = []
+        for x in (q, zero) * 4:
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                da.distr_attn_fwd_ex(x, k, v, o, p)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        print(f"  B{B} N{N} Br{Br}: {min(times[0::2]):.3f} | {min(times[1::2]):.3f} ms", flush=True)
+        assert min(times[1::2]) < 4 * min(times[0::2])
+
+
 # bf16 backward of short sequences in one workgroup per head: 32 keys per wave (4 waves up to 128 keys, 8 up to 256),
 # row tiles of 64 in blocks of 32 and 16; one past the range on either side takes the general kernels. Same bar as the
 # bf16 backward tests; a call's results do not depend on the run.
