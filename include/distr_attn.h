@@ -91,7 +91,8 @@ typedef struct {
   const uint8_t *perm_in; /* optional device [B][H][Tq][d]: use this grouping and skip the LSH stage
                              (each row must be a permutation of 0..d-1; it is not checked)          */
   const void *kt_in;      /* optional device buffer written by distr_attn_key_prepass for this k and
-                             n_groups: skip the key pre-pass (bf16 only)                            */
+                             n_groups: skip the key pre-pass (bf16 only). Read where S^ is taken over the
+                             groups, which it makes the faster way more often; otherwise K is read   */
   int Nk;               /* keys / values per head; 0 means N. N != Nk covers decoding against a cache
                            and cross attention (Sec. 2.1 with an N x Nk score matrix). With causal = 1
                            (needs Nk >= N) the last query is aligned with the last key: key n is

@@ -314,8 +314,9 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
     distr = false;
   }
   const bool matrix = r.dtype == DA_BF16 && r.pb.side == 0;
-  const bool replicated = distr && matrix && da::attn_bf16_replicated(r.pb);
-  const bool fused = distr && matrix && !replicated;
+  // (the keys of a fused launch stay together)
+  const int n_possible = matrix ? da::attn_bf16_splits(r.pb, distr ? 1 : 0) : 1;
+  bool fused = distr && matrix && !da::attn_bf16_replicated(r.pb, p->kt_in != nullptr, n_possible);
   // bf16 path, up to 16 projections, no hashes asked for: the attention kernel hashes and groups
   // its own Q block in its prologue (same arithmetic as the LSH kernel); the table is written
   // only if the caller gave perm_out.
@@ -343,7 +344,7 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   // such workgroup would repeat the LSH stage: it then runs as a kernel of its own (not for the few rows
   // of a decoding call, whose grouping is done before the first keys arrive).
   const bool few = matrix && !fused && da::attn_bf16_few_rows(r.pb);
-  const int n_split = (matrix && !fused) ? da::attn_bf16_splits(r.pb, distr ? 1 : 0) : 1;
+  const int n_split = fused ? 1 : n_possible;
   const size_t split_table = (own_table && n_split > 1 && !(few && lsh_in_kernel)) ? perm_bytes(r) : 0;
   const size_t split_need = split_table + share_bytes(r, n_split);
   ShareLease lease;
@@ -360,6 +361,7 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
       share = lease.ptr;
     }
   }
+  if (!share && n_split > 1 && distr && p->kt_in) fused = !da::attn_bf16_replicated(r.pb, true, 1);
   if (share) {
     r.pb.n_split = n_split;
     table = split_table ? (uint8_t*)share : nullptr;

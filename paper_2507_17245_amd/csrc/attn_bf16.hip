@@ -1,5 +1,7 @@
 // Entry of the bf16 attention kernels: which shapes are built, and the dispatch over the K/V tile
 // size (one translation unit per tile size: attn_bf16_bc32/64/128.hip, kernel in attn_bf16_impl.h).
+#include <algorithm>
+
 #include "da_common.h"
 
 namespace da {
@@ -27,17 +29,33 @@ bool attn_bf16_supported(const Problem& pb, int distr) {
   return true;
 }
 
-// Q~ K^T (see ScoreMode in attn_bf16_impl.h) instead of Q_r K_f^T where the transposed copy of K costs more
-// than the shorter contraction saves. Per key of a kv head the copy moves 4 d bytes (0.8 ps d at 5 TB/s), and
-// its launch costs 4 us; the fused kernel saves about a seventh of 4 d FLOP per visible (query, key) pair
-// (0.5 fs d at 1.1 PFLOP/s): equal at 1570 visible rows per key plus the launch's share.
-// Measured, Q~ K^T | fused: B64 H12 N197 d64 40 | 46 us; H16 N1024 d64 causal 20 | 22; H16 N4096 d64 causal 53 | 54;
-// H32 Hkv8 N4096 d64 causal 84 | 77; H16 N2048 d128 causal 40 | 49; H8 N852 d128
-// Br256 G4 35 | 38; H16 N8192 d128 causal 282 | 253; N200 Nk32768 d128 109 | 500.
-bool attn_bf16_replicated(const Problem& pb) {
+// Q~ K^T (see ScoreMode in attn_bf16_impl.h) instead of Q_r K_f^T where the transposed copy of K costs more than the
+// shorter contraction saves. The copy: its launch (4.5 us) and 0.35 us per million elements. The saving: `gain` us per
+// 10^9 (visible pairs times channels), by the group size (larger groups save products but have more channels to sum up); a
+// launch lasts at least as long as its longest wave, 32 rows against all keys, however few SIMDs have one. With the copy
+// at hand (kt_in) what is left is the prologue at d = 128, where Q~ is gathered faster than Q_r (1.7 us; not for blocks
+// of 256 rows), against a wave's walk, and calls too small for either to matter.
+// Groups of 16 fuse at a loss, and a fused launch cannot deal its keys out: there the copy's bytes are weighed against
+// the whole product, 1570 visible rows per key and the launch.
+// Measured, copy + fused | fused | Q~ K^T, us:
+//   G2  d64  H16 N1024 causal 20 | 17 | 18, N4096 53 | 44 | 52, N5372 78 | 67 | 81; B2 H16 Hkv4 N523 Br256 23 | 19 | 21
+//       d128 H16 N1024 causal 35 | 30 | 26, N4412 99 | 90 | 97; B4 H16 N1024 60 | 46 | 49
+//   G4  d64  H16 N1024 causal 20 | 17 | 18, N4043 50 | 43 | 51, N5372 70 | 61 | 78
+//       d128 H16 N1024 causal 32 | 28 | 26, N3321 71 | 62 | 70, N4412 90 | 80 | 96; B2 H16 N534 Nk25907 473 | 430 | 395
+//   G8  d64  H16 N1024 causal 22 | 19 | 18; d128 H16 N2021 48 | 40 | 43, N2685 73 | 63 | 78; B4 H16 N1894 117 | 106 | 134
+//   G16 d64  H16 N4096 causal 78 | 68 | 55; d128 H16 N2048 causal 83 | 69 | 41
+//   keys dealt out: H16 N200 Nk32768 d128 G2 516 | 428 | 86, N1000 Nk8192 125 | 114 | 85
+bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split) {
   if (attn_bf16_few_rows(pb) || attn_bf16_short(pb, 1)) return true;
-  const double rows = (double)(pb.H / pb.Hkv) * pb.N * (pb.causal ? 1.0 - 0.5 * pb.N / pb.Nk : 1.0);
-  return rows < 1570.0 + 7.8e9 / ((double)pb.d * pb.B * pb.Hkv * pb.Nk);
+  const int G = pb.d / pb.n_groups;
+  const double rows = (double)(pb.H / pb.Hkv) * pb.N * (pb.causal ? 1.0 - 0.5 * pb.N / pb.Nk : 1.0);   // per key
+  const double keys = (double)pb.B * pb.Hkv * pb.Nk;
+  if (G >= 16 || n_split > 1) return rows < 1570.0 + 7.8e9 / (pb.d * keys);
+  const double gain = pb.d == 64 ? (G == 2 ? 0.8 : G == 4 ? 0.75 : 0.25) : (G == 2 ? 0.3 : G == 4 ? 0.5 : 0.6);
+  const double simds = 1024.0 * 32, wave_rows = (double)pb.B * pb.H * ((pb.N + pb.Br - 1) / pb.Br) * pb.Br;
+  const double walk = (have_kt && pb.d == 128 ? simds : std::min(wave_rows, simds)) * pb.Nk;
+  const double copy = have_kt ? (pb.d == 64 ? 0.1 : pb.Br == 256 ? 0.0 : 1.7) : 4.5 + 0.35e-6 * keys * pb.d;
+  return copy > gain * 1e-9 * pb.d * std::max(rows * keys, walk);
 }
 
 // Key shares per Q block, for launches that would leave compute units without a workgroup: one

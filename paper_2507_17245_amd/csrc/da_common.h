@@ -200,9 +200,10 @@ hipError_t launch_attn_bf16(const void* q, const void* k, const void* v, void* o
 hipError_t launch_attn_f32(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                            const Problem& pb, int dtype, int distr, hipStream_t stream);
 bool attn_bf16_supported(const Problem& pb, int distr);
-// The rules of the bf16 forward (attn_bf16.hip): whether S^ is taken as Q~ K^T, and into how many
-// shares the keys of a Q block are cut when the product is that one or the exact one.
-bool attn_bf16_replicated(const Problem& pb);
+// The rules of the bf16 forward (attn_bf16.hip): whether S^ is taken as Q~ K^T (have_kt: the transposed keys are at
+// hand; n_split: the shares it would be cut into), and into how many shares the keys of a Q block are cut when the
+// product is that one or the exact one.
+bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split);
 int attn_bf16_splits(const Problem& pb, int distr);
 // Few query rows against many keys (decoding): a kernel of its own, with its own number of shares.
 bool attn_bf16_few_rows(const Problem& pb);
