@@ -172,10 +172,11 @@ __global__ __launch_bounds__(kThreads) void bwd_delta_kernel(const float* __rest
 }
 
 // ------------------------------------------------------------------------------------------------
-// W waves. Eight at d = 64, two per SIMD, with the K and V rows that all of them multiply by in LDS; four, with K and V
-// in registers, at d = 128, where their tiles fill the LDS, and for fewer than eight query tiles, which would
+// W waves. Eight at d = 64, two per SIMD, with the K and V rows that all of them multiply by in LDS; four, with V in
+// registers, at d = 128, where their tiles fill the LDS but for K's, and for fewer than eight query tiles, which would
 // leave waves without any (backward of d = 64, four | eight waves: H8 N2048 248 | 237 us, H8 Hkv2 N1024 causal 189 | 171,
-// H8 N256 29.1 | 27.9, H1 N64 17.2 | 17.7).
+// H8 N256 29.1 | 27.9, H1 N64 17.2 | 17.7). K in registers at d = 128 spilled 97 of them (backward, exact,
+// H8 N1024: 203 us; in LDS 151).
 // G: channels per group where the scores are summed over the groups, as the forward sums them (2, 4); 1: over the
 // channels, with Q~. P = exp(S - lse) then rests on the bits of S that lse was taken of: with S over the channels and lse
 // of sums over groups, scores of 25 put dK and dV 2.6 times as far from 64 bits.
@@ -185,10 +186,10 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
     const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dk, float* __restrict__ dv,
     const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Br, int Tq, int n_groups, int causal, float scale) {
   constexpr int NB = D / 32, RS = Tile<D>::RS;
-  constexpr bool SHARED = W == 8;
+  constexpr bool SHARED = W == 8, K_LDS = SHARED || G > 1 || D == 128;
   __shared__ __attribute__((aligned(16))) float q_lds[W][kTile * RS];    // Q~ tile of each wave, at the end its dK
   __shared__ __attribute__((aligned(16))) float do_lds[W][kTile * RS];   // dO tile, at the end dV
-  __shared__ __attribute__((aligned(16))) float k_lds[SHARED || G > 1 ? kTile * RS : 4];
+  __shared__ __attribute__((aligned(16))) float k_lds[K_LDS ? kTile * RS : 4];
   __shared__ __attribute__((aligned(16))) float v_lds[SHARED ? kTile * RS : 4];
   __shared__ __attribute__((aligned(16))) float stat_lds[W][2][kTile];   // lse, D_i
   __shared__ __attribute__((aligned(16))) uint8_t map_lds[W][3][D];
@@ -252,10 +253,10 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
     if (perm && it + W < n_it) load_map(it + W);
   }
 
-  float kop[SHARED || G > 1 ? 1 : D / 2], vop[SHARED ? 1 : D / 2];
+  float kop[K_LDS ? 1 : D / 2], vop[SHARED ? 1 : D / 2];
   const __amdgpu_buffer_rsrc_t k_rsrc = head_rsrc(k + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
   const __amdgpu_buffer_rsrc_t v_rsrc = head_rsrc(v + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
-  if constexpr (SHARED || G > 1) {
+  if constexpr (K_LDS) {
     if (w < (SHARED ? 2 : 1)) {
       Tile<D> x;
       x.load(w ? v_rsrc : k_rsrc, t, lane);
@@ -301,7 +302,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
     wave_order();
     f32x16 s, dp;
     if constexpr (G > 1) s = group_product<D, G>(&q_lds[w][lq * RS], &k_lds[lq * RS], hh, map_lds[w][2]);
-    else if constexpr (SHARED) s = row_product<D>(&q_lds[w][lq * RS], hh, &k_lds[lq * RS]);
+    else if constexpr (K_LDS) s = row_product<D>(&q_lds[w][lq * RS], hh, &k_lds[lq * RS]);
     else s = row_product<D>(&q_lds[w][lq * RS], hh, kop);
     if (it + W < n_it) load_do(it + W);   // (only now: the registers were those of the sum)
     if constexpr (SHARED) dp = row_product<D, DpSum<D>>(&do_lds[w][lq * RS], hh, &v_lds[lq * RS]);
