@@ -70,9 +70,10 @@ __device__ inline void lsh_stage_rows(const T* block, int rows, int r0, char* ds
   }
 }
 
-// Sign codes of the bf16 block's channels, projections p0 .. p0 + 15, into lds.code.
+// Sign codes of the bf16 block's channels, projections p0 .. p0 + 15, into lds.code. `rows`: a multiple of 32, the rest of
+// the block is zeros.
 template <int D, int BR>
-__device__ inline void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int p0, int n_planes) {
+__device__ inline void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int rows, int p0, int n_planes) {
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
   constexpr int RPAD = LshLds<bf16, D, BR>::RPAD, ROWB = D * 2;
   const bf16* rp1 = (const bf16*)lds.table;
@@ -94,6 +95,7 @@ __device__ inline void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int p0, int n_
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f}, bnd = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int ks = 0; ks < BR / 32; ++ks) {
+      if (32 * ks >= rows) break;
       const int row0 = 32 * ks + 8 * kg + (pl16 >> 2), row1 = row0 + 4;
       const int chunk = 2 * ct + ((pl16 & 3) >> 1), inch = 8 * (pl16 & 1);
       const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds.rows + row0 * ROWB + ((chunk ^ lsh_chunk_swz<D>(row0)) << 4) + inch));
@@ -114,7 +116,7 @@ __device__ inline void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int p0, int n_
       any_doubt |= doubt[i];
     }
     if (__builtin_amdgcn_ballot_w64(any_doubt) != 0)
-      settle_doubts(doubt, positive, BR, rp1, rp2, RPAD, [&](int row, int ch) {
+      settle_doubts(doubt, positive, rows, rp1, rp2, RPAD, [&](int row, int ch) {
         return *(const bf16*)(lds.rows + row * ROWB + (((2 * ct + (ch >> 3)) ^ lsh_chunk_swz<D>(row)) << 4) + (ch & 7) * 2);
       });
 #pragma unroll
@@ -138,6 +140,7 @@ __device__ inline void lsh_block(const T* __restrict__ block, int rows, int n_pl
   using L = LshLds<T, D, BR>;
   constexpr int NPG = kLshThreads / D;        // threads per channel
   const int tid = threadIdx.x, c = tid % D, pg = tid / D;
+  const int taken = (rows + 31) / 32 * 32;    // (a block of few rows costs what they cost)
   for (int p0 = 0; p0 < n_planes; p0 += 16) {
     if constexpr (L::MATRIX) {
       if (p0 == 0) lsh_stage_rows<T, D, BR, true>(block, rows, 0, lds.rows);
@@ -146,6 +149,7 @@ __device__ inline void lsh_block(const T* __restrict__ block, int rows, int n_pl
       bf16* rp2 = rp1 + 16 * L::RPAD;
       for (int i = tid; i < BR * 16; i += kLshThreads) {
         const int r = i % BR, pl = i / BR;
+        if (r >= taken) continue;
         const float rv = p0 + pl < n_planes ? hyperplane_entry(seed, (uint32_t)(p0 + pl), (uint32_t)r) : 0.0f;
         const bf16 r1 = (bf16)rv;
         rp1[pl * L::RPAD + r] = r1;
@@ -153,18 +157,18 @@ __device__ inline void lsh_block(const T* __restrict__ block, int rows, int n_pl
       }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
-      lsh_codes_matrix<D, BR>(lds, p0, n_planes);
+      lsh_codes_matrix<D, BR>(lds, taken, p0, n_planes);
     } else {
       constexpr int PPT = 16 / NPG;           // projections per thread: pg*PPT .. pg*PPT + PPT - 1
       float* R = (float*)lds.table;           // [row][16]
       float acc[PPT];
 #pragma unroll
       for (int j = 0; j < PPT; ++j) acc[j] = 0.0f;
-      for (int r0 = 0; r0 < BR; r0 += L::CR) {
+      for (int r0 = 0; r0 < rows; r0 += L::CR) {
         if (p0 + r0 > 0) __syncthreads();     // the staged rows are no longer read
         lsh_stage_rows<T, D, L::CR, false>(block, rows, r0, lds.rows);
         if (r0 == 0) {
-          for (int i = tid; i < BR * 16; i += kLshThreads)
+          for (int i = tid; i < min(rows, BR) * 16; i += kLshThreads)
             R[i] = p0 + (i & 15) < n_planes ? hyperplane_entry(seed, (uint32_t)(p0 + (i & 15)), (uint32_t)(i >> 4)) : 0.0f;
           if (p0 == 0 && tid < D) lds.code[tid] = 0;
         }
