@@ -343,7 +343,7 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   // Keys dealt out to several workgroups per Q block, where scratch for their sums is at hand. Every
   // such workgroup would repeat the LSH stage: it then runs as a kernel of its own (not for the few rows
   // of a decoding call, whose grouping is done before the first keys arrive).
-  const bool few = matrix && !fused && da::attn_bf16_few_rows(r.pb);
+  const bool few = matrix && !fused && da::attn_bf16_few_rows(r.pb, distr ? 1 : 0);
   const int n_split = fused ? 1 : n_possible;
   const size_t split_table = (own_table && n_split > 1 && !(few && lsh_in_kernel)) ? perm_bytes(r) : 0;
   const size_t split_need = split_table + share_bytes(r, n_split);

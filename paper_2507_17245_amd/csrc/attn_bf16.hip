@@ -46,7 +46,7 @@ bool attn_bf16_supported(const Problem& pb, int distr) {
 //   G16 d64  H16 N4096 causal 78 | 68 | 55; d128 H16 N2048 causal 83 | 69 | 41
 //   keys dealt out: H16 N200 Nk32768 d128 G2 516 | 428 | 86, N1000 Nk8192 125 | 114 | 85
 bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split) {
-  if (attn_bf16_few_rows(pb) || attn_bf16_short(pb, 1)) return true;
+  if (attn_bf16_few_rows(pb, 1) || attn_bf16_short(pb, 1)) return true;
   const int G = pb.d / pb.n_groups;
   const double rows = (double)(pb.H / pb.Hkv) * pb.N * (pb.causal ? 1.0 - 0.5 * pb.N / pb.Nk : 1.0);   // per key
   const double keys = (double)pb.B * pb.Hkv * pb.Nk;
@@ -70,7 +70,7 @@ int attn_bf16_splits(const Problem& pb, int distr) {
   long long n = 1024 / (pb.Br / 32) / units;
   if (n > tiles / 4) n = tiles / 4;
   if (n < 2 || tiles - tiles / n < (distr ? 30 : 12)) n = 1;
-  if (attn_bf16_few_rows(pb)) n = attn_bf16_few_splits(pb);
+  if (attn_bf16_few_rows(pb, distr)) n = attn_bf16_few_splits(pb);
   const long long row_bytes = (long long)pb.B * pb.H * pb.N * (pb.d * 4 + 8);
   if (n * row_bytes > (24LL << 20)) n = (24LL << 20) / row_bytes;
   return n > 1 ? (int)n : 1;
@@ -141,7 +141,7 @@ hipError_t launch_attn_bf16_combine(void* o, const Problem& pb, hipStream_t stre
 hipError_t launch_attn_bf16(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                             const void* kt, const Problem& pb, int distr, hipStream_t stream) {
   if (!attn_bf16_supported(pb, distr)) return hipErrorInvalidValue;
-  if (!kt && attn_bf16_few_rows(pb)) return launch_attn_bf16_few(q, k, v, o, perm, pb, distr, stream);
+  if (!kt && attn_bf16_few_rows(pb, distr)) return launch_attn_bf16_few(q, k, v, o, perm, pb, distr, stream);
   if (!kt && attn_bf16_short(pb, distr)) return launch_attn_bf16_short(q, k, v, o, perm, pb, distr, stream);
   if (pb.Bc == 32) return launch_attn_bf16_bc32(q, k, v, o, perm, kt, pb, distr, stream);
   if (pb.Bc == 128) return launch_attn_bf16_bc128(q, k, v, o, perm, kt, pb, distr, stream);

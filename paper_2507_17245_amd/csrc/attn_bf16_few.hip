@@ -14,7 +14,7 @@
 //     cache. The grouping of a head's N <= 64 rows (one Q block) is computed by the workgroup, in the
 //     defining float order, while its first tiles travel.
 // Layouts, operands and the rounding of P are the general kernel's (attn_bf16_impl.h).
-// Measured (B1 H32 Hkv8 N1 Nk16384 d64, 34 MB of keys and values): 12 us + 4 us for the combine kernel, 130 us +
+// Measured (B1 H32 Hkv8 N1 Nk16384 d64, 34 MB of keys and values): 11 us + 4 us for the combine kernel, 130 us +
 // 7 us for the key pre-pass before; B16 H32 Hkv4 N1 Nk8192: 33 us, 4.1 TB/s (174 us).
 #include <cfloat>
 
@@ -44,7 +44,6 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
   __shared__ __attribute__((aligned(16))) bf16 q_lds[kFewRows][D + 8];
   __shared__ f32x2 stat_lds[kFewWaves][kFewRows];
   // grouping, for every head that has a row here
-  __shared__ __attribute__((aligned(16))) uint16_t hash_lds[GROUPED ? kFewRows : 1][GROUPED ? D : 8];
   __shared__ uint8_t perm_lds[GROUPED ? kFewRows : 1][GROUPED ? D : 1];
   __shared__ uint8_t from_lds[GROUPED ? kFewRows : 1][GROUPED ? D : 1];
   __shared__ float R_lds[GROUPED ? 64 * 16 : 1];
@@ -117,6 +116,8 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
   if (tile < t1) load_tile(even, tile);
   if constexpr (GROUPED) {
     const int group = D / n_groups;
+    uint32_t* keys = (uint32_t*)k_lds1;   // (receives its first tile after the barrier that ends this stage)
+    static_assert(kFewRows * D * 4 <= kFewWaves * kFewTileBytes, "the keys of all heads fit");
     __syncthreads();
     if (perm == nullptr) {
       // signs of the float sums, one fused multiply-add per row, rows ascending, from +0
@@ -141,22 +142,21 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
 #pragma unroll
         for (int p = 0; p < 16; ++p)
           if (p < n_planes && acc[p] > 0.0f) bits |= 1u << (n_planes - 1 - p);   // projection 0 = top bit
-        hash_lds[i / D][c] = (uint16_t)lsh_hash_of_code(bits, gray_mode);
+        keys[i] = lsh_hash_of_code(bits, gray_mode) << 7 | c;   // (at most 16 bits: hash and channel make one key)
       }
       __syncthreads();
       // rank by counting = stable ascending sort
       for (int i = tid; i < n_heads * D; i += kFewThreads) {
-        const int c = i % D;
-        const uint16_t* hs = hash_lds[i / D];
-        const uint32_t mine = hs[c];
+        const uint32_t* others = keys + i / D * D;
+        const uint32_t mine = keys[i];
         int rank = 0;
-#pragma unroll 4
-        for (int o8 = 0; o8 < D; o8 += 8) {
-          const s16x8 h = *(const s16x8*)&hs[o8];
+#pragma unroll 8
+        for (int o4 = 0; o4 < D; o4 += 4) {
+          const u32x4 other = *(const u32x4*)&others[o4];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) rank += ((uint16_t)h[j] < mine || ((uint16_t)h[j] == mine && o8 + j < c)) ? 1 : 0;
+          for (int j = 0; j < 4; ++j) rank += other[j] < mine ? 1 : 0;
         }
-        perm_lds[i / D][rank] = (uint8_t)c;
+        perm_lds[i / D][rank] = (uint8_t)(i % D);
       }
       __syncthreads();
       if (perm_w && part == 0)
@@ -341,12 +341,18 @@ hipError_t launch_d(const void* q, const void* k, const void* v, void* o, const 
 // Where this kernel is the better one: H32 Hkv32 N32 Nk8192 d64 26 us against 28 with the general kernel (keys
 // split there too), but N64 47 against 36 (two row tiles of one head read the keys twice); grouped heads
 // win up to 128 rows (Hkv4 N16: 20 against 25; B8 Hkv4 N16 Nk2048 d128: 36 against 58). Below 256 keys there
-// is no tile for every wave.
-bool attn_bf16_few_rows(const Problem& pb) {
-  return pb.N <= 32 && (long long)(pb.H / pb.Hkv) * pb.N <= 128 && pb.Nk >= 256;
+// is no tile for every wave. Exact calls, whose workgroups of the general kernel start at once, need more than two tiles
+// per wave (H16 N1 Nk512 d64 7.9 against 7.4, Nk1000 9.0 against 11.5; d128 Nk512 9.5 against 10.6) and, where no heads
+// share their keys, no more workgroups than compute units (B16 H32 N1 Nk1000 d64 24.3 against 22.2).
+bool attn_bf16_few_rows(const Problem& pb, int distr) {
+  const int rep = pb.H / pb.Hkv;
+  if (pb.N > 32 || (long long)rep * pb.N > 128 || pb.Nk < 256) return false;
+  return distr || ((long long)pb.Nk * pb.d > 32768 && (rep > 1 || (long long)pb.B * pb.H <= 256));
 }
 
-// One workgroup per compute unit (the tiles in flight take its LDS), every wave at least one tile.
+// One workgroup per compute unit (the tiles in flight take its LDS), every wave at least one tile; undivided unless five
+// tiles come off a wave's walk, which is what the combine kernel costs (H16 N1 d64, 1 | 16 and more shares: Nk1000 8.7 | 11.2 us,
+// Nk1500 11.1 | 11.2, Nk2200 14.5 | 11.1; d128 Nk512 9.5 | 11.3, Nk1000 14.2 | 11.3).
 int attn_bf16_few_splits(const Problem& pb) {
   const int RT = (pb.H / pb.Hkv * pb.N + kFewRows - 1) / kFewRows;
   const long long units = (long long)pb.B * pb.Hkv * RT;
@@ -354,7 +360,8 @@ int attn_bf16_few_splits(const Problem& pb) {
   const long long tiles = (pb.Nk + tile - 1) / tile;
   long long n = 256 / units;
   if (n > tiles / kFewWaves) n = tiles / kFewWaves;
-  return n > 1 ? (int)n : 1;
+  if (n < 2 || tiles - tiles / n < 20) n = 1;
+  return (int)n;
 }
 
 hipError_t launch_attn_bf16_few(const void* q, const void* k, const void* v, void* o, const uint8_t* perm, const Problem& pb,

@@ -321,7 +321,7 @@ __global__ __launch_bounds__(NW * 64, 4) void attn_bf16_short_kernel(
 // What the LDS holds. Exact, with fewer heads than compute units, the general kernel's Q blocks spread further
 // (H12 N197 B1: 6.6 | 7.3 us).
 bool attn_bf16_short(const Problem& pb, int distr) {
-  return pb.d == 64 && pb.N <= 256 && pb.Nk <= 256 && !attn_bf16_few_rows(pb) && (distr || (long long)pb.B * pb.H >= 256);
+  return pb.d == 64 && pb.N <= 256 && pb.Nk <= 256 && !attn_bf16_few_rows(pb, distr) && (distr || (long long)pb.B * pb.H >= 256);
 }
 
 hipError_t launch_attn_bf16_short(const void* q, const void* k, const void* v, void* o, const uint8_t* perm, const Problem& pb,

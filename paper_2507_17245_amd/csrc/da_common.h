@@ -206,7 +206,7 @@ bool attn_bf16_supported(const Problem& pb, int distr);
 bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split);
 int attn_bf16_splits(const Problem& pb, int distr);
 // Few query rows against many keys (decoding): a kernel of its own, with its own number of shares.
-bool attn_bf16_few_rows(const Problem& pb);
+bool attn_bf16_few_rows(const Problem& pb, int distr);
 int attn_bf16_few_splits(const Problem& pb);
 hipError_t launch_attn_bf16_few(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                                 const Problem& pb, int distr, hipStream_t stream);

@@ -53,7 +53,10 @@ def test_float_backward(d, N, Nk, causal, G):
 # key tiles of 64 (d = 64) or 32 (d = 128) dealt out to four waves of each share.
 @pytest.mark.parametrize("base,d", [("llama", 64), ("long", 128)])
 @pytest.mark.parametrize("B,H,Hkv,N,Nk,causal", [(1, 4, 1, 1, 256, True), (2, 8, 2, 3, 300, True), (1, 4, 4, 32, 1000, True), (1, 2, 1, 64, 513, False),
-                                                 (1, 32, 1, 1, 777, True), (1, 12, 2, 17, 4100, True), (3, 2, 2, 5, 16383, False), (300, 1, 1, 2, 320, True)])
+                                                 (1, 32, 1, 1, 777, True), (1, 12, 2, 17, 4100, True), (3, 2, 2, 5, 16383, False), (300, 1, 1, 2, 320, True),
+                                                 # around the lengths from which keys are dealt out, and from which exact calls come here
+                                                 (1, 4, 4, 2, 1345, True), (1, 4, 4, 2, 1409, True), (1, 8, 2, 4, 672, False), (1, 8, 2, 4, 705, False),
+                                                 (2, 4, 4, 3, 512, True), (2, 4, 4, 3, 513, True), (2, 4, 2, 3, 257, True)])
 def test_bf16_few_rows(base, d, B, H, Hkv, N, Nk, causal):
     cfg = W.CONFIGS[base].scaled(B=B, H=H, Hkv=Hkv, N=N, Nk=Nk, Br=64, n_groups=d // 2, causal=causal, recipe="normal")
     assert cfg.d == d
