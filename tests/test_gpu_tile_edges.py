@@ -211,10 +211,12 @@ def test_bf16_key_shares_on_many_streams():
 
 
 # LSH kernel: blocks staged 128 rows at a time (float) or whole (bf16, matrix pipe), 16 projections at a time;
-# a tensor that is not 16-byte aligned takes a path of its own. Tables and hashes to the bit.
+# a tensor that is not 16-byte aligned takes a path of its own; a sequence shorter than a block takes the kernel of a
+# shorter one. Tables and hashes to the bit.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d,Br", [(64, 64), (64, 256), (128, 64), (128, 128), (128, 256)])
-@pytest.mark.parametrize("N,n_planes,offset", [(1, 16, 0), (65, 3, 0), (257, 17, 0), (300, 32, 1), (129, 16, 1)])
+@pytest.mark.parametrize("N,n_planes,offset", [(1, 16, 0), (65, 3, 0), (257, 17, 0), (300, 32, 1), (129, 16, 1),
+                                                 (32, 17, 0), (33, 32, 1), (64, 16, 0), (128, 17, 0)])
 def test_lsh_kernel(dtype, d, Br, N, n_planes, offset):
     import torch
 
