@@ -35,6 +35,9 @@ bool attn_bf16_supported(const Problem& pb, int distr) {
 // launch lasts at least as long as its longest wave, 32 rows against all keys, however few SIMDs have one. With the copy
 // at hand (kt_in) what is left is the prologue at d = 128, where Q~ is gathered faster than Q_r (1.7 us; not for blocks
 // of 256 rows), against a wave's walk, and calls too small for either to matter.
+// Blocks of 64 x 128 at d = 128 hold a CU's LDS with two waves (whole K tiles; K_f is a quarter of one), so that more
+// than one workgroup per CU is a second round: fused | Q~ K^T there, G8 B11 H16 Hkv8 N99 Nk1150 46 | 59, B20 H16 Hkv4 N226
+// Nk385 79 | 99, one round, H16 N1024 causal 34 | 28; G4 B20 H16 Hkv4 N226 Nk385 92 | 102.
 // Groups of 16 fuse at a loss, and a fused launch cannot deal its keys out: there the copy's bytes are weighed against
 // the whole product, 1570 visible rows per key and the launch.
 // Measured, copy + fused | fused | Q~ K^T, us:
@@ -51,7 +54,8 @@ bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split) {
   const double rows = (double)(pb.H / pb.Hkv) * pb.N * (pb.causal ? 1.0 - 0.5 * pb.N / pb.Nk : 1.0);   // per key
   const double keys = (double)pb.B * pb.Hkv * pb.Nk;
   if (G >= 16 || n_split > 1) return rows < 1570.0 + 7.8e9 / (pb.d * keys);
-  const double gain = pb.d == 64 ? (G == 2 ? 0.8 : G == 4 ? 0.75 : 0.25) : (G == 2 ? 0.3 : G == 4 ? 0.5 : 0.6);
+  double gain = pb.d == 64 ? (G == 2 ? 0.8 : G == 4 ? 0.75 : 0.25) : (G == 2 ? 0.3 : G == 4 ? 0.5 : 0.6);
+  if (pb.d == 128 && pb.Bc == 128 && pb.Br == 64 && G >= 4 && (long long)pb.B * pb.H * ((pb.N + 63) / 64) > 256) gain = G == 4 ? 4.0 : 6.0;
   const double simds = 1024.0 * 32, wave_rows = (double)pb.B * pb.H * ((pb.N + pb.Br - 1) / pb.Br) * pb.Br;
   const double walk = (have_kt && pb.d == 128 ? simds : std::min(wave_rows, simds)) * pb.Nk;
   const double copy = have_kt ? (pb.d == 64 ? 0.1 : pb.Br == 256 ? 0.0 : 1.7) : 4.5 + 0.35e-6 * keys * pb.d;

@@ -86,6 +86,16 @@ def test_fused_d128(N, Nk, causal, Br, Bc, G):
 
 
 # groups of 16 (contraction zero-padded to one matrix step): fused from many rows per key on
+# Blocks of 64 x 128 at d = 128 take the fused product as soon as there are more workgroups than compute units, with kt_in
+# or without: the same bits.
+@pytest.mark.parametrize("G", [4, 8])
+@pytest.mark.parametrize("N,Nk,causal", [(513, 700, False), (577, 901, True)])
+def test_blocks_of_64_by_128(N, Nk, causal, G):
+    cfg = _cfg(128, H=32, Hkv=4, N=N, Nk=Nk, causal=causal, Br=64, Bc=128, n_groups=128 // G)
+    q, k, v, o = _check(cfg, heads=(0, 31))
+    assert np.array_equal(_call(cfg, q, k, v, None)[0], o)
+
+
 @pytest.mark.parametrize("d,N,Br", [(64, 2070, 64), (64, 2070, 256), (128, 1590, 64), (128, 1590, 128)])
 def test_fused_groups_of_16(d, N, Br):
     _check(_cfg(d, H=32, Hkv=1, N=N, Nk=N, causal=False, Br=Br, n_groups=d // 16), heads=(0, 13, 31))
