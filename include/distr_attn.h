@@ -204,7 +204,8 @@ int distr_attn_hyperplanes(uint64_t seed, int n_planes, int Br, float *host_out)
  * DISTR_ATTN_NOALLOC_MAX_BYTES inside the library instead of a workspace, so the call allocates
  * and frees nothing (p->workspace is ignored). Each GPU the library runs on holds its own copy
  * of the array until the process ends. A problem whose scratch exceeds the array is refused
- * with DA_ERR_WORKSPACE before anything is launched (kt_in removes the K^T part of the need).
+ * with DA_ERR_WORKSPACE before anything is launched (kt_in removes the K^T part of the need; so does
+ * S^ over the channels, which a small problem takes where there is no room for the copy).
  * All calls on one GPU share the array: calls that overlap in time on one GPU race; calls
  * queued on one stream do not.
  */

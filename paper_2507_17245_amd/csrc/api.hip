@@ -255,7 +255,10 @@ int scratch_base(const da_params* p, const Resolved& r, size_t need, bool no_all
                     "being captured: pass a workspace, or run the call once before capturing", need);
       void* ptr = nullptr;
       hipError_t e = hipMalloc(&ptr, need);
-      if (e != hipSuccess) return fail(DA_ERR_WORKSPACE, "hipMalloc(%zu) failed: %s", need, hipGetErrorString(e));
+      if (e != hipSuccess) {
+        (void)hipGetLastError();   // (not the next launch's)
+        return fail(DA_ERR_WORKSPACE, "hipMalloc(%zu) failed: %s", need, hipGetErrorString(e));
+      }
       if (g_ws_ptr[dev]) g_ws_retired[dev].push_back(g_ws_ptr[dev]);
       g_ws_ptr[dev] = ptr;
       g_ws_bytes[dev] = need;
@@ -370,6 +373,12 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
     lsh_in_kernel = lsh_in_kernel && few;
   } else if (!base && kt_room + table_need) {
     rc = scratch_base(p, r, kt_room + table_need, no_alloc, &base);
+    // Without room for the copy (the static array, a capture) a call that is light enough for it is taken as Q~ K^T.
+    if (rc == DA_ERR_WORKSPACE && kt_room && da::attn_bf16_light(r.pb)) {
+      fused = false;
+      kt_room = 0;
+      rc = table_need ? scratch_base(p, r, table_need, no_alloc, &base) : DA_OK;
+    }
     if (rc) return rc;
   }
   if (!share && table_need) table = (uint8_t*)(base + kt_room);

@@ -29,6 +29,16 @@ bool attn_bf16_supported(const Problem& pb, int distr) {
   return true;
 }
 
+// Query rows that see a key, masked ones taken off.
+static double visible_rows(const Problem& pb) {
+  return (double)(pb.H / pb.Hkv) * pb.N * (pb.causal ? 1.0 - 0.5 * pb.N / pb.Nk : 1.0);
+}
+
+// The transposed copy's bytes and launch against a seventh of the whole product, 1570 visible rows per key.
+bool attn_bf16_light(const Problem& pb) {
+  return visible_rows(pb) < 1570.0 + 7.8e9 / ((double)pb.d * pb.B * pb.Hkv * pb.Nk);
+}
+
 // Q~ K^T (see ScoreMode in attn_bf16_impl.h) instead of Q_r K_f^T where the transposed copy of K costs more than the
 // shorter contraction saves. The copy: its launch (4.5 us) and 0.35 us per million elements. The saving: `gain` us per
 // 10^9 (visible pairs times channels), by the group size (larger groups save products but have more channels to sum up); a
@@ -38,8 +48,7 @@ bool attn_bf16_supported(const Problem& pb, int distr) {
 // Blocks of 64 x 128 at d = 128 hold a CU's LDS with two waves (whole K tiles; K_f is a quarter of one), so that more
 // than one workgroup per CU is a second round: fused | Q~ K^T there, G8 B11 H16 Hkv8 N99 Nk1150 46 | 59, B20 H16 Hkv4 N226
 // Nk385 79 | 99, one round, H16 N1024 causal 34 | 28; G4 B20 H16 Hkv4 N226 Nk385 92 | 102.
-// Groups of 16 fuse at a loss, and a fused launch cannot deal its keys out: there the copy's bytes are weighed against
-// the whole product, 1570 visible rows per key and the launch.
+// Groups of 16 fuse at a loss, and a fused launch cannot deal its keys out: there attn_bf16_light decides.
 // Measured, copy + fused | fused | Q~ K^T, us:
 //   G2  d64  H16 N1024 causal 20 | 17 | 18, N4096 53 | 44 | 52, N5372 78 | 67 | 81; B2 H16 Hkv4 N523 Br256 23 | 19 | 21
 //       d128 H16 N1024 causal 35 | 30 | 26, N4412 99 | 90 | 97; B4 H16 N1024 60 | 46 | 49
@@ -51,9 +60,9 @@ bool attn_bf16_supported(const Problem& pb, int distr) {
 bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split) {
   if (attn_bf16_few_rows(pb, 1) || attn_bf16_short(pb, 1)) return true;
   const int G = pb.d / pb.n_groups;
-  const double rows = (double)(pb.H / pb.Hkv) * pb.N * (pb.causal ? 1.0 - 0.5 * pb.N / pb.Nk : 1.0);   // per key
+  const double rows = visible_rows(pb);
   const double keys = (double)pb.B * pb.Hkv * pb.Nk;
-  if (G >= 16 || n_split > 1) return rows < 1570.0 + 7.8e9 / (pb.d * keys);
+  if (G >= 16 || n_split > 1) return attn_bf16_light(pb);
   double gain = pb.d == 64 ? (G == 2 ? 0.8 : G == 4 ? 0.75 : 0.25) : (G == 2 ? 0.3 : G == 4 ? 0.5 : 0.6);
   if (pb.d == 128 && pb.Bc == 128 && pb.Br == 64 && G >= 4 && (long long)pb.B * pb.H * ((pb.N + 63) / 64) > 256) gain = G == 4 ? 4.0 : 6.0;
   const double simds = 1024.0 * 32, wave_rows = (double)pb.B * pb.H * ((pb.N + pb.Br - 1) / pb.Br) * pb.Br;

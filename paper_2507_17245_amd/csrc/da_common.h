@@ -204,6 +204,7 @@ bool attn_bf16_supported(const Problem& pb, int distr);
 // hand; n_split: the shares it would be cut into), and into how many shares the keys of a Q block are cut when the
 // product is that one or the exact one.
 bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split);
+bool attn_bf16_light(const Problem& pb);   // Q~ K^T is good enough to run where there is no room for the transposed copy
 int attn_bf16_splits(const Problem& pb, int distr);
 // Few query rows against many keys (decoding): a kernel of its own, with its own number of shares.
 bool attn_bf16_few_rows(const Problem& pb, int distr);

@@ -123,6 +123,30 @@ def test_fused_without_kt_in():
         assert np.array_equal(got.double().cpu().numpy(), o)
 
 
+def test_no_room_for_the_transposed_keys():
+    """Transposed keys that the fixed array does not hold: the entry that allocates nothing takes the product over the channels
+    where that is light enough, instead of refusing the call; with room it is fused."""
+    import torch
+
+    import gpu_util as U
+    import paper_2507_17245_amd as da
+    cfg = _cfg(64, B=2, H=16, Hkv=16, N=1000, Nk=8192, causal=False, Br=128, n_groups=32)
+    print(f"case {cfg}", flush=True)
+    host = W.make(cfg)
+    q, k, v = (U.to_dev(x, "bf16") for x in host)
+    p = da.make_params(q, k, v, Br=cfg.Br, n_groups=cfg.n_groups, n_planes=cfg.n_planes, lsh_seed=cfg.lsh_seed)
+    assert da.distr_attn_kt_bytes(p) > da.distr_attn_noalloc_max_bytes()
+    fused = da.distr_attn_fwd_ex(q, k, v, torch.empty_like(q), p).double().cpu().numpy()
+    assert np.array_equal(fused, _call(cfg, q, k, v, _transposed(cfg, q, k))[0])
+    o = da.distr_attn_fwd_noalloc(q, k, v, torch.empty_like(q), p).double().cpu().numpy()
+    tiles = W.sample_tiles(cfg, heads=(0, 15), batch=1)
+    ref = oracle.distr_fwd_tiles(*host, U.oracle_params(cfg), tiles)
+    for i, (b, h, t) in enumerate(tiles):
+        rows = min(cfg.Br, cfg.N - t * cfg.Br)
+        for x in (fused, o):
+            U.assert_close(x[b, h, t * cfg.Br:t * cfg.Br + rows], ref[i, :rows], "bf16", f"block {b, h, t}")
+
+
 def test_fused_clamps_to_half_range():
     """|q| * scale * log2 e beyond 65504 and |k| beyond 65504 / G* are clamped (documented limit of the product over the
     groups). One large value in head 0's queries, one in head 1's keys, on a channel that is sampled, against small
