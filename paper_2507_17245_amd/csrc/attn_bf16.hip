@@ -72,7 +72,7 @@ bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split) {
 }
 
 // Key shares per Q block, for launches that would leave compute units without a workgroup: one
-// four-wave workgroup (two of two waves) for each, at least four tiles per share, and only where the
+// four-wave workgroup (two of two waves, half of one of eight) for each, at least four tiles per share, and only where the
 // tiles taken off a workgroup's walk outweigh the combine kernel (4 us, about 12 tiles) and, grouped,
 // the LSH stage in a kernel of its own (another 18). Measured, 1 | 256 | 512 workgroups: exact H16 N200 Nk8192
 // d64 71 | 19 | 22 us; N1000 Nk8192 d128 109 | 72 | 80; N200 Nk32768 d128 486 | 90 | 87; N2048 d64 causal 22 | 22 | 29.
@@ -91,7 +91,8 @@ int attn_bf16_splits(const Problem& pb, int distr) {
 
 // O of a row = sum over the shares of 2^(reference - largest reference) O_share, over the same sum of the
 // row sums. A workgroup takes 256 / L / (D/4) rows, a thread four channels of every L-th share: few rows
-// with many shares (decoding) would otherwise be a chain of loads in a handful of waves.
+// with many shares (decoding) would otherwise be a chain of loads in a handful of waves. A share whose sum is not above
+// zero is empty or holds a NaN: its weight is 0, and 0 times its NaN sum still makes the row NaN.
 template <int D, int L>
 __global__ __launch_bounds__(256) void attn_bf16_combine_kernel(const float* __restrict__ part_o, const f32x2* __restrict__ part_stat,
                                                                 bf16* __restrict__ o, float* __restrict__ lse, int rows, int n_split) {

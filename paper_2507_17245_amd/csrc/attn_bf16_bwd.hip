@@ -699,7 +699,7 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(const float* __restrict
 // head in one workgroup and one launch. Wave w owns the keys 32*w .. as in bwd_dkv_kernel; row tiles of 64
 // pass through LDS, where they are also prepared (D_i, Q~). dS of a tile, of all keys, meets in LDS, and
 // the workgroup takes dQ~^T = K^T dS^T from it: five products instead of the seven of the two kernels, Q, dO
-// and O read once, no scratch.
+// and O read once, nothing in scratch (the call still asks for the room of the other kernels).
 //
 // Bound: memory traffic (5 + 3 tensors of N rows) where there are heads to fill the chip, LDS cycles next.
 // Iteration `it`, one barrier each, so that a wave's products, LDS phases and waits fall beside

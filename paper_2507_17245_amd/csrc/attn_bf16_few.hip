@@ -12,7 +12,7 @@
 //     at the full rate. The states meet in LDS at the end, the shares in the combine kernel;
 //   * DistrAttention is taken as S^ = Q~ K^T (ScoreMode kReplicated): no transposed copy of the
 //     cache. The grouping of a head's N <= 64 rows (one Q block) is computed by the workgroup, in the
-//     defining float order, while its first tiles travel.
+//     defining float order, while its first tiles travel; hash and channel rank as one key.
 // Layouts, operands and the rounding of P are the general kernel's (attn_bf16_impl.h).
 // Measured (B1 H32 Hkv8 N1 Nk16384 d64, 34 MB of keys and values): 11 us + 4 us for the combine kernel, 130 us +
 // 7 us for the key pre-pass before; B16 H32 Hkv4 N1 Nk8192: 33 us, 4.1 TB/s (174 us).

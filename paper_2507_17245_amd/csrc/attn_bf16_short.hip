@@ -10,7 +10,7 @@
 //     32 keys on the matrix pipe beside the exponentials of these; causal waves stop at their last key;
 //   * DistrAttention is taken as S^ = Q~ K^T (ScoreMode kReplicated).
 // Layouts, operands, rounding of P and the lazy reference are the general kernel's (attn_bf16_impl.h).
-// Measured, general | this: H12 N197 B64 44 | 31 us (exact 29 | 21), B8 14.3 | 13.1, B1 13.0 | 12.0; N128 B64 23 | 15;
+// Measured, general | this: H12 N197 B64 41 | 27 us (exact 29 | 21), B8 14.3 | 13.1, B1 13.0 | 12.0; N128 B64 23 | 15;
 // N64 B64 12.1 | 11.1, B4 9.3 | 7.6; H32 Hkv8 causal N256 B16 exact 20 | 14.
 #include "attn_bf16_impl.h"
 

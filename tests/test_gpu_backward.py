@@ -1,4 +1,4 @@
-"""GPU parity of the backward pass (float tensors: float arithmetic on the vector ALUs; bf16 tensors: matrix-core kernels) against the CPU oracle (gradient of the forward with the
+"""GPU parity of the backward pass (float tensors: float matrix instructions; bf16 tensors: bf16 ones) against the CPU oracle (gradient of the forward with the
 grouping held fixed; the paper, Sec. 4.3-4.4, trains through the method without giving one)."""
 import numpy as np
 import pytest

@@ -64,10 +64,11 @@ def test_caller_grouping_table(base, kw):
 
 
 def test_half_range_clamp_of_the_reduced_product():
-    """bf16 DistrAttention holds Q_r (times softmax_scale * log2 e) and K_f in half precision:
-    |q| * softmax_scale * log2(e) beyond 65504 and |k| beyond 65504 / G* are clamped (documented
-    input limit). The oracle, fed the clamped values and the grouping of the unclamped Q (the
-    LSH stage sees the original values), must agree."""
+    """Values beyond the limits of the product over the groups (|q| * softmax_scale * log2(e) and |k| * G* over 65504) in
+    a call of at most 256 rows, which takes the product over the channels: the single visible scores are so far apart that
+    the softmax is the same with the values clamped or not, so the output must agree with the oracle on clamped values and
+    the grouping of the unclamped Q. The clamp itself is checked where the product over the groups runs, in the tests of
+    the fused kernel."""
     import gpu_util as U
     for n_groups in (32, 16):
         cfg = small("vit", B=1, H=2, Hkv=2, N=150, n_groups=n_groups)

@@ -62,6 +62,10 @@ def _check(cfg, heads=None, batches=(0,)):
     for kw in (dict(hash_out=hashes), dict(perm_in=perm)):                # the LSH kernel's table, the caller's
         o2, lse2 = _call(cfg, q, k, v, kt, **kw)
         assert np.array_equal(o2, o) and np.array_equal(lse2, lse)
+    # the transposed keys do not depend on the grouping's options: those of a call with others serve as well
+    with_others = cfg.scaled(lsh_seed=cfg.lsh_seed + 1, n_planes=cfg.n_planes + 3, Br=64 if cfg.Br == 128 else 128)
+    o3, _ = _call(cfg, q, k, v, _transposed(with_others, q, k))
+    assert np.array_equal(o3, o)
     other, _ = _call(cfg, q, k, v, _transposed(cfg, q, -k))
     assert np.abs(other - o).max() > 0.1, "kt_in was not read"
     return q, k, v, o
