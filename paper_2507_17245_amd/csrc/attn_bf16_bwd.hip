@@ -153,12 +153,15 @@ __device__ inline void read_transposed(const char* tile, int blk, const OperandO
 //                  Tw-fold in length; with (nearly) all of them resident at once, head after head leaves compute
 //                  units with only long or only short ones. A head still stays on one XCD when the head count
 //                  is a multiple of 8.
-enum UnitOrder { kHeadMajor, kLongestFirst };
-constexpr int kBalancedUnits = 8 * 256;
+//   kPaired        the same with the second round reversed (paired_tile), where two workgroups share a compute unit: not for
+//                  dK/dV at d = 128, which fills one (H16 N4096 270 us, 289 reversed). Backward, longest first | this: d64 H32
+//                  N2048 93.5 | 88.9 us, H16 N4096 162 | 151, H32 Hkv8 N4096 274 | 266; d128 H16 N2048 132 | 127.
+enum UnitOrder { kHeadMajor, kLongestFirst, kPaired };
+constexpr int kBalancedUnits = 8 * kComputeUnits;
 __device__ inline void unit_of(int id, int units, int Tw, int order, int& head, int& tile) {
-  if (order == kLongestFirst) {
+  if (order != kHeadMajor) {
     const int heads = units / Tw;
-    tile = id / heads;
+    tile = order == kPaired ? paired_tile(id / heads, heads, Tw) : id / heads;
     head = id % heads;
   } else {
     if ((units & 7) == 0) id = (id & 7) * (units >> 3) + (id >> 3);
@@ -1087,8 +1090,8 @@ hipError_t launch_attn_bf16_bwd(const void* q, const void* k, const void* v, con
 #undef DA_SHORT
     return hipGetLastError();
   }
-  const int dq_order = pb.causal && q_units <= kBalancedUnits ? kLongestFirst : kHeadMajor;
-  const int dkv_order = pb.causal && k_units * hsplit <= kBalancedUnits ? kLongestFirst : kHeadMajor;
+  const int dq_order = pb.causal && q_units <= kBalancedUnits ? kPaired : kHeadMajor;
+  const int dkv_order = pb.causal && k_units * hsplit <= kBalancedUnits ? (pb.d == 64 ? kPaired : kLongestFirst) : kHeadMajor;
 #define DA_BWD(DD)                                                                                                   \
   do {                                                                                                               \
     hipLaunchKernelGGL((bwd_dq_kernel<DD>), dim3((unsigned)q_units), dim3(kBwdThreads), 0, stream, (const bf16*)q,   \

@@ -181,14 +181,15 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
   // n_split > 1: the unit's key tiles are dealt out to that many workgroups (below).
   int unit = n_split > 1 ? (int)blockIdx.x % total_units : (int)blockIdx.x;
   int bh, t;
-  if (causal == 2) {
+  if (causal >= 2) {
     // Causal blocks differ up to Tq-fold in length. When (nearly) all of them are resident at
     // once, head after head would leave whole compute units with only long or only short
     // blocks: take them longest first over all heads, so that every round of the dispatcher
     // spreads one length class over the chip and the short blocks fill the slots that free up
     // last. With a head count that is a multiple of 8 a head still stays on one XCD.
     const int n_bh = total_units / Tq;
-    t = Tq - 1 - unit / n_bh;
+    t = unit / n_bh;
+    t = Tq - 1 - (causal == 3 ? paired_tile(t, n_bh, Tq) : t);
     bh = unit % n_bh;
   } else {
     // Each XCD walks a contiguous range of units, so the Q blocks of one head run together
@@ -945,8 +946,14 @@ hipError_t launch_one(const void* q, const void* k, const void* v, void* o, cons
   // causal_mode 2 = blocks issued longest first over all heads (see the kernel): for problems
   // of up to 8 workgroups per compute unit, where load balance matters more than L2 locality
   // (with more blocks the dispatcher balances by itself and the head-major order fetches half
-  // as many bytes from HBM).
-  const int causal_mode = pb.causal ? (units <= 8 * 256 ? 2 : 1) : 0;
+  // as many bytes from HBM). 3 = the second round of them reversed: where two workgroups share a compute unit (blocks
+  // of 256 rows fill one: H16 N8192 d128 exact 249 us, 287 reversed) and, fused at d = 64, up to three rounds (three
+  // fit there, beyond them it is even: N7500 H16 120 | 119, N3700 H32 66 | 67). Measured, 2 | 3, exact and fused:
+  //   d64   H32 N2048 30.0 | 28.6, 35.7 | 33.4; H32 N2500 40.0 | 36.2, 42.5 | 39.5; H24 N4096 67.4 | 62.5, 68.3 | 63.4
+  //         exact, more rounds: H32 N4096 79.1 | 76.4, H16 N7500 132 | 123, H32 N6000 155.3 | 154.8
+  //   d128  H32 N2048 47.9 | 44.4, 53.3 | 50.6; H16 N4096 82.3 | 75.9, 88.7 | 82.3; H16 N8192 264 | 253, 253 | 242
+  const bool paired = BR <= 128 && (MODE != kFused || D == 128 || units <= 3 * kComputeUnits);
+  const int causal_mode = pb.causal ? (units <= 8 * kComputeUnits ? (paired ? 3 : 2) : 1) : 0;
   hipLaunchKernelGGL((attn_bf16_kernel<D, BR, BC, KRED, MODE, NG>), dim3((unsigned)(units * pb.n_split)), dim3(BR * 2), 0,
                      stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, perm, (const f16*)kt,
                      (pb.Nk + kKtPad - 1) / kKtPad * kKtPad, pb.H, pb.Hkv, pb.N, pb.Nk, Tq, causal_mode,

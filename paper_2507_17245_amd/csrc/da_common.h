@@ -125,6 +125,17 @@ __device__ inline void settle_doubts(const bool (&doubt)[4], bool (&positive)[4]
       if (lane == __builtin_ctzll(left)) positive[i] = up & 1;
 }
 
+// Causal tiles issued longest first over all heads: which tile (0 = the longest) comes at place `at` of a head's `tiles`
+// ones, with the second round of workgroups (one per compute unit) in the opposite order: the compute unit that got the
+// longest tile of the first round gets the shortest of the second, where it would otherwise get the longest again. The units'
+// sums then differ by a round's spread instead of twice that, which is more than the workgroups that follow even out (at
+// 1024 of them the third and fourth round are a third of the work, at 512 there is none).
+constexpr int kComputeUnits = 256;
+__device__ inline int paired_tile(int at, int heads, int tiles) {
+  const int round = heads < kComputeUnits ? kComputeUnits / heads : 1;
+  return at >= round && at < 2 * round ? min(2 * round, tiles) - 1 - (at - round) : at;
+}
+
 // Exchange between the wave halves: v_permlane32_swap swaps the upper 32 lanes of its first
 // operand with the lower 32 lanes of its second; fed the same value twice it leaves, in every
 // lane, the values of lanes l % 32 (first operand) and l % 32 + 32 (second operand). Written as

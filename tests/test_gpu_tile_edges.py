@@ -338,3 +338,19 @@ def test_bf16_short(N, Nk, causal, B, Br, G):
     o, _, _ = U.run_gpu(cfg, q, k, v, distr=False, lse_out=lse)
     U.assert_close(o, oracle.exact_fwd(q, k, v, p), "bf16")
     assert np.abs(lse.cpu().numpy() - oracle.lse(q, k, p, distr=False)).max() <= 2e-2
+
+
+# Causal launches whose second round of workgroups is issued in the opposite order: a whole second round, one that the
+# tiles end inside of, more heads than compute units. Every row of every head, forward and gradients.
+@pytest.mark.parametrize("B,H,Hkv,N,Br", [(1, 100, 50, 500, 64), (2, 12, 4, 910, 64), (1, 300, 300, 200, 64), (2, 70, 70, 600, 128)])
+def test_causal_order(B, H, Hkv, N, Br):
+    import gpu_util as U
+    from test_gpu_backward import run_backward
+    cfg = W.CONFIGS["llama"].scaled(B=B, H=H, Hkv=Hkv, N=N, Br=Br, recipe="normal")
+    _forward(cfg)
+    _forward(cfg, distr=False)
+    q, k, v = W.make(cfg)
+    dout = W.make_grad(cfg)
+    for what, g, r in zip(("dq", "dk", "dv"), run_backward(cfg, q, k, v, dout, True), oracle.distr_bwd(q, k, v, dout, U.oracle_params(cfg))):
+        err, unit = np.abs(g - r), max(1.0, np.abs(r).max())
+        assert err.max() <= U.BF16_MAX_ABS * unit and err.mean() <= U.BF16_MEAN_ABS * unit, f"{what}: {err.max():.4g} {err.mean():.4g}"
