@@ -16,13 +16,11 @@
 //          taken again the defining way.
 //   float  the defining sums on the vector ALUs, from LDS.
 // Measured (rows walked column by column in global memory, four at a time | now): bf16 H16 N200 d128 Br128
-// 21.5 | 9.2 us, H16 N2048 d64 Br256 17 | 9.0, float H8 N2048 d64 Br128 13.8 | 5.7 us, float H8 N2048 d64 blocks of 64 rows
+// 21.5 | 6.9 us, H16 N2048 d64 Br256 17 | 9.0, float H8 N2048 d64 Br128 13.8 | 5.7 us, float H8 N2048 d64 blocks of 64 rows
 // 6.4 | 4.9 us.
 #include "da_common.h"
 
 namespace da {
-
-constexpr int kLshThreads = 256;
 
 // LDS of one workgroup
 template <typename T, int D, int BR>
@@ -45,13 +43,13 @@ __device__ inline int lsh_chunk_swz(int row) {
 }
 
 // Rows r0 .. of `block` (`rows` of them exist, the rest reads as zeros) into LDS.
-template <typename T, int D, int CR, bool SWZ>
+template <typename T, int D, int CR, bool SWZ, int THREADS>
 __device__ inline void lsh_stage_rows(const T* block, int rows, int r0, char* dst) {
   typedef __attribute__((address_space(3))) void lds_void;
-  constexpr int CH = D * (int)sizeof(T) / 16, N = CR * CH / kLshThreads;
-  static_assert(CR * CH % kLshThreads == 0, "whole loads per thread");
+  constexpr int CH = D * (int)sizeof(T) / 16, N = (CR * CH + THREADS - 1) / THREADS;
+  static_assert(CR * CH % 64 == 0, "whole loads per wave");
   if (((uintptr_t)block & 15) != 0) {   // (a tensor of the stand-alone entry, which asks for no alignment)
-    for (int i = threadIdx.x; i < CR * D; i += kLshThreads) {
+    for (int i = threadIdx.x; i < CR * D; i += THREADS) {
       const int row = i / D, at = i % D * (int)sizeof(T), chunk = at / 16;
       *(T*)(dst + row * (D * (int)sizeof(T)) + (SWZ ? chunk ^ lsh_chunk_swz<D>(row) : chunk) * 16 + at % 16) =
           r0 + row < rows ? block[(size_t)(r0 + row) * D + i % D] : (T)0.0f;
@@ -62,7 +60,8 @@ __device__ inline void lsh_stage_rows(const T* block, int rows, int r0, char* ds
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)block, 0, (unsigned)rows * D * sizeof(T), 0x00020000);
 #pragma unroll
   for (int j = 0; j < N; ++j) {
-    const int blk = j * (kLshThreads / 64) + wave, slot = blk * 64 + lane;
+    const int blk = j * (THREADS / 64) + wave, slot = blk * 64 + lane;
+    if (CR * CH % THREADS != 0 && blk * 64 >= CR * CH) break;   // (more waves than 1 KB blocks)
     const int row = slot / CH, pc = slot % CH;
     const int chunk = SWZ ? pc ^ lsh_chunk_swz<D>(row) : pc;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + blk * 1024), 16, row * (D * (int)sizeof(T)) + chunk * 16,
@@ -72,7 +71,7 @@ __device__ inline void lsh_stage_rows(const T* block, int rows, int r0, char* ds
 
 // Sign codes of the bf16 block's channels, projections p0 .. p0 + 15, into lds.code. `rows`: a multiple of 32, the rest of
 // the block is zeros.
-template <int D, int BR>
+template <int D, int BR, int THREADS>
 __device__ inline void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int rows, int p0, int n_planes) {
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
   constexpr int RPAD = LshLds<bf16, D, BR>::RPAD, ROWB = D * 2;
@@ -91,7 +90,7 @@ __device__ inline void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int rows, int 
   // (2 * (2*BR + BR/16) * 2^-24), and the defining chain's, BR fused multiply-adds (BR * 2^-24).
   // The absolute term covers products flushed to zero.
   constexpr float kDoubt = 3.1e-7f * BR, kTiny = 1e-30f;
-  for (int ct = wave; ct < D / 16; ct += kLshThreads / 64) {
+  for (int ct = wave; ct < D / 16; ct += THREADS / 64) {
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f}, bnd = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int ks = 0; ks < BR / 32; ++ks) {
@@ -134,20 +133,20 @@ __device__ inline void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int rows, int 
 }
 
 // `rows` rows of D channels at `block`; perm and hash (either may be null): the block's table entries.
-template <typename T, int D, int BR>
+template <typename T, int D, int BR, int THREADS>
 __device__ inline void lsh_block(const T* __restrict__ block, int rows, int n_planes, int gray_mode, uint64_t seed,
                                  uint8_t* __restrict__ perm, uint32_t* __restrict__ hash, LshLds<T, D, BR>& lds) {
   using L = LshLds<T, D, BR>;
-  constexpr int NPG = kLshThreads / D;        // threads per channel
+  constexpr int NPG = THREADS / D;            // threads per channel
   const int tid = threadIdx.x, c = tid % D, pg = tid / D;
   const int taken = (rows + 31) / 32 * 32;    // (a block of few rows costs what they cost)
   for (int p0 = 0; p0 < n_planes; p0 += 16) {
     if constexpr (L::MATRIX) {
-      if (p0 == 0) lsh_stage_rows<T, D, BR, true>(block, rows, 0, lds.rows);
+      if (p0 == 0) lsh_stage_rows<T, D, BR, true, THREADS>(block, rows, 0, lds.rows);
       else __syncthreads();                   // the last table is no longer read
       bf16* rp1 = (bf16*)lds.table;
       bf16* rp2 = rp1 + 16 * L::RPAD;
-      for (int i = tid; i < BR * 16; i += kLshThreads) {
+      for (int i = tid; i < BR * 16; i += THREADS) {
         const int r = i % BR, pl = i / BR;
         if (r >= taken) continue;
         const float rv = p0 + pl < n_planes ? hyperplane_entry(seed, (uint32_t)(p0 + pl), (uint32_t)r) : 0.0f;
@@ -157,7 +156,7 @@ __device__ inline void lsh_block(const T* __restrict__ block, int rows, int n_pl
       }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
-      lsh_codes_matrix<D, BR>(lds, taken, p0, n_planes);
+      lsh_codes_matrix<D, BR, THREADS>(lds, taken, p0, n_planes);
     } else {
       constexpr int PPT = 16 / NPG;           // projections per thread: pg*PPT .. pg*PPT + PPT - 1
       float* R = (float*)lds.table;           // [row][16]
@@ -166,9 +165,9 @@ __device__ inline void lsh_block(const T* __restrict__ block, int rows, int n_pl
       for (int j = 0; j < PPT; ++j) acc[j] = 0.0f;
       for (int r0 = 0; r0 < rows; r0 += L::CR) {
         if (p0 + r0 > 0) __syncthreads();     // the staged rows are no longer read
-        lsh_stage_rows<T, D, L::CR, false>(block, rows, r0, lds.rows);
+        lsh_stage_rows<T, D, L::CR, false, THREADS>(block, rows, r0, lds.rows);
         if (r0 == 0) {
-          for (int i = tid; i < min(rows, BR) * 16; i += kLshThreads)
+          for (int i = tid; i < min(rows, BR) * 16; i += THREADS)
             R[i] = p0 + (i & 15) < n_planes ? hyperplane_entry(seed, (uint32_t)(p0 + (i & 15)), (uint32_t)(i >> 4)) : 0.0f;
           if (p0 == 0 && tid < D) lds.code[tid] = 0;
         }
@@ -221,30 +220,45 @@ __device__ inline void lsh_block(const T* __restrict__ block, int rows, int n_pl
   if (tid < D) perm[tid] = lds.perm[tid];
 }
 
-template <typename T, int D, int BR>
-__global__ __launch_bounds__(kLshThreads) void lsh_group_kernel(
+template <typename T, int D, int BR, int THREADS>
+__global__ __launch_bounds__(THREADS) void lsh_group_kernel(
     const T* __restrict__ q, uint8_t* __restrict__ perm_out, uint32_t* __restrict__ hash_out,
     int N, int Tq, int n_planes, int gray_mode, uint64_t seed) {
   __shared__ LshLds<T, D, BR> lds;
   const int t = blockIdx.x % Tq;
   const size_t bh = blockIdx.x / Tq;
   const size_t at = (size_t)blockIdx.x * D;
-  lsh_block<T, D, BR>(q + (bh * N + (size_t)t * BR) * D, min(BR, N - t * BR), n_planes, gray_mode, seed,
+  lsh_block<T, D, BR, THREADS>(q + (bh * N + (size_t)t * BR) * D, min(BR, N - t * BR), n_planes, gray_mode, seed,
                       perm_out ? perm_out + at : nullptr, hash_out ? hash_out + at : nullptr, lds);
 }
 
 template <typename T, int D>
 static hipError_t launch_rows(const T* q, const Problem& pb, uint8_t* perm_out, uint32_t* hash_out, hipStream_t stream) {
   const int Tq = (pb.N + pb.Br - 1) / pb.Br;
-  const dim3 grid((unsigned)((long long)pb.B * pb.H * Tq)), block(kLshThreads);
-#define DA_LSH(BR)                                                                                                       \
-  hipLaunchKernelGGL((lsh_group_kernel<T, D, BR>), grid, block, 0, stream, q, perm_out, hash_out, pb.N, Tq, pb.n_planes, \
-                     pb.gray_mode, pb.seed)
+  const long long units = (long long)pb.B * pb.H * Tq;
+#define DA_LSH_T(BR, THREADS)                                                                                                       \
+  hipLaunchKernelGGL((lsh_group_kernel<T, D, BR, THREADS>), dim3((unsigned)units), dim3(THREADS), 0, stream, q, perm_out, hash_out, \
+                     pb.N, Tq, pb.n_planes, pb.gray_mode, pb.seed)
+#define DA_LSH(BR)                                                      \
+  do {                                                                  \
+    if constexpr (sizeof(T) == 2 || D == 128) {                         \
+      if (wide) DA_LSH_T(BR, 512);                                      \
+    }                                                                   \
+    if constexpr (sizeof(T) == 2 || D == 64) {                          \
+      if (!wide) DA_LSH_T(BR, 256);                                     \
+    }                                                                   \
+  } while (0)
   // Q blocks of 64, 128, 256 rows, K blocks (mirrored form) of 32, 64, 128. A sequence shorter than its block takes the
   // kernel of the shortest block that holds it: less LDS, so more workgroups on a CU (N44 Br256 d128 bf16 with 17
   // projections, 576 heads: 11 us as a block of 64, 15 walked in global memory).
   int rows = pb.Br;
   while (rows > 32 && pb.N <= rows / 2) rows /= 2;
+  // Threads of a workgroup: 512 where the chip is not full without them, and for the float sums of 128 channels at any size
+  // (two projections a thread and chain, not eight; the 1024 chains of 64 channels are short with 256 threads, and barriers
+  // of more waves cost more). us, 256 | 512 threads: bf16 d128 H16 N200 Br128 8.2 | 6.9, H16 N2048 Br256 15.8 | 10.9,
+  // 1000 rows of 48 heads in blocks of 64 8.7 | 10.0; bf16 d64 H16 N2048 Br128 6.6 | 6.2, 1024 blocks 10.7 | 12.5; float d128
+  // H8 N2048 Br128 8.8 | 6.6, 8192 blocks 154 | 139; float d64 H8 N2048 Br128 5.4 | 5.9.
+  const bool wide = sizeof(T) == 2 ? units <= kComputeUnits : D == 128;
   switch (rows) {
     case 32: DA_LSH(32); break;
     case 64: DA_LSH(64); break;
@@ -253,6 +267,7 @@ static hipError_t launch_rows(const T* q, const Problem& pb, uint8_t* perm_out, 
     default: return hipErrorInvalidValue;
   }
 #undef DA_LSH
+#undef DA_LSH_T
   return hipGetLastError();
 }
 
