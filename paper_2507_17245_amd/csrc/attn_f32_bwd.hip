@@ -15,19 +15,21 @@
 //
 //   bwd_delta_kernel  D_i of every row, left at the head of dq, which the last kernel overwrites
 //   bwd_dkv_kernel    one workgroup per (kv head, 32 keys), lane = key, K and V rows resident; its waves deal the 32-row query tiles of all query heads of the kv head
-//                     out among themselves. Q~ = Q whose channels are replaced by their group's
-//                     sampled one, gathered from global memory (dK = scale dS^T Q~: every member of a
-//                     group receives its group's column). S^ over the groups of 2 or 4 channels, as in
-//                     the other kernels, else Q~ K^T.
+//                     out among themselves. Groups of 2 and 4 channels: a wave takes a run of tiles, sums K_f of its keys once for
+//                     every Q block it enters and reads Q_r (gathered from global memory, groups' order) for S^ and
+//                     dK_f, both over n_groups; dK_f of a Q block meets the channels by way of LDS when the wave leaves it.
+//                     Other group sizes: Q~ = Q whose channels are replaced by their group's sampled one (dK =
+//                     scale dS^T Q~: every member of a group receives its group's column).
 //   bwd_dq_kernel     one workgroup per 32 query rows, lane = query row, waves deal the key tiles
 //                     out. Groups of 2 and 4 channels: the K tile lies in LDS in sorted channel order,
 //                     members adjacent and summed as they are read, S^ and dQ_r contract over
 //                     n_groups; other group sizes take Q~ and sum dQ~ over the members at the end.
 // The waves' partial sums meet in LDS once, at the end, in a fixed order: as in the forward no wave waits
 // for another before that, and few rows still give every SIMD work. Bound: the matrix
-// instruction (64 cycles for 4096 FLOP), 7 products over d per (query, key) pair, 6 with groups of two.
-// Measured (B1 H8 N2048 d64 n_groups 32): delta 4, dK/dV 174, dQ 90 us, 87 and 95 TFLOP/s of the 157 the
-// instruction can reach (float multiply-adds on the vector ALUs: dK/dV 2740, dQ 1980 us).
+// instruction (64 cycles for 4096 FLOP): 7 products over d per (query, key) pair, 5 with groups of two, 4 with groups
+// of four. Measured (B1 H8 N2048 d64 n_groups 32): delta 4, dK/dV 144, dQ 91 us; the matrix pipe is busy 2/3 of the time
+// (dK/dV with S^ and dK over the groups' members, K_f summed for every tile anew: 176 us; backward d128 642 -> 504 us, groups of four
+// 572 -> 411; float multiply-adds on the vector ALUs: dK/dV 2740, dQ 1980 us).
 #include <type_traits>
 
 #include "f32_tiles.h"
@@ -104,23 +106,15 @@ __device__ inline f32x16 row_product(const float* row, int hh, const float* b) {
   }
   return acc.sum();
 }
-// contraction over groups of G channels: `order` is the block's sorted order, q a row of Q~, k a row of K
-template <int D, int G>
-__device__ inline f32x16 group_product(const float* q, const float* k, int hh, const uint8_t* order) {
-  ChannelSum<D / G / 2> acc;
+// (rows of KRED floats, HS = KRED/2 of them from either half of the wave) x (operand b)
+template <int HS>
+__device__ inline f32x16 group_product(const float* row, int hh, const float (&b)[HS]) {
+  ChannelSum<HS> acc;
 #pragma unroll
-  for (int c16 = 0; c16 < D / 2; c16 += 16) {
-    const u32x4 e4 = *(const u32x4*)&order[hh * (D / 2) + c16];
+  for (int c = 0; c < HS; c += 4) {
+    const f32x4 x = *(const f32x4*)&row[hh * HS + c];
 #pragma unroll
-    for (int e = 0; e < 16; e += G) {
-      int ch[G];
-#pragma unroll
-      for (int m = 0; m < G; ++m) ch[m] = (e4[(e + m) >> 2] >> (8 * ((e + m) & 3))) & (D - 1);
-      float x = k[ch[0]];
-#pragma unroll
-      for (int m = 1; m < G; ++m) x += k[ch[m]];
-      acc.step((c16 + e) / G, q[ch[0]], x);
-    }
+    for (int e = 0; e < 4; ++e) acc.step(c + e, x[e], b[c + e]);
   }
   return acc.sum();
 }
@@ -192,7 +186,11 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
   __shared__ __attribute__((aligned(16))) float k_lds[K_LDS ? kTile * RS : 4];
   __shared__ __attribute__((aligned(16))) float v_lds[SHARED ? kTile * RS : 4];
   __shared__ __attribute__((aligned(16))) float stat_lds[W][2][kTile];   // lse, D_i
-  __shared__ __attribute__((aligned(16))) uint8_t map_lds[W][3][D];
+  // G = 1: sorted order, sampled channel of a channel's group. G > 1: of this Q block and the one before or after it, sorted
+  // order and the channels' groups
+  __shared__ __attribute__((aligned(16))) uint8_t map_lds[W][G > 1 ? 4 : 2][D];
+  // G > 1: Q_r, KRED sampled channels a row, in groups' order; ROWS of its rows per load
+  constexpr int KRED = D / G, HS = KRED / 2, RQ = KRED + 4, NG = (KRED + 31) / 32, ROWS = G > 1 ? 64 / KRED : 1, QL = kTile / ROWS;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -232,25 +230,53 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
     wave_order();
     return *(const uint32_t*)&from[lane % (D / 4) * 4];
   };
-  Tile<D> qt, dt;
+  typename std::conditional<G == 1, Tile<D>, char>::type qt;
+  float qr[QL];
+  Tile<D> dt;
   float lse_reg, delta_reg;
-  auto load_q = [&](int it) {
+  // G > 1: the table of iteration it's Q block into place `slot`; map_reg holds it
+  auto block_of = [&](int it) { return (int)(head_of(it) * Tq) + tile_of(it) * kTile / Br; };
+  auto store_map = [&](int slot) {
+    uint8_t* order = map_lds[w][2 * slot];
+    uint8_t* groups = map_lds[w][2 * slot + 1];
+    wave_order();
+#pragma unroll
+    for (int u = 0; u < D / 64; ++u) {
+      const int i = u * 64 + lane, c = map_reg[u] & (D - 1);
+      order[i] = (uint8_t)c;
+      groups[c] = (uint8_t)(i / G);
+    }
+    wave_order();
+  };
+  auto load_q = [&](int it, int slot) {
     const size_t bh = head_of(it);
     const int i0 = tile_of(it);
     const __amdgpu_buffer_rsrc_t q_rsrc = head_rsrc(q + bh * N * D, (unsigned)N * D * 4);
-    if (perm) qt.gather(q_rsrc, i0, lane, sampled());
-    else qt.load(q_rsrc, i0, lane);
+    if constexpr (G > 1) {
+      const int c = map_lds[w][2 * slot][lane % KRED * G];   // the sampled channel of this lane's group
+#pragma unroll
+      for (int u = 0; u < QL; ++u)
+        qr[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(q_rsrc, lane / KRED * (D * 4) + c * 4, i0 * Tile<D>::BYTES + u * ROWS * (D * 4), 0));
+    } else {
+      if (perm) qt.gather(q_rsrc, i0, lane, sampled());
+      else qt.load(q_rsrc, i0, lane);
+    }
     const int row = min(i0 * kTile + lq, N - 1);
     lse_reg = lse[bh * N + row];
     delta_reg = delta[bh * N + row];
   };
   auto load_do = [&](int it) { dt.load(head_rsrc(dout + head_of(it) * N * D, (unsigned)N * D * 4), tile_of(it), lane); };
-  int it = w;
-  if (it < n_it) {
+  // G = 1: the waves deal the tiles out one by one; G > 1: runs of them, so that a wave stays in a Q block
+  constexpr int STEP = G > 1 ? 1 : W;
+  int it = G > 1 ? n_it * w / W : w;
+  const int it_end = G > 1 ? n_it * (w + 1) / W : n_it;
+  int slot = 0;
+  if (it < it_end) {
     if (perm) load_map(it);
-    load_q(it);
+    if constexpr (G > 1) store_map(0);
+    load_q(it, 0);
     load_do(it);
-    if (perm && it + W < n_it) load_map(it + W);
+    if (perm && it + STEP < it_end) load_map(it + STEP);
   }
 
   float kop[K_LDS ? 1 : D / 2], vop[SHARED ? 1 : D / 2];
@@ -285,26 +311,87 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
     zero(dkacc[mb]);
     zero(dvacc[mb]);
   }
+  // G > 1: K_f of the workgroup's keys and dK_f of the Q block the wave is in
+  float kf[G > 1 ? HS : 1];
+  f32x16 dkf[G > 1 ? NG : 1];
+  auto fuse_keys = [&]() {
+    if constexpr (G > 1) {
+#pragma unroll
+      for (int c = 0; c < D / 2; c += 8) {
+        const u32x2 e2 = *(const u32x2*)&map_lds[w][2 * slot][hh * (D / 2) + c];
+#pragma unroll
+        for (int e = 0; e < 8; e += G) {
+          float x = k_lds[lq * RS + ((e2[e >> 2] >> (8 * (e & 3))) & (D - 1))];
+#pragma unroll
+          for (int m = 1; m < G; ++m) x += k_lds[lq * RS + ((e2[(e + m) >> 2] >> (8 * ((e + m) & 3))) & (D - 1))];
+          kf[(c + e) / G] = x;
+        }
+      }
+#pragma unroll
+      for (int mb = 0; mb < NG; ++mb) zero(dkf[mb]);
+    }
+  };
+  // every channel receives its group's column (register i, lane half hh: groups NG * acc_row(i) .., channels NB * acc_row(i) ..)
+  auto unfuse = [&](int of) {
+    if constexpr (G > 1) {
+      float* mine = &q_lds[w][lq * RQ];
+      wave_order();
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int mb = 0; mb < NG; ++mb)
+          if (KRED >= 32 || acc_row(i, 0) < KRED) mine[acc_row(i, hh) * NG + mb] = dkf[mb][i];
+      wave_order();
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4)
+#pragma unroll
+        for (int c = 0; c < 4 * NB; c += 4) {
+          const uint32_t g4 = *(const uint32_t*)&map_lds[w][2 * of + 1][NB * (8 * i4 + 4 * hh) + c];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dkacc[(c + e) % NB][4 * i4 + (c + e) / NB] += mine[(g4 >> (8 * e)) & (KRED - 1)];
+        }
+    }
+  };
+  int block = it < it_end && G > 1 ? block_of(it) : 0;
+  if constexpr (G > 1) {
+    if (it < it_end) fuse_keys();
+  }
 
-  for (; it < n_it; it += W) {
+  for (; it < it_end; it += STEP) {
     const int i0 = tile_of(it) * kTile;
+    if constexpr (G > 1) {
+      if (block_of(it) != block) {
+        unfuse(slot);
+        slot ^= 1;
+        block = block_of(it);
+        fuse_keys();
+      }
+    }
     wave_order();   // the reads of the previous tile come first
-    qt.store(q_lds[w], lane);
+    if constexpr (G > 1) {
+#pragma unroll
+      for (int u = 0; u < QL; ++u) q_lds[w][(u * ROWS + lane / KRED) * RQ + lane % KRED] = qr[u];
+    } else {
+      qt.store(q_lds[w], lane);
+    }
     dt.store(do_lds[w], lane);
     stat_lds[w][hh][lq] = hh ? delta_reg : lse_reg;
-    if constexpr (G > 1) {   // this tile's sorted order, before the next tile's takes its place
-      if (lane < D / 4) ((uint32_t*)map_lds[w][2])[lane] = ((const uint32_t*)map_lds[w][0])[lane];
-    }
-    if (it + W < n_it) {
-      load_q(it + W);
-      if (perm && it + 2 * W < n_it) load_map(it + 2 * W);
+    if (it + STEP < it_end) {
+      if constexpr (G > 1) {
+        const bool same = block_of(it + 1) == block;
+        if (!same) store_map(slot ^ 1);
+        load_q(it + 1, same ? slot : slot ^ 1);
+      } else {
+        load_q(it + STEP, 0);
+      }
+      if (perm && it + 2 * STEP < it_end) load_map(it + 2 * STEP);
     }
     wave_order();
     f32x16 s, dp;
-    if constexpr (G > 1) s = group_product<D, G>(&q_lds[w][lq * RS], &k_lds[lq * RS], hh, map_lds[w][2]);
+    if constexpr (G > 1) s = group_product<HS>(&q_lds[w][lq * RQ], hh, kf);
     else if constexpr (K_LDS) s = row_product<D>(&q_lds[w][lq * RS], hh, &k_lds[lq * RS]);
     else s = row_product<D>(&q_lds[w][lq * RS], hh, kop);
-    if (it + W < n_it) load_do(it + W);   // (only now: the registers were those of the sum)
+    if (it + STEP < it_end) load_do(it + STEP);   // (only now: the registers were those of the sum)
     if constexpr (SHARED) dp = row_product<D, DpSum<D>>(&do_lds[w][lq * RS], hh, &v_lds[lq * RS]);
     else dp = row_product<D, DpSum<D>>(&do_lds[w][lq * RS], hh, vop);
 #pragma unroll
@@ -326,14 +413,56 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) dp[i] *= s[i];
-    column_product<D>(do_lds[w], lq, hh, s, dvacc);
+    // (G > 1: a wave's run of tiles makes the chains of the causal mask's heavy rows long, so that a tile's dV is summed by
+    // itself first, like dK; at d = 128 in groups of two, two channel blocks at a time: with four, 36 registers spilled)
+    if constexpr (G > 1 && (NB == 2 || G == 4)) {
+      f32x16 part[NB];
+#pragma unroll
+      for (int mb = 0; mb < NB; ++mb) zero(part[mb]);
+      column_product<D>(do_lds[w], lq, hh, s, part);
+#pragma unroll
+      for (int mb = 0; mb < NB; ++mb) dvacc[mb] += part[mb];
+    } else if constexpr (G > 1) {
+#pragma unroll
+      for (int m0 = 0; m0 < NB; m0 += 2) {
+        f32x16 part[2];
+        zero(part[0]);
+        zero(part[1]);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const f32x2 x = *(const f32x2*)&do_lds[w][acc_row(i, hh) * RS + lq * NB + m0];
+          part[0] = mfma(x[0], s[i], part[0]);
+          part[1] = mfma(x[1], s[i], part[1]);
+        }
+        dvacc[m0] += part[0];
+        dvacc[m0 + 1] += part[1];
+      }
+    } else {
+      column_product<D>(do_lds[w], lq, hh, s, dvacc);
+    }
     // (a tile's dK is summed by itself first: many heads and rows would make the chain long)
-    f32x16 part[NB];
+    if constexpr (G > 1) {
+      // lane m owns the groups NG*m .. (with 16 groups the upper lanes repeat the lower)
+      f32x16 part[NG];
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) zero(part[mb]);
-    column_product<D>(q_lds[w], lq, hh, dp, part);
+      for (int mb = 0; mb < NG; ++mb) zero(part[mb]);
 #pragma unroll
-    for (int mb = 0; mb < NB; ++mb) dkacc[mb] += part[mb];
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int mb = 0; mb < NG; ++mb) part[mb] = mfma(q_lds[w][acc_row(i, hh) * RQ + lq * NG % KRED + mb], dp[i], part[mb]);
+#pragma unroll
+      for (int mb = 0; mb < NG; ++mb) dkf[mb] += part[mb];
+    } else {
+      f32x16 part[NB];
+#pragma unroll
+      for (int mb = 0; mb < NB; ++mb) zero(part[mb]);
+      column_product<D>(q_lds[w], lq, hh, dp, part);
+#pragma unroll
+      for (int mb = 0; mb < NB; ++mb) dkacc[mb] += part[mb];
+    }
+  }
+  if constexpr (G > 1) {
+    if (n_it * w / W < it_end) unfuse(slot);
   }
 
   wave_order();
