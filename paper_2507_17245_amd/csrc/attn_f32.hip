@@ -11,7 +11,7 @@
 //                            a score accumulator holds the keys 8*(i/4) + i%4 (+ 4 in the upper
 //                            half of the wave), which is the contraction index of step i.
 //
-// Split: a workgroup owns 32 query rows and its NW waves deal the 32-key tiles out among
+// Split: a workgroup owns 32 query rows and its NW (4 or 8) waves deal the 32-key tiles out among
 // themselves, each with a softmax state of its own; the states meet in LDS once at the end. No wave
 // waits for another before that, and a problem of few rows still fills the chip: sharing tiles
 // among waves of different rows instead would leave N = 256 with 8 working waves.
@@ -346,21 +346,37 @@ hipError_t launch_one(const void* q, const void* k, const void* v, void* o, cons
   return hipGetLastError();
 }
 
+// Eight waves per workgroup where the row tiles leave compute units idle and there are tiles for all of them (dealt out by K blocks
+// in the mirrored form): two waves per SIMD, as two workgroups would be; with more row tiles than compute units two workgroups of
+// four have fewer states to merge. At d = 128 a wave's registers fill its SIMD. us, 4 | 8 waves, exact, groups of two, mirrored:
+//   H1 N2048 40.9 | 38.2, 44.3 | 38.1, 51.6 | 41.6; H8 N1024 causal 24.0 | 23.1, 27.5 | 25.3, 29.5 | 25.4
+//   H4 N521 16.4 | 15.7, 20.6 | 19.2, 21.3 | 19.1; 8 key tiles (H1 N256) 8.9 | 9.2, 12.6 | 12.7; H8 N1500 57.5 | 60.0
+template <typename E, int D, int G, int MODE>
+hipError_t launch_waves(const void* q, const void* k, const void* v, void* o, const uint8_t* perm, const Problem& pb, int n_groups,
+                        hipStream_t stream) {
+  if constexpr (D == 64) {
+    const int tiles = (pb.Nk + kTile - 1) / kTile, TB = MODE == kKeyFull || MODE == kKeyFused ? pb.Bc / kTile : 1;
+    if ((long long)pb.B * pb.H * ((pb.N + kTile - 1) / kTile) <= kComputeUnits && tiles > 8 && (tiles + TB - 1) / TB > 4)
+      return launch_one<E, D, G, MODE, 8>(q, k, v, o, perm, pb, n_groups, stream);
+  }
+  return launch_one<E, D, G, MODE, 4>(q, k, v, o, perm, pb, n_groups, stream);
+}
+
 template <typename E, int D>
 hipError_t launch_typed(const void* q, const void* k, const void* v, void* o, const uint8_t* perm, const Problem& pb,
                         int distr, hipStream_t stream) {
   if ((long long)pb.B * pb.H * ((pb.N + kTile - 1) / kTile) > 0x7fffffffLL) return hipErrorInvalidValue;
   const int G = distr ? D / pb.n_groups : 1;
   if (distr && pb.side == 1) {
-    if (G == 2) return launch_one<E, D, 2, kKeyFused, 4>(q, k, v, o, perm, pb, pb.n_groups, stream);
-    if (G == 4) return launch_one<E, D, 4, kKeyFused, 4>(q, k, v, o, perm, pb, pb.n_groups, stream);
-    return launch_one<E, D, 1, kKeyFull, 4>(q, k, v, o, perm, pb, pb.n_groups, stream);
+    if (G == 2) return launch_waves<E, D, 2, kKeyFused>(q, k, v, o, perm, pb, pb.n_groups, stream);
+    if (G == 4) return launch_waves<E, D, 4, kKeyFused>(q, k, v, o, perm, pb, pb.n_groups, stream);
+    return launch_waves<E, D, 1, kKeyFull>(q, k, v, o, perm, pb, pb.n_groups, stream);
   }
   if constexpr (std::is_same<E, float>::value) {
-    if (!distr) return launch_one<E, D, 1, kQueryFull, 4>(q, k, v, o, nullptr, pb, D, stream);
-    if (G == 2) return launch_one<E, D, 2, kQueryFused, 4>(q, k, v, o, perm, pb, pb.n_groups, stream);
-    if (G == 4) return launch_one<E, D, 4, kQueryFused, 4>(q, k, v, o, perm, pb, pb.n_groups, stream);
-    return launch_one<E, D, 1, kQueryFull, 4>(q, k, v, o, perm, pb, pb.n_groups, stream);
+    if (!distr) return launch_waves<E, D, 1, kQueryFull>(q, k, v, o, nullptr, pb, D, stream);
+    if (G == 2) return launch_waves<E, D, 2, kQueryFused>(q, k, v, o, perm, pb, pb.n_groups, stream);
+    if (G == 4) return launch_waves<E, D, 4, kQueryFused>(q, k, v, o, perm, pb, pb.n_groups, stream);
+    return launch_waves<E, D, 1, kQueryFull>(q, k, v, o, perm, pb, pb.n_groups, stream);
   }
   return hipErrorInvalidValue;   // bf16 tensors take this path for the mirrored form only
 }

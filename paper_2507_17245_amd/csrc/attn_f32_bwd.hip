@@ -488,16 +488,16 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
 // ------------------------------------------------------------------------------------------------
 // G: channels per group where the score and dQ_r products contract over the groups (2, 4); 1: over the
 // channels, with Q~.
-template <int D, int G>
-__global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dq_kernel(
+template <int D, int G, int W>
+__global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ o,
     const float* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ dq, const uint8_t* __restrict__ perm,
     int H, int Hkv, int N, int Nk, int Br, int Tq, int n_groups, int causal, float scale) {
   constexpr int NB = D / 32, RS = Tile<D>::RS;
   constexpr int KRED = D / G, HS = KRED / 2;
   constexpr int NG = G == 1 ? NB : (KRED + 31) / 32;   // 32-row blocks of the dQ_r accumulator
-  __shared__ __attribute__((aligned(16))) float k_lds[kWaves][kTile * RS];   // at the end the wave's dQ_r
-  __shared__ __attribute__((aligned(16))) float v_lds[kWaves][kTile * RS];
+  __shared__ __attribute__((aligned(16))) float k_lds[W][kTile * RS];   // at the end the wave's dQ_r
+  __shared__ __attribute__((aligned(16))) float v_lds[W][kTile * RS];
   __shared__ uint8_t order_lds[D];   // sorted order of the block's channels
   __shared__ uint8_t map_lds[D];     // G > 1: a channel's position in it; G = 1: its group's sampled channel
   __shared__ uint8_t pos_lds[D];     // (G = 1) a channel's position in the sorted order
@@ -538,13 +538,13 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dq_kernel(
   if (perm) {
     // D is a power of two: an out-of-range entry of a caller's table cannot index past a row
     const uint8_t* pr = perm + ((size_t)bh * Tq + r0 / Br) * D;
-    for (int i = tid; i < D; i += kThreads) {
+    for (int i = tid; i < D; i += (W * 64)) {
       order_lds[i] = pr[i] & (D - 1);
       pos_lds[pr[i] & (D - 1)] = (uint8_t)i;
       map_lds[pr[i] & (D - 1)] = G > 1 ? (uint8_t)i : (uint8_t)(pr[i / group * group] & (D - 1));
     }
   } else {
-    for (int i = tid; i < D; i += kThreads) order_lds[i] = map_lds[i] = (uint8_t)i;
+    for (int i = tid; i < D; i += (W * 64)) order_lds[i] = map_lds[i] = (uint8_t)i;
   }
   __syncthreads();
   float qop[HS], doop[D / 2], dl = 0.0f;
@@ -566,14 +566,14 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dq_kernel(
   f32x16 dqacc[NG];
 #pragma unroll
   for (int mb = 0; mb < NG; ++mb) zero(dqacc[mb]);
-  for (int tile = w; tile < n_tiles; tile += kWaves) {
+  for (int tile = w; tile < n_tiles; tile += W) {
     wave_order();   // the reads of the previous tile come first
     if constexpr (G > 1) kt.scatter(k_lds[w], lane, kdst);
     else kt.store(k_lds[w], lane);
     vt.store(v_lds[w], lane);
-    if (tile + kWaves < n_tiles) {
-      kt.load(k_rsrc, tile + kWaves, lane);
-      vt.load(v_rsrc, tile + kWaves, lane);
+    if (tile + W < n_tiles) {
+      kt.load(k_rsrc, tile + W, lane);
+      vt.load(v_rsrc, tile + W, lane);
     }
     wave_order();
     f32x16 s;
@@ -636,15 +636,15 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 2 : 1)) void bwd_dq_kernel(
     for (int mb = 0; mb < NG; ++mb)
       if (KRED >= 32 || acc_row(i, hh) < KRED) mine[acc_row(i, hh) * NG + mb] = dqacc[mb][i];
   __syncthreads();
-  for (int i = tid; i < kTile * KRED / 4; i += kThreads) {
+  for (int i = tid; i < kTile * KRED / 4; i += (W * 64)) {
     const int row = i / (KRED / 4), c = i % (KRED / 4) * 4;
     f32x4 x = *(const f32x4*)&k_lds[0][row * RS + c];
 #pragma unroll
-    for (int j = 1; j < kWaves; ++j) x += *(const f32x4*)&k_lds[j][row * RS + c];
+    for (int j = 1; j < W; ++j) x += *(const f32x4*)&k_lds[j][row * RS + c];
     *(f32x4*)&v_lds[0][row * RS + c] = x;
   }
   __syncthreads();
-  for (int i = tid; i < kTile * D / 4; i += kThreads) {
+  for (int i = tid; i < kTile * D / 4; i += (W * 64)) {
     const int row = i / (D / 4), c = i % (D / 4) * 4;
     if (r0 + row >= N) continue;
     f32x4 y;
@@ -701,12 +701,24 @@ hipError_t launch_d(const float* q, const float* k, const float* v, const float*
     DA_DKV(4, 1);
   }
 #undef DA_DKV
-#define DA_DQ(GG)                                                                                                          \
-  hipLaunchKernelGGL((bwd_dq_kernel<D, GG>), dim3((unsigned)q_units), dim3(kThreads), 0, stream, q, k, v, o, dout, lse, dq, \
+  // dQ: eight waves as in the forward (launch_waves in attn_f32.hip)
+#define DA_DQ(GG, W)                                                                                                       \
+  hipLaunchKernelGGL((bwd_dq_kernel<D, GG, W>), dim3((unsigned)q_units), dim3(W * 64), 0, stream, q, k, v, o, dout, lse, dq, \
                      table, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, n_groups, pb.causal, pb.scale)
-  if (G == 2) DA_DQ(2);
-  else if (G == 4) DA_DQ(4);
-  else DA_DQ(1);
+  const bool wide = D == 64 && q_units <= kComputeUnits && (pb.Nk + kTile - 1) / kTile > 8;
+  if constexpr (D == 64) {
+    if (wide && G == 2) DA_DQ(2, 8);
+    else if (wide && G == 4) DA_DQ(4, 8);
+    else if (wide) DA_DQ(1, 8);
+  }
+  if (wide) {
+  } else if (G == 2) {
+    DA_DQ(2, 4);
+  } else if (G == 4) {
+    DA_DQ(4, 4);
+  } else {
+    DA_DQ(1, 4);
+  }
 #undef DA_DQ
   return hipGetLastError();
 }

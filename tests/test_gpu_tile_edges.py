@@ -354,3 +354,22 @@ def test_causal_order(B, H, Hkv, N, Br):
     for what, g, r in zip(("dq", "dk", "dv"), run_backward(cfg, q, k, v, dout, True), oracle.distr_bwd(q, k, v, dout, U.oracle_params(cfg))):
         err, unit = np.abs(g - r), max(1.0, np.abs(r).max())
         assert err.max() <= U.BF16_MAX_ABS * unit and err.mean() <= U.BF16_MEAN_ABS * unit, f"{what}: {err.max():.4g} {err.mean():.4g}"
+
+
+# Float kernels at d = 64 with eight waves (more than eight key tiles, at most 256 row tiles): around the number of tiles from which
+# they are taken, tiles that only some waves get, K blocks of the mirrored form dealt out to them.
+@pytest.mark.parametrize("B,H,Hkv,N,Nk,causal", [(1, 4, 2, 33, 256, False), (1, 4, 2, 33, 257, True), (1, 2, 1, 290, 545, True), (2, 2, 2, 70, 1000, False),
+                                                 (1, 64, 32, 128, 300, False), (1, 64, 32, 129, 300, True)])
+@pytest.mark.parametrize("side,Bc,G", [(0, 64, 1), (0, 64, 2), (0, 64, 4), (0, 64, 8), (1, 32, 2), (1, 128, 4), (1, 64, 8)])
+def test_float_eight_waves(B, H, Hkv, N, Nk, causal, side, Bc, G):
+    import gpu_util as U
+    from test_gpu_backward import TOL, run_backward
+    cfg = W.CONFIGS["tiny"].scaled(B=B, H=H, Hkv=Hkv, N=N, Nk=Nk, causal=causal, side=side, Bc=Bc, n_groups=64 // G, recipe="normal", n_planes=16)
+    _forward(cfg)
+    if side:
+        return
+    q, k, v = W.make(cfg)
+    dout = W.make_grad(cfg)
+    for what, g, r in zip(("dq", "dk", "dv"), run_backward(cfg, q, k, v, dout, True), oracle.distr_bwd(q, k, v, dout, U.oracle_params(cfg))):
+        err = np.abs(g - r).max()
+        assert err <= TOL * max(1.0, np.abs(r).max()), f"{what}: {err:.4g}"
