@@ -76,11 +76,15 @@ bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split) {
 // tiles taken off a workgroup's walk outweigh the combine kernel (4 us, about 12 tiles) and, grouped,
 // the LSH stage in a kernel of its own (another 18). Measured, 1 | 256 | 512 workgroups: exact H16 N200 Nk8192
 // d64 71 | 19 | 22 us; N1000 Nk8192 d128 109 | 72 | 80; N200 Nk32768 d128 486 | 90 | 87; N2048 d64 causal 22 | 22 | 29.
+// Blocks of 64 rows at d = 128 take one workgroup, of two halves (launch_one), for each where that comes out even: half the sums to
+// combine. exact, distr, two for each | one: H16 N64 Nk30000 50 | 46, 56 | 52; N200 Nk2100 19.9 | 17.3, 29.1 | 29.0; N700 Nk12000
+// Hkv4 (176 blocks) 105 | 119; 256 blocks, N1024 Nk2048 31 | 26, 39 | 30, but B2 H32 N200 Nk8000 90 | 96, 97 | 98.
 int attn_bf16_splits(const Problem& pb, int distr) {
   if (attn_bf16_short(pb, distr)) return 1;
   const long long units = (long long)pb.B * pb.H * ((pb.N + pb.Br - 1) / pb.Br);
   const int tiles = (pb.Nk + pb.Bc - 1) / pb.Bc;
   long long n = 1024 / (pb.Br / 32) / units;
+  if (pb.d == 128 && pb.Br == 64 && pb.Bc == 64 && kComputeUnits / units * units > 240 && (n > 2 || tiles <= 64)) n = kComputeUnits / units;
   if (n > tiles / 4) n = tiles / 4;
   if (n < 2 || tiles - tiles / n < (distr ? 30 : 12)) n = 1;
   if (attn_bf16_few_rows(pb, distr)) n = attn_bf16_few_splits(pb);

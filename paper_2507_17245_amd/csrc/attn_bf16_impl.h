@@ -4,7 +4,9 @@
 //
 // Work split. One workgroup owns one Q block of BR rows of one (batch, head); each of its
 // BR/32 wavefronts owns 32 query rows for the whole inner loop over K/V tiles of BC rows
-// (the paper's l and m: BR in {64, 128, 256}, BC in {32, 64, 128}).
+// (the paper's l and m: BR in {64, 128, 256}, BC in {32, 64, 128}). Launches that leave SIMDs
+// without a wave, or with one, take twice the wavefronts per workgroup (KS = 2): each half of them has
+// tile buffers of its own and walks half of the block's tiles, the two softmax states meet in LDS at the end.
 //
 // Matrix-core mapping (v_mfma_f32_32x32x16_bf16, fp32 accumulate). Both products are taken
 // transposed so that one lane owns one query row's softmax state:
@@ -96,19 +98,21 @@ enum ScoreMode { kExact, kFused, kReplicated };
 
 // KRED: contraction length of the score product (a multiple of the MFMA step, 16). NG: number of
 // channel groups; smaller than KRED only for n_groups 4 and 8, whose operands are zero-padded to 16
-// (kFused; the other modes are built once for every n_groups, NG = KRED = D).
-template <int D, int BR, int BC, int KRED, int MODE, int NG = KRED>
+// (kFused; the other modes are built once for every n_groups, NG = KRED = D). KS: shares of a block's tiles.
+template <int D, int BR, int BC, int KRED, int MODE, int NG = KRED, int KS = 1>
 struct Cfg {
   static constexpr bool FUSED = MODE == kFused;
   static constexpr bool GROUPED = MODE != kExact;
-  static constexpr int NW = BR / 32;              // wavefronts per workgroup
+  static constexpr int RW = BR / 32;              // wavefronts side by side over the block's rows
+  static constexpr int NW = RW * KS;              // wavefronts per workgroup
+  static constexpr int TH = RW * 64;              // threads that share a stream of tiles
   static constexpr int T = NW * 64;               // threads
   static constexpr int G = D / NG;                // channels per group
   static constexpr int CH = D / 8;                // 16-byte chunks per row
   static constexpr int MB = BC / 32;              // 32-key blocks of the score product per tile
   static constexpr int TT = BC / 16;              // 16-key steps of P.V per tile
   static constexpr int NBLK = BC * CH / 64;       // 1 KB blocks (one wave-level direct load each) per tile
-  static constexpr int CPT = (NBLK + NW - 1) / NW;  // direct loads each wave issues per tile
+  static constexpr int CPT = (NBLK + RW - 1) / RW;  // direct loads each wave issues per tile
   // LDS layouts.
   //  * V tiles, and K tiles of the exact path, arrive by direct global->LDS loads (each
   //    wave-level load drops 64 x 16 bytes contiguously), so rows are unpadded (D*2 bytes) and
@@ -131,7 +135,7 @@ struct Cfg {
   static constexpr int KTROWB = BC * 2;           // bytes of a K^T / K_f^T row (BC keys)
   static constexpr int PPR = BC / 8;              // 16-byte pieces (8 keys) per K^T / K_f^T row
   static constexpr int KX_BYTES = FUSED ? KRED * KTROWB : TILEB;   // one Kx buffer: K_f^T or K
-  static constexpr int FUSE_OUT = (NG * PPR + T - 1) / T;   // 16-byte fused outputs per thread and tile
+  static constexpr int FUSE_OUT = (NG * PPR + TH - 1) / TH;   // 16-byte fused outputs per thread and tile
   static constexpr int KSTEPS = KRED / 16;        // MFMA steps of the score product
   // Register budget: two waves per SIMD, except the widest tile at d = 128, whose two score sets
   // (128 registers) leave room for one.
@@ -146,26 +150,25 @@ struct Cfg {
 // overflowed or NaN sum fails the comparison too), and the sum is needed anyway.
 constexpr float kTau = 8.0f;
 
-template <int D, int BR, int BC, int KRED, int MODE, int NG>
-__global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_SIMD)) void attn_bf16_kernel(
+template <int D, int BR, int BC, int KRED, int MODE, int NG, int KS>
+__global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::WAVES_PER_SIMD)) void attn_bf16_kernel(
     const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
     bf16* __restrict__ o, const uint8_t* __restrict__ perm, const f16* __restrict__ kt, int Npad,
     int H, int Hkv, int N, int Nk, int Tq, int causal, float scale_log2e, int total_units, int n_planes,
     int gray_mode, uint64_t lsh_seed, float* __restrict__ lse, const char* __restrict__ rtab,
     uint8_t* __restrict__ perm_w, int n_groups, int n_split, float* __restrict__ part_o, f32x2* __restrict__ part_stat) {
-  using C = Cfg<D, BR, BC, KRED, MODE, NG>;
+  using C = Cfg<D, BR, BC, KRED, MODE, NG, KS>;
   constexpr bool FUSED = C::FUSED, GROUPED = C::GROUPED;
   constexpr float kSumTrigger = (BC / 2) * 256.0f;   // BC/2 keys per lane and tile, each at most 2^kTau
+  float trigger = kSumTrigger;                       // (KS = 2: below zero until the row has met a score above -infinity)
   using kx8 = typename std::conditional<FUSED, f16x8, bf16x8>::type;
   // Kx and V tiles are double-buffered: while tile i multiplies, tile i+1 (V) / i+2 (K) lands.
   // Each buffer is a separate LDS object: the compiler can then tell that the operand reads of
   // one buffer do not depend on the direct loads still in flight into the other.
-  __shared__ __attribute__((aligned(1024))) char kx_lds0[C::KX_BYTES];
-  __shared__ __attribute__((aligned(1024))) char kx_lds1[C::KX_BYTES];
-  __shared__ __attribute__((aligned(1024))) char v_lds0[C::TILEB];
-  __shared__ __attribute__((aligned(1024))) char v_lds1[C::TILEB];
-  auto kx_buf = [&](int par) -> char* { return par ? kx_lds1 : kx_lds0; };
-  auto v_buf = [&](int par) -> char* { return par ? v_lds1 : v_lds0; };
+  __shared__ __attribute__((aligned(1024))) char kx_lds0[KS * C::KX_BYTES];
+  __shared__ __attribute__((aligned(1024))) char kx_lds1[KS * C::KX_BYTES];
+  __shared__ __attribute__((aligned(1024))) char v_lds0[KS * C::TILEB];
+  __shared__ __attribute__((aligned(1024))) char v_lds1[KS * C::TILEB];
   // The block's permutation is only needed while the prologue builds the sampled-query operands
   // and the fusion offsets: it borrows the head of the second V buffer, which receives its
   // first tile in the first loop iteration (after the prologue's barriers).
@@ -174,8 +177,12 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rw = KS == 1 ? wave : wave % C::RW, half = KS == 1 ? 0 : wave / C::RW;   // which 32 rows, and which half of the block's tiles
+  const int tid_h = tid - half * C::TH;
   const int lq = lane & 31;   // query row of this lane inside the wave's 32 rows
   const int hh = lane >> 5;   // which half of each 8-wide contraction chunk this lane feeds
+  auto kx_buf = [&](int par) -> char* { return (par ? kx_lds1 : kx_lds0) + half * C::KX_BYTES; };
+  auto v_buf = [&](int par) -> char* { return (par ? v_lds1 : v_lds0) + half * C::TILEB; };
 
   // Workgroup -> (batch*head, Q block). Consecutive workgroup ids go round-robin over the 8 XCDs.
   // n_split > 1: the unit's key tiles are dealt out to that many workgroups (below).
@@ -230,8 +237,24 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
     shift -= t0 * BC;
     n_tiles = t1 - t0;
   }
+  // KS = 2: the first half of the tiles goes to one half of the waves, the second to the other; the two meet in LDS
+  // at the end. A share without tiles walks one past the last key: zeros (range check), masked out.
+  int tile0 = 0, n_most = n_tiles;
+  if constexpr (KS == 2) {
+    n_most = (n_tiles + 1) / 2;
+    if (half) {
+      tile0 = n_tiles > 1 ? n_most : (Nk + BC - 1) / BC;
+      n_tiles = max(n_tiles - n_most, 1);
+      kh += (size_t)tile0 * BC * D;
+      vh += (size_t)tile0 * BC * D;
+      Nk = max(Nk - tile0 * BC, 0);
+      shift -= tile0 * BC;
+    } else {
+      n_tiles = n_most;
+    }
+  }
 
-  const int qw0 = r0 + wave * 32;              // first query row of this wave
+  const int qw0 = r0 + rw * 32;              // first query row of this wave
   const int q_abs = qw0 + lq;                  // this lane's query row
   const int q_ld = min(q_abs, N - 1);          // ragged block: load a valid row, never store it
 
@@ -274,7 +297,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
         __builtin_amdgcn_make_buffer_rsrc((void*)(rtab + 1024), 0, 2 * PB * 1024, 0x00020000);
 #pragma unroll
     for (int j = 0; j < decltype(n_c)::value; ++j) {
-      const int blk = j * (BR / 32) + wave;
+      const int blk = j * C::NW + wave;
       if (blk < 2 * PB) {
         char* dst = blk < PB ? d1 + blk * 1024 : d2 + (blk - PB) * 1024;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(r_rsrc, (lds_void_r*)dst, 16, lane * 16, blk * 1024, 0, 0);
@@ -462,9 +485,9 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
       // have borrowed them), the fusion never writes them; visible to every wave after the
       // barrier that ends the prologue.
       const f16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-      for (int i = NG * C::KTROWB / 16 + tid; i < C::KX_BYTES / 16; i += C::T) {
-        ((f16x8*)kx_lds0)[i] = zero;
-        ((f16x8*)kx_lds1)[i] = zero;
+      for (int i = NG * C::KTROWB / 16 + tid_h; i < C::KX_BYTES / 16; i += C::TH) {
+        ((f16x8*)kx_buf(0))[i] = zero;
+        ((f16x8*)kx_buf(1))[i] = zero;
       }
     }
   }
@@ -490,12 +513,12 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
 #pragma unroll
       for (int s = 0; s < C::KSTEPS; ++s)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) qop[s][j] = q_staged(wave * 32 + lq, from_lds[16 * s + 8 * hh + j] & (D - 1));
+        for (int j = 0; j < 8; ++j) qop[s][j] = q_staged(rw * 32 + lq, from_lds[16 * s + 8 * hh + j] & (D - 1));
     } else {
       // The wave's rows pass through its part of the K buffers, RPR at a time (16-byte chunks exchanged by the row; its
       // LDS accesses take effect in its order): gathered from global memory, two bytes per load and lane, they cost a
       // launch of few blocks several microseconds (H8 N852 causal Br256 45 -> 35 us, H16 N1024 Br128 32 -> 27). The map holds byte offsets; chunk ^ x is offset ^ 16 x.
-      constexpr int PART = C::KX_BYTES / (C::NW / 2), RPR = PART / C::ROWB < 32 ? PART / C::ROWB : 32;
+      constexpr int PART = KS * C::KX_BYTES / (C::NW / 2), RPR = PART / C::ROWB < 32 ? PART / C::ROWB : 32;
       static_assert(RPR >= 4 && 32 % RPR == 0 && D == 128, "whole loads per round");
       u32x4 x[8];                          // load j: rows 4*j .. 4*j + 3
 #pragma unroll
@@ -538,7 +561,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
 #pragma unroll
       for (int j = 0; j < 8; ++j)
         if (NG == KRED || 16 * s + 8 * hh + j < NG)
-          qop[s][j] = to_half_sat((QSTAGE ? (float)q_staged(wave * 32 + lq, perm_lds[(16 * s + 8 * hh + j) * C::G])
+          qop[s][j] = to_half_sat((QSTAGE ? (float)q_staged(rw * 32 + lq, perm_lds[(16 * s + 8 * hh + j) * C::G])
                                           : (float)qrow[perm_lds[(16 * s + 8 * hh + j) * C::G]]) * scale_log2e);
         else
           qop[s][j] = (f16)0.0f;   // padding of the contraction: no group there
@@ -556,7 +579,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
 
   // ---- fusion bookkeeping, fixed for the Q block ------------------------------------------------
   // Fused output u of this thread is the 16-byte piece (8 keys) number idx % 8 of group
-  // idx / PPR, idx = tid + u*T: it sums the same piece of the group's G channel rows of K^T
+  // idx / PPR, idx = tid_h + u*TH: it sums the same piece of the group's G channel rows of K^T
   // (f_src: byte offset of the piece inside the head's K^T, tile 0) and lands in row idx / 8 of
   // K_f^T at the swizzled position (f_dst).
   int f_src[FUSED ? C::FUSE_OUT : 1][FUSED ? C::G : 1];
@@ -564,11 +587,11 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
   if constexpr (FUSED) {
 #pragma unroll
     for (int u = 0; u < C::FUSE_OUT; ++u) {
-      const int idx = min(tid + u * C::T, NG * C::PPR - 1);
+      const int idx = min(tid_h + u * C::TH, NG * C::PPR - 1);
       const int j = idx / C::PPR, c8 = idx % C::PPR;
 #pragma unroll
       for (int g = 0; g < C::G; ++g)
-        f_src[u][g] = perm_lds[j * C::G + g] * Npad * 2 + c8 * 16;
+        f_src[u][g] = perm_lds[j * C::G + g] * Npad * 2 + tile0 * C::KTROWB + c8 * 16;
       f_dst[u] = j * C::KTROWB + ((((c8 >> 1) ^ kf_swizzle<BC>(j)) << 1) | (c8 & 1)) * 16;
     }
   }
@@ -585,13 +608,13 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
   const __amdgpu_buffer_rsrc_t v_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)vh, 0, head_bytes, 0x00020000);
 
   // Direct global->LDS tile loads. Wave-level load j of this wave fills the 1 KB block
-  // j*NW + wave of the tile; lane i owns the 16 bytes at offset 16*i of that block, i.e. LDS
+  // j*RW + rw of the tile; lane i owns the 16 bytes at offset 16*i of that block, i.e. LDS
   // row (slot / CH), chunk position (slot % CH) with slot = 64*block + i, and fetches the global
   // chunk the swizzle assigns to that position.
   int dma_k[FUSED ? 1 : C::CPT], dma_v[C::CPT];
 #pragma unroll
   for (int j = 0; j < C::CPT; ++j) {
-    const int slot = (j * C::NW + wave) * 64 + lane;
+    const int slot = (j * C::RW + rw) * 64 + lane;
     const int row = slot / C::CH, pc = slot % C::CH;
     if constexpr (!FUSED) dma_k[j] = row * C::ROWB + (pc ^ (D == 128 ? (row & 15) : ((row >> 1) & 7))) * 16;
     const int lseg = (pc >> 1) ^ v_swizzle<C::ROWB>(row);
@@ -601,8 +624,8 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
   auto dma_blocks = [&](auto n_c, __amdgpu_buffer_rsrc_t rsrc, int soff, const int* voff, char* dst) {
 #pragma unroll
     for (int j = 0; j < decltype(n_c)::value; ++j)
-      if (C::NBLK % C::NW == 0 || j * C::NW + wave < C::NBLK)   // (more waves than 1 KB blocks: the rest sit out)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + (j * C::NW + wave) * 1024), 16,
+      if (C::NBLK % C::RW == 0 || j * C::RW + rw < C::NBLK)   // (more waves than 1 KB blocks: the rest sit out)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + (j * C::RW + rw) * 1024), 16,
                                                  voff[j], soff, 0, 0);
   };
   auto dma_tile = [&](__amdgpu_buffer_rsrc_t rsrc, int tile, const int* voff, char* dst) {
@@ -639,7 +662,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
         f16x8 acc = pc[u][0];
 #pragma unroll
         for (int g = 1; g < C::G; ++g) acc += pc[u][g];
-        if (NG * C::PPR % C::T == 0 || tid + u * C::T < NG * C::PPR) *(f16x8*)(dst + f_dst[u]) = acc;
+        if (NG * C::PPR % C::TH == 0 || tid_h + u * C::TH < NG * C::PPR) *(f16x8*)(dst + f_dst[u]) = acc;
       }
     }
   };
@@ -777,7 +800,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
         }
     }
     if constexpr (decltype(rescale_c)::value) {
-      const float alpha = __builtin_amdgcn_exp2f(-delta);
+      const float alpha = __builtin_amdgcn_exp2f(KS == 1 ? -delta : fminf(-delta, 0.0f));   // (a first reference has no sums)
       l_run *= alpha;
 #pragma unroll
       for (int mb = 0; mb < D / 32; ++mb)
@@ -808,11 +831,13 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
     if constexpr (HAS_NEXT) qk(par ^ 1, sn);
     bf16x8 pop[C::TT];
     float rs = exp_tile(sc, pop);
-    if (__builtin_amdgcn_ballot_w64(!(rs <= kSumTrigger)) != 0) {
+    if (__builtin_amdgcn_ballot_w64(!(rs <= (KS == 1 ? kSumTrigger : trigger))) != 0) {
       // Some row of this wave met a score more than kTau above its reference: such rows take the
       // tile's maximum as their new reference and the tile's P is computed again.
       const float mt = tile_max(sc);
-      shift_reference(mt > kTau ? mt : 0.0f, std::true_type(), sc, next_c, sn);
+      const bool first = KS > 1 && trigger < 0.0f && mt > -INFINITY;
+      if (first) trigger = kSumTrigger;
+      shift_reference(mt > kTau || first ? mt : 0.0f, std::true_type(), sc, next_c, sn);
       rs = exp_tile(sc, pop);
     }
     l_run += rs;
@@ -860,7 +885,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
   };
 
   // ---- prologue: tiles 0 (K, V) and 1 (K) into LDS, scores of tile 0 ---------------------------
-  dma_tile(v_rsrc, 0, dma_v, v_lds0);
+  dma_tile(v_rsrc, 0, dma_v, v_buf(0));
   if constexpr (FUSED) {
     Pieces first;        // tiles 0 and 1 travel together (registers are plentiful before the loop)
     load_pieces(0, first);
@@ -871,8 +896,8 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
     dma_wait();          // V(0) has landed (and, with it, the pieces of tile 2)
     __syncthreads();     // K_f^T(0), K_f^T(1) and V(0) are visible
   } else {
-    dma_tile(k_rsrc, 0, dma_k, kx_lds0);
-    if (n_tiles > 1) dma_tile(k_rsrc, 1, dma_k, kx_lds1);
+    dma_tile(k_rsrc, 0, dma_k, kx_buf(0));
+    if (n_tiles > 1) dma_tile(k_rsrc, 1, dma_k, kx_buf(1));
     dma_wait();
     __syncthreads();
   }
@@ -887,6 +912,7 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
   // (a row that sees no key of a workgroup's share, whose first tile is then masked, keeps reference 0)
   const float first_max = tile_max(s0);
   shift_reference(first_max > -INFINITY ? first_max : 0.0f, no, s0, no, s1);
+  if (KS > 1 && !(first_max > -INFINITY)) trigger = -1.0f;
   // The first iteration refills the buffer of tile 0 (direct load of K(2), or the fusion of
   // K_f^T(2)): every wave must have read its scores of tile 0 out of it first.
   __syncthreads();
@@ -906,39 +932,85 @@ __global__ __launch_bounds__(BR * 2, (Cfg<D, BR, BC, KRED, MODE, NG>::WAVES_PER_
   body(no, no, it, it & 1, s0, s1);
 
   // ---- epilogue: O = O_acc / l, bf16, 8-byte stores ---------------------------------------------
-  const float l_tot = half_swap_sum(l_run);
+  float l_tot = half_swap_sum(l_run);
+  constexpr int OB = D / 32 / KS;            // 32-channel blocks of the output that this wave finishes
+  const int c0 = KS == 2 ? half * (D / 2) : 0;
+  f32x16 out[OB];
+  if constexpr (KS == 2) {
+    // Each half hands the other one half of the channels and finishes the rest; a lane has the same row in both. The references
+    // are the rounded ones that the halves' P were taken against, so that a weight has the rounding of one subtraction.
+    if (n_tiles < n_most) __syncthreads();   // (the other half's last tile)
+    static_assert(C::RW * OB * 4096 <= KS * C::TILEB && KS * C::RW * 32 * 8 <= KS * C::KX_BYTES, "the exchange fits the tile buffers");
+    f32x2* stat = (f32x2*)kx_lds0;
+    f32x4* give = (f32x4*)(half ? v_lds1 : v_lds0) + rw * (OB * 256) + lane;
+    const f32x4* take = (const f32x4*)(half ? v_lds0 : v_lds1) + rw * (OB * 256) + lane;
+    if (hh == 0) stat[wave * 32 + lq] = f32x2{-nref, l_tot};
+#pragma unroll
+    for (int mb = 0; mb < OB; ++mb) {
+      f32x16 theirs;
+      if (half) {
+        theirs = oacc[mb];
+        out[mb] = oacc[mb + OB];
+      } else {
+        theirs = oacc[mb + OB];
+        out[mb] = oacc[mb];
+      }
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) give[(mb * 4 + i4) * 64] = f32x4{theirs[4 * i4], theirs[4 * i4 + 1], theirs[4 * i4 + 2], theirs[4 * i4 + 3]};
+    }
+    __syncthreads();
+    // (a half that saw nothing of a row has sum 0 and no reference; a NaN sum makes the row NaN)
+    const f32x2 st = stat[(wave ^ C::RW) * 32 + lq];
+    const float mine_ref = l_tot > 0.0f ? -nref : -INFINITY, other_ref = st[1] > 0.0f ? st[0] : -INFINITY;
+    const float ref = fmaxf(mine_ref, other_ref);
+    const float wm = mine_ref > -INFINITY ? __builtin_amdgcn_exp2f(mine_ref - ref) : 0.0f;
+    const float wo = other_ref > -INFINITY ? __builtin_amdgcn_exp2f(other_ref - ref) : 0.0f;
+    l_tot = __builtin_fmaf(wm, l_tot, wo * st[1]);
+    nref = ref > -INFINITY ? -ref : 0.0f;   // (an empty share of n_split)
+#pragma unroll
+    for (int mb = 0; mb < OB; ++mb)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        const f32x4 x = take[(mb * 4 + i4) * 64];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[mb][4 * i4 + j] = __builtin_fmaf(wm, out[mb][4 * i4 + j], wo * x[j]);
+      }
+  } else {
+#pragma unroll
+    for (int mb = 0; mb < OB; ++mb) out[mb] = oacc[mb];
+  }
   if (n_split > 1) {
     if (q_abs < N) {
-      if (hh == 0) part_stat[q_abs] = f32x2{-nref, l_tot};
-      float* prow = part_o + (size_t)q_abs * D;
+      if (hh == 0 && half == 0) part_stat[q_abs] = f32x2{-nref, l_tot};
+      float* prow = part_o + (size_t)q_abs * D + c0;
 #pragma unroll
-      for (int mb = 0; mb < D / 32; ++mb)
+      for (int mb = 0; mb < OB; ++mb)
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4)
           *(f32x4*)(prow + 32 * mb + 8 * i4 + 4 * hh) =
-              f32x4{oacc[mb][4 * i4], oacc[mb][4 * i4 + 1], oacc[mb][4 * i4 + 2], oacc[mb][4 * i4 + 3]};
+              f32x4{out[mb][4 * i4], out[mb][4 * i4 + 1], out[mb][4 * i4 + 2], out[mb][4 * i4 + 3]};
     }
     return;
   }
   const float inv = 1.0f / l_tot;
   // row statistics for a backward pass: ln(sum of exp(score)) = ln 2 * (reference + log2(l))
-  if (lse && q_abs < N && hh == 0) lse[(size_t)bh * N + q_abs] = 0.6931471805599453f * (__builtin_log2f(l_tot) - nref);
+  if (lse && q_abs < N && hh == 0 && half == 0) lse[(size_t)bh * N + q_abs] = 0.6931471805599453f * (__builtin_log2f(l_tot) - nref);
   if (q_abs < N) {
-    bf16* orow = o + ((size_t)bh * N + q_abs) * D;
+    bf16* orow = o + ((size_t)bh * N + q_abs) * D + c0;
 #pragma unroll
-    for (int mb = 0; mb < D / 32; ++mb)
+    for (int mb = 0; mb < OB; ++mb)
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
         bf16x4 pk;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) pk[j] = (bf16)(oacc[mb][4 * i4 + j] * inv);
+        for (int j = 0; j < 4; ++j) pk[j] = (bf16)(out[mb][4 * i4 + j] * inv);
         *(bf16x4*)(orow + 32 * mb + 8 * i4 + 4 * hh) = pk;
       }
   }
 }
 
-template <int D, int BR, int BC, int KRED, int MODE, int NG = KRED>
-hipError_t launch_one(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
+template <int D, int BR, int BC, int KRED, int MODE, int NG, int KS>
+hipError_t launch_ks(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                       const void* kt, const Problem& pb, hipStream_t stream) {
   const int Tq = (pb.N + BR - 1) / BR;
   const long long units = (long long)pb.B * pb.H * Tq;
@@ -954,13 +1026,36 @@ hipError_t launch_one(const void* q, const void* k, const void* v, void* o, cons
   //   d128  H32 N2048 47.9 | 44.4, 53.3 | 50.6; H16 N4096 82.3 | 75.9, 88.7 | 82.3; H16 N8192 264 | 253, 253 | 242
   const bool paired = BR <= 128 && (MODE != kFused || D == 128 || units <= 3 * kComputeUnits);
   const int causal_mode = pb.causal ? (units <= 8 * kComputeUnits ? (paired ? 3 : 2) : 1) : 0;
-  hipLaunchKernelGGL((attn_bf16_kernel<D, BR, BC, KRED, MODE, NG>), dim3((unsigned)(units * pb.n_split)), dim3(BR * 2), 0,
+  hipLaunchKernelGGL((attn_bf16_kernel<D, BR, BC, KRED, MODE, NG, KS>), dim3((unsigned)(units * pb.n_split)), dim3(BR * 2 * KS), 0,
                      stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, perm, (const f16*)kt,
                      (pb.Nk + kKtPad - 1) / kKtPad * kKtPad, pb.H, pb.Hkv, pb.N, pb.Nk, Tq, causal_mode,
                      scale_log2e, (int)units, pb.n_planes, pb.gray_mode, pb.seed, pb.lse,
                      kt ? (const char*)kt + kt_copy_bytes(pb.B, pb.Hkv, pb.d, pb.Nk) : nullptr,
                      MODE != kExact ? pb.perm_w : nullptr, pb.n_groups, pb.n_split, pb.part_o, (f32x2*)pb.part_stat);
   return hipGetLastError();
+}
+
+template <int D, int BR, int BC, int KRED, int MODE, int NG = KRED>
+hipError_t launch_one(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
+                      const void* kt, const Problem& pb, hipStream_t stream) {
+  // Two halves of the keys per workgroup (KS = 2) where workgroups of one half each would leave SIMDs with a wave or none:
+  // the longest block's walk is halved, and the prologue's grouping has twice the threads. Blocks of 64 rows: as many workgroups as
+  // are resident with twice the waves. Blocks of 128 rows, whose eight waves then fill a compute unit and meet at every
+  // tile's barrier: one for each, and walks long enough to pay for the exchange at the end. us, KS 1 | 2, exact and distr:
+  //   Br64  d64  B2 H32 Hkv8 N200 Nk8000 63 | 47, 68 | 52; H16 Hkv4 N700 Nk12000 86 | 57, 94 | 62; H32 N1000 Nk4000 52 | 39, 57 | 42;
+  //              H12 N400 8.2 | 7.6, 12.2 | 10.5; 672 workgroups (B8 H12 N400) 12.8 | 15.1, 17.2 | 20.6
+  //         d128 H12 N400 11.4 | 10.3, 18.4 | 15.0; H16 N1024 21.5 | 16.5, 27.8 | 21.2; 512 workgroups 59 | 69, 65 | 78
+  //   Br128 causal, d64 H8 N4096 40.1 | 35.0, 43.1 | 37.9; d128 59.8 | 54.4, 66.4 | 60.1; H16 N2048 33.5 | 31.9, 40.3 | 37.4;
+  //         16 tiles and fewer (N1024, N512) 0-9 % slower; 512 workgroups (H32 N2048) 29.6 | 29.5, 36.0 | 39.4; not causal d128
+  //         exact H16 N2048 38.4 | 39.2
+  if constexpr (BC == 64 && BR <= 128) {
+    constexpr bool GROUPED = MODE != kExact;
+    const long long wgs = (long long)pb.B * pb.H * ((pb.N + BR - 1) / BR) * pb.n_split;
+    const int tiles = (pb.Nk + BC - 1) / BC / pb.n_split;
+    if (BR == 64 ? wgs <= (D == 64 ? 2 : 1) * kComputeUnits && tiles >= 4 : wgs <= kComputeUnits && tiles >= 24 && (D == 64 || GROUPED || pb.causal))
+      return launch_ks<D, BR, BC, KRED, MODE, NG, 2>(q, k, v, o, perm, kt, pb, stream);
+  }
+  return launch_ks<D, BR, BC, KRED, MODE, NG, 1>(q, k, v, o, perm, kt, pb, stream);
 }
 
 // Group counts built for a K/V tile of BC rows: every supported one for the default tile of

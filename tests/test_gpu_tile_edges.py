@@ -373,3 +373,50 @@ def test_float_eight_waves(B, H, Hkv, N, Nk, causal, side, Bc, G):
     for what, g, r in zip(("dq", "dk", "dv"), run_backward(cfg, q, k, v, dout, True), oracle.distr_bwd(q, k, v, dout, U.oracle_params(cfg))):
         err = np.abs(g - r).max()
         assert err <= TOL * max(1.0, np.abs(r).max()), f"{what}: {err:.4g}"
+
+
+# Two halves of the keys per workgroup: blocks whose second half has no tile (causal, one tile) or one less than the first, ragged last
+# tiles, halves of a share of dealt-out keys (some of them empty), the fused product with odd group counts, the edges of the rule.
+@pytest.mark.parametrize("base,Br,B,H,Hkv,N,Nk,causal,G", [
+    ("llama", 64, 1, 4, 2, 200, 200, True, 2), ("llama", 64, 2, 3, 3, 257, 449, False, 4), ("long", 64, 1, 4, 4, 300, 330, True, 2),
+    ("long", 64, 1, 2, 1, 65, 197, False, 8), ("llama", 64, 1, 2, 2, 130, 3000, True, 2), ("long", 64, 1, 3, 3, 100, 2500, True, 4),
+    ("llama", 128, 1, 2, 1, 1537, 1537, True, 2), ("long", 128, 1, 2, 2, 1600, 1637, True, 2), ("llama", 128, 1, 1, 1, 140, 4700, True, 2),
+    ("long", 128, 1, 2, 1, 130, 6001, False, 4), ("llama", 64, 1, 64, 64, 512, 512, True, 2), ("llama", 64, 1, 65, 65, 512, 512, True, 2)])
+def test_halves(base, Br, B, H, Hkv, N, Nk, causal, G):
+    import gpu_util as U
+    import torch
+    d = W.CONFIGS[base].d
+    cfg = W.CONFIGS[base].scaled(B=B, H=H, Hkv=Hkv, N=N, Nk=Nk, Br=Br, n_groups=d // G, causal=causal, recipe="normal")
+    print(f"case {cfg}", flush=True)
+    q, k, v = W.make(cfg)
+    p = U.oracle_params(cfg)
+    lse = torch.empty((B, H, N), dtype=torch.float32, device="cuda")
+    o, perm, _ = U.run_gpu(cfg, q, k, v, want_perm_only=True, lse_out=lse)
+    assert np.array_equal(perm, oracle.lsh_group(q, p)[1])
+    U.assert_close(o, oracle.distr_fwd(q, k, v, p), "bf16")
+    assert np.abs(lse.cpu().numpy() - oracle.lse(q, k, p)).max() <= 2e-2
+    _forward(cfg, distr=False)
+
+
+# A half whose first tiles hold only scores of minus infinity for a row, and finite ones far below zero behind them: the row's
+# reference is its first finite score, whichever half that is in.
+@pytest.mark.parametrize("d,Br,H,N,Nk", [(64, 64, 2, 70, 640), (128, 64, 2, 70, 640), (64, 128, 66, 130, 1664)])
+def test_halves_with_masked_keys(d, Br, H, N, Nk):
+    import torch
+    import paper_2507_17245_amd as da
+    g = torch.Generator().manual_seed(5)
+    q = torch.randn(1, H, N, d, generator=g).abs() + 0.5
+    k = torch.randn(1, H, Nk, d, generator=g)
+    k = -k.abs() * 20.0 - 1.0                       # scores around -10^2 .. -10^3
+    half = (Nk // 64 + 1) // 2 * 64
+    k[:, 0::2, half:half + 130] = -float("inf")                 # even heads: the second half begins with masked keys
+    k[:, 1::2, :Nk - 70] = -float("inf")                        # odd heads: all but the last tiles are masked
+    v = torch.randn(1, H, Nk, d, generator=g)
+    q, k, v = (x.to(torch.bfloat16).cuda() for x in (q, k, v))
+    o = torch.full_like(q, float("nan"))
+    print(f"case d{d} Br{Br} N{N} Nk{Nk}", flush=True)
+    da.distr_attn_exact_fwd_ex(q, k, v, o, da.make_params(q, k, v, Br=Br, Bc=64, n_groups=d))
+    s = q.double().cpu() @ k.double().cpu().transpose(-1, -2) / d ** 0.5
+    want = torch.softmax(s, -1) @ v.double().cpu()
+    got = o.double().cpu()
+    assert torch.isfinite(got).all() and (got - want).abs().max() <= 2e-2
