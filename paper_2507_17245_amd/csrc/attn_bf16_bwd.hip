@@ -1033,10 +1033,22 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_short_kernel(
 // Workgroups of the dK/dV launch that share one kv head's keys but take different query heads: used
 // when the launch would otherwise not fill the chip twice over (grouped-query shapes with few kv
 // heads; under the causal mask its workgroups differ many-fold in length and need company).
+// Every share costs a float copy of dK and dV, written here and read by bwd_reduce_kernel. Where a smaller number of
+// shares fills the chip by itself (one workgroup per compute unit, two at d = 64; under the mask, d = 128, two rounds) and the
+// key tiles are whole, it is taken: the resident workgroups end together. A launch that is less full, or whose heads end in
+// a ragged tile (masked at every step, so its workgroup is the last), lives on many short ones, and so does the mask at d = 64.
+// Whole backward, us, all heads dealt out | the rule: d128 causal H32 Hkv8 N4096 545 | 519, N3712 465 | 444, B8 N512 215 | 168; not causal
+// N2048 267 | 256, N4096 937 | 893, H24 Hkv4 N4096 708 | 688, B16 H32 Hkv8 N128 81 | 65; d64 not causal N4096 480 | 474, B4 N1024 160 | 150,
+// B16 N256 85 | 74. Fewer shares elsewhere: d64 causal H32 Hkv8 N4096 284 | 297, ragged N3800 d128 859 | 975, 3/4 full (B2 H24 Hkv4
+// N2048 d64) 191 | 200.
 static int dkv_head_split(const Problem& pb) {
   const int rep = pb.H / pb.Hkv;
   const long long k_units = (long long)pb.B * pb.Hkv * ((pb.Nk + kBwdRows - 1) / kBwdRows);
-  return (rep > 1 && k_units < 512) ? rep : 1;
+  if (k_units >= 2 * kComputeUnits) return 1;
+  const long long full = (pb.causal || pb.d == 64 ? 2 : 1) * kComputeUnits;
+  for (int n = 1; n < rep && pb.Nk % kBwdRows == 0 && !(pb.causal && pb.d == 64); ++n)
+    if (rep % n == 0 && k_units * n > full * 7 / 8 && k_units * n <= full) return n;
+  return rep;
 }
 
 // Where the one-workgroup backward is taken: what its LDS holds (keys, and the tables of groups of up to 4

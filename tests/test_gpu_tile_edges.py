@@ -420,3 +420,22 @@ def test_halves_with_masked_keys(d, Br, H, N, Nk):
     want = torch.softmax(s, -1) @ v.double().cpu()
     got = o.double().cpu()
     assert torch.isfinite(got).all() and (got - want).abs().max() <= 2e-2
+
+
+# Grouped heads whose dK/dV workgroups take some of a kv head's query heads: all of them, a half, a third, a quarter, one each beside the
+# edge of the rule (7/8 of a full chip) and for a ragged tile of keys.
+@pytest.mark.parametrize("base,H,Hkv,N,Nk,causal", [("long", 480, 240, 64, 128, False), ("long", 480, 120, 64, 128, False), ("long", 480, 80, 64, 128, False),
+                                                    ("long", 448, 112, 64, 128, False), ("long", 480, 120, 64, 127, False), ("long", 480, 60, 70, 256, True),
+                                                    ("llama", 480, 120, 64, 256, False), ("llama", 480, 60, 70, 256, True)])
+@pytest.mark.parametrize("distr", [True, False])
+def test_head_shares(base, H, Hkv, N, Nk, causal, distr):
+    import gpu_util as U
+    from test_gpu_backward import run_backward
+    cfg = W.CONFIGS[base].scaled(B=1, H=H, Hkv=Hkv, N=N, Nk=Nk, causal=causal, Br=64, n_groups=W.CONFIGS[base].d // 2, recipe="normal")
+    print(f"case {cfg}", flush=True)
+    q, k, v = W.make(cfg)
+    dout = W.make_grad(cfg)
+    ref = (oracle.distr_bwd if distr else oracle.exact_bwd)(q, k, v, dout, U.oracle_params(cfg))
+    for what, g, r in zip(("dq", "dk", "dv"), run_backward(cfg, q, k, v, dout, distr), ref):
+        err, unit = np.abs(g - r), max(1.0, np.abs(r).max())
+        assert err.max() <= U.BF16_MAX_ABS * unit and err.mean() <= U.BF16_MEAN_ABS * unit, f"{what}: {err.max():.4g} {err.mean():.4g}"
