@@ -160,7 +160,11 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   using C = Cfg<D, BR, BC, KRED, MODE, NG, KS>;
   constexpr bool FUSED = C::FUSED, GROUPED = C::GROUPED;
   constexpr float kSumTrigger = (BC / 2) * 256.0f;   // BC/2 keys per lane and tile, each at most 2^kTau
-  float trigger = kSumTrigger;                       // (KS = 2: below zero until the row has met a score above -infinity)
+  // A row whose first tile holds only scores of -infinity (masked keys; those of a share or half that the causal mask hides)
+  // takes its first score above that as its reference: against 0, scores of -150 and less would be lost. The fused product has no such
+  // scores (its operands are clamped), and undivided keys begin with one that every row sees.
+  constexpr bool LATE_FIRST = KS > 1 || !FUSED;
+  float trigger = kSumTrigger;                       // (LATE_FIRST: below zero until the row has met such a score)
   using kx8 = typename std::conditional<FUSED, f16x8, bf16x8>::type;
   // Kx and V tiles are double-buffered: while tile i multiplies, tile i+1 (V) / i+2 (K) lands.
   // Each buffer is a separate LDS object: the compiler can then tell that the operand reads of
@@ -800,7 +804,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
         }
     }
     if constexpr (decltype(rescale_c)::value) {
-      const float alpha = __builtin_amdgcn_exp2f(KS == 1 ? -delta : fminf(-delta, 0.0f));   // (a first reference has no sums)
+      const float alpha = __builtin_amdgcn_exp2f(LATE_FIRST ? fminf(-delta, 0.0f) : -delta);   // (a first reference has no sums)
       l_run *= alpha;
 #pragma unroll
       for (int mb = 0; mb < D / 32; ++mb)
@@ -831,11 +835,11 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
     if constexpr (HAS_NEXT) qk(par ^ 1, sn);
     bf16x8 pop[C::TT];
     float rs = exp_tile(sc, pop);
-    if (__builtin_amdgcn_ballot_w64(!(rs <= (KS == 1 ? kSumTrigger : trigger))) != 0) {
-      // Some row of this wave met a score more than kTau above its reference: such rows take the
+    if (__builtin_amdgcn_ballot_w64(!(rs <= (LATE_FIRST ? trigger : kSumTrigger))) != 0) {
+      // Some row of this wave met a score more than kTau above its reference, or its first one above -infinity: such rows take the
       // tile's maximum as their new reference and the tile's P is computed again.
       const float mt = tile_max(sc);
-      const bool first = KS > 1 && trigger < 0.0f && mt > -INFINITY;
+      const bool first = LATE_FIRST && trigger < 0.0f && mt > -INFINITY;
       if (first) trigger = kSumTrigger;
       shift_reference(mt > kTau || first ? mt : 0.0f, std::true_type(), sc, next_c, sn);
       rs = exp_tile(sc, pop);
@@ -907,12 +911,11 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   f32x16 s0[C::MB], s1[C::MB];
   qk(0, s0);             // against the initial reference 0
   apply_mask(0, s0);
-  // The first tile sets the reference to its row maximum (key 0 is visible to every row, so the
-  // maximum is finite); nothing has been accumulated yet, so nothing is rescaled.
-  // (a row that sees no key of a workgroup's share, whose first tile is then masked, keeps reference 0)
+  // The first tile sets the reference to its row maximum; nothing has been accumulated yet, so nothing is rescaled. Where that is
+  // -infinity the reference stays 0 until a later tile has a score above it, for good if none has.
   const float first_max = tile_max(s0);
   shift_reference(first_max > -INFINITY ? first_max : 0.0f, no, s0, no, s1);
-  if (KS > 1 && !(first_max > -INFINITY)) trigger = -1.0f;
+  if (LATE_FIRST && !(first_max > -INFINITY)) trigger = -1.0f;
   // The first iteration refills the buffer of tile 0 (direct load of K(2), or the fusion of
   // K_f^T(2)): every wave must have read its scores of tile 0 out of it first.
   __syncthreads();

@@ -158,3 +158,34 @@ def test_float_gradients_at_large_scores(d, G):
         err = ((x.double().cpu() - want[name]).norm() / want[name].norm()).item()
         print(f"  {name}: {err:.2e}", flush=True)
         assert err <= bound[name], f"{name}: {err:.3g}"
+
+
+# Whole tiles of masked keys in front of scores far below zero, in workgroups that walk the keys in one piece: more blocks of 64 rows than
+# are taken in two halves, blocks of 128 rows with few tiles, of 256 rows, shares of dealt-out keys that begin with masked tiles,
+# K tiles of 32 and 128 rows. q's channels are all alike, so that the grouped form has the exact form's scores.
+@pytest.mark.parametrize("B,H,Hkv,N,Nk,d,Br,Bc,causal", [
+    (3, 64, 64, 200, 300, 64, 64, 64, True), (3, 32, 16, 200, 300, 128, 64, 64, False), (1, 4, 2, 300, 400, 64, 128, 64, True),
+    (1, 2, 2, 200, 700, 128, 128, 64, False), (1, 4, 4, 300, 500, 64, 256, 64, True), (1, 2, 1, 300, 500, 128, 256, 64, False),
+    (1, 2, 2, 300, 4096, 64, 256, 64, True), (1, 2, 1, 260, 2100, 128, 128, 64, True), (1, 2, 2, 300, 500, 64, 128, 32, False), (1, 2, 2, 300, 500, 128, 128, 128, True)])
+@pytest.mark.parametrize("distr", [False, True])
+def test_masked_tiles_before_low_scores(B, H, Hkv, N, Nk, d, Br, Bc, causal, distr):
+    import torch
+
+    import paper_2507_17245_amd as da
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    shape = ("bf16", B, H, Hkv, N, Nk, d, Br, causal)
+    q = (torch.randn((B, H, N, 1), generator=gen, device="cuda").abs() + 0.5).expand(B, H, N, d).contiguous().bfloat16()
+    k = (-20.0 * torch.randn((B, Hkv, Nk, d), generator=gen, device="cuda").abs() - 1.0).bfloat16()     # scores of -60 .. -600
+    v = torch.randn((B, Hkv, Nk, d), generator=gen, device="cuda").bfloat16()
+    k[:, 0::2, :200] = -math.inf                          # the first tile of every row, at any tile size
+    k[:, 1::2] = torch.where(torch.arange(Nk, device="cuda")[:, None] % 448 < 192, -math.inf, k[:, 1::2])   # and of some shares
+    o, lse = torch.full_like(q, math.nan), torch.full((B, H, N), math.nan, device="cuda")
+    print(f"case {shape} Bc {Bc} distr={distr}", flush=True)
+    p = da.make_params(q, k, v, Br=Br, Bc=Bc, n_groups=d // 2 if distr else d, causal=causal, lse_out=lse)
+    (da.distr_attn_fwd_ex if distr else da.distr_attn_exact_fwd_ex)(q, k, v, o, p)
+    want, want_lse = _plain(shape, q, k, v)
+    o, lse = o.double().cpu(), lse.double().cpu()
+    rows = torch.isfinite(want_lse)                       # (a causal row may see masked keys only: NaN in both)
+    assert rows.any() and torch.equal(torch.isnan(o[..., 0]), ~rows)
+    assert (o - want)[rows].abs().max() <= 2e-2
+    assert ((lse - want_lse)[rows].abs() / want_lse[rows].abs().clamp(min=1.0)).max() <= 2e-2
