@@ -372,6 +372,8 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
           }
         }
       } else {
+        // (H16 N120 Br128 took 15.3 us where the code in front had put this loop, 14.6 on a 64-byte instruction line)
+        asm volatile(".p2align 6");
         for (int i = tid; i < BR * 16; i += C::T)
           R_lds[i] = (i & 15) < n_planes ? hyperplane_entry(lsh_seed, (uint32_t)(i & 15), (uint32_t)(i >> 4)) : 0.0f;
       }
@@ -923,6 +925,9 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   // Tile it+1 needs no mask while it+1 < n_full. The main loop is unrolled by two so that the
   // two score register sets swap roles without copies.
   int it = 0;
+  // (at d = 128 blocks of 64 rows run one wave per SIMD, which waits for its instructions itself: by where the loop lies in the 64-byte lines
+  // H8 N4000 Nk5000 took 91 to 103 us)
+  if constexpr (D == 128 && BR == 64 && KS == 1) asm volatile(".p2align 6");
   for (; it + 2 < n_full; it += 2) {
     body(no, yes, it, 0, s0, s1);
     body(no, yes, it + 1, 1, s1, s0);
