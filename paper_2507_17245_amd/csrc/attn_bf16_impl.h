@@ -1049,18 +1049,29 @@ hipError_t launch_one(const void* q, const void* k, const void* v, void* o, cons
   // Two halves of the keys per workgroup (KS = 2) where workgroups of one half each would leave SIMDs with a wave or none:
   // the longest block's walk is halved, and the prologue's grouping has twice the threads. Blocks of 64 rows: as many workgroups as
   // are resident with twice the waves. Blocks of 128 rows, whose eight waves then fill a compute unit and meet at every
-  // tile's barrier: one for each, and walks long enough to pay for the exchange at the end. us, KS 1 | 2, exact and distr:
+  // tile's barrier: one for each, and walks long enough to pay for the exchange at the end. Where blocks find no tiles of each other in an
+  // L2 the walk waits for memory, in halves for the later of two loads (waves wait 41 % of their cycles, whole 27 %): long shares of
+  // 64-row blocks at d = 64 stay whole there, and at d = 128 middling ones of 128-row blocks. us, KS 1 | 2, exact and distr:
   //   Br64  d64  B2 H32 Hkv8 N200 Nk8000 63 | 47, 68 | 52; H16 Hkv4 N700 Nk12000 86 | 57, 94 | 62; H32 N1000 Nk4000 52 | 39, 57 | 42;
   //              H12 N400 8.2 | 7.6, 12.2 | 10.5; 672 workgroups (B8 H12 N400) 12.8 | 15.1, 17.2 | 20.6
+  //              nothing shared, causal: H11 N700 (4 shares) Nk16000 64.2 | 70.5, 69.9 | 75.8, but B3 H9 Hkv3 N300 Nk16000 (15 blocks on 8 XCDs)
+  //              81 | 59, 86 | 63, and H250 N50 Nk8000 (2 shares) 1.06 | 1; 4 tiles a share, H13 N64 Nk8000, 1.05 | 1
   //         d128 H12 N400 11.4 | 10.3, 18.4 | 15.0; H16 N1024 21.5 | 16.5, 27.8 | 21.2; 512 workgroups 59 | 69, 65 | 78
   //   Br128 causal, d64 H8 N4096 40.1 | 35.0, 43.1 | 37.9; d128 59.8 | 54.4, 66.4 | 60.1; H16 N2048 33.5 | 31.9, 40.3 | 37.4;
   //         16 tiles and fewer (N1024, N512) 0-9 % slower; 512 workgroups (H32 N2048) 29.6 | 29.5, 36.0 | 39.4; not causal d128
-  //         exact H16 N2048 38.4 | 39.2
+  //         exact H16 N2048 38.4 | 39.2; 24 tiles, one block a head: H16 N54 Nk1500 KS 2 7 % faster, H250 N60 4 % slower, from 62 on 5 % faster
+  //         d128, nothing shared, tiles per share: H11 N700 Nk5000 (26) 34.9 | 36.6, H32 Hkv8 N100 Nk16000 (31) 1 | 1.09, H25 N200 Nk16000 (50)
+  //         68.8 | 71.2, but H100 N100 Nk8000 (62) 99 | 92, Nk16000 (125) 176 | 160, H28 N180 Nk30000 (117) 149 | 135
   if constexpr (BC == 64 && BR <= 128) {
     constexpr bool GROUPED = MODE != kExact;
     const long long wgs = (long long)pb.B * pb.H * ((pb.N + BR - 1) / BR) * pb.n_split;
     const int tiles = (pb.Nk + BC - 1) / BC / pb.n_split;
-    if (BR == 64 ? wgs <= (D == 64 ? 2 : 1) * kComputeUnits && tiles >= 4 : wgs <= kComputeUnits && tiles >= 24 && (D == 64 || GROUPED || pb.causal))
+    const bool halves =
+        BR == 64 ? wgs <= (D == 64 ? 2 : 1) * kComputeUnits && tiles >= 4 &&
+                       (D == 128 || pb.n_split <= 2 || tiles < 12 || blocks_sharing_l2(pb) > (pb.causal ? 11 : 8))
+                 : wgs <= kComputeUnits && tiles >= (pb.N <= BR && pb.n_split == 1 && wgs > kComputeUnits / 2 ? 32 : 24) &&
+                       (D == 64 || ((GROUPED || pb.causal) && (pb.n_split == 1 || tiles > 64 || (pb.N > BR && blocks_sharing_l2(pb) >= 12))));
+    if (halves)
       return launch_ks<D, BR, BC, KRED, MODE, NG, 2>(q, k, v, o, perm, kt, pb, stream);
   }
   return launch_ks<D, BR, BC, KRED, MODE, NG, 1>(q, k, v, o, perm, kt, pb, stream);

@@ -3,6 +3,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <numeric>
+
 namespace da {
 
 typedef __bf16 bf16;
@@ -195,6 +198,15 @@ struct Problem {
   float* part_o = nullptr;
   float* part_stat = nullptr;
 };
+
+// Q blocks that read the same keys, per XCD and in eighths (12: one and a half), in a bf16 forward of up to 8 blocks per compute
+// unit: workgroup ids go round-robin over the 8 XCDs, causal blocks one after the other over all heads, others in a
+// range of heads per XCD where there are a multiple of 8 of them. Two or more find each other's tiles in the L2.
+inline int blocks_sharing_l2(const Problem& pb) {
+  const int Tq = (pb.N + pb.Br - 1) / pb.Br, heads = pb.B * pb.H, mine = pb.H / pb.Hkv * Tq;
+  if (!pb.causal) return (long long)heads * Tq % 8 == 0 ? 8 * mine : mine;
+  return std::max(mine, Tq * std::gcd(heads, 8));
+}
 
 // Launchers (defined next to their kernels). All return hipError_t of the launch.
 hipError_t launch_lsh_group(const void* q, int dtype, const Problem& pb, uint8_t* perm_out,

@@ -439,3 +439,11 @@ def test_head_shares(base, H, Hkv, N, Nk, causal, distr):
     for what, g, r in zip(("dq", "dk", "dv"), run_backward(cfg, q, k, v, dout, distr), ref):
         err, unit = np.abs(g - r), max(1.0, np.abs(r).max())
         assert err.max() <= U.BF16_MAX_ABS * unit and err.mean() <= U.BF16_MEAN_ABS * unit, f"{what}: {err.max():.4g} {err.mean():.4g}"
+
+
+# Dealt-out keys by the number of workgroups a block takes and whether each walks its keys whole or in halves, on both sides of the rules: shares
+# whose blocks find nothing of each other in an L2 (few heads on an XCD), short, middling and long ones.
+@pytest.mark.parametrize("base,Br,H,N,Nk", [("llama", 64, 150, 64, 2500), ("llama", 64, 130, 40, 2250), ("long", 128, 100, 33, 3200), ("long", 128, 100, 33, 8400)])
+@pytest.mark.parametrize("distr", [True, False])
+def test_shares_whole_and_in_halves(base, Br, H, N, Nk, distr):
+    _forward(W.CONFIGS[base].scaled(B=1, H=H, Hkv=H, N=N, Nk=Nk, Br=Br, causal=True, recipe="normal"), distr)
