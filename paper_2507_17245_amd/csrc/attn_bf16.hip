@@ -76,17 +76,25 @@ bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split) {
 // tiles taken off a workgroup's walk outweigh the combine kernel (4 us, about 12 tiles) and, grouped,
 // the LSH stage in a kernel of its own (another 18). Measured, 1 | 256 | 512 workgroups: exact H16 N200 Nk8192
 // d64 71 | 19 | 22 us; N1000 Nk8192 d128 109 | 72 | 80; N200 Nk32768 d128 486 | 90 | 87; N2048 d64 causal 22 | 22 | 29.
-// Blocks of 64 rows at d = 128 take one workgroup, of two halves (launch_one), for each where that comes out even: half the sums to
-// combine. exact, distr, two for each | one: H16 N64 Nk30000 50 | 46, 56 | 52; N200 Nk2100 19.9 | 17.3, 29.1 | 29.0; N700 Nk12000
-// Hkv4 (176 blocks) 105 | 119; 256 blocks, N1024 Nk2048 31 | 26, 39 | 30, but B2 H32 N200 Nk8000 90 | 96, 97 | 98.
+// Blocks of 64 rows at d = 128 take one workgroup, of two halves (launch_one), for each where that leaves at most 16 compute units
+// idle and does not undo the sharing out: half the sums to combine. The halves wait for the later of two loads at every tile (the same bytes
+// and L2 hits either way; H32 N120 Nk30000 exact 104 us in the kernel, 126 in halves): blocks that find each other's tiles in an L2 gain
+// on short walks only. exact, distr, two for each | one: nothing shared, H32 N64 Nk4096 21.9 | 20.6, 28.9 | 26.6, Nk30000 97 | 94, 105 | 101,
+// H11 N700 Nk16000 138 | 125, 146 | 132; shared, by tiles per workgroup, one / two: 16-32 (H32 N120 or N200, Nk4096) 0.85-1.00, 43-47 (H32 N120
+// Nk12000, N200 Nk6000) 0.94-1.02, 62-78 (N200 Nk8000, N120 Nk20000) 1.01-1.17, more up to 1.24, and with no shares to combine at all (256
+// blocks) 64 tiles 0.92-0.95, 94 0.98-1.02, 125 1.11. 80 units idle (H44 N200) Nk4096 1.09, Nk30000 1.33; distr H32 Hkv8 N200 Nk3000, where two
+// shares are not worth the LSH launch, 34.6 | 39.5.
 int attn_bf16_splits(const Problem& pb, int distr) {
   if (attn_bf16_short(pb, distr)) return 1;
   const long long units = (long long)pb.B * pb.H * ((pb.N + pb.Br - 1) / pb.Br);
   const int tiles = (pb.Nk + pb.Bc - 1) / pb.Bc;
-  long long n = 1024 / (pb.Br / 32) / units;
-  if (pb.d == 128 && pb.Br == 64 && pb.Bc == 64 && kComputeUnits / units * units > 240 && (n > 2 || tiles <= 64)) n = kComputeUnits / units;
-  if (n > tiles / 4) n = tiles / 4;
-  if (n < 2 || tiles - tiles / n < (distr ? 30 : 12)) n = 1;
+  const auto worth = [&](long long n) { return n > 1 && tiles - tiles / n >= (distr ? 30 : 12); };
+  long long n = std::min<long long>(1024 / (pb.Br / 32) / units, tiles / 4);
+  const long long one = kComputeUnits / units, few = std::min<long long>(one, tiles / 4);
+  if (pb.d == 128 && pb.Br == 64 && pb.Bc == 64 && one * units >= kComputeUnits - 16 && (blocks_sharing_l2(pb) < 12 || tiles <= std::max(64LL, 48 * one)) &&
+      (one == 1 || worth(few) || !worth(n)))
+    n = few;
+  if (!worth(n)) n = 1;
   if (attn_bf16_few_rows(pb, distr)) n = attn_bf16_few_splits(pb);
   const long long row_bytes = (long long)pb.B * pb.H * pb.N * (pb.d * 4 + 8);
   if (n * row_bytes > (24LL << 20)) n = (24LL << 20) / row_bytes;

@@ -447,3 +447,10 @@ def test_head_shares(base, H, Hkv, N, Nk, causal, distr):
 @pytest.mark.parametrize("distr", [True, False])
 def test_shares_whole_and_in_halves(base, Br, H, N, Nk, distr):
     _forward(W.CONFIGS[base].scaled(B=1, H=H, Hkv=H, N=N, Nk=Nk, Br=Br, causal=True, recipe="normal"), distr)
+
+
+# Blocks of 64 rows at d = 128: one workgroup or two for each compute unit, by the tiles of a share and by whether blocks share an L2.
+@pytest.mark.parametrize("H,Hkv,N,Nk", [(128, 128, 65, 4096), (128, 16, 65, 4160), (32, 8, 129, 2900), (32, 8, 129, 3900), (8, 8, 64, 2100), (250, 50, 33, 4200)])
+@pytest.mark.parametrize("distr", [True, False])
+def test_one_workgroup_or_two(H, Hkv, N, Nk, distr):
+    _forward(W.CONFIGS["long"].scaled(B=1, H=H, Hkv=Hkv, N=N, Nk=Nk, Br=64, causal=True, recipe="normal"), distr)
