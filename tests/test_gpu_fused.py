@@ -89,7 +89,20 @@ def test_fused_d128(N, Nk, causal, Br, Bc, G):
     _check(_cfg(128, H=32, Hkv=2, N=N, Nk=Nk, causal=causal, Br=Br, Bc=Bc, n_groups=128 // G), heads=(0, 15, 31))
 
 
-# groups of 16 (contraction zero-padded to one matrix step): fused from many rows per key on
+# Few enough workgroups for two halves of the keys in each (up to 256; 512 of 64 rows at d = 64; blocks of 128 rows from 24 tiles on): K_f of
+# either half from its own tiles of K^T, zero rows that pad 4 and 8 groups in both. Halves of a tile each, of an odd number, none at all (causal).
+@pytest.mark.parametrize("d,Br,G,H,Hkv,N,Nk,causal", [
+    (d, Br, G, *shape) for d, Br, shapes in ((64, 64, ((8, 2, 1000, 1000, True), (16, 16, 520, 700, False))),
+                                             (64, 128, ((16, 4, 1600, 1600, True), (16, 16, 300, 1563, False))),
+                                             (128, 64, ((8, 2, 1391, 1391, True), (16, 16, 300, 1473, False))),
+                                             (128, 128, ((16, 4, 1600, 1600, True), (16, 16, 700, 1540, False))))
+    for G in (2, 4, 8) for shape in shapes] + [
+    (64, 64, 16, 32, 1, 490, 9000, False), (64, 128, 16, 32, 1, 700, 6000, False), (128, 64, 16, 32, 1, 490, 4400, False), (128, 128, 16, 32, 1, 700, 3000, False)])
+def test_fused_in_halves(d, Br, G, H, Hkv, N, Nk, causal):
+    assert H * -(-N // Br) <= 256 and (Br == 64 or Nk > 23 * 64)
+    _check(_cfg(d, H=H, Hkv=Hkv, N=N, Nk=Nk, causal=causal, Br=Br, n_groups=d // G), heads=None if Nk < 1000 else (0, H // 2, H - 1))
+
+
 # Blocks of 64 x 128 at d = 128 take the fused product as soon as there are more workgroups than compute units, with kt_in
 # or without: the same bits.
 @pytest.mark.parametrize("G", [4, 8])
@@ -100,6 +113,7 @@ def test_blocks_of_64_by_128(N, Nk, causal, G):
     assert np.array_equal(_call(cfg, q, k, v, None)[0], o)
 
 
+# groups of 16 (contraction zero-padded to one matrix step): fused from many rows per key on
 @pytest.mark.parametrize("d,N,Br", [(64, 2070, 64), (64, 2070, 256), (128, 1590, 64), (128, 1590, 128)])
 def test_fused_groups_of_16(d, N, Br):
     _check(_cfg(d, H=32, Hkv=1, N=N, Nk=N, causal=False, Br=Br, n_groups=d // 16), heads=(0, 13, 31))

@@ -49,6 +49,23 @@ def test_float_backward(d, N, Nk, causal, G):
         assert err <= TOL * max(1.0, np.abs(r).max()), f"{what}: {err:.4g}"
 
 
+# Float dK/dV over the groups: a wave takes a run of the query tiles of all heads of a kv head. Runs of one tile, of none, runs that begin
+# inside a Q block, cover several, cross from one head into the next and, under the mask, skip the tiles above a key tile.
+@pytest.mark.parametrize("H,Hkv,N,Nk,Br,causal", [(1, 1, 40, 33, 64, False), (2, 1, 97, 40, 64, False), (6, 1, 330, 70, 64, False), (6, 1, 330, 350, 64, True),
+                                                  (5, 1, 200, 200, 128, True), (3, 1, 500, 33, 256, False)])
+@pytest.mark.parametrize("d,G", [(64, 2), (64, 4), (128, 2), (128, 4)])
+def test_float_dkv_runs(H, Hkv, N, Nk, Br, causal, d, G):
+    import gpu_util as U
+    from test_gpu_backward import TOL, run_backward
+    cfg = W.CONFIGS["tiny"].scaled(B=2, H=H, Hkv=Hkv, N=N, Nk=Nk, d=d, Br=Br, causal=causal, n_groups=d // G, recipe="normal", n_planes=16)
+    print(f"case {cfg}", flush=True)
+    q, k, v = W.make(cfg)
+    dout = W.make_grad(cfg)
+    for what, g, r in zip(("dq", "dk", "dv"), run_backward(cfg, q, k, v, dout, True), oracle.distr_bwd(q, k, v, dout, U.oracle_params(cfg))):
+        err = np.abs(g - r).max()
+        assert err <= TOL * max(1.0, np.abs(r).max()), f"{what}: {err:.4g}"
+
+
 # bf16, few query rows against many keys: rows of all query heads of a kv head packed into tiles of 32,
 # key tiles of 64 (d = 64) or 32 (d = 128) dealt out to four waves of each share.
 @pytest.mark.parametrize("base,d", [("llama", 64), ("long", 128)])
@@ -239,6 +256,28 @@ def test_lsh_kernel(dtype, d, Br, N, n_planes, offset):
     assert np.array_equal(hsh.cpu().numpy().view(np.uint32), want_hash)
 
 
+# The same with more blocks than compute units, where a bf16 block has 256 threads instead of 512.
+@pytest.mark.parametrize("d,Br", [(64, 64), (64, 256), (128, 64), (128, 128), (128, 256)])
+@pytest.mark.parametrize("N,n_planes,offset", [(1, 16, 0), (65, 3, 0), (257, 17, 0), (300, 32, 1), (129, 16, 1), (33, 32, 1)])
+def test_lsh_kernel_many_blocks(d, Br, N, n_planes, offset):
+    import torch
+
+    import gpu_util as U
+    import paper_2507_17245_amd as da
+    cfg = W.CONFIGS["tiny"].scaled(B=1, H=260, Hkv=260, N=N, d=d, Br=Br, n_groups=d // 2, n_planes=n_planes, recipe="normal")
+    q = torch.from_numpy(W.make(cfg)[0]).bfloat16()
+    print(f"case {cfg} offset {offset}", flush=True)
+    tq = torch.empty(q.numel() + 8, dtype=torch.bfloat16, device="cuda")[offset:offset + q.numel()].view(q.shape)
+    tq.copy_(q)
+    perm = torch.zeros((1, 260, cfg.Tq, d), dtype=torch.uint8, device="cuda")
+    hsh = torch.zeros((1, 260, cfg.Tq, d), dtype=torch.int32, device="cuda")
+    da.distr_attn_lsh_group(tq, da.make_params(tq, tq, tq, Br=Br, n_groups=d // 2, lsh_seed=cfg.lsh_seed, n_planes=n_planes,
+                                               perm_out=perm, hash_out=hsh))
+    want_hash, want_perm, _ = oracle.lsh_group(q.float().numpy(), U.oracle_params(cfg))
+    assert np.array_equal(perm.cpu().numpy(), want_perm)
+    assert np.array_equal(hsh.cpu().numpy().view(np.uint32), want_hash)
+
+
 # Projections the matrix pipe leaves in doubt: `n` channels of every 16 sum to almost nothing along one projection (columns
 # built as in test_projections_that_nearly_cancel). One at a time is summed by the wave, a few by a lane each, many by
 # every lane for its own channels; in the LSH kernel and in the forward kernels' own stages. Tables to the bit.
@@ -340,13 +379,15 @@ def test_bf16_short(N, Nk, causal, B, Br, G):
     assert np.abs(lse.cpu().numpy() - oracle.lse(q, k, p, distr=False)).max() <= 2e-2
 
 
-# Causal launches whose second round of workgroups is issued in the opposite order: a whole second round, one that the
-# tiles end inside of, more heads than compute units. Every row of every head, forward and gradients.
-@pytest.mark.parametrize("B,H,Hkv,N,Br", [(1, 100, 50, 500, 64), (2, 12, 4, 910, 64), (1, 300, 300, 200, 64), (2, 70, 70, 600, 128)])
-def test_causal_order(B, H, Hkv, N, Br):
+# Causal launches whose second round of workgroups is issued in the opposite order: in the forward a whole second round and one that
+# the tiles end inside of, in the backward (tiles of 128 rows) the same at d = 64 and 128; more heads than half the compute units, or than all
+# of them, where nothing is reversed (300 rows; 200 take the one-workgroup kernels). Every row of every head, forward and gradients.
+@pytest.mark.parametrize("base,B,H,Hkv,N,Br", [("llama", 1, 100, 50, 500, 64), ("llama", 2, 12, 4, 910, 64), ("llama", 2, 70, 70, 600, 128), ("llama", 1, 300, 300, 200, 64), ("llama", 1, 300, 100, 300, 64),
+                                               ("llama", 1, 40, 20, 1100, 128), ("llama", 1, 64, 64, 1030, 64), ("long", 1, 40, 40, 1100, 128), ("long", 1, 64, 32, 900, 64)])
+def test_causal_order(base, B, H, Hkv, N, Br):
     import gpu_util as U
     from test_gpu_backward import run_backward
-    cfg = W.CONFIGS["llama"].scaled(B=B, H=H, Hkv=Hkv, N=N, Br=Br, recipe="normal")
+    cfg = W.CONFIGS[base].scaled(B=B, H=H, Hkv=Hkv, N=N, Br=Br, recipe="normal")
     _forward(cfg)
     _forward(cfg, distr=False)
     q, k, v = W.make(cfg)
@@ -376,12 +417,13 @@ def test_float_eight_waves(B, H, Hkv, N, Nk, causal, side, Bc, G):
 
 
 # Two halves of the keys per workgroup: blocks whose second half has no tile (causal, one tile) or one less than the first, ragged last
-# tiles, halves of a share of dealt-out keys (some of them empty), the fused product with odd group counts, the edges of the rule.
+# tiles, halves of a share of dealt-out keys (blocks of 64 rows and, with 24 tiles a share, of 128), the edges of the rule. Exact and Q~ K^T; the
+# fused product is in test_fused_in_halves.
 @pytest.mark.parametrize("base,Br,B,H,Hkv,N,Nk,causal,G", [
     ("llama", 64, 1, 4, 2, 200, 200, True, 2), ("llama", 64, 2, 3, 3, 257, 449, False, 4), ("long", 64, 1, 4, 4, 300, 330, True, 2),
     ("long", 64, 1, 2, 1, 65, 197, False, 8), ("llama", 64, 1, 2, 2, 130, 3000, True, 2), ("long", 64, 1, 3, 3, 100, 2500, True, 4),
     ("llama", 128, 1, 2, 1, 1537, 1537, True, 2), ("long", 128, 1, 2, 2, 1600, 1637, True, 2), ("llama", 128, 1, 1, 1, 140, 4700, True, 2),
-    ("long", 128, 1, 2, 1, 130, 6001, False, 4), ("llama", 64, 1, 64, 64, 512, 512, True, 2), ("llama", 64, 1, 65, 65, 512, 512, True, 2)])
+    ("long", 128, 1, 2, 1, 130, 6001, False, 4), ("llama", 128, 1, 64, 64, 140, 3900, True, 2), ("long", 128, 1, 64, 32, 140, 3900, True, 4), ("llama", 64, 1, 64, 64, 512, 512, True, 2), ("llama", 64, 1, 65, 65, 512, 512, True, 2)])
 def test_halves(base, Br, B, H, Hkv, N, Nk, causal, G):
     import gpu_util as U
     import torch
