@@ -254,17 +254,20 @@ def main():
             fn()
             ms = ev_time(fn, steps)
             out[name] = {"ms": ms, "alu_frac": fl / (ms * 1e-3) / 1e12 / PEAK_FP32_TFLOPS}
-        # backward: two kernels (dQ; dK and dV), each rebuilds the scores and dP: 2 * (2k + 2d) FLOP per pair and kernel
+        # backward: the dQ and the dK/dV kernel each rebuild the scores and dP, and add dQ, or dK and dV: 7 products. Groups of two and four
+        # take scores, dQ and dK over the groups; other sizes all of them over the channels, like the exact call
+        width = cfg.n_groups if cfg.d // cfg.n_groups in (2, 4) else cfg.d
+        bw_fl_d, bw_fl_e = 2.0 * pairs * (4 * width + 3 * cfg.d), 14.0 * pairs * cfg.d
         da.distr_attn_fwd_ex(q, k, v, o, p_d)
         bw_d = lambda: da.distr_attn_bwd_ex(q, k, v, o, dout, lse, dq, dk, dv, p_d)
         bw_d()
         ms = ev_time(bw_d, steps)
-        out["backward"] = {"ms": ms, "alu_frac": 4.0 * fl_d / (ms * 1e-3) / 1e12 / PEAK_FP32_TFLOPS}
+        out["backward"] = {"ms": ms, "alu_frac": bw_fl_d / (ms * 1e-3) / 1e12 / PEAK_FP32_TFLOPS}
         da.distr_attn_exact_fwd_ex(q, k, v, o, p_e)
         bw_e = lambda: da.distr_attn_exact_bwd_ex(q, k, v, o, dout, lse, dq, dk, dv, p_e)
         bw_e()
         ms = ev_time(bw_e, steps)
-        out["backward_exact"] = {"ms": ms, "alu_frac": 4.0 * fl_e / (ms * 1e-3) / 1e12 / PEAK_FP32_TFLOPS}
+        out["backward_exact"] = {"ms": ms, "alu_frac": bw_fl_e / (ms * 1e-3) / 1e12 / PEAK_FP32_TFLOPS}
         return out
 
     def backward_table(cfg, tensors, steps):

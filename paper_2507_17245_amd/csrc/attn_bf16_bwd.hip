@@ -1037,6 +1037,9 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_short_kernel(
 // shares fills the chip by itself (one workgroup per compute unit, two at d = 64; under the mask, d = 128, two rounds) and the
 // key tiles are whole, it is taken: the resident workgroups end together. A launch that is less full, or whose heads end in
 // a ragged tile (masked at every step, so its workgroup is the last), lives on many short ones, and so does the mask at d = 64.
+// The line: heads dealt out by a smaller number are faster from 0.8 of a full chip on (time over that of all dealt out, at 3/4, 13/16,
+// 7/8 and all of it: d128 not causal 0.93-0.95, 0.94-0.96, 0.95-0.97, 0.95-0.98; causal 0.93-1.00, 0.89-0.98, 0.89-0.95, 0.90-0.96; d64 not causal
+// 1.03-1.06, 0.95-0.97, 0.96-0.97, 0.97-0.99) and lose past it (17/16: 1.11, 0.93-0.98, 1.06-1.09); 7/8 is on the safe side of that.
 // Whole backward, us, all heads dealt out | the rule: d128 causal H32 Hkv8 N4096 545 | 519, N3712 465 | 444, B8 N512 215 | 168; not causal
 // N2048 267 | 256, N4096 937 | 893, H24 Hkv4 N4096 708 | 688, B16 H32 Hkv8 N128 81 | 65; d64 not causal N4096 480 | 474, B4 N1024 160 | 150,
 // B16 N256 85 | 74. Fewer shares elsewhere: d64 causal H32 Hkv8 N4096 284 | 297, ragged N3800 d128 859 | 975, 3/4 full (B2 H24 Hkv4

@@ -138,7 +138,7 @@ struct Cfg {
   static constexpr int FUSE_OUT = (NG * PPR + TH - 1) / TH;   // 16-byte fused outputs per thread and tile
   static constexpr int KSTEPS = KRED / 16;        // MFMA steps of the score product
   // Register budget: two waves per SIMD, except the widest tile at d = 128, whose two score sets
-  // (128 registers) leave room for one.
+  // (128 registers) leave room for one. (Blocks of 128 rows at d = 128 in two halves, over the channels, spill four outside the loop.)
   static constexpr int WAVES_PER_SIMD = (BC == 128 && D == 128) ? 1 : 2;
 };
 

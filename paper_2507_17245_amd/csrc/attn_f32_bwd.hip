@@ -27,8 +27,9 @@
 // The waves' partial sums meet in LDS once, at the end, in a fixed order: as in the forward no wave waits
 // for another before that, and few rows still give every SIMD work. Bound: the matrix
 // instruction (64 cycles for 4096 FLOP): 7 products over d per (query, key) pair, 5 with groups of two, 4 with groups
-// of four. Measured (B1 H8 N2048 d64 n_groups 32): delta 4, dK/dV 144, dQ 91 us; the matrix pipe is busy 2/3 of the time
-// (dK/dV with S^ and dK over the groups' members, K_f summed for every tile anew: 176 us; backward d128 642 -> 504 us, groups of four
+// of four. Measured (B1 H8 N2048 d64 n_groups 32): delta 4, dK/dV 144, dQ 91 us; the matrix pipes are busy 60 and 62 % of the launch
+// (67 and 71 % of the cycles in which their CU has work), the waves wait for them to take an instruction 57 and 68 % of their cycles
+// and for memory, LDS and barriers 23 and 14 %; tiles hit the L2 (95 %). (dK/dV with S^ and dK over the groups' members, K_f summed for every tile anew: 176 us; backward d128 642 -> 504 us, groups of four
 // 572 -> 411; float multiply-adds on the vector ALUs: dK/dV 2740, dQ 1980 us).
 #include <type_traits>
 
@@ -414,7 +415,8 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) dp[i] *= s[i];
     // (G > 1: a wave's run of tiles makes the chains of the causal mask's heavy rows long, so that a tile's dV is summed by
-    // itself first, like dK; at d = 128 in groups of two, two channel blocks at a time: with four, 36 registers spilled)
+    // itself first, like dK; at d = 128 in groups of two, two channel blocks at a time: with four, 36 registers spilled. As it is
+    // 12 do there, and 6 and 2 at d = 64 with eight waves in groups of two and four, some of them reloaded at every tile)
     if constexpr (G > 1 && (NB == 2 || G == 4)) {
       f32x16 part[NB];
 #pragma unroll

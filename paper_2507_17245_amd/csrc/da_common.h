@@ -132,7 +132,8 @@ __device__ inline void settle_doubts(const bool (&doubt)[4], bool (&positive)[4]
 // ones, with the second round of workgroups (one per compute unit) in the opposite order: the compute unit that got the
 // longest tile of the first round gets the shortest of the second, where it would otherwise get the longest again. The units'
 // sums then differ by a round's spread instead of twice that, which is more than the workgroups that follow even out (at
-// 1024 of them the third and fourth round are a third of the work, at 512 there is none).
+// 1024 of them the third and fourth round are a third of the work, at 512 there is none). With more heads than half the
+// compute units a round holds one tile of a head and nothing is reversed.
 constexpr int kComputeUnits = 256;
 __device__ inline int paired_tile(int at, int heads, int tiles) {
   const int round = heads < kComputeUnits ? kComputeUnits / heads : 1;

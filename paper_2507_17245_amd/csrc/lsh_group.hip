@@ -254,7 +254,7 @@ static hipError_t launch_rows(const T* q, const Problem& pb, uint8_t* perm_out, 
   int rows = pb.Br;
   while (rows > 32 && pb.N <= rows / 2) rows /= 2;
   // Threads of a workgroup: 512 where the chip is not full without them, and for the float sums of 128 channels at any size
-  // (two projections a thread and chain, not eight; the 1024 chains of 64 channels are short with 256 threads, and barriers
+  // (four projections a thread, not eight; at 64 channels 256 threads have four each already, and barriers
   // of more waves cost more). us, 256 | 512 threads: bf16 d128 H16 N200 Br128 8.2 | 6.9, H16 N2048 Br256 15.8 | 10.9,
   // 1000 rows of 48 heads in blocks of 64 8.7 | 10.0; bf16 d64 H16 N2048 Br128 6.6 | 6.2, 1024 blocks 10.7 | 12.5; float d128
   // H8 N2048 Br128 8.8 | 6.6, 8192 blocks 154 | 139; float d64 H8 N2048 Br128 5.4 | 5.9.
