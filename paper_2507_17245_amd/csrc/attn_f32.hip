@@ -4,8 +4,11 @@
 // Same steps as the bf16 kernel (Sec. 2.2.2 tiling; Sec. 3.2 sampling and fusion per Q block,
 // Sec. 3.3; Eq. 2) on the float matrix instruction v_mfma_f32_32x32x2_f32 (float operands, float
 // products and sums: the precision of the vector ALUs at twice their rate without packed forms).
-// Bound: that instruction, 64 cycles for 4096 FLOP. Both products are taken transposed, so that
-// one lane owns one query row:
+// Bound: that instruction, 64 cycles for 4096 FLOP; where both operands are floats summed over groups of two or four channels
+// (float_by_pieces in f32_tiles.h) the products are taken of three bf16 pieces each (6 products of 32 cycles for 8 of 64; every
+// float is the sum of its pieces, and the distance from 64 bits is a fifth below that of the float instruction). There a tile is
+// 36 products and 16 for the splitting, bound by issue and the clock (1.85 GHz under them, pipes busy 60 %).
+// Both products are taken transposed, so that one lane owns one query row:
 //   S^T[kv][q] = Kx Qx^T     A = keys from LDS, B = queries in registers
 //   O^T[ch][q] = V^T P^T     A = V straight from global memory, B = P in registers: register i of
 //                            a score accumulator holds the keys 8*(i/4) + i%4 (+ 4 in the upper
@@ -15,9 +18,8 @@
 // themselves, each with a softmax state of its own; the states meet in LDS once at the end. No wave
 // waits for another before that, and a problem of few rows still fills the chip: sharing tiles
 // among waves of different rows instead would leave N = 256 with 8 working waves.
-// Measured (B1 H8 N2048 d64 n_groups 32): 71 us, 92 TFLOP/s of the 157 the instruction can reach
-// (float multiply-adds on the vector ALUs, a thread quad per row: 1430 us); mirrored 73 us (1439);
-// B1 H1 N256: 9 us (162).
+// Measured (B1 H8 N2048 d64 n_groups 32): by pieces 57 us, by floats 72 (92 TFLOP/s of the 157 the instruction can reach; float
+// multiply-adds on the vector ALUs, a thread quad per row: 1430 us); mirrored 65 and 78; B1 H1 N256: 9 us (162).
 //
 // Score product, by MODE:
 //   kQueryFused  the wave writes its K tile into LDS in sorted channel order, a group's G channels
@@ -43,7 +45,7 @@ namespace {
 
 enum Mode { kQueryFull, kQueryFused, kKeyFull, kKeyFused };
 
-template <typename E, int D, int G, int MODE, int NW>
+template <typename E, int D, int G, int MODE, int NW, bool PIECES>
 __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     const E* __restrict__ q, const E* __restrict__ k, const E* __restrict__ v, E* __restrict__ o,
     const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Br, int Tq, int Tw, int n_groups,
@@ -61,6 +63,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
   __shared__ __attribute__((aligned(16))) float k_lds[NW][kTile * RS];   // K tile of each wave, at the end its output
   __shared__ float stat_lds[NW][2][kTile];
   __shared__ __attribute__((aligned(16))) uint8_t map_lds[kMirrored ? NW : 1][D];
+  __shared__ uint32_t mark_lds[kTile];   // PIECES: what is known of a row (kRowAgain ..)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -107,9 +110,9 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     for (int u = 0; u < QU; ++u) x[u] = Quad<E>::load(q_rsrc, (u * T + tid) * 4 * (int)sizeof(E), r0 * (D * (int)sizeof(E)));
 #pragma unroll
     for (int u = 0; u < QU; ++u) *(f32x4*)&q_lds[(u * T + tid) / (D / 4) * RS + (u * T + tid) % (D / 4) * 4] = Quad<E>::values(x[u]);
+    if (PIECES && tid < kTile) mark_lds[tid] = 0;
   }
   int kdst[4];          // kQueryFused: where the lane's four channels go in a row sorted by group
-  float qop[HS];
   if constexpr (!kMirrored) {
     // map: position of a channel in sorted order (kQueryFused) / sampled channel of its group (kQueryFull)
     if (perm) {
@@ -121,226 +124,283 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     } else {
       for (int i = tid; i < D; i += T) map_lds[0][i] = (uint8_t)i;
     }
-    __syncthreads();
-    if constexpr (kFused) {
+  }
+  __syncthreads();
+  if constexpr (kFused && !kMirrored) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) kdst[e] = map_lds[0][(lane * 4 + e) % D] & (D - 1);
+    for (int e = 0; e < 4; ++e) kdst[e] = map_lds[0][(lane * 4 + e) % D] & (D - 1);
+  }
+
+  // One walk over the keys for the rows of the bit mask `rows`, products by pieces or on the float instruction. By pieces, the rows
+  // to be taken again with floats are returned.
+  auto pass = [&](auto pieces, uint32_t rows) -> uint32_t {
+    constexpr bool BY_PIECES = decltype(pieces)::value;
+    const Splitter splitter(lane);
+    float qop[HS];
+    if constexpr (MODE == kQueryFused) {
       // sampling: the group's first channel in sorted order
       const uint8_t* pr = perm + ((size_t)bh * Tq + r0 / Br) * D;
 #pragma unroll
       for (int s = 0; s < HS; ++s) qop[s] = q_lds[lq * RS + (pr[(hh * HS + s) * G] & (D - 1))];
-    } else {
+    } else if constexpr (MODE == kQueryFull) {
 #pragma unroll
       for (int s = 0; s < HS; ++s) qop[s] = q_lds[lq * RS + (map_lds[0][hh * HS + s] & (D - 1))];
-    }
-  } else {
-    __syncthreads();
-    if constexpr (MODE == kKeyFull) {
+    } else if constexpr (MODE == kKeyFull) {
 #pragma unroll
       for (int s = 0; s < HS; ++s) qop[s] = q_lds[lq * RS + hh * HS + s];
     }
-  }
+    Pieces qpc[BY_PIECES ? HS / 8 : 1];
+    auto split_q = [&]() {
+      if constexpr (BY_PIECES) split_steps<HS, false>(splitter, qop, [&](int s, const Pieces& p) { qpc[s] = p; });
+    };
+    if constexpr (!kMirrored) split_q();
+    float* kt = k_lds[w];
+    int koff[kMirrored ? HS : 1];   // channel of the K row that contraction slot s takes (mirrored form)
+    f32x16 oacc[NB];
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb) zero(oacc[mb]);
+    // Reference and scores stay unscaled until their difference is taken: exact to the last bit of the difference
+    // whatever their size (one fused multiply-add against a scaled reference keeps the rounding of the reference).
+    float m_run = -FLT_MAX, l_run = 0.0f;   // l over this lane's half of the keys
+    const float scale_log2e = scale * 1.4426950408889634f;
+    const int q_abs = r0 + lq;
+    const int lim = causal ? min(q_abs + shift, Nk - 1) : Nk - 1;   // last key this row sees
 
-  float* kt = k_lds[w];
-  int koff[kMirrored ? HS : 1];   // channel of the K row that contraction slot s takes (mirrored form)
-  f32x16 oacc[NB];
+    asm volatile(".p2align 6");   // the loop on an instruction line: by where the code in front put it H1 N256 took 12.4 .. 12.7 us
+    while (tile < n_tiles) {
+      // ---- stage the K tile (and, mirrored, the K block's grouping) -------------------------------
+      wave_order();   // the reads of the previous tile come first
 #pragma unroll
-  for (int mb = 0; mb < NB; ++mb) zero(oacc[mb]);
-  // Reference and scores stay unscaled until their difference is taken: exact to the last bit of the difference
-  // whatever their size (one fused multiply-add against a scaled reference keeps the rounding of the reference).
-  float m_run = -FLT_MAX, l_run = 0.0f;   // l over this lane's half of the keys
-  const float scale_log2e = scale * 1.4426950408889634f;
-  const int q_abs = r0 + lq;
-  const int lim = causal ? min(q_abs + shift, Nk - 1) : Nk - 1;   // last key this row sees
-
-  while (tile < n_tiles) {
-    // ---- stage the K tile (and, mirrored, the K block's grouping) -------------------------------
-    wave_order();   // the reads of the previous tile come first
+      for (int u = 0; u < KU; ++u) {
+        const f32x4 x = Quad<E>::values(kreg[u]);
+        const int row = (u * 64 + lane) / (D / 4), c = (u * 64 + lane) % (D / 4) * 4;
+        if constexpr (MODE == kQueryFused) {
 #pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const f32x4 x = Quad<E>::values(kreg[u]);
-      const int row = (u * 64 + lane) / (D / 4), c = (u * 64 + lane) % (D / 4) * 4;
-      if constexpr (MODE == kQueryFused) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) kt[row * RS + kdst[e]] = x[e];
-      } else {
-        *(f32x4*)&kt[row * RS + c] = x;
-      }
-    }
-    const bool new_block = kMirrored && tile % TB == 0;
-    if constexpr (kMirrored) {
-      if (new_block) {
-        if constexpr (kFused) {
-#pragma unroll
-          for (int u = 0; u < D / 64; ++u) map_lds[w][u * 64 + lane] = map_reg[u] & (D - 1);
+          for (int e = 0; e < 4; ++e) kt[row * RS + kdst[e]] = x[e];
         } else {
-          // a channel's group's first channel: lane i of the sorted order names its own
-          const int group = D / n_groups;
-          uint8_t* tmp = (uint8_t*)&stat_lds[w][0][0];   // (the softmax states use it after the loop only)
-#pragma unroll
-          for (int u = 0; u < D / 64; ++u) tmp[u * 64 + lane] = map_reg[u] & (D - 1);
-          wave_order();
-#pragma unroll
-          for (int u = 0; u < D / 64; ++u) {
-            const int i = u * 64 + lane;
-            map_lds[w][tmp[i]] = tmp[i / group * group];
-          }
+          *(f32x4*)&kt[row * RS + c] = x;
         }
       }
-    }
-    wave_order();
-    // V of this tile, then K of the next one: in flight under the score product and P.V
-    constexpr int VR = NB / 2;   // raw pairs per row of V and lane
-    typename Pair<E>::raw vreg[16][VR];
-    auto load_v = [&](int i) {
+      const bool new_block = kMirrored && tile % TB == 0;
+      if constexpr (kMirrored) {
+        if (new_block) {
+          if constexpr (kFused) {
 #pragma unroll
-      for (int j = 0; j < VR; ++j)
-        vreg[i][j] = Pair<E>::load(v_rsrc, (acc_row(i, hh) * D + lq * NB + 2 * j) * (int)sizeof(E), tile * (kTile * D * (int)sizeof(E)));
-    };
+            for (int u = 0; u < D / 64; ++u) map_lds[w][u * 64 + lane] = map_reg[u] & (D - 1);
+          } else {
+            // a channel's group's first channel: lane i of the sorted order names its own
+            const int group = D / n_groups;
+            uint8_t* tmp = (uint8_t*)&stat_lds[w][0][0];   // (the softmax states use it after the loop only)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) load_v(i);
-    // (unconditional, so that the waits for V can count the loads of K behind it: the last tile again
-    // when there is no next one)
-    const int following = next_tile(tile);
-    load_k(min(following, n_tiles - 1));
-
-    if constexpr (kMirrored) {
-      if (new_block) {
-        // entries of this half of the wave: positions hh*D/2 .. of the sorted order (kKeyFused), the
-        // sampled channels of its channels (kKeyFull)
+            for (int u = 0; u < D / 64; ++u) tmp[u * 64 + lane] = map_reg[u] & (D - 1);
+            wave_order();
 #pragma unroll
-        for (int c16 = 0; c16 < D / 2; c16 += 16) {
-          const u32x4 e4 = *(const u32x4*)&map_lds[w][hh * (D / 2) + c16];
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int ch = (e4[e >> 2] >> (8 * (e & 3))) & (D - 1);
-            if constexpr (MODE == kKeyFull) {
-              koff[c16 + e] = ch;
-            } else {
-              const float x = q_lds[lq * RS + ch];   // fusion of Q, members in sorted order
-              if ((c16 + e) % G == 0) {
-                koff[(c16 + e) / G] = ch;
-                qop[(c16 + e) / G] = x;
-              } else {
-                qop[(c16 + e) / G] += x;
-              }
+            for (int u = 0; u < D / 64; ++u) {
+              const int i = u * 64 + lane;
+              map_lds[w][tmp[i]] = tmp[i / group * group];
             }
           }
         }
       }
+      wave_order();
+      // V of this tile, then K of the next one: in flight under the score product and P.V
+      constexpr int VR = NB / 2;   // raw pairs per row of V and lane
+      typename Pair<E>::raw vreg[16][VR];
+      auto load_v = [&](int i) {
+#pragma unroll
+        for (int j = 0; j < VR; ++j)
+          vreg[i][j] = Pair<E>::load(v_rsrc, (acc_row(i, hh) * D + lq * NB + 2 * j) * (int)sizeof(E), tile * (kTile * D * (int)sizeof(E)));
+      };
+#pragma unroll
+      for (int i = 0; i < 16; ++i) load_v(i);
+      // (unconditional, so that the waits for V can count the loads of K behind it: the last tile again
+      // when there is no next one)
+      const int following = next_tile(tile);
+      load_k(min(following, n_tiles - 1));
+
+      if constexpr (kMirrored) {
+        if (new_block) {
+          // entries of this half of the wave: positions hh*D/2 .. of the sorted order (kKeyFused), the
+          // sampled channels of its channels (kKeyFull)
+#pragma unroll
+          for (int c16 = 0; c16 < D / 2; c16 += 16) {
+            const u32x4 e4 = *(const u32x4*)&map_lds[w][hh * (D / 2) + c16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              const int ch = (e4[e >> 2] >> (8 * (e & 3))) & (D - 1);
+              if constexpr (MODE == kKeyFull) {
+                koff[c16 + e] = ch;
+              } else {
+                const float x = q_lds[lq * RS + ch];   // fusion of Q, members in sorted order
+                if ((c16 + e) % G == 0) {
+                  koff[(c16 + e) / G] = ch;
+                  qop[(c16 + e) / G] = x;
+                } else {
+                  qop[(c16 + e) / G] += x;
+                }
+              }
+            }
+          }
+          if constexpr (MODE == kKeyFused) split_q();
+        }
+      }
+
+      // ---- scores -----------------------------------------------------------------------------------
+      PieceSum by_pieces;
+      ChannelSum<HS> by_floats;
+      float kop[BY_PIECES ? HS : 1];
+      auto put = [&](int s, float x) {   // float s of the lane's half row
+        if constexpr (BY_PIECES) kop[s] = x;
+        else by_floats.step(s, x, qop[s]);
+      };
+      if constexpr (kMirrored) {
+#pragma unroll
+        for (int s = 0; s < HS; ++s) put(s, kt[lq * RS + koff[s]]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < D / 2; c += 4) {
+          const f32x4 x = *(const f32x4*)&kt[lq * RS + hh * (D / 2) + c];
+          if constexpr (MODE == kQueryFull) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) put(c + e, x[e]);
+          } else if constexpr (G == 2) {
+            put(c / 2, x[0] + x[1]);
+            put(c / 2 + 1, x[2] + x[3]);
+          } else {
+            put(c / 4, ((x[0] + x[1]) + x[2]) + x[3]);
+          }
+        }
+      }
+      f32x16 sacc;
+      if constexpr (BY_PIECES) {
+        split_steps<HS>(splitter, kop, [&](int s, const Pieces& p) { by_pieces.step(p, qpc[s]); });
+        sacc = by_pieces.sum();
+      } else {
+        sacc = by_floats.sum();
+      }
+      const int n0 = tile * kTile;
+      if (n0 + kTile > Nk || (causal && n0 + kTile - 1 > r0 + shift)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (n0 + acc_row(i, hh) > lim) sacc[i] = -INFINITY;
+      }
+      // ---- online softmax step (Sec. 2.2.2) -------------------------------------------------------
+      float mt = sacc[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) mt = fmaxf(mt, sacc[i]);
+      const float m_new = fmaxf(m_run, half_swap_max(mt));
+      if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
+        l_run *= alpha;
+#pragma unroll
+        for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) oacc[mb][i] *= alpha;
+        m_run = m_new;
+      }
+      float ps[16], sum0 = 0.0f, sum1 = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        ps[i] = __builtin_amdgcn_exp2f((sacc[i] - m_run) * scale_log2e);
+        ps[i + 1] = __builtin_amdgcn_exp2f((sacc[i + 1] - m_run) * scale_log2e);
+        sum0 += ps[i];
+        sum1 += ps[i + 1];
+      }
+      l_run += sum0 + sum1;
+      // ---- O^T += V^T P^T -----------------------------------------------------------------------------
+      if constexpr (BY_PIECES) {
+        f32x16 x;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = ps[i];
+        Pieces p0, p1, v0, v1;
+        splitter(x, p0, p1);
+#pragma unroll
+        for (int mb = 0; mb < NB; ++mb) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) x[i] = Pair<E>::value(vreg[i][mb >> 1], mb & 1);
+          splitter(x, v0, v1);
+          oacc[mb] = mfma(v0, p0, oacc[mb]);
+          oacc[mb] = mfma(v1, p1, oacc[mb]);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+          for (int mb = 0; mb < NB; ++mb)
+            oacc[mb] = mfma(Pair<E>::value(vreg[i][mb >> 1], mb & 1), ps[i], oacc[mb]);
+      }
+      tile = following;
     }
 
-    // ---- scores -----------------------------------------------------------------------------------
-    ChannelSum<HS> acc;
-    if constexpr (kMirrored) {
+    // ---- the waves' states meet: rows of (reference, sum), then the outputs -------------------------
+    const float l_tot = half_swap_sum(l_run);
+    wave_order();
+    if (hh == 0) {
+      stat_lds[w][0][lq] = m_run;
+      stat_lds[w][1][lq] = l_tot;
+    }
+    __syncthreads();
+    float m_all = stat_lds[0][0][lq];
 #pragma unroll
-      for (int s = 0; s < HS; ++s) acc.step(s, kt[lq * RS + koff[s]], qop[s]);
-    } else {
+    for (int j = 1; j < NW; ++j) m_all = fmaxf(m_all, stat_lds[j][0][lq]);
+    float l_all = 0.0f;
 #pragma unroll
-      for (int c = 0; c < D / 2; c += 4) {
-        const f32x4 x = *(const f32x4*)&kt[lq * RS + hh * (D / 2) + c];
-        if constexpr (MODE == kQueryFull) {
+    for (int j = 0; j < NW; ++j) l_all += stat_lds[j][1][lq] * __builtin_amdgcn_exp2f((stat_lds[j][0][lq] - m_all) * scale_log2e);
+    const float weight = __builtin_amdgcn_exp2f((m_run - m_all) * scale_log2e) / l_all;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc.step(c + e, x[e], qop[c + e]);
-        } else if constexpr (G == 2) {
-          acc.step(c / 2, x[0] + x[1], qop[c / 2]);
-          acc.step(c / 2 + 1, x[2] + x[3], qop[c / 2 + 1]);
+    for (int i = 0; i < 16; ++i) {
+      const int m = acc_row(i, hh);
+      if constexpr (NB == 2) {
+        const float x[2] = {oacc[0][i] * weight, oacc[1][i] * weight};
+        __builtin_memcpy(__builtin_assume_aligned(&kt[lq * RS + m * 2], 8), x, 8);
+      } else {
+        const f32x4 x = {oacc[0][i] * weight, oacc[1][i] * weight, oacc[2][i] * weight, oacc[NB - 1][i] * weight};
+        *(f32x4*)&kt[lq * RS + m * 4] = x;
+      }
+    }
+    // row statistics for a backward pass: ln(sum of exp(score)) = rounded reference (see scaled_plus) + ln(sum)
+    if (lse && w == 0 && hh == 0 && q_abs < N && rows >> lq & 1)
+      lse[(size_t)bh * N + q_abs] = __builtin_fmaf(__builtin_log2f(l_all), 0.6931471805599453f, m_all * scale);
+    __syncthreads();
+    for (int i = tid; i < kTile * D / 4; i += T) {
+      const int row = i / (D / 4), c = i % (D / 4) * 4;
+      if (r0 + row < N && rows >> row & 1) {
+        f32x4 x = *(const f32x4*)&k_lds[0][row * RS + c];
+#pragma unroll
+        for (int j = 1; j < NW; ++j) x += *(const f32x4*)&k_lds[j][row * RS + c];
+        if constexpr (BY_PIECES) atomicOr(&mark_lds[row], row_mark(x));
+        E* dst = o + ((size_t)bh * N + r0 + row) * D + c;
+        if constexpr (std::is_same<E, float>::value) {
+          *(f32x4*)dst = x;
         } else {
-          acc.step(c / 4, ((x[0] + x[1]) + x[2]) + x[3], qop[c / 4]);
+          const bf16x4 y = {(bf16)x[0], (bf16)x[1], (bf16)x[2], (bf16)x[3]};
+          *(bf16x4*)dst = y;
         }
       }
     }
-    f32x16 sacc = acc.sum();
-    const int n0 = tile * kTile;
-    if (n0 + kTile > Nk || (causal && n0 + kTile - 1 > r0 + shift)) {
+    if constexpr (!BY_PIECES) return 0;
+    bool out = false;
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (n0 + acc_row(i, hh) > lim) sacc[i] = -INFINITY;
-    }
-    // ---- online softmax step (Sec. 2.2.2) -------------------------------------------------------
-    float mt = sacc[0];
-#pragma unroll
-    for (int i = 1; i < 16; ++i) mt = fmaxf(mt, sacc[i]);
-    const float m_new = fmaxf(m_run, half_swap_max(mt));
-    if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
-      l_run *= alpha;
-#pragma unroll
-      for (int mb = 0; mb < NB; ++mb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[mb][i] *= alpha;
-      m_run = m_new;
-    }
-    float ps[16], sum0 = 0.0f, sum1 = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 16; i += 2) {
-      ps[i] = __builtin_amdgcn_exp2f((sacc[i] - m_run) * scale_log2e);
-      ps[i + 1] = __builtin_amdgcn_exp2f((sacc[i + 1] - m_run) * scale_log2e);
-      sum0 += ps[i];
-      sum1 += ps[i + 1];
-    }
-    l_run += sum0 + sum1;
-    // ---- O^T += V^T P^T -----------------------------------------------------------------------------
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-#pragma unroll
-      for (int mb = 0; mb < NB; ++mb)
-        oacc[mb] = mfma(Pair<E>::value(vreg[i][mb >> 1], mb & 1), ps[i], oacc[mb]);
-    tile = following;
-  }
-
-  // ---- the waves' states meet: rows of (reference, sum), then the outputs -------------------------
-  const float l_tot = half_swap_sum(l_run);
-  wave_order();
-  if (hh == 0) {
-    stat_lds[w][0][lq] = m_run;
-    stat_lds[w][1][lq] = l_tot;
-  }
-  __syncthreads();
-  float m_all = stat_lds[0][0][lq];
-#pragma unroll
-  for (int j = 1; j < NW; ++j) m_all = fmaxf(m_all, stat_lds[j][0][lq]);
-  float l_all = 0.0f;
-#pragma unroll
-  for (int j = 0; j < NW; ++j) l_all += stat_lds[j][1][lq] * __builtin_amdgcn_exp2f((stat_lds[j][0][lq] - m_all) * scale_log2e);
-  const float weight = __builtin_amdgcn_exp2f((m_run - m_all) * scale_log2e) / l_all;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int m = acc_row(i, hh);
-    if constexpr (NB == 2) {
-      const float x[2] = {oacc[0][i] * weight, oacc[1][i] * weight};
-      __builtin_memcpy(__builtin_assume_aligned(&kt[lq * RS + m * 2], 8), x, 8);
-    } else {
-      const f32x4 x = {oacc[0][i] * weight, oacc[1][i] * weight, oacc[2][i] * weight, oacc[NB - 1][i] * weight};
-      *(f32x4*)&kt[lq * RS + m * 4] = x;
-    }
-  }
-  // row statistics for a backward pass: ln(sum of exp(score)) = rounded reference (see scaled_plus) + ln(sum)
-  if (lse && w == 0 && hh == 0 && q_abs < N)
-    lse[(size_t)bh * N + q_abs] = __builtin_fmaf(__builtin_log2f(l_all), 0.6931471805599453f, m_all * scale);
-  __syncthreads();
-  for (int i = tid; i < kTile * D / 4; i += T) {
-    const int row = i / (D / 4), c = i % (D / 4) * 4;
-    if (r0 + row < N) {
-      f32x4 x = *(const f32x4*)&k_lds[0][row * RS + c];
-#pragma unroll
-      for (int j = 1; j < NW; ++j) x += *(const f32x4*)&k_lds[j][row * RS + c];
-      E* dst = o + ((size_t)bh * N + r0 + row) * D + c;
-      if constexpr (std::is_same<E, float>::value) {
-        *(f32x4*)dst = x;
-      } else {
-        const bf16x4 y = {(bf16)x[0], (bf16)x[1], (bf16)x[2], (bf16)x[3]};
-        *(bf16x4*)dst = y;
-      }
-    }
+    for (int c = 0; c < D / 2; c += 4) out |= outside_pieces(*(const f32x4*)&q_lds[lq * RS + hh * (D / 2) + c]);
+    __syncthreads();
+    return rows_again(mark_lds[lq] | (out ? kRowAgain : 0));
+  };
+  if constexpr (PIECES) {
+    const uint32_t again = pass(std::true_type(), ~0u);
+    if (again == 0) return;
+    tile = w * TB;
+    if (tile < n_tiles) load_k(tile);
+    pass(std::false_type(), again);
+  } else {
+    pass(std::false_type(), ~0u);
   }
 }
 
-template <typename E, int D, int G, int MODE, int NW>
+template <typename E, int D, int G, int MODE, int NW, bool PIECES>
 hipError_t launch_one(const void* q, const void* k, const void* v, void* o, const uint8_t* perm, const Problem& pb,
                       int n_groups, hipStream_t stream) {
   const int Tq = (pb.N + pb.Br - 1) / pb.Br, Tw = (pb.N + kTile - 1) / kTile;
-  hipLaunchKernelGGL((attn_f32_kernel<E, D, G, MODE, NW>), dim3((unsigned)((long long)pb.B * pb.H * Tw)), dim3(NW * 64), 0, stream,
+  hipLaunchKernelGGL((attn_f32_kernel<E, D, G, MODE, NW, PIECES>), dim3((unsigned)((long long)pb.B * pb.H * Tw)), dim3(NW * 64), 0, stream,
                      (const E*)q, (const E*)k, (const E*)v, (E*)o, perm, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, Tw, n_groups,
                      pb.causal, pb.scale, pb.Bc, pb.lse);
   return hipGetLastError();
@@ -354,12 +414,20 @@ hipError_t launch_one(const void* q, const void* k, const void* v, void* o, cons
 template <typename E, int D, int G, int MODE>
 hipError_t launch_waves(const void* q, const void* k, const void* v, void* o, const uint8_t* perm, const Problem& pb, int n_groups,
                         hipStream_t stream) {
-  if constexpr (D == 64) {
-    const int tiles = (pb.Nk + kTile - 1) / kTile, TB = MODE == kKeyFull || MODE == kKeyFused ? pb.Bc / kTile : 1;
-    if ((long long)pb.B * pb.H * ((pb.N + kTile - 1) / kTile) <= kComputeUnits && tiles > 8 && (tiles + TB - 1) / TB > 4)
-      return launch_one<E, D, G, MODE, 8>(q, k, v, o, perm, pb, n_groups, stream);
+  constexpr bool kFused = MODE == kQueryFused || MODE == kKeyFused;
+  const int tiles = (pb.Nk + kTile - 1) / kTile, TB = MODE == kKeyFull || MODE == kKeyFused ? pb.Bc / kTile : 1;
+  const bool wide = D == 64 && (long long)pb.B * pb.H * ((pb.N + kTile - 1) / kTile) <= kComputeUnits && tiles > 8 && (tiles + TB - 1) / TB > 4;
+  if constexpr (kFused && (D == 64 || MODE == kKeyFused)) {
+    if (float_by_pieces(pb)) {
+      if constexpr (D == 64) {
+        if (wide) return launch_one<E, D, G, MODE, 8, true>(q, k, v, o, perm, pb, n_groups, stream);
+      }
+      return launch_one<E, D, G, MODE, 4, true>(q, k, v, o, perm, pb, n_groups, stream);
+    }
+  } else if constexpr (D == 64) {
+    if (wide) return launch_one<E, D, G, MODE, 8, false>(q, k, v, o, perm, pb, n_groups, stream);
   }
-  return launch_one<E, D, G, MODE, 4>(q, k, v, o, perm, pb, n_groups, stream);
+  return launch_one<E, D, G, MODE, 4, false>(q, k, v, o, perm, pb, n_groups, stream);
 }
 
 template <typename E, int D>

@@ -1,6 +1,6 @@
 // Backward of the attention forward (exact and DistrAttention) for gfx950 in float arithmetic: the
 // reference-precision path, for float tensors (bf16 tensors take the matrix-core kernels of
-// attn_bf16_bwd.hip). Products on v_mfma_f32_32x32x2_f32 (float operands and sums), no atomics
+// attn_bf16_bwd.hip). Products on v_mfma_f32_32x32x2_f32, some of them by bf16 pieces (float operands and sums), no atomics
 // (results do not depend on the run), no scratch.
 //
 // The paper trains through the approximation (Sec. 4.3, 4.4) and gives no gradient. Computed
@@ -45,6 +45,8 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 typedef Quad<float> Q4;
 
+typedef __attribute__((address_space(3))) void lds_void;
+
 // A row of 32-row tile registers: piece u of a lane is row (u*64 + lane) / (D/4) of the tile, channels
 // 4*((u*64 + lane) % (D/4)) ..; rows past the end of the head read as zeros.
 template <int D>
@@ -76,6 +78,22 @@ struct Tile {
 #pragma unroll
       for (int e = 0; e < 4; ++e) lds[(u * 64 + lane) / (D / 4) * RS + to[e]] = y[e];
     }
+  }
+};
+
+  // The tile straight into LDS rows of D floats whose 16-byte pieces are exchanged by the row (what was read there has arrived).
+  template <int D, int G>
+struct TileToLds {
+  static constexpr int KU = Tile<D>::KU, BYTES = Tile<D>::BYTES, FLOATS = KU * 260;
+  // Float c of a row: one instruction leaves 256 floats in a row (four rows at D = 64), 16 bytes lie between two instructions'.
+  static __device__ int at(int row, int c) { return row / (256 / D) * 260 + row % (256 / D) * D + c; }
+  int voff;
+  __device__ explicit TileToLds(int lane) : voff(lane * 16) {}
+  __device__ void load(__amdgpu_buffer_rsrc_t rsrc, int tile, float* dst) const {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < KU; ++u)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + u * 260), 16, voff, tile * BYTES + u * 1024, 0, 0);
   }
 };
 
@@ -488,6 +506,318 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------
+// Groups of two and four channels at d = 64, from more than eight key tiles on (float_by_pieces): S^ and dP by bf16 pieces (V's lie
+// in LDS, K_f's in registers for a Q block), in the same order as the forward, whose lse P = exp(S^ - lse) rests on; dV and dK_f on
+// the float instruction, tile by tile. By pieces these need 48 registers more: 70 spilled, and dK/dV took 244 us; with one wave per SIMD and
+// none spilled 164. The dO tile comes straight into LDS as soon as its columns have been read (through registers, 32 spilled: 148).
+// Bound: issue and both matrix instructions' time. B1 H8 N2048 n_groups 32: 141 -> 126 us, 16 groups 128 -> 115.
+template <int D, int W, int G>
+__global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ dout,
+    const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dk, float* __restrict__ dv,
+    const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Br, int Tq, int causal, float scale) {
+  constexpr int NB = D / 32, RS = Tile<D>::RS;
+  constexpr int KRED = D / G, HS = KRED / 2, RQ = KRED + 4, NG = (KRED + 31) / 32, ROWS = 64 / KRED, QL = kTile / ROWS;
+  __shared__ __attribute__((aligned(16))) float q_lds[W][kTile * RQ];                  // Q_r tile of each wave: KRED sampled channels a row, in groups' order
+  __shared__ __attribute__((aligned(16))) float do_lds[W][TileToLds<D, G>::FLOATS];   // dO tile, at the end dV and dK
+  __shared__ __attribute__((aligned(16))) float k_lds[kTile * RS];                        // of the workgroup's keys
+  __shared__ __attribute__((aligned(16))) PieceRows<D> v_lds;
+  __shared__ __attribute__((aligned(16))) float stat_lds[W][2][kTile];   // lse, D_i
+  __shared__ uint32_t mark_lds[kTile];   // what is known of a key's row (kRowAgain ..)
+  __shared__ __attribute__((aligned(16))) uint8_t map_lds[W][4][D];   // of this Q block and the one before or after it: sorted order, the channels' groups
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lq = lane & 31, hh = lane >> 5;
+  // causal: the keys that most queries see come first; the tile index is the slow one, so that a
+  // kv head stays on one XCD when their number is a multiple of 8
+  const int n_bk = gridDim.x / ((Nk + kTile - 1) / kTile);
+  const int t = blockIdx.x / n_bk, bk = blockIdx.x % n_bk;
+  const int b = bk / Hkv, hk = bk % Hkv, rep = H / Hkv;
+  const int n0 = t * kTile, key = n0 + lq;
+  const int shift = Nk - N;   // causal: query i sees key n iff n <= i + shift
+
+  const int first = causal ? max(0, n0 - shift) / kTile : 0;   // first tile with a row that sees key n0
+  const int tiles = (N + kTile - 1) / kTile - first;           // per query head
+  const int n_it = tiles * rep;
+  auto head_of = [&](int it) { return (size_t)b * H + hk * rep + it / tiles; };
+  auto tile_of = [&](int it) { return first + it % tiles; };
+
+  uint8_t map_reg[D / 64];   // table row of an iteration's Q block
+  auto load_map = [&](int it) {
+    const uint8_t* pr = perm + (head_of(it) * Tq + tile_of(it) * kTile / Br) * D;
+#pragma unroll
+    for (int u = 0; u < D / 64; ++u) map_reg[u] = pr[u * 64 + lane];
+  };
+  float qr[QL];
+  float lse_reg, delta_reg;
+  // the table of iteration it's Q block into place `slot`; map_reg holds it
+  auto block_of = [&](int it) { return (int)(head_of(it) * Tq) + tile_of(it) * kTile / Br; };
+  auto store_map = [&](int slot) {
+    uint8_t* order = map_lds[w][2 * slot];
+    uint8_t* groups = map_lds[w][2 * slot + 1];
+    wave_order();
+#pragma unroll
+    for (int u = 0; u < D / 64; ++u) {
+      const int i = u * 64 + lane, c = map_reg[u] & (D - 1);
+      order[i] = (uint8_t)c;
+      groups[c] = (uint8_t)(i / G);
+    }
+    wave_order();
+  };
+  auto load_q = [&](int it, int slot) {
+    const size_t bh = head_of(it);
+    const int i0 = tile_of(it);
+    const __amdgpu_buffer_rsrc_t q_rsrc = head_rsrc(q + bh * N * D, (unsigned)N * D * 4);
+    const int c = map_lds[w][2 * slot][lane % KRED * G];   // the sampled channel of this lane's group
+#pragma unroll
+    for (int u = 0; u < QL; ++u)
+      qr[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(q_rsrc, lane / KRED * (D * 4) + c * 4, i0 * Tile<D>::BYTES + u * ROWS * (D * 4), 0));
+    const int row = min(i0 * kTile + lq, N - 1);
+    lse_reg = lse[bh * N + row];
+    delta_reg = delta[bh * N + row];
+  };
+  // straight into LDS, behind the last reads of the tile before
+  const TileToLds<D, G> to_lds(lane);
+  auto load_do = [&](int it) {
+    to_lds.load(head_rsrc(dout + head_of(it) * N * D, (unsigned)N * D * 4), tile_of(it), do_lds[w]);
+  };
+  auto do_at = [&](int row, int c) { return TileToLds<D, G>::at(row, c); };
+  // the waves deal out runs of tiles, so that a wave stays in a Q block
+  const int it_first = n_it * w / W, it_end = n_it * (w + 1) / W;
+  int slot = 0;
+  auto load_first = [&]() {
+    slot = 0;
+    if (it_first < it_end) {
+      load_map(it_first);
+      store_map(0);
+      load_q(it_first, 0);
+      load_do(it_first);
+      if (it_first + 1 < it_end) load_map(it_first + 1);
+    }
+  };
+  load_first();
+  if (tid < kTile) mark_lds[tid] = 0;
+
+  const __amdgpu_buffer_rsrc_t k_rsrc = head_rsrc(k + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
+  const __amdgpu_buffer_rsrc_t v_rsrc = head_rsrc(v + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
+  Tile<D> kt;
+  if (w == 0) {
+    kt.load(k_rsrc, t, lane);
+    kt.store(k_lds, lane);
+  }
+  for (int c = (W - 1 - w) * 8; c < D / 2; c += W * 8) {
+    const int at = hh * (D / 2) + c;
+    const f32x4 x = Q4::values(Q4::load(v_rsrc, (lq * D + at) * 4, n0 * (D * 4))), y = Q4::values(Q4::load(v_rsrc, (lq * D + at + 4) * 4, n0 * (D * 4)));
+    v_lds.store(lq, at, split(f32x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]}));
+  }
+  __syncthreads();
+  if (w == 0) {
+#pragma unroll
+    for (int u = 0; u < Tile<D>::KU; ++u)
+      if (outside_pieces(Q4::values(kt.x[u]))) atomicOr(&mark_lds[(u * 64 + lane) / (D / 4)], kRowAgain);
+  }
+  // The rows (keys) of the bit mask `rows`, S^ and dP by pieces or on the float instruction. By pieces, the rows to be taken again are
+  // returned.
+  auto pass = [&](auto pieces, uint32_t rows) -> uint32_t {
+    constexpr bool BY_PIECES = decltype(pieces)::value;
+    const Splitter splitter(lane);
+    f32x16 dkacc[NB], dvacc[NB];
+#pragma unroll
+    for (int mb = 0; mb < NB; ++mb) {
+      zero(dkacc[mb]);
+      zero(dvacc[mb]);
+    }
+    // K_f of the workgroup's keys and dK_f of the Q block the wave is in
+    Pieces kf[BY_PIECES ? HS / 8 : 1];
+    float kf32[BY_PIECES ? 1 : HS];
+    f32x16 dkf[NG];
+    auto fuse_keys = [&]() {
+      float sum[HS];
+#pragma unroll
+      for (int c = 0; c < D / 2; c += 8) {
+        const u32x2 e2 = *(const u32x2*)&map_lds[w][2 * slot][hh * (D / 2) + c];
+#pragma unroll
+        for (int e = 0; e < 8; e += G) {
+          float x = k_lds[lq * RS + ((e2[e >> 2] >> (8 * (e & 3))) & (D - 1))];
+#pragma unroll
+          for (int m = 1; m < G; ++m) x += k_lds[lq * RS + ((e2[(e + m) >> 2] >> (8 * ((e + m) & 3))) & (D - 1))];
+          sum[(c + e) / G] = x;
+        }
+      }
+      if constexpr (BY_PIECES) {
+        split_steps<HS>(splitter, sum, [&](int s, const Pieces& p) { kf[s] = p; });
+      } else {
+#pragma unroll
+        for (int s = 0; s < HS; ++s) kf32[s] = sum[s];
+      }
+#pragma unroll
+      for (int mb = 0; mb < NG; ++mb) zero(dkf[mb]);
+    };
+    // every channel receives its group's column (register i, lane half hh: groups NG * acc_row(i) .., channels NB * acc_row(i) ..)
+    auto unfuse = [&](int of) {
+      float* mine = &q_lds[w][lq * RQ];
+      wave_order();
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int mb = 0; mb < NG; ++mb)
+          if (KRED >= 32 || acc_row(i, 0) < KRED) mine[acc_row(i, hh) * NG + mb] = dkf[mb][i];
+      wave_order();
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4)
+#pragma unroll
+        for (int c = 0; c < 4 * NB; c += 4) {
+          const uint32_t g4 = *(const uint32_t*)&map_lds[w][2 * of + 1][NB * (8 * i4 + 4 * hh) + c];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dkacc[(c + e) % NB][4 * i4 + (c + e) / NB] += mine[(g4 >> (8 * e)) & (KRED - 1)];
+        }
+    };
+    int it = it_first, block = it < it_end ? block_of(it) : 0;
+    if (it < it_end) fuse_keys();
+
+    for (; it < it_end; ++it) {
+      const int i0 = tile_of(it) * kTile;
+      if (block_of(it) != block) {
+        unfuse(slot);
+        slot ^= 1;
+        block = block_of(it);
+        fuse_keys();
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the dO tile has landed
+      wave_order();   // the reads of the previous tile come first
+#pragma unroll
+      for (int u = 0; u < QL; ++u) q_lds[w][(u * ROWS + lane / KRED) * RQ + lane % KRED] = qr[u];
+      stat_lds[w][hh][lq] = hh ? delta_reg : lse_reg;
+      if (it + 1 < it_end) {
+        const bool same = block_of(it + 1) == block;
+        if (!same) store_map(slot ^ 1);
+        load_q(it + 1, same ? slot : slot ^ 1);
+        if (it + 2 < it_end) load_map(it + 2);
+      }
+      wave_order();
+      f32x16 s, dp;
+      {
+        float x[HS];
+#pragma unroll
+        for (int c = 0; c < HS; c += 4) {
+          const f32x4 y = *(const f32x4*)&q_lds[w][lq * RQ + hh * HS + c];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[c + e] = y[e];
+        }
+        if constexpr (BY_PIECES) {
+          PieceSum acc;
+          split_steps<HS>(splitter, x, [&](int s, const Pieces& p) { acc.template step<true>(p, kf[s]); });
+          s = acc.sum();
+        } else {
+          ChannelSum<HS> acc;
+#pragma unroll
+          for (int s = 0; s < HS; ++s) acc.step(s, x[s], kf32[s]);
+          s = acc.sum();
+        }
+      }
+      zero(dp);
+#pragma unroll
+      for (int c0 = 0; c0 < D / 2; c0 += 16) {
+        float x[16];
+#pragma unroll
+        for (int c = 0; c < 16; c += 4) {
+          const f32x4 y = *(const f32x4*)&do_lds[w][do_at(lq, hh * (D / 2) + c0 + c)];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[c + e] = y[e];
+        }
+        if constexpr (BY_PIECES) {
+          split_steps<16>(splitter, x, [&](int s, const Pieces& p) { dp = mfma(p, v_lds.load(lq, hh * (D / 2) + c0 + 8 * s), dp); });
+        } else {
+#pragma unroll
+          for (int c = 0; c < 16; c += 4) {
+            const f32x4 y = Q4::values(Q4::load(v_rsrc, (lq * D + hh * (D / 2) + c0 + c) * 4, n0 * (D * 4)));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dp = mfma(x[c + e], y[e], dp);
+          }
+        }
+      }
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        const f32x4 ls = *(const f32x4*)&stat_lds[w][0][8 * i4 + 4 * hh], dl = *(const f32x4*)&stat_lds[w][1][8 * i4 + 4 * hh];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int i = 4 * i4 + e;
+          s[i] = __builtin_amdgcn_exp2f(scaled_plus(s[i], scale, -ls[e]) * kLog2e);
+          dp[i] = dp[i] - dl[e];
+        }
+      }
+      if (i0 + kTile > N || (causal && i0 + shift < n0 + kTile - 1)) {   // rows past N; the causal diagonal
+        asm volatile("");   // (a branch: few tiles are masked)
+        const int from = causal ? key - shift : 0;   // first row that sees the key
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int row = i0 + acc_row(i, hh);
+          s[i] = (int)(row >= N) | (int)(row < from) ? 0.0f : s[i];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) dp[i] *= s[i];
+      {
+        f32x16 part[NB];
+#pragma unroll
+        for (int mb = 0; mb < NB; ++mb) zero(part[mb]);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const f32x2 y = *(const f32x2*)&do_lds[w][do_at(acc_row(i, hh), lq * NB)];
+          part[0] = mfma(y[0], s[i], part[0]);
+          part[1] = mfma(y[1], s[i], part[1]);
+        }
+        if (it + 1 < it_end) load_do(it + 1);
+#pragma unroll
+        for (int mb = 0; mb < NB; ++mb) dvacc[mb] += part[mb];
+      }
+      {
+        // lane m owns the groups NG*m .. (with 16 groups the upper lanes repeat the lower)
+        f32x16 part[NG];
+#pragma unroll
+        for (int mb = 0; mb < NG; ++mb) zero(part[mb]);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+          for (int mb = 0; mb < NG; ++mb) part[mb] = mfma(q_lds[w][acc_row(i, hh) * RQ + lq * NG % KRED + mb], dp[i], part[mb]);
+#pragma unroll
+        for (int mb = 0; mb < NG; ++mb) dkf[mb] += part[mb];
+      }
+    }
+    if (it_first < it_end) unfuse(slot);
+
+    // the waves' sums meet, dV, then dK, by way of the dO tiles
+#pragma unroll
+    for (int of = 0; of < 2; ++of) {
+      if (of) __syncthreads();
+      else wave_order();
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        *(f32x2*)&do_lds[w][do_at(lq, acc_row(i, hh) * 2)] = of ? f32x2{dkacc[0][i], dkacc[1][i]} : f32x2{dvacc[0][i], dvacc[1][i]};
+      __syncthreads();
+      for (int i = tid; i < kTile * D / 4; i += W * 64) {
+        const int row = i / (D / 4), c = i % (D / 4) * 4;
+        if (n0 + row < Nk && rows >> row & 1) {
+          f32x4 x = *(const f32x4*)&do_lds[0][do_at(row, c)];
+#pragma unroll
+          for (int j = 1; j < W; ++j) x += *(const f32x4*)&do_lds[j][do_at(row, c)];
+          if constexpr (BY_PIECES) atomicOr(&mark_lds[row], row_mark(x));
+          *(f32x4*)((of ? dk : dv) + ((size_t)bk * Nk + n0 + row) * D + c) = of ? x * scale : x;
+        }
+      }
+    }
+    if constexpr (!BY_PIECES) return 0;
+    __syncthreads();
+    return rows_again(mark_lds[lq]);
+  };
+  const uint32_t again = pass(std::true_type(), ~0u);
+  if (again == 0) return;
+  load_first();
+  pass(std::false_type(), again);
+}
+
+// ------------------------------------------------------------------------------------------------
 // G: channels per group where the score and dQ_r products contract over the groups (2, 4); 1: over the
 // channels, with Q~.
 template <int D, int G, int W>
@@ -600,6 +930,7 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f(scaled_plus(s[i], scale, -lse_row) * kLog2e);
     if (n0 + kTile > Nk || (causal && n0 + kTile - 1 > r0 + shift)) {
+      asm volatile("");   // (a branch: few tiles are masked)
 #pragma unroll
       for (int i = 0; i < 16; ++i)
         if (n0 + acc_row(i, hh) > lim) s[i] = 0.0f;
@@ -671,6 +1002,241 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_kernel(
   }
 }
 
+// The same by bf16 pieces, all three products (groups of two and four at d = 64, as bwd_dkv_pieces_kernel; Q_r's and dO's pieces lie in LDS).
+// 48 products and 20 for the splitting a tile instead of 64 of twice the time. B1 H8 N2048 n_groups 32: 90 -> 75 us, 16 groups 84 -> 73.
+template <int D, int G, int W>
+__global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ o,
+    const float* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ dq, const uint8_t* __restrict__ perm,
+    int H, int Hkv, int N, int Nk, int Br, int Tq, int causal, float scale) {
+  constexpr int RS = Tile<D>::RS;
+  constexpr int KRED = D / G, HS = KRED / 2;
+  constexpr int NG = (KRED + 31) / 32;   // 32-row blocks of the dQ_r accumulator
+  __shared__ __attribute__((aligned(16))) float k_lds[W][kTile * RS];   // V, then K tile of each wave; at the end its dQ_r
+  __shared__ __attribute__((aligned(16))) PieceRows<KRED> q_lds;
+  __shared__ __attribute__((aligned(16))) PieceRows<D> do_lds;
+  __shared__ __attribute__((aligned(16))) float sum_lds[kTile * RS];
+  __shared__ uint32_t mark_lds[kTile];   // what is known of a row (kRowAgain ..)
+  __shared__ uint8_t order_lds[D];   // sorted order of the block's channels
+  __shared__ uint8_t map_lds[D];     // a channel's position in it
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lq = lane & 31, hh = lane >> 5;
+  const int Tw = (N + kTile - 1) / kTile;
+  const int n_bh = gridDim.x / Tw;
+  const int t = causal ? Tw - 1 - (int)blockIdx.x / n_bh : (int)blockIdx.x / n_bh;   // longest first
+  const int bh = blockIdx.x % n_bh;
+  const int b = bh / H, hk = bh % H / (H / Hkv);
+  const int r0 = t * kTile, q_abs = r0 + lq;
+  const int shift = Nk - N;
+
+  const size_t head = (size_t)bh * N * D;
+  const __amdgpu_buffer_rsrc_t k_rsrc = head_rsrc(k + (size_t)(b * Hkv + hk) * Nk * D, (unsigned)Nk * D * 4);
+  const __amdgpu_buffer_rsrc_t v_rsrc = head_rsrc(v + (size_t)(b * Hkv + hk) * Nk * D, (unsigned)Nk * D * 4);
+  const int n_end = causal ? min(Nk, r0 + kTile + shift) : Nk;
+  const int n_tiles = (n_end + kTile - 1) / kTile;
+  const int lim = causal ? min(q_abs + shift, Nk - 1) : Nk - 1;   // last key this row sees
+
+  Tile<D> kt, vt;
+  auto load_first = [&]() {
+    if (w < n_tiles) {
+      kt.load(k_rsrc, w, lane);
+      vt.load(v_rsrc, w, lane);
+    }
+  };
+  load_first();
+  if (tid < kTile) mark_lds[tid] = 0;
+  // Q, dO and O rows pass through LDS (one tile per wave 0, 1, 2)
+  {
+    const float* src = w == 0 ? q : w == 1 ? dout : o;
+    Tile<D> x;
+    if (w < 3) {
+      x.load(head_rsrc(src + head, (unsigned)N * D * 4), t, lane);
+      x.store(k_lds[w], lane);
+    }
+  }
+  {
+    // D is a power of two: an out-of-range entry of a caller's table cannot index past a row
+    const uint8_t* pr = perm + ((size_t)bh * Tq + r0 / Br) * D;
+    for (int i = tid; i < D; i += W * 64) {
+      order_lds[i] = pr[i] & (D - 1);
+      map_lds[pr[i] & (D - 1)] = (uint8_t)i;
+    }
+  }
+  __syncthreads();
+  float dl = 0.0f;
+  int kdst[4];
+#pragma unroll
+  for (int c = 0; c < D / 2; ++c) dl = __builtin_fmaf(k_lds[1][lq * RS + hh * (D / 2) + c], k_lds[2][lq * RS + hh * (D / 2) + c], dl);
+  for (int s = w * 8; s < HS; s += W * 8) {
+    f32x8 x;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      x[e] = k_lds[0][lq * RS + order_lds[(hh * HS + s + e) * G]];
+    q_lds.store(lq, hh * HS + s, split(x));
+    if (outside_pieces(x.lo) | outside_pieces(x.hi)) atomicOr(&mark_lds[lq], kRowAgain);
+  }
+  for (int s = w * 8; s < D / 2; s += W * 8) {
+    f32x8 x;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = k_lds[1][lq * RS + hh * (D / 2) + s + e];
+    do_lds.store(lq, hh * (D / 2) + s, split(x));
+  }
+  dl = half_swap_sum(dl);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) kdst[e] = map_lds[lane % (D / 4) * 4 + e] & (D - 1);
+  const float lse_row = lse[(size_t)bh * N + min(q_abs, N - 1)];
+  __syncthreads();   // the staged rows have been read
+
+  // The rows of the bit mask `rows`, products by pieces or on the float instruction. By pieces, the rows to be taken again are returned.
+  auto pass = [&](auto pieces, uint32_t rows) -> uint32_t {
+    constexpr bool BY_PIECES = decltype(pieces)::value;
+    const Splitter splitter(lane);
+    float qop[BY_PIECES ? 1 : HS], doop[BY_PIECES ? 1 : D / 2];
+    if constexpr (!BY_PIECES) {
+      const __amdgpu_buffer_rsrc_t q_rsrc = head_rsrc(q + head, (unsigned)N * D * 4), do_rsrc = head_rsrc(dout + head, (unsigned)N * D * 4);
+#pragma unroll
+      for (int s = 0; s < HS; ++s)
+        qop[s] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(q_rsrc, lq * (D * 4) + order_lds[(hh * HS + s) * G] * 4, r0 * (D * 4), 0));
+#pragma unroll
+      for (int c = 0; c < D / 2; ++c)
+        doop[c] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(do_rsrc, lq * (D * 4) + (hh * (D / 2) + c) * 4, r0 * (D * 4), 0));
+    }
+    f32x16 dqacc[NG];
+#pragma unroll
+    for (int mb = 0; mb < NG; ++mb) zero(dqacc[mb]);
+    for (int tile = w; tile < n_tiles; tile += W) {
+      wave_order();   // the reads of the previous tile come first
+      vt.store(k_lds[w], lane);
+      wave_order();
+      float x[D / 2];
+#pragma unroll
+      for (int c = 0; c < D / 2; c += 4) {
+        const f32x4 y = *(const f32x4*)&k_lds[w][lq * RS + hh * (D / 2) + c];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[c + e] = y[e];
+      }
+      wave_order();
+      kt.scatter(k_lds[w], lane, kdst);
+      if (tile + W < n_tiles) {
+        kt.load(k_rsrc, tile + W, lane);
+        vt.load(v_rsrc, tile + W, lane);
+      }
+      wave_order();
+      f32x16 dp;
+      if constexpr (BY_PIECES) {
+        zero(dp);
+        split_steps<D / 2>(splitter, x, [&](int s, const Pieces& p) { dp = mfma(p, do_lds.load(lq, hh * (D / 2) + 8 * s), dp); });
+      } else {
+        OneChain acc;
+#pragma unroll
+        for (int c = 0; c < D / 2; ++c) acc.step(c, x[c], doop[c]);
+        dp = acc.sum();
+      }
+      float y[HS];
+#pragma unroll
+      for (int c = 0; c < D / 2; c += 4) {
+        const f32x4 x = *(const f32x4*)&k_lds[w][lq * RS + hh * (D / 2) + c];
+        if constexpr (G == 2) {
+          y[c / 2] = x[0] + x[1];
+          y[c / 2 + 1] = x[2] + x[3];
+        } else {
+          y[c / 4] = ((x[0] + x[1]) + x[2]) + x[3];
+        }
+      }
+      f32x16 s;
+      if constexpr (BY_PIECES) {
+        PieceSum acc;
+        split_steps<HS>(splitter, y, [&](int s, const Pieces& p) { acc.step(p, q_lds.load(lq, hh * HS + 8 * s)); });
+        s = acc.sum();
+      } else {
+        ChannelSum<HS> acc;
+#pragma unroll
+        for (int c = 0; c < HS; ++c) acc.step(c, y[c], qop[c]);
+        s = acc.sum();
+      }
+      const int n0 = tile * kTile;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f(scaled_plus(s[i], scale, -lse_row) * kLog2e);
+      if (n0 + kTile > Nk || (causal && n0 + kTile - 1 > r0 + shift)) {
+        asm volatile("");   // (a branch: few tiles are masked)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (n0 + acc_row(i, hh) > lim) s[i] = 0.0f;
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] *= dp[i] - dl;
+      // lane m owns the columns NG*m .. (of 32 * NG slots; with 16 groups the upper lanes repeat the lower)
+      f32x16 kc[NG];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float* src = &k_lds[w][acc_row(i, hh) * RS + (lq * NG % KRED) * G];
+#pragma unroll
+        for (int mb = 0; mb < NG; ++mb) {
+          if constexpr (G == 2) {
+            const f32x2 y = *(const f32x2*)(src + mb * G);
+            kc[mb][i] = y[0] + y[1];
+          } else {
+            const f32x4 y = *(const f32x4*)(src + mb * G);
+            kc[mb][i] = ((y[0] + y[1]) + y[2]) + y[3];
+          }
+        }
+      }
+      if constexpr (BY_PIECES) {
+        Pieces s0, s1, k0, k1;
+        splitter(s, s0, s1);
+#pragma unroll
+        for (int mb = 0; mb < NG; ++mb) {
+          splitter(kc[mb], k0, k1);
+          dqacc[mb] = mfma(k0, s0, dqacc[mb]);
+          dqacc[mb] = mfma(k1, s1, dqacc[mb]);
+        }
+      } else {
+#pragma unroll
+        for (int mb = 0; mb < NG; ++mb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) dqacc[mb] = mfma(kc[mb][i], s[i], dqacc[mb]);
+      }
+    }
+
+    wave_order();
+    // dQ_r of the wave, then summed over the waves
+    float* mine = &k_lds[w][lq * RS];
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+      for (int mb = 0; mb < NG; ++mb)
+        if (KRED >= 32 || acc_row(i, hh) < KRED) mine[acc_row(i, hh) * NG + mb] = dqacc[mb][i];
+    __syncthreads();
+    for (int i = tid; i < kTile * KRED / 4; i += W * 64) {
+      const int row = i / (KRED / 4), c = i % (KRED / 4) * 4;
+      f32x4 x = *(const f32x4*)&k_lds[0][row * RS + c];
+#pragma unroll
+      for (int j = 1; j < W; ++j) x += *(const f32x4*)&k_lds[j][row * RS + c];
+      *(f32x4*)&sum_lds[row * RS + c] = x;
+      if (BY_PIECES && r0 + row < N) atomicOr(&mark_lds[row], row_mark(x));
+    }
+    __syncthreads();
+    for (int i = tid; i < kTile * D / 4; i += W * 64) {
+      const int row = i / (D / 4), c = i % (D / 4) * 4;
+      if (r0 + row >= N || !(rows >> row & 1)) continue;
+      f32x4 y;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int pos = map_lds[c + e] & (D - 1);
+        y[e] = pos % G == 0 ? scale * sum_lds[row * RS + pos / G] : 0.0f;
+      }
+      *(f32x4*)(dq + head + (size_t)(r0 + row) * D + c) = y;
+    }
+    return BY_PIECES ? rows_again(mark_lds[lq]) : 0;
+  };
+  const uint32_t again = pass(std::true_type(), ~0u);
+  if (again == 0) return;
+  load_first();
+  pass(std::false_type(), again);
+}
+
 template <int D>
 hipError_t launch_d(const float* q, const float* k, const float* v, const float* o, const float* dout, const float* lse,
                     float* dq, float* dk, float* dv, const uint8_t* perm, const Problem& pb, int distr, hipStream_t stream) {
@@ -689,12 +1255,21 @@ hipError_t launch_d(const float* q, const float* k, const float* v, const float*
                      table, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, n_groups, pb.causal, pb.scale)
   const bool eight = D == 64 && (long long)(pb.H / pb.Hkv) * ((pb.N + kTile - 1) / kTile) >= 8;
   const int G = D / n_groups;
+  const bool pieces = distr && float_by_pieces(pb);
   if constexpr (D == 64) {
-    if (eight && G == 2) DA_DKV(8, 2);
+#define DA_DKVP(W, GG)                                                                                                      \
+  hipLaunchKernelGGL((bwd_dkv_pieces_kernel<D, W, GG>), dim3((unsigned)k_units), dim3(W * 64), 0, stream, q, k, v, dout, lse, delta, dk, dv, \
+                     table, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, pb.causal, pb.scale)
+    if (pieces && eight && G == 2) DA_DKVP(8, 2);
+    else if (pieces && eight) DA_DKVP(8, 4);
+    else if (pieces && G == 2) DA_DKVP(4, 2);
+    else if (pieces) DA_DKVP(4, 4);
+    else if (eight && G == 2) DA_DKV(8, 2);
     else if (eight && G == 4) DA_DKV(8, 4);
     else if (eight) DA_DKV(8, 1);
+#undef DA_DKVP
   }
-  if (eight) {
+  if (pieces || eight) {
   } else if (G == 2) {
     DA_DKV(4, 2);
   } else if (G == 4) {
@@ -704,14 +1279,25 @@ hipError_t launch_d(const float* q, const float* k, const float* v, const float*
   }
 #undef DA_DKV
   // dQ: eight waves as in the forward (launch_waves in attn_f32.hip)
+  const bool wide = D == 64 && q_units <= kComputeUnits && (pb.Nk + kTile - 1) / kTile > 8;
+  if constexpr (D == 64) {
+    if (pieces) {
+#define DA_DQ(GG, W)                                                                                                       \
+  hipLaunchKernelGGL((bwd_dq_pieces_kernel<D, GG, W>), dim3((unsigned)q_units), dim3(W * 64), 0, stream, q, k, v, o, dout, lse, dq, \
+                     table, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, pb.causal, pb.scale)
+      if (wide && G == 2) DA_DQ(2, 8);
+      else if (wide) DA_DQ(4, 8);
+      else if (G == 2) DA_DQ(2, 4);
+      else DA_DQ(4, 4);
+#undef DA_DQ
+      return hipGetLastError();
+    }
+  }
 #define DA_DQ(GG, W)                                                                                                       \
   hipLaunchKernelGGL((bwd_dq_kernel<D, GG, W>), dim3((unsigned)q_units), dim3(W * 64), 0, stream, q, k, v, o, dout, lse, dq, \
                      table, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, n_groups, pb.causal, pb.scale)
-  const bool wide = D == 64 && q_units <= kComputeUnits && (pb.Nk + kTile - 1) / kTile > 8;
   if constexpr (D == 64) {
-    if (wide && G == 2) DA_DQ(2, 8);
-    else if (wide && G == 4) DA_DQ(4, 8);
-    else if (wide) DA_DQ(1, 8);
+    if (wide) DA_DQ(1, 8);   // (groups of two and four take the pieces where it is wide)
   }
   if (wide) {
   } else if (G == 2) {

@@ -55,6 +55,166 @@ struct ChannelSum {
   }
 };
 
+// Eight floats as operands of v_mfma_f32_32x32x16_bf16: hi + mid + lo with eight significand bits each (rounded to
+// nearest, so that mid and lo are at most 2^-9 and 2^-17 of the float), together the float itself.
+struct Pieces {
+  bf16x8 hi, mid, lo;
+};
+typedef __attribute__((ext_vector_type(8))) float f32x8;
+__device__ inline bf16x8 round8(f32x8 x) { return __builtin_convertvector(x, bf16x8); }
+__device__ inline f32x8 rest8(f32x8 x, bf16x8 y) {
+  const u32x4 b = __builtin_bit_cast(u32x4, y);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    x[2 * j] -= __builtin_bit_cast(float, b[j] << 16);
+    x[2 * j + 1] -= __builtin_bit_cast(float, b[j] & 0xffff0000u);
+  }
+  return x;
+}
+__device__ inline Pieces split(f32x8 x) {
+  Pieces p;
+  p.hi = round8(x);
+  x = rest8(x, p.hi);
+  p.mid = round8(x);
+  p.lo = round8(rest8(x, p.mid));
+  return p;
+}
+__device__ inline f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+// The same for sixteen floats a lane as two operands, the subtractions taken by the matrix instruction: the floats are
+// an accumulator, and what is subtracted, the operand of steps t = 0 and 1, contributes -1 times its own place (at(8 t + j)). 24
+// instead of 88 vector instructions, for 4 products.
+struct Splitter {
+  bf16x8 minus[2];
+  __device__ explicit Splitter(int lane) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) minus[t][j] = (bf16)((lane & 31) == acc_row(8 * t + j, lane >> 5) ? -1.0f : 0.0f);
+  }
+  __device__ void operator()(f32x16 x, Pieces& p0, Pieces& p1) const {
+    p0.hi = round8(x.lo);
+    p1.hi = round8(x.hi);
+    x = mfma(minus[1], p1.hi, mfma(minus[0], p0.hi, x));
+    p0.mid = round8(x.lo);
+    p1.mid = round8(x.hi);
+    x = mfma(minus[1], p1.mid, mfma(minus[0], p0.mid, x));
+    p0.lo = round8(x.lo);
+    p1.lo = round8(x.hi);
+  }
+};
+// c += a b without what mid lo, lo mid and lo lo add (2^-25 of a b at most), the small products first.
+__device__ inline f32x16 mfma_rest(const Pieces& a, const Pieces& b, f32x16 c) {
+  c = mfma(a.lo, b.hi, c);
+  c = mfma(a.hi, b.lo, c);
+  c = mfma(a.mid, b.mid, c);
+  c = mfma(a.mid, b.hi, c);
+  return mfma(a.hi, b.mid, c);
+}
+__device__ inline f32x16 mfma(const Pieces& a, const Pieces& b, f32x16 c) { return mfma(a.hi, b.hi, mfma_rest(a, b, c)); }
+
+// HS floats of a lane's half row as operands, split on the way: step(s, pieces)
+template <int HS, bool BY_MFMA = true, typename STEP>
+__device__ inline void split_steps(const Splitter& splitter, const float (&x)[HS], STEP step) {
+  if constexpr (HS == 8 || !BY_MFMA) {
+#pragma unroll
+    for (int s = 0; s < HS; s += 8) {
+      f32x8 y;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = x[s + e];
+      step(s / 8, split(y));
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < HS; s += 16) {
+      f32x16 y;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) y[e] = x[s + e];
+      Pieces p0, p1;
+      splitter(y, p0, p1);
+      step(s / 8, p0);
+      step(s / 8 + 1, p1);
+    }
+  }
+}
+
+// A sum over the channels, 16 a step, the products of the leading pieces and the others in a chain each.
+struct PieceSum {
+  f32x16 lead, rest;
+  __device__ PieceSum() {
+    zero(lead);
+    zero(rest);
+  }
+  // b_first: the products in the order that step(b, a) takes them in
+  template <bool b_first = false>
+  __device__ void step(const Pieces& a, const Pieces& b) {
+    if constexpr (b_first) {
+      rest = mfma(a.hi, b.lo, rest);
+      rest = mfma(a.lo, b.hi, rest);
+      rest = mfma(a.mid, b.mid, rest);
+      rest = mfma(a.hi, b.mid, rest);
+      rest = mfma(a.mid, b.hi, rest);
+    } else {
+      rest = mfma_rest(a, b, rest);
+    }
+    lead = mfma(a.hi, b.hi, lead);
+  }
+  __device__ f32x16 sum() const { return lead + rest; }
+};
+
+// Products by pieces: groups of two and four channels at d = 64, and the mirrored form (which has no backward to agree with on the
+// scores' last bits) at any d, from more than eight key tiles on. us of a call, float products | pieces, H1 d64 groups of two:
+//   forward  N256 8.3 | 8.7, N320 10.0 | 9.1, N512 11.9 | 10.7, N1024 19.2 | 15.9; mirrored 8.7 | 9.2, 11.6 | 10.8, 12.8 | 11.9, 21.0 | 18.0
+//   backward N128 18.3 | 20.0, N256 25.9 | 26.5, N320 34.7 | 31.8, N512 38.6 | 34.5, N1024 60.3 | 52.4
+inline bool float_by_pieces(const Problem& pb) {
+  const int G = pb.d / pb.n_groups;
+  return (G == 2 || G == 4) && (pb.d == 64 || pb.side == 1) && pb.Nk > 8 * kTile;
+}
+
+// What pieces do not hold as floats do: infinities and NaN (a product with them makes every sum of its row NaN), operands so
+// small that their last piece is lost, and products of such with very large ones. A workgroup looks at the results of its 32 rows
+// and takes those again with float products that are not finite, or not zero and nowhere as large as 2^-60, or whose query row
+// holds something outside 2^-64 .. 2^64: what remains has lost less than 2^-20 of its own rounding.
+constexpr uint32_t kRowAgain = 1, kRowNonzero = 2, kRowLarge = 4;
+__device__ inline uint32_t row_mark(f32x4 x) {
+  uint32_t mark = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float a = __builtin_fabsf(x[e]);
+    mark |= (a < INFINITY ? 0u : kRowAgain) | (a != 0.0f ? kRowNonzero : 0u) | (a >= 0x1p-60f ? kRowLarge : 0u);
+  }
+  return mark;
+}
+// Something of 2^64 and more, or NaN, or below 2^-64 but not zero. (Comparisons without a branch.)
+__device__ inline bool outside_pieces(f32x4 x) {
+  uint32_t out = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t a = __builtin_bit_cast(uint32_t, (float)x[e]) & 0x7fffffffu;
+    out |= (uint32_t)(a - 0x1f800000u >= 0x40000000u) & (uint32_t)(a != 0);   // the bits of 2^-64; those of 2^64 less these
+  }
+  return out != 0;
+}
+// mark: of the lane's row; the same 32 rows in both halves of the wave
+__device__ inline uint32_t rows_again(uint32_t mark) {
+  const uint64_t rows = __builtin_amdgcn_ballot_w64((mark & kRowAgain) != 0 || (mark & (kRowNonzero | kRowLarge)) == kRowNonzero);
+  return (uint32_t)rows | (uint32_t)(rows >> 32);
+}
+
+// Pieces of 32 rows of C floats in LDS; rows 16 bytes apart in the banks, a lane's operand is one read per piece.
+template <int C>
+struct PieceRows {
+  static constexpr int RS = C + 8;
+  bf16 x[3][kTile * RS];
+  __device__ void store(int row, int c, const Pieces& p) {
+    *(bf16x8*)&x[0][row * RS + c] = p.hi;
+    *(bf16x8*)&x[1][row * RS + c] = p.mid;
+    *(bf16x8*)&x[2][row * RS + c] = p.lo;
+  }
+  __device__ Pieces load(int row, int c) const {
+    return {*(const bf16x8*)&x[0][row * RS + c], *(const bf16x8*)&x[1][row * RS + c], *(const bf16x8*)&x[2][row * RS + c]};
+  }
+};
+
 // x * scale + y with the product rounded: a score that is its row's maximum, whose lse is the rounded maximum plus
 // ln(sum), then gives exactly -ln(sum) in the backward pass, however large it is.
 __device__ inline float scaled_plus(float x, float scale, float y) {

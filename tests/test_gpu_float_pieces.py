@@ -1,0 +1,129 @@
+"""Float products taken as bf16 pieces: what pieces do not hold as floats do (infinities, NaN, magnitudes far from one) comes out as
+float products give it, row by row, and every other row is what it is without it. Groups of two and four channels and the mirrored
+form; sizes around the tiles of 32 rows, with four and eight waves per workgroup, and Q blocks that a wave's run of tiles enters and leaves."""
+import math
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# H, Hkv, N, Nk, d, G, causal, side
+FORWARD = [(2, 1, 33, 65, 64, 2, True, 0), (8, 2, 200, 300, 64, 2, True, 0), (1, 1, 300, 520, 64, 4, True, 0), (3, 3, 1, 31, 64, 4, True, 0),
+           (2, 1, 100, 300, 64, 2, True, 1), (2, 2, 97, 129, 128, 4, True, 1), (1, 1, 64, 800, 64, 2, True, 1)]
+BACKWARD = [(2, 1, 33, 65, 64, 2, True, 0), (8, 2, 300, 300, 64, 2, True, 0), (2, 2, 300, 520, 64, 4, True, 0), (1, 1, 257, 257, 64, 2, True, 0)]
+
+
+def _inputs(case):
+    import torch
+    H, Hkv, N, Nk, d, G, causal, side = case
+    gen = torch.Generator(device="cuda").manual_seed(21)
+    # channels alike on the sampled side, so that the grouped scores are the exact ones whatever the grouping
+    q = torch.randn((1, H, N, 1 if side == 0 else d), generator=gen, device="cuda").abs().expand(1, H, N, d) + 0.5
+    k = torch.randn((1, Hkv, Nk, d if side == 0 else 1), generator=gen, device="cuda").expand(1, Hkv, Nk, d)
+    v = torch.randn((1, Hkv, Nk, d), generator=gen, device="cuda")
+    return q.contiguous(), k.contiguous(), v
+
+
+def _params(da, case, q, k, v, **more):
+    H, Hkv, N, Nk, d, G, causal, side = case
+    return da.make_params(q, k, v, Br=64, Bc=32, n_groups=d // G, causal=causal, side=side, softmax_scale=0.02, **more)
+
+
+def _forward(case, q, k, v):
+    import torch
+
+    import paper_2507_17245_amd as da
+    print(f"case {case}", flush=True)
+    o, lse = torch.zeros_like(q), torch.zeros(q.shape[:3], device="cuda")
+    da.distr_attn_fwd_ex(q, k, v, o, _params(da, case, q, k, v, **({} if case[7] else {"lse_out": lse})))
+    return o, lse
+
+
+def _plain(case, q, k, v):
+    import torch
+    H, Hkv, N, Nk, d, G, causal, side = case
+    k, v = (x.double().repeat_interleave(H // Hkv, dim=1) for x in (k, v))
+    s = torch.matmul(q.double(), k.transpose(2, 3).contiguous()) * 0.02
+    hidden = torch.arange(Nk, device="cuda")[None, :] > torch.arange(N, device="cuda")[:, None] + Nk - N
+    s = s.masked_fill(hidden, -math.inf)
+    return torch.matmul(torch.softmax(s, dim=-1), v), torch.logsumexp(s, dim=-1), hidden
+
+
+@pytest.mark.parametrize("case", FORWARD, ids=str)
+def test_infinite_keys(case):
+    import torch
+    q, k, v = _inputs(case)
+    Nk, at = k.shape[2], k.shape[2] - 1 - q.shape[2] // 2
+    k[:, :, :Nk // 8] = -math.inf
+    low, low_lse = _forward(case, q, k, v)
+    want, want_lse, hidden = _plain(case, q, k, v)
+    assert torch.isfinite(want).all()
+    assert (low - want).abs().max() <= 1e-4 and (case[7] or (low_lse - want_lse).abs().max() <= 1e-4)
+    k[:, :, at] = math.inf        # a row that sees it is NaN, every other row the same to the bit
+    o, lse = _forward(case, q, k, v)
+    assert torch.isnan(o[:, :, ~hidden[:, at]]).all()
+    assert torch.equal(o[:, :, hidden[:, at]], low[:, :, hidden[:, at]])
+    assert case[7] or torch.equal(lse[:, :, hidden[:, at]], low_lse[:, :, hidden[:, at]])
+
+
+@pytest.mark.parametrize("case", FORWARD, ids=str)
+@pytest.mark.parametrize("by", [(1.0, 1.0, 2.0 ** -100), (1.0, 1.0, 2.0 ** 100), (2.0 ** 70, 2.0 ** -70, 1.0), (2.0 ** -110, 2.0 ** 110, 1.0)])
+def test_magnitudes(case, by):
+    """Bound: four times what the same inputs give at magnitude one (3e-7 at most)."""
+    q, k, v = _inputs(case)
+    o, lse = _forward(case, q * by[0], k * by[1], v * by[2])
+    want = _plain(case, q, k, v)[0] * by[2]
+    assert ((o.double() - want) / by[2]).norm() <= 1.2e-6 * (want / by[2]).norm()
+
+
+def _backward(case, q, k, v, dout):
+    import torch
+
+    import paper_2507_17245_amd as da
+    o, lse = _forward(case, q, k, v)
+    grads = [torch.zeros_like(x) for x in (q, k, v)]
+    da.distr_attn_bwd_ex(q, k, v, o, dout, lse, *grads, _params(da, case, q, k, v))
+    return grads
+
+
+@pytest.mark.parametrize("case", BACKWARD, ids=str)
+@pytest.mark.parametrize("value", [math.inf, math.nan])
+def test_gradients_that_are_not_finite(case, value):
+    """One element of dout: its row of dq and the keys that the row sees are not finite; every other row of dq, and the keys of tiles
+    that no row of its tile sees, are the same to the bit."""
+    import torch
+    q, k, v = _inputs(case)
+    dout = torch.randn(q.shape, generator=torch.Generator(device="cuda").manual_seed(22), device="cuda")
+    clean = _backward(case, q, k, v, dout)
+    row = q.shape[2] // 3
+    dout[:, :, row, 9] = value
+    dq, dk, dv = _backward(case, q, k, v, dout)
+    seen = k.shape[2] - q.shape[2] + row + 1
+    sampled = clean[0][:, :, row] != 0
+    assert not torch.isfinite(dq[:, :, row][sampled]).any()
+    dq[:, :, row] = clean[0][:, :, row]
+    assert torch.equal(dq, clean[0])
+    assert not torch.isfinite(dk[:, :, :seen]).any() and not torch.isfinite(dv[:, :, :seen, 9]).any()
+    far = -(-(k.shape[2] - q.shape[2] + (row | 31) + 1) // 32) * 32
+    assert torch.equal(dk[:, :, far:], clean[1][:, :, far:]) and torch.equal(dv[:, :, far:], clean[2][:, :, far:])
+
+
+@pytest.mark.parametrize("case", BACKWARD, ids=str)
+@pytest.mark.parametrize("size", [2.0 ** -100, 2.0 ** 60])
+def test_gradients_far_from_one(case, size):
+    """dout times a power of two: the gradients' distance from 64 bits stays what it is at one (bound: four times that, 1e-6)."""
+    import torch
+    H, Hkv, N, Nk, d, G, causal, side = case
+    q, k, v = _inputs(case)
+    dout = torch.randn(q.shape, generator=torch.Generator(device="cuda").manual_seed(23), device="cuda")
+    dq, dk, dv = _backward(case, q, k, v, dout * size)
+    o, lse, hidden = _plain(case, q, k, v)
+    kk, vv = (x.double().repeat_interleave(H // Hkv, dim=1) for x in (k, v))
+    p = torch.exp((torch.matmul(q.double(), kk.transpose(2, 3).contiguous()) * 0.02).masked_fill(hidden, -math.inf) - lse[..., None])
+    g = dout.double()
+    ds = p * (torch.matmul(g, vv.transpose(2, 3).contiguous()) - (g * o).sum(-1, keepdim=True)) * 0.02
+    # dq's sampled channels hold the sum over their groups: summed over all channels it is the exact gradient's sum
+    for got, want in ((dq.double().sum(-1), torch.matmul(ds, kk).sum(-1)),
+                      (dk.double(), torch.matmul(ds.transpose(2, 3).contiguous(), q.double()).view(1, Hkv, -1, Nk, d).sum(2)),
+                      (dv.double(), torch.matmul(p.transpose(2, 3).contiguous(), g).view(1, Hkv, -1, Nk, d).sum(2))):
+        assert (got / size - want).norm() <= 4e-6 * want.norm()
