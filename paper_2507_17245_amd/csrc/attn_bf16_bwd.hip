@@ -532,7 +532,7 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) asm volatile("" : "+a"(dkacc[cb]), "+a"(dvacc[cb]));
 #pragma unroll
-      for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(kop[s]), "+v"(vop[s]));
+      for (int s = 0; s < KS; ++s) asm volatile("" : "+a"(kop[s]), "+a"(vop[s]));
     }
     wait_loads();
     __syncthreads();   // this tile has landed; the other buffers' readers are done
@@ -540,14 +540,14 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
       if constexpr (par) ctx.issue(it + 1, q_lds0, do_lds0, lse_lds0, dl_lds0);
       else ctx.issue(it + 1, q_lds1, do_lds1, lse_lds1, dl_lds1);
     }
-    // Operands are read a phase ahead of the MFMAs that take them; the vector work of a 32-row
-    // block sits next to the matrix work of the other one.
-    bf16x8 ar[KS], at[CB][2], pop0[2], ds0[2], pop1[2], ds1[2];
+    // Operands are read a phase ahead of the MFMAs that take them (into the other of two sets of registers), and the
+    // vector work of a 32-row block sits beside the matrix work of the phases behind it.
+    bf16x8 ar0[KS], ar1[KS], at0[CB][2], at1[CB][2], pop0[2], ds0[2], pop1[2], ds1[2];
     f32x16 s0, p0, s1, p1;
     f32x4 l4[4];
-    auto product = [&](const bf16x8 (&b)[KS], f32x16& acc) {
+    auto product = [&](const bf16x8 (&a)[KS], const bf16x8 (&b)[KS], f32x16& acc) {
 #pragma unroll
-      for (int s = 0; s < KS; ++s) acc = mfma(ar[s], b[s], acc);
+      for (int s = 0; s < KS; ++s) acc = mfma(a[s], b[s], acc);
     };
     // a block's row statistics come in the accumulator's order: lse for the exponent, -D straight into the
     // accumulator of dP
@@ -563,25 +563,26 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
         for (int e = 0; e < 4; ++e) acc[4 * i4 + e] = x[e];
       }
     };
-    auto p_ds_operands = [&](const f32x16& sacc, const f32x16& dpacc, int qb, bf16x8 (&pop)[2], bf16x8 (&dsop)[2]) {
-      float pv[16];
+    // S to P, in place and as an operand; dP to dS
+    auto p_operands = [&](f32x16& sacc, int qb, bf16x8 (&pop)[2]) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) pv[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], sl2e, -l4[i >> 2][i & 3]));
+      for (int i = 0; i < 16; ++i) sacc[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], sl2e, -l4[i >> 2][i & 3]));
       if constexpr (decltype(masked_c)::value) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int qi = i0 + 32 * qb + acc_row(i, hh);
           const bool vis = valid && qi < N && !(causal && key > qi + shift);
-          pv[i] = vis ? pv[i] : 0.0f;
+          sacc[i] = vis ? sacc[i] : 0.0f;
         }
       }
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        pop[i >> 3][i & 7] = (bf16)pv[i];
-        dsop[i >> 3][i & 7] = (bf16)(pv[i] * dpacc[i]);
-      }
+      for (int i = 0; i < 16; ++i) pop[i >> 3][i & 7] = (bf16)sacc[i];
     };
-    auto update = [&](const bf16x8 (&b)[2], f32x16 (&acc)[CB]) {
+    auto ds_operands = [&](const f32x16& pv, const f32x16& dpacc, bf16x8 (&dsop)[2]) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) dsop[i >> 3][i & 7] = (bf16)(pv[i] * dpacc[i]);
+    };
+    auto update = [&](const bf16x8 (&at)[CB][2], const bf16x8 (&b)[2], f32x16 (&acc)[CB]) {
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
@@ -589,36 +590,45 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
     };
     zero(s0);
     zero(s1);
-    read_rows<D>(q_lds, 0, off, ar);
-    fence();
-    product(kop, s0);
-    read_rows<D>(do_lds, 0, off, ar);
+    read_rows<D>(q_lds, 0, off, ar0);
     read_neg_d(0, p0);
-    fence();
-    product(vop, p0);
-    read_rows<D>(q_lds, 1, off, ar);
     read_lse(0);
     fence();
-    product(kop, s1);
-    read_rows<D>(do_lds, 1, off, ar);
+    read_rows<D>(do_lds, 0, off, ar1);
+    fence();
+    product(ar0, kop, s0);
+    fence();
+    read_rows<D>(q_lds, 1, off, ar0);
+    fence();
+    product(ar1, vop, p0);
+    p_operands(s0, 0, pop0);
+    fence();
+    read_rows<D>(do_lds, 1, off, ar1);
     read_neg_d(1, p1);
-    fence();
-    product(vop, p1);
-    p_ds_operands(s0, p0, 0, pop0, ds0);
-    read_transposed<D>(do_lds, 0, off, at);
-    fence();
-    update(pop0, dvacc);
-    read_transposed<D>(q_lds, 0, off, at);
     read_lse(1);
     fence();
-    update(ds0, dkacc);
-    p_ds_operands(s1, p1, 1, pop1, ds1);
-    read_transposed<D>(do_lds, 1, off, at);
+    product(ar0, kop, s1);
+    ds_operands(s0, p0, ds0);
     fence();
-    update(pop1, dvacc);
-    read_transposed<D>(q_lds, 1, off, at);
+    read_transposed<D>(do_lds, 0, off, at0);
     fence();
-    update(ds1, dkacc);
+    product(ar1, vop, p1);
+    p_operands(s1, 1, pop1);
+    fence();
+    read_transposed<D>(q_lds, 0, off, at1);
+    fence();
+    update(at0, pop0, dvacc);
+    ds_operands(s1, p1, ds1);
+    fence();
+    read_transposed<D>(do_lds, 1, off, at0);
+    fence();
+    update(at1, ds0, dkacc);
+    fence();
+    read_transposed<D>(q_lds, 1, off, at1);
+    fence();
+    update(at0, pop1, dvacc);
+    fence();
+    update(at1, ds1, dkacc);
   };
   // Iterations [a, b), b - a even, with or without the mask; buffer parity = iteration parity.
   // The loop is unrolled by two over fixed buffers, masked and unmasked tiles run in loops of
