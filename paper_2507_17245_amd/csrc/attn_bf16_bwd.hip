@@ -917,6 +917,10 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_short_kernel(
   bf16x8 kt[NW];
 #pragma unroll
   for (int s = 0; s < NW; ++s) kt[s] = tr16(ds_lds[0], ch16, s);
+  if (key0 >= Nk) {                                  // dS of a wave without keys: zero, as its K rows in the other buffer are
+#pragma unroll
+    for (int u = 0; u < 4; ++u) *(u32x4*)(ds_lds[1] + w * 4096 + u * 1024 + (tid & 63) * 16) = u32x4{0u, 0u, 0u, 0u};
+  }
   __syncthreads();
 
 #pragma unroll 1
@@ -927,7 +931,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_short_kernel(
       const char* qt = q_lds[par];
       const char* dot = do_lds[par];
       // ---- S, dP, P, dS; dV, dK; dS into LDS
-      const int blocks = r0 + 32 < N ? 2 : 1;        // 32-row blocks of the tile that hold rows
+      const int blocks = key0 >= Nk ? 0 : r0 + 32 < N ? 2 : 1;   // 32-row blocks of the tile that hold rows (a wave without keys: none)
 #pragma unroll 1
       for (int qb = 0; qb < blocks; ++qb) {
         char* ds_dst = ds_lds[par];
