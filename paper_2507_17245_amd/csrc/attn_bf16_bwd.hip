@@ -489,6 +489,9 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
   // causal: query i sees key n iff n <= i + shift; the first tile with a row that sees key n0
   const int i_start = causal ? max(0, n0 - shift) / kBwdStream * kBwdStream : 0;
   const int tiles = ((N - i_start + kBwdStream - 1) / kBwdStream + 1) & ~1;   // per query head, even
+  // the rows that see this lane's key: see_from .. see_from + see_rows - 1
+  const int see_from = causal ? key - shift : 0;
+  const unsigned see_rows = valid && see_from < N ? (unsigned)(N - see_from) : 0u;
   const int n_it = rep * tiles;
   const TileLoader<D> loader(w, lane);
   const QueryStream<D> ctx = {qrep, dout, lse2p, delta, (size_t)b * H + (hk * hsplit + hs) * rep, N, i_start, tiles, w, lane, loader};
@@ -540,8 +543,13 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
       if constexpr (par) ctx.issue(it + 1, q_lds0, do_lds0, lse_lds0, dl_lds0);
       else ctx.issue(it + 1, q_lds1, do_lds1, lse_lds1, dl_lds1);
     }
-    // Operands are read a phase ahead of the MFMAs that take them (into the other of two sets of registers), and the
-    // vector work of a 32-row block sits beside the matrix work of the phases behind it.
+    // Operands are read a phase ahead of the MFMAs that take them, into the other of two sets of registers, and the vector work
+    // of a 32-row block sits beside the matrix work of the phases behind it. A lone wave (d = 128) reads them before the phase's
+    // products begin: read behind most of them, every phase began by waiting for LDS (B4 H16 N8192 4.34 ms, 4.15 so). With two
+    // waves (d = 64) their place in the phase is the compiler's (first: B2 H16 N4096 causal backward 248 us, 250).
+    auto first = [&]() {
+      if constexpr (D == 128) fence();
+    };
     bf16x8 ar0[KS], ar1[KS], at0[CB][2], at1[CB][2], pop0[2], ds0[2], pop1[2], ds1[2];
     f32x16 s0, p0, s1, p1;
     f32x4 l4[4];
@@ -569,11 +577,7 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
       for (int i = 0; i < 16; ++i) sacc[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], sl2e, -l4[i >> 2][i & 3]));
       if constexpr (decltype(masked_c)::value) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int qi = i0 + 32 * qb + acc_row(i, hh);
-          const bool vis = valid && qi < N && !(causal && key > qi + shift);
-          sacc[i] = vis ? sacc[i] : 0.0f;
-        }
+        for (int i = 0; i < 16; ++i) sacc[i] = (unsigned)(i0 + 32 * qb + acc_row(i, hh) - see_from) < see_rows ? sacc[i] : 0.0f;
       }
 #pragma unroll
       for (int i = 0; i < 16; ++i) pop[i >> 3][i & 7] = (bf16)sacc[i];
@@ -595,37 +599,37 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
     read_lse(0);
     fence();
     read_rows<D>(do_lds, 0, off, ar1);
-    fence();
+    first();
     product(ar0, kop, s0);
     fence();
     read_rows<D>(q_lds, 1, off, ar0);
-    fence();
+    first();
     product(ar1, vop, p0);
     p_operands(s0, 0, pop0);
     fence();
     read_rows<D>(do_lds, 1, off, ar1);
     read_neg_d(1, p1);
     read_lse(1);
-    fence();
+    first();
     product(ar0, kop, s1);
     ds_operands(s0, p0, ds0);
     fence();
     read_transposed<D>(do_lds, 0, off, at0);
-    fence();
+    first();
     product(ar1, vop, p1);
     p_operands(s1, 1, pop1);
     fence();
     read_transposed<D>(q_lds, 0, off, at1);
-    fence();
+    first();
     update(at0, pop0, dvacc);
     ds_operands(s1, p1, ds1);
     fence();
     read_transposed<D>(do_lds, 1, off, at0);
-    fence();
+    first();
     update(at1, ds0, dkacc);
     fence();
     read_transposed<D>(q_lds, 1, off, at1);
-    fence();
+    first();
     update(at0, pop1, dvacc);
     fence();
     update(at1, ds1, dkacc);
