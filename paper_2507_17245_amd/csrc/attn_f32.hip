@@ -166,7 +166,8 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     const int q_abs = r0 + lq;
     const int lim = causal ? min(q_abs + shift, Nk - 1) : Nk - 1;   // last key this row sees
 
-    asm volatile(".p2align 6");   // the loop on an instruction line: by where the code in front put it H1 N256 took 12.4 .. 12.7 us
+    // The loop on an instruction line: by where the code in front put it H1 N256 in groups of two took 12.4 .. 12.7 us.
+    if constexpr (kFused && D == 64) asm volatile(".p2align 6");
     while (tile < n_tiles) {
       // ---- stage the K tile (and, mirrored, the K block's grouping) -------------------------------
       wave_order();   // the reads of the previous tile come first

@@ -536,6 +536,9 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
   const int b = bk / Hkv, hk = bk % Hkv, rep = H / Hkv;
   const int n0 = t * kTile, key = n0 + lq;
   const int shift = Nk - N;   // causal: query i sees key n iff n <= i + shift
+  // the rows that see this lane's key: see_from .. see_from + see_rows - 1
+  const int see_from = causal ? key - shift : 0;
+  const unsigned see_rows = see_from < N ? (unsigned)(N - see_from) : 0u;
 
   const int first = causal ? max(0, n0 - shift) / kTile : 0;   // first tile with a row that sees key n0
   const int tiles = (N + kTile - 1) / kTile - first;           // per query head
@@ -749,12 +752,8 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
       }
       if (i0 + kTile > N || (causal && i0 + shift < n0 + kTile - 1)) {   // rows past N; the causal diagonal
         asm volatile("");   // (a branch: few tiles are masked)
-        const int from = causal ? key - shift : 0;   // first row that sees the key
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int row = i0 + acc_row(i, hh);
-          s[i] = (int)(row >= N) | (int)(row < from) ? 0.0f : s[i];
-        }
+        for (int i = 0; i < 16; ++i) s[i] = (unsigned)(i0 + acc_row(i, hh) - see_from) < see_rows ? s[i] : 0.0f;
       }
 #pragma unroll
       for (int i = 0; i < 16; ++i) dp[i] *= s[i];
