@@ -141,7 +141,8 @@ int distr_attn_exact_fwd_ex(const void *q, const void *k, const void *v, void *o
  * one channel per group (Sec. 2.1).
  * bf16 tensors: matrix-core kernels (bf16 operands, fp32 accumulate; P and dS^ are rounded to bf16
  * before the products that take them), d in {64, 128}, any n_groups that divides d. float tensors:
- * float arithmetic on the float matrix instruction (a reference-precision path).
+ * float arithmetic (a reference-precision path): products on the float matrix instruction or, in groups of
+ * two and four channels, of three bf16 pieces that make up each float, at least as near to 64 bits.
  * q, k, v, p: as given to the forward; o: its output; lse: its lse_out; dout [B][H][N][d]: gradient
  * of the loss with respect to o, same dtype. Written: dq [B][H][N][d], dk and dv [B][Hkv][Nk][d]
  * (p->dtype, device, 16-byte aligned, distinct from every input and from each other). The grouping is recomputed

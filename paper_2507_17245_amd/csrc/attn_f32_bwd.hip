@@ -1,7 +1,7 @@
 // Backward of the attention forward (exact and DistrAttention) for gfx950 in float arithmetic: the
 // reference-precision path, for float tensors (bf16 tensors take the matrix-core kernels of
-// attn_bf16_bwd.hip). Products on v_mfma_f32_32x32x2_f32, some of them by bf16 pieces (float operands and sums), no atomics
-// (results do not depend on the run), no scratch.
+// attn_bf16_bwd.hip). Products on v_mfma_f32_32x32x2_f32 (float operands and sums), in groups of two and four channels at d = 64
+// most of them by bf16 pieces (f32_tiles.h), no atomics (results do not depend on the run), no scratch.
 //
 // The paper trains through the approximation (Sec. 4.3, 4.4) and gives no gradient. Computed
 // here: the derivative of the forward with every Q block's grouping held fixed (the permutation
@@ -24,10 +24,11 @@
 //                     out. Groups of 2 and 4 channels: the K tile lies in LDS in sorted channel order,
 //                     members adjacent and summed as they are read, S^ and dQ_r contract over
 //                     n_groups; other group sizes take Q~ and sum dQ~ over the members at the end.
+//   bwd_dkv_pieces_kernel, bwd_dq_pieces_kernel   the same by pieces, for calls that float_by_pieces names
 // The waves' partial sums meet in LDS once, at the end, in a fixed order: as in the forward no wave waits
 // for another before that, and few rows still give every SIMD work. Bound: the matrix
 // instruction (64 cycles for 4096 FLOP): 7 products over d per (query, key) pair, 5 with groups of two, 4 with groups
-// of four. Measured (B1 H8 N2048 d64 n_groups 32): delta 4, dK/dV 144, dQ 91 us; the matrix pipes are busy 60 and 62 % of the launch
+// of four. Measured on it (B1 H8 N2048 d64 n_groups 32; by pieces 126 and 75 us): delta 4, dK/dV 144, dQ 91 us; the matrix pipes are busy 60 and 62 % of the launch
 // (67 and 71 % of the cycles in which their CU has work), the waves wait for them to take an instruction 57 and 68 % of their cycles
 // and for memory, LDS and barriers 23 and 14 %; tiles hit the L2 (95 %). (dK/dV with S^ and dK over the groups' members, K_f summed for every tile anew: 176 us; backward d128 642 -> 504 us, groups of four
 // 572 -> 411; float multiply-adds on the vector ALUs: dK/dV 2740, dQ 1980 us).
