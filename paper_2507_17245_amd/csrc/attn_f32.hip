@@ -63,7 +63,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
   __shared__ __attribute__((aligned(16))) float k_lds[NW][kTile * RS];   // K tile of each wave, at the end its output
   __shared__ float stat_lds[NW][2][kTile];
   __shared__ __attribute__((aligned(16))) uint8_t map_lds[kMirrored ? NW : 1][D];
-  __shared__ uint32_t mark_lds[kTile];   // PIECES: what is known of a row (kRowAgain ..)
+  __shared__ uint32_t mark_lds[kTile + 1];   // PIECES: what is known of a row (kRowAgain ..); whether a key is beyond_pieces
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     for (int u = 0; u < QU; ++u) x[u] = Quad<E>::load(q_rsrc, (u * T + tid) * 4 * (int)sizeof(E), r0 * (D * (int)sizeof(E)));
 #pragma unroll
     for (int u = 0; u < QU; ++u) *(f32x4*)&q_lds[(u * T + tid) / (D / 4) * RS + (u * T + tid) % (D / 4) * 4] = Quad<E>::values(x[u]);
-    if (PIECES && tid < kTile) mark_lds[tid] = 0;
+    if (PIECES && tid <= kTile) mark_lds[tid] = 0;
   }
   int kdst[4];          // kQueryFused: where the lane's four channels go in a row sorted by group
   if constexpr (!kMirrored) {
@@ -132,7 +132,9 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
   }
 
   // One walk over the keys for the rows of the bit mask `rows`, products by pieces or on the float instruction. By pieces, the rows
-  // to be taken again with floats are returned.
+  // to be taken again are returned; a second walk takes the scores by pieces that the first took by them (beyond_pieces), and with
+  // k_again set it is for the rows, too, that see a key that is not held by pieces.
+  bool k_again = false;
   auto pass = [&](auto pieces, uint32_t rows) -> uint32_t {
     constexpr bool BY_PIECES = decltype(pieces)::value;
     const Splitter splitter(lane);
@@ -149,11 +151,23 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
 #pragma unroll
       for (int s = 0; s < HS; ++s) qop[s] = q_lds[lq * RS + hh * HS + s];
     }
-    Pieces qpc[BY_PIECES ? HS / 8 : 1];
+    Pieces qpc[PIECES ? HS / 8 : 1];
     auto split_q = [&]() {
-      if constexpr (BY_PIECES) split_steps<HS, false>(splitter, qop, [&](int s, const Pieces& p) { qpc[s] = p; });
+      if constexpr (PIECES) split_steps<HS, false>(splitter, qop, [&](int s, const Pieces& p) { qpc[s] = p; });
     };
     if constexpr (!kMirrored) split_q();
+    uint32_t any_beyond = 0, q_beyond = 0;   // rows whose scores are not by pieces
+    auto find_q_beyond = [&]() {
+      float m = 0.0f;
+      if constexpr (kMirrored) {
+#pragma unroll
+        for (int c = 0; c < D / 2; c += 4) m = largest(m, *(const f32x4*)&q_lds[lq * RS + hh * (D / 2) + c]);
+      } else {
+        m = largest(qop);
+      }
+      q_beyond = rows_of(beyond_pieces(m));
+    };
+    if constexpr (PIECES && !BY_PIECES) find_q_beyond();
     float* kt = k_lds[w];
     int koff[kMirrored ? HS : 1];   // channel of the K row that contraction slot s takes (mirrored form)
     f32x16 oacc[NB];
@@ -171,9 +185,11 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     while (tile < n_tiles) {
       // ---- stage the K tile (and, mirrored, the K block's grouping) -------------------------------
       wave_order();   // the reads of the previous tile come first
+      float k_largest = 0.0f;
 #pragma unroll
       for (int u = 0; u < KU; ++u) {
         const f32x4 x = Quad<E>::values(kreg[u]);
+        if constexpr (BY_PIECES) k_largest = largest(k_largest, x);
         const int row = (u * 64 + lane) / (D / 4), c = (u * 64 + lane) % (D / 4) * 4;
         if constexpr (MODE == kQueryFused) {
 #pragma unroll
@@ -182,6 +198,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
           *(f32x4*)&kt[row * RS + c] = x;
         }
       }
+      if constexpr (BY_PIECES) any_beyond |= rows_of(beyond_pieces(k_largest));
       const bool new_block = kMirrored && tile % TB == 0;
       if constexpr (kMirrored) {
         if (new_block) {
@@ -249,9 +266,9 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
       // ---- scores -----------------------------------------------------------------------------------
       PieceSum by_pieces;
       ChannelSum<HS> by_floats;
-      float kop[BY_PIECES ? HS : 1];
+      float kop[PIECES ? HS : 1];
       auto put = [&](int s, float x) {   // float s of the lane's half row
-        if constexpr (BY_PIECES) kop[s] = x;
+        if constexpr (PIECES) kop[s] = x;
         else by_floats.step(s, x, qop[s]);
       };
       if constexpr (kMirrored) {
@@ -273,11 +290,25 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
         }
       }
       f32x16 sacc;
-      if constexpr (BY_PIECES) {
+      if constexpr (PIECES) {
         split_steps<HS>(splitter, kop, [&](int s, const Pieces& p) { by_pieces.step(p, qpc[s]); });
         sacc = by_pieces.sum();
-      } else {
+      }
+      if constexpr (!PIECES) {
         sacc = by_floats.sum();
+      } else if constexpr (!BY_PIECES) {
+        float m = 0.0f;
+#pragma unroll
+        for (int c = 0; c < D / 2; c += 4) m = largest(m, *(const f32x4*)&kt[lq * RS + hh * (D / 2) + c]);
+        const uint32_t k_beyond = rows_of(beyond_pieces(m));
+        if (k_beyond != 0 && tile * kTile + __builtin_ctz(k_beyond) <= lim) atomicOr(&mark_lds[lq], kRowBeyond);
+        if ((q_beyond | k_beyond) != 0) {
+#pragma unroll
+          for (int s = 0; s < HS; ++s) by_floats.step(s, kop[s], qop[s]);
+          const f32x16 y = by_floats.sum();
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sacc[i] = ((q_beyond >> lq | k_beyond >> acc_row(i, hh)) & 1) != 0 ? y[i] : sacc[i];
+        }
       }
       const int n0 = tile * kTile;
       if (n0 + kTile > Nk || (causal && n0 + kTile - 1 > r0 + shift)) {
@@ -360,12 +391,13 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
       }
     }
     // row statistics for a backward pass: ln(sum of exp(score)) = rounded reference (see scaled_plus) + ln(sum)
-    if (lse && w == 0 && hh == 0 && q_abs < N && rows >> lq & 1)
+    auto wanted = [&](int row) { return (rows >> row & 1) != 0 || (PIECES && !BY_PIECES && (mark_lds[row] & kRowBeyond) != 0); };
+    if (lse && w == 0 && hh == 0 && q_abs < N && wanted(lq))
       lse[(size_t)bh * N + q_abs] = __builtin_fmaf(__builtin_log2f(l_all), 0.6931471805599453f, m_all * scale);
     __syncthreads();
     for (int i = tid; i < kTile * D / 4; i += T) {
       const int row = i / (D / 4), c = i % (D / 4) * 4;
-      if (r0 + row < N && rows >> row & 1) {
+      if (r0 + row < N && wanted(row)) {
         f32x4 x = *(const f32x4*)&k_lds[0][row * RS + c];
 #pragma unroll
         for (int j = 1; j < NW; ++j) x += *(const f32x4*)&k_lds[j][row * RS + c];
@@ -380,15 +412,15 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
       }
     }
     if constexpr (!BY_PIECES) return 0;
-    bool out = false;
-#pragma unroll
-    for (int c = 0; c < D / 2; c += 4) out |= outside_pieces(*(const f32x4*)&q_lds[lq * RS + hh * (D / 2) + c]);
+    if (any_beyond != 0) atomicOr(&mark_lds[kTile], 1u);
+    find_q_beyond();
     __syncthreads();
-    return rows_again(mark_lds[lq] | (out ? kRowAgain : 0));
+    k_again = mark_lds[kTile] != 0;
+    return rows_again(mark_lds[lq]) | q_beyond;
   };
   if constexpr (PIECES) {
     const uint32_t again = pass(std::true_type(), ~0u);
-    if (again == 0) return;
+    if (again == 0 && !k_again) return;
     tile = w * TB;
     if (tile < n_tiles) load_k(tile);
     pass(std::false_type(), again);

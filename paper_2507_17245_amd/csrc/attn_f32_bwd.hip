@@ -524,7 +524,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
   __shared__ __attribute__((aligned(16))) float k_lds[kTile * RS];                        // of the workgroup's keys
   __shared__ __attribute__((aligned(16))) PieceRows<D> v_lds;
   __shared__ __attribute__((aligned(16))) float stat_lds[W][2][kTile];   // lse, D_i
-  __shared__ uint32_t mark_lds[kTile];   // what is known of a key's row (kRowAgain ..)
+  __shared__ uint32_t mark_lds[kTile + 1];   // what is known of a key's row (kRowAgain ..); whether a query row is beyond_pieces
   __shared__ __attribute__((aligned(16))) uint8_t map_lds[W][4][D];   // of this Q block and the one before or after it: sorted order, the channels' groups
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -601,7 +601,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
     }
   };
   load_first();
-  if (tid < kTile) mark_lds[tid] = 0;
+  if (tid <= kTile) mark_lds[tid] = 0;
 
   const __amdgpu_buffer_rsrc_t k_rsrc = head_rsrc(k + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
   const __amdgpu_buffer_rsrc_t v_rsrc = head_rsrc(v + (size_t)bk * Nk * D, (unsigned)Nk * D * 4);
@@ -619,10 +619,12 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
   if (w == 0) {
 #pragma unroll
     for (int u = 0; u < Tile<D>::KU; ++u)
-      if (outside_pieces(Q4::values(kt.x[u]))) atomicOr(&mark_lds[(u * 64 + lane) / (D / 4)], kRowAgain);
+      if (beyond_pieces(largest(0.0f, Q4::values(kt.x[u])))) atomicOr(&mark_lds[(u * 64 + lane) / (D / 4)], kRowAgain);
   }
   // The rows (keys) of the bit mask `rows`, S^ and dP by pieces or on the float instruction. By pieces, the rows to be taken again are
-  // returned.
+  // returned; a second walk takes the scores by pieces that the first took by them (beyond_pieces), and with q_again set it is for
+  // the keys, too, that a query row sees which is not held by pieces.
+  bool q_again = false;
   auto pass = [&](auto pieces, uint32_t rows) -> uint32_t {
     constexpr bool BY_PIECES = decltype(pieces)::value;
     const Splitter splitter(lane);
@@ -633,11 +635,17 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
       zero(dvacc[mb]);
     }
     // K_f of the workgroup's keys and dK_f of the Q block the wave is in
-    Pieces kf[BY_PIECES ? HS / 8 : 1];
-    float kf32[BY_PIECES ? 1 : HS];
+    Pieces kf[HS / 8];
     f32x16 dkf[NG];
-    auto fuse_keys = [&]() {
-      float sum[HS];
+    uint32_t any_beyond = 0;
+    bool key_beyond = false;
+    if constexpr (!BY_PIECES) {
+      float m = 0.0f;
+#pragma unroll
+      for (int c = 0; c < D / 2; c += 4) m = largest(m, *(const f32x4*)&k_lds[lq * RS + hh * (D / 2) + c]);
+      key_beyond = (rows_of(beyond_pieces(m)) >> lq & 1) != 0;
+    }
+    auto fused_keys = [&](float (&sum)[HS]) {
 #pragma unroll
       for (int c = 0; c < D / 2; c += 8) {
         const u32x2 e2 = *(const u32x2*)&map_lds[w][2 * slot][hh * (D / 2) + c];
@@ -649,12 +657,11 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
           sum[(c + e) / G] = x;
         }
       }
-      if constexpr (BY_PIECES) {
-        split_steps<HS>(splitter, sum, [&](int s, const Pieces& p) { kf[s] = p; });
-      } else {
-#pragma unroll
-        for (int s = 0; s < HS; ++s) kf32[s] = sum[s];
-      }
+    };
+    auto fuse_keys = [&]() {
+      float sum[HS];
+      fused_keys(sum);
+      split_steps<HS>(splitter, sum, [&](int s, const Pieces& p) { kf[s] = p; });
 #pragma unroll
       for (int mb = 0; mb < NG; ++mb) zero(dkf[mb]);
     };
@@ -692,6 +699,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
       wave_order();   // the reads of the previous tile come first
 #pragma unroll
       for (int u = 0; u < QL; ++u) q_lds[w][(u * ROWS + lane / KRED) * RQ + lane % KRED] = qr[u];
+      if constexpr (BY_PIECES) any_beyond |= rows_of(beyond_pieces(largest(qr)));
       stat_lds[w][hh][lq] = hh ? delta_reg : lse_reg;
       if (it + 1 < it_end) {
         const bool same = block_of(it + 1) == block;
@@ -709,15 +717,24 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
 #pragma unroll
           for (int e = 0; e < 4; ++e) x[c + e] = y[e];
         }
-        if constexpr (BY_PIECES) {
+        {
           PieceSum acc;
           split_steps<HS>(splitter, x, [&](int s, const Pieces& p) { acc.template step<true>(p, kf[s]); });
           s = acc.sum();
-        } else {
-          ChannelSum<HS> acc;
+        }
+        if constexpr (!BY_PIECES) {
+          const uint32_t q_beyond = rows_of(beyond_pieces(largest(x)));
+          if (q_beyond != 0 && i0 + 31 - __builtin_clz(q_beyond) >= see_from) atomicOr(&mark_lds[lq], kRowBeyond);
+          if (q_beyond != 0 || rows_of(key_beyond) != 0) {
+            ChannelSum<HS> acc;
+            float y[HS];
+            fused_keys(y);
 #pragma unroll
-          for (int s = 0; s < HS; ++s) acc.step(s, x[s], kf32[s]);
-          s = acc.sum();
+            for (int s = 0; s < HS; ++s) acc.step(s, x[s], y[s]);
+            const f32x16 z = acc.sum();
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = key_beyond || (q_beyond >> acc_row(i, hh) & 1) != 0 ? z[i] : s[i];
+          }
         }
       }
       zero(dp);
@@ -798,7 +815,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
       __syncthreads();
       for (int i = tid; i < kTile * D / 4; i += W * 64) {
         const int row = i / (D / 4), c = i % (D / 4) * 4;
-        if (n0 + row < Nk && rows >> row & 1) {
+        if (n0 + row < Nk && ((rows >> row & 1) != 0 || (!BY_PIECES && (mark_lds[row] & kRowBeyond) != 0))) {
           f32x4 x = *(const f32x4*)&do_lds[0][do_at(row, c)];
 #pragma unroll
           for (int j = 1; j < W; ++j) x += *(const f32x4*)&do_lds[j][do_at(row, c)];
@@ -808,11 +825,13 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
       }
     }
     if constexpr (!BY_PIECES) return 0;
+    if (any_beyond != 0) atomicOr(&mark_lds[kTile], 1u);
     __syncthreads();
+    q_again = mark_lds[kTile] != 0;
     return rows_again(mark_lds[lq]);
   };
   const uint32_t again = pass(std::true_type(), ~0u);
-  if (again == 0) return;
+  if (again == 0 && !q_again) return;
   load_first();
   pass(std::false_type(), again);
 }
@@ -1016,7 +1035,7 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
   __shared__ __attribute__((aligned(16))) PieceRows<KRED> q_lds;
   __shared__ __attribute__((aligned(16))) PieceRows<D> do_lds;
   __shared__ __attribute__((aligned(16))) float sum_lds[kTile * RS];
-  __shared__ uint32_t mark_lds[kTile];   // what is known of a row (kRowAgain ..)
+  __shared__ uint32_t mark_lds[kTile + 1];   // what is known of a row (kRowAgain ..); whether a key is beyond_pieces
   __shared__ uint8_t order_lds[D];   // sorted order of the block's channels
   __shared__ uint8_t map_lds[D];     // a channel's position in it
 
@@ -1046,7 +1065,7 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
     }
   };
   load_first();
-  if (tid < kTile) mark_lds[tid] = 0;
+  if (tid <= kTile) mark_lds[tid] = 0;
   // Q, dO and O rows pass through LDS (one tile per wave 0, 1, 2)
   {
     const float* src = w == 0 ? q : w == 1 ? dout : o;
@@ -1075,7 +1094,7 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
     for (int e = 0; e < 8; ++e)
       x[e] = k_lds[0][lq * RS + order_lds[(hh * HS + s + e) * G]];
     q_lds.store(lq, hh * HS + s, split(x));
-    if (outside_pieces(x.lo) | outside_pieces(x.hi)) atomicOr(&mark_lds[lq], kRowAgain);
+    if (beyond_pieces(largest(largest(0.0f, x.lo), x.hi))) atomicOr(&mark_lds[lq], kRowAgain);
   }
   for (int s = w * 8; s < D / 2; s += W * 8) {
     f32x8 x;
@@ -1089,20 +1108,15 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
   const float lse_row = lse[(size_t)bh * N + min(q_abs, N - 1)];
   __syncthreads();   // the staged rows have been read
 
-  // The rows of the bit mask `rows`, products by pieces or on the float instruction. By pieces, the rows to be taken again are returned.
+  // The rows of the bit mask `rows`, products by pieces or on the float instruction. By pieces, the rows to be taken again are returned;
+  // a second walk takes the scores by pieces that the first took by them (beyond_pieces), and with k_again set it is for the rows, too,
+  // that see a key that is not held by pieces.
+  bool k_again = false;
   auto pass = [&](auto pieces, uint32_t rows) -> uint32_t {
     constexpr bool BY_PIECES = decltype(pieces)::value;
     const Splitter splitter(lane);
-    float qop[BY_PIECES ? 1 : HS], doop[BY_PIECES ? 1 : D / 2];
-    if constexpr (!BY_PIECES) {
-      const __amdgpu_buffer_rsrc_t q_rsrc = head_rsrc(q + head, (unsigned)N * D * 4), do_rsrc = head_rsrc(dout + head, (unsigned)N * D * 4);
-#pragma unroll
-      for (int s = 0; s < HS; ++s)
-        qop[s] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(q_rsrc, lq * (D * 4) + order_lds[(hh * HS + s) * G] * 4, r0 * (D * 4), 0));
-#pragma unroll
-      for (int c = 0; c < D / 2; ++c)
-        doop[c] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(do_rsrc, lq * (D * 4) + (hh * (D / 2) + c) * 4, r0 * (D * 4), 0));
-    }
+    const __amdgpu_buffer_rsrc_t q_rsrc = head_rsrc(q + head, (unsigned)N * D * 4), do_rsrc = head_rsrc(dout + head, (unsigned)N * D * 4);
+    uint32_t any_beyond = 0;
     f32x16 dqacc[NG];
 #pragma unroll
     for (int mb = 0; mb < NG; ++mb) zero(dqacc[mb]);
@@ -1119,6 +1133,12 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
       }
       wave_order();
       kt.scatter(k_lds[w], lane, kdst);
+      if constexpr (BY_PIECES) {
+        float m = 0.0f;
+#pragma unroll
+        for (int u = 0; u < Tile<D>::KU; ++u) m = largest(m, Q4::values(kt.x[u]));
+        any_beyond |= rows_of(beyond_pieces(m));
+      }
       if (tile + W < n_tiles) {
         kt.load(k_rsrc, tile + W, lane);
         vt.load(v_rsrc, tile + W, lane);
@@ -1131,13 +1151,18 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
       } else {
         OneChain acc;
 #pragma unroll
-        for (int c = 0; c < D / 2; ++c) acc.step(c, x[c], doop[c]);
+        for (int c = 0; c < D / 2; c += 4) {
+          const f32x4 y = Q4::values(Q4::load(do_rsrc, (lq * D + hh * (D / 2) + c) * 4, r0 * (D * 4)));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc.step(c + e, x[c + e], y[e]);
+        }
         dp = acc.sum();
       }
-      float y[HS];
+      float y[HS], m = 0.0f;
 #pragma unroll
       for (int c = 0; c < D / 2; c += 4) {
         const f32x4 x = *(const f32x4*)&k_lds[w][lq * RS + hh * (D / 2) + c];
+        if constexpr (!BY_PIECES) m = largest(m, x);
         if constexpr (G == 2) {
           y[c / 2] = x[0] + x[1];
           y[c / 2 + 1] = x[2] + x[3];
@@ -1146,15 +1171,26 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
         }
       }
       f32x16 s;
-      if constexpr (BY_PIECES) {
+      {
         PieceSum acc;
         split_steps<HS>(splitter, y, [&](int s, const Pieces& p) { acc.step(p, q_lds.load(lq, hh * HS + 8 * s)); });
         s = acc.sum();
-      } else {
-        ChannelSum<HS> acc;
+      }
+      if constexpr (!BY_PIECES) {
+        float qop[HS];
 #pragma unroll
-        for (int c = 0; c < HS; ++c) acc.step(c, y[c], qop[c]);
-        s = acc.sum();
+        for (int c = 0; c < HS; ++c)
+          qop[c] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(q_rsrc, (lq * D + order_lds[(hh * HS + c) * G]) * 4, r0 * (D * 4), 0));
+        const uint32_t q_beyond = rows_of(beyond_pieces(largest(qop))), k_beyond = rows_of(beyond_pieces(m));
+        if (k_beyond != 0 && tile * kTile + __builtin_ctz(k_beyond) <= lim) atomicOr(&mark_lds[lq], kRowBeyond);
+        if ((q_beyond | k_beyond) != 0) {
+          ChannelSum<HS> acc;
+#pragma unroll
+          for (int c = 0; c < HS; ++c) acc.step(c, y[c], qop[c]);
+          const f32x16 z = acc.sum();
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[i] = ((q_beyond >> lq | k_beyond >> acc_row(i, hh)) & 1) != 0 ? z[i] : s[i];
+        }
       }
       const int n0 = tile * kTile;
 #pragma unroll
@@ -1220,7 +1256,7 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
     __syncthreads();
     for (int i = tid; i < kTile * D / 4; i += W * 64) {
       const int row = i / (D / 4), c = i % (D / 4) * 4;
-      if (r0 + row >= N || !(rows >> row & 1)) continue;
+      if (r0 + row >= N || !((rows >> row & 1) != 0 || (!BY_PIECES && (mark_lds[row] & kRowBeyond) != 0))) continue;
       f32x4 y;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -1229,10 +1265,14 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
       }
       *(f32x4*)(dq + head + (size_t)(r0 + row) * D + c) = y;
     }
-    return BY_PIECES ? rows_again(mark_lds[lq]) : 0;
+    if constexpr (!BY_PIECES) return 0;
+    if (any_beyond != 0) atomicOr(&mark_lds[kTile], 1u);
+    __syncthreads();
+    k_again = mark_lds[kTile] != 0;
+    return rows_again(mark_lds[lq]);
   };
   const uint32_t again = pass(std::true_type(), ~0u);
-  if (again == 0) return;
+  if (again == 0 && !k_again) return;
   load_first();
   pass(std::false_type(), again);
 }

@@ -167,14 +167,37 @@ struct PieceSum {
 //   backward N128 18.3 | 20.0, N256 25.9 | 26.5, N320 34.7 | 31.8, N512 38.6 | 34.5, N1024 60.3 | 52.4
 inline bool float_by_pieces(const Problem& pb) {
   const int G = pb.d / pb.n_groups;
-  return (G == 2 || G == 4) && (pb.d == 64 || pb.side == 1) && pb.Nk > 8 * kTile;
+  return (G == 2 || G == 4) && (pb.d == 64 || pb.side == 1) && pb.Nk > 8 * kTile && pb.scale <= 0x1p20f;
+}
+
+// Which scores are taken by pieces, in every kernel alike (P = exp(S - lse) wants the S that lse was taken of): those of a query
+// row (its sampled channels; all of them in the mirrored form) and a key row below 2^60. What pieces lose of the smallest floats
+// is then 2^-60 of a score at most, and the scale is no larger than 2^20. The other scores are float products, pair by pair, in a
+// second walk of the workgroups that have such rows.
+constexpr float kPieceLimit = 0x1p60f;
+__device__ inline float largest(float m, float x, float y) {   // (of magnitudes; NaN stays)
+  return __builtin_elementwise_maximum(m, __builtin_elementwise_maximum(__builtin_fabsf(x), __builtin_fabsf(y)));
+}
+__device__ inline float largest(float m, float x) { return __builtin_elementwise_maximum(m, __builtin_fabsf(x)); }
+__device__ inline float largest(float m, f32x4 x) { return largest(largest(m, x[0], x[1]), x[2], x[3]); }
+template <int C>
+__device__ inline float largest(const float (&x)[C]) {
+  float m = 0.0f;
+#pragma unroll
+  for (int c = 0; c < C; c += 2) m = largest(m, x[c], x[c + 1]);
+  return m;
+}
+__device__ inline bool beyond_pieces(float m) { return !(m < kPieceLimit); }
+// rows of a bit mask, from what either half of the wave says of its 32 rows
+__device__ inline uint32_t rows_of(bool any) {
+  const uint64_t rows = __builtin_amdgcn_ballot_w64(any);
+  return (uint32_t)rows | (uint32_t)(rows >> 32);
 }
 
 // What pieces do not hold as floats do: infinities and NaN (a product with them makes every sum of its row NaN), operands so
 // small that their last piece is lost, and products of such with very large ones. A workgroup looks at the results of its 32 rows
-// and takes those again with float products that are not finite, or not zero and nowhere as large as 2^-60, or whose query row
-// holds something outside 2^-64 .. 2^64: what remains has lost less than 2^-20 of its own rounding.
-constexpr uint32_t kRowAgain = 1, kRowNonzero = 2, kRowLarge = 4;
+// and takes those again that are not finite, or not zero and nowhere as large as 2^-60: all but the scores with float products.
+constexpr uint32_t kRowAgain = 1, kRowNonzero = 2, kRowLarge = 4, kRowBeyond = 8;
 __device__ inline uint32_t row_mark(f32x4 x) {
   uint32_t mark = 0;
 #pragma unroll
@@ -184,20 +207,9 @@ __device__ inline uint32_t row_mark(f32x4 x) {
   }
   return mark;
 }
-// Something of 2^64 and more, or NaN, or below 2^-64 but not zero. (Comparisons without a branch.)
-__device__ inline bool outside_pieces(f32x4 x) {
-  uint32_t out = 0;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const uint32_t a = __builtin_bit_cast(uint32_t, (float)x[e]) & 0x7fffffffu;
-    out |= (uint32_t)(a - 0x1f800000u >= 0x40000000u) & (uint32_t)(a != 0);   // the bits of 2^-64; those of 2^64 less these
-  }
-  return out != 0;
-}
 // mark: of the lane's row; the same 32 rows in both halves of the wave
 __device__ inline uint32_t rows_again(uint32_t mark) {
-  const uint64_t rows = __builtin_amdgcn_ballot_w64((mark & kRowAgain) != 0 || (mark & (kRowNonzero | kRowLarge)) == kRowNonzero);
-  return (uint32_t)rows | (uint32_t)(rows >> 32);
+  return rows_of((mark & kRowAgain) != 0 || (mark & (kRowNonzero | kRowLarge)) == kRowNonzero);
 }
 
 // Pieces of 32 rows of C floats in LDS; rows 16 bytes apart in the banks, a lane's operand is one read per piece.

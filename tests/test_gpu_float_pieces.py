@@ -127,3 +127,44 @@ def test_gradients_far_from_one(case, size):
                       (dk.double(), torch.matmul(ds.transpose(2, 3).contiguous(), q.double()).view(1, Hkv, -1, Nk, d).sum(2)),
                       (dv.double(), torch.matmul(p.transpose(2, 3).contiguous(), g).view(1, Hkv, -1, Nk, d).sum(2))):
         assert (got / size - want).norm() <= 4e-6 * want.norm()
+
+
+# the keys of every row apart by more than exp() reaches: P is 1 at the last key with the largest score and 0 elsewhere
+ONE_KEY = [(8, 2, 300, 300, 64, 2, True, 0), (1, 1, 290, 320, 64, 4, True, 0), (64, 64, 129, 300, 64, 2, True, 0), (64, 64, 130, 290, 64, 4, True, 0)]
+
+
+@pytest.mark.parametrize("case", ONE_KEY, ids=str)
+@pytest.mark.parametrize("what", ["ordinary", "small q", "small k", "large q", "large k", "infinite k", "no q"])
+def test_scores_of_both_passes(case, what):
+    """P = exp(S - lse) of the backward is of the very scores that the forward's lse is of, whichever way they are summed: with one key that
+    counts it is exactly 1 at scores of 1e4 and more, where the two ways differ by up to 1 %. Bound: the rounding of a float sum of 600."""
+    import torch
+    H, Hkv, N, Nk, d, G, causal, side = case
+    q, k, v = _inputs(case)
+    gen = torch.Generator(device="cuda").manual_seed(24)
+    k = 100.0 * torch.arange(1, Nk + 1, device="cuda")[None, None, :, None] * (1.0 + 1e-3 * torch.randn(k.shape, generator=gen, device="cuda"))
+    if what == "small q":
+        q[:, :, 2::7, 5] = 1e-20
+    elif what == "small k":
+        k[:, :, 3::7, 10] += k[:, :, 3::7, 9]
+        k[:, :, 3::7, 9] = 1e-20
+    elif what == "large q":
+        q[:, :, 1::5] *= 2.0 ** 70
+    elif what == "large k":
+        k[:, :, 5::50] *= 2.0 ** 70
+    elif what == "infinite k":
+        k[:, :, 7::40] = -math.inf
+    elif what == "no q":
+        q[:, :, 2::9] = 0.0
+        k[:, :, 20::30] *= 2.0 ** 70
+    dout = torch.randn(q.shape, generator=gen, device="cuda")
+    o, _ = _forward(case, q, k, v)
+    dv = _backward(case, q, k, v, dout)[2]
+    kk, vv = (x.double().repeat_interleave(H // Hkv, dim=1) for x in (k, v))
+    hidden = torch.arange(Nk, device="cuda")[None, :] > torch.arange(N, device="cuda")[:, None] + Nk - N
+    s = torch.matmul(q.double(), kk.transpose(2, 3).contiguous()) * 0.02
+    p = torch.softmax(s.masked_fill(hidden, -math.inf), dim=-1)
+    want = torch.matmul(p, vv)
+    assert (o.double() - want).norm() <= 1e-6 * want.norm()
+    want = torch.matmul(p.transpose(2, 3).contiguous(), dout.double()).view(1, Hkv, -1, Nk, d).sum(2)
+    assert (dv.double() - want).norm() <= 2e-6 * want.norm()
