@@ -158,7 +158,11 @@ struct PieceSum {
     }
     lead = mfma(a.hi, b.hi, lead);
   }
-  __device__ f32x16 sum() const { return lead + rest; }
+  __device__ f32x16 sum() const {
+    f32x16 total = lead + rest;
+    asm volatile("" : "+v"(total));   // here: behind a branch the compiler does not wait long enough for the products on every path
+    return total;
+  }
 };
 
 // Products by pieces: groups of two and four channels at d = 64, and the mirrored form (which has no backward to agree with on the
