@@ -613,7 +613,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
   for (int c = (W - 1 - w) * 8; c < D / 2; c += W * 8) {
     const int at = hh * (D / 2) + c;
     const f32x4 x = Q4::values(Q4::load(v_rsrc, (lq * D + at) * 4, n0 * (D * 4))), y = Q4::values(Q4::load(v_rsrc, (lq * D + at + 4) * 4, n0 * (D * 4)));
-    v_lds.store(lq, at, split(f32x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]}));
+    v_lds.store(lq, at, split(f32x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]} * kRaise));
   }
   __syncthreads();
   if (w == 0) {
@@ -627,6 +627,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
   bool q_again = false;
   auto pass = [&](auto pieces, uint32_t rows) -> uint32_t {
     constexpr bool BY_PIECES = decltype(pieces)::value;
+    constexpr float raise = BY_PIECES ? kRaise : 1.0f, dp_raise = raise * raise;   // of dO and V; of dP, D_i, dS and dK_f
     const Splitter splitter(lane);
     f32x16 dkacc[NB], dvacc[NB];
 #pragma unroll
@@ -700,7 +701,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
 #pragma unroll
       for (int u = 0; u < QL; ++u) q_lds[w][(u * ROWS + lane / KRED) * RQ + lane % KRED] = qr[u];
       if constexpr (BY_PIECES) any_beyond |= rows_of(beyond_pieces(largest(qr)));
-      stat_lds[w][hh][lq] = hh ? delta_reg : lse_reg;
+      stat_lds[w][hh][lq] = hh ? delta_reg * dp_raise : lse_reg;
       if (it + 1 < it_end) {
         const bool same = block_of(it + 1) == block;
         if (!same) store_map(slot ^ 1);
@@ -745,7 +746,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
         for (int c = 0; c < 16; c += 4) {
           const f32x4 y = *(const f32x4*)&do_lds[w][do_at(lq, hh * (D / 2) + c0 + c)];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) x[c + e] = y[e];
+          for (int e = 0; e < 4; ++e) x[c + e] = y[e] * raise;
         }
         if constexpr (BY_PIECES) {
           split_steps<16>(splitter, x, [&](int s, const Pieces& p) { dp = mfma(p, v_lds.load(lq, hh * (D / 2) + c0 + 8 * s), dp); });
@@ -819,8 +820,8 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
           f32x4 x = *(const f32x4*)&do_lds[0][do_at(row, c)];
 #pragma unroll
           for (int j = 1; j < W; ++j) x += *(const f32x4*)&do_lds[j][do_at(row, c)];
-          if constexpr (BY_PIECES) atomicOr(&mark_lds[row], row_mark(x));
-          *(f32x4*)((of ? dk : dv) + ((size_t)bk * Nk + n0 + row) * D + c) = of ? x * scale : x;
+          if (BY_PIECES && of) atomicOr(&mark_lds[row], row_mark(x) & kRowAgain);
+          *(f32x4*)((of ? dk : dv) + ((size_t)bk * Nk + n0 + row) * D + c) = of ? x * (1.0f / dp_raise) * scale : x;
         }
       }
     }
@@ -1099,7 +1100,7 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
   for (int s = w * 8; s < D / 2; s += W * 8) {
     f32x8 x;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = k_lds[1][lq * RS + hh * (D / 2) + s + e];
+    for (int e = 0; e < 8; ++e) x[e] = k_lds[1][lq * RS + hh * (D / 2) + s + e] * kRaise;
     do_lds.store(lq, hh * (D / 2) + s, split(x));
   }
   dl = half_swap_sum(dl);
@@ -1114,7 +1115,9 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
   bool k_again = false;
   auto pass = [&](auto pieces, uint32_t rows) -> uint32_t {
     constexpr bool BY_PIECES = decltype(pieces)::value;
+    constexpr float raise = BY_PIECES ? kRaise : 1.0f, dp_raise = raise * raise;   // of dO, V and K_f; of dP, D and dS
     const Splitter splitter(lane);
+    const float raised_dl = dl * dp_raise;
     const __amdgpu_buffer_rsrc_t q_rsrc = head_rsrc(q + head, (unsigned)N * D * 4), do_rsrc = head_rsrc(dout + head, (unsigned)N * D * 4);
     uint32_t any_beyond = 0;
     f32x16 dqacc[NG];
@@ -1129,7 +1132,7 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
       for (int c = 0; c < D / 2; c += 4) {
         const f32x4 y = *(const f32x4*)&k_lds[w][lq * RS + hh * (D / 2) + c];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[c + e] = y[e];
+        for (int e = 0; e < 4; ++e) x[c + e] = y[e] * raise;
       }
       wave_order();
       kt.scatter(k_lds[w], lane, kdst);
@@ -1202,7 +1205,7 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
           if (n0 + acc_row(i, hh) > lim) s[i] = 0.0f;
       }
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s[i] *= dp[i] - dl;
+      for (int i = 0; i < 16; ++i) s[i] *= dp[i] - raised_dl;
       // lane m owns the columns NG*m .. (of 32 * NG slots; with 16 groups the upper lanes repeat the lower)
       f32x16 kc[NG];
 #pragma unroll
@@ -1212,10 +1215,10 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
         for (int mb = 0; mb < NG; ++mb) {
           if constexpr (G == 2) {
             const f32x2 y = *(const f32x2*)(src + mb * G);
-            kc[mb][i] = y[0] + y[1];
+            kc[mb][i] = (y[0] + y[1]) * raise;
           } else {
             const f32x4 y = *(const f32x4*)(src + mb * G);
-            kc[mb][i] = ((y[0] + y[1]) + y[2]) + y[3];
+            kc[mb][i] = (((y[0] + y[1]) + y[2]) + y[3]) * raise;
           }
         }
       }
@@ -1250,8 +1253,8 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
       f32x4 x = *(const f32x4*)&k_lds[0][row * RS + c];
 #pragma unroll
       for (int j = 1; j < W; ++j) x += *(const f32x4*)&k_lds[j][row * RS + c];
-      *(f32x4*)&sum_lds[row * RS + c] = x;
-      if (BY_PIECES && r0 + row < N) atomicOr(&mark_lds[row], row_mark(x));
+      *(f32x4*)&sum_lds[row * RS + c] = x * (1.0f / (dp_raise * raise));
+      if (BY_PIECES && r0 + row < N) atomicOr(&mark_lds[row], row_mark(x) & kRowAgain);
     }
     __syncthreads();
     for (int i = tid; i < kTile * D / 4; i += W * 64) {

@@ -174,6 +174,10 @@ inline bool float_by_pieces(const Problem& pb) {
   return (G == 2 || G == 4) && (pb.d == 64 || pb.side == 1) && pb.Nk > 8 * kTile && pb.scale <= 0x1p20f;
 }
 
+// A float times 2^24 is the sum of its pieces whatever its size, up to 2^103: its last bit, 2^-125 at least, is within bf16's range.
+// Larger ones come out infinite or NaN and are taken again.
+constexpr float kRaise = 0x1p24f;
+
 // Which scores are taken by pieces, in every kernel alike (P = exp(S - lse) wants the S that lse was taken of): those of a query
 // row (its sampled channels; all of them in the mirrored form) and a key row below 2^60. What pieces lose of the smallest floats
 // is then 2^-60 of a score at most, and the scale is no larger than 2^20. The other scores are float products, pair by pair, in a

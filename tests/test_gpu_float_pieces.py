@@ -168,3 +168,47 @@ def test_scores_of_both_passes(case, what):
     assert (o.double() - want).norm() <= 1e-6 * want.norm()
     want = torch.matmul(p.transpose(2, 3).contiguous(), dout.double()).view(1, Hkv, -1, Nk, d).sum(2)
     assert (dv.double() - want).norm() <= 2e-6 * want.norm()
+
+
+def _apart(x, channel, by, others):
+    """One channel times `by`, the others times `others`."""
+    x = x * others
+    x[..., channel] *= by / others
+    return x
+
+
+@pytest.mark.parametrize("case", [c for c in BACKWARD if c[3] > 256] + [(64, 64, 129, 300, 64, 2, True, 0), (64, 64, 130, 290, 64, 4, True, 0)], ids=str)
+@pytest.mark.parametrize("what", ["small v", "small v, large dout", "large v, small dout", "a channel of v and dout", "a channel of v and dout, small others",
+                                  "small k"])
+def test_gradients_of_operands_far_apart(case, what):
+    """V and dO, or K, that are far from one in all channels or in one: every product of the backward keeps the bits of its operands. Against
+    64 bits, what is of another size by itself; bound as above."""
+    import torch
+    H, Hkv, N, Nk, d, G, causal, side = case
+    q, k, v = _inputs(case)
+    dout = torch.randn(q.shape, generator=torch.Generator(device="cuda").manual_seed(25), device="cuda")
+    if what == "small v":
+        v = v * 2.0 ** -115
+    elif what == "small v, large dout":
+        v, dout = v * 2.0 ** -118, dout * 2.0 ** 70
+    elif what == "large v, small dout":
+        v, dout = v * 2.0 ** 110, dout * 2.0 ** -118
+    elif what == "a channel of v and dout":
+        v, dout = _apart(v, 9, 2.0 ** 120, 1.0), _apart(dout, 9, 2.0 ** -120, 1.0)
+    elif what == "a channel of v and dout, small others":
+        v, dout = _apart(v, 9, 2.0 ** 90, 2.0 ** -16), _apart(dout, 9, 2.0 ** -122, 2.0 ** -16)
+    elif what == "small k":
+        k = k * 2.0 ** -105
+    dq, dk, dv = _backward(case, q, k, v, dout)
+    o, lse, hidden = _plain(case, q, k, v)
+    kk, vv = (x.double().repeat_interleave(H // Hkv, dim=1) for x in (k, v))
+    p = torch.exp((torch.matmul(q.double(), kk.transpose(2, 3).contiguous()) * 0.02).masked_fill(hidden, -math.inf) - lse[..., None])
+    g = dout.double()
+    ds = p * (torch.matmul(g, vv.transpose(2, 3).contiguous()) - (g * o).sum(-1, keepdim=True)) * 0.02
+    for name, got, want in (("dq", dq.double().sum(-1), torch.matmul(ds, kk).sum(-1)),
+                            ("dk", dk.double(), torch.matmul(ds.transpose(2, 3).contiguous(), q.double()).view(1, Hkv, -1, Nk, d).sum(2)),
+                            ("dv", dv.double(), torch.matmul(p.transpose(2, 3).contiguous(), g).view(1, Hkv, -1, Nk, d).sum(2))):
+        for part in (slice(0, 9), slice(9, 10), slice(10, None)) if name == "dv" else (slice(None),):
+            a, b = got[..., part], want[..., part]
+            unit = b.abs().max()
+            assert unit > 0 and ((a - b) / unit).norm() <= 4e-6 * (b / unit).norm(), (name, part)
