@@ -343,13 +343,13 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
       if constexpr (BY_PIECES) {
         f32x16 x;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = ps[i];
+        for (int i = 0; i < 16; ++i) x[i] = ps[i] * kRaise;
         Pieces p0, p1, v0, v1;
         splitter(x, p0, p1);
 #pragma unroll
         for (int mb = 0; mb < NB; ++mb) {
 #pragma unroll
-          for (int i = 0; i < 16; ++i) x[i] = Pair<E>::value(vreg[i][mb >> 1], mb & 1);
+          for (int i = 0; i < 16; ++i) x[i] = Pair<E>::value(vreg[i][mb >> 1], mb & 1) * kRaise;
           splitter(x, v0, v1);
           oacc[mb] = mfma(v0, p0, oacc[mb]);
           oacc[mb] = mfma(v1, p1, oacc[mb]);
@@ -379,6 +379,12 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
 #pragma unroll
     for (int j = 0; j < NW; ++j) l_all += stat_lds[j][1][lq] * __builtin_amdgcn_exp2f((stat_lds[j][0][lq] - m_all) * scale_log2e);
     const float weight = __builtin_amdgcn_exp2f((m_run - m_all) * scale_log2e) / l_all;
+    if constexpr (BY_PIECES) {
+#pragma unroll
+      for (int mb = 0; mb < NB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[mb][i] *= 1.0f / (kRaise * kRaise);
+    }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int m = acc_row(i, hh);
@@ -401,7 +407,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
         f32x4 x = *(const f32x4*)&k_lds[0][row * RS + c];
 #pragma unroll
         for (int j = 1; j < NW; ++j) x += *(const f32x4*)&k_lds[j][row * RS + c];
-        if constexpr (BY_PIECES) atomicOr(&mark_lds[row], row_mark(x));
+        if (BY_PIECES && !all_finite(x)) atomicOr(&mark_lds[row], kRowAgain);
         E* dst = o + ((size_t)bh * N + r0 + row) * D + c;
         if constexpr (std::is_same<E, float>::value) {
           *(f32x4*)dst = x;
@@ -416,7 +422,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     find_q_beyond();
     __syncthreads();
     k_again = mark_lds[kTile] != 0;
-    return rows_again(mark_lds[lq]) | q_beyond;
+    return rows_of((mark_lds[lq] & kRowAgain) != 0) | q_beyond;
   };
   if constexpr (PIECES) {
     const uint32_t again = pass(std::true_type(), ~0u);

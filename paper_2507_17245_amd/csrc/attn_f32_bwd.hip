@@ -820,7 +820,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
           f32x4 x = *(const f32x4*)&do_lds[0][do_at(row, c)];
 #pragma unroll
           for (int j = 1; j < W; ++j) x += *(const f32x4*)&do_lds[j][do_at(row, c)];
-          if (BY_PIECES && of) atomicOr(&mark_lds[row], row_mark(x) & kRowAgain);
+          if (BY_PIECES && of && !all_finite(x)) atomicOr(&mark_lds[row], kRowAgain);
           *(f32x4*)((of ? dk : dv) + ((size_t)bk * Nk + n0 + row) * D + c) = of ? x * (1.0f / dp_raise) * scale : x;
         }
       }
@@ -829,7 +829,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
     if (any_beyond != 0) atomicOr(&mark_lds[kTile], 1u);
     __syncthreads();
     q_again = mark_lds[kTile] != 0;
-    return rows_again(mark_lds[lq]);
+    return rows_of((mark_lds[lq] & kRowAgain) != 0);
   };
   const uint32_t again = pass(std::true_type(), ~0u);
   if (again == 0 && !q_again) return;
@@ -1254,7 +1254,7 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
 #pragma unroll
       for (int j = 1; j < W; ++j) x += *(const f32x4*)&k_lds[j][row * RS + c];
       *(f32x4*)&sum_lds[row * RS + c] = x * (1.0f / (dp_raise * raise));
-      if (BY_PIECES && r0 + row < N) atomicOr(&mark_lds[row], row_mark(x) & kRowAgain);
+      if (BY_PIECES && r0 + row < N && !all_finite(x)) atomicOr(&mark_lds[row], kRowAgain);
     }
     __syncthreads();
     for (int i = tid; i < kTile * D / 4; i += W * 64) {
@@ -1272,7 +1272,7 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
     if (any_beyond != 0) atomicOr(&mark_lds[kTile], 1u);
     __syncthreads();
     k_again = mark_lds[kTile] != 0;
-    return rows_again(mark_lds[lq]);
+    return rows_of((mark_lds[lq] & kRowAgain) != 0);
   };
   const uint32_t again = pass(std::true_type(), ~0u);
   if (again == 0 && !k_again) return;

@@ -202,23 +202,10 @@ __device__ inline uint32_t rows_of(bool any) {
   return (uint32_t)rows | (uint32_t)(rows >> 32);
 }
 
-// What pieces do not hold as floats do: infinities and NaN (a product with them makes every sum of its row NaN), operands so
-// small that their last piece is lost, and products of such with very large ones. A workgroup looks at the results of its 32 rows
-// and takes those again that are not finite, or not zero and nowhere as large as 2^-60: all but the scores with float products.
-constexpr uint32_t kRowAgain = 1, kRowNonzero = 2, kRowLarge = 4, kRowBeyond = 8;
-__device__ inline uint32_t row_mark(f32x4 x) {
-  uint32_t mark = 0;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float a = __builtin_fabsf(x[e]);
-    mark |= (a < INFINITY ? 0u : kRowAgain) | (a != 0.0f ? kRowNonzero : 0u) | (a >= 0x1p-60f ? kRowLarge : 0u);
-  }
-  return mark;
-}
-// mark: of the lane's row; the same 32 rows in both halves of the wave
-__device__ inline uint32_t rows_again(uint32_t mark) {
-  return rows_of((mark & kRowAgain) != 0 || (mark & (kRowNonzero | kRowLarge)) == kRowNonzero);
-}
+// Infinities and NaN (a product with them makes every sum of its row NaN) and what is too large are found in the results: a workgroup
+// takes the rows of its 32 again that are not finite, all but the scores with float products.
+constexpr uint32_t kRowAgain = 1, kRowBeyond = 2;   // kRowBeyond: with a score that is not by pieces (beyond_pieces)
+__device__ inline bool all_finite(f32x4 x) { return largest(0.0f, x) < INFINITY; }
 
 // Pieces of 32 rows of C floats in LDS; rows 16 bytes apart in the banks, a lane's operand is one read per piece.
 template <int C>

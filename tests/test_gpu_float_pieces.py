@@ -172,9 +172,9 @@ def test_scores_of_both_passes(case, what):
 
 def _apart(x, channel, by, others):
     """One channel times `by`, the others times `others`."""
-    x = x * others
-    x[..., channel] *= by / others
-    return x
+    y = x * others
+    y[..., channel] = x[..., channel] * by
+    return y
 
 
 @pytest.mark.parametrize("case", [c for c in BACKWARD if c[3] > 256] + [(64, 64, 129, 300, 64, 2, True, 0), (64, 64, 130, 290, 64, 4, True, 0)], ids=str)
@@ -212,3 +212,36 @@ def test_gradients_of_operands_far_apart(case, what):
             a, b = got[..., part], want[..., part]
             unit = b.abs().max()
             assert unit > 0 and ((a - b) / unit).norm() <= 4e-6 * (b / unit).norm(), (name, part)
+
+
+PIECES_FORWARD = [(2, 1, 33, 300, 64, 2, True, 0), (64, 64, 129, 300, 64, 2, True, 0), (64, 64, 130, 290, 64, 4, True, 0), (1, 1, 300, 520, 64, 4, True, 0),
+                  (2, 1, 100, 300, 64, 2, True, 1), (64, 64, 129, 300, 64, 2, True, 1), (2, 2, 97, 300, 128, 4, True, 1), (2, 1, 97, 300, 128, 2, True, 1)]
+
+
+@pytest.mark.parametrize("case", PIECES_FORWARD, ids=str)
+@pytest.mark.parametrize("by,others", [(2.0 ** -115, 1.0), (2.0 ** 115, 1.0), (2.0 ** 60, 2.0 ** -60), (2.0 ** -60, 2.0 ** 60), (2.0 ** -118, 2.0 ** 70)])
+def test_a_channel_of_v_by_itself(case, by, others):
+    """Every channel of the output is as near to 64 bits as it is at magnitude one (bound: test_magnitudes), whatever the others are."""
+    q, k, v = _inputs(case)
+    v = _apart(v, 9, by, others)
+    o = _forward(case, q, k, v)[0].double()
+    want = _plain(case, q, k, v)[0]
+    for part in (slice(0, 9), slice(9, 10), slice(10, None)):
+        unit = want[..., part].abs().max()
+        assert ((o - want)[..., part] / unit).norm() <= 1.2e-6 * (want[..., part] / unit).norm()
+
+
+@pytest.mark.parametrize("case", PIECES_FORWARD, ids=str)
+@pytest.mark.parametrize("size", [2.0 ** 122, 2.0 ** 86, 2.0 ** 66])
+def test_small_weights_of_large_values(case, size):
+    """Weights of 2^-122 that alone have values. Bound: P = exp2 of -122, whose argument has the rounding of three products and one difference."""
+    import torch
+    q, k, v = _inputs(case)
+    q.fill_(1.0)
+    k.zero_()
+    k[:, :, :3] = -66.0 * 64 / case[4]
+    v[:, :, 3:] = 0.0
+    v[:, :, :3] *= size
+    o = _forward(case, q, k, v)[0].double() / size
+    want = _plain(case, q, k, v / size)[0]
+    assert (o - want).norm() <= 122 * 0.7 * 4 * 2.0 ** -24 * want.norm()
