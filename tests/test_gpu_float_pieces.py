@@ -1,6 +1,8 @@
 """Float products taken as bf16 pieces: what pieces do not hold as floats do (infinities, NaN, magnitudes far from one) comes out as
 float products give it, row by row, and every other row is what it is without it. Groups of two and four channels and the mirrored
-form; sizes around the tiles of 32 rows, with four and eight waves per workgroup, and Q blocks that a wave's run of tiles enters and leaves."""
+form; sizes around the tiles of 32 rows, and Q blocks that a wave's run of tiles enters and leaves. Products are by pieces from 257 keys on;
+with more than 256 row tiles (64 heads of 129 rows) the forward and dQ have four waves per workgroup, with fewer than eight query tiles
+per kv head dK/dV has, otherwise eight at d = 64."""
 import math
 
 import pytest
@@ -9,8 +11,11 @@ pytestmark = pytest.mark.gpu
 
 # H, Hkv, N, Nk, d, G, causal, side
 FORWARD = [(2, 1, 33, 65, 64, 2, True, 0), (8, 2, 200, 300, 64, 2, True, 0), (1, 1, 300, 520, 64, 4, True, 0), (3, 3, 1, 31, 64, 4, True, 0),
-           (2, 1, 100, 300, 64, 2, True, 1), (2, 2, 97, 129, 128, 4, True, 1), (1, 1, 64, 800, 64, 2, True, 1)]
-BACKWARD = [(2, 1, 33, 65, 64, 2, True, 0), (8, 2, 300, 300, 64, 2, True, 0), (2, 2, 300, 520, 64, 4, True, 0), (1, 1, 257, 257, 64, 2, True, 0)]
+           (2, 1, 100, 300, 64, 2, True, 1), (2, 2, 97, 129, 128, 4, True, 1), (1, 1, 64, 800, 64, 2, True, 1),
+           (64, 64, 129, 300, 64, 2, True, 0), (64, 32, 130, 290, 64, 4, True, 0), (3, 3, 1, 287, 64, 4, True, 0), (2, 1, 33, 257, 64, 2, True, 0),
+           (64, 64, 129, 300, 64, 4, True, 1), (64, 64, 129, 300, 64, 2, True, 1), (2, 2, 97, 300, 128, 4, True, 1), (2, 1, 97, 300, 128, 2, True, 1)]
+BACKWARD = [(2, 1, 33, 65, 64, 2, True, 0), (8, 2, 300, 300, 64, 2, True, 0), (2, 2, 300, 520, 64, 4, True, 0), (1, 1, 257, 257, 64, 2, True, 0),
+            (64, 64, 129, 300, 64, 2, True, 0), (64, 64, 130, 290, 64, 4, True, 0), (2, 1, 33, 300, 64, 2, True, 0), (2, 1, 33, 260, 64, 4, True, 0)]
 
 
 def _inputs(case):
@@ -177,7 +182,7 @@ def _apart(x, channel, by, others):
     return y
 
 
-@pytest.mark.parametrize("case", [c for c in BACKWARD if c[3] > 256] + [(64, 64, 129, 300, 64, 2, True, 0), (64, 64, 130, 290, 64, 4, True, 0)], ids=str)
+@pytest.mark.parametrize("case", [c for c in BACKWARD if c[3] > 256], ids=str)
 @pytest.mark.parametrize("what", ["small v", "small v, large dout", "large v, small dout", "a channel of v and dout", "a channel of v and dout, small others",
                                   "small k"])
 def test_gradients_of_operands_far_apart(case, what):
@@ -245,3 +250,27 @@ def test_small_weights_of_large_values(case, size):
     o = _forward(case, q, k, v)[0].double() / size
     want = _plain(case, q, k, v / size)[0]
     assert (o - want).norm() <= 122 * 0.7 * 4 * 2.0 ** -24 * want.norm()
+
+
+@pytest.mark.parametrize("case", [c for c in PIECES_FORWARD if c[7]], ids=str)
+@pytest.mark.parametrize("what", ["ordinary", "infinite k", "nan", "large k", "large q", "a channel of v", "infinite v"])
+def test_mirrored_form_of_bf16_tensors(case, what):
+    """The same arithmetic as for float tensors of these values, rounded at the end."""
+    import torch
+    q, k, v = (x.bfloat16() for x in _inputs(case))
+    if what == "infinite k":
+        k[:, :, 4:40] = -math.inf
+    elif what == "nan":
+        k[:, :, -3, 7] = math.nan
+    elif what == "large k":
+        k[:, :, 11::37] *= 2.0 ** 70
+    elif what == "large q":
+        q[:, :, 1::9] *= 2.0 ** 70
+    elif what == "a channel of v":
+        v = _apart(v, 9, 2.0 ** -115, 1.0)
+    elif what == "infinite v":
+        v[:, :, -2, 3] = math.inf
+    o = _forward(case, q, k, v)[0]
+    want = _forward(case, q.float(), k.float(), v.float())[0].bfloat16()
+    assert torch.equal(torch.isnan(o), torch.isnan(want)) and torch.isnan(o).any() == (what in ("nan", "infinite v"))
+    assert torch.equal(o.nan_to_num(nan=0.0, posinf=1.0), want.nan_to_num(nan=0.0, posinf=1.0))
