@@ -20,7 +20,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak (published)
-PEAK_FP32_TFLOPS = 157.3   # MI355X fp32 vector peak
+PEAK_FP32_TFLOPS = 157.3   # MI355X fp32 peak, vector and float matrix instruction
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E peak (published)
 
 
@@ -229,8 +229,10 @@ def main():
     def float_path_table(steps):
         """The float (reference-precision) path on a shape large enough to fill the chip: forward,
         the mirrored form that samples K and fuses Q (Sec. 3.1, Fig. 4 right), and the backward
-        pass (gradient with the grouping held fixed), each with the exact counterpart and the
-        executed FLOPs against the fp32 vector peak (these kernels are built for accuracy checks)."""
+        pass (gradient with the grouping held fixed), each with the exact counterpart. alu_frac: the
+        call's FLOPs against the fp32 peak, which for the grouped calls (products of three bf16 pieces a
+        float) is a rate only; pipe_frac: the share of the time that the matrix pipes need for its products
+        at their peaks, six bf16 products for one by pieces."""
         cfg = W.CONFIGS["tiny"].scaled(name="float", H=8, Hkv=8, N=2048, Br=128, n_planes=16, recipe="normal")
         q, k, v = (to_dev(x, "f32") for x in W.make(cfg))
         dout = to_dev(W.make_grad(cfg), "f32")
@@ -253,7 +255,9 @@ def main():
         for name, (fn, fl) in runs.items():
             fn()
             ms = ev_time(fn, steps)
-            out[name] = {"ms": ms, "alu_frac": fl / (ms * 1e-3) / 1e12 / PEAK_FP32_TFLOPS}
+            rate = fl / (ms * 1e-3) / 1e12
+            out[name] = {"ms": ms, "alu_frac": rate / PEAK_FP32_TFLOPS,
+                         "pipe_frac": rate / PEAK_FP32_TFLOPS if name == "forward_exact" else 6.0 * rate / PEAK_BF16_TFLOPS}
         # backward: the dQ and the dK/dV kernel each rebuild the scores and dP, and add dQ, or dK and dV: 7 products. Groups of two and four
         # take scores, dQ and dK over the groups; other sizes all of them over the channels, like the exact call
         width = cfg.n_groups if cfg.d // cfg.n_groups in (2, 4) else cfg.d
@@ -262,12 +266,15 @@ def main():
         bw_d = lambda: da.distr_attn_bwd_ex(q, k, v, o, dout, lse, dq, dk, dv, p_d)
         bw_d()
         ms = ev_time(bw_d, steps)
-        out["backward"] = {"ms": ms, "alu_frac": bw_fl_d / (ms * 1e-3) / 1e12 / PEAK_FP32_TFLOPS}
+        fl_float = 2.0 * pairs * (width + cfg.d)   # dK and dV: on the float instruction
+        out["backward"] = {"ms": ms, "alu_frac": bw_fl_d / (ms * 1e-3) / 1e12 / PEAK_FP32_TFLOPS,
+                           "pipe_frac": (6.0 * (bw_fl_d - fl_float) / PEAK_BF16_TFLOPS + fl_float / PEAK_FP32_TFLOPS) / (ms * 1e-3) / 1e12}
         da.distr_attn_exact_fwd_ex(q, k, v, o, p_e)
         bw_e = lambda: da.distr_attn_exact_bwd_ex(q, k, v, o, dout, lse, dq, dk, dv, p_e)
         bw_e()
         ms = ev_time(bw_e, steps)
-        out["backward_exact"] = {"ms": ms, "alu_frac": bw_fl_e / (ms * 1e-3) / 1e12 / PEAK_FP32_TFLOPS}
+        out["backward_exact"] = {"ms": ms, "alu_frac": bw_fl_e / (ms * 1e-3) / 1e12 / PEAK_FP32_TFLOPS,
+                                 "pipe_frac": bw_fl_e / (ms * 1e-3) / 1e12 / PEAK_FP32_TFLOPS}
         return out
 
     def backward_table(cfg, tensors, steps):

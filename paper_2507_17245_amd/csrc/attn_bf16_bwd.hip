@@ -528,9 +528,9 @@ __global__ __launch_bounds__(kBwdThreads, (D == 64 ? 2 : 1)) void bwd_dkv_kernel
     const float* lse_lds = par ? lse_lds1 : lse_lds0;
     const float* dl_lds = par ? dl_lds1 : dl_lds0;
     const int i0 = i_start + kBwdStream * (it % tiles);
-    // Register classes, stated once per tile: the accumulators of dK and dV live in the
-    // accumulator half of the register file, the resident K and V operands in the vector half
-    // (left to itself the allocator moved 128 accumulator registers back and forth per tile).
+    // Register classes, stated once per tile: the accumulators of dK and dV and the resident K and V
+    // operands live in the accumulator half of the register file, the operands read from LDS in the vector
+    // half (left to itself the allocator moved 128 accumulator registers back and forth per tile).
     if constexpr (D == 128) {
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) asm volatile("" : "+a"(dkacc[cb]), "+a"(dvacc[cb]));

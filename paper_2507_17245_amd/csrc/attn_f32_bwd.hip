@@ -82,8 +82,8 @@ struct Tile {
   }
 };
 
-  // The tile straight into LDS rows of D floats whose 16-byte pieces are exchanged by the row (what was read there has arrived).
-  template <int D, int G>
+// The tile straight into LDS, rows of D floats with 16 bytes behind every 256 floats (what was read there has arrived).
+template <int D>
 struct TileToLds {
   static constexpr int KU = Tile<D>::KU, BYTES = Tile<D>::BYTES, FLOATS = KU * 260;
   // Float c of a row: one instruction leaves 256 floats in a row (four rows at D = 64), 16 bytes lie between two instructions'.
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
   constexpr int NB = D / 32, RS = Tile<D>::RS;
   constexpr int KRED = D / G, HS = KRED / 2, RQ = KRED + 4, NG = (KRED + 31) / 32, ROWS = 64 / KRED, QL = kTile / ROWS;
   __shared__ __attribute__((aligned(16))) float q_lds[W][kTile * RQ];                  // Q_r tile of each wave: KRED sampled channels a row, in groups' order
-  __shared__ __attribute__((aligned(16))) float do_lds[W][TileToLds<D, G>::FLOATS];   // dO tile, at the end dV and dK
+  __shared__ __attribute__((aligned(16))) float do_lds[W][TileToLds<D>::FLOATS];   // dO tile, at the end dV and dK
   __shared__ __attribute__((aligned(16))) float k_lds[kTile * RS];                        // of the workgroup's keys
   __shared__ __attribute__((aligned(16))) PieceRows<D> v_lds;
   __shared__ __attribute__((aligned(16))) float stat_lds[W][2][kTile];   // lse, D_i
@@ -582,11 +582,11 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
     delta_reg = delta[bh * N + row];
   };
   // straight into LDS, behind the last reads of the tile before
-  const TileToLds<D, G> to_lds(lane);
+  const TileToLds<D> to_lds(lane);
   auto load_do = [&](int it) {
     to_lds.load(head_rsrc(dout + head_of(it) * N * D, (unsigned)N * D * 4), tile_of(it), do_lds[w]);
   };
-  auto do_at = [&](int row, int c) { return TileToLds<D, G>::at(row, c); };
+  auto do_at = [&](int row, int c) { return TileToLds<D>::at(row, c); };
   // the waves deal out runs of tiles, so that a wave stays in a Q block
   const int it_first = n_it * w / W, it_end = n_it * (w + 1) / W;
   int slot = 0;

@@ -56,7 +56,8 @@ struct ChannelSum {
 };
 
 // Eight floats as operands of v_mfma_f32_32x32x16_bf16: hi + mid + lo with eight significand bits each (rounded to
-// nearest, so that mid and lo are at most 2^-9 and 2^-17 of the float), together the float itself.
+// nearest, so that mid and lo are at most 2^-8 and 2^-17 of the float), together the float itself unless it is below 2^-110
+// (bf16 ends at 2^-133) or so near the largest that hi is infinite.
 struct Pieces {
   bf16x8 hi, mid, lo;
 };
@@ -102,7 +103,7 @@ struct Splitter {
     p1.lo = round8(x.hi);
   }
 };
-// c += a b without what mid lo, lo mid and lo lo add (2^-25 of a b at most), the small products first.
+// c += a b without what mid lo, lo mid and lo lo add (2^-24 of a b at most), the small products first.
 __device__ inline f32x16 mfma_rest(const Pieces& a, const Pieces& b, f32x16 c) {
   c = mfma(a.lo, b.hi, c);
   c = mfma(a.hi, b.lo, c);
