@@ -143,8 +143,8 @@ int distr_attn_exact_fwd_ex(const void *q, const void *k, const void *v, void *o
  * before the products that take them), d in {64, 128}, any n_groups that divides d. float tensors:
  * float arithmetic (a reference-precision path): products on the float matrix instruction or, in groups of
  * two and four channels, of the three bf16 pieces that make up each float (what that leaves out is 2^-24 of a
- * product at most; gradients measured no farther from 64 bits). Scores of query or key rows that reach 2^60,
- * and results that pieces make infinite or NaN, are taken on the float instruction.
+ * product at most; gradients measured no farther from 64 bits). Scores with an operand that reaches 2^60, and
+ * results that pieces make infinite or NaN, are taken on the float instruction.
  * q, k, v, p: as given to the forward; o: its output; lse: its lse_out; dout [B][H][N][d]: gradient
  * of the loss with respect to o, same dtype. Written: dq [B][H][N][d], dk and dv [B][Hkv][Nk][d]
  * (p->dtype, device, 16-byte aligned, distinct from every input and from each other). The grouping is recomputed

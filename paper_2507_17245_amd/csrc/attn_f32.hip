@@ -139,6 +139,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
   bool k_again = false;
   auto pass = [&](auto pieces, uint32_t rows) -> uint32_t {
     constexpr bool BY_PIECES = decltype(pieces)::value;
+    constexpr float raise_v = std::is_same<E, float>::value ? kRaise : 1.0f;   // (a bf16 value is its first piece)
     const Splitter splitter(lane);
     float qop[HS];
     if constexpr (MODE == kQueryFused) {
@@ -187,11 +188,9 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     while (tile < n_tiles) {
       // ---- stage the K tile (and, mirrored, the K block's grouping) -------------------------------
       wave_order();   // the reads of the previous tile come first
-      float k_largest = 0.0f;
 #pragma unroll
       for (int u = 0; u < KU; ++u) {
         const f32x4 x = Quad<E>::values(kreg[u]);
-        if constexpr (BY_PIECES) k_largest = largest(k_largest, x);
         const int row = (u * 64 + lane) / (D / 4), c = (u * 64 + lane) % (D / 4) * 4;
         if constexpr (MODE == kQueryFused) {
 #pragma unroll
@@ -200,7 +199,6 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
           *(f32x4*)&kt[row * RS + c] = x;
         }
       }
-      if constexpr (BY_PIECES) any_beyond |= rows_of(beyond_pieces(k_largest));
       const bool new_block = kMirrored && tile % TB == 0;
       if constexpr (kMirrored) {
         if (new_block) {
@@ -293,16 +291,14 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
       }
       f32x16 sacc;
       if constexpr (PIECES) {
+        if constexpr (BY_PIECES) any_beyond |= rows_of(beyond_pieces(largest(kop)));
         split_steps<HS>(splitter, kop, [&](int s, const Pieces& p) { by_pieces.step(p, qpc[s]); });
         sacc = by_pieces.sum();
       }
       if constexpr (!PIECES) {
         sacc = by_floats.sum();
       } else if constexpr (!BY_PIECES) {
-        float m = 0.0f;
-#pragma unroll
-        for (int c = 0; c < D / 2; c += 4) m = largest(m, *(const f32x4*)&kt[lq * RS + hh * (D / 2) + c]);
-        const uint32_t k_beyond = rows_of(beyond_pieces(m));
+        const uint32_t k_beyond = rows_of(beyond_pieces(largest(kop)));
         if (k_beyond != 0 && tile * kTile + __builtin_ctz(k_beyond) <= lim) atomicOr(&mark_lds[lq], kRowBeyond);
         if ((q_beyond | k_beyond) != 0) {
 #pragma unroll
@@ -351,7 +347,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
 #pragma unroll
         for (int mb = 0; mb < NB; ++mb) {
 #pragma unroll
-          for (int i = 0; i < 16; ++i) x[i] = Pair<E>::value(vreg[i][mb >> 1], mb & 1) * kRaise;
+          for (int i = 0; i < 16; ++i) x[i] = Pair<E>::value(vreg[i][mb >> 1], mb & 1) * raise_v;
           splitter(x, v0, v1);
           oacc[mb] = mfma(v0, p0, oacc[mb]);
           oacc[mb] = mfma(v1, p1, oacc[mb]);
@@ -385,7 +381,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
 #pragma unroll
       for (int mb = 0; mb < NB; ++mb)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[mb][i] *= 1.0f / (kRaise * kRaise);
+        for (int i = 0; i < 16; ++i) oacc[mb][i] *= 1.0f / (kRaise * raise_v);
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {

@@ -524,7 +524,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
   __shared__ __attribute__((aligned(16))) float k_lds[kTile * RS];                        // of the workgroup's keys
   __shared__ __attribute__((aligned(16))) PieceRows<D> v_lds;
   __shared__ __attribute__((aligned(16))) float stat_lds[W][2][kTile];   // lse, D_i
-  __shared__ uint32_t mark_lds[kTile + 1];   // what is known of a key's row (kRowAgain ..); whether a query row is beyond_pieces
+  __shared__ uint32_t mark_lds[kTile + 1];   // what is known of a key's row (kRowAgain ..); whether a score's operand is beyond_pieces
   __shared__ __attribute__((aligned(16))) uint8_t map_lds[W][4][D];   // of this Q block and the one before or after it: sorted order, the channels' groups
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -616,15 +616,10 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
     v_lds.store(lq, at, split(f32x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]} * kRaise));
   }
   __syncthreads();
-  if (w == 0) {
-#pragma unroll
-    for (int u = 0; u < Tile<D>::KU; ++u)
-      if (beyond_pieces(largest(0.0f, Q4::values(kt.x[u])))) atomicOr(&mark_lds[(u * 64 + lane) / (D / 4)], kRowAgain);
-  }
   // The rows (keys) of the bit mask `rows`, S^ and dP by pieces or on the float instruction. By pieces, the rows to be taken again are
-  // returned; a second walk takes the scores by pieces that the first took by them (beyond_pieces), and with q_again set it is for
-  // the keys, too, that a query row sees which is not held by pieces.
-  bool q_again = false;
+  // returned; a second walk takes the scores by pieces that the first took by them (beyond_pieces), and with s_again set it is for
+  // the keys, too, that have other scores.
+  bool s_again = false;
   auto pass = [&](auto pieces, uint32_t rows) -> uint32_t {
     constexpr bool BY_PIECES = decltype(pieces)::value;
     constexpr float raise = BY_PIECES ? kRaise : 1.0f, dp_raise = raise * raise;   // of dO and V; of dP, D_i, dS and dK_f
@@ -639,13 +634,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
     Pieces kf[HS / 8];
     f32x16 dkf[NG];
     uint32_t any_beyond = 0;
-    bool key_beyond = false;
-    if constexpr (!BY_PIECES) {
-      float m = 0.0f;
-#pragma unroll
-      for (int c = 0; c < D / 2; c += 4) m = largest(m, *(const f32x4*)&k_lds[lq * RS + hh * (D / 2) + c]);
-      key_beyond = (rows_of(beyond_pieces(m)) >> lq & 1) != 0;
-    }
+    uint32_t key_beyond = 0;   // of the Q block the wave is in
     auto fused_keys = [&](float (&sum)[HS]) {
 #pragma unroll
       for (int c = 0; c < D / 2; c += 8) {
@@ -662,6 +651,8 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
     auto fuse_keys = [&]() {
       float sum[HS];
       fused_keys(sum);
+      key_beyond = rows_of(beyond_pieces(largest(sum)));
+      if constexpr (BY_PIECES) any_beyond |= key_beyond;
       split_steps<HS>(splitter, sum, [&](int s, const Pieces& p) { kf[s] = p; });
 #pragma unroll
       for (int mb = 0; mb < NG; ++mb) zero(dkf[mb]);
@@ -725,8 +716,8 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
         }
         if constexpr (!BY_PIECES) {
           const uint32_t q_beyond = rows_of(beyond_pieces(largest(x)));
-          if (q_beyond != 0 && i0 + 31 - __builtin_clz(q_beyond) >= see_from) atomicOr(&mark_lds[lq], kRowBeyond);
-          if (q_beyond != 0 || rows_of(key_beyond) != 0) {
+          if ((q_beyond != 0 && i0 + 31 - __builtin_clz(q_beyond) >= see_from) || (key_beyond >> lq & 1) != 0) atomicOr(&mark_lds[lq], kRowBeyond);
+          if ((q_beyond | key_beyond) != 0) {
             ChannelSum<HS> acc;
             float y[HS];
             fused_keys(y);
@@ -734,7 +725,7 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
             for (int s = 0; s < HS; ++s) acc.step(s, x[s], y[s]);
             const f32x16 z = acc.sum();
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[i] = key_beyond || (q_beyond >> acc_row(i, hh) & 1) != 0 ? z[i] : s[i];
+            for (int i = 0; i < 16; ++i) s[i] = ((key_beyond >> lq | q_beyond >> acc_row(i, hh)) & 1) != 0 ? z[i] : s[i];
           }
         }
       }
@@ -828,11 +819,11 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
     if constexpr (!BY_PIECES) return 0;
     if (any_beyond != 0) atomicOr(&mark_lds[kTile], 1u);
     __syncthreads();
-    q_again = mark_lds[kTile] != 0;
+    s_again = mark_lds[kTile] != 0;
     return rows_of((mark_lds[lq] & kRowAgain) != 0);
   };
   const uint32_t again = pass(std::true_type(), ~0u);
-  if (again == 0 && !q_again) return;
+  if (again == 0 && !s_again) return;
   load_first();
   pass(std::false_type(), again);
 }
@@ -1136,12 +1127,6 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
       }
       wave_order();
       kt.scatter(k_lds[w], lane, kdst);
-      if constexpr (BY_PIECES) {
-        float m = 0.0f;
-#pragma unroll
-        for (int u = 0; u < Tile<D>::KU; ++u) m = largest(m, Q4::values(kt.x[u]));
-        any_beyond |= rows_of(beyond_pieces(m));
-      }
       if (tile + W < n_tiles) {
         kt.load(k_rsrc, tile + W, lane);
         vt.load(v_rsrc, tile + W, lane);
@@ -1161,11 +1146,10 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
         }
         dp = acc.sum();
       }
-      float y[HS], m = 0.0f;
+      float y[HS];
 #pragma unroll
       for (int c = 0; c < D / 2; c += 4) {
         const f32x4 x = *(const f32x4*)&k_lds[w][lq * RS + hh * (D / 2) + c];
-        if constexpr (!BY_PIECES) m = largest(m, x);
         if constexpr (G == 2) {
           y[c / 2] = x[0] + x[1];
           y[c / 2 + 1] = x[2] + x[3];
@@ -1173,6 +1157,8 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
           y[c / 4] = ((x[0] + x[1]) + x[2]) + x[3];
         }
       }
+      const uint32_t k_beyond = rows_of(beyond_pieces(largest(y)));
+      any_beyond |= k_beyond;
       f32x16 s;
       {
         PieceSum acc;
@@ -1184,7 +1170,7 @@ __global__ __launch_bounds__(W * 64, (D == 64 ? 2 : 1)) void bwd_dq_pieces_kerne
 #pragma unroll
         for (int c = 0; c < HS; ++c)
           qop[c] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(q_rsrc, (lq * D + order_lds[(hh * HS + c) * G]) * 4, r0 * (D * 4), 0));
-        const uint32_t q_beyond = rows_of(beyond_pieces(largest(qop))), k_beyond = rows_of(beyond_pieces(m));
+        const uint32_t q_beyond = rows_of(beyond_pieces(largest(qop)));
         if (k_beyond != 0 && tile * kTile + __builtin_ctz(k_beyond) <= lim) atomicOr(&mark_lds[lq], kRowBeyond);
         if ((q_beyond | k_beyond) != 0) {
           ChannelSum<HS> acc;

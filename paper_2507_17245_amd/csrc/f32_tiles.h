@@ -179,10 +179,11 @@ inline bool float_by_pieces(const Problem& pb) {
 // Larger ones come out infinite or NaN and are taken again.
 constexpr float kRaise = 0x1p24f;
 
-// Which scores are taken by pieces, in every kernel alike (P = exp(S - lse) wants the S that lse was taken of): those of a query
-// row (its sampled channels; all of them in the mirrored form) and a key row below 2^60. What pieces lose of the smallest floats
-// is then 2^-60 of a score at most, and the scale is no larger than 2^20. The other scores are float products, pair by pair, in a
-// second walk of the workgroups that have such rows.
+// Which scores are taken by pieces, in every kernel alike (P = exp(S - lse) wants the S that lse was taken of): those whose operands,
+// the sampled channels of a query row and the sums of a key row over the Q block's groups (the mirrored form: all channels of
+// the query row, the sampled ones of the key row), are below 2^60. What pieces lose of the smallest floats is then 2^-60 of a
+// score at most, and the scale is no larger than 2^20. The other scores are float products, pair by pair, in a second walk of
+// the workgroups that have such rows.
 constexpr float kPieceLimit = 0x1p60f;
 __device__ inline float largest(float m, float x, float y) {   // (of magnitudes; NaN stays)
   return __builtin_elementwise_maximum(m, __builtin_elementwise_maximum(__builtin_fabsf(x), __builtin_fabsf(y)));
