@@ -170,7 +170,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
       }
       q_beyond = rows_of(beyond_pieces(m));
     };
-    if constexpr (PIECES && !BY_PIECES) find_q_beyond();
+    if constexpr (PIECES) find_q_beyond();
     float* kt = k_lds[w];
     int koff[kMirrored ? HS : 1];   // channel of the K row that contraction slot s takes (mirrored form)
     f32x16 oacc[NB];
@@ -417,7 +417,6 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     }
     if constexpr (!BY_PIECES) return 0;
     if (any_beyond != 0) atomicOr(&mark_lds[kTile], 1u);
-    find_q_beyond();
     __syncthreads();
     k_again = mark_lds[kTile] != 0;
     return rows_of((mark_lds[lq] & kRowAgain) != 0) | q_beyond;
