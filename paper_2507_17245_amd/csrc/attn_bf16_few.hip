@@ -262,16 +262,16 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
         const char* p0 = vb + va_off[mb] + 16 * tt * ROWB;
         oacc[mb] = mfma_32x32x16(lds_read_tr_pair<bf16x8>(p0, p0 + 8 * ROWB), pop[tt], oacc[mb]);
       }
-    // Where the loop ends the compiler waits for these products by its longest way out; on the shortest their sums would be
-    // read two instructions early.
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 1");
   };
   while (tile < t1) {
     step(even, tile);
     tile += kFewWaves;
     if (tile >= t1) break;
     step(odd, tile);
+    // Where the loop ends the compiler waits for these products by its longest way out; on the shortest their sums would be
+    // read two instructions early.
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 1");
     tile += kFewWaves;
   }
 
