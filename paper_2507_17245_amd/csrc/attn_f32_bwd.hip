@@ -510,7 +510,8 @@ __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_kernel(
 // Groups of two and four channels at d = 64, from more than eight key tiles on (float_by_pieces): S^ and dP by bf16 pieces (V's lie
 // in LDS, K_f's in registers for a Q block), in the same order as the forward, whose lse P = exp(S^ - lse) rests on; dV and dK_f on
 // the float instruction, tile by tile. By pieces these need 48 registers more: 70 spilled, and dK/dV took 244 us; with one wave per SIMD and
-// none spilled 164. The dO tile comes straight into LDS as soon as its columns have been read (through registers, 32 spilled: 148).
+// none spilled 164. dO and V are raised by 2^24 before they are split (groups of four, H16 N1500: whole backward 195 -> 199 us), a second
+// walk takes what pieces do not hold. The dO tile comes straight into LDS as soon as its columns have been read (through registers, 32 spilled: 148).
 // Bound: issue and both matrix instructions' time. B1 H8 N2048 n_groups 32: 141 -> 126 us, 16 groups 128 -> 115.
 template <int D, int W, int G>
 __global__ __launch_bounds__(W * 64, W / 4) void bwd_dkv_pieces_kernel(
