@@ -150,6 +150,45 @@ struct Cfg {
 // overflowed or NaN sum fails the comparison too), and the sum is needed anyway.
 constexpr float kTau = 8.0f;
 
+// Row sums of P, the B operands of P.V (lane = row lane % 32, either half of the wave its half of the keys). They are taken over the
+// rounded P, the values P.V really uses: numerator and denominator then carry the same rounding, which cancels for rows dominated
+// by few keys. On the matrix pipe: v_mfma_f32_16x16x32_bf16 takes lanes 16 g .. 16 g + 15 as rows 8 g .. of a 32 x 16 operand,
+// whose groups g = 0, 2 belong to rows 0..15 of P and g = 1, 3 to rows 16..31; the left operand has ones where the group is that of
+// the result's lane and zeros elsewhere, so that every lane receives the whole sum of its own row. 16 cycles of the pipe for eight
+// values a lane. (v_dot2c_f32_bf16 against (1, 1), one for two values, is no vector instruction like the others: it waits for the
+// matrix pipe and holds it up, 13 cycles each between products. 8 exponentials with 3, 4, 6, 8 products beside them,
+// cycles by dot products | by this one, two waves per SIMD: 177 | 136, 209 | 160, 256 | 214, 310 | 273.)
+// An infinity or a NaN in a row makes the sum of the row 16 away NaN, too (zero times it): a tile with sums that are not finite takes
+// them again by_lanes, with dot products. (Keeping the matrix pipe's sums of the other rows there, to the last bit, cost every call 1-2 %.)
+struct RowSum {
+  bf16x8 own;
+  __device__ explicit RowSum(int lane) {
+    const bf16 x = (bf16)(((lane >> 2 ^ lane >> 4) & 1) == 0 ? 1.0f : 0.0f);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) own[j] = x;
+  }
+  template <int TT>
+  __device__ float operator()(const bf16x8 (&pop)[TT]) const {
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(own, pop[tt], acc, 0, 0, 0);
+    return acc[0];
+  }
+  template <int TT>
+  static __device__ float by_lanes(const bf16x8 (&pop)[TT]) {
+    const bf16x2 ones = {(bf16)1.0f, (bf16)1.0f};
+    float rs0 = 0.0f, rs1 = 0.0f;
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int j = 0; j < 8; j += 4) {
+        rs0 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pop[tt][j], pop[tt][j + 1]}, ones, rs0, false);
+        rs1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pop[tt][j + 2], pop[tt][j + 3]}, ones, rs1, false);
+      }
+    return half_swap_sum(rs0 + rs1);
+  }
+};
+
 template <int D, int BR, int BC, int KRED, int MODE, int NG, int KS>
 __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::WAVES_PER_SIMD)) void attn_bf16_kernel(
     const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
@@ -159,7 +198,12 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
     uint8_t* __restrict__ perm_w, int n_groups, int n_split, float* __restrict__ part_o, f32x2* __restrict__ part_stat) {
   using C = Cfg<D, BR, BC, KRED, MODE, NG, KS>;
   constexpr bool FUSED = C::FUSED, GROUPED = C::GROUPED;
-  constexpr float kSumTrigger = (BC / 2) * 256.0f;   // BC/2 keys per lane and tile, each at most 2^kTau
+  // Sums of P on the matrix pipe (RowSum) where they take no registers that the wave has not got: fused kernels hold ten more
+  // than with dot products, which costs a wave per SIMD or spills, and at d = 128 (blocks of 128 rows, one long wave) what the clock falls by. us, dot products | this:
+  //   exact and Q~ K^T, d64 H32 Hkv8 N4096 causal 84.4 | 83.4, H16 N1500 18.9 | 18.2, Br256 N3000 53.8 | 51.3; B32 H12 N400 37.4 | 36.3;
+  //   d128 H16 N8192 causal 266 | 262, Br256 N3000 77.1 | 71.0; fused d64 N16384 490 | 502; d128 N32768 3182 | 3240, but Br256 N3000 88.6 | 82.5
+  constexpr bool MATRIX_SUM = FUSED ? D == 128 && BR == 256 && BC == 64 && NG >= 16 : D == 64 || BC != 128;
+  constexpr float kSumTrigger = (MATRIX_SUM ? BC : BC / 2) * 256.0f;   // keys per sum and tile, each at most 2^kTau
   // A row whose first tile holds only scores of -infinity (masked keys; those of a share or half that the causal mask hides)
   // takes its first score above that as its reference: against 0, scores of -150 and less would be lost. The fused product has no such
   // scores (its operands are clamped), and undivided keys begin with one that every row sees.
@@ -688,7 +732,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   f32x16 neg_ref;
 #pragma unroll
   for (int i = 0; i < 16; ++i) neg_ref[i] = 0.0f;
-  float l_run = 0.0f;        // over this lane's half of the keys
+  float l_run = 0.0f;        // (MATRIX_SUM: over all keys, otherwise over this lane's half of them)
 
   // LDS byte offsets of this lane's operands inside a buffer.
   // Score product, A operand (exact): row lq (+32 per key block), logical chunk 2*s + hh.
@@ -766,11 +810,8 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
     mt = half_swap_max(mt);
     return PRESCALED ? mt : __builtin_fmaf(mt, scale_log2e, nref);
   };
-  // P = exp2(scores) rounded to bf16, as the B operands of P.V; returns this lane's row sum. The
-  // sum is taken over the rounded P, the values P.V really uses (one bf16 dot product with (1, 1)
-  // per register pair): numerator and denominator then carry the same rounding, which cancels
-  // for rows dominated by few keys.
-  auto exp_tile = [&](const f32x16 (&sc)[C::MB], bf16x8 (&pop)[C::TT]) -> float {
+  // P = exp2(scores) rounded to bf16, as the B operands of P.V; with sum_c returns this lane's row sum, by dot products.
+  auto exp_tile = [&](const f32x16 (&sc)[C::MB], bf16x8 (&pop)[C::TT], auto sum_c) -> float {
     const bf16x2 ones = {(bf16)1.0f, (bf16)1.0f};
     float rs0 = 0.0f, rs1 = 0.0f;
 #pragma unroll
@@ -782,14 +823,18 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
           x0 = __builtin_fmaf(x0, scale_log2e, nref);
           x1 = __builtin_fmaf(x1, scale_log2e, nref);
         }
-        bf16x2 pr = {(bf16)__builtin_amdgcn_exp2f(x0), (bf16)__builtin_amdgcn_exp2f(x1)};
+        const bf16x2 pr = {(bf16)__builtin_amdgcn_exp2f(x0), (bf16)__builtin_amdgcn_exp2f(x1)};
         pop[mb * 2 + (i >> 3)][i & 7] = pr[0];
         pop[mb * 2 + (i >> 3)][(i & 7) + 1] = pr[1];
-        if (i & 2) rs1 = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, rs1, false);
-        else rs0 = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, rs0, false);
+        if constexpr (decltype(sum_c)::value) {
+          if (i & 2) rs1 = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, rs1, false);
+          else rs0 = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, rs0, false);
+        }
       }
     return rs0 + rs1;
   };
+  const RowSum row_sum(lane);
+  const std::integral_constant<bool, !MATRIX_SUM> sum_here;
   // The reference of this lane's row moves up by `delta`: everything that is relative to it
   // follows (row sum, output accumulator, the scores already computed against the old one).
   auto shift_reference = [&](float delta, auto rescale_c, f32x16 (&sc)[C::MB], auto next_c, f32x16 (&sn)[C::MB]) {
@@ -836,7 +881,8 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
     }
     if constexpr (HAS_NEXT) qk(par ^ 1, sn);
     bf16x8 pop[C::TT];
-    float rs = exp_tile(sc, pop);
+    float rs = exp_tile(sc, pop, sum_here);
+    if constexpr (MATRIX_SUM) rs = row_sum(pop);
     if (__builtin_amdgcn_ballot_w64(!(rs <= (LATE_FIRST ? trigger : kSumTrigger))) != 0) {
       // Some row of this wave met a score more than kTau above its reference, or its first one above -infinity: such rows take the
       // tile's maximum as their new reference and the tile's P is computed again.
@@ -844,7 +890,8 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
       const bool first = LATE_FIRST && trigger < 0.0f && mt > -INFINITY;
       if (first) trigger = kSumTrigger;
       shift_reference(mt > kTau || first ? mt : 0.0f, std::true_type(), sc, next_c, sn);
-      rs = exp_tile(sc, pop);
+      rs = exp_tile(sc, pop, sum_here);
+      if constexpr (MATRIX_SUM) rs = RowSum::by_lanes(pop);
     }
     l_run += rs;
     // ---- O^T += V^T . P^T: step tt covers keys 16*tt + {8*(j/4) + 4*hh + j%4} of the tile,
@@ -940,7 +987,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   body(no, no, it, it & 1, s0, s1);
 
   // ---- epilogue: O = O_acc / l, bf16, 8-byte stores ---------------------------------------------
-  float l_tot = half_swap_sum(l_run);
+  float l_tot = MATRIX_SUM ? l_run : half_swap_sum(l_run);
   constexpr int OB = D / 32 / KS;            // 32-channel blocks of the output that this wave finishes
   const int c0 = KS == 2 ? half * (D / 2) : 0;
   f32x16 out[OB];

@@ -189,3 +189,36 @@ def test_masked_tiles_before_low_scores(B, H, Hkv, N, Nk, d, Br, Bc, causal, dis
     assert rows.any() and torch.equal(torch.isnan(o[..., 0]), ~rows)
     assert (o - want)[rows].abs().max() <= 2e-2
     assert ((lse - want_lse)[rows].abs() / want_lse[rows].abs().clamp(min=1.0)).max() <= 2e-2
+
+
+@pytest.mark.parametrize("shape", [("bf16", 1, 4, 2, 300, 300, 64, 128, True), ("bf16", 1, 2, 2, 200, 333, 128, 256, False),
+                                   ("bf16", 1, 2, 2, 1100, 1100, 128, 256, False), ("bf16", 1, 2, 1, 200, 4099, 64, 128, True)], ids=str)
+@pytest.mark.parametrize("distr", [False, True])
+@pytest.mark.parametrize("value", [math.nan, math.inf, 2.0 ** 100])
+def test_rows_keep_to_themselves(shape, distr, value):
+    """A query row whose scores are NaN, infinite or far above the others', in every 32 rows: sums of rows are
+    taken together, and no other row changes by more than the order of its float sums (its P, the same to the bit, is
+    summed another way where a row beside it is not finite: 64 additions a tile, 2^-24 each at most, and with them
+    outputs move by a bf16 step at most). The tables are given: a block's grouping knows all of its rows."""
+    import torch
+
+    import paper_2507_17245_amd as da
+    dtype, B, H, Hkv, N, Nk, d, Br, causal = shape
+    q, k, v = _inputs(shape)
+    table = torch.stack([torch.randperm(d) for _ in range(B * H * -(-N // Br))]).to(torch.uint8).cuda()
+    rows = torch.arange(N, device="cuda") % 32 == 5
+    outs = []
+    for x in (None, value):
+        y = q.clone()
+        if x is not None:
+            y[:, :, rows] = torch.tensor(x, device="cuda").to(y.dtype)
+        o, lse = torch.zeros_like(q), torch.zeros((B, H, N), device="cuda")
+        p = da.make_params(y, k, v, Br=Br, n_groups=d // 2 if distr else d, causal=causal, lse_out=lse,
+                           perm_in=table.view(B, H, -1, d) if distr else None)
+        print(f"case {shape} distr={distr} {x}", flush=True)
+        (da.distr_attn_fwd_ex if distr else da.distr_attn_exact_fwd_ex)(y, k, v, o, p)
+        outs.append((o[:, :, ~rows], lse[:, :, ~rows]))
+    assert torch.isfinite(outs[0][0]).all()
+    (o, lse), (o1, lse1) = outs
+    assert (o1.float() - o.float()).abs().le(2.0 ** -7 * o.float().abs()).all()
+    assert (lse1 - lse).abs().max() <= 64 * 2.0 ** -24 + 2.0 ** -20   # (and the rounding of a statistic of up to 16)
