@@ -320,10 +320,11 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   // (the keys of a fused launch stay together)
   const int n_possible = matrix ? da::attn_bf16_splits(r.pb, distr ? 1 : 0) : 1;
   bool fused = distr && matrix && !da::attn_bf16_replicated(r.pb, p->kt_in != nullptr, n_possible);
-  // bf16 path, up to 16 projections, no hashes asked for: the attention kernel hashes and groups
-  // its own Q block in its prologue (same arithmetic as the LSH kernel); the table is written
+  // bf16 path, up to 16 projections, and float calls of few workgroups (attn_f32_groups), no hashes asked for: the attention
+  // kernel hashes and groups its own Q block in its prologue (same arithmetic as the LSH kernel); the table is written
   // only if the caller gave perm_out.
-  bool lsh_in_kernel = distr && matrix && !p->perm_in && !p->hash_out && r.pb.n_planes <= 16;
+  bool lsh_in_kernel = distr && !p->perm_in && !p->hash_out &&
+                       (matrix ? r.pb.n_planes <= 16 : da::attn_f32_groups(r.pb, r.dtype));
   const bool own_table = distr && !p->perm_in && !p->perm_out;
   // Scratch: [K^T copy | permutation table]. Only the parts this call writes are asked for: no K^T
   // copy when the caller brings kt_in, on the float path or for Q~ K^T, no table when the grouping comes
@@ -338,9 +339,10 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   void* kt = nullptr;
   char* base = nullptr;
   size_t kt_room = fused ? kt_need : 0;
-  if (distr && p->workspace && !no_alloc && kt_need + table_need) {
+  const size_t table_asked = own_table && !(matrix && lsh_in_kernel) ? perm_bytes(r) : 0;   // (the float path's table, too, whoever groups)
+  if (distr && p->workspace && !no_alloc && kt_need + table_asked) {
     kt_room = kt_need;
-    rc = scratch_base(p, r, kt_need + table_need, false, &base);
+    rc = scratch_base(p, r, kt_need + table_asked, false, &base);
     if (rc) return rc;
   }
   // Keys dealt out to several workgroups per Q block, where scratch for their sums is at hand. Every
@@ -384,6 +386,7 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   if (!share && table_need) table = (uint8_t*)(base + kt_room);
   const uint8_t* perm = p->perm_in;
   if (lsh_in_kernel) r.pb.perm_w = p->perm_out;
+  r.pb.group_in_kernel = lsh_in_kernel && !matrix;
   if (distr && !p->perm_in && !lsh_in_kernel) {
     if (p->perm_out) table = p->perm_out;
     rc = check_launch(r.pb.side == 1

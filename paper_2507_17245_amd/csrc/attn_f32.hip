@@ -21,7 +21,7 @@
 // waits for another before that, and a problem of few rows still fills the chip: sharing tiles
 // among waves of different rows instead would leave N = 256 with 8 working waves.
 // Measured (B1 H8 N2048 d64 n_groups 32): by pieces 57 us, by floats 72 (92 TFLOP/s of the 157 the instruction can reach; float
-// multiply-adds on the vector ALUs, a thread quad per row: 1430 us); mirrored 65 and 78; B1 H1 N256: 9 us (162).
+// multiply-adds on the vector ALUs, a thread quad per row: 1430 us); mirrored 65 and 78; B1 H1 N256, grouping and all: 10.6 us (a kernel in front of it for the grouping: 12.4).
 //
 // Score product, by MODE:
 //   kQueryFused  the wave writes its K tile into LDS in sorted channel order, a group's G channels
@@ -40,18 +40,23 @@
 #include <type_traits>
 
 #include "f32_tiles.h"
+#include "lsh_block.h"
 
 namespace da {
 
 namespace {
 
+constexpr int kOwnRows = 256;   // of a Q block that a workgroup groups itself, d = 64 (94 KB of LDS with the tiles)
+
 enum Mode { kQueryFull, kQueryFused, kKeyFull, kKeyFused };
 
-template <typename E, int D, int G, int MODE, int NW, bool PIECES>
+// OWN: the workgroup groups the Q block that its rows lie in itself, into lds.perm, and writes its table where perm_w is given
+// (rule: launch_waves).
+template <typename E, int D, int G, int MODE, int NW, bool PIECES, bool OWN>
 __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     const E* __restrict__ q, const E* __restrict__ k, const E* __restrict__ v, E* __restrict__ o,
     const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Br, int Tq, int Tw, int n_groups,
-    int causal, float scale, int Bc, float* __restrict__ lse) {
+    int causal, float scale, int Bc, float* __restrict__ lse, uint8_t* __restrict__ perm_w, int n_planes, int gray_mode, uint64_t seed) {
   constexpr bool kMirrored = MODE == kKeyFull || MODE == kKeyFused;
   constexpr bool kFused = MODE == kQueryFused || MODE == kKeyFused;
   constexpr int T = NW * 64;
@@ -66,6 +71,8 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
   __shared__ float stat_lds[NW][2][kTile];
   __shared__ __attribute__((aligned(16))) uint8_t map_lds[kMirrored ? NW : 1][D];
   __shared__ uint32_t mark_lds[kTile + 1];   // PIECES: what is known of a row (kRowAgain ..); whether a key is beyond_pieces
+
+  __shared__ typename std::conditional<OWN, LshLds<float, D, kOwnRows>, char>::type lsh_lds;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -101,8 +108,24 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
       for (int u = 0; u < D / 64; ++u) map_reg[u] = perm[row * D + u * 64 + lane];
     }
   };
+  // V of a tile is asked for behind the products of the tile before it, in front of the staging of its own K (a compute unit takes the
+  // 24 KB of a wave's tile in at 64 bytes a cycle, half a microsecond for four waves, in which a wave cannot go on): d128 H4 N2000 89.2 ->
+  // 85.1 us, groups of four H2 N1000 44.8 -> 41.2, d64 H8 N2048 59.0 -> 58.0. The mirrored form at d = 64 is slower with it (62.8 -> 64.3).
+  constexpr bool V_AHEAD = !kMirrored || D == 128;
+  constexpr int VR = NB / 2;   // raw pairs per row of V and lane
+  typename Pair<E>::raw vreg[16][VR];
+  auto load_v = [&](int tile) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+      for (int j = 0; j < VR; ++j)
+        vreg[i][j] = Pair<E>::load(v_rsrc, (acc_row(i, hh) * D + lq * NB + 2 * j) * (int)sizeof(E), tile * (kTile * D * (int)sizeof(E)));
+  };
   int tile = w * TB;
-  if (tile < n_tiles) load_k(tile);
+  if (tile < n_tiles) {
+    load_k(tile);
+    if (V_AHEAD) load_v(tile);
+  }
 
   // Q rows of the workgroup into LDS; the Q block's permutation beside them.
   {
@@ -114,12 +137,22 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     for (int u = 0; u < QU; ++u) *(f32x4*)&q_lds[(u * T + tid) / (D / 4) * RS + (u * T + tid) % (D / 4) * 4] = Quad<E>::values(x[u]);
     if (PIECES && tid <= kTile) mark_lds[tid] = 0;
   }
+  if constexpr (OWN) {
+    const int t_block = r0 / Br;
+    lsh_block<float, D, kOwnRows, T, true>((const float*)q + ((size_t)bh * N + (size_t)t_block * Br) * D, min(Br, N - t_block * Br), n_planes,
+                                              gray_mode, seed, perm_w && r0 % Br == 0 ? perm_w + ((size_t)bh * Tq + t_block) * D : nullptr, nullptr, lsh_lds);
+  }
+  // the Q block's permutation
+  auto table = [&]() {
+    if constexpr (OWN) return (const uint8_t*)lsh_lds.perm;
+    else return perm + ((size_t)bh * Tq + r0 / Br) * D;
+  };
   int kdst[4];          // kQueryFused: where the lane's four channels go in a row sorted by group
   if constexpr (!kMirrored) {
     // map: position of a channel in sorted order (kQueryFused) / sampled channel of its group (kQueryFull)
-    if (perm) {
+    if (OWN || perm) {
       // D is a power of two: an out-of-range entry of a caller's table cannot index past a row
-      const uint8_t* pr = perm + ((size_t)bh * Tq + r0 / Br) * D;
+      const uint8_t* pr = table();
       const int group = D / n_groups;
       for (int i = tid; i < D; i += T)
         map_lds[0][pr[i] & (D - 1)] = kFused ? (uint8_t)i : (uint8_t)(pr[i / group * group] & (D - 1));
@@ -144,7 +177,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     float qop[HS];
     if constexpr (MODE == kQueryFused) {
       // sampling: the group's first channel in sorted order
-      const uint8_t* pr = perm + ((size_t)bh * Tq + r0 / Br) * D;
+      const uint8_t* pr = table();
 #pragma unroll
       for (int s = 0; s < HS; ++s) qop[s] = q_lds[lq * RS + (pr[(hh * HS + s) * G] & (D - 1))];
     } else if constexpr (MODE == kQueryFull) {
@@ -221,18 +254,9 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
         }
       }
       wave_order();
-      // V of this tile, then K of the next one: in flight under the score product and P.V
-      constexpr int VR = NB / 2;   // raw pairs per row of V and lane
-      typename Pair<E>::raw vreg[16][VR];
-      auto load_v = [&](int i) {
-#pragma unroll
-        for (int j = 0; j < VR; ++j)
-          vreg[i][j] = Pair<E>::load(v_rsrc, (acc_row(i, hh) * D + lq * NB + 2 * j) * (int)sizeof(E), tile * (kTile * D * (int)sizeof(E)));
-      };
-#pragma unroll
-      for (int i = 0; i < 16; ++i) load_v(i);
-      // (unconditional, so that the waits for V can count the loads of K behind it: the last tile again
-      // when there is no next one)
+      // (V of this tile and) K of the next one: in flight under the products
+      if (!V_AHEAD) load_v(tile);
+      // (unconditional, so that the waits for V can count the loads of K behind it: the last tile again when there is no next one)
       const int following = next_tile(tile);
       load_k(min(following, n_tiles - 1));
 
@@ -359,6 +383,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
           for (int mb = 0; mb < NB; ++mb)
             oacc[mb] = mfma(Pair<E>::value(vreg[i][mb >> 1], mb & 1), ps[i], oacc[mb]);
       }
+      if (V_AHEAD) load_v(min(following, n_tiles - 1));
       tile = following;
     }
 
@@ -425,21 +450,33 @@ __global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
     const uint32_t again = pass(std::true_type(), ~0u);
     if (again == 0 && !k_again) return;
     tile = w * TB;
-    if (tile < n_tiles) load_k(tile);
+    if (tile < n_tiles) {
+      load_k(tile);
+      if (V_AHEAD) load_v(tile);
+    }
     pass(std::false_type(), again);
   } else {
     pass(std::false_type(), ~0u);
   }
 }
 
+template <typename E, int D, int G, int MODE, int NW, bool PIECES, bool OWN>
+hipError_t launch_own(const void* q, const void* k, const void* v, void* o, const uint8_t* perm, const Problem& pb,
+                      int n_groups, hipStream_t stream) {
+  const int Tq = (pb.N + pb.Br - 1) / pb.Br, Tw = (pb.N + kTile - 1) / kTile;
+  hipLaunchKernelGGL((attn_f32_kernel<E, D, G, MODE, NW, PIECES, OWN>), dim3((unsigned)((long long)pb.B * pb.H * Tw)), dim3(NW * 64), 0, stream,
+                     (const E*)q, (const E*)k, (const E*)v, (E*)o, perm, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, Tw, n_groups,
+                     pb.causal, pb.scale, pb.Bc, pb.lse, pb.perm_w, pb.n_planes, pb.gray_mode, pb.seed);
+  return hipGetLastError();
+}
+
 template <typename E, int D, int G, int MODE, int NW, bool PIECES>
 hipError_t launch_one(const void* q, const void* k, const void* v, void* o, const uint8_t* perm, const Problem& pb,
                       int n_groups, hipStream_t stream) {
-  const int Tq = (pb.N + pb.Br - 1) / pb.Br, Tw = (pb.N + kTile - 1) / kTile;
-  hipLaunchKernelGGL((attn_f32_kernel<E, D, G, MODE, NW, PIECES>), dim3((unsigned)((long long)pb.B * pb.H * Tw)), dim3(NW * 64), 0, stream,
-                     (const E*)q, (const E*)k, (const E*)v, (E*)o, perm, pb.H, pb.Hkv, pb.N, pb.Nk, pb.Br, Tq, Tw, n_groups,
-                     pb.causal, pb.scale, pb.Bc, pb.lse);
-  return hipGetLastError();
+  if constexpr (std::is_same<E, float>::value && D == 64 && (MODE == kQueryFull || MODE == kQueryFused)) {
+    if (pb.group_in_kernel) return launch_own<E, D, G, MODE, NW, PIECES, true>(q, k, v, o, nullptr, pb, n_groups, stream);
+  }
+  return launch_own<E, D, G, MODE, NW, PIECES, false>(q, k, v, o, perm, pb, n_groups, stream);
 }
 
 // Eight waves per workgroup where the row tiles leave compute units idle and there are tiles for all of them (dealt out by K blocks
@@ -486,6 +523,15 @@ hipError_t launch_typed(const void* q, const void* k, const void* v, void* o, co
 }
 
 }  // namespace
+
+// Grouping by the float kernel itself instead of a kernel in front of it: at d = 64, where every workgroup has a compute unit to
+// itself, so that its LDS and the grouping, repeated by the workgroups of a Q block, cost nothing but their time, which K and V of the first
+// tiles travel in. us, LSH kernel | itself, groups of two: H1 N64 9.9 | 8.4, H1 N256 (4 projections) 12.4 | 10.6, H4 N200 causal 13.5 | 11.5,
+// H8 N700 causal 18.4 | 16.0, H8 N1000 22.2 | 21.1, H2 N2000 30.6 | 29.2. At d = 128 (twice the channels for four waves, which
+// the LSH kernel gives eight) it loses: H2 N100 16.4 | 21.9, H4 N2000 89 | 96.
+bool attn_f32_groups(const Problem& pb, int dtype) {
+  return dtype == 1 && pb.side == 0 && pb.d == 64 && (long long)pb.B * pb.H * ((pb.N + kTile - 1) / kTile) <= kComputeUnits;
+}
 
 // dtype 0: bf16 tensors (converted on load, rounded on store), 1: float tensors; float arithmetic either way
 hipError_t launch_attn_f32(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,

@@ -191,8 +191,9 @@ struct Problem {
               // per K block of Bc rows (float-arithmetic kernel)
   int Bc;     // rows of a K block (only side 1 depends on it)
   float* lse; // optional device [B][H][N]: log-sum-exp of every row's visible scores (natural log)
-  uint8_t* perm_w = nullptr;   // optional device [B][H][Tq][d]: where the bf16 attention kernel's own LSH
+  uint8_t* perm_w = nullptr;   // optional device [B][H][Tq][d]: where the attention kernel's own LSH
                                // stage leaves its table
+  bool group_in_kernel = false;   // float forward: the attention kernel groups its Q blocks itself (attn_f32_groups)
   // bf16 forward with the key tiles of a Q block dealt out to n_split workgroups: their sums, float
   // [n_split][B][H][N][d], and (reference, row sum) pairs, float [n_split][B][H][N][2], exp2 domain
   int n_split = 1;
@@ -223,6 +224,7 @@ hipError_t launch_attn_bf16(const void* q, const void* k, const void* v, void* o
                             const void* kt, const Problem& pb, int distr, hipStream_t stream);
 hipError_t launch_attn_f32(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                            const Problem& pb, int dtype, int distr, hipStream_t stream);
+bool attn_f32_groups(const Problem& pb, int dtype);   // float forward: the kernel can group its Q blocks itself
 bool attn_bf16_supported(const Problem& pb, int distr);
 // The rules of the bf16 forward (attn_bf16.hip): whether S^ is taken as Q~ K^T (have_kt: the transposed keys are at
 // hand; n_split: the shares it would be cut into), and into how many shares the keys of a Q block are cut when the

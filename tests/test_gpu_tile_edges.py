@@ -496,3 +496,26 @@ def test_shares_whole_and_in_halves(base, Br, H, N, Nk, distr):
 @pytest.mark.parametrize("distr", [True, False])
 def test_one_workgroup_or_two(H, Hkv, N, Nk, distr):
     _forward(W.CONFIGS["long"].scaled(B=1, H=H, Hkv=Hkv, N=N, Nk=Nk, Br=64, causal=True, recipe="normal"), distr)
+
+
+@pytest.mark.parametrize("B,H,N,causal", [(1, 1, 1, False), (1, 2, 33, True), (1, 1, 256, False), (2, 3, 300, True), (1, 8, 1000, False), (1, 256, 32, False)])
+@pytest.mark.parametrize("Br,G", [(64, 2), (128, 4), (256, 2), (256, 8)])
+@pytest.mark.parametrize("n_planes", [1, 4, 5, 16, 17, 32])
+def test_float_groups_itself(B, H, N, causal, Br, G, n_planes):
+    """Float calls whose workgroups have a compute unit each group their Q blocks themselves: the tables are the LSH
+    kernel's (which the oracle pins), and the output is to the bit what that table gives when it is handed in."""
+    import torch
+
+    import paper_2507_17245_amd as da
+    gen = torch.Generator(device="cuda").manual_seed(N + n_planes)
+    q, k, v = (torch.randn((B, H, N, 64), generator=gen, device="cuda") for _ in range(3))
+    want, got = (torch.zeros((B, H, -(-N // Br), 64), dtype=torch.uint8, device="cuda") for _ in range(2))
+    o, o_given, o_quiet = (torch.zeros_like(q) for _ in range(3))
+    options = dict(Br=Br, n_groups=64 // G, causal=causal, lsh_seed=9, n_planes=n_planes)
+    print(f"case {(B, H, N, causal, Br, G, n_planes)}", flush=True)
+    da.distr_attn_lsh_group(q, da.make_params(q, k, v, perm_out=want, **options))
+    da.distr_attn_fwd_ex(q, k, v, o, da.make_params(q, k, v, perm_out=got, **options))
+    da.distr_attn_fwd_ex(q, k, v, o_given, da.make_params(q, k, v, perm_in=want, **options))
+    da.distr_attn_fwd_ex(q, k, v, o_quiet, da.make_params(q, k, v, **options))
+    assert torch.equal(got, want)
+    assert torch.equal(o, o_given) and torch.equal(o_quiet, o_given)
