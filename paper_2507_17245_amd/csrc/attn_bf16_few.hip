@@ -12,10 +12,12 @@
 //     at the full rate. The states meet in LDS at the end, the shares in the combine kernel;
 //   * DistrAttention is taken as S^ = Q~ K^T (ScoreMode kReplicated): no transposed copy of the
 //     cache. The grouping of a head's N <= 64 rows (one Q block) is computed by the workgroup, in the
-//     defining float order, while its first tiles travel; hash and channel rank as one key.
+//     defining float order, while its first tiles travel (behind barriers that wait for LDS alone: with __syncthreads, which
+//     waits for the tiles too, a decoding call took 14.2 us, 13.0 now); hash and channel rank as one key.
 // Layouts, operands and the rounding of P are the general kernel's (attn_bf16_impl.h).
-// Measured (B1 H32 Hkv8 N1 Nk16384 d64, 34 MB of keys and values): 11 us + 4 us for the combine kernel, 130 us +
-// 7 us for the key pre-pass before; B16 H32 Hkv4 N1 Nk8192: 33 us, 4.1 TB/s (174 us).
+// Measured (B1 H32 Hkv8 N1 Nk16384 d64, 34 MB of keys and values): 10 us + 3 us for the combine kernel, 130 us +
+// 7 us for the key pre-pass before; B16 H32 Hkv4 N1 Nk8192: 33 us, 4.1 TB/s (174 us). (The last share of a row tile to end as the one that
+// adds them up, by stores and loads past the L2 and a counter: 16.2 us; the start of a kernel costs less.)
 #include <cfloat>
 
 #include "attn_bf16_impl.h"
@@ -114,11 +116,12 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
     *(bf16x8*)&q_lds[i / CH][i % CH * 8] = qx[u];
   }
   if (tile < t1) load_tile(even, tile);
+  // (barriers that leave the tiles in flight)
   if constexpr (GROUPED) {
     const int group = D / n_groups;
     uint32_t* keys = (uint32_t*)k_lds1;   // (receives its first tile after the barrier that ends this stage)
     static_assert(kFewRows * D * 4 <= kFewWaves * kFewTileBytes, "the keys of all heads fit");
-    __syncthreads();
+    lds_barrier();
     if (perm == nullptr) {
       // signs of the float sums, one fused multiply-add per row, rows ascending, from +0
       for (int i = tid; i < n_heads * D; i += kFewThreads) {
@@ -144,7 +147,7 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
           if (p < n_planes && acc[p] > 0.0f) bits |= 1u << (n_planes - 1 - p);   // projection 0 = top bit
         keys[i] = lsh_hash_of_code(bits, gray_mode) << 7 | c;   // (at most 16 bits: hash and channel make one key)
       }
-      __syncthreads();
+      lds_barrier();
       // rank by counting = stable ascending sort
       for (int i = tid; i < n_heads * D; i += kFewThreads) {
         const uint32_t* others = keys + i / D * D;
@@ -158,7 +161,7 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
         }
         perm_lds[i / D][rank] = (uint8_t)(i % D);
       }
-      __syncthreads();
+      lds_barrier();
       if (perm_w && part == 0)
         for (int i = tid; i < n_heads * D; i += kFewThreads) perm_w[((size_t)bk * rep + head0) * D + i] = perm_lds[i / D][i % D];
     }
@@ -167,7 +170,7 @@ __global__ __launch_bounds__(kFewThreads, 2) void attn_bf16_few_kernel(
       from_lds[i / D][pl[i % D]] = pl[i % D / group * group];
     }
   }
-  __syncthreads();
+  lds_barrier();
   bf16x8 qop[KS];
 #pragma unroll
   for (int s = 0; s < KS; ++s) {

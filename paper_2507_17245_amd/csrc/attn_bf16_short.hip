@@ -8,6 +8,8 @@
 //     projections shared by all waves, then one wave ranks a block, which takes no further barrier;
 //   * wave w owns the rows 32*w .. and walks the keys 32 at a time without a barrier, the scores of the next
 //     32 keys on the matrix pipe beside the exponentials of these; causal waves stop at their last key;
+//   * V travels behind K: the barrier after Q~ waits for LDS alone, and the first scores for K alone (H12 N197 B64 28.7 -> 27.4 us, exact
+//     23.7 -> 23.0, where __syncthreads waited for K before V was asked for);
 //   * DistrAttention is taken as S^ = Q~ K^T (ScoreMode kReplicated).
 // Layouts, operands, rounding of P and the lazy reference are the general kernel's (attn_bf16_impl.h).
 // Measured, general | this: H12 N197 B64 41 | 27 us (exact 29 | 21), B8 14.3 | 13.1, B1 13.0 | 12.0; N128 B64 23 | 15;
@@ -173,15 +175,17 @@ __global__ __launch_bounds__(NW * 64, 4) void attn_bf16_short_kernel(
 #pragma unroll
       for (int j = 0; j < 8; ++j) qop[s][j] = *(const bf16*)(row + ((f[j >> 2] >> (8 * (j & 3))) & 255));
     }
-    __syncthreads();                     // Q has been read
+    lds_barrier();                       // Q has been read; K travels on
     load(as_v, vh, Nk, v_lds);
   } else {
-    load(as_k, kh, Nk, k_lds);
-    load(as_v, vh, Nk, v_lds);
 #pragma unroll
     for (int s = 0; s < KS; ++s) qop[s] = *(const bf16x8*)(qh + (size_t)min(my_row, N - 1) * D + 16 * s + 8 * hh);
+    load(as_k, kh, Nk, k_lds);
+    load(as_v, vh, Nk, v_lds);
   }
-  landed();
+  // K has landed (V, whose four loads are the last, is awaited behind the first scores)
+  asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+  lds_barrier();
   const int qw0 = wave * 32, q_abs = qw0 + lq;
 
   // ---- 32 keys at a time
@@ -287,6 +291,7 @@ __global__ __launch_bounds__(NW * 64, 4) void attn_bf16_short_kernel(
     first = first == -INFINITY ? block_max(later) : first;
   }
   nref = first == -INFINITY ? 0.0f : -first;
+  landed();
   if (n_blocks > 0) body(std::true_type(), 0, s0, s1);
   for (int b = 1; b < n_blocks; b += 2) {
     body(std::false_type(), b, s1, s0);

@@ -181,6 +181,14 @@ inline size_t kt_copy_bytes(int B, int Hkv, int d, int Nk) {
   return ((size_t)B * Hkv * d * npad * 2 + 255) & ~(size_t)255;
 }
 
+// A barrier for what the waves have written to LDS and read from it themselves. __syncthreads waits for every load in flight
+// besides, those into LDS for later among them (so does a fence for LDS alone).
+__device__ inline void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 struct Problem {
   int B, H, Hkv, N, d, Br, n_groups, causal, n_planes, gray_mode;
   uint64_t seed;
