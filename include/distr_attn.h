@@ -60,6 +60,7 @@ typedef enum { DA_BF16 = 0, DA_F32 = 1 } da_dtype;
 typedef struct {
   int B, H, Hkv, N, d;
   int Br;               /* rows of a query block, the paper's l; one LSH grouping per block (Sec. 3.3) */
+                        /* (exact calls, which group nothing, may cut the queries otherwise)            */
   int Bc;               /* rows of a key/value block, the paper's m (Sec. 2.2.2)                     */
   int n_groups;         /* k = d / G*: contraction length of S^ = Q_r K_f^T (Sec. 3.1 Eq. 2, Sec. 3.2) */
   int causal;           /* 0 / 1: key n is visible to query i iff n <= i                            */

@@ -317,6 +317,7 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
     distr = false;
   }
   const bool matrix = r.dtype == DA_BF16 && r.pb.side == 0;
+  if (matrix && !distr) r.pb.Br = da::attn_bf16_exact_rows(r.pb);
   // (the keys of a fused launch stay together)
   const int n_possible = matrix ? da::attn_bf16_splits(r.pb, distr ? 1 : 0) : 1;
   bool fused = distr && matrix && !da::attn_bf16_replicated(r.pb, p->kt_in != nullptr, n_possible);
@@ -539,7 +540,9 @@ size_t distr_attn_workspace_bytes(const da_params* p) {
   Resolved r;
   if (resolve(p, true, &r)) return 0;
   const size_t whole = (needs_kt(r) ? kt_bytes(r) : 0) + perm_bytes(r);
-  const size_t split = needs_kt(r) ? perm_bytes(r) + share_bytes(r, std::max(da::attn_bf16_splits(r.pb, 0), da::attn_bf16_splits(r.pb, 1))) : 0;
+  da::Problem exact = r.pb;
+  exact.Br = da::attn_bf16_exact_rows(r.pb);
+  const size_t split = needs_kt(r) ? perm_bytes(r) + share_bytes(r, std::max(da::attn_bf16_splits(exact, 0), da::attn_bf16_splits(r.pb, 1))) : 0;
   return whole > split ? whole : split;
 }
 

@@ -71,6 +71,36 @@ bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split) {
   return copy > gain * 1e-9 * pb.d * std::max(rows * keys, walk);
 }
 
+// Query rows of an exact call's workgroups. Nothing is grouped, so the block that the caller names binds nothing: its rows are those that
+// suit the launch. Keys about as many as queries, us, 64 | 128 | 256 rows:
+//   64 while two halves of the keys (launch_one) of such blocks fill the chip once: d64 causal H16 N1000 10.2 | 13.7 | 20.6, H8 N2900 20 | 25 | 43,
+//      d128 H16 N1000 15.3 | 19.3 | 28.9, not causal H8 N2000 25 | 33 | 40, and not yet H8 N2900 52 | 43 | 63;
+//      at d = 64 under the mask up to one and a half rounds of 128 rows (H16 N2000 17.5 | 19.8, H32 N1400 17.7 | 18.8, B4 H16 N700 11.6 | 12.4, but
+//      H16 N4096 51 | 47), not causal where all are resident and at least a twelfth of the rows would be padding (B16 H12 N280 11.4 | 13.5, B4 H16 N700
+//      15.5 | 16.5, but N577 33 | 29);
+//   256 without the mask, where they fill more than half of one round of compute units (d128 H16 N2900 94 | 79 | 72, N4096 149 | 123 | 118, d64 49 | 48 | 44,
+//      80 | 74 | 71) or, at d = 128, whole ones (N16000 2081 | 1784 | 1687, but N6000, one and a half, 309 | 260 | 283), with little padding;
+//   128 otherwise (the caller's 256, causal d64 H16 N9000: 215 | 173 | 193).
+// Many more keys than queries (their shares fill the chip): the caller's, up to 128 (N500 on 8000 keys, H16 d64 29 | 27 | 39), and 128 at d = 128 on
+// long walks (N512 on 30000 keys 142 | 122, N1000 on 8000 83 | 70, N128 on 2500 15.5 | 17.4) unless they are a tenth more rows.
+int attn_bf16_exact_rows(const Problem& pb) {
+  if (pb.Bc != 64) return pb.Br;
+  const long long heads = (long long)pb.B * pb.H;
+  const auto padded = [&](int rows) { return (pb.N + rows - 1LL) / rows * rows; };
+  const auto wgs = [&](int rows) { return heads * padded(rows) / rows; };
+  if (pb.Nk >= 2LL * pb.N) {
+    const bool more = pb.d == 128 && pb.N > 64 && pb.Nk >= 6000 && 10 * padded(128) <= 11 * padded(64);
+    return more ? 128 : std::min(pb.Br, 128);
+  }
+  if (wgs(64) <= kComputeUnits) return 64;
+  if (pb.d == 64 && (pb.causal ? 2 * wgs(128) <= 3 * kComputeUnits : wgs(64) <= 5 * kComputeUnits && 12 * padded(64) <= 11 * padded(128))) return 64;
+  if (!pb.causal && 10 * padded(256) <= 11 * padded(128)) {
+    const long long n = wgs(256), rounds = (n + kComputeUnits - 1) / kComputeUnits;
+    if (rounds == 1 ? 2 * n > kComputeUnits : pb.d == 128 && 20 * n >= 19 * kComputeUnits * rounds) return 256;
+  }
+  return 128;
+}
+
 // Key shares per Q block, for launches that would leave compute units without a workgroup: one
 // four-wave workgroup (two of two waves, half of one of eight) for each, at least four tiles per share, and only where the
 // tiles taken off a workgroup's walk outweigh the combine kernel (4 us, about 12 tiles) and, grouped,
@@ -88,7 +118,9 @@ int attn_bf16_splits(const Problem& pb, int distr) {
   if (attn_bf16_short(pb, distr)) return 1;
   const long long units = (long long)pb.B * pb.H * ((pb.N + pb.Br - 1) / pb.Br);
   const int tiles = (pb.Nk + pb.Bc - 1) / pb.Bc;
-  const auto worth = [&](long long n) { return n > 1 && tiles - tiles / n >= (distr ? 30 : 12); };
+  // (exact blocks of 64 rows that two halves of the keys are walked for anyway have half as much to gain: H8 N1000 14 us in four shares, 10 in none)
+  const bool in_halves = !distr && pb.Br == 64 && pb.Bc == 64 && units <= (pb.d == 64 ? 2 : 1) * kComputeUnits;
+  const auto worth = [&](long long n) { return n > 1 && tiles - tiles / n >= (distr ? 30 : in_halves ? 24 : 12); };
   long long n = std::min<long long>(1024 / (pb.Br / 32) / units, tiles / 4);
   const long long one = kComputeUnits / units, few = std::min<long long>(one, tiles / 4);
   if (pb.d == 128 && pb.Br == 64 && pb.Bc == 64 && one * units >= kComputeUnits - 16 && (blocks_sharing_l2(pb) < 12 || tiles <= std::max(64LL, 48 * one)) &&

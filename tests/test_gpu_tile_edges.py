@@ -519,3 +519,34 @@ def test_float_groups_itself(B, H, N, causal, Br, G, n_planes):
     da.distr_attn_fwd_ex(q, k, v, o_quiet, da.make_params(q, k, v, **options))
     assert torch.equal(got, want)
     assert torch.equal(o, o_given) and torch.equal(o_quiet, o_given)
+
+
+@pytest.mark.parametrize("B,H,Hkv,N,Nk,d,causal", [
+    (1, 8, 8, 2048, 2048, 64, True), (1, 8, 4, 2049, 2049, 128, False), (1, 6, 6, 8129, 8129, 64, True), (16, 12, 12, 280, 280, 64, False),
+    (16, 12, 12, 300, 300, 64, False), (1, 16, 16, 2100, 2500, 128, False), (1, 16, 4, 2100, 2100, 64, False), (1, 4, 4, 65, 6000, 128, True),
+    (1, 4, 4, 150, 6000, 128, True), (1, 8, 8, 1000, 1000, 128, True)])
+def test_exact_rows_of_a_workgroup(B, H, Hkv, N, Nk, d, causal):
+    """Exact calls choose their workgroups' rows by the launch: every Br gives the same rows (up to the order of the sums where
+    shares of the keys differ), and they are plain attention's, on either side of each line of the rule."""
+    import math
+
+    import torch
+
+    import paper_2507_17245_amd as da
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v = (torch.randn(s, generator=gen, device="cuda").bfloat16() for s in ((B, H, N, d), (B, Hkv, Nk, d), (B, Hkv, Nk, d)))
+    rows = torch.cat([torch.arange(0, N, max(1, N // 37)), torch.arange(max(0, N - 40), N)]).unique()
+    b, h = B - 1, H - 1
+    kd, vd = (x[b, h // (H // Hkv)].double().cpu() for x in (k, v))
+    s = torch.matmul(q[b, h].double().cpu()[rows], kd.t().contiguous()) / math.sqrt(d)
+    if causal:
+        s = s.masked_fill(torch.arange(Nk)[None, :] > rows[:, None] + (Nk - N), -math.inf)
+    want, want_lse = torch.matmul(torch.softmax(s, dim=-1), vd), torch.logsumexp(s, dim=-1)
+    for Br in (64, 128, 256):
+        print(f"case {(B, H, Hkv, N, Nk, d, causal)} Br={Br}", flush=True)
+        o, lse = torch.zeros_like(q), torch.zeros((B, H, N), device="cuda")
+        da.distr_attn_exact_fwd_ex(q, k, v, o, da.make_params(q, k, v, Br=Br, causal=causal, lse_out=lse))
+        err = (o[b, h].double().cpu()[rows] - want).abs()
+        assert err.max() <= 2e-2 and err.mean() <= 2e-3
+        assert (lse[b, h].double().cpu()[rows] - want_lse).abs().max() <= 2e-3
+        assert torch.isfinite(o.float()).all() and (o.float().abs().sum(dim=-1) > 0).all()
