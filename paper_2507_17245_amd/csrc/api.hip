@@ -370,6 +370,7 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   if (!share && n_split > 1 && distr && p->kt_in) fused = !da::attn_bf16_replicated(r.pb, true, 1);
   if (share) {
     r.pb.n_split = n_split;
+    if (distr && !few) r.pb.rows = da::attn_bf16_shared_rows(r.pb);
     table = split_table ? (uint8_t*)share : nullptr;
     r.pb.part_stat = (float*)(share + split_table);
     r.pb.part_o = (float*)(share + split_table + share_stat_bytes(r, n_split));

@@ -101,6 +101,14 @@ int attn_bf16_exact_rows(const Problem& pb) {
   return 128;
 }
 
+// Query rows of a grouped call's workgroups when its keys are dealt out, whose grouping then comes from a table: two Q blocks of 64 rows at
+// d = 128 on long walks (blocks of 64 have half the waves to a tile there), unless they are a tenth more rows. us, one | two: H16 N100 Nk16000
+// 44.4 | 39.6, N200 Nk30000 95 | 80, N700 Nk8000 80 | 72, H32 Hkv8 N500 Nk8000 95 | 86, N200 58 | 51. On 2500 keys exact blocks of 64 are the faster.
+int attn_bf16_shared_rows(const Problem& pb) {
+  const auto padded = [&](int rows) { return (pb.N + rows - 1LL) / rows * rows; };
+  return pb.d == 128 && pb.Br == 64 && pb.Bc == 64 && pb.N > 64 && pb.Nk >= 6000 && 10 * padded(128) <= 11 * padded(64) ? 128 : pb.Br;
+}
+
 // Key shares per Q block, for launches that would leave compute units without a workgroup: one
 // four-wave workgroup (two of two waves, half of one of eight) for each, at least four tiles per share, and only where the
 // tiles taken off a workgroup's walk outweigh the combine kernel (4 us, about 12 tiles) and, grouped,
@@ -114,8 +122,10 @@ int attn_bf16_exact_rows(const Problem& pb) {
 // Nk12000, N200 Nk6000) 0.94-1.02, 62-78 (N200 Nk8000, N120 Nk20000) 1.01-1.17, more up to 1.24, and with no shares to combine at all (256
 // blocks) 64 tiles 0.92-0.95, 94 0.98-1.02, 125 1.11. 80 units idle (H44 N200) Nk4096 1.09, Nk30000 1.33; distr H32 Hkv8 N200 Nk3000, where two
 // shares are not worth the LSH launch, 34.6 | 39.5.
-int attn_bf16_splits(const Problem& pb, int distr) {
-  if (attn_bf16_short(pb, distr)) return 1;
+int attn_bf16_splits(const Problem& asked, int distr) {
+  if (attn_bf16_short(asked, distr)) return 1;
+  Problem pb = asked;
+  if (distr) pb.Br = attn_bf16_shared_rows(asked);
   const long long units = (long long)pb.B * pb.H * ((pb.N + pb.Br - 1) / pb.Br);
   const int tiles = (pb.Nk + pb.Bc - 1) / pb.Bc;
   // (exact blocks of 64 rows that two halves of the keys are walked for anyway have half as much to gain: H8 N1000 14 us in four shares, 10 in none)
@@ -123,7 +133,7 @@ int attn_bf16_splits(const Problem& pb, int distr) {
   const auto worth = [&](long long n) { return n > 1 && tiles - tiles / n >= (distr ? 30 : in_halves ? 24 : 12); };
   long long n = std::min<long long>(1024 / (pb.Br / 32) / units, tiles / 4);
   const long long one = kComputeUnits / units, few = std::min<long long>(one, tiles / 4);
-  if (pb.d == 128 && pb.Br == 64 && pb.Bc == 64 && one * units >= kComputeUnits - 16 && (blocks_sharing_l2(pb) < 12 || tiles <= std::max(64LL, 48 * one)) &&
+  if (pb.d == 128 && pb.Br == 64 && pb.Bc == 64 && one * units >= kComputeUnits - 16 && (blocks_sharing_l2(pb, pb.Br) < 12 || tiles <= std::max(64LL, 48 * one)) &&
       (one == 1 || worth(few) || !worth(n)))
     n = few;
   if (!worth(n)) n = 1;

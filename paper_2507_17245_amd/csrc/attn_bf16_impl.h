@@ -195,7 +195,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
     bf16* __restrict__ o, const uint8_t* __restrict__ perm, const f16* __restrict__ kt, int Npad,
     int H, int Hkv, int N, int Nk, int Tq, int causal, float scale_log2e, int total_units, int n_planes,
     int gray_mode, uint64_t lsh_seed, float* __restrict__ lse, const char* __restrict__ rtab,
-    uint8_t* __restrict__ perm_w, int n_groups, int n_split, float* __restrict__ part_o, f32x2* __restrict__ part_stat) {
+    uint8_t* __restrict__ perm_w, int n_groups, int Br, int n_split, float* __restrict__ part_o, f32x2* __restrict__ part_stat) {
   using C = Cfg<D, BR, BC, KRED, MODE, NG, KS>;
   constexpr bool FUSED = C::FUSED, GROUPED = C::GROUPED;
   // Sums of P on the matrix pipe (RowSum) where they take no registers that the wave has not got: fused kernels hold ten more
@@ -359,9 +359,11 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   }
   if constexpr (GROUPED) {
     if (perm != nullptr) {
-      const size_t pbase = ((size_t)bh * Tq + t) * D;
-      // D is a power of two: an out-of-range entry of a caller's table cannot index past a row
-      for (int i = tid; i < D; i += C::T) perm_lds[i] = perm[pbase + i] & (D - 1);
+      // One row of the table for each of the workgroup's Q blocks (of Br rows; several for kReplicated only). D is a power
+      // of two: an out-of-range entry of a caller's table cannot index past a row.
+      const int blocks = (N + Br - 1) / Br, first = t * (BR / Br);
+      for (int i = tid; i < BR / Br * D; i += C::T)
+        perm_lds[i] = first + i / D < blocks ? perm[((size_t)bh * blocks + first) * D + i] & (D - 1) : (uint8_t)(i % D);
     } else {
       // ---- LSH hash-and-group of this Q block inside the workgroup (Sec. 3.2, 3.3) -------------
       // The table equals the stand-alone LSH kernel's bit for bit: a projection's sign is that of
@@ -555,15 +557,16 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   kx8 qop[C::KSTEPS];
   if constexpr (MODE == kReplicated) {
     // Q~: the sampled channel of every channel's group, by way of a map in LDS
-    uint8_t* from_lds = perm_lds + D;
-    const int group = D / n_groups;
+    const int group = D / n_groups, n_maps = BR / Br * D;
+    uint8_t* from_lds = perm_lds + n_maps;
+    const uint8_t* from = from_lds + rw * 32 / Br * D;   // the map of this wave's Q block
     if constexpr (QSTAGE) {
-      if (tid < D) from_lds[perm_lds[tid]] = perm_lds[tid / group * group];
+      for (int i = tid; i < n_maps; i += C::T) from_lds[i / D * D + perm_lds[i]] = perm_lds[i / group * group];
       __syncthreads();
 #pragma unroll
       for (int s = 0; s < C::KSTEPS; ++s)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) qop[s][j] = q_staged(rw * 32 + lq, from_lds[16 * s + 8 * hh + j] & (D - 1));
+        for (int j = 0; j < 8; ++j) qop[s][j] = q_staged(rw * 32 + lq, from[16 * s + 8 * hh + j] & (D - 1));
     } else {
       // The wave's rows pass through its part of the K buffers, RPR at a time (16-byte chunks exchanged by the row; its
       // LDS accesses take effect in its order): gathered from global memory, two bytes per load and lane, they cost a
@@ -574,7 +577,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
 #pragma unroll
       for (int j = 0; j < 8; ++j)
         x[j] = *(const u32x4*)(qh + (size_t)min(qw0 + 4 * j + (lane >> 4), N - 1) * D + (lane & 15) * 8);
-      if (tid < D) from_lds[perm_lds[tid]] = (uint8_t)(2 * perm_lds[tid / group * group]);
+      for (int i = tid; i < n_maps; i += C::T) from_lds[i / D * D + perm_lds[i]] = (uint8_t)(2 * perm_lds[i / group * group]);
       __syncthreads();
       char* mine = (wave & 1 ? kx_lds1 : kx_lds0) + (wave >> 1) * (RPR * C::ROWB);
       const int row = lq % RPR;
@@ -590,7 +593,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int s = 0; s < C::KSTEPS; ++s) {
-          const u32x2 f = *(const u32x2*)&from_lds[16 * s + 8 * hh];
+          const u32x2 f = *(const u32x2*)&from[16 * s + 8 * hh];
           const uint32_t at[2] = {(f[0] & 0xfefefefeu) ^ flip, (f[1] & 0xfefefefeu) ^ flip};
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
@@ -860,26 +863,29 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
     }
   };
 
+  // What tile `it` brings in. The buffers these loads fill were last read in the previous iteration, which every wave
+  // has left (barrier): K(it+2) replaces K(it), V(it+1) replaces V(it-1).
+  auto feed = [&](int it, int par) {
+    // distr: the pieces of K^T(it+2), loaded during the previous iteration, are summed now
+    // into the buffer K_f^T(it) has left, and the loads of K^T(it+3) take their registers.
+    // Nothing in this iteration depends on the fusion: it runs beside the MFMAs.
+    if constexpr (FUSED) {
+      fuse_pieces(par, piece);       // K^T(it+2), loaded during the previous iteration
+      load_pieces(it + 3, piece);
+    }
+    if constexpr (!FUSED) dma_tile(k_rsrc, it + 2, dma_k, kx_buf(par));
+    dma_tile(v_rsrc, it + 1, dma_v, v_buf(par ^ 1));
+  };
   // One tile `it`, whose scores `sc` are masked and relative to the row's reference:
   //   scores of tile it+1 into `sn` (matrix pipe)  ||  exp2, bf16 P, row sum of `sc` (vector ALUs)
   //   the rare reference move, then O^T += V^T . P^T for tile it (matrix pipe), the mask of
   //   tile it+1 where it needs one, one barrier.
   auto body = [&](auto mask_next_c, auto next_c, int it, int par, f32x16 (&sc)[C::MB], f32x16 (&sn)[C::MB]) {
     constexpr bool HAS_NEXT = decltype(next_c)::value;
-    // The buffers these loads fill were last read in the previous iteration, which every wave
-    // has left (barrier): K(it+2) replaces K(it), V(it+1) replaces V(it-1).
     if constexpr (HAS_NEXT) {
-      // distr: the pieces of K^T(it+2), loaded during the previous iteration, are summed now
-      // into the buffer K_f^T(it) has left, and the loads of K^T(it+3) take their registers.
-      // Nothing in this iteration depends on the fusion: it runs beside the MFMAs.
-      if constexpr (FUSED) {
-        fuse_pieces(par, piece);       // K^T(it+2), loaded during the previous iteration
-        load_pieces(it + 3, piece);
-      }
-      if constexpr (!FUSED) dma_tile(k_rsrc, it + 2, dma_k, kx_buf(par));
-      dma_tile(v_rsrc, it + 1, dma_v, v_buf(par ^ 1));
+      feed(it, par);
+      qk(par ^ 1, sn);
     }
-    if constexpr (HAS_NEXT) qk(par ^ 1, sn);
     bf16x8 pop[C::TT];
     float rs = exp_tile(sc, pop, sum_here);
     if constexpr (MATRIX_SUM) rs = row_sum(pop);
@@ -955,6 +961,22 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
     __syncthreads();
   }
 
+  // A wave without rows (of a head's last block) brings its part of the tiles in and takes no products: what its SIMD and the power
+  // allow is the other waves' (200 rows on 32768 keys, H16 d128 86.0 -> 82.2 us, H32 N300 on 16000 130 -> 122, d64 H16 47.1 -> 44.9).
+  if (MODE != kFused && qw0 >= N) {
+    __syncthreads();
+    for (int it = 0; it < n_tiles - 1; ++it) {
+      feed(it, it & 1);
+      dma_wait();
+      __syncthreads();
+    }
+    __syncthreads();
+    if constexpr (KS == 2) {
+      if (n_tiles < n_most) __syncthreads();
+      __syncthreads();
+    }
+    return;
+  }
   const std::true_type yes;
   const std::false_type no;
   f32x16 s0[C::MB], s1[C::MB];
@@ -1086,7 +1108,7 @@ hipError_t launch_ks(const void* q, const void* k, const void* v, void* o, const
                      (pb.Nk + kKtPad - 1) / kKtPad * kKtPad, pb.H, pb.Hkv, pb.N, pb.Nk, Tq, causal_mode,
                      scale_log2e, (int)units, pb.n_planes, pb.gray_mode, pb.seed, pb.lse,
                      kt ? (const char*)kt + kt_copy_bytes(pb.B, pb.Hkv, pb.d, pb.Nk) : nullptr,
-                     MODE != kExact ? pb.perm_w : nullptr, pb.n_groups, pb.n_split, pb.part_o, (f32x2*)pb.part_stat);
+                     MODE != kExact ? pb.perm_w : nullptr, pb.n_groups, MODE == kExact ? BR : pb.Br, pb.n_split, pb.part_o, (f32x2*)pb.part_stat);
   return hipGetLastError();
 }
 
@@ -1115,9 +1137,9 @@ hipError_t launch_one(const void* q, const void* k, const void* v, void* o, cons
     const int tiles = (pb.Nk + BC - 1) / BC / pb.n_split;
     const bool halves =
         BR == 64 ? wgs <= (D == 64 ? 2 : 1) * kComputeUnits && tiles >= 4 &&
-                       (D == 128 || pb.n_split <= 2 || tiles < 12 || blocks_sharing_l2(pb) > (pb.causal ? 11 : 8))
+                       (D == 128 || pb.n_split <= 2 || tiles < 12 || blocks_sharing_l2(pb, BR) > (pb.causal ? 11 : 8))
                  : wgs <= kComputeUnits && tiles >= (pb.N <= BR && pb.n_split == 1 && wgs > kComputeUnits / 2 ? 32 : 24) &&
-                       (D == 64 || ((GROUPED || pb.causal) && (pb.n_split == 1 || tiles > 64 || (pb.N > BR && blocks_sharing_l2(pb) >= 12))));
+                       (D == 64 || ((GROUPED || pb.causal) && (pb.n_split == 1 || tiles > 64 || (pb.N > BR && blocks_sharing_l2(pb, BR) >= 12))));
     if (halves)
       return launch_ks<D, BR, BC, KRED, MODE, NG, 2>(q, k, v, o, perm, kt, pb, stream);
   }
@@ -1158,12 +1180,13 @@ hipError_t dispatch_kred(const void* q, const void* k, const void* v, void* o, c
 template <int BC>
 hipError_t dispatch_shape(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                           const void* kt, const Problem& pb, int distr, hipStream_t stream) {
-  if (pb.d == 64 && pb.Br == 64) return dispatch_kred<64, 64, BC>(q, k, v, o, perm, kt, pb, distr, stream);
-  if (pb.d == 64 && pb.Br == 128) return dispatch_kred<64, 128, BC>(q, k, v, o, perm, kt, pb, distr, stream);
-  if (pb.d == 64 && pb.Br == 256) return dispatch_kred<64, 256, BC>(q, k, v, o, perm, kt, pb, distr, stream);
-  if (pb.d == 128 && pb.Br == 64) return dispatch_kred<128, 64, BC>(q, k, v, o, perm, kt, pb, distr, stream);
-  if (pb.d == 128 && pb.Br == 128) return dispatch_kred<128, 128, BC>(q, k, v, o, perm, kt, pb, distr, stream);
-  if (pb.d == 128 && pb.Br == 256) return dispatch_kred<128, 256, BC>(q, k, v, o, perm, kt, pb, distr, stream);
+  const int rows = pb.rows > pb.Br ? pb.rows : pb.Br;
+  if (pb.d == 64 && rows == 64) return dispatch_kred<64, 64, BC>(q, k, v, o, perm, kt, pb, distr, stream);
+  if (pb.d == 64 && rows == 128) return dispatch_kred<64, 128, BC>(q, k, v, o, perm, kt, pb, distr, stream);
+  if (pb.d == 64 && rows == 256) return dispatch_kred<64, 256, BC>(q, k, v, o, perm, kt, pb, distr, stream);
+  if (pb.d == 128 && rows == 64) return dispatch_kred<128, 64, BC>(q, k, v, o, perm, kt, pb, distr, stream);
+  if (pb.d == 128 && rows == 128) return dispatch_kred<128, 128, BC>(q, k, v, o, perm, kt, pb, distr, stream);
+  if (pb.d == 128 && rows == 256) return dispatch_kred<128, 256, BC>(q, k, v, o, perm, kt, pb, distr, stream);
   return hipErrorInvalidValue;
 }
 

@@ -205,6 +205,7 @@ struct Problem {
   // bf16 forward with the key tiles of a Q block dealt out to n_split workgroups: their sums, float
   // [n_split][B][H][N][d], and (reference, row sum) pairs, float [n_split][B][H][N][2], exp2 domain
   int n_split = 1;
+  int rows = 0;   // query rows of such a call's workgroups where they are more than a Q block's (attn_bf16_shared_rows)
   float* part_o = nullptr;
   float* part_stat = nullptr;
 };
@@ -212,8 +213,8 @@ struct Problem {
 // Q blocks that read the same keys, per XCD and in eighths (12: one and a half), in a bf16 forward of up to 8 blocks per compute
 // unit: workgroup ids go round-robin over the 8 XCDs, causal blocks one after the other over all heads, others in a
 // range of heads per XCD where there are a multiple of 8 of them. Two or more find each other's tiles in the L2.
-inline int blocks_sharing_l2(const Problem& pb) {
-  const int Tq = (pb.N + pb.Br - 1) / pb.Br, heads = pb.B * pb.H, mine = pb.H / pb.Hkv * Tq;
+inline int blocks_sharing_l2(const Problem& pb, int rows) {
+  const int Tq = (pb.N + rows - 1) / rows, heads = pb.B * pb.H, mine = pb.H / pb.Hkv * Tq;
   if (!pb.causal) return (long long)heads * Tq % 8 == 0 ? 8 * mine : mine;
   return std::max(mine, Tq * std::gcd(heads, 8));
 }
@@ -240,6 +241,7 @@ bool attn_bf16_supported(const Problem& pb, int distr);
 bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split);
 bool attn_bf16_light(const Problem& pb);   // Q~ K^T is good enough to run where there is no room for the transposed copy
 int attn_bf16_splits(const Problem& pb, int distr);
+int attn_bf16_shared_rows(const Problem& pb);   // query rows of a grouped call's workgroups when its keys are dealt out
 int attn_bf16_exact_rows(const Problem& pb);   // query rows of an exact call's workgroups, in the place of Br
 // Few query rows against many keys (decoding): a kernel of its own, with its own number of shares.
 bool attn_bf16_few_rows(const Problem& pb, int distr);

@@ -550,3 +550,22 @@ def test_exact_rows_of_a_workgroup(B, H, Hkv, N, Nk, d, causal):
         assert err.max() <= 2e-2 and err.mean() <= 2e-3
         assert (lse[b, h].double().cpu()[rows] - want_lse).abs().max() <= 2e-3
         assert torch.isfinite(o.float()).all() and (o.float().abs().sum(dim=-1) > 0).all()
+
+
+# Two Q blocks of 64 rows in a workgroup (d = 128, keys dealt out): a second block without rows, of one row and whole, on either side of the
+# rule's lines, the table given or made; and waves without rows, which take no products, whole and in halves.
+@pytest.mark.parametrize("H,Hkv,N,Nk,Br", [(2, 2, 65, 5999, 64), (2, 2, 65, 6000, 64), (2, 1, 128, 6001, 64), (1, 1, 129, 6400, 64), (3, 3, 190, 6000, 64), (2, 2, 250, 6000, 64),
+                                           (2, 2, 100, 6000, 128), (2, 1, 160, 3000, 128), (2, 2, 290, 2000, 256), (70, 70, 65, 1700, 128)])
+@pytest.mark.parametrize("n_groups,given", [(64, False), (32, True)])
+def test_blocks_that_share_a_workgroup(H, Hkv, N, Nk, Br, n_groups, given):
+    import gpu_util as U
+    import torch
+    cfg = W.CONFIGS["long"].scaled(B=1, H=H, Hkv=Hkv, N=N, Nk=Nk, Br=Br, causal=True, n_groups=n_groups, recipe="normal")
+    print(f"case {cfg}", flush=True)
+    q, k, v = W.make(cfg)
+    p = U.oracle_params(cfg)
+    table = oracle.lsh_group(q, p)[1] if given else None
+    lse = torch.empty((1, H, N), dtype=torch.float32, device="cuda")
+    o, _, _ = U.run_gpu(cfg, q, k, v, lse_out=lse, perm_in=table)
+    U.assert_close(o, oracle.distr_fwd(q, k, v, p), "bf16")
+    assert np.abs(lse.cpu().numpy() - oracle.lse(q, k, p, distr=True)).max() <= 2e-2
