@@ -327,6 +327,26 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   bool lsh_in_kernel = distr && !p->perm_in && !p->hash_out &&
                        (matrix ? r.pb.n_planes <= 16 : da::attn_f32_groups(r.pb, r.dtype));
   const bool own_table = distr && !p->perm_in && !p->perm_out;
+  // Workgroups of a part of a Q block take its grouping from a table, made by the LSH kernel where the attention kernel would have
+  // grouped whole ones: only where there is room for it that no other call writes to (whole ones needed none).
+  ShareLease lease;
+  bool leased_table = false;
+  if (distr && matrix && !fused && n_possible == 1) {
+    const int rows = da::attn_bf16_grouped_rows(r.pb);
+    bool room = !(lsh_in_kernel && own_table);
+    if (rows && !room && !no_alloc) {
+      if (p->workspace) {
+        room = ((uintptr_t)p->workspace & 255u) == 0 && p->workspace_bytes >= (p->kt_in ? 0 : kt_bytes(r)) + perm_bytes(r);
+      } else if (perm_bytes(r) <= kShareBytes) {
+        lease.take(r.stream);
+        room = leased_table = lease.ptr != nullptr;
+      }
+    }
+    if (rows && room) {
+      r.pb.rows = rows;
+      lsh_in_kernel = false;
+    }
+  }
   // Scratch: [K^T copy | permutation table]. Only the parts this call writes are asked for: no K^T
   // copy when the caller brings kt_in, on the float path or for Q~ K^T, no table when the grouping comes
   // from perm_in, goes to perm_out, or stays inside the attention kernel. (A caller's workspace is
@@ -335,8 +355,8 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   if (distr && matrix && p->kt_in && ((uintptr_t)p->kt_in & 255u) != 0)
     return fail(DA_ERR_INVALID_ARG, "kt_in must be 256-byte aligned");
   const size_t kt_need = (distr && matrix && !p->kt_in) ? kt_bytes(r) : 0;
-  const size_t table_need = (own_table && !lsh_in_kernel) ? perm_bytes(r) : 0;
-  uint8_t* table = nullptr;
+  const size_t table_need = (own_table && !lsh_in_kernel && !leased_table) ? perm_bytes(r) : 0;
+  uint8_t* table = leased_table ? (uint8_t*)lease.ptr : nullptr;
   void* kt = nullptr;
   char* base = nullptr;
   size_t kt_room = fused ? kt_need : 0;
@@ -353,7 +373,6 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   const int n_split = fused ? 1 : n_possible;
   const size_t split_table = (own_table && n_split > 1 && !(few && lsh_in_kernel)) ? perm_bytes(r) : 0;
   const size_t split_need = split_table + share_bytes(r, n_split);
-  ShareLease lease;
   char* share = nullptr;
   if (n_split > 1) {
     if (no_alloc || p->workspace) {

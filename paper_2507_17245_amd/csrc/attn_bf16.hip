@@ -109,6 +109,22 @@ int attn_bf16_shared_rows(const Problem& pb) {
   return pb.d == 128 && pb.Br == 64 && pb.Bc == 64 && pb.N > 64 && pb.Nk >= 6000 && 10 * padded(128) <= 11 * padded(64) ? 128 : pb.Br;
 }
 
+// Query rows of a grouped call's workgroups (Q~ K^T, keys not dealt out): a part of a Q block where an exact call would take fewer rows
+// (0: a whole one). Their grouping comes from a table, which the LSH kernel has to make where the call would have had it in its
+// prologue (5-7 us instead of 3-6): for blocks of 256 rows always worth it, for blocks of 128 with halves of 64 on one round of compute units
+// and more than a dozen tiles. us, whole | parts: Br256 d64 H16 N600 22.9 | 18.7, N1000 30.1 | 21.3, N2000 43.5 | 28.4, d128 43.7 | 29.5 (N1000), not causal
+// H8 N3000 83.9 | 59.7; Br128 d64 H16 N1000 20.4 | 18.4, H8 N3000 33.7 | 30.0, d128 H8 N1000 27.7 | 25.0, but d64 H32 N700 16.6 | 17.3, N1400 25.2 | 27.7,
+// not causal H32 N700 17.8 | 20.5, H8 N600 15.8 | 16.2. Wherever the
+// table comes from the rows are the same, so that the output's bits are.
+int attn_bf16_grouped_rows(const Problem& pb) {
+  if (pb.Bc != 64 || pb.Br == 64 || attn_bf16_few_rows(pb, 1) || attn_bf16_short(pb, 1)) return 0;
+  const int rows = attn_bf16_exact_rows(pb);
+  if (rows >= pb.Br) return 0;
+  const long long n = (long long)pb.B * pb.H * ((pb.N + 63) / 64);
+  if (pb.Br == 256 || (n <= kComputeUnits && pb.Nk >= 800)) return rows;
+  return pb.d == 64 && pb.causal && n <= 2 * kComputeUnits && pb.Nk >= 1800 ? rows : 0;
+}
+
 // Key shares per Q block, for launches that would leave compute units without a workgroup: one
 // four-wave workgroup (two of two waves, half of one of eight) for each, at least four tiles per share, and only where the
 // tiles taken off a workgroup's walk outweigh the combine kernel (4 us, about 12 tiles) and, grouped,

@@ -359,10 +359,10 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   }
   if constexpr (GROUPED) {
     if (perm != nullptr) {
-      // One row of the table for each of the workgroup's Q blocks (of Br rows; several for kReplicated only). D is a power
+      // One row of the table for each of the workgroup's Q blocks (of Br rows; kReplicated: several, or a part of one). D is a power
       // of two: an out-of-range entry of a caller's table cannot index past a row.
-      const int blocks = (N + Br - 1) / Br, first = t * (BR / Br);
-      for (int i = tid; i < BR / Br * D; i += C::T)
+      const int blocks = (N + Br - 1) / Br, first = r0 / Br;
+      for (int i = tid; i < max(BR / Br, 1) * D; i += C::T)
         perm_lds[i] = first + i / D < blocks ? perm[((size_t)bh * blocks + first) * D + i] & (D - 1) : (uint8_t)(i % D);
     } else {
       // ---- LSH hash-and-group of this Q block inside the workgroup (Sec. 3.2, 3.3) -------------
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   kx8 qop[C::KSTEPS];
   if constexpr (MODE == kReplicated) {
     // Q~: the sampled channel of every channel's group, by way of a map in LDS
-    const int group = D / n_groups, n_maps = BR / Br * D;
+    const int group = D / n_groups, n_maps = max(BR / Br, 1) * D;
     uint8_t* from_lds = perm_lds + n_maps;
     const uint8_t* from = from_lds + rw * 32 / Br * D;   // the map of this wave's Q block
     if constexpr (QSTAGE) {
@@ -1180,7 +1180,7 @@ hipError_t dispatch_kred(const void* q, const void* k, const void* v, void* o, c
 template <int BC>
 hipError_t dispatch_shape(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                           const void* kt, const Problem& pb, int distr, hipStream_t stream) {
-  const int rows = pb.rows > pb.Br ? pb.rows : pb.Br;
+  const int rows = pb.rows ? pb.rows : pb.Br;
   if (pb.d == 64 && rows == 64) return dispatch_kred<64, 64, BC>(q, k, v, o, perm, kt, pb, distr, stream);
   if (pb.d == 64 && rows == 128) return dispatch_kred<64, 128, BC>(q, k, v, o, perm, kt, pb, distr, stream);
   if (pb.d == 64 && rows == 256) return dispatch_kred<64, 256, BC>(q, k, v, o, perm, kt, pb, distr, stream);

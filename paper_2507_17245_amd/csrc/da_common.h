@@ -205,7 +205,7 @@ struct Problem {
   // bf16 forward with the key tiles of a Q block dealt out to n_split workgroups: their sums, float
   // [n_split][B][H][N][d], and (reference, row sum) pairs, float [n_split][B][H][N][2], exp2 domain
   int n_split = 1;
-  int rows = 0;   // query rows of such a call's workgroups where they are more than a Q block's (attn_bf16_shared_rows)
+  int rows = 0;   // query rows of a workgroup where the table is given and they are not a Q block's (Q~ K^T; attn_bf16_shared_rows, attn_bf16_grouped_rows)
   float* part_o = nullptr;
   float* part_stat = nullptr;
 };
@@ -241,6 +241,7 @@ bool attn_bf16_supported(const Problem& pb, int distr);
 bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split);
 bool attn_bf16_light(const Problem& pb);   // Q~ K^T is good enough to run where there is no room for the transposed copy
 int attn_bf16_splits(const Problem& pb, int distr);
+int attn_bf16_grouped_rows(const Problem& pb);   // the same when they stay together, fewer than a Q block's (0: a Q block's)
 int attn_bf16_shared_rows(const Problem& pb);   // query rows of a grouped call's workgroups when its keys are dealt out
 int attn_bf16_exact_rows(const Problem& pb);   // query rows of an exact call's workgroups, in the place of Br
 // Few query rows against many keys (decoding): a kernel of its own, with its own number of shares.

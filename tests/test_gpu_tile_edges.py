@@ -569,3 +569,55 @@ def test_blocks_that_share_a_workgroup(H, Hkv, N, Nk, Br, n_groups, given):
     o, _, _ = U.run_gpu(cfg, q, k, v, lse_out=lse, perm_in=table)
     U.assert_close(o, oracle.distr_fwd(q, k, v, p), "bf16")
     assert np.abs(lse.cpu().numpy() - oracle.lse(q, k, p, distr=True)).max() <= 2e-2
+
+
+# Workgroups of a part of a Q block (Q~ K^T, keys together): ragged parts, a last block shorter than a part, one part of two; with a table
+# handed in, made by the call, asked for: the same bits; and with a workspace that has no room for one (whole blocks then).
+@pytest.mark.parametrize("base,H,N,Br,causal", [("llama", 4, 830, 128, True), ("llama", 6, 1030, 256, True), ("llama", 2, 300, 256, False), ("long", 4, 810, 128, True),
+                                                ("long", 3, 577, 256, False), ("long", 6, 1300, 256, True)])
+def test_parts_of_a_block(base, H, N, Br, causal):
+    import gpu_util as U
+    import torch
+
+    import paper_2507_17245_amd as da
+    cfg = W.CONFIGS[base].scaled(B=1, H=H, Hkv=H, N=N, Br=Br, causal=causal, recipe="normal")
+    print(f"case {cfg}", flush=True)
+    q, k, v = W.make(cfg)
+    want = oracle.distr_fwd(q, k, v, U.oracle_params(cfg))
+    tq, tk, tv = (U.to_dev(x, "bf16") for x in (q, k, v))
+    options = dict(Br=Br, Bc=cfg.Bc, n_groups=cfg.n_groups, causal=causal, lsh_seed=cfg.lsh_seed, n_planes=cfg.n_planes)
+    table = torch.zeros((1, H, cfg.Tq, cfg.d), dtype=torch.uint8, device="cuda")
+    room = torch.empty(da.distr_attn_kt_bytes(da.make_params(tq, tk, tv, **options)), dtype=torch.uint8, device="cuda")
+    outs = []
+    for more in (dict(perm_out=table), dict(), dict(perm_in=table), dict(workspace=room)):
+        o = torch.zeros_like(tq)
+        da.distr_attn_fwd_ex(tq, tk, tv, o, da.make_params(tq, tk, tv, **options, **more))
+        outs.append(o)
+    U.assert_close(outs[0].float().cpu().numpy().astype(np.float64), want, "bf16")
+    assert torch.equal(table.cpu(), torch.from_numpy(oracle.lsh_group(q, U.oracle_params(cfg))[1]))
+    assert all(torch.equal(o, outs[0]) for o in outs[1:3])
+    U.assert_close(outs[3].float().cpu().numpy().astype(np.float64), want, "bf16")
+
+
+def test_parts_of_a_block_on_many_streams():
+    """Calls in flight on several streams, none of which was given a workspace, keep their tables apart."""
+    import torch
+
+    import paper_2507_17245_amd as da
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    qs = [torch.randn((1, 8, 1000, 64), generator=gen, device="cuda").bfloat16() for _ in range(6)]
+    k, v = (torch.randn((1, 8, 1000, 64), generator=gen, device="cuda").bfloat16() for _ in range(2))
+
+    def call(q, o):
+        da.distr_attn_fwd_ex(q, k, v, o, da.make_params(q, k, v, Br=256, n_groups=32, causal=True))
+    want, got = ([torch.zeros_like(q) for q in qs] for _ in range(2))
+    for q, o in zip(qs, want):
+        call(q, o)
+        torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in qs]
+    for _ in range(10):
+        for q, o, stream in zip(qs, got, streams):
+            with torch.cuda.stream(stream):
+                call(q, o)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
