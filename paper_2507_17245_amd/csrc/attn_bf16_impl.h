@@ -145,8 +145,8 @@ struct Cfg {
 // Lazy reference maximum. A row keeps its reference until one of its scores runs more than kTau
 // (log2 units) ahead of it: P is then at most 2^kTau, numerator and denominator share the
 // reference, so the result is the same ratio, and the accumulator rescale (one multiply per
-// accumulator register) almost never runs. The test needs no row maximum: a lane's row sum over
-// the BC/2 keys it owns in a tile exceeds (BC/2) * 2^kTau only if one of them exceeds 2^kTau (an
+// accumulator register) almost never runs. The test needs no row maximum: a row's sum over n
+// keys of a tile (all BC, or the BC/2 that a lane owns) exceeds n * 2^kTau only if one of them exceeds 2^kTau (an
 // overflowed or NaN sum fails the comparison too), and the sum is needed anyway.
 constexpr float kTau = 8.0f;
 
