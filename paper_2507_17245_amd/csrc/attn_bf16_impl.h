@@ -143,27 +143,28 @@ struct Cfg {
 };
 
 // Lazy reference maximum. A row keeps its reference until one of its scores runs more than kTau
-// (log2 units) ahead of it: P is then at most 2^kTau, numerator and denominator share the
+// (log2 units) ahead of it and the test finds it: numerator and denominator share the
 // reference, so the result is the same ratio, and the accumulator rescale (one multiply per
-// accumulator register) almost never runs. The test needs no row maximum: a row's sum over n
-// keys of a tile (all BC, or the BC/2 that a lane owns) exceeds n * 2^kTau only if one of them exceeds 2^kTau (an
-// overflowed or NaN sum fails the comparison too), and the sum is needed anyway.
+// accumulator register) almost never runs. The test needs no row maximum: a lane's row sum over
+// the BC/2 keys it owns in a tile exceeds (BC/2) * 2^kTau only if one of them exceeds 2^kTau (an
+// overflowed or NaN sum fails the comparison too), and the sum is needed anyway. One that exceeds 2^kTau alone
+// may stay below it: P is at most (BC/2) * 2^kTau. Over all BC keys the test would let twice that pass and the largest weight would be the
+// exact P = 1 less often (exact H4 N1500 d64, queries of four times the scale: error against 64 bits 2.6 % larger, of the row statistics 27 %).
 constexpr float kTau = 8.0f;
 
 // Row sums of P, the B operands of P.V (lane = row lane % 32, either half of the wave its half of the keys). They are taken over the
 // rounded P, the values P.V really uses: numerator and denominator then carry the same rounding, which cancels for rows dominated
-// by few keys. On the matrix pipe: v_mfma_f32_16x16x32_bf16 takes lanes 16 g .. 16 g + 15 as rows 8 g .. of a 32 x 16 operand,
-// whose groups g = 0, 2 belong to rows 0..15 of P and g = 1, 3 to rows 16..31; the left operand has ones where the group is that of
-// the result's lane and zeros elsewhere, so that every lane receives the whole sum of its own row. 16 cycles of the pipe for eight
-// values a lane. (v_dot2c_f32_bf16 against (1, 1), one for two values, is no vector instruction like the others: it waits for the
+// by few keys. On the matrix pipe: v_mfma_f32_16x16x32_bf16 takes lanes 16 g .. 16 g + 15 as rows 8 g .. of a 32 x 16 operand;
+// the left operand has ones where the group is that of the result's lane and zeros elsewhere, so that every lane receives the sum of
+// its own values. 16 cycles of the pipe for eight values a lane. (v_dot2c_f32_bf16 against (1, 1), one for two values, is no vector instruction like the others: it waits for the
 // matrix pipe and holds it up, 13 cycles each between products. 8 exponentials with 3, 4, 6, 8 products beside them,
 // cycles by dot products | by this one, two waves per SIMD: 177 | 136, 209 | 160, 256 | 214, 310 | 273.)
-// An infinity or a NaN in a row makes the sum of the row 16 away NaN, too (zero times it): a tile with sums that are not finite takes
+// An infinity or a NaN in a lane makes the sums of the lanes 16, 32 and 48 away NaN, too (zero times it): a tile with sums that are not finite takes
 // them again by_lanes, with dot products. (Keeping the matrix pipe's sums of the other rows there, to the last bit, cost every call 1-2 %.)
 struct RowSum {
   bf16x8 own;
   __device__ explicit RowSum(int lane) {
-    const bf16 x = (bf16)(((lane >> 2 ^ lane >> 4) & 1) == 0 ? 1.0f : 0.0f);
+    const bf16 x = (bf16)(((lane >> 2 ^ lane >> 4) & 3) == 0 ? 1.0f : 0.0f);
 #pragma unroll
     for (int j = 0; j < 8; ++j) own[j] = x;
   }
@@ -185,7 +186,7 @@ struct RowSum {
         rs0 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pop[tt][j], pop[tt][j + 1]}, ones, rs0, false);
         rs1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pop[tt][j + 2], pop[tt][j + 3]}, ones, rs1, false);
       }
-    return half_swap_sum(rs0 + rs1);
+    return rs0 + rs1;
   }
 };
 
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   //   exact and Q~ K^T, d64 H32 Hkv8 N4096 causal 84.4 | 83.4, H16 N1500 18.9 | 18.2, Br256 N3000 53.8 | 51.3; B32 H12 N400 37.4 | 36.3;
   //   d128 H16 N8192 causal 266 | 262, Br256 N3000 77.1 | 71.0; fused d64 N16384 490 | 502; d128 N32768 3182 | 3240, but Br256 N3000 88.6 | 82.5
   constexpr bool MATRIX_SUM = FUSED ? D == 128 && BR == 256 && BC == 64 && NG >= 16 : D == 64 || BC != 128;
-  constexpr float kSumTrigger = (MATRIX_SUM ? BC : BC / 2) * 256.0f;   // keys per sum and tile, each at most 2^kTau
+  constexpr float kSumTrigger = (BC / 2) * 256.0f;   // BC/2 keys per lane and tile, each at most 2^kTau
   // A row whose first tile holds only scores of -infinity (masked keys; those of a share or half that the causal mask hides)
   // takes its first score above that as its reference: against 0, scores of -150 and less would be lost. The fused product has no such
   // scores (its operands are clamped), and undivided keys begin with one that every row sees.
@@ -735,7 +736,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   f32x16 neg_ref;
 #pragma unroll
   for (int i = 0; i < 16; ++i) neg_ref[i] = 0.0f;
-  float l_run = 0.0f;        // (MATRIX_SUM: over all keys, otherwise over this lane's half of them)
+  float l_run = 0.0f;        // over this lane's half of the keys
 
   // LDS byte offsets of this lane's operands inside a buffer.
   // Score product, A operand (exact): row lq (+32 per key block), logical chunk 2*s + hh.
@@ -1009,7 +1010,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   body(no, no, it, it & 1, s0, s1);
 
   // ---- epilogue: O = O_acc / l, bf16, 8-byte stores ---------------------------------------------
-  float l_tot = MATRIX_SUM ? l_run : half_swap_sum(l_run);
+  float l_tot = half_swap_sum(l_run);
   constexpr int OB = D / 32 / KS;            // 32-channel blocks of the output that this wave finishes
   const int c0 = KS == 2 ? half * (D / 2) : 0;
   f32x16 out[OB];

@@ -222,3 +222,32 @@ def test_rows_keep_to_themselves(shape, distr, value):
     (o, lse), (o1, lse1) = outs
     assert (o1.float() - o.float()).abs().le(2.0 ** -7 * o.float().abs()).all()
     assert (lse1 - lse).abs().max() <= 64 * 2.0 ** -24 + 2.0 ** -20   # (and the rounding of a statistic of up to 16)
+
+
+@pytest.mark.parametrize("shape", [(4, 300, 300, 64, 128, 64, False), (4, 300, 300, 64, 128, 64, True), (2, 400, 400, 128, 64, 64, True), (16, 1100, 1100, 128, 256, 64, False),
+                                   (12, 2200, 2200, 64, 128, 64, True), (2, 200, 6200, 64, 128, 64, False), (4, 300, 300, 64, 128, 128, False),
+                                   (4, 300, 300, 128, 64, 32, False)], ids=str)
+@pytest.mark.parametrize("distr", [False, True])
+def test_reference_moves_for_a_score_far_above(shape, distr):
+    """The row sum that moves a row's reference is that of the BC / 2 keys a lane owns: a weight of 2^(1/8) times its limit, BC / 2 times
+    2^8, is above it whatever the others are. The reference is then the largest score, whose weight is 1 and half of it 1/2, both exact: what is left is the
+    rounding of a statistic of up to 16 in a few operations. Against the old reference both would be rounded to bf16, 2^-8.4 above."""
+    import torch
+
+    import paper_2507_17245_amd as da
+    H, N, Nk, d, Br, Bc, causal = shape
+    far = 7 + math.log2(Bc) + 0.125
+    score = torch.full((Nk,), -100.0, dtype=torch.float64)
+    score[0], score[Bc + 6], score[Bc + 7] = 0.0, far, far - 1
+    q, k = torch.zeros((1, H, N, d), device="cuda"), torch.zeros((1, H, Nk, d), device="cuda")
+    q[..., 0], k[..., 0] = 1.0, score.float().cuda()
+    q, k = q.bfloat16(), k.bfloat16()
+    v, o, lse = torch.randn_like(k), torch.zeros_like(q), torch.zeros((1, H, N), device="cuda")
+    table = torch.arange(d, device="cuda").to(torch.uint8).expand(1, H, -(-N // Br), d).contiguous()
+    p = da.make_params(q, k, v, Br=Br, Bc=Bc, n_groups=d // 2 if distr else d, causal=causal, lse_out=lse, softmax_scale=math.log(2.0),
+                       perm_in=table if distr else None)
+    print(f"case {shape} distr={distr}", flush=True)
+    (da.distr_attn_fwd_ex if distr else da.distr_attn_exact_fwd_ex)(q, k, v, o, p)
+    want = torch.logsumexp(score * math.log(2.0), dim=0).item()
+    seen = torch.arange(N) + (Nk - N if causal else Nk) >= Bc + 7
+    assert seen.any() and (lse[0, :, seen.cuda()].double() - want).abs().max() <= 2.0 ** -16
