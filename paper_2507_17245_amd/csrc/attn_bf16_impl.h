@@ -138,7 +138,7 @@ struct Cfg {
   static constexpr int FUSE_OUT = (NG * PPR + TH - 1) / TH;   // 16-byte fused outputs per thread and tile
   static constexpr int KSTEPS = KRED / 16;        // MFMA steps of the score product
   // Register budget: two waves per SIMD, except the widest tile at d = 128, whose two score sets
-  // (128 registers) leave room for one. (Blocks of 128 rows at d = 128 in two halves, over the channels, spill four outside the loop.)
+  // (128 registers) leave room for one.
   static constexpr int WAVES_PER_SIMD = (BC == 128 && D == 128) ? 1 : 2;
 };
 
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
     bf16* __restrict__ o, const uint8_t* __restrict__ perm, const f16* __restrict__ kt, int Npad,
     int H, int Hkv, int N, int Nk, int Tq, int causal, float scale_log2e, int total_units, int n_planes,
     int gray_mode, uint64_t lsh_seed, float* __restrict__ lse, const char* __restrict__ rtab,
-    uint8_t* __restrict__ perm_w, int n_groups, int Br, int n_split, float* __restrict__ part_o, f32x2* __restrict__ part_stat) {
+    uint8_t* __restrict__ perm_w, int n_groups, int Br_log2, int n_split, float* __restrict__ part_o, f32x2* __restrict__ part_stat) {
   using C = Cfg<D, BR, BC, KRED, MODE, NG, KS>;
   constexpr bool FUSED = C::FUSED, GROUPED = C::GROUPED;
   // Sums of P on the matrix pipe (RowSum) where they take no registers that the wave has not got: fused kernels hold ten more
@@ -358,12 +358,17 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
     static_assert(QBLK % C::NW == 0, "whole blocks per wave");
     stage_q_block(std::integral_constant<int, QBLK / C::NW>(), q_stage);
   }
+  // Q blocks of 1 << log2_rows rows (kReplicated: not always the workgroup's), and the entries of the tables its rows are in: of one
+  // block, or of two of 64 rows at d = 128. Constants where they can be: divided and looked up for every launch, the maps of a block that
+  // no other shares its workgroup with took H32 N1400 d64 from 22.3 to 22.7 us (now 22.5), and fused kernels one more register.
+  const int log2_rows = MODE == kReplicated ? Br_log2 : __builtin_ctz(BR);
+  const int n_maps = MODE == kReplicated && D == 128 && BR == 128 ? max(BR >> log2_rows, 1) * D : D;
   if constexpr (GROUPED) {
     if (perm != nullptr) {
-      // One row of the table for each of the workgroup's Q blocks (of Br rows; kReplicated: several, or a part of one). D is a power
+      // One row of the table for each of the workgroup's Q blocks (kReplicated: several, or a part of one). D is a power
       // of two: an out-of-range entry of a caller's table cannot index past a row.
-      const int blocks = (N + Br - 1) / Br, first = r0 / Br;
-      for (int i = tid; i < max(BR / Br, 1) * D; i += C::T)
+      const int blocks = ((N - 1) >> log2_rows) + 1, first = r0 >> log2_rows;
+      for (int i = tid; i < n_maps; i += C::T)
         perm_lds[i] = first + i / D < blocks ? perm[((size_t)bh * blocks + first) * D + i] & (D - 1) : (uint8_t)(i % D);
     } else {
       // ---- LSH hash-and-group of this Q block inside the workgroup (Sec. 3.2, 3.3) -------------
@@ -558,11 +563,11 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   kx8 qop[C::KSTEPS];
   if constexpr (MODE == kReplicated) {
     // Q~: the sampled channel of every channel's group, by way of a map in LDS
-    const int group = D / n_groups, n_maps = max(BR / Br, 1) * D;
+    const int group = D / n_groups;
     uint8_t* from_lds = perm_lds + n_maps;
-    const uint8_t* from = from_lds + rw * 32 / Br * D;   // the map of this wave's Q block
+    const uint8_t* from = D == 128 && BR == 128 ? from_lds + (rw * 32 >> log2_rows) * D : from_lds;   // the map of this wave's Q block
     if constexpr (QSTAGE) {
-      for (int i = tid; i < n_maps; i += C::T) from_lds[i / D * D + perm_lds[i]] = perm_lds[i / group * group];
+      if (tid < D) from_lds[perm_lds[tid]] = perm_lds[tid / group * group];
       __syncthreads();
 #pragma unroll
       for (int s = 0; s < C::KSTEPS; ++s)
@@ -963,8 +968,9 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   }
 
   // A wave without rows (of a head's last block) brings its part of the tiles in and takes no products: what its SIMD and the power
-  // allow is the other waves' (200 rows on 32768 keys, H16 d128 86.0 -> 82.2 us, H32 N300 on 16000 130 -> 122, d64 H16 47.1 -> 44.9).
-  if (MODE != kFused && qw0 >= N) {
+  // allow is the other waves' (200 rows on 32768 keys, H16 d128 86.0 -> 82.2 us, H32 N300 on 16000 130 -> 122, d64 H16 47.1 -> 44.9). Tiles
+  // of 64 keys: with 128 at d = 128 the addresses that this loop keeps double what blocks of 256 rows spill (35 registers -> 77).
+  if (MODE != kFused && BC == 64 && qw0 >= N) {
     __syncthreads();
     for (int it = 0; it < n_tiles - 1; ++it) {
       feed(it, it & 1);
@@ -1109,7 +1115,7 @@ hipError_t launch_ks(const void* q, const void* k, const void* v, void* o, const
                      (pb.Nk + kKtPad - 1) / kKtPad * kKtPad, pb.H, pb.Hkv, pb.N, pb.Nk, Tq, causal_mode,
                      scale_log2e, (int)units, pb.n_planes, pb.gray_mode, pb.seed, pb.lse,
                      kt ? (const char*)kt + kt_copy_bytes(pb.B, pb.Hkv, pb.d, pb.Nk) : nullptr,
-                     MODE != kExact ? pb.perm_w : nullptr, pb.n_groups, MODE == kExact ? BR : pb.Br, pb.n_split, pb.part_o, (f32x2*)pb.part_stat);
+                     MODE != kExact ? pb.perm_w : nullptr, pb.n_groups, __builtin_ctz(pb.Br), pb.n_split, pb.part_o, (f32x2*)pb.part_stat);
   return hipGetLastError();
 }
 
