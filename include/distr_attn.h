@@ -127,7 +127,9 @@ int distr_attn_exact_fwd(const void *q, const void *k, const void *v, void *o, i
  * projections and neither perm_in nor hash_out, the attention kernel runs the LSH stage of each
  * query block in that block's own workgroup (same arithmetic and tables as distr_attn_lsh_group;
  * the table is written only if perm_out is given, e.g. to hand it to the backward pass as
- * perm_in); otherwise the stage is a kernel of its own. */
+ * perm_in); otherwise, and where workgroups take parts of blocks of 128 or 256 rows (short prompts), the stage
+ * is a kernel of its own. What that kernel hands such workgroups lies in o until they write their rows
+ * of it. */
 int distr_attn_fwd_ex(const void *q, const void *k, const void *v, void *o, const da_params *p);
 int distr_attn_exact_fwd_ex(const void *q, const void *k, const void *v, void *o, const da_params *p);
 

@@ -328,35 +328,22 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
                        (matrix ? r.pb.n_planes <= 16 : da::attn_f32_groups(r.pb, r.dtype));
   const bool own_table = distr && !p->perm_in && !p->perm_out;
   // Workgroups of a part of a Q block take its grouping from a table, made by the LSH kernel where the attention kernel would have
-  // grouped whole ones: only where there is room for it that no other call writes to (whole ones needed none).
-  ShareLease lease;
-  bool leased_table = false;
-  if (distr && matrix && !fused && n_possible == 1) {
-    const int rows = da::attn_bf16_grouped_rows(r.pb);
-    bool room = !(lsh_in_kernel && own_table);
-    if (rows && !room && !no_alloc) {
-      if (p->workspace) {
-        room = ((uintptr_t)p->workspace & 255u) == 0 && p->workspace_bytes >= (p->kt_in ? 0 : kt_bytes(r)) + perm_bytes(r);
-      } else if (perm_bytes(r) <= kShareBytes) {
-        lease.take(r.stream);
-        room = leased_table = lease.ptr != nullptr;
-      }
-    }
-    if (rows && room) {
-      r.pb.rows = rows;
-      lsh_in_kernel = false;
-    }
+  // grouped whole ones. That kernel leaves a workgroup its row in o, where its own first output row will be: no scratch, and rows,
+  // and with them the bits of the output, that are the same for a call wherever it is made (under capture, without allocations, on any stream).
+  if (distr && matrix && !fused && n_possible == 1 && (r.pb.rows = da::attn_bf16_grouped_rows(r.pb)) != 0) {
+    r.pb.table_in_o = lsh_in_kernel && own_table;
+    lsh_in_kernel = r.pb.table_in_o;
   }
   // Scratch: [K^T copy | permutation table]. Only the parts this call writes are asked for: no K^T
   // copy when the caller brings kt_in, on the float path or for Q~ K^T, no table when the grouping comes
-  // from perm_in, goes to perm_out, or stays inside the attention kernel. (A caller's workspace is
+  // from perm_in, goes to perm_out or o, or stays inside the attention kernel. (A caller's workspace is
   // checked for the K^T copy whichever product the call takes: what is enough depends on the
   // arguments alone.)
   if (distr && matrix && p->kt_in && ((uintptr_t)p->kt_in & 255u) != 0)
     return fail(DA_ERR_INVALID_ARG, "kt_in must be 256-byte aligned");
   const size_t kt_need = (distr && matrix && !p->kt_in) ? kt_bytes(r) : 0;
-  const size_t table_need = (own_table && !lsh_in_kernel && !leased_table) ? perm_bytes(r) : 0;
-  uint8_t* table = leased_table ? (uint8_t*)lease.ptr : nullptr;
+  const size_t table_need = (own_table && !lsh_in_kernel) ? perm_bytes(r) : 0;
+  uint8_t* table = r.pb.table_in_o ? (uint8_t*)o : nullptr;
   void* kt = nullptr;
   char* base = nullptr;
   size_t kt_room = fused ? kt_need : 0;
@@ -373,6 +360,7 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   const int n_split = fused ? 1 : n_possible;
   const size_t split_table = (own_table && n_split > 1 && !(few && lsh_in_kernel)) ? perm_bytes(r) : 0;
   const size_t split_need = split_table + share_bytes(r, n_split);
+  ShareLease lease;
   char* share = nullptr;
   if (n_split > 1) {
     if (no_alloc || p->workspace) {
@@ -408,11 +396,11 @@ int attention(const void* q, const void* k, const void* v, void* o, const da_par
   const uint8_t* perm = p->perm_in;
   if (lsh_in_kernel) r.pb.perm_w = p->perm_out;
   r.pb.group_in_kernel = lsh_in_kernel && !matrix;
-  if (distr && !p->perm_in && !lsh_in_kernel) {
+  if (distr && !p->perm_in && (!lsh_in_kernel || r.pb.table_in_o)) {
     if (p->perm_out) table = p->perm_out;
     rc = check_launch(r.pb.side == 1
                           ? da::launch_lsh_group(k, r.dtype, key_side_problem(r.pb), table, p->hash_out, r.stream)
-                          : da::launch_lsh_group(q, r.dtype, r.pb, table, p->hash_out, r.stream),
+                          : da::launch_lsh_group(q, r.dtype, r.pb, table, p->hash_out, r.stream, r.pb.table_in_o ? r.pb.rows : 0),
                       "lsh_group launch", r.stream);
     if (rc) return rc;
     perm = table;

@@ -115,7 +115,7 @@ int attn_bf16_shared_rows(const Problem& pb) {
 // and more than a dozen tiles. us, whole | parts: Br256 d64 H16 N600 22.9 | 18.7, N1000 30.1 | 21.3, N2000 43.5 | 28.4, d128 43.7 | 29.5 (N1000), not causal
 // H8 N3000 83.9 | 59.7; Br128 d64 H16 N1000 20.4 | 18.4, H8 N3000 33.7 | 30.0, d128 H8 N1000 27.7 | 25.0, but d64 H32 N700 16.6 | 17.3, N1400 25.2 | 27.7,
 // not causal H32 N700 17.8 | 20.5, H8 N600 15.8 | 16.2. Wherever the
-// table comes from the rows are the same, so that the output's bits are.
+// table comes from (the caller, o) the rows are the same, so that the output's bits are.
 int attn_bf16_grouped_rows(const Problem& pb) {
   if (pb.Bc != 64 || pb.Br == 64 || attn_bf16_few_rows(pb, 1) || attn_bf16_short(pb, 1)) return 0;
   const int rows = attn_bf16_exact_rows(pb);

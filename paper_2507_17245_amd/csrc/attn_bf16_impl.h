@@ -196,7 +196,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
     bf16* __restrict__ o, const uint8_t* __restrict__ perm, const f16* __restrict__ kt, int Npad,
     int H, int Hkv, int N, int Nk, int Tq, int causal, float scale_log2e, int total_units, int n_planes,
     int gray_mode, uint64_t lsh_seed, float* __restrict__ lse, const char* __restrict__ rtab,
-    uint8_t* __restrict__ perm_w, int n_groups, int Br_log2, int n_split, float* __restrict__ part_o, f32x2* __restrict__ part_stat) {
+    uint8_t* __restrict__ perm_w, int n_groups, int Br_log2, int table_in_o, int n_split, float* __restrict__ part_o, f32x2* __restrict__ part_stat) {
   using C = Cfg<D, BR, BC, KRED, MODE, NG, KS>;
   constexpr bool FUSED = C::FUSED, GROUPED = C::GROUPED;
   // Sums of P on the matrix pipe (RowSum) where they take no registers that the wave has not got: fused kernels hold ten more
@@ -367,10 +367,12 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   if constexpr (GROUPED) {
     if (perm != nullptr) {
       // One row of the table for each of the workgroup's Q blocks (kReplicated: several, or a part of one). D is a power
-      // of two: an out-of-range entry of a caller's table cannot index past a row.
+      // of two: an out-of-range entry of a caller's table cannot index past a row. table_in_o: the row lies in o, where the workgroup's first
+      // output row will.
       const int blocks = ((N - 1) >> log2_rows) + 1, first = r0 >> log2_rows;
+      const uint8_t* rows = MODE == kReplicated && table_in_o ? (const uint8_t*)(o + ((size_t)bh * N + r0) * D) : perm + ((size_t)bh * blocks + first) * D;
       for (int i = tid; i < n_maps; i += C::T)
-        perm_lds[i] = first + i / D < blocks ? perm[((size_t)bh * blocks + first) * D + i] & (D - 1) : (uint8_t)(i % D);
+        perm_lds[i] = first + i / D < blocks ? rows[i] & (D - 1) : (uint8_t)(i % D);
     } else {
       // ---- LSH hash-and-group of this Q block inside the workgroup (Sec. 3.2, 3.3) -------------
       // The table equals the stand-alone LSH kernel's bit for bit: a projection's sign is that of
@@ -1116,7 +1118,7 @@ hipError_t launch_ks(const void* q, const void* k, const void* v, void* o, const
                      (pb.Nk + kKtPad - 1) / kKtPad * kKtPad, pb.H, pb.Hkv, pb.N, pb.Nk, Tq, causal_mode,
                      scale_log2e, (int)units, pb.n_planes, pb.gray_mode, pb.seed, pb.lse,
                      kt ? (const char*)kt + kt_copy_bytes(pb.B, pb.Hkv, pb.d, pb.Nk) : nullptr,
-                     MODE != kExact ? pb.perm_w : nullptr, pb.n_groups, __builtin_ctz(pb.Br), pb.n_split, pb.part_o, (f32x2*)pb.part_stat);
+                     MODE != kExact ? pb.perm_w : nullptr, pb.n_groups, __builtin_ctz(pb.Br), pb.table_in_o, pb.n_split, pb.part_o, (f32x2*)pb.part_stat);
   return hipGetLastError();
 }
 

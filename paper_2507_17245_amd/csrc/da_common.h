@@ -206,6 +206,7 @@ struct Problem {
   // [n_split][B][H][N][d], and (reference, row sum) pairs, float [n_split][B][H][N][2], exp2 domain
   int n_split = 1;
   int rows = 0;   // query rows of a workgroup where the table is given and they are not a Q block's (Q~ K^T; attn_bf16_shared_rows, attn_bf16_grouped_rows)
+  bool table_in_o = false;   // the LSH kernel has left every such workgroup its row of the table in o, at its first output row
   float* part_o = nullptr;
   float* part_stat = nullptr;
 };
@@ -220,8 +221,9 @@ inline int blocks_sharing_l2(const Problem& pb, int rows) {
 }
 
 // Launchers (defined next to their kernels). All return hipError_t of the launch.
+// part_rows (bf16): perm_out is no table but a tensor like q, where every part_rows rows of a block begin with its row of the table.
 hipError_t launch_lsh_group(const void* q, int dtype, const Problem& pb, uint8_t* perm_out,
-                            uint32_t* hash_out, hipStream_t stream);
+                            uint32_t* hash_out, hipStream_t stream, int part_rows = 0);
 // K [B][Hkv][Nk][d] bf16 -> K^T [B][Hkv][d][Npad] half (Npad = Nk rounded up to kKtPad), for the distr path,
 // followed at kt_copy_bytes() by the projection-matrix table (kRtabBytes) for pb's seed, n_planes and Br.
 hipError_t launch_kt_prepass(const void* k, void* kt, const Problem& pb, hipStream_t stream);
