@@ -202,9 +202,10 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   // Sums of P on the matrix pipe (RowSum) where they take no registers that the wave has not got: fused kernels hold ten more
   // than with dot products, which costs a wave per SIMD or spills, and at d = 128 (blocks of 128 rows, one long wave) what the clock falls by. us, dot products | this:
   //   exact and Q~ K^T, d64 Br256 N3000 46.0 | 45.1, Q~ K^T 42.5 | 41.4, Br64 N200 on 30000 keys 43.0 | 42.6, Br128 45.4 | 44.8;
-  //   exact d64 Br128, H32 N2048 causal 25.3 | 25.9, H16 N4096 44.0 | 44.5, H32 Hkv8 N4096 81.9 | 81.9 (not taken for B4 H32 N2500 132.9 | 130.7);
+  //   exact d64 Br128, keys together, H32 N2048 causal 25.3 | 25.9, H16 N4096 44.0 | 44.5, H32 Hkv8 N4096 81.9 | 81.9 (not taken for B4 H32 N2500 132.9 | 130.7),
+  //   in halves N300 on 16000 keys 33.6 | 32.8, N200 on 30000 40.6 | 40.2; Q~ K^T d64 Br128 H32 N1000 18.5 | 18.5, B2 H32 N530 on 4000 58.8 | 58.5;
   //   d128 H16 N8192 causal 266 | 262, Br256 N3000 77.1 | 71.0; fused d64 N16384 490 | 502; d128 N32768 3182 | 3240, but Br256 N3000 88.6 | 82.5
-  constexpr bool MATRIX_SUM = FUSED ? D == 128 && BR == 256 && BC == 64 && NG >= 16 : D == 64 ? MODE != kExact || BR != 128 : BC != 128;
+  constexpr bool MATRIX_SUM = FUSED ? D == 128 && BR == 256 && BC == 64 && NG >= 16 : D == 64 ? BR != 128 || KS == 2 || MODE != kExact : BC != 128;
   constexpr float kSumTrigger = (BC / 2) * 256.0f;   // BC/2 keys per lane and tile, each at most 2^kTau
   // A row whose first tile holds only scores of -infinity (masked keys; those of a share or half that the causal mask hides)
   // takes its first score above that as its reference: against 0, scores of -150 and less would be lost. The fused product has no such
@@ -1006,7 +1007,7 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   int it = 0;
   // (at d = 128 blocks of 64 rows run one wave per SIMD, which waits for its instructions itself: by where the loop lies in the 64-byte lines
   // H8 N4000 Nk5000 took 91 to 103 us; exact d64 Br128 H32 N2048 26.95 | 26.80, H16 N4096 46.16 | 46.04)
-  if constexpr ((D == 128 && BR == 64 && KS == 1) || (D == 64 && BR == 128 && MODE == kExact)) asm volatile(".p2align 6");
+  if constexpr ((D == 128 && BR == 64 && KS == 1) || (D == 64 && BR == 128 && KS == 1 && MODE == kExact)) asm volatile(".p2align 6");
   for (; it + 2 < n_full; it += 2) {
     body(no, yes, it, 0, s0, s1);
     body(no, yes, it + 1, 1, s1, s0);
