@@ -46,14 +46,14 @@ namespace da {
 
 namespace {
 
-constexpr int kOwnRows = 256;   // of a Q block that a workgroup groups itself, d = 64 (94 KB of LDS with the tiles)
+constexpr int kOwnRows = 256;   // of a Q block that a workgroup groups itself, d = 64 (with the tiles 93 KB of LDS, 128 KB for eight waves: one workgroup to a CU)
 
 enum Mode { kQueryFull, kQueryFused, kKeyFull, kKeyFused };
 
 // OWN: the workgroup groups the Q block that its rows lie in itself, into lds.perm, and writes its table where perm_w is given
 // (rule: launch_waves).
 template <typename E, int D, int G, int MODE, int NW, bool PIECES, bool OWN>
-__global__ __launch_bounds__(NW * 64, (D == 64 ? 2 : 1)) void attn_f32_kernel(
+__global__ __launch_bounds__(NW * 64, (D == 64 && !(OWN && NW == 4) ? 2 : 1)) void attn_f32_kernel(
     const E* __restrict__ q, const E* __restrict__ k, const E* __restrict__ v, E* __restrict__ o,
     const uint8_t* __restrict__ perm, int H, int Hkv, int N, int Nk, int Br, int Tq, int Tw, int n_groups,
     int causal, float scale, int Bc, float* __restrict__ lse, uint8_t* __restrict__ perm_w, int n_planes, int gray_mode, uint64_t seed) {
