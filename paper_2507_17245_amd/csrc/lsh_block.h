@@ -29,7 +29,7 @@ __device__ inline int lsh_chunk_swz(int row) {
 
 // Rows r0 .. of `block` (`rows` of them exist, the rest reads as zeros) into LDS.
 template <typename T, int D, int CR, bool SWZ, int THREADS>
-__device__ inline void lsh_stage_rows(const T* block, int rows, int r0, char* dst) {
+__device__ __forceinline__ void lsh_stage_rows(const T* block, int rows, int r0, char* dst) {
   typedef __attribute__((address_space(3))) void lds_void;
   constexpr int CH = D * (int)sizeof(T) / 16, N = (CR * CH + THREADS - 1) / THREADS;
   static_assert(CR * CH % 64 == 0, "whole loads per wave");
@@ -57,7 +57,7 @@ __device__ inline void lsh_stage_rows(const T* block, int rows, int r0, char* ds
 // Sign codes of the bf16 block's channels, projections p0 .. p0 + 15, into lds.code. `rows`: a multiple of 32, the rest of
 // the block is zeros.
 template <int D, int BR, int THREADS>
-__device__ inline void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int rows, int p0, int n_planes) {
+__device__ __forceinline__ void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int rows, int p0, int n_planes) {
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
   constexpr int RPAD = LshLds<bf16, D, BR>::RPAD, ROWB = D * 2;
   const bf16* rp1 = (const bf16*)lds.table;
@@ -118,9 +118,9 @@ __device__ inline void lsh_codes_matrix(LshLds<bf16, D, BR>& lds, int rows, int 
 }
 
 // `rows` rows of D channels at `block`; perm and hash (either may be null): the block's table entries. With KEEP the workgroup
-// has the permutation in lds.perm, too.
+// has the permutation in lds.perm, too. (Inlined by force: as a function that two kernels call, bf16 H32 N4096 d64 10.2 -> 23.3 us.)
 template <typename T, int D, int BR, int THREADS, bool KEEP = false>
-__device__ inline void lsh_block(const T* __restrict__ block, int rows, int n_planes, int gray_mode, uint64_t seed,
+__device__ __forceinline__ void lsh_block(const T* __restrict__ block, int rows, int n_planes, int gray_mode, uint64_t seed,
                                  uint8_t* __restrict__ perm, uint32_t* __restrict__ hash, LshLds<T, D, BR>& lds) {
   using L = LshLds<T, D, BR>;
   constexpr int NPG = THREADS / D;            // threads per channel
@@ -146,8 +146,6 @@ __device__ inline void lsh_block(const T* __restrict__ block, int rows, int n_pl
     } else {
       // A thread takes PPT projections, pg*PPT .. pg*PPT + PPT - 1: as few as there are for everyone.
       float* R = (float*)lds.table;           // [row][16]
-      const int np = min(16, n_planes - p0);
-      uint32_t bits = 0;
       auto project = [&](auto ppt_c) {
         constexpr int PPT = decltype(ppt_c)::value, PL = PPT * NPG;   // PL: projections of the table that are generated
         float acc[PPT];
@@ -157,8 +155,10 @@ __device__ inline void lsh_block(const T* __restrict__ block, int rows, int n_pl
           if (p0 + r0 > 0) __syncthreads();   // the staged rows are no longer read
           lsh_stage_rows<T, D, L::CR, false, THREADS>(block, rows, r0, lds.rows);
           if (r0 == 0) {
-            for (int i = tid; i < min(rows, BR) * PL; i += THREADS)
-              R[i / PL * 16 + i % PL] = i % PL < np ? hyperplane_entry(seed, (uint32_t)(p0 + i % PL), (uint32_t)(i / PL)) : 0.0f;
+            for (int i = tid; i < min(rows, BR) * PL; i += THREADS) {
+              const int p = p0 + (i & (PL - 1)), r = i / PL;
+              R[PL == 16 ? i : r * 16 + p] = p < n_planes ? hyperplane_entry(seed, (uint32_t)p, (uint32_t)r) : 0.0f;
+            }
             if (p0 == 0 && tid < D) lds.code[tid] = 0;
           }
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -173,16 +173,19 @@ __device__ inline void lsh_block(const T* __restrict__ block, int rows, int n_pl
             for (int j = 0; j < PPT; ++j) acc[j] = __builtin_fmaf(xr, Rt[r * 16 + j], acc[j]);
           }
         }
+        // (n_planes and p0 are at hand; their difference is one register more, which at 64 rows and d = 128 left the loop above the rows of one step
+        // in flight instead of eight: 4.8 -> 5.8 us)
+        uint32_t bits = 0;
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
-          const int p = pg * PPT + j;
-          if (p < np && acc[j] > 0.0f) bits |= 1u << (n_planes - 1 - p0 - p);   // projection 0 = top bit
+          const int p = p0 + pg * PPT + j;
+          if (p < n_planes && acc[j] > 0.0f) bits |= 1u << (n_planes - 1 - p);   // projection 0 = top bit
         }
+        if (bits) atomicOr(&lds.code[c], bits);
       };
       // (four projections at a workgroup of four threads a channel: tiny calls, whose workgroups all wait for this; H1 N256 11.3 | 10.6 us)
-      if (KEEP && NPG == 4 && np <= 4) project(std::integral_constant<int, KEEP ? 1 : 16 / NPG>());
+      if (KEEP && NPG == 4 && n_planes <= 4) project(std::integral_constant<int, KEEP ? 1 : 16 / NPG>());
       else project(std::integral_constant<int, 16 / NPG>());
-      if (bits) atomicOr(&lds.code[c], bits);
     }
   }
   __syncthreads();

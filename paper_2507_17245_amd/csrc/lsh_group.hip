@@ -22,27 +22,27 @@
 
 namespace da {
 
-template <typename T, int D, int BR, int THREADS>
+// PARTS: not a table, but in a tensor like q the block's row of it at every part of part_rows rows.
+template <typename T, int D, int BR, int THREADS, bool PARTS>
 __global__ __launch_bounds__(THREADS) void lsh_group_kernel(
     const T* __restrict__ q, uint8_t* __restrict__ perm_out, uint32_t* __restrict__ hash_out,
     int N, int Tq, int n_planes, int gray_mode, uint64_t seed, int part_rows) {
   __shared__ LshLds<T, D, BR> lds;
   const int t = blockIdx.x % Tq;
   const size_t bh = blockIdx.x / Tq;
-  // part_rows: not a table, but in a bf16 tensor like q the block's row of it at every part of so many rows
-  const size_t at = part_rows ? (bh * N + (size_t)t * BR) * (D * 2) : (size_t)blockIdx.x * D;
+  const size_t at = PARTS ? (bh * N + (size_t)t * BR) * (D * sizeof(T)) : (size_t)blockIdx.x * D;
   lsh_block<T, D, BR, THREADS>(q + (bh * N + (size_t)t * BR) * D, min(BR, N - t * BR), n_planes, gray_mode, seed,
                       perm_out ? perm_out + at : nullptr, hash_out ? hash_out + at : nullptr, lds);
-  if (part_rows && threadIdx.x < D)
-    for (int r = part_rows; r < min(BR, N - t * BR); r += part_rows) perm_out[at + (size_t)r * (D * 2) + threadIdx.x] = lds.perm[threadIdx.x];
+  if (PARTS && threadIdx.x < D)
+    for (int r = part_rows; r < min(BR, N - t * BR); r += part_rows) perm_out[at + (size_t)r * (D * sizeof(T)) + threadIdx.x] = lds.perm[threadIdx.x];
 }
 
-template <typename T, int D>
+template <typename T, int D, bool PARTS>
 static hipError_t launch_rows(const T* q, const Problem& pb, uint8_t* perm_out, uint32_t* hash_out, int part_rows, hipStream_t stream) {
   const int Tq = (pb.N + pb.Br - 1) / pb.Br;
   const long long units = (long long)pb.B * pb.H * Tq;
 #define DA_LSH_T(BR, THREADS)                                                                                                       \
-  hipLaunchKernelGGL((lsh_group_kernel<T, D, BR, THREADS>), dim3((unsigned)units), dim3(THREADS), 0, stream, q, perm_out, hash_out, \
+  hipLaunchKernelGGL((lsh_group_kernel<T, D, BR, THREADS, PARTS>), dim3((unsigned)units), dim3(THREADS), 0, stream, q, perm_out, hash_out, \
                      pb.N, Tq, pb.n_planes, pb.gray_mode, pb.seed, part_rows)
 #define DA_LSH(BR)                                                      \
   do {                                                                  \
@@ -78,10 +78,13 @@ static hipError_t launch_rows(const T* q, const Problem& pb, uint8_t* perm_out, 
 
 hipError_t launch_lsh_group(const void* q, int dtype, const Problem& pb, uint8_t* perm_out,
                             uint32_t* hash_out, hipStream_t stream, int part_rows) {
-  if (dtype == 0 && pb.d == 64) return launch_rows<bf16, 64>((const bf16*)q, pb, perm_out, hash_out, part_rows, stream);
-  if (dtype == 0 && pb.d == 128) return launch_rows<bf16, 128>((const bf16*)q, pb, perm_out, hash_out, part_rows, stream);
-  if (dtype == 1 && pb.d == 64) return launch_rows<float, 64>((const float*)q, pb, perm_out, hash_out, 0, stream);
-  if (dtype == 1 && pb.d == 128) return launch_rows<float, 128>((const float*)q, pb, perm_out, hash_out, 0, stream);
+  if (part_rows && dtype == 0 && pb.d == 64) return launch_rows<bf16, 64, true>((const bf16*)q, pb, perm_out, hash_out, part_rows, stream);
+  if (part_rows && dtype == 0 && pb.d == 128) return launch_rows<bf16, 128, true>((const bf16*)q, pb, perm_out, hash_out, part_rows, stream);
+  if (part_rows) return hipErrorInvalidValue;
+  if (dtype == 0 && pb.d == 64) return launch_rows<bf16, 64, false>((const bf16*)q, pb, perm_out, hash_out, 0, stream);
+  if (dtype == 0 && pb.d == 128) return launch_rows<bf16, 128, false>((const bf16*)q, pb, perm_out, hash_out, 0, stream);
+  if (dtype == 1 && pb.d == 64) return launch_rows<float, 64, false>((const float*)q, pb, perm_out, hash_out, 0, stream);
+  if (dtype == 1 && pb.d == 128) return launch_rows<float, 128, false>((const float*)q, pb, perm_out, hash_out, 0, stream);
   return hipErrorInvalidValue;
 }
 
