@@ -110,8 +110,9 @@ __global__ __launch_bounds__(NW * 64, (D == 64 && !(OWN && NW == 4) ? 2 : 1)) vo
   };
   // V of a tile is asked for behind the products of the tile before it, in front of the staging of its own K (a compute unit takes the
   // 24 KB of a wave's tile in at 64 bytes a cycle, half a microsecond for four waves, in which a wave cannot go on): d128 H4 N2000 89.2 ->
-  // 85.1 us, groups of four H2 N1000 44.8 -> 41.2, d64 H8 N2048 59.0 -> 58.0. The mirrored form at d = 64 is slower with it (62.8 -> 64.3).
-  constexpr bool V_AHEAD = !kMirrored || D == 128;
+  // 85.1 us, groups of four H2 N1000 44.8 -> 41.2, d64 H8 N2048 59.0 -> 58.0. Slower with it: the mirrored form at d = 64 (62.8 -> 64.3), and eight waves
+  // that begin with their first tiles (table given or exact, two waves to a SIMD: H8 N300 8.8 -> 9.4, exact 11.3 -> 11.8, H4 N500 13.4 -> 14.4).
+  constexpr bool V_AHEAD = D == 128 || (!kMirrored && (OWN || NW == 4));
   constexpr int VR = NB / 2;   // raw pairs per row of V and lane
   typename Pair<E>::raw vreg[16][VR];
   auto load_v = [&](int tile) {
