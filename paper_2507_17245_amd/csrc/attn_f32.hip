@@ -529,7 +529,10 @@ hipError_t launch_typed(const void* q, const void* k, const void* v, void* o, co
 // itself, so that its LDS and the grouping, repeated by the workgroups of a Q block, cost nothing but their time, which K and V of the first
 // tiles travel in. us, LSH kernel | itself, groups of two: H1 N64 9.9 | 8.4, H1 N256 (4 projections) 12.4 | 10.6, H4 N200 causal 13.5 | 11.5,
 // H8 N700 causal 18.4 | 16.0, H8 N1000 22.2 | 21.1, H2 N2000 30.6 | 29.2. At d = 128 (twice the channels for four waves, which
-// the LSH kernel gives eight) it loses: H2 N100 16.4 | 21.9, H4 N2000 89 | 96.
+// the LSH kernel gives eight) it loses: H2 N100 16.4 | 21.9, H4 N2000 89 | 96. Blocks of 256 rows, 16 projections: H1 N256 17.2 | 16.1,
+// H4 N300 17.6 | 17.3, H8 N1000 25.5 | 24.5, H2 N4000 60.6 | 59.2. More than 16 projections walk the block's rows once more, 32 of them: H1 N256 Br256
+// 24.1 | 22.7, H8 N1000 32.4 | 32.1, Br64 H4 N300 14.9 | 14.3, but Br128 H8 N300 17.5 | 17.6, groups of eight H4 N500 Br256 29.6 | 30.2: no line of their own,
+// as a call that groups itself needs no room for a table.
 bool attn_f32_groups(const Problem& pb, int dtype) {
   return dtype == 1 && pb.side == 0 && pb.d == 64 && (long long)pb.B * pb.H * ((pb.N + kTile - 1) / kTile) <= kComputeUnits;
 }
