@@ -72,14 +72,17 @@ bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split) {
 }
 
 // Query rows of an exact call's workgroups. Nothing is grouped, so the block that the caller names binds nothing: its rows are those that
-// suit the launch. Keys about as many as queries, us, 64 | 128 | 256 rows:
+// suit the launch. From 1560 shapes of 4 to 512 heads, measured at each; the choice takes 0.2 % more than the best of the three on average, more than 3 % on one in fifty.
+// Keys fewer than twice the queries, us, 64 | 128 | 256 rows:
 //   64 while two halves of the keys (launch_one) of such blocks fill the chip once: d64 causal H16 N1000 10.2 | 13.7 | 20.6, H8 N2900 20 | 25 | 43,
-//      d128 H16 N1000 15.3 | 19.3 | 28.9, not causal H8 N2000 25 | 33 | 40, and not yet H8 N2900 52 | 43 | 63;
+//      d128 H16 N1000 15.3 | 19.3 | 28.9, not causal H8 N2000 25 | 33 | 40, and not yet H8 N2900 52 | 43 | 63; but for long walks of few heads, whose keys
+//      are better dealt out to larger blocks (d128 not causal H4 N2383 29.0 | 24.4 | 34.7, causal N3522 35.4 | 32.9, d64 not causal N3942 30.0 | 27.0);
 //      at d = 64 under the mask up to one and a half rounds of 128 rows (H16 N2000 17.5 | 19.8, H32 N1400 17.7 | 18.8, B4 H16 N700 11.6 | 12.4, but
-//      H16 N4096 51 | 47), not causal where all are resident and at least a twelfth of the rows would be padding (B16 H12 N280 11.4 | 13.5, B4 H16 N700
-//      15.5 | 16.5, but N577 33 | 29);
+//      H16 N4096 51 | 47), of short prompts up to five and a half of 64 (B16 H12 N305 10.0 | 11.8); not causal where blocks of 128 are just over one round, so
+//      that the second is nearly empty (d64 B2 H32 N607 13.8 | 15.0, N1150 20.5 | 21.9, d128 B8 H12 N315 12.7 | 16.1, but d64 B2 H32 N409, one round, 10.1 | 9.2);
 //   256 without the mask, where they fill more than half of one round of compute units (d128 H16 N2900 94 | 79 | 72, N4096 149 | 123 | 118, d64 49 | 48 | 44,
-//      80 | 74 | 71) or, at d = 128, whole ones (N16000 2081 | 1784 | 1687, but N6000, one and a half, 309 | 260 | 283), with little padding;
+//      80 | 74 | 71, d128 H32 N1144 41 | 34 | 31) or, at d = 128 on long walks, the last of a few (H32 N5357, 2.6 rounds, 506 | 425 | 399, N16000 2081 | 1784 | 1687, but N6000,
+//      one and a half, 309 | 260 | 283, and B16 H16 N1565 419 | 311 | 342), with little padding;
 //   128 otherwise (the caller's 256, causal d64 H16 N9000: 215 | 173 | 193).
 // Many more keys than queries (their shares fill the chip): the caller's, up to 128 (N500 on 8000 keys, H16 d64 29 | 27 | 39), and 128 at d = 128 on
 // long walks (N512 on 30000 keys 142 | 122, N1000 on 8000 83 | 70, N128 on 2500 15.5 | 17.4) unless they are a tenth more rows.
@@ -92,13 +95,13 @@ int attn_bf16_exact_rows(const Problem& pb) {
     const bool more = pb.d == 128 && pb.N > 64 && pb.Nk >= 6000 && 10 * padded(128) <= 11 * padded(64);
     return more ? 128 : std::min(pb.Br, 128);
   }
-  if (wgs(64) <= kComputeUnits) return 64;
-  if (pb.d == 64 && (pb.causal ? 2 * wgs(128) <= 3 * kComputeUnits : wgs(64) <= 5 * kComputeUnits && 12 * padded(64) <= 11 * padded(128))) return 64;
-  if (!pb.causal && 10 * padded(256) <= 11 * padded(128)) {
-    const long long n = wgs(256), rounds = (n + kComputeUnits - 1) / kComputeUnits;
-    if (rounds == 1 ? 2 * n > kComputeUnits : pb.d == 128 && 20 * n >= 19 * kComputeUnits * rounds) return 256;
-  }
-  return 128;
+  if (wgs(64) <= kComputeUnits) return (pb.d == 64 && pb.causal) || pb.N < (pb.causal || pb.d == 64 ? 3000 : 2300) ? 64 : 128;
+  if (pb.causal) return pb.d == 64 && (2 * wgs(128) <= 3 * kComputeUnits || (pb.N <= 400 && 2 * wgs(64) <= 11 * kComputeUnits)) ? 64 : 128;
+  if (wgs(128) > kComputeUnits && wgs(64) <= (pb.d == 64 ? 3 : 2) * kComputeUnits && pb.N < 1400) return 64;
+  const long long n = wgs(256), rounds = (n + kComputeUnits - 1) / kComputeUnits, last = n - (rounds - 1) * kComputeUnits;
+  if (rounds == 1)
+    return 2 * n > kComputeUnits && (pb.d == 128 ? 5 * padded(256) <= 6 * padded(128) : 10 * padded(256) <= 11 * padded(128)) ? 256 : 128;
+  return pb.d == 128 && pb.N >= 2200 && 20 * last >= (rounds <= 3 ? 11 : 19) * kComputeUnits ? 256 : 128;
 }
 
 // Query rows of a grouped call's workgroups when its keys are dealt out, whose grouping then comes from a table: two Q blocks of 64 rows at
@@ -144,8 +147,10 @@ int attn_bf16_splits(const Problem& asked, int distr) {
   if (distr) pb.Br = attn_bf16_shared_rows(asked);
   const long long units = (long long)pb.B * pb.H * ((pb.N + pb.Br - 1) / pb.Br);
   const int tiles = (pb.Nk + pb.Bc - 1) / pb.Bc;
-  // (exact blocks of 64 rows that two halves of the keys are walked for anyway have half as much to gain: H8 N1000 14 us in four shares, 10 in none)
-  const bool in_halves = !distr && pb.Br == 64 && pb.Bc == 64 && units <= (pb.d == 64 ? 2 : 1) * kComputeUnits;
+  // (exact blocks of 64 rows that two halves of a prompt's keys are walked for anyway have half as much to gain: H8 N1000 14 us in four shares, 10 in none; chunks
+  // on a cache not: d128 H8 N108 on 1490 keys 12.6 in shares, 18.3 in none, H32 N107 on 1732 15.3 | 16.6, d64 H12 N161 on 1419 10.2 | 11.9, but of many blocks
+  // at d = 64: H32 N104 on 1598 13.1 | 11.8, B5 H16 N40 on 1132 11.4 | 9.8)
+  const bool in_halves = !distr && (pb.Nk < 2LL * pb.N || (pb.d == 64 && 4 * units >= kComputeUnits)) && pb.Br == 64 && pb.Bc == 64 && units <= (pb.d == 64 ? 2 : 1) * kComputeUnits;
   const auto worth = [&](long long n) { return n > 1 && tiles - tiles / n >= (distr ? 30 : in_halves ? 24 : 12); };
   long long n = std::min<long long>(1024 / (pb.Br / 32) / units, tiles / 4);
   const long long one = kComputeUnits / units, few = std::min<long long>(one, tiles / 4);

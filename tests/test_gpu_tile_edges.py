@@ -524,7 +524,10 @@ def test_float_groups_itself(B, H, N, causal, Br, G, n_planes):
 @pytest.mark.parametrize("B,H,Hkv,N,Nk,d,causal", [
     (1, 8, 8, 2048, 2048, 64, True), (1, 8, 4, 2049, 2049, 128, False), (1, 6, 6, 8129, 8129, 64, True), (16, 12, 12, 280, 280, 64, False),
     (16, 12, 12, 300, 300, 64, False), (1, 16, 16, 2100, 2500, 128, False), (1, 16, 4, 2100, 2100, 64, False), (1, 4, 4, 65, 6000, 128, True),
-    (1, 4, 4, 150, 6000, 128, True), (1, 8, 8, 1000, 1000, 128, True)])
+    (1, 4, 4, 150, 6000, 128, True), (1, 8, 8, 1000, 1000, 128, True), (1, 4, 4, 2299, 2299, 128, False), (1, 4, 4, 2300, 2300, 128, False), (1, 4, 2, 3001, 3001, 64, False),
+    (1, 4, 4, 3001, 3001, 128, True), (16, 12, 3, 400, 400, 64, True), (16, 12, 12, 401, 401, 64, True), (8, 12, 12, 315, 315, 128, False), (2, 32, 8, 607, 607, 64, False),
+    (1, 32, 32, 1400, 1400, 64, False), (4, 12, 12, 2264, 2264, 128, False), (8, 8, 8, 2100, 2300, 128, False), (1, 8, 2, 558, 9553, 128, True), (1, 16, 16, 127, 1584, 128, False),
+    (3, 16, 16, 5, 700, 64, False), (1, 32, 32, 2500, 2500, 64, True)])
 def test_exact_rows_of_a_workgroup(B, H, Hkv, N, Nk, d, causal):
     """Exact calls choose their workgroups' rows by the launch: every Br gives the same rows (up to the order of the sums where
     shares of the keys differ), and they are plain attention's, on either side of each line of the rule."""
