@@ -157,7 +157,7 @@ __device__ __forceinline__ void lsh_block(const T* __restrict__ block, int rows,
           if (r0 == 0) {
             for (int i = tid; i < min(rows, BR) * PL; i += THREADS) {
               const int p = p0 + (i & (PL - 1)), r = i / PL;
-              R[PL == 16 ? i : r * 16 + p] = p < n_planes ? hyperplane_entry(seed, (uint32_t)p, (uint32_t)r) : 0.0f;
+              R[PL == 16 ? i : r * 16 + (i & (PL - 1))] = p < n_planes ? hyperplane_entry(seed, (uint32_t)p, (uint32_t)r) : 0.0f;
             }
             if (p0 == 0 && tid < D) lds.code[tid] = 0;
           }
@@ -184,7 +184,7 @@ __device__ __forceinline__ void lsh_block(const T* __restrict__ block, int rows,
         if (bits) atomicOr(&lds.code[c], bits);
       };
       // (four projections at a workgroup of four threads a channel: tiny calls, whose workgroups all wait for this; H1 N256 11.3 | 10.6 us)
-      if (KEEP && NPG == 4 && n_planes <= 4) project(std::integral_constant<int, KEEP ? 1 : 16 / NPG>());
+      if (KEEP && NPG == 4 && n_planes - p0 <= 4) project(std::integral_constant<int, KEEP ? 1 : 16 / NPG>());
       else project(std::integral_constant<int, 16 / NPG>());
     }
   }
