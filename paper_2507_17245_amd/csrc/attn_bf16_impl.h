@@ -190,7 +190,19 @@ struct RowSum {
   }
 };
 
-template <int D, int BR, int BC, int KRED, int MODE, int NG, int KS>
+// Sums of P on the matrix pipe (RowSum) where they take no registers that the wave has not got: fused kernels hold ten more
+// than with dot products, which costs a wave per SIMD or spills, and at d = 128 (blocks of 128 rows, one long wave) what the clock falls by. us, dot products | this:
+//   exact and Q~ K^T, d64 Br256 N3000 46.0 | 45.1, Q~ K^T 42.5 | 41.4, Br64 N200 on 30000 keys 43.0 | 42.6, Br128 45.4 | 44.8;
+//   exact d64 Br128 in halves N300 on 16000 keys 33.6 | 32.8, N200 on 30000 40.6 | 40.2; Q~ K^T d64 Br128 H32 N1000 18.5 | 18.5, B2 H32 N530 on 4000 58.8 | 58.5;
+//   d128 H16 N8192 causal 266 | 262, Br256 N3000 77.1 | 71.0; fused d64 N16384 490 | 502; d128 N32768 3182 | 3240, but Br256 N3000 88.6 | 82.5.
+// One wave per SIMD waits for its sums itself: not at d = 64 with tiles of 128 keys and 64 rows (exact N2034 on 4337 keys 49.8 | 51.4), and by the launch (launch_ks)
+// at d = 128 with 64 rows and in exact blocks of 128 at d = 64.
+template <int D, int BR, int BC, int MODE, int NG, int KS>
+constexpr bool kMatrixSum = MODE == kFused ? D == 128 && BR == 256 && BC == 64 && NG >= 16
+                            : D == 64      ? BR != 64 || BC != 128
+                                           : BC != 128;
+
+template <int D, int BR, int BC, int KRED, int MODE, int NG, int KS, bool MATRIX_SUM>
 __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::WAVES_PER_SIMD)) void attn_bf16_kernel(
     const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
     bf16* __restrict__ o, const uint8_t* __restrict__ perm, const f16* __restrict__ kt, int Npad,
@@ -199,13 +211,6 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
     uint8_t* __restrict__ perm_w, int n_groups, int Br_log2, int table_in_o, int n_split, float* __restrict__ part_o, f32x2* __restrict__ part_stat) {
   using C = Cfg<D, BR, BC, KRED, MODE, NG, KS>;
   constexpr bool FUSED = C::FUSED, GROUPED = C::GROUPED;
-  // Sums of P on the matrix pipe (RowSum) where they take no registers that the wave has not got: fused kernels hold ten more
-  // than with dot products, which costs a wave per SIMD or spills, and at d = 128 (blocks of 128 rows, one long wave) what the clock falls by. us, dot products | this:
-  //   exact and Q~ K^T, d64 Br256 N3000 46.0 | 45.1, Q~ K^T 42.5 | 41.4, Br64 N200 on 30000 keys 43.0 | 42.6, Br128 45.4 | 44.8;
-  //   exact d64 Br128, keys together, H32 N2048 causal 25.3 | 25.9, H16 N4096 44.0 | 44.5, H32 Hkv8 N4096 81.9 | 81.9 (not taken for B4 H32 N2500 132.9 | 130.7),
-  //   in halves N300 on 16000 keys 33.6 | 32.8, N200 on 30000 40.6 | 40.2; Q~ K^T d64 Br128 H32 N1000 18.5 | 18.5, B2 H32 N530 on 4000 58.8 | 58.5;
-  //   d128 H16 N8192 causal 266 | 262, Br256 N3000 77.1 | 71.0; fused d64 N16384 490 | 502; d128 N32768 3182 | 3240, but Br256 N3000 88.6 | 82.5
-  constexpr bool MATRIX_SUM = FUSED ? D == 128 && BR == 256 && BC == 64 && NG >= 16 : D == 64 ? BR != 128 || KS == 2 || MODE != kExact : BC != 128;
   constexpr float kSumTrigger = (BC / 2) * 256.0f;   // BC/2 keys per lane and tile, each at most 2^kTau
   // A row whose first tile holds only scores of -infinity (masked keys; those of a share or half that the causal mask hides)
   // takes its first score above that as its reference: against 0, scores of -150 and less would be lost. The fused product has no such
@@ -972,9 +977,10 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   }
 
   // A wave without rows (of a head's last block) brings its part of the tiles in and takes no products: what its SIMD and the power
-  // allow is the other waves' (200 rows on 32768 keys, H16 d128 86.0 -> 82.2 us, H32 N300 on 16000 130 -> 122, d64 H16 47.1 -> 44.9). Tiles
-  // of 64 keys: with 128 at d = 128 the addresses that this loop keeps double what blocks of 256 rows spill (35 registers -> 77).
-  if (MODE != kFused && BC == 64 && qw0 >= N) {
+  // allow is the other waves' (200 rows on 32768 keys, H16 d128 86.0 -> 82.2 us, H32 N300 on 16000 130 -> 122, d64 H16 47.1 -> 44.9; tiles of 128 keys, Br256
+  // d64 B2 H32 N2122 59.2 -> 56.4). Not in exact blocks of 256 rows with tiles of 128 keys at d = 128, where the addresses that this loop keeps double what the other
+  // waves spill (35 registers -> 77; H16 N3072 not causal 140 -> 187, for B2 H8 N420 28.1 -> 24.0).
+  if (MODE != kFused && !(MODE == kExact && D == 128 && BR == 256 && BC == 128) && qw0 >= N) {
     __syncthreads();
     for (int it = 0; it < n_tiles - 1; ++it) {
       feed(it, it & 1);
@@ -1006,8 +1012,9 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   // two score register sets swap roles without copies.
   int it = 0;
   // (at d = 128 blocks of 64 rows run one wave per SIMD, which waits for its instructions itself: by where the loop lies in the 64-byte lines
-  // H8 N4000 Nk5000 took 91 to 103 us; exact d64 Br128 H32 N2048 26.95 | 26.80, H16 N4096 46.16 | 46.04)
-  if constexpr ((D == 128 && BR == 64 && KS == 1) || (D == 64 && BR == 128 && KS == 1 && MODE == kExact)) asm volatile(".p2align 6");
+  // H8 N4000 Nk5000 took 91 to 103 us; exact d64 Br128 H32 N2048 26.95 | 26.80, H16 N4096 46.16 | 46.04; fused d64 Br256 with tiles of 32 keys H12 N5276
+  // 117.9 | 115.6)
+  if constexpr ((FUSED && D == 64 && BR == 256 && BC == 32) || (D == 128 && BR == 64 && KS == 1) || (D == 64 && BR == 128 && KS == 1 && MODE == kExact)) asm volatile(".p2align 6");
   for (; it + 2 < n_full; it += 2) {
     body(no, yes, it, 0, s0, s1);
     body(no, yes, it + 1, 1, s1, s0);
@@ -1097,8 +1104,8 @@ __global__ __launch_bounds__(BR * 2 * KS, (Cfg<D, BR, BC, KRED, MODE, NG, KS>::W
   }
 }
 
-template <int D, int BR, int BC, int KRED, int MODE, int NG, int KS>
-hipError_t launch_ks(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
+template <int D, int BR, int BC, int KRED, int MODE, int NG, int KS, bool MATRIX_SUM>
+hipError_t launch_sum(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
                       const void* kt, const Problem& pb, hipStream_t stream) {
   const int Tq = (pb.N + BR - 1) / BR;
   const long long units = (long long)pb.B * pb.H * Tq;
@@ -1114,13 +1121,34 @@ hipError_t launch_ks(const void* q, const void* k, const void* v, void* o, const
   //   d128  H32 N2048 47.9 | 44.4, 53.3 | 50.6; H16 N4096 82.3 | 75.9, 88.7 | 82.3; H16 N8192 264 | 253, 253 | 242
   const bool paired = BR <= 128 && (MODE != kFused || D == 128 || units <= 3 * kComputeUnits);
   const int causal_mode = pb.causal ? (units <= 8 * kComputeUnits ? (paired ? 3 : 2) : 1) : 0;
-  hipLaunchKernelGGL((attn_bf16_kernel<D, BR, BC, KRED, MODE, NG, KS>), dim3((unsigned)(units * pb.n_split)), dim3(BR * 2 * KS), 0,
+  hipLaunchKernelGGL((attn_bf16_kernel<D, BR, BC, KRED, MODE, NG, KS, MATRIX_SUM>), dim3((unsigned)(units * pb.n_split)), dim3(BR * 2 * KS), 0,
                      stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, perm, (const f16*)kt,
                      (pb.Nk + kKtPad - 1) / kKtPad * kKtPad, pb.H, pb.Hkv, pb.N, pb.Nk, Tq, causal_mode,
                      scale_log2e, (int)units, pb.n_planes, pb.gray_mode, pb.seed, pb.lse,
                      kt ? (const char*)kt + kt_copy_bytes(pb.B, pb.Hkv, pb.d, pb.Nk) : nullptr,
                      MODE != kExact ? pb.perm_w : nullptr, pb.n_groups, __builtin_ctz(pb.Br), pb.table_in_o, pb.n_split, pb.part_o, (f32x2*)pb.part_stat);
   return hipGetLastError();
+}
+
+template <int D, int BR, int BC, int KRED, int MODE, int NG, int KS>
+hipError_t launch_ks(const void* q, const void* k, const void* v, void* o, const uint8_t* perm,
+                     const void* kt, const Problem& pb, hipStream_t stream) {
+  constexpr bool kSum = kMatrixSum<D, BR, BC, MODE, NG, KS>;
+  // Blocks of 64 rows at d = 128 (one wave per SIMD) take their row sums by dot products on long walks that keep the whole chip busy: 24 tiles and
+  // more, but for the prompts of a causal call, whose blocks differ in length. us, dot products | matrix pipe: H16 Hkv4 N563 on 15710 keys 95.5 |
+  // 103.9, H32 N922 on 8710 148.9 | 156.6, H16 N318 on 13807 57.2 | 59.7, H8 N4000 not causal 77.3 | 84.0, H12 N1847 41.3 | 43.1, H16 N189 on 17275 48.5 | 49.5; but
+  // causal H16 N1500 33.5 | 32.6, N3000 59.0 | 57.0, H8 N4000 on 5000 81.7 | 80.0, exact H16 N1000 15.6 | 14.9, N150 on 3000 (5 tiles) 18.4 | 17.4, N944 on 2865 (22) 32.3 | 30.5.
+  // Exact blocks of 128 rows at d = 64 that walk all keys: by dot products under the mask while blocks go longest first over all heads, where the last of them leave a
+  // wave to a SIMD (H32 N2048 25.3 | 25.9, H16 N4096 44.0 | 44.5, H32 Hkv8 N4096 81.9 | 81.9; but B4 H32 N2500 132.9 | 130.7, not causal 206.5 | 203.6, B16 H12 N412 19.0 | 18.3).
+  if constexpr (D == 128 && BR == 64 && BC == 64 && kSum) {
+    if (!(pb.causal && pb.Nk < 2LL * pb.N) && (pb.Nk + BC - 1) / BC / pb.n_split / KS >= 24)
+      return launch_sum<D, BR, BC, KRED, MODE, NG, KS, false>(q, k, v, o, perm, kt, pb, stream);
+  }
+  if constexpr (D == 64 && BR == 128 && MODE == kExact && KS == 1) {
+    if (pb.causal && (long long)pb.B * pb.H * ((pb.N + BR - 1) / BR) <= 8 * kComputeUnits)
+      return launch_sum<D, BR, BC, KRED, MODE, NG, KS, false>(q, k, v, o, perm, kt, pb, stream);
+  }
+  return launch_sum<D, BR, BC, KRED, MODE, NG, KS, kSum>(q, k, v, o, perm, kt, pb, stream);
 }
 
 template <int D, int BR, int BC, int KRED, int MODE, int NG = KRED>

@@ -666,3 +666,10 @@ def test_parts_of_a_block_wherever_called(base, H, N, Br, causal):
         torch.cuda.synchronize()
         graph.replay()
         check(o, f"replay {rep}")
+
+
+@pytest.mark.parametrize("H,Hkv,N,Nk,causal", [(2, 2, 130, 1535, False), (2, 2, 130, 1601, False), (16, 16, 1030, 1600, True), (16, 16, 1030, 2100, True), (9, 3, 2000, 2000, False)])
+def test_row_sums_either_way(H, Hkv, N, Nk, causal):
+    """Grouped blocks of 64 rows at d = 128 take the row sums of P by dot products or on the matrix pipe by the length of the walk and the mask: on
+    either side of the rule's lines, whole and in halves, the output is the method's."""
+    _forward(W.CONFIGS["long"].scaled(B=1, H=H, Hkv=Hkv, N=N, Nk=Nk, Br=64, causal=causal, recipe="normal"), True)
