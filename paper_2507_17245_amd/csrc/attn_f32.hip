@@ -138,7 +138,7 @@ __global__ __launch_bounds__(NW * 64, (D == 64 && !(OWN && NW == 4) ? 2 : 1)) vo
     for (int u = 0; u < QU; ++u) *(f32x4*)&q_lds[(u * T + tid) / (D / 4) * RS + (u * T + tid) % (D / 4) * 4] = Quad<E>::values(x[u]);
     if (PIECES && tid <= kTile) mark_lds[tid] = 0;
   }
-  if (V_AHEAD && !OWN && tile < n_tiles) load_v(tile);   // (in front of Q it would be waited for with it: H1 N47 d128 9.2 | 9.5 us)
+  if (V_AHEAD && !OWN && tile < n_tiles) load_v(tile);   // (in front of Q it would be waited for with it: d128 H8 N600 causal 33.6 -> 34.6 us)
   if constexpr (OWN) {
     const int t_block = r0 / Br;
     lsh_block<float, D, kOwnRows, T, true>((const float*)q + ((size_t)bh * N + (size_t)t_block * Br) * D, min(Br, N - t_block * Br), n_planes,

@@ -243,8 +243,8 @@ bool attn_bf16_supported(const Problem& pb, int distr);
 bool attn_bf16_replicated(const Problem& pb, bool have_kt, int n_split);
 bool attn_bf16_light(const Problem& pb);   // Q~ K^T is good enough to run where there is no room for the transposed copy
 int attn_bf16_splits(const Problem& pb, int distr);
-int attn_bf16_grouped_rows(const Problem& pb);   // the same when they stay together, fewer than a Q block's (0: a Q block's)
 int attn_bf16_shared_rows(const Problem& pb);   // query rows of a grouped call's workgroups when its keys are dealt out
+int attn_bf16_grouped_rows(const Problem& pb);  // the same when they stay together, fewer than a Q block's (0: a Q block's)
 int attn_bf16_exact_rows(const Problem& pb);   // query rows of an exact call's workgroups, in the place of Br
 // Few query rows against many keys (decoding): a kernel of its own, with its own number of shares.
 bool attn_bf16_few_rows(const Problem& pb, int distr);
